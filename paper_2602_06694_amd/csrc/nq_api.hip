@@ -340,6 +340,15 @@ extern "C" int nq_get_option(const char* name, int* value)
 // ---------------------------------------------------------------------------------------------
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+// Tokens of one pass of the paths that take any batch in passes: a workspace of about 8 MiB per layer, at least 64 and at
+// most 512 tokens, whole groups of 16.  (A pass is four dependent launches of 4 to 10 us, so the more tokens the better; a model
+// whose layers all take this path holds one such workspace per layer.)
+static int pass_tokens(size_t bytes_per_token)
+{
+    const size_t fit = ((size_t)8 << 20) / std::max<size_t>(1, bytes_per_token) / 16 * 16;
+    return (int)std::max<size_t>(64, std::min<size_t>(512, fit));
+}
+
 static void free_handle(nq_handle h)
 {
     if (!h) return;
@@ -1118,32 +1127,35 @@ static int transposed_forward(const char* who, nq_handle h, const void* g, float
     const size_t gs = dtype_size(h->y_dtype);
     int rc = check_xy(who, g, w, (size_t)batch * h->d_out * gs, (size_t)batch * h->d_in * sizeof(float));
     if (rc != NQ_OK) return rc;
-    // workspace for passes of up to 8 tokens: the intermediate u = s_mid (.) U^T (s_out (.) g) [8][r padded], then the
-    // partial sums of the larger of the two products
-    const int nb_max = NQ_DECODE_MAX_BATCH;
+    // Workspace of one pass: the intermediate u = s_mid (.) U^T (s_out (.) g) [tokens][r padded], then the fixed-point input of the
+    // larger of the two products.  The first call allocates it, for its own batch (at least 64 tokens) up to one pass, and it
+    // stays at that: a later, larger batch takes more passes.
     const size_t r_pad = (size_t)n_steps(h->r) * kTileCols;
-    const size_t u_bytes = align_up(nb_max * r_pad * sizeof(float), 256);
-    const size_t need = u_bytes + std::max(gemv_t_partial_bytes(h->d_out, h->r, nb_max), gemv_t_partial_bytes(h->r, h->d_in, nb_max));
-    if (h->tp_bytes < need) {
+    auto pass_bytes = [&](int nb, size_t* u_bytes) {
+        *u_bytes = align_up((size_t)nb * r_pad * sizeof(float), 256);
+        return *u_bytes + std::max(gemm_t_scratch_bytes(h->d_out, nb), gemm_t_scratch_bytes(h->r, nb));
+    };
+    size_t u_bytes = 0;
+    if (!h->tp_alloc) {
+        const int tokens = std::min(pass_tokens(pass_bytes(16, &u_bytes) / 16), std::max(64, (int)round_up(batch, 16)));
         NQ_HIP(hipDeviceSynchronize());
-        if (h->tp_alloc) NQ_HIP(hipFree(h->tp_alloc));
-        h->tp_alloc = nullptr;
-        h->tp_bytes = 0;
-        NQ_HIP(hipMalloc(&h->tp_alloc, need));
-        h->tp_bytes = need;
+        NQ_HIP(hipMalloc(&h->tp_alloc, pass_bytes(tokens, &u_bytes)));
+        h->tp_tokens = tokens;
     }
+    const int nb_max = h->tp_tokens;
+    (void)pass_bytes(nb_max, &u_bytes);
     float* u = (float*)h->tp_alloc;
-    double* partial = (double*)((char*)h->tp_alloc + u_bytes);
+    void* scratch = (char*)h->tp_alloc + u_bytes;
     hipStream_t s = (hipStream_t)stream;
     for (int b0 = 0; b0 < batch; b0 += nb_max) {
         const int nb = std::min(nb_max, batch - b0);
         // u = s_mid (.) U^T (s_out (.) g): the tiles of U ([d_out][r]) read along their columns
-        rc = launch_gemv_t(h->u_tiles, h->d_out, h->r, (const char*)g + (size_t)b0 * h->d_out * gs, h->y_dtype, (int)h->d_out, h->s_out,
-                           h->s_mid, u, NQ_F32, (int)r_pad, nb, partial, s);
+        rc = launch_gemm_t(h->u_tiles, h->d_out, h->r, (const char*)g + (size_t)b0 * h->d_out * gs, h->y_dtype, (int)h->d_out, h->s_out,
+                           h->s_mid, u, (int)r_pad, nb, scratch, s);
         if (rc != NQ_OK) return rc;
         // w = V u: the tiles of V^T ([r][d_in]) read along their columns
-        rc = launch_gemv_t(h->vt_tiles, h->r, h->d_in, u, NQ_F32, (int)r_pad, nullptr, with_s_in ? h->s_in : nullptr,
-                           w + (size_t)b0 * h->d_in, NQ_F32, (int)h->d_in, nb, partial, s);
+        rc = launch_gemm_t(h->vt_tiles, h->r, h->d_in, u, NQ_F32, (int)r_pad, nullptr, with_s_in ? h->s_in : nullptr,
+                           w + (size_t)b0 * h->d_in, (int)h->d_in, nb, scratch, s);
         if (rc != NQ_OK) return rc;
     }
     return NQ_OK;

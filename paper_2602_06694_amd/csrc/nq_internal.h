@@ -231,7 +231,7 @@ struct nq_binlr_s {
     int pf_batch;
     // workspace of the transposed products (allocated by their first call)
     void* tp_alloc;
-    size_t tp_bytes;
+    int tp_tokens;        // tokens one pass may hold
 };
 
 
@@ -288,9 +288,9 @@ int schedule_full_rowblocks();
 int shared_min_batch();          // smallest batch that takes the shared-input kernel in launches that fill the chip            // row blocks from which a launch counts as filling the chip
 
 // ---- launchers (nq_transposed.hip) -----------------------------------------------------------
-size_t gemv_t_partial_bytes(int64_t M, int64_t N, int batch);
-int launch_gemv_t(const uint32_t* tiles, int64_t M, int64_t N, const void* in, int in_dtype, int in_stride, const uint16_t* in_scale,
-                  const uint16_t* out_scale, void* out, int out_dtype, int out_stride, int batch, double* partial, hipStream_t s);
+size_t gemm_t_scratch_bytes(int64_t M, int batch);
+int launch_gemm_t(const uint32_t* tiles, int64_t M, int64_t N, const void* in, int in_dtype, int in_stride, const uint16_t* in_scale,
+                  const uint16_t* out_scale, float* out, int out_stride, int batch, void* scratch, hipStream_t s);
 
 // ---- launchers (nq_exec.hip) ---------------------------------------------------------------
 bool small_layer_fits(nq_handle h, int batch);

@@ -1,104 +1,310 @@
 // Products with the TRANSPOSED sign matrices from the resident tiles of a layer (the training-time siblings of the
-// forward: Section 3.4 and Algorithm 1, Phase 3 need  V (U^T (s_out (.) g))  for the gradient of the input scales).
-// No second copy of the bits is made.  Inside a 128 x 64 tile a lane owns 16 columns and, of each, the 8 rows
-// 16 p + (lane & 15): a column's rows are spread over 16 lanes, which no matrix instruction reduces over, so this path
-// adds on the vector ALU in binary64 (exact sign products, one rounding when the result is stored).
+// forward: Section 3.4 and Algorithm 1, Phase 3 need  V (U^T (s_out (.) g))  for the gradient of the input scales and of
+// the input).  No second copy of the bits is made: a wave turns each 1 KiB tile round in registers and feeds it to the
+// int8 matrix cores, against activations held as exact fixed point.
+//
+// Turning a tile round.  In the forward layout (nq_internal.h) lane (g, j) of a tile holds, in byte b of word v, bit p, the
+// sign of row 16p + j, column 16g + 4v + b.  The transposed product reduces over ROWS, so a matrix-instruction operand needs a
+// column per lane (its low four lane bits) and rows along the bytes.  The tile is loaded with its lanes renamed -- physical
+// lane bits 0-1 = j bits 0-1, bits 2-3 = g, bits 4-5 = j bits 2-3: free, the address of a lane's 16 bytes is arbitrary --
+// and then only a 4 x 4 byte transposition inside each quad of lanes is missing (two exchange steps of one DPP move and one
+// byte permute per word).  After it, lane bits 0-3 are a column, lane bits 4-5 and the byte are row bits, and the eight bits of
+// a byte are the row's remaining three: operand register i of half h is (word_v >> (4h + i)) & 0x01010101, for the columns
+// 16g + 4v + b of word v.  That is 80 vector instructions per tile beside 32 matrix instructions of 16 cycles for 16 tokens.
+//
+// Fixed point with four byte slices (|q| <= 2^30 of the token's maximum), exact int32 sums, joined and scaled in binary64,
+// one rounding to fp32 when a result is stored: the error against binary64 stays that of the one rounding (3.6e-8 of the
+// result's norm on normal data, as with binary64 additions on the vector ALU, which this replaces: a gradient pass of 64
+// tokens through a 4096 x 4096 r = 1024 layer took 235 us in passes of 8 tokens, 16 launches of 2 to 12 us).
 #include "nq_internal.h"
 #include "nq_device.h"
 
 namespace nq {
 
-constexpr int kTWaves = 4;
+constexpr int kTSlices = 4;
+constexpr int kTWaves = 8;              // waves of a workgroup share one (64 columns, 16 tokens) result: they split its row blocks
+constexpr int kTTokens = 16;            // tokens of a workgroup: the 16 columns of one matrix instruction, one slice at a time
+constexpr uint32_t kTRbBytes = 2 * kTSlices * 64;       // a token's fixed-point bytes per 128-row block: [half][slice][4 pieces][16]
 
-// partial[(sp * batch + tok) * n_pad + col] = sum over the row blocks rb = 4 sp + wave (mod 4 n_split) of
-//     sum_row sign(row, col) * in_scale[row] * in[tok][row]
-__global__ __launch_bounds__(64 * kTWaves) void gemv_t_kernel(const uint32_t* __restrict__ tiles, int nsteps, int n_rb, int M,
-                                                              const void* __restrict__ in, int in_dtype, int in_stride,
-                                                              const uint16_t* __restrict__ in_scale, double* __restrict__ partial,
-                                                              int n_split, int batch)
+// ---------------------------------------------------------------------------------------------
+// scaled input -> fixed point.  One workgroup per token.  A thread owns pieces: piece (s, c) of a token holds, as four words
+// i of four bytes, rows 64 s + 16 i + 4 c + (0..3) -- the order in which the turned-round tile meets its rows.
+// ---------------------------------------------------------------------------------------------
+struct TQuantArgs {
+    const void* in;             // [batch][in_stride] of in_dtype
+    const uint16_t* scale;      // fp16 [M] or nullptr
+    uint8_t* bq;                // [batch][n_pieces / 4][slices][4][16]
+    QMeta* meta;                // [batch]
+    int M, in_dtype, in_stride;
+    int n_pieces;               // 4 per 64 rows, whole row blocks
+};
+
+// the 16 scaled values of piece `pc`; binary64: an fp32 value times an fp16 scale is exact
+__device__ __forceinline__ void tq_load(const TQuantArgs& a, size_t base, int pc, bool vec, double v[16])
 {
-    __shared__ double red[kTWaves][kTileCols];
-    const int st = blockIdx.x, sp = blockIdx.y, tok = blockIdx.z;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int ri = lane & 15, cg = lane >> 4;
-    double acc[16];
+    const int r0 = (pc >> 2) * 64 + 4 * (pc & 3);
 #pragma unroll
-    for (int j = 0; j < 16; ++j) acc[j] = 0.0;
-    for (int rb = sp * kTWaves + wave; rb < n_rb; rb += kTWaves * n_split) {
-        const v4u wd = *(const v4u*)(tiles + ((size_t)rb * nsteps + st) * kTileWords + 4 * lane);
-        const uint32_t w[4] = {wd.x, wd.y, wd.z, wd.w};
-        double x[8];
+    for (int i = 0; i < 4; ++i) {
+        const int r = r0 + 16 * i;
+        float f[4] = {0.f, 0.f, 0.f, 0.f}, sc[4] = {1.f, 1.f, 1.f, 1.f};
+        if (vec && r + 4 <= a.M) {
+            if (a.in_dtype == NQ_F32) {
+                const v4f t = *(gptr_v4f)((const float*)a.in + base + r);
+                f[0] = t.x; f[1] = t.y; f[2] = t.z; f[3] = t.w;
+            } else {
+                typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+                const v2u t = *(const __attribute__((address_space(1))) v2u*)((const uint16_t*)a.in + base + r);
+                const uint16_t h[4] = {(uint16_t)(t.x & 0xFFFFu), (uint16_t)(t.x >> 16), (uint16_t)(t.y & 0xFFFFu), (uint16_t)(t.y >> 16)};
 #pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            const int row = rb * kTileRows + 16 * p + ri;
-            double v = 0.0;                                        // rows beyond M hold 0 bits and contribute nothing
-            if (row < M) {
-                v = (double)load_as_float(in, in_dtype, (size_t)tok * in_stride + row);
-                if (in_scale) v *= (double)half_bits_to_float(in_scale[row]);
+                for (int k = 0; k < 4; ++k) f[k] = a.in_dtype == NQ_F16 ? half_bits_to_float(h[k]) : bf16_bits_to_float(h[k]);
             }
-            x[p] = v;
+            if (a.scale) {
+                typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+                const v2u t = *(const __attribute__((address_space(1))) v2u*)(a.scale + r);
+                sc[0] = half_bits_to_float((uint16_t)(t.x & 0xFFFFu)); sc[1] = half_bits_to_float((uint16_t)(t.x >> 16));
+                sc[2] = half_bits_to_float((uint16_t)(t.y & 0xFFFFu)); sc[3] = half_bits_to_float((uint16_t)(t.y >> 16));
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (r + k < a.M) {                          // rows beyond M are padding: zeros
+                    f[k] = load_as_float(a.in, a.in_dtype, (int64_t)(base + r + k));
+                    if (a.scale) sc[k] = half_bits_to_float(a.scale[r + k]);
+                }
+            }
         }
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-#pragma unroll
-                for (int p = 0; p < 8; ++p) acc[4 * v + b] += ((w[v] >> (8 * b + p)) & 1u) ? x[p] : -x[p];
+        for (int k = 0; k < 4; ++k) v[4 * i + k] = (double)f[k] * (double)sc[k];
     }
-    // the 16 lanes of a column group hold the 16 row offsets of the same columns
+}
+
+// q of 16 values -> the four slices of their piece (slices 64 bytes apart); returns sum q
+__device__ __forceinline__ long long tq_store(const double v[16], double inv_step, bool bad, uint8_t* dst)
+{
+    long long sum = 0;
+    uint32_t w[kTSlices][4];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        double s = acc[j];
+    for (int i = 0; i < 4; ++i) {
+        uint32_t d[kTSlices][4];
 #pragma unroll
-        for (int off = 1; off < 16; off <<= 1) s += __shfl_xor(s, off);
-        if (ri == 0) red[wave][16 * cg + j] = s;
+        for (int k = 0; k < 4; ++k) {
+            int q = bad ? 0 : (int)rint(v[4 * i + k] * inv_step);          // |q| <= 2^30
+            sum += q;
+#pragma unroll
+            for (int s = kTSlices - 1; s >= 0; --s) {                       // slice kTSlices - 1 is the lowest byte
+                d[s][k] = (uint32_t)q;
+                q = (q + 128) >> 8;
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < kTSlices; ++s) w[s][i] = pack_low_bytes(d[s][0], d[s][1], d[s][2], d[s][3]);
     }
+#pragma unroll
+    for (int s = 0; s < kTSlices; ++s) *(uint4*)(dst + s * 64) = make_uint4(w[s][0], w[s][1], w[s][2], w[s][3]);
+    return sum;
+}
+
+constexpr int kTQThreads = 512;
+
+__global__ void __launch_bounds__(kTQThreads) quantize_t_kernel(TQuantArgs a)
+{
+    __shared__ double sm_max[kTQThreads / 64], sm_sum[kTQThreads / 64];
+    __shared__ int sm_bad[kTQThreads / 64];
+    const int tok = blockIdx.x, tid = threadIdx.x, wave = tid >> 6;
+    const size_t base = (size_t)tok * a.in_stride;
+    const bool vec = (a.in_stride & 3) == 0;                // groups of four elements start 8- (16-bit) or 16-byte (fp32) aligned
+    double v[16], m = 0.0;
+    int bad = 0;
+    // (a thread's first piece stays in registers between the two passes; longer vectors re-read the others)
+    for (int pc = tid + ((a.n_pieces - 1 - tid) / kTQThreads) * kTQThreads; pc >= 0; pc -= kTQThreads) {
+        if (pc >= a.n_pieces) break;
+        tq_load(a, base, pc, vec, v);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const double t = fabs(v[i]);
+            if (!(t <= 1.0e300)) bad = 1;                   // NaN or infinity
+            m = fmax(m, t);
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
+    bad = __builtin_amdgcn_ballot_w64(bad != 0) != 0;
+    if ((tid & 63) == 0) { sm_max[wave] = m; sm_bad[wave] = bad; }
     __syncthreads();
-    if (threadIdx.x < kTileCols) {
-        const int c = threadIdx.x;
-        const double s = (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
-        partial[((size_t)sp * batch + tok) * ((size_t)nsteps * kTileCols) + (size_t)st * kTileCols + c] = s;
+    m = sm_max[0];
+    bad = sm_bad[0];
+#pragma unroll
+    for (int w = 1; w < kTQThreads / 64; ++w) { m = fmax(m, sm_max[w]); bad |= sm_bad[w]; }
+    // step = 2^(e - 30) with m = f 2^e, f in [0.5, 1): |q| <= 2^30
+    int e = 0;
+    if (m > 0.0 && !bad) (void)frexp(m, &e);
+    const double step = ldexp(1.0, e - 30), inv_step = ldexp(1.0, 30 - e);
+    double s = 0.0;
+    uint8_t* const dst = a.bq + (size_t)tok * a.n_pieces * (kTSlices * 16);
+    for (int pc = tid; pc < a.n_pieces; pc += kTQThreads) {
+        if (pc != tid) tq_load(a, base, pc, vec, v);
+        s += (double)tq_store(v, inv_step, bad != 0, dst + (size_t)(pc >> 2) * (kTSlices * 64) + (pc & 3) * 16);
+    }
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);        // below 2^46: exact
+    if ((tid & 63) == 0) sm_sum[wave] = s;
+    __syncthreads();
+    if (tid == 0) {
+        double tot = 0.0;
+        for (int w = 0; w < kTQThreads / 64; ++w) tot += sm_sum[w];
+        QMeta mt;
+        mt.two_step = bad ? (double)__builtin_nanf("") : 2.0 * step;
+        mt.neg_qs = -tot * step;
+        a.meta[tok] = mt;
     }
 }
 
-// out[tok][col] = out_scale[col] * sum_sp partial[sp][tok][col]   (splits added in index order)
-__global__ __launch_bounds__(256) void gemv_t_finish_kernel(const double* __restrict__ partial, int n_split, int batch, int n_pad, int N,
-                                                            const uint16_t* __restrict__ out_scale, void* __restrict__ out, int out_dtype,
-                                                            int out_stride)
+// ---------------------------------------------------------------------------------------------
+// out[tok][col] = out_scale[col] * sum_row sign(row, col) v[tok][row], 64 columns x 16 tokens per workgroup
+// grid = (64-column steps, token groups), block = 512
+// ---------------------------------------------------------------------------------------------
+struct TStageArgs {
+    const uint32_t* tiles;
+    const uint8_t* bq;
+    const QMeta* meta;
+    const uint16_t* out_scale;      // fp16 [N] or nullptr
+    float* out;                     // [batch][out_stride]
+    int N, n_steps, n_rb, out_stride, batch;
+};
+
+// rows of four bytes -> columns of four bytes inside each quad of lanes: byte b of lane t becomes byte t of lane b
+__device__ __forceinline__ uint32_t quad_transpose(uint32_t w, uint32_t sel2, uint32_t sel1)
 {
-    const int col = blockIdx.x * 256 + threadIdx.x, tok = blockIdx.y;
-    if (col >= N) return;
-    double s = 0.0;
-    for (int sp = 0; sp < n_split; ++sp) s += partial[((size_t)sp * batch + tok) * n_pad + col];
-    if (out_scale) s *= (double)half_bits_to_float(out_scale[col]);
-    store_out(out, out_dtype, (size_t)tok * out_stride + col, (float)s);
+    const uint32_t a = (uint32_t)__builtin_amdgcn_mov_dpp((int)w, 0x4E, 0xF, 0xF, true);       // quad_perm [2,3,0,1]
+    w = __builtin_amdgcn_perm(a, w, sel2);
+    const uint32_t b = (uint32_t)__builtin_amdgcn_mov_dpp((int)w, 0xB1, 0xF, 0xF, true);       // quad_perm [1,0,3,2]
+    return __builtin_amdgcn_perm(b, w, sel1);
 }
 
-int gemv_t_splits(int64_t M, int64_t N, int batch)
+// Bound: instruction issue and latency, not memory (a tile meets 16 tokens, so 1 KiB costs 512 matrix-core cycles of one
+// SIMD).  Eight waves per workgroup because at the row counts of real layers (8 to 224 row blocks) a result's reduction is the
+// only thing left to spread over the chip once columns and tokens have been.
+__global__ void __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) gemm_t_kernel(TStageArgs a)
 {
-    const int n_rb = (int)n_rowblocks(M), nst = (int)n_steps(N);
-    int want = 512 / (nst * batch > 0 ? nst * batch : 1);
-    const int most = n_rb / kTWaves > 0 ? n_rb / kTWaves : 1;
-    if (want > most) want = most;
-    if (want > 8) want = 8;
-    return want < 1 ? 1 : want;
+    __shared__ v4i red[2][kTWaves][4][64];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int g = lane >> 4, n = lane & 15;
+    const int st = blockIdx.x, t0 = blockIdx.y * kTTokens;
+    const int tok = t0 + n < a.batch ? t0 + n : a.batch - 1;        // a column past the batch repeats the last token and is not stored
+    const int tile_lane = (lane & 3) | ((lane >> 4) & 3) << 2 | ((lane >> 2) & 3) << 4;
+    const uint32_t sel2 = lane & 2 ? 0x03020706u : 0x05040100u, sel1 = lane & 1 ? 0x03070105u : 0x06020400u;
+    const char* w_base = (const char*)(a.tiles + (size_t)st * kTileWords) + 16 * tile_lane;
+    const size_t w_rb = (size_t)a.n_steps * (kTileWords * 4);
+    const char* b_base = (const char*)a.bq + (size_t)tok * a.n_rb * kTRbBytes + 16 * g;
+    v4i acc[4][kTSlices];
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int s = 0; s < kTSlices; ++s) acc[v][s] = v4i{0, 0, 0, 0};
+    // two tiles in flight; past the end the last one is read again and not used
+    const int last = a.n_rb - 1;
+    v4u w[2], b[2][2][kTSlices];
+#define NQ_T_ISSUE(k, rb)                                                                                   \
+    do {                                                                                                    \
+        const int rr = (rb) < last ? (rb) : last;                                                           \
+        w[k] = load_global_v4u(w_base + (size_t)rr * w_rb, 0);                                              \
+        _Pragma("unroll") for (int h = 0; h < 2; ++h)                                                       \
+            _Pragma("unroll") for (int s = 0; s < kTSlices; ++s)                                            \
+                b[k][h][s] = load_global_v4u(b_base + (size_t)rr * kTRbBytes, (uint32_t)((h * kTSlices + s) * 64)); \
+    } while (0)
+#define NQ_T_MAC(k)                                                                                         \
+    do {                                                                                                    \
+        _Pragma("unroll") for (int v = 0; v < 4; ++v) {                                                     \
+            const uint32_t t = quad_transpose(w[k][v], sel2, sel1);                                         \
+            _Pragma("unroll") for (int h = 0; h < 2; ++h) {                                                 \
+                v4u op;                                                                                     \
+                _Pragma("unroll") for (int i = 0; i < 4; ++i) op[i] = (t >> (4 * h + i)) & 0x01010101u;     \
+                _Pragma("unroll") for (int s = 0; s < kTSlices; ++s)                                        \
+                    acc[v][s] = __builtin_amdgcn_mfma_i32_16x16x64_i8((v4i)op, (v4i)b[k][h][s], acc[v][s], 0, 0, 0); \
+            }                                                                                               \
+        }                                                                                                   \
+    } while (0)
+    NQ_T_ISSUE(0, wave);
+    __builtin_amdgcn_sched_barrier(0);
+    NQ_T_ISSUE(1, wave + kTWaves);
+    __builtin_amdgcn_sched_barrier(0);
+    int rb = wave;
+    for (; rb + kTWaves < a.n_rb; rb += 2 * kTWaves) {
+        NQ_T_MAC(0);
+        NQ_T_ISSUE(0, rb + 2 * kTWaves);
+        __builtin_amdgcn_sched_barrier(0);
+        NQ_T_MAC(1);
+        NQ_T_ISSUE(1, rb + 3 * kTWaves);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (rb < a.n_rb) NQ_T_MAC(0);
+#undef NQ_T_ISSUE
+#undef NQ_T_MAC
+
+    // the eight partial sums of every result, two slices per round through 64 KiB of LDS; wave v of the first four takes word v
+    v4i sum[kTSlices];
+#pragma unroll
+    for (int s = 0; s < kTSlices; ++s) sum[s] = v4i{0, 0, 0, 0};
+#pragma unroll
+    for (int round = 0; round < kTSlices / 2; ++round) {
+        if (round) __syncthreads();
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) red[s][wave][v][lane] = acc[v][2 * round + s];
+        __syncthreads();
+        if (wave < 4) {
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int k = 0; k < kTWaves; ++k) sum[2 * round + s] += red[s][k][wave][lane];
+        }
+    }
+    if (wave >= 4 || t0 + n >= a.batch) return;
+    // lane (g, n), register k: column 16 g + 4 v + k of the step, token n
+    const int col = st * kTileCols + 16 * g + 4 * wave;
+    const double two_step = a.meta[tok].two_step, neg_qs = a.meta[tok].neg_qs;
+    float r[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        // below 2^46: exact; so is the product with the power of two, and the difference needs at most 48 bits
+        double raw = (double)sum[0][k];
+#pragma unroll
+        for (int s = 1; s < kTSlices; ++s) raw = fma(raw, 256.0, (double)sum[s][k]);
+        double val = fma(raw, two_step, neg_qs);
+        if (a.out_scale && col + k < a.N) val *= (double)half_bits_to_float(a.out_scale[col + k]);
+        r[k] = (float)val;
+    }
+    float* const o = a.out + (size_t)tok * a.out_stride + col;
+    if ((a.out_stride & 3) == 0 && col + 4 <= a.N) {
+        *(v4f*)o = v4f{r[0], r[1], r[2], r[3]};
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (col + k < a.N) o[k] = r[k];
+    }
 }
 
-size_t gemv_t_partial_bytes(int64_t M, int64_t N, int batch)
+static size_t al256(size_t v) { return (v + 255) / 256 * 256; }
+
+size_t gemm_t_scratch_bytes(int64_t M, int batch)
 {
-    return (size_t)gemv_t_splits(M, N, batch) * batch * (size_t)n_steps(N) * kTileCols * sizeof(double);
+    return al256((size_t)batch * n_rowblocks(M) * kTRbBytes) + al256((size_t)batch * sizeof(QMeta));
 }
 
-// A is [M][N] as sign tiles; out[tok][0..N) = out_scale (.) A^T (in_scale (.) in[tok][0..M)).  `partial`: device,
-// gemv_t_partial_bytes(M, N, batch).
-int launch_gemv_t(const uint32_t* tiles, int64_t M, int64_t N, const void* in, int in_dtype, int in_stride, const uint16_t* in_scale,
-                  const uint16_t* out_scale, void* out, int out_dtype, int out_stride, int batch, double* partial, hipStream_t s)
+// A is [M][N] as sign tiles; out[tok][0..N) = out_scale (.) A^T (in_scale (.) in[tok][0..M)).  `scratch`: device,
+// gemm_t_scratch_bytes(M, batch), 16-byte aligned.
+int launch_gemm_t(const uint32_t* tiles, int64_t M, int64_t N, const void* in, int in_dtype, int in_stride, const uint16_t* in_scale,
+                  const uint16_t* out_scale, float* out, int out_stride, int batch, void* scratch, hipStream_t s)
 {
-    const int n_rb = (int)n_rowblocks(M), nst = (int)n_steps(N), n_split = gemv_t_splits(M, N, batch);
-    hipLaunchKernelGGL(gemv_t_kernel, dim3(nst, n_split, batch), dim3(64 * kTWaves), 0, s, tiles, nst, n_rb, (int)M, in, in_dtype, in_stride,
-                       in_scale, partial, n_split, batch);
-    hipLaunchKernelGGL(gemv_t_finish_kernel, dim3((unsigned)((N + 255) / 256), batch), dim3(256), 0, s, (const double*)partial, n_split, batch,
-                       nst * kTileCols, (int)N, out_scale, out, out_dtype, out_stride);
+    const int n_rb = (int)n_rowblocks(M);
+    uint8_t* bq = (uint8_t*)scratch;
+    QMeta* meta = (QMeta*)(bq + al256((size_t)batch * n_rb * kTRbBytes));
+    const TQuantArgs q{in, in_scale, bq, meta, (int)M, in_dtype, in_stride, n_rb * 8};
+    hipLaunchKernelGGL(quantize_t_kernel, dim3(batch), dim3(kTQThreads), 0, s, q);
+    NQ_HIP(hipGetLastError());
+    const TStageArgs t{tiles, bq, meta, out_scale, out, (int)N, (int)n_steps(N), n_rb, out_stride, batch};
+    hipLaunchKernelGGL(gemm_t_kernel, dim3((unsigned)((N + kTileCols - 1) / kTileCols), (unsigned)((batch + kTTokens - 1) / kTTokens)),
+                       dim3(64 * kTWaves), 0, s, t);
     NQ_HIP(hipGetLastError());
     return NQ_OK;
 }

@@ -1,0 +1,67 @@
+"""The products with the transposed sign matrices (nq_binlr_forward_transposed_unscaled, nq_binlr_backward_input) at the
+edges of their kernels: 64-column steps, 128-row blocks, eight waves per reduction, groups of 16 tokens, passes."""
+import numpy as np
+import pytest
+
+from paper_2602_06694_amd import binding as nq
+from paper_2602_06694_amd import synth
+from gpu_util import Layer, to_device
+
+pytestmark = pytest.mark.gpu
+
+# u = U^T(..) and w = V u are each rounded once to fp32 (relative 2-norm error 2^-24 / sqrt(3) each for values spread over
+# their binade, at most 2^-24); the fixed point behind them is 2^-31 of a token's maximum, below a tenth of that here.
+NORM_TOL = 2 * 2.0**-24
+
+
+def _reference(L, g64):
+    d = L.data
+    U = nq.nq_unpack_signs(d.U_words, L.r).astype(np.float64)
+    V = nq.nq_unpack_signs(d.V_words, L.r).astype(np.float64)
+    return ((g64 * d.s_out.astype(np.float64)) @ U) @ V.T
+
+
+def _norm_err(a, ref):
+    return np.linalg.norm(a.astype(np.float64) - ref) / np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("d_out,d_in,r,batch,dt", [
+    (1, 1, 1, 1, "f32"), (64, 64, 64, 16, "bf16"), (127, 63, 65, 17, "f16"), (129, 65, 128, 15, "f32"),
+    (1024, 130, 129, 33, "bf16"),            # eight row blocks: one per wave
+    (1025, 66, 257, 2, "f16"),               # nine: the second tile of one wave only
+    (2051, 321, 1100, 31, "f32"),            # seventeen; rows of an odd length (scalar loads)
+    (260, 200, 70, 530, "bf16"),             # more than one pass of 512 tokens
+    (9000, 300, 64, 3, "f32"),               # a vector longer than the quantiser keeps in registers
+])
+def test_transposed_products_at_the_edges(d_out, d_in, r, batch, dt):
+    import torch
+    L = Layer(d_out, d_in, r, "f32", seed=5100 + r, y_dtype=dt)
+    g_np = synth.gen_x(batch, d_out, 5200 + batch, dt)
+    g = to_device(g_np, dt)
+    w = torch.full((batch, d_in), float("nan"), dtype=torch.float32, device="cuda")
+    dx = torch.full((batch, d_in), float("nan"), dtype=torch.float32, device="cuda")
+    nq.nq_binlr_forward_transposed_unscaled(L.h, g, w, batch)
+    nq.nq_binlr_backward_input(L.h, g, dx, batch)
+    torch.cuda.synchronize()
+    ref = _reference(L, synth.x_as_f64(g_np, dt))
+    for t in range(batch):                   # token by token: each has its own fixed-point step
+        assert _norm_err(w[t].cpu().numpy(), ref[t]) <= NORM_TOL, t
+        assert _norm_err(dx[t].cpu().numpy(), ref[t] * L.data.s_in.astype(np.float64)) <= NORM_TOL, t
+    L.close()
+
+
+def test_a_non_finite_gradient_poisons_its_own_token_only():
+    import torch
+    d_out, d_in, r, batch = 300, 200, 100, 19
+    L = Layer(d_out, d_in, r, "f32", seed=5300)
+    g_np = synth.gen_x(batch, d_out, 5301, "f32")
+    g_np[3, 7], g_np[16, 299], g_np[18] = np.inf, np.nan, 0.0
+    w = torch.zeros((batch, d_in), dtype=torch.float32, device="cuda")
+    nq.nq_binlr_forward_transposed_unscaled(L.h, to_device(g_np, "f32"), w, batch)
+    torch.cuda.synchronize()
+    got = w.cpu().numpy()
+    assert np.isnan(got[[3, 16]]).all() and not got[18].any()
+    clean = [t for t in range(batch) if t not in (3, 16, 18)]
+    ref = _reference(L, np.nan_to_num(g_np, nan=0.0, posinf=0.0).astype(np.float64))
+    assert _norm_err(got[clean], ref[clean]) <= NORM_TOL
+    L.close()
