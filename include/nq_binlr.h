@@ -68,8 +68,8 @@ extern "C" {
 #define NQ_FLAG_DECODE_VALU  1u  /* every batch runs the plain fp32 vector-ALU kernels instead of the
                                     fixed-point matrix-core kernels (slow; a second implementation
                                     kept for cross-checks and as the paper-style "mask + FMA" GEMV) */
-#define NQ_FLAG_NO_PREFILL   2u  /* never take the dense MFMA path: a batch above 8 is run as chunks of 8
-                                    through the streaming kernels (their accuracy, their cost per chunk) */
+#define NQ_FLAG_NO_PREFILL   2u  /* never take the dense MFMA path: a batch above 8 is run as nq_binlr_forward_exact
+                                    runs it: through the streaming kernels (their accuracy, their cost per pass) */
 
 typedef struct nq_binlr_s* nq_handle;   /* one factorized layer resident on one GPU */
 typedef struct nq_plan_s*  nq_plan;     /* a fixed list of independent forwards */
@@ -144,6 +144,9 @@ int nq_binlr_set_mid_scale(nq_handle h, const uint16_t* s_mid_fp16);
 
 /* Grow the per-layer workspace so that forwards with ANY batch <= max_batch allocate nothing
  * (the dense path's need is not monotone in the batch; the largest need up to max_batch is taken).
+ * Also holds, from a max_batch of 9 on, the exact path's workspace for passes of up to max_batch tokens
+ * (about 8 MiB at most, or 64 tokens): nq_binlr_forward_exact, nq_binlr_forward_unscaled and
+ * NQ_FLAG_NO_PREFILL layers take such passes instead of passes of 8; the results are the same bits.
  * May allocate and synchronise. */
 int nq_binlr_reserve(nq_handle h, int max_batch);
 /* What has been reserved: the largest batch that allocates nothing, and the bytes of the dense
@@ -175,9 +178,9 @@ int nq_binlr_forward(nq_handle h, const void* x, void* y, int batch, void* strea
 #define NQ_STATIC_SCRATCH_BYTES (2u << 20)
 int nq_binlr_forward_static(nq_handle h, const void* x, void* y, int batch, void* stream);
 
-/* The same product for ANY batch through the streaming kernels only, in passes of up to 8 tokens
- * (exact integer accumulation of 24-bit fixed-point activations: the accuracy of a batch <= 8
- * forward, at the cost of one pass over the bits per 8 tokens) -- the per-call way to ask for the
+/* The same product for ANY batch through the streaming kernels only, in passes of 8 tokens, or of more
+ * where nq_binlr_reserve has made room for them (exact integer accumulation of 24-bit fixed-point
+ * activations: the accuracy of a batch <= 8 forward) -- the per-call way to ask for the
  * exact path above batch 8, where nq_binlr_forward takes the fp16-operand dense path.
  * Pointers, types and stream as in nq_binlr_forward; allocates nothing. */
 int nq_binlr_forward_exact(nq_handle h, const void* x, void* y, int batch, void* stream);
@@ -191,8 +194,8 @@ int nq_binlr_forward_exact(nq_handle h, const void* x, void* y, int batch, void*
  * nq_scale_grad does the products and the sum over the batch. */
 
 /* z = U (V^T (s_in (.) x)) [(.) s_mid where set]: the forward without its output scale.  Pointers
- * and types as in nq_binlr_forward (z has y_dtype).  Any batch, run as passes of up to 8 tokens through the
- * streaming kernels (exact integer accumulation).  Asynchronous on `stream`. */
+ * and types as in nq_binlr_forward (z has y_dtype).  Any batch, run as nq_binlr_forward_exact runs it
+ * (exact integer accumulation).  Asynchronous on `stream`. */
 int nq_binlr_forward_unscaled(nq_handle h, const void* x, void* z, int batch, void* stream);
 
 /* w = V (s_mid (.) (U^T (s_out (.) g))): the layer's transpose applied to g without the input scale

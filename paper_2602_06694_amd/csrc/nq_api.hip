@@ -356,6 +356,7 @@ static void free_handle(nq_handle h)
     slab_release(h->ws_slab, h->ws_alloc, h->ws_bytes);
     if (h->pf_alloc) (void)hipFree(h->pf_alloc);
     if (h->tp_alloc) (void)hipFree(h->tp_alloc);
+    if (h->xt_alloc) (void)hipFree(h->xt_alloc);
     if (h->s_mid) (void)hipFree(h->s_mid);
     delete h;
 }
@@ -554,7 +555,18 @@ extern "C" int nq_binlr_reserve(nq_handle h, int max_batch)
 {
     if (!h) return fail(NQ_E_NULL, "nq_binlr_reserve: NULL handle");
     if (max_batch < 1) return fail(NQ_E_INVALID_ARG, "nq_binlr_reserve: max_batch must be >= 1");
-    if (max_batch < NQ_PREFILL_MIN_BATCH || (h->flags & (NQ_FLAG_NO_PREFILL | NQ_FLAG_DECODE_VALU))) return NQ_OK;   // decode workspace is fixed
+    if (max_batch <= NQ_DECODE_MAX_BATCH || (h->flags & NQ_FLAG_DECODE_VALU)) return NQ_OK;   // decode workspace is fixed
+    // the exact path's workspace for passes of more than eight tokens (its calls themselves never allocate)
+    const int tokens = std::min(pass_tokens(carve_workspace(nullptr, nullptr, h->d_in, h->r, 16) / 16), (int)round_up(max_batch, 16));
+    if (h->xt_tokens < tokens) {
+        NQ_HIP(hipDeviceSynchronize());
+        if (h->xt_alloc) NQ_HIP(hipFree(h->xt_alloc));
+        h->xt_alloc = nullptr;
+        h->xt_tokens = 0;
+        NQ_HIP(hipMalloc(&h->xt_alloc, carve_workspace(nullptr, nullptr, h->d_in, h->r, tokens)));
+        h->xt_tokens = tokens;
+    }
+    if (max_batch < NQ_PREFILL_MIN_BATCH || (h->flags & NQ_FLAG_NO_PREFILL)) return NQ_OK;
     // The dense path's need is not monotone in the batch: smaller batches split the reduction
     // over more workgroups and keep more partial sums.  It depends on the batch only through its
     // padding to whole 64-token tiles, so the maximum over every padding up to max_batch's is taken.
@@ -666,6 +678,39 @@ static int decode_once(nq_handle h, const DecodeWorkspace& w, const void* x, voi
     return launch_stage(nullptr, s2, nullptr, (rb2 + per2 - 1) / per2, w2, per2, batch, s);
 }
 
+// any batch through the exact streaming kernels; `unscaled`: z = U (V^T (s_in (.) x)).  Passes of as many tokens as the workspace
+// of nq_binlr_reserve holds, of eight through the decode workspace where nothing has been reserved (or eight and fewer are left):
+// the same bits either way.  Allocates nothing.
+static int run_in_passes(nq_handle h, const void* x, void* y, int batch, hipStream_t s, bool unscaled)
+{
+    const size_t xs = dtype_size(h->x_dtype), ys = dtype_size(h->y_dtype);
+    const bool wide = h->xt_tokens > NQ_DECODE_MAX_BATCH && !(h->flags & NQ_FLAG_DECODE_VALU);
+    DecodeWorkspace w;
+    if (wide) (void)carve_workspace(&w, (char*)h->xt_alloc, h->d_in, h->r, h->xt_tokens);
+    for (int b0 = 0; b0 < batch;) {
+        const int left = batch - b0;
+        const char* xp = (const char*)x + (size_t)b0 * h->d_in * xs;
+        char* yp = (char*)y + (size_t)b0 * h->d_out * ys;
+        int rc, nb;
+        if (wide && left > NQ_DECODE_MAX_BATCH) {
+            nb = std::min(h->xt_tokens, left);
+            const QuantDesc qx = make_qx(h, w, xp), qt = make_qt(h, w);
+            StageDesc s2 = make_s2(h, w, yp);
+            if (unscaled) s2.out_scale = nullptr;
+            if ((rc = launch_quantize(nullptr, qx, 1, qx.n_chunks, nb, s)) != NQ_OK) return rc;
+            if ((rc = launch_stage_exact(make_s1(h, w), nb, s)) != NQ_OK) return rc;
+            if ((rc = launch_quantize(nullptr, qt, 1, qt.n_chunks, nb, s)) != NQ_OK) return rc;
+            rc = launch_stage_exact(s2, nb, s);
+        } else {
+            nb = std::min(NQ_DECODE_MAX_BATCH, left);
+            rc = decode_once(h, h->ws, xp, yp, nb, s, unscaled);
+        }
+        if (rc != NQ_OK) return rc;
+        b0 += nb;
+    }
+    return NQ_OK;
+}
+
 static int check_xy(const char* who, const void* x, const void* y, size_t x_bytes, size_t y_bytes)
 {
     char buf[160];
@@ -695,13 +740,7 @@ extern "C" int nq_binlr_forward(nq_handle h, const void* x, void* y, int batch, 
         a.d_out = h->d_out; a.d_in = h->d_in; a.r = h->r; a.batch = batch; a.x_dtype = h->x_dtype; a.y_dtype = h->y_dtype;
         return launch_prefill(a, s);
     }
-    // larger batches without the dense path: chunks of 8 through the streaming path (each chunk re-reads the bits)
-    for (int b0 = 0; b0 < batch; b0 += NQ_DECODE_MAX_BATCH) {
-        int nb = std::min(NQ_DECODE_MAX_BATCH, batch - b0);
-        rc = decode_once(h, h->ws, (const char*)x + (size_t)b0 * h->d_in * xs, (char*)y + (size_t)b0 * h->d_out * ys, nb, s);
-        if (rc != NQ_OK) return rc;
-    }
-    return NQ_OK;
+    return run_in_passes(h, x, y, batch, s, false);            // larger batches without the dense path
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1090,7 +1129,7 @@ extern "C" int nq_plan_forward_timed(nq_plan p, void* stream, float ms[4])
     return NQ_OK;
 }
 
-// any batch through the streaming kernels, in passes of up to 8 tokens; `unscaled`: z = U (V^T (s_in (.) x))
+// any batch through the streaming kernels, in passes; `unscaled`: z = U (V^T (s_in (.) x))
 static int forward_in_passes(const char* who, nq_handle h, const void* x, void* y, int batch, void* stream, bool unscaled)
 {
     char buf[96];
@@ -1099,13 +1138,7 @@ static int forward_in_passes(const char* who, nq_handle h, const void* x, void* 
     const size_t xs = dtype_size(h->x_dtype), ys = dtype_size(h->y_dtype);
     int rc = check_xy(who, x, y, (size_t)batch * h->d_in * xs, (size_t)batch * h->d_out * ys);
     if (rc != NQ_OK) return rc;
-    for (int b0 = 0; b0 < batch; b0 += NQ_DECODE_MAX_BATCH) {
-        const int nb = std::min(NQ_DECODE_MAX_BATCH, batch - b0);
-        rc = decode_once(h, h->ws, (const char*)x + (size_t)b0 * h->d_in * xs, (char*)y + (size_t)b0 * h->d_out * ys, nb,
-                         (hipStream_t)stream, unscaled);
-        if (rc != NQ_OK) return rc;
-    }
-    return NQ_OK;
+    return run_in_passes(h, x, y, batch, (hipStream_t)stream, unscaled);
 }
 
 extern "C" int nq_binlr_forward_unscaled(nq_handle h, const void* x, void* z, int batch, void* stream)

@@ -232,6 +232,9 @@ struct nq_binlr_s {
     // workspace of the transposed products (allocated by their first call)
     void* tp_alloc;
     int tp_tokens;        // tokens one pass may hold
+    // workspace of the exact path's passes of more than eight tokens (allocated by nq_binlr_reserve)
+    void* xt_alloc;
+    int xt_tokens;
 };
 
 
@@ -291,6 +294,9 @@ int shared_min_batch();          // smallest batch that takes the shared-input k
 size_t gemm_t_scratch_bytes(int64_t M, int batch);
 int launch_gemm_t(const uint32_t* tiles, int64_t M, int64_t N, const void* in, int in_dtype, int in_stride, const uint16_t* in_scale,
                   const uint16_t* out_scale, float* out, int out_stride, int batch, void* scratch, hipStream_t s);
+
+// ---- launchers (nq_exact.hip) ---------------------------------------------------------------
+int launch_stage_exact(const StageDesc& d, int batch, hipStream_t s);
 
 // ---- launchers (nq_exec.hip) ---------------------------------------------------------------
 bool small_layer_fits(nq_handle h, int batch);
