@@ -1,30 +1,38 @@
 // Dense (prefill, batch >= 9) path of  y = s_out (.) (U (V^T (s_in (.) x)))   (Section 3.1 Eq. 1;
 // Appendix E.3, "Binary GEMM Inference"): both contractions run on the fp16 matrix cores of gfx950.
 //
-//   pre   : x'' = fp16( s_in (.) x * 2^a_b )          per token b, 2^a_b puts max|x''| in [2^12, 2^13)
-//   gemm1 : T   = fp16( (X'' V) * g )                 g = power of two so that |T| <= 2^15 always
-//   gemm2 : y   = (T U^T) (.) s_out / (2^a_b * g)     fp32 out
+//   pre   : x'' = s_in (.) x * 2^a_b                  per token b, 2^a_b puts max|x''| in [2^12, 2^13)
+//   gemm1 : T   = (X'' V) * g                         g = power of two so that |T| <= 2^14 always
+//   gemm2 : y   = (T U^T) (.) s_out / (2^a_b * g)     fp32 accumulation throughout
 //
-// The sign matrices stay in the 1-bit tile layout of the streaming kernels.  A wave owns 128
-// output rows (one tile row block) and turns each 16-byte tile fragment in registers into the A
-// operands of v_mfma_f32_16x16x32_f16 with ONE vector AND per two weights: a weight's bit is left
-// where it is inside its 16-bit half, and a half with only bit p set IS an fp16 number, the
-// denormal 2^(p-24), which the matrix cores take at full precision.  Plane p (rows 16p .. 16p+15)
-// therefore accumulates 2^(p-24) * P with P = sum over the +1 weights of the activations, and the
-// signed sum follows as 2P - S, S = the plain sum of the activations of the token (two-operand
-// dot products on the chunks a thread stages anyway).  Against building +-1.0 operands (a shift
-// and a bit-field insert per two weights) this halves the vector instructions beside the MFMAs;
-// the two share the issue port of a SIMD, which was saturated.  The 64-token activation tile is
-// shared by the four waves of a workgroup through LDS, and two workgroups share a CU (two waves
-// per SIMD keep the matrix pipe fed).
+// A product with signs, two columns at a time, on the SPARSE matrix instruction.  For signs s1, s2 of a pair of columns
+//
+//   s1 x1 + s2 x2 = s1 * (x1 + x2)  where s1 = s2,   s1 * (x1 - x2)  where they differ,
+//
+// so with the operand holding the sum AND the difference of every pair (rounded to fp16, as x'' itself would be: the same
+// relative rounding on half as many terms of twice the square, hence the same error), a row of signs has exactly one nonzero,
+// +-1, per pair -- two in any four operand positions, which is what v_smfmac_f32_16x16x64_f16 takes: 64 columns in the 16
+// cycles in which the dense instruction does 32.  Nothing is pruned: the products left out are with exact zeros.
+//
+// The sign matrices stay in the 1-bit tile layout of the streaming kernels.  A wave owns 128 output rows (one tile row
+// block) and builds the operand of each 16-row plane in registers: the signs s1 shifted to the sign bits of +-1.0 (two vector
+// instructions per four weights), the positions from s1 xor s2 gathered once per tile (about 22 instructions for all eight
+// planes).  2.8 vector instructions per matrix instruction at 64 tokens a tile, and they are what bounds the loop: the two share
+// a SIMD's issue, each vector instruction costs about 2.5 of the matrix core's cycles (a loop of random operands sustains 4.15
+// PFLOP/s without, 2.3 with them; the clock falls to 2.0 .. 2.2 GHz under it).  Signs from memory and activations go straight
+// to LDS, without registers in between.
+// Measured (MI355X, bf16 in and out, whole forwards), dense instruction -> this: 8192 x 28672 r = 3520 at 2048 tokens
+// 390 -> 302 us; 28672 x 8192 at 512 tokens 116 -> 91 us; the first layer's two GEMMs 266 + 75 -> 190 + 60 us.
+// Not taken: 128-token tiles at one wave per SIMD (half the vector instructions per matrix instruction, no second wave to
+// hide the rest: level); 8-bit sparse operands in two slices (half the vector instructions, but the fixed point that outlier
+// tokens then get is coarser than fp16); three 6-bit slices with block scales (finer than fp16, 1.5 times the matrix cycles: level).
 //
 // fp16 (not bf16) operands: +-1 is exact in both and the MFMA rate is the same, but rounding x'
 // and t to 8 mantissa bits breaks the 1e-3 parity bar while 11 bits hold it with margin.
 //
-// Activation element order.  The two half2 registers made from one tile word hold reduction
-// indices (k0, k2) and (k1, k3); instead of permuting registers, X'' and T are STORED with the
-// middle two elements of every aligned group of four swapped, so a plain 16-byte LDS read yields
-// the matching B operand.
+// Operand order.  Of a step (64 columns) the lane group g of a tile holds columns 16 g + 4 v + b as byte b of word v; the pairs
+// are (word 0, word 1) and (word 2, word 3) at one byte index, i.e. columns c and c + 4, and X'' and T are STORED as
+// the pairs' sums and differences in the order in which the instruction meets them (pf_store_pairs).
 #include <algorithm>
 #include <cstdio>
 #include <type_traits>
@@ -41,15 +49,14 @@ typedef const __attribute__((address_space(1))) v4u32* gp_v4u32;
 
 constexpr int kPfTokens = 64;           // tokens per workgroup tile (4 MFMA column groups)
 constexpr int kPfWaves = 4;             // waves per workgroup, one 128-row block each
-constexpr int kPfLdsStride = 72;        // halves per token row in LDS (64 + 8: conflict-free 16-byte reads)
-constexpr int kPfThreads = 64 * kPfWaves;
+constexpr int kPfSlots = 4;             // 64-column steps staged in LDS at a time (one read, three on their way)
 constexpr int kPfTrStride = 132;        // floats per token row of a wave's epilogue region (128 + 4: conflict-free both ways)
 
-typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+typedef _Float16 v16h __attribute__((ext_vector_type(16)));
 enum { EPI_PARTIAL = 0, EPI_T = 1, EPI_Y = 2 };
 
 struct GemmArgs {
-    const _Float16* act;       // [m_pad][lda] halves, element order swizzled (see above)
+    const _Float16* act;       // [m_pad][lda] halves: pair sums and differences (see above)
     const uint32_t* tiles;     // sign tiles of the weight: rows = outputs, columns = reduction
     float* partial;            // EPI_PARTIAL: [splits][m_pad][n_pad] raw accumulators
     _Float16* t_out;           // EPI_T: [m_pad][ldt]
@@ -113,20 +120,33 @@ __device__ __forceinline__ void pf_load8(const void* x, int dtype, const uint16_
     }
 }
 
-// one workgroup per token: max |x'|, then x'' = fp16(x' * 2^a) in the swizzled element order.
-// Up to kPreHeld groups of eight values per thread stay in registers between the two passes
-// (rows up to 32768 elements are read once); longer rows are read twice.
-constexpr int kPreThreads = 1024;
-constexpr int kPreHeld = 4;
-
-__device__ __forceinline__ void pf_store8(_Float16* dst, const float v[8], float sc)
+// 16 consecutive values of a token (columns 16 g .. 16 g + 15 of a 64-column step), each times sc -> the sums and differences
+// of their eight pairs as fp16, in the order the matrix instruction meets them: dst = the token's step + 8 g halves, the second
+// eight go 32 halves further on.  A pair is (column c, column c + 4): bytes of one index in two words of a tile.
+__device__ __forceinline__ void pf_store_pairs(_Float16* dst, const float v[16], float sc)
 {
-    // storage order inside every aligned group of four: 0, 2, 1, 3
-    v8h o;
-    o[0] = (_Float16)(v[0] * sc); o[1] = (_Float16)(v[2] * sc); o[2] = (_Float16)(v[1] * sc); o[3] = (_Float16)(v[3] * sc);
-    o[4] = (_Float16)(v[4] * sc); o[5] = (_Float16)(v[6] * sc); o[6] = (_Float16)(v[5] * sc); o[7] = (_Float16)(v[7] * sc);
-    *(v8h*)dst = o;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        v8h o;
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+            // (scaled by the power of two first: sums of values near fp32's largest would overflow)
+            const int i = h + 2 * n;
+            const float a = v[i] * sc, b = v[4 + i] * sc, c = v[8 + i] * sc, d = v[12 + i] * sc;
+            o[4 * n] = (_Float16)(a + b);
+            o[4 * n + 1] = (_Float16)(a - b);
+            o[4 * n + 2] = (_Float16)(c + d);
+            o[4 * n + 3] = (_Float16)(c - d);
+        }
+        *(v8h*)(dst + 32 * h) = o;
+    }
 }
+
+// one workgroup per token: max |x'|, then the pairs of x'' = x' * 2^a as fp16.  A thread takes 16 columns at a time; up to
+// kPreHeld such chunks per thread stay in registers between the two passes (rows up to 32768 elements are read once); longer
+// rows are read twice.  The workgroup is no wider than the row needs (pre_threads).
+constexpr int kPreThreads = 1024;
+constexpr int kPreHeld = 2;
 
 // DT: the element type of x (a template parameter, so that the loads of the fast path sit in
 // straight-line code: all of a thread's chunks are requested back to back, then converted).
@@ -138,86 +158,103 @@ prefill_prescale_kernel(const void* __restrict__ x, const uint16_t* __restrict__
     __shared__ float sm[kPreThreads / 64];
     constexpr int x_dtype = DT;
     const int tok = blockIdx.x;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, threads = blockDim.x;
     const int64_t base = (int64_t)tok * d_in;
     constexpr int esz = DT == NQ_F32 ? 4 : 2;
+    const int n16 = lda / 16;
+    const bool held = n16 <= threads * kPreHeld;
+    // rows that fit the registers: no branch around a load.  A chunk past the last whole one re-reads chunk 0 and counts as
+    // zeros, the last, partial one is filled element by element.  (The loads are 16 bytes at the alignment of an element,
+    // which global memory takes: rows of odd lengths are read as wide as those of model shapes.  333 rows of 4095 fp16
+    // elements: 5.3 us, element by element 10.3.)
+    const bool fast = held && d_in >= 16;
     const bool vec = (((size_t)d_in * esz) & 15) == 0;      // every token row starts 16-byte aligned
-    const int n8 = lda / 8;
-    const bool held = n8 <= kPreThreads * kPreHeld;
-    // rows of whole, aligned chunks (every model shape): no branch around a load.  A thread's chunk
-    // past the end of the row re-reads chunk 0 and counts as zeros.
-    const bool fast = held && vec && (d_in & 7) == 0;
-    float hv[kPreHeld][8];
+    float hv[kPreHeld][16];
     float m = 0.f;
     if (fast) {
-        const int n_in = d_in / 8;
-        typedef const __attribute__((address_space(1))) v4f* gp_v4f;
-        v4u32 xr0[kPreHeld], sr[kPreHeld];
-        v4f xf0[kPreHeld], xf1[kPreHeld];
+        const int n_in = d_in / 16;
+        typedef v4f v4f_any __attribute__((aligned(4)));
+        typedef v4u32 v4u32_any __attribute__((aligned(2)));
+        typedef const __attribute__((address_space(1))) v4f_any* gp_v4f;
+        typedef const __attribute__((address_space(1))) v4u32_any* gp_v4u32_any;
+        v4u32 xr[kPreHeld][2], sr[kPreHeld][2];
+        v4f xf[kPreHeld][4];
         const char* const xrow = (const char*)x + (size_t)base * esz;
 #pragma unroll
         for (int k = 0; k < kPreHeld; ++k) {
-            const int c = tid + k * kPreThreads;
+            const int c = tid + k * threads;
             const uint32_t cc = (uint32_t)(c < n_in ? c : 0);
             if (DT == NQ_F32) {
-                xf0[k] = *(gp_v4f)(xrow + cc * 32u);
-                xf1[k] = *(gp_v4f)(xrow + cc * 32u + 16u);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) xf[k][i] = *(gp_v4f)(xrow + cc * 64u + 16u * i);
             } else {
-                xr0[k] = *(gp_v4u32)(xrow + cc * 16u);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) xr[k][i] = *(gp_v4u32_any)(xrow + cc * 32u + 16u * i);
             }
-            sr[k] = *(gp_v4u32)((const char*)s_in + cc * 16u);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) sr[k][i] = *(gp_v4u32)((const char*)s_in + cc * 32u + 16u * i);
         }
 #pragma unroll
         for (int k = 0; k < kPreHeld; ++k) {
-            const bool valid = tid + k * kPreThreads < n_in;
-            float xv[8];
-            if (DT == NQ_F32) {
-                const v4f a = xf0[k], b = xf1[k];
-                xv[0] = a.x; xv[1] = a.y; xv[2] = a.z; xv[3] = a.w;
-                xv[4] = b.x; xv[5] = b.y; xv[6] = b.z; xv[7] = b.w;
-            } else {
-                const uint32_t w[4] = {xr0[k].x, xr0[k].y, xr0[k].z, xr0[k].w};
+            const bool valid = tid + k * threads < n_in;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                float xv[8];
+                if (DT == NQ_F32) {
+                    const v4f a = xf[k][2 * h], b = xf[k][2 * h + 1];
+                    xv[0] = a.x; xv[1] = a.y; xv[2] = a.z; xv[3] = a.w;
+                    xv[4] = b.x; xv[5] = b.y; xv[6] = b.z; xv[7] = b.w;
+                } else {
+                    const uint32_t w[4] = {xr[k][h].x, xr[k][h].y, xr[k][h].z, xr[k][h].w};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const uint16_t lo = (uint16_t)(w[i] & 0xFFFFu), hi = (uint16_t)(w[i] >> 16);
+                        xv[2 * i] = DT == NQ_F16 ? h2f(lo) : __builtin_bit_cast(float, (uint32_t)lo << 16);
+                        xv[2 * i + 1] = DT == NQ_F16 ? h2f(hi) : __builtin_bit_cast(float, (uint32_t)hi << 16);
+                    }
+                }
+                const uint32_t sw[4] = {sr[k][h].x, sr[k][h].y, sr[k][h].z, sr[k][h].w};
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const uint16_t lo = (uint16_t)(w[i] & 0xFFFFu), hi = (uint16_t)(w[i] >> 16);
-                    xv[2 * i] = DT == NQ_F16 ? h2f(lo) : __builtin_bit_cast(float, (uint32_t)lo << 16);
-                    xv[2 * i + 1] = DT == NQ_F16 ? h2f(hi) : __builtin_bit_cast(float, (uint32_t)hi << 16);
+                    const float v0 = xv[2 * i] * h2f((uint16_t)(sw[i] & 0xFFFFu));
+                    const float v1 = xv[2 * i + 1] * h2f((uint16_t)(sw[i] >> 16));
+                    hv[k][8 * h + 2 * i] = valid ? v0 : 0.f;
+                    hv[k][8 * h + 2 * i + 1] = valid ? v1 : 0.f;
+                    m = fmaxf(m, fmaxf(fabsf(hv[k][8 * h + 2 * i]), fabsf(hv[k][8 * h + 2 * i + 1])));
                 }
             }
-            const uint32_t sw[4] = {sr[k].x, sr[k].y, sr[k].z, sr[k].w};
+            if ((d_in & 15) && tid + k * threads == n_in) {
+                pf_load8(x, x_dtype, s_in, base, n_in * 16, d_in, false, hv[k]);
+                pf_load8(x, x_dtype, s_in, base, n_in * 16 + 8, d_in, false, hv[k] + 8);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float v0 = xv[2 * i] * h2f((uint16_t)(sw[i] & 0xFFFFu));
-                const float v1 = xv[2 * i + 1] * h2f((uint16_t)(sw[i] >> 16));
-                hv[k][2 * i] = valid ? v0 : 0.f;
-                hv[k][2 * i + 1] = valid ? v1 : 0.f;
-                m = fmaxf(m, fmaxf(fabsf(hv[k][2 * i]), fabsf(hv[k][2 * i + 1])));
+                for (int i = 0; i < 16; ++i) m = fmaxf(m, fabsf(hv[k][i]));
             }
         }
     } else if (held) {
 #pragma unroll
         for (int k = 0; k < kPreHeld; ++k) {
-            const int c = tid + k * kPreThreads;
-            if (c < n8) {
-                pf_load8(x, x_dtype, s_in, base, c * 8, d_in, vec, hv[k]);
+            const int c = tid + k * threads;
+            if (c < n16) {
+                pf_load8(x, x_dtype, s_in, base, c * 16, d_in, false, hv[k]);
+                pf_load8(x, x_dtype, s_in, base, c * 16 + 8, d_in, false, hv[k] + 8);
 #pragma unroll
-                for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(hv[k][i]));
+                for (int i = 0; i < 16; ++i) m = fmaxf(m, fabsf(hv[k][i]));
             }
         }
     } else {
-        for (int c = tid; c < n8; c += kPreThreads) {
-            float v[8];
-            pf_load8(x, x_dtype, s_in, base, c * 8, d_in, vec, v);
+        for (int c = tid; c < n16; c += threads) {
+            float v[16];
+            pf_load8(x, x_dtype, s_in, base, c * 16, d_in, vec, v);
+            pf_load8(x, x_dtype, s_in, base, c * 16 + 8, d_in, vec, v + 8);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(v[i]));
+            for (int i = 0; i < 16; ++i) m = fmaxf(m, fabsf(v[i]));
         }
     }
     for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
     if ((tid & 63) == 0) sm[tid >> 6] = m;
     __syncthreads();
     m = sm[0];
-#pragma unroll
-    for (int w = 1; w < kPreThreads / 64; ++w) m = fmaxf(m, sm[w]);
+    for (int w = 1; w < threads / 64; ++w) m = fmaxf(m, sm[w]);
     // 2^a with max * 2^a in [2^12, 2^13); a NaN/Inf token keeps a = 0 and poisons only itself
     float sc = 1.0f;
     if (m > 0.f && m <= 3.0e38f) {
@@ -227,18 +264,20 @@ prefill_prescale_kernel(const void* __restrict__ x, const uint16_t* __restrict__
         a = a > 100 ? 100 : (a < -100 ? -100 : a);
         sc = ldexpf(1.0f, a);
     }
+    // chunk c = columns 16 (c & 3) .. of step c >> 2
     _Float16* row = xs + (size_t)tok * lda;
     if (held) {
 #pragma unroll
         for (int k = 0; k < kPreHeld; ++k) {
-            const int c = tid + k * kPreThreads;
-            if (c < n8) pf_store8(row + c * 8, hv[k], sc);
+            const int c = tid + k * threads;
+            if (c < n16) pf_store_pairs(row + (c >> 2) * 64 + (c & 3) * 8, hv[k], sc);
         }
     } else {
-        for (int c = tid; c < n8; c += kPreThreads) {
-            float v[8];
-            pf_load8(x, x_dtype, s_in, base, c * 8, d_in, vec, v);
-            pf_store8(row + c * 8, v, sc);
+        for (int c = tid; c < n16; c += threads) {
+            float v[16];
+            pf_load8(x, x_dtype, s_in, base, c * 16, d_in, vec, v);
+            pf_load8(x, x_dtype, s_in, base, c * 16 + 8, d_in, vec, v + 8);
+            pf_store_pairs(row + (c >> 2) * 64 + (c & 3) * 8, v, sc);
         }
     }
     if (tid == 0) tok_scale[tok] = 1.0f / (sc * g_t);
@@ -248,67 +287,155 @@ prefill_prescale_kernel(const void* __restrict__ x, const uint16_t* __restrict__
 // GEMM:  C[token][n] = sum_k act[token][k] * sign(tiles[n][k])
 // grid = (m_tiles * n_tiles, splits); block = 256 (4 waves x 128 output rows, 64 tokens)
 // ---------------------------------------------------------------------------------------------
-// acc + the sum of the eight fp16 values of a 16-byte chunk (each times `ones`): four v_dot2_f32_f16
-__device__ __forceinline__ float pf_sum8(const uint4& c, half2v ones, float acc)
+// 16 consecutive results of gemm 1 (columns n0 .. n0 + 15 of T, n0 a multiple of 16) of token `tok` -> T as gemm 2 reads it:
+// times g, times the rank-wise scale of the three-scale variant where there is one (its own power of two is folded into g);
+// columns beyond the real rank are exact zeros (they are padding of the next reduction).
+__device__ __forceinline__ void store_t16(const GemmArgs& a, int tok, int n0, const float c[16])
 {
-    // (the words are copied out first: a bit cast applied directly to an element of a vector
-    // type may read the vector's first element instead)
-    const uint32_t w0 = c.x, w1 = c.y, w2 = c.z, w3 = c.w;
-    acc = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2v, w0), ones, acc, false);
-    acc = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2v, w1), ones, acc, false);
-    acc = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2v, w2), ones, acc, false);
-    return __builtin_amdgcn_fdot2(__builtin_bit_cast(half2v, w3), ones, acc, false);
-}
-
-// One lane's four results of gemm 1 (rows n0 .. n0 + 3 of token `tok`, raw accumulators of negated
-// signs) -> fp16 T: times g, times the rank-wise scale of the three-scale variant where there is
-// one (its own power of two is folded into g), rows beyond the real rank exact zeros (they are
-// padding of the next reduction); stored in the swizzled order 0, 2, 1, 3.
-__device__ __forceinline__ void store_t(const GemmArgs& a, int tok, int n0, const v4f c)
-{
-    float f[4] = {-a.t_scale, -a.t_scale, -a.t_scale, -a.t_scale};
-    if (a.mid_scale) {
-        const uint2 m = *(const uint2*)(a.mid_scale + n0);
-        f[0] *= h2f((uint16_t)(m.x & 0xFFFFu));
-        f[1] *= h2f((uint16_t)(m.x >> 16));
-        f[2] *= h2f((uint16_t)(m.y & 0xFFFFu));
-        f[3] *= h2f((uint16_t)(m.y >> 16));
+    float f[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) f[i] = a.t_scale;
+    if (a.mid_scale && n0 < a.n_pad) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const uint4 m = *(const uint4*)(a.mid_scale + n0 + 8 * q);
+            const uint32_t w[4] = {m.x, m.y, m.z, m.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                f[8 * q + 2 * i] *= h2f((uint16_t)(w[i] & 0xFFFFu));
+                f[8 * q + 2 * i + 1] *= h2f((uint16_t)(w[i] >> 16));
+            }
+        }
     }
-    v4h o;
-    o.x = (_Float16)(n0 + 0 < a.n_real ? c.x * f[0] : 0.f);
-    o.y = (_Float16)(n0 + 2 < a.n_real ? c.z * f[2] : 0.f);
-    o.z = (_Float16)(n0 + 1 < a.n_real ? c.y * f[1] : 0.f);
-    o.w = (_Float16)(n0 + 3 < a.n_real ? c.w * f[3] : 0.f);
-    *(v4h*)(a.t_out + (size_t)tok * a.ldt + n0) = o;
+    float v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = n0 + i < a.n_real ? c[i] * f[i] : 0.f;
+    pf_store_pairs(a.t_out + (size_t)tok * a.ldt + (n0 >> 6) * 64 + ((n0 >> 4) & 3) * 8, v, 1.0f);
 }
 
-// TG = token groups of 16 per workgroup tile: 4 (64 tokens) normally; 2 (32 tokens) for narrow
-// outputs at small batches, where 64-token tiles are too few to cover the chip and splitting the
-// reduction instead would cost partial sums and a finalize pass (the sign expansion is then shared
-// by half as many MFMAs: lower efficiency per workgroup, but no extra passes).
+// A lane's 16 tile bytes as the sparse matrix instruction takes them.  Word v, byte b, bit p = the sign of (row 16 p + j, column
+// 16 g + 4 v + b); the pairs are (word 0, word 1) and (word 2, word 3) of one byte index, and a group of four operand positions
+// (two pairs: sum, difference, sum, difference) is one byte index, in the order 0, 2, 1, 3.
+//   r01, r23: words 0 and 2 with bytes 0 and 1 (2 and 3) side by side in 16-bit halves: the signs of the pairs' first members
+//   i0: 16-bit halves = planes 0 | 4 (bits 2 k) and 1 | 5 (bits 2 k + 1), bit 2 k = whether the signs of pair k differ; i1: 2 | 6, 3 | 7
+struct PfBits { uint32_t r01, r23, i0, i1; };
+__device__ __forceinline__ uint32_t pf_bfi(uint32_t m, uint32_t a, uint32_t b) { return (m & a) | (~m & b); }
+__device__ __forceinline__ uint32_t pf_gather_nibbles(uint32_t a)
+{
+    return pf_bfi(0xF0F00F0Fu, a, pf_bfi(0x0000FFFFu, a >> 12, a << 12));
+}
+__device__ __forceinline__ PfBits pf_bits(const v4u32 w)
+{
+    const uint32_t fa = w.x ^ w.y, fb = w.z ^ w.w;
+    PfBits b;
+    b.r01 = __builtin_amdgcn_perm(w.z, w.x, 0x05040100u);
+    b.r23 = __builtin_amdgcn_perm(w.z, w.x, 0x07060302u);
+    b.i0 = pf_gather_nibbles(pf_bfi(0x33333333u, fa, fb << 2));
+    b.i1 = pf_gather_nibbles(pf_bfi(0x33333333u, fa >> 2, fb));
+    return b;
+}
+// masks and constants of the two functions below, in registers: as literals the compiler spends an AND and an OR where
+// one v_and_or_b32 does
+struct PfConst { uint32_t sign, one, even, base; };
+__device__ __forceinline__ PfConst pf_const()
+{
+    PfConst k = {0x80008000u, 0x3C003C00u, 0x55555555u, 0x88888888u};
+    asm volatile("" : "+s"(k.sign), "+v"(k.one), "+s"(k.even), "+v"(k.base));
+    return k;
+}
+// the eight values (+-1.0) of plane p
+template <int P>
+__device__ __forceinline__ v4u32 pf_signs(const PfBits& b, const PfConst& k)
+{
+    v4u32 a;
+    a.x = ((b.r01 << (15 - P)) & k.sign) | k.one;
+    a.y = ((b.r23 << (15 - P)) & k.sign) | k.one;
+    a.z = ((b.r01 << (7 - P)) & k.sign) | k.one;
+    a.w = ((b.r23 << (7 - P)) & k.sign) | k.one;
+    return a;
+}
+// positions of the nonzeros of planes P (low half) and P + 4 (high half), P = 0..3
+template <int P>
+__device__ __forceinline__ uint32_t pf_index(const PfBits& b, const PfConst& k)
+{
+    const uint32_t w = P < 2 ? b.i0 : b.i1;
+    return ((P & 1 ? w >> 1 : w) & k.even) | k.base;
+}
+
+// four consecutive outputs o (already scaled) of y, row-major: one store at the alignment of an element (global memory takes
+// it: rows of any length are written as wide as those of model shapes), or element by element in a row's last, partial group
+// (`left` = elements to the row's end).  STREAM: non-temporal.  The second GEMM
+// of an 11005 x 4095 r = 1663 layer at 333 tokens: 24 us, with element stores 41.
+template <bool STREAM>
+__device__ __forceinline__ void store_y4(void* y, int dtype, size_t at, int left, const v4f o)
+{
+    typedef uint32_t v2u32 __attribute__((ext_vector_type(2)));
+    typedef v4f v4f_any __attribute__((aligned(4)));
+    typedef v2u32 v2u32_any __attribute__((aligned(2)));
+    if (left >= 4) {
+        if (dtype == NQ_F32) {
+            v4f_any* const p = (v4f_any*)((float*)y + at);
+            if (STREAM) __builtin_nontemporal_store(o, p);
+            else *p = o;
+        } else {
+            v2u32 pk;
+            pk.x = (uint32_t)float_to_out16(o.x, dtype) | ((uint32_t)float_to_out16(o.y, dtype) << 16);
+            pk.y = (uint32_t)float_to_out16(o.z, dtype) | ((uint32_t)float_to_out16(o.w, dtype) << 16);
+            v2u32_any* const p = (v2u32_any*)((uint16_t*)y + at);
+            if (STREAM) __builtin_nontemporal_store(pk, p);
+            else *p = pk;
+        }
+    } else {
+        if (left > 0) store_out(y, dtype, at, o.x);
+        if (left > 1) store_out(y, dtype, at + 1, o.y);
+        if (left > 2) store_out(y, dtype, at + 2, o.z);
+    }
+}
+// the output scales of four consecutive rows n0 .. n0 + 3 (n0 a multiple of 4; zero past the end)
+__device__ __forceinline__ v4f load_scale4(const uint16_t* scale, int n0, int n)
+{
+    v4f r = {0.f, 0.f, 0.f, 0.f};
+    if (n0 + 4 <= n) {
+        const uint2 sc = *(const uint2*)(scale + n0);
+        r.x = h2f((uint16_t)(sc.x & 0xFFFFu));
+        r.y = h2f((uint16_t)(sc.x >> 16));
+        r.z = h2f((uint16_t)(sc.y & 0xFFFFu));
+        r.w = h2f((uint16_t)(sc.y >> 16));
+    } else {
+        if (n0 < n) r.x = h2f(scale[n0]);
+        if (n0 + 1 < n) r.y = h2f(scale[n0 + 1]);
+        if (n0 + 2 < n) r.z = h2f(scale[n0 + 2]);
+    }
+    return r;
+}
+
+// C[token][n] = sum_k act[token][k] * sign(tiles[n][k]); grid = (m_tiles * n_tiles, splits), four waves x 128 output rows.
+// TG = token groups of 16 per workgroup tile: 4 (64 tokens) normally; 2 (32 tokens) where 64-token tiles are too few to cover
+// the chip, or leave a last round nearly empty (the sign operands then serve half as many matrix instructions: a step
+// costs a CU 0.255 us against 0.34, but a tile is half as large).
 // KS = 2: eight waves; waves 4..7 take the same rows and tokens as waves 0..3 but the second half of
-// the workgroup's part of the reduction (with activation buffers of their own), and hand their
-// accumulators to their partners through LDS before the epilogue.  For GEMMs whose tiles (times
-// splits) number no more than the CUs: such a workgroup fills its CU by itself (two waves per
+// the workgroup's part of the reduction (with staging buffers of their own), and hand their
+// accumulators to their partners through LDS before the epilogue.  Such a workgroup fills its CU by itself (two waves per
 // SIMD), and the reduction is halved without partial sums in memory.
-template <int EPI, int TG, int KS = 1>
-__global__ void __launch_bounds__(kPfThreads * KS) __attribute__((amdgpu_waves_per_eu(2, TG == 4 ? 2 : 4)))
+template <int EPI, int TG, int KS>
+__global__ void __launch_bounds__(64 * kPfWaves * KS) __attribute__((amdgpu_waves_per_eu(2, TG == 4 ? 2 : 4)))
 prefill_gemm_kernel(GemmArgs a)
 {
-    static_assert(TG == 2 || TG == 4, "32- or 64-token tiles");
-    static_assert(KS == 1 || (KS == 2 && TG == 4), "the in-workgroup split is built for 64-token tiles");
+    static_assert((TG == 2 && KS == 1) || (TG == 4 && (KS == 1 || KS == 2)), "32- or 64-token tiles; only the latter split their part in two");
+    constexpr int WR = kPfWaves;
     constexpr int kTok = 16 * TG;
-    // four activation buffers (per half of the workgroup); after the reduction the same memory serves
-    // the exchange of accumulators and the epilogue
-    constexpr int kActBuf = kTok * kPfLdsStride;                            // halves per buffer
-    constexpr int kLdsBytes = KS * 4 * kActBuf * 2 > kPfWaves * 16 * kPfTrStride * 4 ? KS * 4 * kActBuf * 2 : kPfWaves * 16 * kPfTrStride * 4;
-    static_assert(KS == 1 || kLdsBytes >= kPfWaves * 2 * 8 * 64 * 16, "exchange of two token groups per round");
-    __shared__ __attribute__((aligned(16))) char lds_raw[kLdsBytes];
-    const int tid = threadIdx.x & (kPfThreads - 1);                     // thread within its half
-    const int lane = tid & 63;
-    const int wave8 = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int wave = wave8 & (kPfWaves - 1), grp = wave8 / kPfWaves;
-    _Float16 (*const lds_act)[kActBuf] = (_Float16 (*)[kActBuf])lds_raw + 4 * grp;
+    // a slot holds one step: per wave the activations that it fetches (pieces of 8 tokens x 128 bytes), then its tile (1 KiB).
+    // After the reduction the same memory serves the exchange of accumulators and the epilogue.
+    constexpr int kPieces = 2 * TG / WR;                                // activation pieces per wave and step
+    constexpr int kWaveBytes = (kPieces + 1) * 1024, kSlotBytes = WR * kWaveBytes;
+    static_assert(kTok == 8 * kPieces * WR && kPieces <= 2, "a token group is two pieces");
+    constexpr int kRing = kPfSlots * kSlotBytes, kEpiBytes = WR * 16 * kPfTrStride * 4;
+    constexpr int kLdsBytes = KS * kRing > kEpiBytes ? KS * kRing : kEpiBytes;
+    static_assert(KS == 1 || kLdsBytes >= WR * 2 * 8 * 64 * 16, "exchange of two token groups per round");
+    __shared__ __attribute__((aligned(1024))) char lds_raw[kLdsBytes];
+    const int lane = threadIdx.x & 63;
+    const int wave_all = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int wave = wave_all % WR, grp = wave_all / WR;                // row block within the tile, part of the reduction
     const int g = lane >> 4, j = lane & 15;
 
     // workgroups that share a token tile run on the same XCD (ids are dealt round-robin to the
@@ -322,24 +449,16 @@ prefill_gemm_kernel(GemmArgs a)
     const int m_tile = id / a.n_tiles, n_tile = id - m_tile * a.n_tiles;
     const int split = blockIdx.y;
     // (with KS = 2 the host makes the workgroup's part a multiple of eight steps: equal halves, both
-    // multiples of four, so that all eight waves pass the same barriers)
+    // multiples of four, so that all waves pass the same barriers)
     const int wg_begin = split * a.steps_per_split;
     const int wg_steps = max(0, min(a.nst, wg_begin + a.steps_per_split) - wg_begin);
     const int n_my = wg_steps / KS;
     const int s_begin = wg_begin + grp * n_my;
 
-    int rb = n_tile * kPfWaves + wave;
+    const int rb = n_tile * WR + wave;
     const bool rb_valid = rb < a.n_rb;
-    if (!rb_valid) rb = a.n_rb - 1;                        // keep loading valid memory, store nothing
+    const int rb_ld = rb_valid ? rb : a.n_rb - 1;          // a wave past the last row block keeps loading valid memory
     const int m0 = m_tile * kTok;
-
-    // activation tile: 64 (32) tokens x 64 halves = 512 (256) chunks of 16 bytes, 2 (1) per thread:
-    // chunk c = tid + 256 i  ->  token c / 8, 16-byte column c % 8
-    const int ld_tok = tid >> 3, ld_kc = tid & 7;                       // chunk i adds 32 tokens
-    const _Float16* act_ptr = a.act + (size_t)(m0 + ld_tok) * a.lda + (size_t)s_begin * 64 + ld_kc * 8;
-    const size_t act_i = (size_t)32 * a.lda;
-    const int lds_off = ld_tok * kPfLdsStride + ld_kc * 8;
-    const v4u32* w_ptr = (const v4u32*)a.tiles + ((size_t)rb * a.nst + s_begin) * 64 + lane;
 
     v4f acc[8][TG];
 #pragma unroll
@@ -347,170 +466,140 @@ prefill_gemm_kernel(GemmArgs a)
 #pragma unroll
         for (int tg = 0; tg < TG; ++tg) acc[p][tg] = v4f{0.f, 0.f, 0.f, 0.f};
 
-    // two register sets for the activation chunks and the tile words: set (s & 1) belongs to step s
-    // (named registers, not arrays: arrays that are written under a condition end up in LDS)
-    uint4 a00, a01 = {0, 0, 0, 0}, a10, a11 = {0, 0, 0, 0};
-    v4u32 wr0, wr1, wr2, wr3 = {0, 0, 0, 0};
-#define PF_LOAD_ACT(R, step)                                                             \
-    do {                                                                                 \
-        const _Float16* q = act_ptr + (size_t)(step) * 64;                               \
-        R##0 = *(const uint4*)(q);                                                       \
-        if (TG == 4) R##1 = *(const uint4*)(q + act_i);                                  \
+    // Everything a step needs goes from memory to LDS without passing through registers, three steps ahead: each wave asks for
+    // its own tile (1 KiB) and its share of the activations (pieces of 8 tokens x 128 bytes).  Lane l of a piece
+    // fetches the 16 bytes (l & 7) ^ (l >> 3) of token l >> 3 (the place in LDS is the lane's): the lanes of a matrix operand
+    // then read 16-byte pieces of 16 tokens without bank conflicts.
+    constexpr int kDma = kPieces + 1;                                   // requests per wave and step
+    const uint32_t row_bytes = (uint32_t)a.lda * 2;
+    // (a request's immediate offset moves its LDS address too: 1024 per piece, taken back in the memory offset)
+    uint32_t act_off[kPieces];
+#pragma unroll
+    for (int i = 0; i < kPieces; ++i)
+        act_off[i] = (uint32_t)(lane >> 3) * row_bytes + (uint32_t)(((lane & 7) ^ (lane >> 3)) * 16) + i * (8 * row_bytes - 1024);
+    const uint32_t tile_off = (uint32_t)lane * 16;
+    const char* const act_base = (const char*)a.act + ((size_t)m0 + 8 * kPieces * wave) * row_bytes + (size_t)s_begin * 128;
+    const char* const tile_base = (const char*)a.tiles + ((size_t)rb_ld * a.nst + s_begin) * (kTileWords * 4);
+    const uint32_t lds_wave = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds_raw + (uint32_t)(grp * kRing + wave * kWaveBytes);
+    // (the requests are written out because for the builtin the compiler waits for all of them before every LDS read.  They
+    // have no register result; M0 holds the LDS address and is not used by anything else here.)
+#define PF_DMA1(lds_addr, voff, base)                                                                                      \
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(base) : "memory")
+#define PF_DMA2(lds_addr, voff0, voff1, base, OFF0, OFF1)                                                                  \
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3 offset:" OFF0                          \
+                 "\n\tglobal_load_lds_dwordx4 %2, %3 offset:" OFF1 ::"s"(lds_addr), "v"(voff0), "v"(voff1), "s"(base) : "memory")
+    // part k = 0 .. 2 of the requests of step `step` (spread over the planes of the step before: issued together they leave
+    // the matrix cores of their SIMD idle for 5 to 9 us in 100)
+#define PF_REQUEST(slot, step, k)                                                                                          \
+    do {                                                                                                                   \
+        const uint32_t la = lds_wave + (slot) * kSlotBytes;                                                                \
+        const char* const ab = act_base + (size_t)(step) * 128;                                                            \
+        const char* const tb = tile_base + (size_t)(step) * (kTileWords * 4);                                              \
+        if ((k) == 0) PF_DMA1(la + kPieces * 1024, tile_off, tb);                                                          \
+        if (kPieces == 1 && (k) == 1) PF_DMA1(la, act_off[0], ab);                                                         \
+        if (kPieces == 2 && (k) == 2) PF_DMA2(la, act_off[0], act_off[kPieces - 1], ab, "0", "1024");                      \
     } while (0)
-    // (ONES = two fp16 1.0, or zero where the chunks are a re-read past the end of the reduction:
-    // the running sums of the thread's chunks, S of its one or two tokens, must see a step once)
-#define PF_STORE_ACT(buf, R, ONES)                                                       \
-    do {                                                                                 \
-        _Float16* q = &lds_act[buf][lds_off];                                            \
-        *(uint4*)(q) = R##0;                                                             \
-        ssum0 = pf_sum8(R##0, ONES, ssum0);                                              \
-        if (TG == 4) {                                                                   \
-            *(uint4*)(q + 32 * kPfLdsStride) = R##1;                                     \
-            ssum1 = pf_sum8(R##1, ONES, ssum1);                                          \
-        }                                                                                \
-    } while (0)
-    // one reduction step on LDS buffer CUR with tile words W; the planes are kept in program
-    // order (scheduling barriers) so that only one expanded operand is alive at a time
-    float ssum0 = 0.f, ssum1 = 0.f;
-    const half2v ones = {(_Float16)1.0f, (_Float16)1.0f}, none = {(_Float16)0.f, (_Float16)0.f};
-    // B operands (activations of the 4 token groups) for one half step: two named register sets
-    // (reduction offsets 0..7 or 8..15 of each 16): set p for the first halves, q for the second
-    v8h p0, p1, p2 = {}, p3 = {}, q0, q1, q2 = {}, q3 = {};
-#define PF_READ_B(R, BUF, H)                                                             \
-    do {                                                                                 \
-        const _Float16* lr = &lds_act[BUF][j * kPfLdsStride + 16 * g + 8 * (H)];         \
-        R##0 = *(const v8h*)(lr);                                                        \
-        R##1 = *(const v8h*)(lr + 1 * 16 * kPfLdsStride);                                \
-        if (TG == 4) {                                                                   \
-            R##2 = *(const v8h*)(lr + 2 * 16 * kPfLdsStride);                            \
-            R##3 = *(const v8h*)(lr + 3 * 16 * kPfLdsStride);                            \
-        }                                                                                \
-    } while (0)
-#define PF_MFMA(P, G, B) acc[P][G] = __builtin_amdgcn_mfma_f32_16x16x32_f16(aop, B, acc[P][G], 0, 0, 0)
-    // one half step: 8 planes x 4 token groups.  w0 / w1 are the two tile words of this half.
-    // The scheduler is asked to alternate one MFMA with one vector op, so that the expansion of
-    // the next plane runs in the shadow of the current plane's MFMAs.
-    // plane p of a half step: bit p of each 16-bit half of the two tile words and of their copies
-    // shifted down by a byte (reduction indices (k0, k2), (k1, k3), (k4, k6), (k5, k7))
-#define PF_EXPAND(AU, p, w0, w0s, w1, w1s)                                               \
-    do {                                                                                 \
-        AU.x = (w0) & (0x00010001u << (p));                                              \
-        AU.y = (w0s) & (0x00010001u << (p));                                             \
-        AU.z = (w1) & (0x00010001u << (p));                                              \
-        AU.w = (w1s) & (0x00010001u << (p));                                             \
-    } while (0)
-#define PF_HALF(R, w0, w1)                                                               \
-    do {                                                                                 \
-        uint32_t w0s = (w0) >> 8, w1s = (w1) >> 8;                                       \
-        asm volatile("" : "+v"(w0s), "+v"(w1s));        /* one shift per word, not one per plane */ \
-        v4u32 au_next;                                                                   \
-        PF_EXPAND(au_next, 0, w0, w0s, w1, w1s);                                         \
-        __builtin_amdgcn_sched_barrier(0);                                               \
-        _Pragma("unroll") for (int p = 0; p < 8; ++p) {                                  \
-            const v8h aop = __builtin_bit_cast(v8h, au_next);                            \
-            if (p < 7) PF_EXPAND(au_next, p + 1, w0, w0s, w1, w1s);                      \
-            PF_MFMA(p, 0, R##0); PF_MFMA(p, 1, R##1);                                    \
-            if (TG == 4) { PF_MFMA(p, 2, R##2); PF_MFMA(p, 3, R##3); }                   \
-            _Pragma("unroll") for (int i = 0; i < TG; ++i) {                             \
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);        /* 1 MFMA */   \
-                __builtin_amdgcn_sched_group_barrier(0x002, 4 / TG, 0);   /* its share of the 4 vector ops */ \
-            }                                                                            \
-            __builtin_amdgcn_sched_barrier(0);                                           \
-        }                                                                                \
-    } while (0)
+    // all but the newest n of this wave's requests have arrived, and its own LDS reads are done; then the same for all waves
+#define PF_WAIT(n) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(n) : "memory")
 
-    // byte b of a tile word holds reduction index 4v+b, its bit p the row 16p + lane%16: bit p of
-    // the two halves of the word are (k0, k2), of the word shifted down by 8 (k1, k3)
-    // n_my is a multiple of 4 (the reduction is padded to 4 steps and so are the splits), and the
-    // loop body is branch-free: prefetches past the end re-read the last step instead of being
-    // skipped, so no control-flow join forces copies of the 256 accumulator registers.
-    // Step s works on LDS buffer s % 4 with tile-word set s % 4; everything it needs was requested
-    // well ahead, and every register set has ONE role per position of the four-step body, so the
-    // loop carries no register copies:
-    //   read the second-half operands of step s | fetch step s+3 from global (activations into the
-    //   free one of two register sets, tile words into the set that step s-1 used) | MFMAs of the
-    //   first half | write step s+2 (fetched during step s-1) into its buffer | read the
-    //   first-half operands of step s+1 (written during step s-1, before the last barrier) | MFMAs
-    //   of the second half | barrier.
-    // Every LDS read is issued half a step before its first use, every global load one and a half
-    // steps (activations) or three (tile words, which come from HBM).  A buffer is overwritten two
-    // steps (two barriers) after its last read.
+    // operand of token group tg, half h (positions 32 h + 8 g .. + 7 of the step): 16-byte piece (g & 1) * 4 + 2 h + (g >> 1) of
+    // token 16 tg + j
+    const int j7 = j & 7;
+    const uint32_t rd0 = (uint32_t)((j >> 3) * (kPieces == 1 ? kWaveBytes : 1024) + j7 * 128 + ((((g & 1) * 4 + (g >> 1)) ^ j7) * 16));
+    const char* const rd_h0 = lds_raw + grp * kRing + rd0;
+    const char* const rd_h1 = lds_raw + grp * kRing + (rd0 ^ 32u);
+    const char* const rd_tile = lds_raw + grp * kRing + wave * kWaveBytes + kPieces * 1024 + lane * 16;
+#define PF_READ_B(SET, slot, tg)                                                                                           \
+    do {                                                                                                                   \
+        const int at = (slot) * kSlotBytes + (2 * (tg) / kPieces) * kWaveBytes + (2 * (tg) % kPieces) * 1024;              \
+        const v8h lo = *(const v8h*)(rd_h0 + at);                                                                          \
+        const v8h hi = *(const v8h*)(rd_h1 + at);                                                                          \
+        bop[SET][tg] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);              \
+    } while (0)
+#define PF_READ_TILE(slot) (*(const v4u32*)(rd_tile + (slot) * kSlotBytes))
+
+    // n_my is a multiple of 4 (the reduction is padded to 4 steps and so are the splits), and the loop body is branch-free:
+    // requests past the end ask for the last step again.  Step s works on registers read during step s - 1; meanwhile
+    // slot s + 1 is read, slots s + 2 and s + 3 fill, and step s + 4 is requested into the slot that step s has left.
     if (n_my > 0) {
         const int last = n_my - 1;
-        // the order in which loads are issued is pinned (scheduling barriers) and is the same in the
-        // prologue and in the loop -- activation chunks, then tile words, per step -- so that the
-        // compiler can wait for "all but the newest n" loads instead of for all of them
-        const int i1 = min(1, last), i2 = min(2, last);
-        PF_LOAD_ACT(a0, 0);
-        wr0 = w_ptr[0];
-        __builtin_amdgcn_sched_barrier(0);
-        PF_LOAD_ACT(a1, i1);
-        wr1 = w_ptr[(size_t)i1 * 64];
-        __builtin_amdgcn_sched_barrier(0);
-        PF_STORE_ACT(0, a0, ones);
-        PF_STORE_ACT(1, a1, 1 <= last ? ones : none);
-        __builtin_amdgcn_sched_barrier(0);
-        PF_LOAD_ACT(a1, i2);
-        wr2 = w_ptr[(size_t)i2 * 64];
-        __builtin_amdgcn_sched_barrier(0);
-        __syncthreads();
-        PF_READ_B(p, 0, 0);
-#define PF_STEP(CUR, NXT, ST, AL, AS, WL, WC, step)                                      \
-    do {                                                                                 \
-        PF_READ_B(q, CUR, 1);                                                            \
-        const int nx = min((step) + 3, last);                                            \
-        __builtin_amdgcn_sched_barrier(0);                                               \
-        PF_LOAD_ACT(AL, nx);                                                             \
-        WL = w_ptr[(size_t)nx * 64];                                                     \
-        __builtin_amdgcn_sched_barrier(0);                                               \
-        PF_HALF(p, WC.x, WC.y);                                                          \
-        PF_STORE_ACT(ST, AS, (step) + 2 <= last ? ones : none);                          \
-        PF_READ_B(p, NXT, 0);                                                            \
-        PF_HALF(q, WC.z, WC.w);                                                          \
-        __syncthreads();                                                                 \
+        v16h bop[2][TG];
+        v4u32 w;
+#pragma unroll
+        for (int k = 0; k < kPfSlots; ++k)
+#pragma unroll
+            for (int part = 0; part < 3; ++part) PF_REQUEST(k, min(k, last), part);
+        PF_WAIT(3 * kDma);
+        w = PF_READ_TILE(0);
+#pragma unroll
+        for (int tg = 0; tg < TG; ++tg) PF_READ_B(0, 0, tg);
+        const PfConst kc = pf_const();
+        PfBits bits = pf_bits(w);
+        v4u32 au = pf_signs<0>(bits, kc);
+        uint32_t ix0 = pf_index<0>(bits, kc), ix1 = 0, ix2 = 0, ix3 = 0;
+        // one plane: the values of the next plane are built, and LDS is read, in the shadow of its matrix instructions
+#define PF_PLANE(P, SET, IX, HALF, NEXT, READS, NVALU)                                                                     \
+    do {                                                                                                                   \
+        const v8h aop = __builtin_bit_cast(v8h, au);                                                                       \
+        NEXT;                                                                                                              \
+        READS;                                                                                                             \
+        _Pragma("unroll") for (int tg = 0; tg < TG; ++tg)                                                                  \
+            acc[P][tg] = __builtin_amdgcn_smfmac_f32_16x16x64_f16(aop, bop[SET][tg], acc[P][tg], (int)IX, 0, HALF);        \
+        _Pragma("unroll") for (int i = 0; i < TG; ++i) {                                                                   \
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                                             \
+            __builtin_amdgcn_sched_group_barrier(0x002, ((NVALU) + TG - 1) / TG, 0);                                       \
+            if (i < 4) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                                  \
+        }                                                                                                                  \
+        __builtin_amdgcn_sched_barrier(0);                                                                                 \
+    } while (0)
+        // the reads of the next step beside plane number k of this one
+#define PF_READS(SET, slot, k)                                                                                             \
+    do {                                                                                                                   \
+        if ((k) == 0) w = PF_READ_TILE(slot);                                                                              \
+        if ((k) < TG) PF_READ_B(SET, slot, (k) % TG);                                                           \
+    } while (0)
+#define PF_STEP(SET, SLOT, step)                                                                                           \
+    do {                                                                                                                   \
+        PF_WAIT(2 * kDma);                                                                                                 \
+        const int nx = min((step) + kPfSlots, last);                                                                       \
+        constexpr int NS = ((SLOT) + 1) % kPfSlots, ST = 1 - (SET);                                                        \
+        PF_PLANE(0, SET, ix0, 0, au = pf_signs<4>(bits, kc); ix1 = pf_index<1>(bits, kc), PF_READS(ST, NS, 0); PF_REQUEST(SLOT, nx, 0), 10);        \
+        PF_PLANE(4, SET, ix0, 1, au = pf_signs<1>(bits, kc); ix2 = pf_index<2>(bits, kc), PF_READS(ST, NS, 1); PF_REQUEST(SLOT, nx, 1), 9);         \
+        PF_PLANE(1, SET, ix1, 0, au = pf_signs<5>(bits, kc); ix3 = pf_index<3>(bits, kc), PF_READS(ST, NS, 2); PF_REQUEST(SLOT, nx, 2), 10);        \
+        PF_PLANE(5, SET, ix1, 1, au = pf_signs<2>(bits, kc), PF_READS(ST, NS, 3), 8);                                      \
+        PF_PLANE(2, SET, ix2, 0, au = pf_signs<6>(bits, kc), , 8);                                      \
+        PF_PLANE(6, SET, ix2, 1, au = pf_signs<3>(bits, kc), , 8);                                      \
+        PF_PLANE(3, SET, ix3, 0, au = pf_signs<7>(bits, kc); bits = pf_bits(w), , 28);                  \
+        PF_PLANE(7, SET, ix3, 1, au = pf_signs<0>(bits, kc); ix0 = pf_index<0>(bits, kc), , 10);                           \
     } while (0)
         for (int s = 0; s < n_my; s += 4) {
-            PF_STEP(0, 1, 2, a0, a1, wr3, wr0, s);
-            PF_STEP(1, 2, 3, a1, a0, wr0, wr1, s + 1);
-            PF_STEP(2, 3, 0, a0, a1, wr1, wr2, s + 2);
-            PF_STEP(3, 0, 1, a1, a0, wr2, wr3, s + 3);
+            PF_STEP(0, 0, s);
+            PF_STEP(1, 1, s + 1);
+            PF_STEP(0, 2, s + 2);
+            PF_STEP(1, 3, s + 3);
         }
 #undef PF_STEP
+#undef PF_PLANE
+#undef PF_READS
     }
-#undef PF_LOAD_ACT
-#undef PF_STORE_ACT
-#undef PF_HALF
-#undef PF_EXPAND
+    // nothing on its way into LDS any more, in no wave: the memory changes hands
+    PF_WAIT(0);
+#undef PF_WAIT
+#undef PF_REQUEST
+#undef PF_DMA1
+#undef PF_DMA2
 #undef PF_READ_B
-#undef PF_MFMA
+#undef PF_READ_TILE
 
-    // S of the tile's tokens: the eight threads that staged a token's chunks add up their sums
-    // (neighbouring lanes), and the sums go through LDS (the activation buffers are done with) to
-    // the lanes that hold the token's results
     float* const lds_f = (float*)&lds_raw[0];
-    ssum0 += __shfl_xor(ssum0, 1); ssum0 += __shfl_xor(ssum0, 2); ssum0 += __shfl_xor(ssum0, 4);
-    if (TG == 4) { ssum1 += __shfl_xor(ssum1, 1); ssum1 += __shfl_xor(ssum1, 2); ssum1 += __shfl_xor(ssum1, 4); }
-    __syncthreads();
-    if (ld_kc == 0) {
-        lds_f[grp * 64 + ld_tok] = ssum0;
-        if (TG == 4) lds_f[grp * 64 + ld_tok + 32] = ssum1;
-    }
-    __syncthreads();
-    float s_tok[TG];
-#pragma unroll
-    for (int tg = 0; tg < TG; ++tg) {
-        s_tok[tg] = lds_f[tg * 16 + j];
-        if (KS == 2) s_tok[tg] += lds_f[64 + tg * 16 + j];
-    }
-    __syncthreads();                                       // the sums are read: LDS changes hands once more
     if (KS == 2) {
-        // waves 4..7 hand their accumulators to waves 0..3, two token groups per round: a lane's 16
+        // the second part's waves hand their accumulators to the first's, two token groups per round: a lane's 16
         // registers of a token group go to the same lane of the partner (no transposition here).
         // Every wave adds what it reads (the second half's sums are not used any further): no
         // branch around a write to the accumulators.
         float* const xr = lds_f + wave * (2 * 8 * 64 * 4);
 #pragma unroll
-        for (int round = 0; round < 2; ++round) {
+        for (int round = 0; round < TG / 2; ++round) {
             if (grp == 1) {
 #pragma unroll
                 for (int tl = 0; tl < 2; ++tl)
@@ -519,47 +608,49 @@ prefill_gemm_kernel(GemmArgs a)
             }
             __syncthreads();
 #pragma unroll
-            for (int tl = 0; tl < 2; ++tl)
+            for (int tl = 0; tl < 2; ++tl) {
 #pragma unroll
                 for (int p = 0; p < 8; ++p) acc[p][2 * round + tl] += *(const v4f*)(xr + ((tl * 8 + p) * 64 + lane) * 4);
+                __builtin_amdgcn_sched_barrier(0);          // (eight reads in flight, not sixteen: registers)
+            }
             __syncthreads();
         }
         if (grp == 1) return;
     }
-    if (!rb_valid) return;
+    if (!rb_valid) {
+        // columns of T beyond the last row block are padding of gemm 2's reduction (at most one row block of them): zeros
+        if (EPI == EPI_T && rb == a.n_rb && rb * kTileRows < a.ldt) {
+            const v8h z = {};
+#pragma unroll
+            for (int i = 0; i < kTok * 16 / 64; ++i) {
+                const int c = lane + 64 * i;
+                *(v8h*)(a.t_out + (size_t)(m0 + (c >> 4)) * a.ldt + rb * kTileRows + (c & 15) * 8) = z;
+            }
+        }
+        return;
+    }
 
     // Result layout: lane (g, j), register v of acc[p][tg]  <->  C[token m0 + 16 tg + j][row 128 rb + 16 p + 4 g + v],
     // i.e. a lane holds 4 consecutive rows of a token and a store straight from the accumulators
     // would write 64-byte pieces of 16 different output rows.  Each wave therefore turns its
     // results round in a private LDS region, 16 tokens at a time: written in the layout above,
     // read back as [token][128 rows], so that one store instruction covers two tokens x 512
-    // contiguous bytes (256 for fp16 T).  Measured on 28672x8192 r=3520 at 2048 tokens: the stores
+    // contiguous bytes (eight tokens x 2 x 64 bytes for T).  Measured on 28672x8192 r=3520 at 2048 tokens: the stores
     // were 18 % of the time of a forward.
-    // c = S - 2^(25-p) acc = -(2P - S): the negated signed sum, so every factor below carries a minus
     float* const tr = lds_f + wave * (16 * kPfTrStride);
     const int rd_col = 4 * (lane & 31), rd_tok = lane >> 5;
     const int n0 = rb * kTileRows + rd_col;                 // the 4 rows this lane stores
-    const bool aligned_y = (a.n_real & 3) == 0;
-    float osc[4] = {0.f, 0.f, 0.f, 0.f};
-    if (EPI == EPI_Y && aligned_y && n0 < a.n_real) {
-        const uint2 sc = *(const uint2*)(a.out_scale + n0);
-        osc[0] = h2f((uint16_t)(sc.x & 0xFFFFu));
-        osc[1] = h2f((uint16_t)(sc.x >> 16));
-        osc[2] = h2f((uint16_t)(sc.y & 0xFFFFu));
-        osc[3] = h2f((uint16_t)(sc.y >> 16));
-    }
+    const v4f osc = EPI == EPI_Y ? load_scale4(a.out_scale, n0, a.n_real) : v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int tg = 0; tg < TG; ++tg) {
         float f = 1.0f;
         if (EPI == EPI_Y) {
             const int tok = m0 + tg * 16 + j;
-            f = tok < a.batch ? -a.tok_scale[tok] : 0.f;
+            f = tok < a.batch ? a.tok_scale[tok] : 0.f;
         }
 #pragma unroll
         for (int p = 0; p < 8; ++p) {
-            const float w_p = -(float)(1u << (25 - p));
-            const v4f r = acc[p][tg];
-            v4f c = {fmaf(r.x, w_p, s_tok[tg]), fmaf(r.y, w_p, s_tok[tg]), fmaf(r.z, w_p, s_tok[tg]), fmaf(r.w, w_p, s_tok[tg])};
+            v4f c = acc[p][tg];
             if (EPI == EPI_Y) c *= f;
             *(v4f*)(tr + j * kPfTrStride + 16 * p + 4 * g) = c;
         }
@@ -567,42 +658,29 @@ prefill_gemm_kernel(GemmArgs a)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        if (EPI == EPI_T) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int t = rd_tok + 2 * i;
-            const int tok = m0 + tg * 16 + t;
-            const v4f c = *(const v4f*)(tr + t * kPfTrStride + rd_col);
-            if (EPI == EPI_PARTIAL) {
-                float* dst = a.partial + ((size_t)split * a.m_pad + tok) * a.n_pad + n0;
-                *(v4f*)dst = c;
-            } else if (EPI == EPI_T) {
-                store_t(a, tok, n0, c);
-            } else {
-                if (tok < a.batch) {
-                    const size_t at = (size_t)tok * a.n_real + n0;
-                    const float cv[4] = {c.x, c.y, c.z, c.w};
-                    if (aligned_y) {                        // rows stay aligned: one store per lane
-                        if (n0 < a.n_real) {
-                            v4f o;
-                            o.x = cv[0] * osc[0];
-                            o.y = cv[1] * osc[1];
-                            o.z = cv[2] * osc[2];
-                            o.w = cv[3] * osc[3];
-                            if (a.y_dtype == NQ_F32) {
-                                __builtin_nontemporal_store(o, (v4f*)((float*)a.y_out + at));
-                            } else {
-                                typedef uint32_t v2u32 __attribute__((ext_vector_type(2)));
-                                v2u32 pk;
-                                pk.x = (uint32_t)float_to_out16(o.x, a.y_dtype) | ((uint32_t)float_to_out16(o.y, a.y_dtype) << 16);
-                                pk.y = (uint32_t)float_to_out16(o.z, a.y_dtype) | ((uint32_t)float_to_out16(o.w, a.y_dtype) << 16);
-                                __builtin_nontemporal_store(pk, (v2u32*)((uint16_t*)a.y_out + at));     // (as the fp32 store: written once, not read here)
-                            }
-                        }
-                    } else {
+            for (int i = 0; i < 2; ++i) {
+                const int t = (lane >> 3) + 8 * i, col = 16 * (lane & 7);
+                float c[16];
 #pragma unroll
-                        for (int v = 0; v < 4; ++v)
-                            if (n0 + v < a.n_real) store_out(a.y_out, a.y_dtype, at + v, cv[v] * h2f(a.out_scale[n0 + v]));
-                    }
+                for (int q = 0; q < 4; ++q) {
+                    const v4f r = *(const v4f*)(tr + t * kPfTrStride + col + 4 * q);
+                    c[4 * q] = r.x; c[4 * q + 1] = r.y; c[4 * q + 2] = r.z; c[4 * q + 3] = r.w;
+                }
+                store_t16(a, m0 + tg * 16 + t, rb * kTileRows + col, c);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int t = rd_tok + 2 * i;
+                const int tok = m0 + tg * 16 + t;
+                const v4f c = *(const v4f*)(tr + t * kPfTrStride + rd_col);
+                if (EPI == EPI_PARTIAL) {
+                    float* dst = a.partial + ((size_t)split * a.m_pad + tok) * a.n_pad + n0;
+                    *(v4f*)dst = c;
+                } else if (tok < a.batch) {
+                    store_y4<true>(a.y_out, a.y_dtype, (size_t)tok * a.n_real + n0, a.n_real - n0, c * osc);
                 }
             }
         }
@@ -611,46 +689,38 @@ prefill_gemm_kernel(GemmArgs a)
     }
 }
 
-// sum the split-K partials and apply the epilogue; one thread per four consecutive outputs
+// sum the split-K partials and apply the epilogue; one thread per four consecutive outputs (y) or 16 columns of T (the
+// columns between the last row block and T's row length are padding of gemm 2's reduction: zeros)
 template <int EPI>
 __global__ void __launch_bounds__(256)
 prefill_finalize_kernel(GemmArgs a)
 {
     const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-    const int n4 = a.n_pad / 4;
-    const size_t total = (size_t)a.m_pad * n4;
-    if (idx >= total) return;
-    const int tok = (int)(idx / n4), n0 = (int)(idx % n4) * 4;
-    v4f c = {0.f, 0.f, 0.f, 0.f};
-    for (int s = 0; s < a.splits; ++s) c += *(const v4f*)(a.partial + ((size_t)s * a.m_pad + tok) * a.n_pad + n0);
     if (EPI == EPI_T) {
-        store_t(a, tok, n0, c);
-    } else {
-        if (tok < a.batch) {
-            const float f = -a.tok_scale[tok];
-            const float cv[4] = {c.x, c.y, c.z, c.w};
-            const size_t at = (size_t)tok * a.n_real + n0;
-            if ((a.n_real & 3) == 0) {                     // rows stay aligned: one load of scales, one store
-                if (n0 < a.n_real) {
-                    const uint2 sc = *(const uint2*)(a.out_scale + n0);
-                    v4f o;
-                    o.x = cv[0] * f * h2f((uint16_t)(sc.x & 0xFFFFu));
-                    o.y = cv[1] * f * h2f((uint16_t)(sc.x >> 16));
-                    o.z = cv[2] * f * h2f((uint16_t)(sc.y & 0xFFFFu));
-                    o.w = cv[3] * f * h2f((uint16_t)(sc.y >> 16));
-                    if (a.y_dtype == NQ_F32) {
-                        *(v4f*)((float*)a.y_out + at) = o;
-                    } else {
-                        uint2 pk;
-                        pk.x = (uint32_t)float_to_out16(o.x, a.y_dtype) | ((uint32_t)float_to_out16(o.y, a.y_dtype) << 16);
-                        pk.y = (uint32_t)float_to_out16(o.z, a.y_dtype) | ((uint32_t)float_to_out16(o.w, a.y_dtype) << 16);
-                        *(uint2*)((uint16_t*)a.y_out + at) = pk;
-                    }
-                }
-            } else {
-                for (int v = 0; v < 4; ++v)
-                    if (n0 + v < a.n_real) store_out(a.y_out, a.y_dtype, at + v, cv[v] * f * h2f(a.out_scale[n0 + v]));
+        const int n16 = a.ldt / 16;
+        if (idx >= (size_t)a.m_pad * n16) return;
+        const int tok = (int)(idx / n16), n0 = (int)(idx % n16) * 16;
+        v4f c4[4] = {};
+        if (n0 < a.n_pad) {
+            for (int s = 0; s < a.splits; ++s) {
+                const float* src = a.partial + ((size_t)s * a.m_pad + tok) * a.n_pad + n0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) c4[q] += *(const v4f*)(src + 4 * q);
             }
+        }
+        float c[16];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { c[4 * q] = c4[q].x; c[4 * q + 1] = c4[q].y; c[4 * q + 2] = c4[q].z; c[4 * q + 3] = c4[q].w; }
+        store_t16(a, tok, n0, c);
+    } else {
+        const int n4 = a.n_pad / 4;
+        if (idx >= (size_t)a.m_pad * n4) return;
+        const int tok = (int)(idx / n4), n0 = (int)(idx % n4) * 4;
+        v4f c = {0.f, 0.f, 0.f, 0.f};
+        for (int s = 0; s < a.splits; ++s) c += *(const v4f*)(a.partial + ((size_t)s * a.m_pad + tok) * a.n_pad + n0);
+        if (tok < a.batch) {
+            const float f = a.tok_scale[tok];
+            store_y4<false>(a.y_out, a.y_dtype, (size_t)tok * a.n_real + n0, a.n_real - n0, c * f * load_scale4(a.out_scale, n0, a.n_real));
         }
     }
 }
@@ -661,24 +731,14 @@ prefill_finalize_kernel(GemmArgs a)
 static size_t al256(size_t v) { return (v + 255) / 256 * 256; }
 
 struct PfLayout {
-    int m_pad, k1, k2, n1_pad, n2_pad;
+    int m_pad;                // tokens rounded up to whole 64-token tiles
+    int k1, k2, n1_pad, n2_pad;
     int splits1, splits2;
     int tg1, tg2;             // token groups of 16 per workgroup tile of the two GEMMs (4 or 2)
-    int ks1, ks2;             // halves of the reduction taken inside a workgroup (1, or 2: eight waves)
+    int ks1, ks2;             // parts of the reduction taken inside a workgroup (1 or 2)
     size_t off_x, off_t, off_scale, off_partial, total;
 };
 
-// Tiling of one GEMM: token groups per workgroup tile (4 = 64 tokens, 2 = 32 tokens) and the number of
-// workgroups the reduction is split over, for outputs that alone give too few workgroups to
-// cover the chip.  Cost model in microseconds, constants measured on the 70B MLP shapes (with the
-// first version of the kernel; the kernel has since gained a few per cent everywhere, and sweeps
-// over splits and tile sizes on those shapes still land on the choices this model makes):
-//  - a reduction step of a 64-token workgroup takes 0.73 us when it has its CU to itself and
-//    1.17 us when two share one (two is all that fits);
-//  - a 32-token workgroup needs 0.60 us per step alone (the sign expansion is not halved), and a
-//    CU completes at most 3.9 of their steps per microsecond (up to four fit);
-//  - splitting costs a finalize launch (2 us) plus, per split, the write and re-read of one set of
-//    fp32 partial sums, not overlapped with anything: about 2.3 MB per microsecond.
 // steps per split, rounded up to a multiple of 4 (as nst itself is): the kernel's loop body is four
 // steps; of 8 where the workgroup halves its part once more (ks = 2: nst is then a multiple of 8 too)
 static int steps_per_split4(int nst, int splits, int ks = 1)
@@ -687,51 +747,43 @@ static int steps_per_split4(int nst, int splits, int ks = 1)
     return (per + q - 1) / q * q;
 }
 
+// Tiling of one GEMM: token groups per workgroup tile (4 = 64 tokens, 2 = 32 tokens), the number of workgroups the
+// reduction is split over, and the halving inside a workgroup.  Cost model in microseconds, fitted to 3200 timings: both GEMMs
+// of 11 layers from 512 x 512 r = 200 to 28672 x 8192 r = 3520 at 10 batches from 16 to 2048, every tile with 1 .. 16 parts (the
+// choices are on average 0.3 % of a forward slower than the best of each, at most 11 %):
+//  - a reduction step of a 64-token workgroup takes 0.377 us when it has its CU to itself, 0.68 when two share it (two is all
+//    that fits), 0.654 where a workgroup of eight waves does two at once; of a 32-token workgroup 0.353 us alone, and a CU
+//    completes one per 0.255 us (up to four fit);
+//  - beside its steps a workgroup takes 9.5 us (64 tokens), 10.5 (eight waves), 6.9 (32 tokens): the first fetch and the epilogue;
+//  - splitting costs the finalize launch (2.8 us) and per part 0.23 us and the write and re-read of one set of fp32
+//    partial sums, 0.29 us per MB.
 struct GemmTiling { int tg, splits, ks; };
 static GemmTiling choose_tiling(int m_pad, int n_rb, int nst, int n_pad)
 {
     const int cus = device_cu_count();
     const int n_tiles = (n_rb + kPfWaves - 1) / kPfWaves;
-    const double partial_us = (double)m_pad * n_pad * 4.0 / 2.3e6;
+    const double partial_mb = (double)m_pad * n_pad * 4.0 / 1e6;
     GemmTiling best = {4, 1, 1};
     double best_cost = 1e30;
-    for (int tg = 4; tg >= 2; tg -= 2) {
-        const int wgs = (m_pad / (16 * tg)) * n_tiles;
-        const int per_cu = tg == 4 ? 2 : 4;
-        for (int s = 1; s <= 16; ++s) {
-            const int per = steps_per_split4(nst, s);
-            if (s > 1 && per < 8) break;
-            const int total = wgs * s;
-            // 32-token tiles were measured, and pay, only where they let an unsplit GEMM cover the chip
-            if (tg == 2 && (s > 1 || total > cus)) break;
-            // workgroups per CU in full rounds, then in the last, partial one
-            auto step_us = [&](int k) {
-                if (tg == 4) return k <= 1 ? 0.73 : 1.17;
-                return std::max(0.60, k / 3.9);
-            };
-            const int full = total / (per_cu * cus), rem = total % (per_cu * cus);
-            double cost = (double)full * per * step_us(per_cu);
-            if (rem) cost += per * step_us((rem + cus - 1) / cus);
-            if (s > 1) cost += 2.0 + s * partial_us;
-            if (cost < best_cost) { best_cost = cost; best = {tg, s, 1}; }
+    auto consider = [&](int tg, int splits, int ks) {
+        const int wgs = (m_pad / (16 * tg)) * n_tiles * splits, per = steps_per_split4(nst, splits, ks);
+        double cost;
+        if (ks == 2) {
+            cost = (wgs + cus - 1) / cus * (per / 2 * 0.654 + 10.5);
+        } else {
+            // full rounds of the CUs' slots, then the last, partial one
+            const int per_cu = tg == 4 ? 2 : 4, full = wgs / (per_cu * cus), rem = wgs % (per_cu * cus), k = (rem + cus - 1) / cus;
+            const double step_full = tg == 4 ? 0.68 : 4 * 0.255, step_rem = tg == 4 ? (k <= 1 ? 0.377 : 0.68) : std::max(0.353, k * 0.255);
+            const double fixed = tg == 4 ? 9.5 : 6.9;
+            cost = full * (per * step_full + fixed) + (rem ? per * step_rem + fixed : 0.0);
         }
-    }
-    // A long reduction whose 64-token tiles number no more than the CUs and that the model leaves
-    // unsplit, or splits no further than into one part per CU: eight-wave workgroups, one per CU,
-    // each halving its part of the reduction through LDS -- half the partial sums in memory, or none.
-    // Measured on the 70B MLP shapes: gemm 1 of the gate layer at 2048 tokens (224 tiles, 128 steps)
-    // 106 -> 99 us, of the down layer (224 tiles, 448 steps, split in two before) 300 -> 284 us
-    // including the finalize pass it no longer needs; gate layer at 1024 tokens (112 tiles, two
-    // parts per tile) 244 -> 213 us per forward, at 512 tokens (56 tiles, four parts) 115 -> 113 us.
-    const int wgs4 = (m_pad / 64) * n_tiles;
-    if (best.tg == 4 && wgs4 <= cus && nst % 8 == 0) {
-        const int s_fill = std::max(1, cus / wgs4);
-        // (a half of at least 16 steps; of 32 where the tile is not split otherwise: 28-step halves of
-        // an unsplit second GEMM measured 2 % slower than four-wave workgroups)
-        // and parts of equal length (three unequal parts of 128 steps at 768 tokens: 194 against 174 us
-        // per forward with four-wave workgroups)
-        if (best.splits <= 2 * s_fill && nst % (8 * s_fill) == 0 && nst / (2 * s_fill) >= (s_fill == 1 ? 32 : 16))
-            best = {4, s_fill, 2};
+        if (splits > 1) cost += 2.8 + splits * (0.23 + 0.29 * partial_mb);
+        if (cost < best_cost) { best_cost = cost; best = {tg, splits, ks}; }
+    };
+    for (int s = 1; s <= 16 && (s == 1 || steps_per_split4(nst, s) >= 4); ++s) {
+        consider(4, s, 1);
+        if (nst % 8 == 0) consider(4, s, 2);
+        if (s == 1) consider(2, 1, 1);
     }
     return best;
 }
@@ -777,39 +829,39 @@ size_t prefill_workspace_bytes(int64_t d_out, int64_t d_in, int64_t r, int batch
     return pf_layout(d_out, d_in, r, batch).total;
 }
 
-// columns [c0, c1) of every row of a [rows][ld] fp16 matrix := 0
-__global__ void __launch_bounds__(256)
-prefill_zero_cols_kernel(_Float16* __restrict__ m, int ld, int c0, int c1, int rows)
+template <int EPI>
+static void launch_gemm(const GemmArgs& a, int tg, int ks, hipStream_t s)
 {
-    const int w = c1 - c0;
-    const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (size_t)rows * w) return;
-    const int row = (int)(idx / w), col = c0 + (int)(idx % w);
-    m[(size_t)row * ld + col] = (_Float16)0.f;
+    const dim3 grid(a.m_tiles * a.n_tiles, a.splits), block(64 * kPfWaves * ks);
+    if (ks == 2) hipLaunchKernelGGL((prefill_gemm_kernel<EPI, 4, 2>), grid, block, 0, s, a);
+    else if (tg == 4) hipLaunchKernelGGL((prefill_gemm_kernel<EPI, 4, 1>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((prefill_gemm_kernel<EPI, 2, 1>), grid, block, 0, s, a);
 }
 
 template <int EPI>
 static int run_gemm(const GemmArgs& a, int tg, int ks, hipStream_t s)
 {
-    dim3 grid(a.m_tiles * a.n_tiles, a.splits);
     if (ks == 2 && (tg != 4 || a.nst % 8 != 0 || a.steps_per_split % 8 != 0)) {
         set_error("prefill: the in-workgroup split needs 64-token tiles and parts of whole groups of eight steps");
         return NQ_E_INVALID_ARG;
     }
     if (a.splits > 1) {
-        if (ks == 2) hipLaunchKernelGGL((prefill_gemm_kernel<EPI_PARTIAL, 4, 2>), grid, dim3(2 * kPfThreads), 0, s, a);
-        else if (tg == 4) hipLaunchKernelGGL((prefill_gemm_kernel<EPI_PARTIAL, 4>), grid, dim3(kPfThreads), 0, s, a);
-        else hipLaunchKernelGGL((prefill_gemm_kernel<EPI_PARTIAL, 2>), grid, dim3(kPfThreads), 0, s, a);
+        launch_gemm<EPI_PARTIAL>(a, tg, ks, s);
         NQ_HIP(hipGetLastError());
-        const size_t total = (size_t)a.m_pad * (a.n_pad / 4);
+        const size_t total = EPI == EPI_T ? (size_t)a.m_pad * (a.ldt / 16) : (size_t)a.m_pad * (a.n_pad / 4);
         hipLaunchKernelGGL((prefill_finalize_kernel<EPI>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, a);
     } else {
-        if (ks == 2) hipLaunchKernelGGL((prefill_gemm_kernel<EPI, 4, 2>), grid, dim3(2 * kPfThreads), 0, s, a);
-        else if (tg == 4) hipLaunchKernelGGL((prefill_gemm_kernel<EPI, 4>), grid, dim3(kPfThreads), 0, s, a);
-        else hipLaunchKernelGGL((prefill_gemm_kernel<EPI, 2>), grid, dim3(kPfThreads), 0, s, a);
+        launch_gemm<EPI>(a, tg, ks, s);
     }
     NQ_HIP(hipGetLastError());
     return NQ_OK;
+}
+
+// width of a pre-scale workgroup: as many threads as the row has chunks of 16 columns for kPreHeld of them each
+static int pre_threads(int lda)
+{
+    const int need = (lda / 16 + kPreHeld - 1) / kPreHeld;
+    return std::min(kPreThreads, std::max(64, (need + 63) / 64 * 64));
 }
 
 int launch_prefill(const PrefillArgs& p, hipStream_t s)
@@ -820,20 +872,20 @@ int launch_prefill(const PrefillArgs& p, hipStream_t s)
     _Float16* t = (_Float16*)(ws + L.off_t);
     float* tok_scale = (float*)(ws + L.off_scale);
     float* partial = (float*)(ws + L.off_partial);
-    // |x''| < 2^13, so |t''| < d_in * 2^13; g brings that to <= 2^15 (fp16 range 65504)
+    // |x''| < 2^13, so |t''| < d_in * 2^13; g brings that to <= 2^14, its pair sums to <= 2^15 (fp16 range 65504)
     int lg = 0;
     while (((int64_t)1 << lg) < p.d_in) ++lg;
     // (with a rank-wise scale, |s_mid| <= 2^mid_exp, T = X''V g s_mid stays within the same bound)
-    const float g_t = ldexpf(1.0f, -(lg > 2 ? lg - 2 : 0) - (p.s_mid ? p.mid_exp : 0));
+    const float g_t = ldexpf(1.0f, -(lg > 1 ? lg - 1 : 0) - (p.s_mid ? p.mid_exp : 0));
 
     if (p.x_dtype == NQ_F32)
-        hipLaunchKernelGGL(prefill_prescale_kernel<NQ_F32>, dim3(p.batch), dim3(kPreThreads), 0, s, p.x, p.s_in, (int)p.d_in,
+        hipLaunchKernelGGL(prefill_prescale_kernel<NQ_F32>, dim3(p.batch), dim3(pre_threads(L.k1)), 0, s, p.x, p.s_in, (int)p.d_in,
                            L.k1, g_t, xs, tok_scale);
     else if (p.x_dtype == NQ_F16)
-        hipLaunchKernelGGL(prefill_prescale_kernel<NQ_F16>, dim3(p.batch), dim3(kPreThreads), 0, s, p.x, p.s_in, (int)p.d_in,
+        hipLaunchKernelGGL(prefill_prescale_kernel<NQ_F16>, dim3(p.batch), dim3(pre_threads(L.k1)), 0, s, p.x, p.s_in, (int)p.d_in,
                            L.k1, g_t, xs, tok_scale);
     else
-        hipLaunchKernelGGL(prefill_prescale_kernel<NQ_BF16>, dim3(p.batch), dim3(kPreThreads), 0, s, p.x, p.s_in, (int)p.d_in,
+        hipLaunchKernelGGL(prefill_prescale_kernel<NQ_BF16>, dim3(p.batch), dim3(pre_threads(L.k1)), 0, s, p.x, p.s_in, (int)p.d_in,
                            L.k1, g_t, xs, tok_scale);
     NQ_HIP(hipGetLastError());
 
@@ -851,14 +903,6 @@ int launch_prefill(const PrefillArgs& p, hipStream_t s)
     a.m_tiles = L.m_pad / (16 * L.tg1);
     int rc = run_gemm<EPI_T>(a, L.tg1, L.ks1, s);
     if (rc != NQ_OK) return rc;
-    if (L.k2 > L.n1_pad) {
-        // columns of T beyond the last 128-row block of gemm1 are padding of gemm2's reduction:
-        // they must be exact zeros (the padded sign bits expand to -1, not to 0)
-        const size_t cnt = (size_t)L.m_pad * (L.k2 - L.n1_pad);
-        hipLaunchKernelGGL(prefill_zero_cols_kernel, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, t, L.k2,
-                           L.n1_pad, L.k2, L.m_pad);
-        NQ_HIP(hipGetLastError());
-    }
     // gemm2: y = T U^T
     a.act = t; a.lda = L.k2; a.tiles = p.u_tiles;
     a.y_out = p.y; a.y_dtype = p.y_dtype; a.tok_scale = tok_scale; a.out_scale = p.s_out;

@@ -1,0 +1,82 @@
+"""The dense path on pair sums and differences (sparse matrix instruction): activations of small integers with unit scales make
+every step of it exact, so the result must equal the integer product bit for bit -- a wrong pair, position, plane, lane or padding
+shows -- at the edges of pairs (8 columns), steps (64), row blocks (128), tiles of 32 and 64 tokens and their groups of
+four waves, and in every tiling; then odd row lengths in every type against the oracle, and values at the ends of fp32's range."""
+import numpy as np
+import pytest
+
+from paper_2602_06694_amd import binding as nq
+from paper_2602_06694_amd import synth
+from gpu_util import Layer, check_rounded, rel_err
+
+pytestmark = pytest.mark.gpu
+
+# x'' and T are rounded to fp16 (2^-11 relative each, as pair sums and differences; random signs): a few 1e-4 of the largest output
+PREFILL_TOL = 7e-4
+
+
+def unit_layer(d_out, d_in, r, x_dtype, y_dtype, seed):
+    ones = lambda n: np.ones(n, dtype=np.float16)
+    return Layer(d_out, d_in, r, x_dtype, y_dtype=y_dtype, data=synth.LayerData(
+        synth.LinearShape("t", d_out, d_in, r), synth.gen_sign_words(d_out, r, seed + 1), synth.gen_sign_words(d_in, r, seed + 2),
+        ones(d_out), ones(d_in)))
+
+
+def signs(words, r):
+    bits = np.unpackbits(np.ascontiguousarray(words).view(np.uint8), axis=1, bitorder="little")[:, :r]
+    return bits.astype(np.int64) * 2 - 1
+
+
+@pytest.mark.parametrize("d_out,d_in,r,batch", [
+    (1, 1, 1, 9), (5, 7, 3, 12), (130, 9, 17, 33), (127, 15, 64, 64), (128, 16, 65, 65), (129, 63, 127, 63), (64, 65, 129, 31),
+    (513, 257, 200, 100), (640, 1000, 385, 130), (1027, 511, 700, 70), (300, 2047, 520, 257)])
+@pytest.mark.parametrize("tg,splits,ks", [(None, None, None), (2, 1, 1), (4, 1, 1), (4, 3, 1), (4, 1, 2), (4, 2, 2)])
+def test_small_integers_are_exact(nqopt, d_out, d_in, r, batch, tg, splits, ks):
+    for name, v in (("pf_tg", tg), ("pf_splits", splits), ("pf_ks", ks)):
+        if v:
+            nqopt.set(name + "1", v)
+            nqopt.set(name + "2", v)
+    L = unit_layer(d_out, d_in, r, "f32", "f32", 8100 + r)
+    x = np.random.default_rng(8200 + batch).integers(-1, 2, (batch, d_in))
+    t = x @ signs(L.data.V_words, r)
+    assert 2 * np.abs(t).max() <= 2048                # pair sums of T are whole numbers that fp16 holds
+    y = L.forward(x.astype(np.float32))
+    assert np.array_equal(y, (t @ signs(L.data.U_words, r).T).astype(np.float32))
+    L.close()
+
+
+@pytest.mark.parametrize("d_out,d_in,r,batch", [(131, 33, 40, 21), (1001, 1503, 257, 70), (258, 4097, 300, 150)])
+@pytest.mark.parametrize("x_dtype,y_dtype", [("f32", "f16"), ("f16", "bf16"), ("bf16", "f32")])
+def test_odd_row_lengths(d_out, d_in, r, batch, x_dtype, y_dtype):
+    L = Layer(d_out, d_in, r, x_dtype, seed=8300 + r, y_dtype=y_dtype)
+    x = synth.gen_x(batch, d_in, 8400 + batch, x_dtype)
+    y, ref = L.forward(x), L.oracle(x)
+    assert np.isfinite(y).all()
+    if y_dtype == "f32":
+        assert rel_err(y, ref) <= PREFILL_TOL
+    else:
+        check_rounded(y, ref, y_dtype, PREFILL_TOL)
+    L.close()
+
+
+def test_values_at_the_ends_of_the_range():
+    """Tokens at the ends of the path's range keep their precision: the per-token power of two is clamped to 2^-100 .. 2^100, and
+    x'' has to stay within fp16 with its pair sums (2^16), so max|x'| < 2^115 / 2 (larger tokens give infinities and NaN);
+    infinities poison their own token only."""
+    d_out, d_in, r = 200, 300, 90
+    L = unit_layer(d_out, d_in, r, "f32", "f32", 8500)
+    L.close()
+    s_out = np.full(d_out, 2.0 ** -14, dtype=np.float16)
+    d = L.data
+    L = Layer(d_out, d_in, r, "f32", data=synth.LayerData(d.shape, d.U_words, d.V_words, s_out, d.s_in))
+    x = synth.gen_x(40, d_in, 8501, "f32")
+    x[3] *= np.float32(2.0 ** 113 / np.abs(x[3]).max())
+    x[4] *= np.float32(1e-30)
+    x[7, 5] = np.inf
+    y, ref = L.forward(x), L.oracle(np.where(np.isfinite(x), x, 0).astype(np.float32))
+    for b in range(40):
+        if b == 7:
+            assert not np.isfinite(y[b]).any()
+        else:
+            assert np.abs(y[b] - ref[b]).max() <= PREFILL_TOL * np.abs(ref[b]).max(), b
+    L.close()
