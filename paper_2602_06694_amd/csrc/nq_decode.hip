@@ -173,19 +173,20 @@ quantize_kernel(const QuantDesc* __restrict__ descs, QuantDesc single, int batch
 
     // pass 2: q = rint(v / step), split into three signed bytes, write the MFMA B-operand layout
     long long local_sum = 0;
-    uint4* const dst = (uint4*)(d.bq) + (size_t)tok * d.n_chunks * kSlices;     // token-major, pieces ordered by bq_piece()
+    uint4* const dst = (uint4*)(d.bq);
+    const int sp = bq_slice_pieces(d.grouped);
     if (held) {
 #pragma unroll
         for (int k = 0; k < kQuantHeld; ++k) {
             const int c = tid + k * kQuantThreads;
             if (c < d.n_chunks)
-                local_sum += quantize_chunk16<STREAMED>(hv[k], inv_step, bad, dst + bq_piece(c, 0));
+                local_sum += quantize_chunk16<STREAMED>(hv[k], inv_step, bad, dst + bq_chunk_piece(tok, c, d.n_chunks, d.grouped), sp);
         }
     } else {
         for (int c = tid; c < d.n_chunks; c += kQuantThreads) {
             float v[16];
             load_chunk16(d, base, c, vec, v);
-            local_sum += quantize_chunk16<STREAMED>(v, inv_step, bad, dst + bq_piece(c, 0));
+            local_sum += quantize_chunk16<STREAMED>(v, inv_step, bad, dst + bq_chunk_piece(tok, c, d.n_chunks, d.grouped), sp);
         }
     }
     double s = (double)local_sum;               // |sum| < 2^39: exact
@@ -253,11 +254,12 @@ quantize_wave_kernel(const QuantDesc* __restrict__ descs, QuantDesc single, int 
     const float inv_step = 1.0f / step;
 
     long long local_sum = 0;
-    uint4* const dst = (uint4*)(d.bq) + (size_t)tok * d.n_chunks * kSlices;
+    uint4* const dst = (uint4*)(d.bq);
+    const int sp = bq_slice_pieces(d.grouped);
 #pragma unroll
     for (int k = 0; k < H; ++k) {
         const int c = lane + 64 * k;
-        if (c < d.n_chunks) local_sum += quantize_chunk16<STREAMED>(hv[k], inv_step, bad != 0, dst + bq_piece(c, 0));
+        if (c < d.n_chunks) local_sum += quantize_chunk16<STREAMED>(hv[k], inv_step, bad != 0, dst + bq_chunk_piece(tok, c, d.n_chunks, d.grouped), sp);
     }
     double sum = (double)local_sum;
     for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
@@ -1594,23 +1596,68 @@ int launch_stage(const StageDesc* d_descs, const StageDesc& single, const WorkIt
 // ---------------------------------------------------------------------------------------------
 // out[j] = sum_b a[b][j] * b[b][j]: the reduction over the batch that turns an upstream gradient
 // and an unscaled product into the gradient of a scale vector (Section 3.4: the scales are tuned
-// with the packed signs frozen).  One thread per column, fp64 accumulation, one rounding.
+// with the packed signs frozen).  fp64 accumulation in a fixed order, one rounding.
+//
+// Bound by latency at real sizes (2 MB for 64 tokens of 4096 columns): a lane owns a column, the waves of a workgroup deal the
+// tokens out among themselves, four tokens' loads in flight per wave, and add their sums through LDS.  64 columns per workgroup,
+// so that 4096 columns are 64 workgroups of up to 16 waves.  One thread per column walking all tokens with one load pair in
+// flight took 33 us there; this takes 2.9.
 // ---------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256)
-scale_grad_kernel(const void* __restrict__ a, int a_dtype, const void* __restrict__ b, int b_dtype, int batch, int64_t n,
-                  float* __restrict__ out)
+constexpr int kSgWaves = 16, kSgUnroll = 4;
+
+template <int DT>
+__device__ __forceinline__ float load_typed(const void* p, size_t i)
 {
-    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (j >= n) return;
+    if (DT == NQ_F32) return ((const __attribute__((address_space(1))) float*)p)[i];
+    const uint16_t u = ((gptr_u16)p)[i];
+    return DT == NQ_F16 ? half_bits_to_float(u) : bf16_bits_to_float(u);
+}
+
+template <int DA, int DB>
+__global__ void __launch_bounds__(64 * kSgWaves)
+scale_grad_kernel(const void* __restrict__ a, const void* __restrict__ b, int batch, int64_t n, float* __restrict__ out)
+{
+    __shared__ double part[kSgWaves][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    const int64_t j = (int64_t)blockIdx.x * 64 + lane;
+    const size_t at = (size_t)(j < n ? j : n - 1);          // lanes past the end repeat the last column and store nothing
     double acc = 0.0;
-    for (int t = 0; t < batch; ++t)
-        acc += (double)load_as_float(a, a_dtype, (int64_t)t * n + j) * (double)load_as_float(b, b_dtype, (int64_t)t * n + j);
+    for (int t0 = wave; t0 < batch; t0 += waves * kSgUnroll) {
+        float va[kSgUnroll], vb[kSgUnroll];
+#pragma unroll
+        for (int k = 0; k < kSgUnroll; ++k) {
+            const int t = t0 + k * waves;
+            const size_t row = (size_t)(t < batch ? t : t0) * (size_t)n + at;
+            va[k] = load_typed<DA>(a, row);
+            vb[k] = load_typed<DB>(b, row);
+        }
+#pragma unroll
+        for (int k = 0; k < kSgUnroll; ++k)
+            if (t0 + k * waves < batch) acc = fma((double)va[k], (double)vb[k], acc);
+    }
+    part[wave][lane] = acc;
+    __syncthreads();
+    if (wave != 0 || j >= n) return;
+    for (int w = 1; w < waves; ++w) acc += part[w][lane];
     out[j] = (float)acc;
+}
+
+template <int DA>
+static void launch_scale_grad_a(const void* a, const void* b, int b_dtype, int batch, int64_t n, float* out, hipStream_t s)
+{
+    // (a wave for every kSgUnroll tokens, up to kSgWaves)
+    const int waves = std::min(kSgWaves, (batch + kSgUnroll - 1) / kSgUnroll);
+    const dim3 grid((unsigned)((n + 63) / 64)), block(64 * waves);
+    if (b_dtype == NQ_F32) hipLaunchKernelGGL((scale_grad_kernel<DA, NQ_F32>), grid, block, 0, s, a, b, batch, n, out);
+    else if (b_dtype == NQ_F16) hipLaunchKernelGGL((scale_grad_kernel<DA, NQ_F16>), grid, block, 0, s, a, b, batch, n, out);
+    else hipLaunchKernelGGL((scale_grad_kernel<DA, NQ_BF16>), grid, block, 0, s, a, b, batch, n, out);
 }
 
 int launch_scale_grad(const void* a, int a_dtype, const void* b, int b_dtype, int batch, int64_t n, float* out, hipStream_t s)
 {
-    hipLaunchKernelGGL(scale_grad_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a, a_dtype, b, b_dtype, batch, n, out);
+    if (a_dtype == NQ_F32) launch_scale_grad_a<NQ_F32>(a, b, b_dtype, batch, n, out, s);
+    else if (a_dtype == NQ_F16) launch_scale_grad_a<NQ_F16>(a, b, b_dtype, batch, n, out, s);
+    else launch_scale_grad_a<NQ_BF16>(a, b, b_dtype, batch, n, out, s);
     NQ_HIP(hipGetLastError());
     return NQ_OK;
 }

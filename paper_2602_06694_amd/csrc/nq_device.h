@@ -96,7 +96,7 @@ __device__ __forceinline__ uint32_t pack_low_bytes(uint32_t a, uint32_t b, uint3
 // q = 65536 hi + 256 mid + lo with signed bytes: lo is the (sign-extended) low byte of q,
 // mid that of q1 = (q - lo) / 256 = (q + 128) >> 8, hi = (q1 + 128) >> 8; only the low bytes are kept
 template <bool STREAMED = false>
-__device__ inline long long quantize_chunk16(const float v[16], float inv_step, bool bad, uint4* dst)
+__device__ inline long long quantize_chunk16(const float v[16], float inv_step, bool bad, uint4* dst, int slice_pieces = 4)
 {
     uint32_t hi[4], mid[4], lo[4];
     int sum = 0;                                            // |q| <= 2^22, 16 of them: fits
@@ -122,12 +122,12 @@ __device__ inline long long quantize_chunk16(const float v[16], float inv_step, 
         // a buffer in global memory that the next launch reads: written around the cache
         typedef __attribute__((address_space(1))) v4u* gptr_wv4u;
         __builtin_nontemporal_store(v4u{hi[0], hi[1], hi[2], hi[3]}, (gptr_wv4u)dst);
-        __builtin_nontemporal_store(v4u{mid[0], mid[1], mid[2], mid[3]}, (gptr_wv4u)dst + 4);
-        __builtin_nontemporal_store(v4u{lo[0], lo[1], lo[2], lo[3]}, (gptr_wv4u)dst + 8);
+        __builtin_nontemporal_store(v4u{mid[0], mid[1], mid[2], mid[3]}, (gptr_wv4u)dst + slice_pieces);
+        __builtin_nontemporal_store(v4u{lo[0], lo[1], lo[2], lo[3]}, (gptr_wv4u)dst + 2 * slice_pieces);
     } else {
         dst[0] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-        dst[4] = make_uint4(mid[0], mid[1], mid[2], mid[3]);
-        dst[8] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+        dst[slice_pieces] = make_uint4(mid[0], mid[1], mid[2], mid[3]);
+        dst[2 * slice_pieces] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
     }
     return sum;
 }

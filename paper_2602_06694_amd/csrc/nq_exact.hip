@@ -7,31 +7,41 @@
 // 3 KiB of fixed point, both from L2 (the tiles of a layer of a few MB are read once per group of 16 tokens, and stay there).
 // Eight waves of a workgroup split the reduction of one (row block, 16 tokens) result: at the sizes of real layers row blocks
 // and token groups alone leave most of the chip idle.
-// 64 tokens of a 4096 x 4096 r = 1024 layer: 26 us (four launches of 4 to 12 us, bound by latency) where passes of eight tokens
+// 64 tokens of a 4096 x 4096 r = 1024 layer: 20 us (four launches of 4 to 8 us, bound by latency) where passes of eight tokens
 // took 32 launches and 185 us.
 #include "nq_internal.h"
 #include "nq_device.h"
 
 namespace nq {
 
-constexpr int kXWaves = 8, kXTokens = 16, kXRing = 4;
+constexpr int kXWaves = 8, kXTokens = 16;
 
-// grid = (row blocks, token groups), block = 512
+// grid = (row blocks x 8 / PL, token groups), block = 512.  PL = bit planes (16 rows each) a workgroup takes of its row block's
+// eight: where row blocks and token groups are few, several workgroups read the same tiles and finish fewer rows each.
+template <int PL>
 __global__ void __launch_bounds__(64 * kXWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) stage_exact_kernel(StageDesc d, int batch)
 {
-    __shared__ v4i red[kXWaves][8][64];
+    constexpr int kXRing = 4;                                       // steps in flight per wave
+    constexpr int kRound = PL <= 2 ? kSlices : 1;                   // slices whose partial sums pass through LDS at a time
+    __shared__ v4i red[kRound][kXWaves][PL][64];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int g = lane >> 4, n = lane & 15;
-    const int rb = blockIdx.x, t0 = blockIdx.y * kXTokens;
+    const int rb = blockIdx.x / (8 / PL), p0 = blockIdx.x % (8 / PL) * PL, t0 = blockIdx.y * kXTokens;
     const int tok = t0 + n < batch ? t0 + n : batch - 1;            // a column past the batch repeats the last token and is not stored
     const char* w_base = (const char*)(d.tiles + (size_t)rb * d.n_steps * kTileWords) + 16 * lane;
-    const char* b_base = (const char*)d.bq + (size_t)tok * d.n_steps * kBqStepBytes + 16 * g;
-    v4i acc[kSlices][8];
+    const char* b_base = (const char*)d.bq + (size_t)blockIdx.y * d.n_steps * kGroupStepBytes + 64 * n + 16 * g;
+    // (what the epilogue needs is requested before the reduction, not behind it)
+    const int row0 = rb * kTileRows + 16 * (p0 + wave % PL) + 4 * g;
+    const QMeta mt = d.meta[tok];
+    float osc[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) osc[v] = d.out_scale ? half_bits_to_float(((gptr_u16)d.out_scale)[row0 + v < d.M ? row0 + v : 0]) : 1.0f;
+    v4i acc[kSlices][PL];
 #pragma unroll
     for (int s = 0; s < kSlices; ++s)
 #pragma unroll
-        for (int p = 0; p < 8; ++p) acc[s][p] = v4i{0, 0, 0, 0};
+        for (int p = 0; p < PL; ++p) acc[s][p] = v4i{0, 0, 0, 0};
     // steps wave, wave + 8, ...; past the end the last step is read again and not used
     const int last = d.n_steps - 1;
     v4u w[kXRing], b[kXRing][kSlices];
@@ -40,19 +50,20 @@ __global__ void __launch_bounds__(64 * kXWaves) __attribute__((amdgpu_waves_per_
         const uint32_t ss = (uint32_t)((step) < last ? (step) : last);                                  \
         w[k] = load_global_v4u(w_base, ss * (kTileWords * 4));                                          \
         _Pragma("unroll") for (int s = 0; s < kSlices; ++s)                                             \
-            b[k][s] = load_global_v4u(b_base, ss * kBqStepBytes + 64 * s);                              \
+            b[k][s] = load_global_v4u(b_base, ss * kGroupStepBytes + 1024 * s);                            \
     } while (0)
 #define NQ_X_MAC(k)                                                                                     \
     do {                                                                                                \
-        _Pragma("unroll") for (int p = 0; p < 8; ++p) {                                                 \
-            const v4i a = (v4i)(w[k] & (0x01010101u << p));                                             \
+        const v4u wk = PL == 8 ? w[k] : w[k] >> (uint32_t)p0;                                           \
+        _Pragma("unroll") for (int p = 0; p < PL; ++p) {                                                \
+            const v4i a = (v4i)(wk & (0x01010101u << p));                                               \
             _Pragma("unroll") for (int s = 0; s < kSlices; ++s)                                         \
                 acc[s][p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, (v4i)b[k][s], acc[s][p], 0, 0, 0); \
         }                                                                                               \
     } while (0)
 #pragma unroll
     for (int k = 0; k < kXRing; ++k) {
-        NQ_X_ISSUE(k, wave + k * kXWaves);
+        if (k == 0 || wave + k * kXWaves <= last) NQ_X_ISSUE(k, wave + k * kXWaves);
         __builtin_amdgcn_sched_barrier(0);
     }
     int st = wave;
@@ -70,30 +81,36 @@ __global__ void __launch_bounds__(64 * kXWaves) __attribute__((amdgpu_waves_per_
 #undef NQ_X_ISSUE
 #undef NQ_X_MAC
 
-    // the partial sums of the eight waves, one slice per round through 64 KiB of LDS; wave p takes bit plane p
+    // the partial sums of the eight waves, through LDS; wave p takes bit plane p0 + p.  (A plane below 7 of a shifted word is
+    // worth 2^p, bit 7 of a byte 2^7 with a minus: int8)
     v4i sum[kSlices];
 #pragma unroll
-    for (int s = 0; s < kSlices; ++s) {
-        if (s) __syncthreads();
+    for (int s0 = 0; s0 < kSlices; s0 += kRound) {
+        if (s0) __syncthreads();
 #pragma unroll
-        for (int p = 0; p < 8; ++p) red[wave][p][lane] = acc[s][p];
+        for (int s = 0; s < kRound; ++s)
+#pragma unroll
+            for (int p = 0; p < PL; ++p) red[s][wave][p][lane] = acc[s0 + s][p];
         __syncthreads();
-        sum[s] = v4i{0, 0, 0, 0};
+        if (wave < PL) {
 #pragma unroll
-        for (int k = 0; k < kXWaves; ++k) sum[s] += red[k][wave][lane];
-        if (wave == 7) sum[s] = -sum[s];                            // plane 7 is the int8 sign bit: it sums -128 b q
+            for (int s = 0; s < kRound; ++s) {
+                sum[s0 + s] = v4i{0, 0, 0, 0};
+#pragma unroll
+                for (int k = 0; k < kXWaves; ++k) sum[s0 + s] += red[s][k][wave][lane];
+                if (PL == 8 && wave == 7) sum[s0 + s] = -sum[s0 + s];
+            }
+        }
     }
-    if (t0 + n >= batch) return;
+    if (wave >= PL || t0 + n >= batch) return;
     // lane (g, n), register v: row 16 plane + 4 g + v, token n; joined and rounded as in the decode kernels' epilogue
-    const int row0 = rb * kTileRows + 16 * wave + 4 * g;
-    const QMeta mt = d.meta[tok];
     const double scale_p = __builtin_ldexp(mt.two_step, -wave);
     float r[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const double raw = fma((double)sum[0][v], 65536.0, fma((double)sum[1][v], 256.0, (double)sum[2][v]));
         const float z = (float)fma(raw, scale_p, mt.neg_qs);
-        r[v] = z * (d.out_scale && row0 + v < d.M ? half_bits_to_float(((gptr_u16)d.out_scale)[row0 + v]) : 1.0f);
+        r[v] = z * osc[v];
     }
     const size_t at = (size_t)tok * d.out_stride + row0;
     if (d.out_dtype == NQ_F32 && (d.out_stride & 3) == 0 && row0 + 4 <= d.M) {
@@ -107,8 +124,16 @@ __global__ void __launch_bounds__(64 * kXWaves) __attribute__((amdgpu_waves_per_
 
 int launch_stage_exact(const StageDesc& d, int batch, hipStream_t s)
 {
-    hipLaunchKernelGGL(stage_exact_kernel, dim3((unsigned)n_rowblocks(d.M), (unsigned)((batch + kXTokens - 1) / kXTokens)),
-                       dim3(64 * kXWaves), 0, s, d, batch);
+    const int n_rb = (int)n_rowblocks(d.M), groups = (batch + kXTokens - 1) / kXTokens;
+    // whole row blocks where they give every second CU a workgroup; below that halves and quarters of them, until they do (a
+    // 4096 x 4096 r = 1024 layer at 64 tokens, 32 and 128 pairs of row block and group: quarters 12.1 -> 7.7 us, halves 6.7 -> 4.7;
+    // with the transposed product's rule the gradients of that layer 70.2 -> 66.1 us)
+    int pl = 8;
+    while (pl > 2 && n_rb * groups * (8 / pl) <= device_cu_count() / 2) pl /= 2;
+    const dim3 grid((unsigned)(n_rb * (8 / pl)), (unsigned)groups), block(64 * kXWaves);
+    if (pl == 8) hipLaunchKernelGGL(stage_exact_kernel<8>, grid, block, 0, s, d, batch);
+    else if (pl == 4) hipLaunchKernelGGL(stage_exact_kernel<4>, grid, block, 0, s, d, batch);
+    else hipLaunchKernelGGL(stage_exact_kernel<2>, grid, block, 0, s, d, batch);
     NQ_HIP(hipGetLastError());
     return NQ_OK;
 }

@@ -33,6 +33,15 @@ constexpr int kSlices = 3;
 // reduction indices): a 64-column step = 4 chunks = 12 pieces, ordered slice-major inside the step.
 __host__ __device__ inline int bq_piece(int chunk, int slice) { return (chunk >> 2) * 12 + slice * 4 + (chunk & 3); }
 
+constexpr uint32_t kGroupStepBytes = 3 * 16 * 64;      // a step of a group of 16 tokens in the grouped order
+// the first of a chunk's pieces (16 bytes) in `bq`, and the distance to the next slice's
+__host__ __device__ inline size_t bq_chunk_piece(int tok, int chunk, int n_chunks, int grouped)
+{
+    return grouped ? ((size_t)(tok >> 4) * (n_chunks >> 2) + (chunk >> 2)) * (kGroupStepBytes / 16) + (tok & 15) * 4 + (chunk & 3)
+                   : (size_t)tok * n_chunks * kSlices + bq_piece(chunk, 0);
+}
+__host__ __device__ inline int bq_slice_pieces(int grouped) { return grouped ? 64 : 4; }
+
 // Per token, written by the quantisation: with step the token's power-of-two quantisation step and
 // sum_q = sum_j q_j, a stage output is  (2 sum_n b_n q_n - sum_q) step = fma(sum_n b_n q_n, two_step, neg_qs).
 // Both constants are exact (scalings of an exact integer by a power of two); two_step is NaN when
@@ -52,6 +61,7 @@ struct QuantDesc {
     int x_stride;            // elements between tokens
     int dtype;               // NQ_F32 / NQ_F16 / NQ_BF16
     int mag_exp;             // |q| <= 2^mag_exp: 22 (three byte slices; also when 0) or 14 (the top slice stays zero)
+    int grouped;             // 1: bq is [groups of 16 tokens][n_steps][3 slices][16 tokens][4 chunks][16] (nq_exact.hip)
 };
 
 struct StageDesc {

@@ -16,6 +16,8 @@
 // one rounding to fp32 when a result is stored: the error against binary64 stays that of the one rounding (3.6e-8 of the
 // result's norm on normal data, as with binary64 additions on the vector ALU, which this replaces: a gradient pass of 64
 // tokens through a 4096 x 4096 r = 1024 layer took 235 us in passes of 8 tokens, 16 launches of 2 to 12 us).
+#include <algorithm>
+
 #include "nq_internal.h"
 #include "nq_device.h"
 
@@ -24,7 +26,9 @@ namespace nq {
 constexpr int kTSlices = 4;
 constexpr int kTWaves = 8;              // waves of a workgroup share one (64 columns, 16 tokens) result: they split its row blocks
 constexpr int kTTokens = 16;            // tokens of a workgroup: the 16 columns of one matrix instruction, one slice at a time
-constexpr uint32_t kTRbBytes = 2 * kTSlices * 64;       // a token's fixed-point bytes per 128-row block: [half][slice][4 pieces][16]
+// the fixed-point bytes of a group of 16 tokens per 128-row block, [half][slice][token][4 pieces][16]: what one load instruction
+// of the product kernel fetches is 1 KiB in one piece
+constexpr uint32_t kTGroupRbBytes = 2 * kTSlices * 16 * 64;
 
 // ---------------------------------------------------------------------------------------------
 // scaled input -> fixed point.  One workgroup per token.  A thread owns pieces: piece (s, c) of a token holds, as four words
@@ -33,52 +37,67 @@ constexpr uint32_t kTRbBytes = 2 * kTSlices * 64;       // a token's fixed-point
 struct TQuantArgs {
     const void* in;             // [batch][in_stride] of in_dtype
     const uint16_t* scale;      // fp16 [M] or nullptr
-    uint8_t* bq;                // [batch][n_pieces / 4][slices][4][16]
+    uint8_t* bq;                // [groups of 16 tokens][n_pieces / 4][slices][16 tokens][4][16]
     QMeta* meta;                // [batch]
     int M, in_dtype, in_stride;
     int n_pieces;               // 4 per 64 rows, whole row blocks
 };
 
-// the 16 scaled values of piece `pc`; binary64: an fp32 value times an fp16 scale is exact
-__device__ __forceinline__ void tq_load(const TQuantArgs& a, size_t base, int pc, bool vec, double v[16])
+// the 16 scaled values of piece `pc`; binary64: an fp32 value times an fp16 scale is exact.  (DT = the type of the input: all of a
+// piece's loads are requested before the first is converted)
+template <int DT>
+__device__ __forceinline__ void tq_load(const TQuantArgs& a, size_t base, int pc, double v[16])
 {
+    typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+    typedef v4f v4f_any __attribute__((aligned(4)));       // rows of odd lengths: 16 and 8 bytes at the alignment of an element
+    typedef v2u v2u_any __attribute__((aligned(2)));
     const int r0 = (pc >> 2) * 64 + 4 * (pc & 3);
+    if (r0 + 52 <= a.M) {                                   // whole pieces: no branch around a load
+        v4f xf[4];
+        v2u xh[4], sc[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = r0 + 16 * i;
-        float f[4] = {0.f, 0.f, 0.f, 0.f}, sc[4] = {1.f, 1.f, 1.f, 1.f};
-        if (vec && r + 4 <= a.M) {
-            if (a.in_dtype == NQ_F32) {
-                const v4f t = *(gptr_v4f)((const float*)a.in + base + r);
-                f[0] = t.x; f[1] = t.y; f[2] = t.z; f[3] = t.w;
-            } else {
-                typedef unsigned int v2u __attribute__((ext_vector_type(2)));
-                const v2u t = *(const __attribute__((address_space(1))) v2u*)((const uint16_t*)a.in + base + r);
-                const uint16_t h[4] = {(uint16_t)(t.x & 0xFFFFu), (uint16_t)(t.x >> 16), (uint16_t)(t.y & 0xFFFFu), (uint16_t)(t.y >> 16)};
-#pragma unroll
-                for (int k = 0; k < 4; ++k) f[k] = a.in_dtype == NQ_F16 ? half_bits_to_float(h[k]) : bf16_bits_to_float(h[k]);
-            }
-            if (a.scale) {
-                typedef unsigned int v2u __attribute__((ext_vector_type(2)));
-                const v2u t = *(const __attribute__((address_space(1))) v2u*)(a.scale + r);
-                sc[0] = half_bits_to_float((uint16_t)(t.x & 0xFFFFu)); sc[1] = half_bits_to_float((uint16_t)(t.x >> 16));
-                sc[2] = half_bits_to_float((uint16_t)(t.y & 0xFFFFu)); sc[3] = half_bits_to_float((uint16_t)(t.y >> 16));
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if (r + k < a.M) {                          // rows beyond M are padding: zeros
-                    f[k] = load_as_float(a.in, a.in_dtype, (int64_t)(base + r + k));
-                    if (a.scale) sc[k] = half_bits_to_float(a.scale[r + k]);
-                }
-            }
+        for (int i = 0; i < 4; ++i) {
+            const int r = r0 + 16 * i;
+            if (DT == NQ_F32) xf[i] = *(const __attribute__((address_space(1))) v4f_any*)((const float*)a.in + base + r);
+            else xh[i] = *(const __attribute__((address_space(1))) v2u_any*)((const uint16_t*)a.in + base + r);
+            if (a.scale) sc[i] = *(const __attribute__((address_space(1))) v2u*)(a.scale + r);
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v[4 * i + k] = (double)f[k] * (double)sc[k];
+        for (int i = 0; i < 4; ++i) {
+            float f[4];
+            if (DT == NQ_F32) {
+                f[0] = xf[i].x; f[1] = xf[i].y; f[2] = xf[i].z; f[3] = xf[i].w;
+            } else {
+                const uint16_t h[4] = {(uint16_t)(xh[i].x & 0xFFFFu), (uint16_t)(xh[i].x >> 16), (uint16_t)(xh[i].y & 0xFFFFu), (uint16_t)(xh[i].y >> 16)};
+#pragma unroll
+                for (int k = 0; k < 4; ++k) f[k] = DT == NQ_F16 ? half_bits_to_float(h[k]) : bf16_bits_to_float(h[k]);
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[4 * i + k] = (double)f[k];
+            if (a.scale) {
+                v[4 * i] *= (double)half_bits_to_float((uint16_t)(sc[i].x & 0xFFFFu));
+                v[4 * i + 1] *= (double)half_bits_to_float((uint16_t)(sc[i].x >> 16));
+                v[4 * i + 2] *= (double)half_bits_to_float((uint16_t)(sc[i].y & 0xFFFFu));
+                v[4 * i + 3] *= (double)half_bits_to_float((uint16_t)(sc[i].y >> 16));
+            }
+        }
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int r = r0 + 16 * i + k;
+            v[4 * i + k] = 0.0;                             // rows beyond M are padding: zeros
+            if (r < a.M) {
+                v[4 * i + k] = (double)load_as_float(a.in, DT, (int64_t)(base + r));
+                if (a.scale) v[4 * i + k] *= (double)half_bits_to_float(a.scale[r]);
+            }
+        }
     }
 }
 
-// q of 16 values -> the four slices of their piece (slices 64 bytes apart); returns sum q
+// q of 16 values -> the four slices of their piece (slices 1 KiB apart); returns sum q
 __device__ __forceinline__ long long tq_store(const double v[16], double inv_step, bool bad, uint8_t* dst)
 {
     long long sum = 0;
@@ -100,25 +119,25 @@ __device__ __forceinline__ long long tq_store(const double v[16], double inv_ste
         for (int s = 0; s < kTSlices; ++s) w[s][i] = pack_low_bytes(d[s][0], d[s][1], d[s][2], d[s][3]);
     }
 #pragma unroll
-    for (int s = 0; s < kTSlices; ++s) *(uint4*)(dst + s * 64) = make_uint4(w[s][0], w[s][1], w[s][2], w[s][3]);
+    for (int s = 0; s < kTSlices; ++s) *(uint4*)(dst + s * 1024) = make_uint4(w[s][0], w[s][1], w[s][2], w[s][3]);
     return sum;
 }
 
-constexpr int kTQThreads = 512;
+constexpr int kTQThreads = 512;         // most threads of a workgroup; short vectors take as many as they have pieces
 
+template <int DT>
 __global__ void __launch_bounds__(kTQThreads) quantize_t_kernel(TQuantArgs a)
 {
     __shared__ double sm_max[kTQThreads / 64], sm_sum[kTQThreads / 64];
     __shared__ int sm_bad[kTQThreads / 64];
-    const int tok = blockIdx.x, tid = threadIdx.x, wave = tid >> 6;
+    const int tok = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, threads = blockDim.x;
     const size_t base = (size_t)tok * a.in_stride;
-    const bool vec = (a.in_stride & 3) == 0;                // groups of four elements start 8- (16-bit) or 16-byte (fp32) aligned
     double v[16], m = 0.0;
     int bad = 0;
     // (a thread's first piece stays in registers between the two passes; longer vectors re-read the others)
-    for (int pc = tid + ((a.n_pieces - 1 - tid) / kTQThreads) * kTQThreads; pc >= 0; pc -= kTQThreads) {
+    for (int pc = tid + ((a.n_pieces - 1 - tid) / threads) * threads; pc >= 0; pc -= threads) {
         if (pc >= a.n_pieces) break;
-        tq_load(a, base, pc, vec, v);
+        tq_load<DT>(a, base, pc, v);
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const double t = fabs(v[i]);
@@ -133,23 +152,23 @@ __global__ void __launch_bounds__(kTQThreads) quantize_t_kernel(TQuantArgs a)
     m = sm_max[0];
     bad = sm_bad[0];
 #pragma unroll
-    for (int w = 1; w < kTQThreads / 64; ++w) { m = fmax(m, sm_max[w]); bad |= sm_bad[w]; }
+    for (int w = 1; w < threads / 64; ++w) { m = fmax(m, sm_max[w]); bad |= sm_bad[w]; }
     // step = 2^(e - 30) with m = f 2^e, f in [0.5, 1): |q| <= 2^30
     int e = 0;
     if (m > 0.0 && !bad) (void)frexp(m, &e);
     const double step = ldexp(1.0, e - 30), inv_step = ldexp(1.0, 30 - e);
     double s = 0.0;
-    uint8_t* const dst = a.bq + (size_t)tok * a.n_pieces * (kTSlices * 16);
-    for (int pc = tid; pc < a.n_pieces; pc += kTQThreads) {
-        if (pc != tid) tq_load(a, base, pc, vec, v);
-        s += (double)tq_store(v, inv_step, bad != 0, dst + (size_t)(pc >> 2) * (kTSlices * 64) + (pc & 3) * 16);
+    uint8_t* const dst = a.bq + (size_t)(tok >> 4) * (a.n_pieces >> 2) * (kTGroupRbBytes / 2) + (tok & 15) * 64;
+    for (int pc = tid; pc < a.n_pieces; pc += threads) {
+        if (pc != tid) tq_load<DT>(a, base, pc, v);
+        s += (double)tq_store(v, inv_step, bad != 0, dst + (size_t)(pc >> 2) * (kTGroupRbBytes / 2) + (pc & 3) * 16);
     }
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);        // below 2^46: exact
     if ((tid & 63) == 0) sm_sum[wave] = s;
     __syncthreads();
     if (tid == 0) {
         double tot = 0.0;
-        for (int w = 0; w < kTQThreads / 64; ++w) tot += sm_sum[w];
+        for (int w = 0; w < threads / 64; ++w) tot += sm_sum[w];
         QMeta mt;
         mt.two_step = bad ? (double)__builtin_nanf("") : 2.0 * step;
         mt.neg_qs = -tot * step;
@@ -159,7 +178,8 @@ __global__ void __launch_bounds__(kTQThreads) quantize_t_kernel(TQuantArgs a)
 
 // ---------------------------------------------------------------------------------------------
 // out[tok][col] = out_scale[col] * sum_row sign(row, col) v[tok][row], 64 columns x 16 tokens per workgroup
-// grid = (64-column steps, token groups), block = 512
+// grid = (64-column steps x 4 / NV, token groups), block = 512.  NV = words of a tile's lane that a workgroup takes of the four,
+// i.e. 16 NV of the 64 columns: where columns and token groups are few, two workgroups share a tile.
 // ---------------------------------------------------------------------------------------------
 struct TStageArgs {
     const uint32_t* tiles;
@@ -182,38 +202,49 @@ __device__ __forceinline__ uint32_t quad_transpose(uint32_t w, uint32_t sel2, ui
 // Bound: instruction issue and latency, not memory (a tile meets 16 tokens, so 1 KiB costs 512 matrix-core cycles of one
 // SIMD).  Eight waves per workgroup because at the row counts of real layers (8 to 224 row blocks) a result's reduction is the
 // only thing left to spread over the chip once columns and tokens have been.
+template <int NV>
 __global__ void __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) gemm_t_kernel(TStageArgs a)
 {
-    __shared__ v4i red[2][kTWaves][4][64];
+    constexpr int kRing = 2;                                        // tiles in flight per wave
+    constexpr int kRound = NV == 4 ? 2 : kTSlices;                  // slices whose partial sums pass through LDS at a time
+    __shared__ v4i red[kRound][kTWaves][NV][64];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int g = lane >> 4, n = lane & 15;
-    const int st = blockIdx.x, t0 = blockIdx.y * kTTokens;
+    const int st = blockIdx.x / (4 / NV), v0 = blockIdx.x % (4 / NV) * NV, t0 = blockIdx.y * kTTokens;
     const int tok = t0 + n < a.batch ? t0 + n : a.batch - 1;        // a column past the batch repeats the last token and is not stored
     const int tile_lane = (lane & 3) | ((lane >> 4) & 3) << 2 | ((lane >> 2) & 3) << 4;
     const uint32_t sel2 = lane & 2 ? 0x03020706u : 0x05040100u, sel1 = lane & 1 ? 0x03070105u : 0x06020400u;
-    const char* w_base = (const char*)(a.tiles + (size_t)st * kTileWords) + 16 * tile_lane;
+    const char* w_base = (const char*)(a.tiles + (size_t)st * kTileWords) + 16 * tile_lane + 4 * v0;
     const size_t w_rb = (size_t)a.n_steps * (kTileWords * 4);
-    const char* b_base = (const char*)a.bq + (size_t)tok * a.n_rb * kTRbBytes + 16 * g;
-    v4i acc[4][kTSlices];
+    const char* b_base = (const char*)a.bq + (size_t)blockIdx.y * a.n_rb * kTGroupRbBytes + 64 * n + 16 * g;
+    // (what the epilogue needs is requested before the reduction, not behind it)
+    const int col = st * kTileCols + 16 * g + 4 * (v0 + wave % NV);
+    const double two_step = a.meta[tok].two_step, neg_qs = a.meta[tok].neg_qs;
+    float osc[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
+    for (int k = 0; k < 4; ++k) osc[k] = a.out_scale ? half_bits_to_float(a.out_scale[col + k < a.N ? col + k : 0]) : 1.0f;
+    v4i acc[NV][kTSlices];
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
 #pragma unroll
         for (int s = 0; s < kTSlices; ++s) acc[v][s] = v4i{0, 0, 0, 0};
-    // two tiles in flight; past the end the last one is read again and not used
+    // past the end the last tile is read again and not used
     const int last = a.n_rb - 1;
-    v4u w[2], b[2][2][kTSlices];
+    typedef unsigned int vNu __attribute__((ext_vector_type(NV)));
+    vNu w[kRing];
+    v4u b[kRing][2][kTSlices];
 #define NQ_T_ISSUE(k, rb)                                                                                   \
     do {                                                                                                    \
         const int rr = (rb) < last ? (rb) : last;                                                           \
-        w[k] = load_global_v4u(w_base + (size_t)rr * w_rb, 0);                                              \
+        w[k] = *(const __attribute__((address_space(1))) vNu*)(w_base + (size_t)rr * w_rb);                 \
         _Pragma("unroll") for (int h = 0; h < 2; ++h)                                                       \
             _Pragma("unroll") for (int s = 0; s < kTSlices; ++s)                                            \
-                b[k][h][s] = load_global_v4u(b_base + (size_t)rr * kTRbBytes, (uint32_t)((h * kTSlices + s) * 64)); \
+                b[k][h][s] = load_global_v4u(b_base + (size_t)rr * kTGroupRbBytes, (uint32_t)((h * kTSlices + s) * 1024)); \
     } while (0)
 #define NQ_T_MAC(k)                                                                                         \
     do {                                                                                                    \
-        _Pragma("unroll") for (int v = 0; v < 4; ++v) {                                                     \
+        _Pragma("unroll") for (int v = 0; v < NV; ++v) {                                                    \
             const uint32_t t = quad_transpose(w[k][v], sel2, sel1);                                         \
             _Pragma("unroll") for (int h = 0; h < 2; ++h) {                                                 \
                 v4u op;                                                                                     \
@@ -223,46 +254,47 @@ __global__ void __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_
             }                                                                                               \
         }                                                                                                   \
     } while (0)
-    NQ_T_ISSUE(0, wave);
-    __builtin_amdgcn_sched_barrier(0);
-    NQ_T_ISSUE(1, wave + kTWaves);
-    __builtin_amdgcn_sched_barrier(0);
-    int rb = wave;
-    for (; rb + kTWaves < a.n_rb; rb += 2 * kTWaves) {
-        NQ_T_MAC(0);
-        NQ_T_ISSUE(0, rb + 2 * kTWaves);
-        __builtin_amdgcn_sched_barrier(0);
-        NQ_T_MAC(1);
-        NQ_T_ISSUE(1, rb + 3 * kTWaves);
+#pragma unroll
+    for (int k = 0; k < kRing; ++k) {
+        if (k == 0 || wave + k * kTWaves <= last) NQ_T_ISSUE(k, wave + k * kTWaves);
         __builtin_amdgcn_sched_barrier(0);
     }
-    if (rb < a.n_rb) NQ_T_MAC(0);
+    int rb = wave;
+    for (; rb + (kRing - 1) * kTWaves < a.n_rb; rb += kRing * kTWaves) {
+#pragma unroll
+        for (int k = 0; k < kRing; ++k) {
+            NQ_T_MAC(k);
+            NQ_T_ISSUE(k, rb + (k + kRing) * kTWaves);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < kRing - 1; ++k)
+        if (rb + k * kTWaves < a.n_rb) NQ_T_MAC(k);
 #undef NQ_T_ISSUE
 #undef NQ_T_MAC
 
-    // the eight partial sums of every result, two slices per round through 64 KiB of LDS; wave v of the first four takes word v
+    // the eight partial sums of every result, through 64 KiB of LDS; wave v of the first NV takes word v0 + v
     v4i sum[kTSlices];
 #pragma unroll
     for (int s = 0; s < kTSlices; ++s) sum[s] = v4i{0, 0, 0, 0};
 #pragma unroll
-    for (int round = 0; round < kTSlices / 2; ++round) {
-        if (round) __syncthreads();
+    for (int s0 = 0; s0 < kTSlices; s0 += kRound) {
+        if (s0) __syncthreads();
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+        for (int s = 0; s < kRound; ++s)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) red[s][wave][v][lane] = acc[v][2 * round + s];
+            for (int v = 0; v < NV; ++v) red[s][wave][v][lane] = acc[v][s0 + s];
         __syncthreads();
-        if (wave < 4) {
+        if (wave < NV) {
 #pragma unroll
-            for (int s = 0; s < 2; ++s)
+            for (int s = 0; s < kRound; ++s)
 #pragma unroll
-                for (int k = 0; k < kTWaves; ++k) sum[2 * round + s] += red[s][k][wave][lane];
+                for (int k = 0; k < kTWaves; ++k) sum[s0 + s] += red[s][k][wave][lane];
         }
     }
-    if (wave >= 4 || t0 + n >= a.batch) return;
+    if (wave >= NV || t0 + n >= a.batch) return;
     // lane (g, n), register k: column 16 g + 4 v + k of the step, token n
-    const int col = st * kTileCols + 16 * g + 4 * wave;
-    const double two_step = a.meta[tok].two_step, neg_qs = a.meta[tok].neg_qs;
     float r[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -271,7 +303,7 @@ __global__ void __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_
 #pragma unroll
         for (int s = 1; s < kTSlices; ++s) raw = fma(raw, 256.0, (double)sum[s][k]);
         double val = fma(raw, two_step, neg_qs);
-        if (a.out_scale && col + k < a.N) val *= (double)half_bits_to_float(a.out_scale[col + k]);
+        val *= (double)osc[k];
         r[k] = (float)val;
     }
     float* const o = a.out + (size_t)tok * a.out_stride + col;
@@ -288,7 +320,7 @@ static size_t al256(size_t v) { return (v + 255) / 256 * 256; }
 
 size_t gemm_t_scratch_bytes(int64_t M, int batch)
 {
-    return al256((size_t)batch * n_rowblocks(M) * kTRbBytes) + al256((size_t)batch * sizeof(QMeta));
+    return (size_t)((batch + kTTokens - 1) / kTTokens) * n_rowblocks(M) * kTGroupRbBytes + al256((size_t)batch * sizeof(QMeta));
 }
 
 // A is [M][N] as sign tiles; out[tok][0..N) = out_scale (.) A^T (in_scale (.) in[tok][0..M)).  `scratch`: device,
@@ -298,13 +330,20 @@ int launch_gemm_t(const uint32_t* tiles, int64_t M, int64_t N, const void* in, i
 {
     const int n_rb = (int)n_rowblocks(M);
     uint8_t* bq = (uint8_t*)scratch;
-    QMeta* meta = (QMeta*)(bq + al256((size_t)batch * n_rb * kTRbBytes));
+    QMeta* meta = (QMeta*)(bq + (size_t)((batch + kTTokens - 1) / kTTokens) * n_rb * kTGroupRbBytes);
     const TQuantArgs q{in, in_scale, bq, meta, (int)M, in_dtype, in_stride, n_rb * 8};
-    hipLaunchKernelGGL(quantize_t_kernel, dim3(batch), dim3(kTQThreads), 0, s, q);
+    const dim3 qgrid(batch), qblock(std::min(kTQThreads, (q.n_pieces + 63) / 64 * 64));
+    if (in_dtype == NQ_F32) hipLaunchKernelGGL(quantize_t_kernel<NQ_F32>, qgrid, qblock, 0, s, q);
+    else if (in_dtype == NQ_F16) hipLaunchKernelGGL(quantize_t_kernel<NQ_F16>, qgrid, qblock, 0, s, q);
+    else hipLaunchKernelGGL(quantize_t_kernel<NQ_BF16>, qgrid, qblock, 0, s, q);
     NQ_HIP(hipGetLastError());
     const TStageArgs t{tiles, bq, meta, out_scale, out, (int)N, (int)n_steps(N), n_rb, out_stride, batch};
-    hipLaunchKernelGGL(gemm_t_kernel, dim3((unsigned)((N + kTileCols - 1) / kTileCols), (unsigned)((batch + kTTokens - 1) / kTTokens)),
-                       dim3(64 * kTWaves), 0, s, t);
+    const int steps = (int)((N + kTileCols - 1) / kTileCols), groups = (batch + kTTokens - 1) / kTTokens;
+    // half tiles where whole ones leave more than half of the CUs without a workgroup (16 steps x 4 groups: 8.3 us against 10)
+    if (steps * groups <= device_cu_count() / 2)
+        hipLaunchKernelGGL(gemm_t_kernel<2>, dim3((unsigned)steps * 2, (unsigned)groups), dim3(64 * kTWaves), 0, s, t);
+    else
+        hipLaunchKernelGGL(gemm_t_kernel<4>, dim3((unsigned)steps, (unsigned)groups), dim3(64 * kTWaves), 0, s, t);
     NQ_HIP(hipGetLastError());
     return NQ_OK;
 }
