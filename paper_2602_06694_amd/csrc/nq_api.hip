@@ -354,7 +354,7 @@ static void free_handle(nq_handle h)
     if (!h) return;
     slab_release(h->w_slab, h->w_alloc, h->w_bytes);
     slab_release(h->ws_slab, h->ws_alloc, h->ws_bytes);
-    if (h->pf_alloc) (void)hipFree(h->pf_alloc);
+    if (h->pf_alloc && !h->pf_in_xt) (void)hipFree(h->pf_alloc);
     if (h->tp_alloc) (void)hipFree(h->tp_alloc);
     if (h->xt_alloc) (void)hipFree(h->xt_alloc);
     if (h->s_mid) (void)hipFree(h->s_mid);
@@ -531,18 +531,27 @@ extern "C" int nq_binlr_set_mid_scale(nq_handle h, const uint16_t* s_mid_fp16)
     return NQ_OK;
 }
 
-// grows the dense path's workspace to `need` bytes (never shrinks it)
+// forgets the dense path's workspace (the device must be idle)
+static int drop_prefill_workspace(nq_handle h)
+{
+    void* const p = h->pf_in_xt ? nullptr : h->pf_alloc;    // inside the exact path's allocation it goes with that
+    h->pf_alloc = nullptr;
+    h->pf_bytes = 0;
+    h->pf_in_xt = false;
+    if (p) NQ_HIP(hipFree(p));
+    return NQ_OK;
+}
+
+// grows the dense path's workspace to `need` bytes (never shrinks it).  Its contents need no initialisation: rows past the batch are
+// computed with and never stored.
 static int grow_prefill_workspace(nq_handle h, size_t need)
 {
     if (need <= h->pf_bytes) return NQ_OK;
     NQ_HIP(hipDeviceSynchronize());
-    if (h->pf_alloc) NQ_HIP(hipFree(h->pf_alloc));
-    h->pf_alloc = nullptr;
-    h->pf_bytes = 0;
+    int rc = drop_prefill_workspace(h);
+    if (rc != NQ_OK) return rc;
     NQ_HIP(hipMalloc(&h->pf_alloc, need));
     h->pf_bytes = need;
-    NQ_HIP(hipMemset(h->pf_alloc, 0, need));
-    NQ_HIP(hipDeviceSynchronize());
     return NQ_OK;
 }
 
@@ -557,27 +566,40 @@ extern "C" int nq_binlr_reserve(nq_handle h, int max_batch)
     if (max_batch < 1) return fail(NQ_E_INVALID_ARG, "nq_binlr_reserve: max_batch must be >= 1");
     if (max_batch <= NQ_DECODE_MAX_BATCH || (h->flags & NQ_FLAG_DECODE_VALU)) return NQ_OK;   // decode workspace is fixed
     // the exact path's workspace for passes of more than eight tokens (its calls themselves never allocate)
-    const int tokens = std::min(pass_tokens(carve_workspace(nullptr, nullptr, h->d_in, h->r, 16) / 16), (int)round_up(max_batch, 16));
-    if (h->xt_tokens < tokens) {
-        NQ_HIP(hipDeviceSynchronize());
-        if (h->xt_alloc) NQ_HIP(hipFree(h->xt_alloc));
-        h->xt_alloc = nullptr;
-        h->xt_tokens = 0;
-        NQ_HIP(hipMalloc(&h->xt_alloc, carve_workspace(nullptr, nullptr, h->d_in, h->r, tokens)));
-        h->xt_tokens = tokens;
-    }
-    if (max_batch < NQ_PREFILL_MIN_BATCH || (h->flags & NQ_FLAG_NO_PREFILL)) return NQ_OK;
+    int tokens = std::min(pass_tokens(carve_workspace(nullptr, nullptr, h->d_in, h->r, 16) / 16), (int)round_up(max_batch, 16));
     // The dense path's need is not monotone in the batch: smaller batches split the reduction
     // over more workgroups and keep more partial sums.  It depends on the batch only through its
     // padding to whole 64-token tiles, so the maximum over every padding up to max_batch's is taken.
+    const bool dense = max_batch >= NQ_PREFILL_MIN_BATCH && !(h->flags & NQ_FLAG_NO_PREFILL);
     size_t need = 0;
-    for (int64_t b = 64; ; b += 64) {
+    for (int64_t b = 64; dense; b += 64) {
         const int bb = (int)std::min<int64_t>(b, max_batch);
         need = std::max(need, prefill_workspace_bytes(h->d_out, h->d_in, h->r, bb));
         if (b >= max_batch) break;
     }
-    int rc = grow_prefill_workspace(h, need);
-    if (rc != NQ_OK) return rc;
+    if (h->xt_tokens < tokens) {
+        // both in one allocation (a second one costs as much as the first: 0.2 to 0.4 ms)
+        need = std::max(need, h->pf_bytes);
+        NQ_HIP(hipDeviceSynchronize());
+        int rc = drop_prefill_workspace(h);
+        if (rc != NQ_OK) return rc;
+        void* const old = h->xt_alloc;
+        h->xt_alloc = nullptr;
+        h->xt_tokens = 0;
+        if (old) NQ_HIP(hipFree(old));
+        const size_t xt_bytes = align_up(carve_workspace(nullptr, nullptr, h->d_in, h->r, tokens), 256);
+        NQ_HIP(hipMalloc(&h->xt_alloc, xt_bytes + need));
+        h->xt_tokens = tokens;
+        if (need) {
+            h->pf_alloc = (char*)h->xt_alloc + xt_bytes;
+            h->pf_bytes = need;
+            h->pf_in_xt = true;
+        }
+    } else if (need > h->pf_bytes) {
+        int rc = grow_prefill_workspace(h, need);
+        if (rc != NQ_OK) return rc;
+    }
+    if (!dense) return NQ_OK;
     h->pf_batch = std::max(h->pf_batch, max_batch);
     return NQ_OK;
 }

@@ -239,6 +239,7 @@ struct nq_binlr_s {
     void* pf_alloc;
     size_t pf_bytes;
     int pf_batch;
+    bool pf_in_xt;        // pf_alloc lies inside xt_alloc (nq_binlr_reserve allocates the two together)
     // workspace of the transposed products (allocated by their first call)
     void* tp_alloc;
     int tp_tokens;        // tokens one pass may hold
