@@ -1103,6 +1103,9 @@ extern "C" int nq_lb_admm(const double* W, int64_t n, int64_t m, int64_t r, cons
     NQ_HIP(hipMemsetAsync(ws.status, 0, 256, s));
     hipLaunchKernelGGL(pad_identity_kernel, dim3(256), dim3(256), 0, s, ws.H, ws.rp, R, 0);
     hipLaunchKernelGGL(pad_identity_kernel, dim3(256), dim3(256), 0, s, ws.Linv, ws.rp, R, 1);
+    // (the inverse of L reads whole blocks of the matrix that holds L below its diagonal, in Hinv's buffer, also where they lie past
+    // the last real block: times zeros, which the workspace's own bits need not survive)
+    if (ws.rp > ws.rr) hipLaunchKernelGGL(pad_identity_kernel, dim3(256), dim3(256), 0, s, ws.Hinv, ws.rp, R, 0);
     NQ_HIP(hipGetLastError());
     if (U != U0) NQ_HIP(hipMemcpyAsync(U, U0, (size_t)n * r * sizeof(double), hipMemcpyDeviceToDevice, s));
     if (V != V0) NQ_HIP(hipMemcpyAsync(V, V0, (size_t)m * r * sizeof(double), hipMemcpyDeviceToDevice, s));
