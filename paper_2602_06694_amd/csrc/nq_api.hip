@@ -617,7 +617,7 @@ static QuantDesc make_qx(nq_handle h, const DecodeWorkspace& w, const void* x)
     QuantDesc q;
     q.x = x; q.scale = h->s_in; q.bq = w.bq_x; q.meta = w.meta_x;
     q.N = (int)h->d_in; q.n_chunks = (int)n_steps(h->d_in) * 4; q.x_stride = (int)h->d_in; q.dtype = h->x_dtype;
-    q.mag_exp = 22; q.grouped = 0;
+    q.mag_exp = 22;
     return q;
 }
 static StageDesc make_s1(nq_handle h, const DecodeWorkspace& w)
@@ -632,7 +632,7 @@ static QuantDesc make_qt(nq_handle h, const DecodeWorkspace& w)
     QuantDesc q;
     q.x = w.t; q.scale = h->s_mid; q.bq = w.bq_t; q.meta = w.meta_t;
     q.N = (int)h->r; q.n_chunks = (int)n_steps(h->r) * 4; q.x_stride = w.t_stride; q.dtype = NQ_F32;
-    q.mag_exp = 22; q.grouped = 0;
+    q.mag_exp = 22;
     return q;
 }
 static StageDesc make_s2(nq_handle h, const DecodeWorkspace& w, void* y)
@@ -716,13 +716,12 @@ static int run_in_passes(nq_handle h, const void* x, void* y, int batch, hipStre
         int rc, nb;
         if (wide && left > NQ_DECODE_MAX_BATCH) {
             nb = std::min(h->xt_tokens, left);
-            QuantDesc qx = make_qx(h, w, xp), qt = make_qt(h, w);
-            qx.grouped = qt.grouped = 1;                    // (the workspace holds whole groups of 16 tokens)
+            const QuantDesc qx = make_qx(h, w, xp), qt = make_qt(h, w);
             StageDesc s2 = make_s2(h, w, yp);
             if (unscaled) s2.out_scale = nullptr;
-            if ((rc = launch_quantize(nullptr, qx, 1, qx.n_chunks, nb, s)) != NQ_OK) return rc;
+            if ((rc = launch_quantize(nullptr, qx, 1, qx.n_chunks, nb, s, true)) != NQ_OK) return rc;
             if ((rc = launch_stage_exact(make_s1(h, w), nb, s)) != NQ_OK) return rc;
-            if ((rc = launch_quantize(nullptr, qt, 1, qt.n_chunks, nb, s)) != NQ_OK) return rc;
+            if ((rc = launch_quantize(nullptr, qt, 1, qt.n_chunks, nb, s, true)) != NQ_OK) return rc;
             rc = launch_stage_exact(s2, nb, s);
         } else {
             nb = std::min(NQ_DECODE_MAX_BATCH, left);

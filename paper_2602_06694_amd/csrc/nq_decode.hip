@@ -102,7 +102,9 @@ constexpr int kQuantHeld = 2;
 // STREAMED: the quantised bytes are written around the cache (non-temporal).  Measured on the pool of
 // 1024 4096x4096 r=1024 layers: step 226 -> 213 us at batch 2, 261 -> 257 us at batch 4, but 382 -> 387 us at
 // batch 8; taken for batch <= 5.
-template <int kQuantThreads, bool STREAMED>
+// GROUPED: the order of the exact product for groups of 16 tokens (the workspace holds whole groups).
+// ANY: whole chunks of rows that do not start 16-byte aligned are read wide too (load_chunk16).
+template <int kQuantThreads, bool STREAMED, bool GROUPED, bool ANY>
 __global__ void __launch_bounds__(kQuantThreads)
 quantize_kernel(const QuantDesc* __restrict__ descs, QuantDesc single, int batch)
 {
@@ -130,7 +132,7 @@ quantize_kernel(const QuantDesc* __restrict__ descs, QuantDesc single, int batch
         for (int k = 0; k < kQuantHeld; ++k) {
             const int c = tid + k * kQuantThreads;
             if (c < d.n_chunks) {
-                load_chunk16(d, base, c, vec, hv[k]);
+                load_chunk16<ANY>(d, base, c, vec, hv[k]);
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     const float a = fabsf(hv[k][i]);
@@ -142,7 +144,7 @@ quantize_kernel(const QuantDesc* __restrict__ descs, QuantDesc single, int batch
     } else {
         for (int c = tid; c < d.n_chunks; c += kQuantThreads) {
             float v[16];
-            load_chunk16(d, base, c, vec, v);
+            load_chunk16<ANY>(d, base, c, vec, v);
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const float a = fabsf(v[i]);
@@ -174,19 +176,18 @@ quantize_kernel(const QuantDesc* __restrict__ descs, QuantDesc single, int batch
     // pass 2: q = rint(v / step), split into three signed bytes, write the MFMA B-operand layout
     long long local_sum = 0;
     uint4* const dst = (uint4*)(d.bq);
-    const int sp = bq_slice_pieces(d.grouped);
     if (held) {
 #pragma unroll
         for (int k = 0; k < kQuantHeld; ++k) {
             const int c = tid + k * kQuantThreads;
             if (c < d.n_chunks)
-                local_sum += quantize_chunk16<STREAMED>(hv[k], inv_step, bad, dst + bq_chunk_piece(tok, c, d.n_chunks, d.grouped), sp);
+                local_sum += quantize_chunk16<STREAMED>(hv[k], inv_step, bad, dst + bq_chunk_piece<GROUPED>(tok, c, d.n_chunks), bq_slice_pieces<GROUPED>());
         }
     } else {
         for (int c = tid; c < d.n_chunks; c += kQuantThreads) {
             float v[16];
-            load_chunk16(d, base, c, vec, v);
-            local_sum += quantize_chunk16<STREAMED>(v, inv_step, bad, dst + bq_chunk_piece(tok, c, d.n_chunks, d.grouped), sp);
+            load_chunk16<ANY>(d, base, c, vec, v);
+            local_sum += quantize_chunk16<STREAMED>(v, inv_step, bad, dst + bq_chunk_piece<GROUPED>(tok, c, d.n_chunks), bq_slice_pieces<GROUPED>());
         }
     }
     double s = (double)local_sum;               // |sum| < 2^39: exact
@@ -211,7 +212,7 @@ quantize_kernel(const QuantDesc* __restrict__ descs, QuantDesc single, int batch
 // this way (13 -> 9 us at batch 4).  Taken for vectors of up to 1024 elements (H = 1); with more
 // chunks per lane (H = 2, 4: vectors of up to 4096) it measured the same as the workgroup kernel
 // or slower.  Same arithmetic element for element: identical bytes and constants.
-template <int H, bool STREAMED>
+template <int H, bool STREAMED, bool GROUPED = false>
 __global__ void __launch_bounds__(256)
 quantize_wave_kernel(const QuantDesc* __restrict__ descs, QuantDesc single, int n_ops, int batch)
 {
@@ -255,11 +256,10 @@ quantize_wave_kernel(const QuantDesc* __restrict__ descs, QuantDesc single, int 
 
     long long local_sum = 0;
     uint4* const dst = (uint4*)(d.bq);
-    const int sp = bq_slice_pieces(d.grouped);
 #pragma unroll
     for (int k = 0; k < H; ++k) {
         const int c = lane + 64 * k;
-        if (c < d.n_chunks) local_sum += quantize_chunk16<STREAMED>(hv[k], inv_step, bad != 0, dst + bq_chunk_piece(tok, c, d.n_chunks, d.grouped), sp);
+        if (c < d.n_chunks) local_sum += quantize_chunk16<STREAMED>(hv[k], inv_step, bad != 0, dst + bq_chunk_piece<GROUPED>(tok, c, d.n_chunks), bq_slice_pieces<GROUPED>());
     }
     double sum = (double)local_sum;
     for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
@@ -273,7 +273,7 @@ quantize_wave_kernel(const QuantDesc* __restrict__ descs, QuantDesc single, int 
 
 // max_chunks: the largest n_chunks among the launch's vectors
 int launch_quantize(const QuantDesc* d_descs, const QuantDesc& single, int n_ops, int max_chunks, int batch,
-                    hipStream_t s)
+                    hipStream_t s, bool grouped)
 {
     const bool no_wave = opt_flag(OPT_NO_QUANT_WAVE);
     // several short vectors: one wave each (a lone short vector keeps the workgroup kernel, whose
@@ -282,7 +282,8 @@ int launch_quantize(const QuantDesc* d_descs, const QuantDesc& single, int n_ops
         const dim3 wgrid((unsigned)(((size_t)n_ops * batch + 3) / 4));
 #define NQ_LAUNCH_QWAVE(H)                                                                              \
     do {                                                                                                \
-        if (batch <= 5) NQ_LAUNCH((quantize_wave_kernel<H, true>), wgrid, dim3(256), 0, s, d_descs, single, n_ops, batch); \
+        if (grouped) NQ_LAUNCH((quantize_wave_kernel<H, false, true>), wgrid, dim3(256), 0, s, d_descs, single, n_ops, batch); \
+        else if (batch <= 5) NQ_LAUNCH((quantize_wave_kernel<H, true>), wgrid, dim3(256), 0, s, d_descs, single, n_ops, batch); \
         else NQ_LAUNCH((quantize_wave_kernel<H, false>), wgrid, dim3(256), 0, s, d_descs, single, n_ops, batch);           \
     } while (0)
         NQ_LAUNCH_QWAVE(1);
@@ -291,15 +292,25 @@ int launch_quantize(const QuantDesc* d_descs, const QuantDesc& single, int n_ops
         return NQ_OK;
     }
     const dim3 grid(n_ops, batch);
+    // (a lone vector whose rows do not start 16-byte aligned; the descriptors of a plan's vectors are on the device)
+    const bool any = !d_descs && ((size_t)single.x_stride * (single.dtype == NQ_F32 ? 4 : 2)) % 16 != 0;
+#define NQ_LAUNCH_QUANT3(T, G, A)                                                                       \
+    do {                                                                                                \
+        if (!G && batch <= 5) NQ_LAUNCH((quantize_kernel<T, !G, G, A>), grid, dim3(T), 0, s, d_descs, single, batch); \
+        else NQ_LAUNCH((quantize_kernel<T, false, G, A>), grid, dim3(T), 0, s, d_descs, single, batch); \
+    } while (0)
 #define NQ_LAUNCH_QUANT(T)                                                                              \
     do {                                                                                                \
-        if (batch <= 5) NQ_LAUNCH((quantize_kernel<T, true>), grid, dim3(T), 0, s, d_descs, single, batch); \
-        else NQ_LAUNCH((quantize_kernel<T, false>), grid, dim3(T), 0, s, d_descs, single, batch);           \
+        if (grouped && any) NQ_LAUNCH_QUANT3(T, true, true);                                            \
+        else if (grouped) NQ_LAUNCH_QUANT3(T, true, false);                                             \
+        else if (any) NQ_LAUNCH_QUANT3(T, false, true);                                                 \
+        else NQ_LAUNCH_QUANT3(T, false, false);                                                         \
     } while (0)
     if (max_chunks <= 256 * kQuantHeld) NQ_LAUNCH_QUANT(256);
     else if (max_chunks <= 512 * kQuantHeld) NQ_LAUNCH_QUANT(512);
     else NQ_LAUNCH_QUANT(1024);
 #undef NQ_LAUNCH_QUANT
+#undef NQ_LAUNCH_QUANT3
     NQ_HIP(hipGetLastError());
     return NQ_OK;
 }
@@ -1523,6 +1534,18 @@ int schedule_full_rowblocks()
 // reductions (the resident variant) stay with the stream kernel below batch 6 (115 against 119 us).
 int shared_min_batch() { return std::max(1, opt_or(OPT_SHARE_MIN_BATCH, 4)); }
 
+// Waves per row block in launches that do not fill the chip: four, and 16 (eight at batch 6 to 8, whose waves hold two
+// column groups) where the reduction is so long that four waves' shares take longer than adding up 16 of them, and every row block
+// still has a CU of its own.  Measured per forward, four waves against the wider workgroup: 8192 x 28672 r = 3520 (448 steps)
+// batch 2 36.4 -> 32.6, batch 4 35.3 -> 34.3, batch 6 48.4 -> 46.3 us; 4096 x 4096 r = 1024 (64 steps) batch 2 15.9 against
+// 17.7, batch 4 16.1 against 16.7.
+static int split_width(int n_rb_total, int mean_steps, int batch)
+{
+    if (batch == 1) return n_rb_total * 4 >= schedule_full_rowblocks() ? 4 : 16;
+    if (n_rb_total > device_cu_count() || mean_steps < 256) return 4;
+    return batch <= 5 ? 16 : kSplit8Schedule;
+}
+
 int stage_schedule(int n_rb_total, int mean_steps, int batch)
 {
     // row blocks from which a launch counts as filling the chip (NQ_SCHEDULE_FULL overrides it,
@@ -1533,10 +1556,10 @@ int stage_schedule(int n_rb_total, int mean_steps, int batch)
     // (batch 1 splits from 33 steps on: stage 2 of the 70B stack, 35 and 55 steps, 452 -> 442 us; pools
     // of 35- and 55-step reductions 64 -> 62 and 91 -> 85 us including the quantisation launch)
     else if (n_rb_total >= full) w = mean_steps >= std::max(1, opt_or(OPT_SPLIT_STEPS, batch == 1 ? 33 : 64)) ? 4 : 1;
-    else w = (n_rb_total * 4 >= full || batch > 2) ? 4 : 16;
+    else w = split_width(n_rb_total, mean_steps, batch);
     {
         const int fw = opt(OPT_FORCE_W);
-        if (fw == 1 || fw == 4 || (fw == 16 && batch <= 2)) w = fw;     // (the shared schedule cannot be forced: it needs a work list)
+        if (fw == 1 || fw == 4 || (fw == 16 && batch <= 5)) w = fw;     // (the shared schedule cannot be forced: it needs a work list)
     }
     return w;
 }
@@ -1590,6 +1613,7 @@ int launch_stage(const StageDesc* d_descs, const StageDesc& single, const WorkIt
         if (w == 4) return launch_split_t<1, 4>(d_descs, single, d_items, n_items, batch, s);
         return launch_split_t<1, 16>(d_descs, single, d_items, n_items, batch, s);
     }
+    if (w == kSplit8Schedule) return launch_split_t<2, 8>(d_descs, single, d_items, n_items, batch, s);
     return launch_split_t<2, 4>(d_descs, single, d_items, n_items, batch, s);
 }
 

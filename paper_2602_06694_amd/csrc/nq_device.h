@@ -3,6 +3,7 @@
 // one-step multiply-accumulate of the streaming kernels (Section 3.1 Eq. 1 evaluated as two
 // sign-matrix x vector products; Appendix E.2).
 #pragma once
+#include <type_traits>
 #include "nq_internal.h"
 
 namespace nq {
@@ -25,11 +26,21 @@ typedef const __attribute__((address_space(1))) v4u* gptr_v4u;    // global (not
 typedef const __attribute__((address_space(1))) v4f* gptr_v4f;
 typedef const __attribute__((address_space(1))) uint16_t* gptr_u16;
 
-// chunk c (16 consecutive elements) of token row `base` of the vector d describes, times its scale
+// chunk c (16 consecutive elements) of token row `base` of the vector d describes, times its scale.  Whole chunks of rows that start
+// 16-byte aligned (`vec`) are read 16 bytes at a time; with ANY those of all rows, at the alignment of an element, which global memory
+// takes (six rows of 3001 fp16 elements: 8.0 -> 6.4 us for their quantisation launch; the kernels that quantise for themselves
+// do without: the wider code costs a 1024 x 1024 layer at batch 1 0.24 of its 10.4 us).
+template <bool ANY = false>
 __device__ inline void load_chunk16(const QuantDesc& d, int64_t base, int c, bool vec, float v[16])
 {
+    typedef v4f v4f_elem __attribute__((aligned(4)));
+    typedef v4u v4u_elem __attribute__((aligned(2)));
+    typedef const __attribute__((address_space(1))) v4f_elem* gptr_v4f_elem;
+    typedef const __attribute__((address_space(1))) v4u_elem* gptr_v4u_elem;
+    typedef typename std::conditional<ANY, gptr_v4f_elem, gptr_v4f>::type gptr_v4f_any;
+    typedef typename std::conditional<ANY, gptr_v4u_elem, gptr_v4u>::type gptr_v4u_any;
     const int j0 = c * 16;
-    if (vec && j0 + 16 <= d.N) {
+    if ((ANY || vec) && j0 + 16 <= d.N) {
         // the scales are requested before the (type-dependent) loads of x, so that both are in flight together
         v4u sraw[2] = {v4u{0, 0, 0, 0}, v4u{0, 0, 0, 0}};
         if (d.scale) {
@@ -39,14 +50,14 @@ __device__ inline void load_chunk16(const QuantDesc& d, int64_t base, int c, boo
         }
         if (d.dtype == NQ_F32) {
             // (global, not generic, address space: plain vector loads, exact wait counts)
-            const gptr_v4f p = (gptr_v4f)((const float*)d.x + base + j0);
+            const gptr_v4f_any p = (gptr_v4f_any)((const float*)d.x + base + j0);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const v4f f = p[q];
                 v[4 * q] = f.x; v[4 * q + 1] = f.y; v[4 * q + 2] = f.z; v[4 * q + 3] = f.w;
             }
         } else {
-            const gptr_v4u p = (gptr_v4u)((const uint16_t*)d.x + base + j0);
+            const gptr_v4u_any p = (gptr_v4u_any)((const uint16_t*)d.x + base + j0);
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
                 const v4u u = p[q];

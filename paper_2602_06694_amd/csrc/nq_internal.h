@@ -34,13 +34,16 @@ constexpr int kSlices = 3;
 __host__ __device__ inline int bq_piece(int chunk, int slice) { return (chunk >> 2) * 12 + slice * 4 + (chunk & 3); }
 
 constexpr uint32_t kGroupStepBytes = 3 * 16 * 64;      // a step of a group of 16 tokens in the grouped order
-// the first of a chunk's pieces (16 bytes) in `bq`, and the distance to the next slice's
-__host__ __device__ inline size_t bq_chunk_piece(int tok, int chunk, int n_chunks, int grouped)
+// The first of a chunk's pieces (16 bytes) in `bq`, token-major as above, or GROUPED (nq_exact.hip): [groups of 16 tokens][n_steps]
+// [3 slices][16 tokens][4 chunks][16]; and the distance to the next slice's piece.
+template <bool GROUPED>
+__host__ __device__ inline size_t bq_chunk_piece(int tok, int chunk, int n_chunks)
 {
-    return grouped ? ((size_t)(tok >> 4) * (n_chunks >> 2) + (chunk >> 2)) * (kGroupStepBytes / 16) + (tok & 15) * 4 + (chunk & 3)
+    return GROUPED ? ((size_t)(tok >> 4) * (n_chunks >> 2) + (chunk >> 2)) * (kGroupStepBytes / 16) + (tok & 15) * 4 + (chunk & 3)
                    : (size_t)tok * n_chunks * kSlices + bq_piece(chunk, 0);
 }
-__host__ __device__ inline int bq_slice_pieces(int grouped) { return grouped ? 64 : 4; }
+template <bool GROUPED>
+__host__ __device__ constexpr int bq_slice_pieces() { return GROUPED ? 64 : 4; }
 
 // Per token, written by the quantisation: with step the token's power-of-two quantisation step and
 // sum_q = sum_j q_j, a stage output is  (2 sum_n b_n q_n - sum_q) step = fma(sum_n b_n q_n, two_step, neg_qs).
@@ -61,7 +64,6 @@ struct QuantDesc {
     int x_stride;            // elements between tokens
     int dtype;               // NQ_F32 / NQ_F16 / NQ_BF16
     int mag_exp;             // |q| <= 2^mag_exp: 22 (three byte slices; also when 0) or 14 (the top slice stays zero)
-    int grouped;             // 1: bq is [groups of 16 tokens][n_steps][3 slices][16 tokens][4 chunks][16] (nq_exact.hip)
 };
 
 struct StageDesc {
@@ -260,7 +262,7 @@ int launch_pack_signs(const void* d_signs, int dtype, int64_t rows, int64_t cols
                       hipStream_t s);
 // single op (descriptor by value) or many (device arrays)
 int launch_quantize(const QuantDesc* d_descs, const QuantDesc& single, int n_ops, int max_chunks, int batch,
-                    hipStream_t s);
+                    hipStream_t s, bool grouped = false);
 int stage_schedule(int n_rb_total, int mean_steps, int batch);
 int stream_target_steps(int batch);
 int stream_max_rbs(int batch);           // row blocks one stream item may chain (bounded by its LDS output buffer)
@@ -275,6 +277,7 @@ constexpr int kSharedSchedule = 8;       // stage_schedule()'s value for the wor
 constexpr int kSharedResidentSchedule = 9;   // the same kernel with the whole input resident in LDS (reductions <= 16 steps)
 // the two with 16-bit fixed point at batch 6..8: a token takes two MFMA columns, eight tokens one group of 16
 constexpr int kSharedSchedule2 = 10, kSharedResidentSchedule2 = 11;
+constexpr int kSplit8Schedule = 12;      // eight waves per row block (batch 6..8; 1, 4 and 16 stand for themselves)
 inline bool is_shared_schedule(int w) { return w >= kSharedSchedule && w <= kSharedResidentSchedule2; }
 int shared_per_wave(int nst, int batch); // row blocks per wave of an item of that kernel
 // w = 1: stream kernel (items are runs of rbs_per_item row blocks); w = 4 / 16: split kernel (one row block
