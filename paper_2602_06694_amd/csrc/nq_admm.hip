@@ -511,6 +511,11 @@ __global__ __launch_bounds__((NB / 4) * (NB / 4)) void potrf_inv_kernel(double* 
 //     P_j of the panel for itself (three 64 x 64 x 64 products instead of one; they cost little next to the
 //     factorisation beside them), keeps them in its own piece of a scratch matrix -- or, tile (i, 0), stores P_i as
 //     block i of L -- and subtracts  P_i P_j^T  from its tile.
+//   * with `S`, workgroup (i, tiles + 1 + j), j <= k, carries the inverse along: it forms P_i and the block
+//     X_kj = -X_kk S_kj  of row k of L^-1 for itself (the first of the column also stores it) and adds  P_i X_kj  to  S_ij,
+//     the sum of L_ip X_pj over p < i that row k + 1 + i of L^-1 waits for.  As many products as a tile of the trailing matrix takes, in the same
+//     launch, while the diagonal block is factorised: what is left of the inversion afterwards is one row of blocks, where
+//     inverting by halves took eight launches, 185 us for r = 1024.
 // The panel is NOT written over A21: other workgroups still read A21, so L's blocks below the diagonal go to a matrix
 // of their own (Lb; the diagonal blocks of L stay in H).  A step is then one launch of the factorisation's length
 // where the panel, the update and the factorisation as launches of their own take three.
@@ -521,6 +526,8 @@ struct StepArgs {
     double* scratch;    // tiles (tiles + 1) / 2 pieces of 2 x 64 x 64
     int ld, o, prio;    // o: first row / column of block column k
     int* status;
+    int tiles;          // row blocks below block column k
+    double *S, *xscratch;       // [..][ld] sums behind the rows of L^-1 still to come, and tiles x (k + 1) pieces of 2 x 64 x 64; or nullptr
 };
 
 __global__ __launch_bounds__(kGemmThreads, 2) void chol_step_kernel(StepArgs a)
@@ -538,6 +545,30 @@ __global__ __launch_bounds__(kGemmThreads, 2) void chol_step_kernel(StepArgs a)
         dgemm_body<64, 64, 4, false, true>(g, 0, 0, 0, lds_dyn);
         __syncthreads();                           // P's first rows are in memory (and LDS is free again)
         potrf_inv_body<kNB>(a.H, ld, a.Linv, ld, a.o + kNB, a.status, a.prio, L21, lds_dyn);
+        return;
+    }
+    if ((int)blockIdx.y > a.tiles) {
+        const int i = (int)blockIdx.x, j = (int)blockIdx.y - a.tiles - 1, k = a.o / kNB;
+        double* const Pi = a.xscratch + (size_t)(i * (k + 1) + j) * (2 * kNB * kNB);
+        GemmArgs g = gemm_args(0, 1, kNB, kNB, kNB, 1.0, A21 + (size_t)i * kNB * ld, ld, X, ld, 0.0, nullptr, 0, Pi, kNB);
+        g.prio = a.prio;
+        dgemm_body<64, 64, 4, false, true>(g, 0, 0, 0, lds_dyn);
+        const double* Xkj = X;                     // j = k: the diagonal block itself
+        int ldx = ld;
+        if (j < k) {
+            double* const dst = i == 0 ? a.Linv + (size_t)a.o * ld + j * kNB : Pi + kNB * kNB;
+            ldx = i == 0 ? ld : kNB;
+            g = gemm_args(0, 0, kNB, kNB, kNB, -1.0, X, ld, a.S + (size_t)a.o * ld + j * kNB, ld, 0.0, nullptr, 0, dst, ldx);
+            g.prio = a.prio;
+            __syncthreads();
+            dgemm_body<64, 64, 4, false, false>(g, 0, 0, 0, lds_dyn);
+            Xkj = dst;
+        }
+        __syncthreads();                           // this workgroup's P_i and X_kj are in memory
+        double* const Sij = a.S + (size_t)(a.o + (i + 1) * kNB) * ld + j * kNB;
+        g = gemm_args(0, 0, kNB, kNB, kNB, 1.0, Pi, kNB, Xkj, ldx, j == k ? 0.0 : 1.0, Sij, ld, Sij, ld);
+        g.prio = a.prio;
+        dgemm_body<64, 64, 4, false, false>(g, 0, 0, 0, lds_dyn);
         return;
     }
     const int i = (int)blockIdx.y - 1, j = (int)blockIdx.x;
@@ -865,14 +896,16 @@ static int factor_and_invert(const AdmmWs& ws, hipStream_t s, int prio)
     // where the blocks of L below the diagonal end up: a matrix of their own with the one-launch step (Hinv's buffer,
     // free until the last product below), in place of A21 with separate launches
     const double* const Lb = fused ? ws.Hinv : ws.H;
+    // the inverse carried along by the step launches, in two of the buffers of the Gram product's parts (ranks that have them)
+    const bool carried = fused && ws.G[0] != nullptr;
     hipLaunchKernelGGL(potrf_inv_kernel<kNB>, dim3(1), dim3((kNB / 4) * (kNB / 4)), potrf_lds, s, ws.H, rp, ws.Linv, rp, 0, ws.status, prio);
     for (int k = 0; k + 1 < q; ++k) {
         const int o = k * kNB;
         const int rem = rr - o - kNB;
         if (fused) {
-            StepArgs sa{ws.H, ws.Hinv, ws.Linv, ws.T, rp, o, prio, ws.status};
             const int tiles = rem / kNB;
-            hipLaunchKernelGGL(chol_step_kernel, dim3(tiles, tiles + 1), dim3(kGemmThreads), step_lds, s, sa);
+            StepArgs sa{ws.H, ws.Hinv, ws.Linv, ws.T, rp, o, prio, ws.status, tiles, carried ? ws.G[0] : nullptr, carried ? ws.G[1] : nullptr};
+            hipLaunchKernelGGL(chol_step_kernel, dim3(tiles, tiles + 1 + (carried ? k + 1 : 0)), dim3(kGemmThreads), step_lds, s, sa);
             continue;
         }
         double* A21 = ws.H + (size_t)(o + kNB) * rp + o;
@@ -892,9 +925,18 @@ static int factor_and_invert(const AdmmWs& ws, hipStream_t s, int prio)
         hipLaunchKernelGGL(potrf_inv_kernel<kNB>, dim3(1), dim3((kNB / 4) * (kNB / 4)), potrf_lds, s, ws.H, rp, ws.Linv, rp, o + kNB, ws.status, prio);
     }
     NQ_HIP(hipGetLastError());
+    if (carried && q > 1) {
+        // the last row of blocks of L^-1
+        const int o = rr - kNB;
+        GemmArgs x = gemm_args(0, 0, kNB, o, kNB, -1.0, ws.Linv + (size_t)o * rp + o, rp, ws.G[0] + (size_t)o * rp, rp, 0.0, nullptr, 0,
+                               ws.Linv + (size_t)o * rp, rp);
+        x.prio = prio;
+        int rc = launch_gemm(x, 1, s);
+        if (rc != NQ_OK) return rc;
+    }
     // L^-1 block-recursively: with the halves of a diagonal block inverted (X11, X22), the block below the
     // diagonal of its inverse is  -X22 L21 X11;  all pairs of one level run as one batched launch.
-    for (int b = kNB; b < rr; b *= 2) {
+    for (int b = kNB; !carried && b < rr; b *= 2) {
         const int pairs = (rr - b + 2 * b - 1) / (2 * b);       // pairs whose lower half holds real rows
         const long long stride = (long long)2 * b * rp + 2 * b;
         GemmArgs t = gemm_args(0, 0, b, b, b, 1.0, Lb + (size_t)b * rp, rp, ws.Linv, rp, 0.0, nullptr, 0, ws.T + (size_t)b * rp, rp);
