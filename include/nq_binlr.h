@@ -320,7 +320,7 @@ int nq_binlr_read_intermediate(nq_handle h, float* t_host, int batch);
  * Allocates and frees its buffer, runs on the default stream, synchronises. */
 int nq_probe_hbm_read(size_t bytes, int iters, int prewarm_ms, double* gb_per_s);
 /* A register-resident loop of dense matrix-core instructions on every CU: dtype NQ_F16 (fp16 operands,
- * fp32 accumulation; the prefill path's instruction) or NQ_I8 (int8, int32 accumulation; the decode
+ * fp32 accumulation; the prefill path runs on its sparse form) or NQ_I8 (int8, int32 accumulation; the decode
  * path's) or NQ_F64 (binary64, the LB-ADMM products').  Returns 1e12 operations per second (one
  * multiply-add = 2).  Synchronises. */
 int nq_probe_mfma(int dtype, double* tera_ops_per_s);
