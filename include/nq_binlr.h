@@ -249,7 +249,8 @@ int nq_plan_forward_timed(nq_plan p, void* stream, float ms[4]);
 /* Debug: which schedule each of the plan's two stage launches uses.  w[0] stage 1, w[1] stage 2:
  * 1 = one wave per item, 4 / 16 = that many waves share a row block, 8 = the waves of a workgroup share an op's
  * input through LDS (batch 4..8), 9 = the same with the whole input resident in LDS (reductions of at
- * most 16 steps), 32 = short batch-1 launch with reductions of 4097..16384 elements in which every
+ * most 16 steps), 10 / 11 = the two on 16-bit fixed point ("two_slice_b8"), 12 = eight waves share a row block
+ * (batch 6..8, long reductions), 32 = short batch-1 launch with reductions of 4097..16384 elements in which every
  * workgroup (16 waves per row block) quantises the input for itself,
  * 33 / 34 = batch-1 launch whose waves quantise their own share of the input (one / four waves per
  * row block; reductions of at most 1024 / 4096 elements). */
