@@ -4,6 +4,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <vector>
 
@@ -440,6 +441,12 @@ static int create_layer(nq_handle* out, int64_t d_out, int64_t d_in, int64_t r, 
     if (rc != NQ_OK) goto done;
     CREATE_HIP(hipMemcpy(h->s_in, s_in_fp16, (size_t)d_in * 2, kind));
     CREATE_HIP(hipMemcpy(h->s_out, s_out_fp16, (size_t)d_out * 2, kind));
+    {
+        std::unique_ptr<uint16_t[]> copy(from_device ? new (std::nothrow) uint16_t[d_in] : nullptr);
+        if (from_device && !copy) { rc = fail(NQ_E_HIP, "nq_binlr_create: out of host memory"); goto done; }
+        if (from_device) CREATE_HIP(hipMemcpy(copy.get(), s_in_fp16, (size_t)d_in * 2, hipMemcpyDeviceToHost));
+        h->pf_plain = prefill_plain(from_device ? copy.get() : s_in_fp16, d_in, x_dtype);
+    }
     CREATE_HIP(hipDeviceSynchronize());
 #undef CREATE_HIP
 done:
@@ -557,7 +564,7 @@ static int grow_prefill_workspace(nq_handle h, size_t need)
 
 static int ensure_prefill_workspace(nq_handle h, int batch)
 {
-    return grow_prefill_workspace(h, prefill_workspace_bytes(h->d_out, h->d_in, h->r, batch));
+    return grow_prefill_workspace(h, prefill_workspace_bytes(h->d_out, h->d_in, h->r, batch, h->pf_plain));
 }
 
 extern "C" int nq_binlr_reserve(nq_handle h, int max_batch)
@@ -574,7 +581,7 @@ extern "C" int nq_binlr_reserve(nq_handle h, int max_batch)
     size_t need = 0;
     for (int64_t b = 64; dense; b += 64) {
         const int bb = (int)std::min<int64_t>(b, max_batch);
-        need = std::max(need, prefill_workspace_bytes(h->d_out, h->d_in, h->r, bb));
+        need = std::max(need, prefill_workspace_bytes(h->d_out, h->d_in, h->r, bb, h->pf_plain));
         if (b >= max_batch) break;
     }
     if (h->xt_tokens < tokens) {
@@ -759,7 +766,7 @@ extern "C" int nq_binlr_forward(nq_handle h, const void* x, void* y, int batch, 
         a.vt_tiles = h->vt_tiles; a.u_tiles = h->u_tiles; a.s_in = h->s_in; a.s_out = h->s_out;
         a.s_mid = h->s_mid; a.mid_exp = h->mid_exp;
         a.x = x; a.y = y; a.workspace = h->pf_alloc;
-        a.d_out = h->d_out; a.d_in = h->d_in; a.r = h->r; a.batch = batch; a.x_dtype = h->x_dtype; a.y_dtype = h->y_dtype;
+        a.d_out = h->d_out; a.d_in = h->d_in; a.r = h->r; a.batch = batch; a.x_dtype = h->x_dtype; a.y_dtype = h->y_dtype; a.plain = h->pf_plain;
         return launch_prefill(a, s);
     }
     return run_in_passes(h, x, y, batch, s, false);            // larger batches without the dense path

@@ -241,6 +241,7 @@ struct nq_binlr_s {
     void* pf_alloc;
     size_t pf_bytes;
     int pf_batch;
+    bool pf_plain;        // the dense path takes its operands one column at a time (prefill_plain)
     bool pf_in_xt;        // pf_alloc lies inside xt_alloc (nq_binlr_reserve allocates the two together)
     // workspace of the transposed products (allocated by their first call)
     void* tp_alloc;
@@ -330,8 +331,11 @@ struct PrefillArgs {
     int64_t d_out, d_in, r;
     int batch;
     int x_dtype, y_dtype;
+    bool plain;                 // operands one column at a time (prefill_plain) instead of pair sums and differences
 };
-size_t prefill_workspace_bytes(int64_t d_out, int64_t d_in, int64_t r, int batch);
+// whether a layer's s_in (fp16, host) leaves s_in (.) x exact in fp16 on enough channels that rounding pair sums would lose precision
+bool prefill_plain(const uint16_t* s_in, int64_t d_in, int x_dtype);
+size_t prefill_workspace_bytes(int64_t d_out, int64_t d_in, int64_t r, int batch, bool plain);
 int launch_prefill(const PrefillArgs& a, hipStream_t s);
 
 }  // namespace nq

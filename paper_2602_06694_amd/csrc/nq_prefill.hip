@@ -10,8 +10,8 @@
 //   s1 x1 + s2 x2 = s1 * (x1 + x2)  where s1 = s2,   s1 * (x1 - x2)  where they differ,
 //
 // so with the operand holding the sum AND the difference of every pair (rounded to fp16, as x'' itself would be: the same
-// relative rounding on half as many terms of twice the square, hence the same error), a row of signs has exactly one nonzero,
-// +-1, per pair -- two in any four operand positions, which is what v_smfmac_f32_16x16x64_f16 takes: 64 columns in the 16
+// relative rounding on half as many terms of twice the square, hence the same error: over the layers and batches timed, 2.9 to
+// 3.6e-4 of the result's norm in fp32 either way), a row of signs has exactly one nonzero, +-1, per pair -- two in any four operand positions, which is what v_smfmac_f32_16x16x64_f16 takes: 64 columns in the 16
 // cycles in which the dense instruction does 32.  Nothing is pruned: the products left out are with exact zeros.
 //
 // The sign matrices stay in the 1-bit tile layout of the streaming kernels.  A wave owns 128 output rows (one tile row
@@ -26,6 +26,10 @@
 // Not taken: 128-token tiles at one wave per SIMD (half the vector instructions per matrix instruction, no second wave to
 // hide the rest: level); 8-bit sparse operands in two slices (half the vector instructions, but the fixed point that outlier
 // tokens then get is coarser than fp16); three 6-bit slices with block scales (finer than fp16, 1.5 times the matrix cycles: level).
+//
+// Where x'' is exact in fp16 as it stands (16-bit activations times power-of-two scales, for instance) the sums would be rounded for
+// nothing.  Such layers (prefill_plain, from s_in and the type of x) take the operands one column at a time through the dense
+// instruction, in the same kernels otherwise (PLAIN).
 //
 // fp16 (not bf16) operands: +-1 is exact in both and the MFMA rate is the same, but rounding x'
 // and t to 8 mantissa bits breaks the 1e-3 parity bar while 11 bits hold it with margin.
@@ -142,6 +146,28 @@ __device__ __forceinline__ void pf_store_pairs(_Float16* dst, const float v[16],
     }
 }
 
+// The same 16 columns as they are, for the dense instruction: half h (columns 16 g + 8 h ..) is piece (g & 1) * 4 + 2 h + (g >> 1) of
+// the token's eight 16-byte pieces of a step, the one that lane group g reads as half h of its operand; inside it the columns are in
+// the order in which pf_signs has words 2 h and 2 h + 1 of a tile.  dst = the token's step + ((g & 1) * 4 + (g >> 1)) * 8 halves.
+__device__ __forceinline__ void pf_store_plain(_Float16* dst, const float v[16], float sc)
+{
+    constexpr int order[8] = {0, 2, 4, 6, 1, 3, 5, 7};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        v8h o;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) o[i] = (_Float16)(v[8 * h + order[i]] * sc);
+        *(v8h*)(dst + 16 * h) = o;
+    }
+}
+// chunk g (columns 16 g ..) of a token's step at `step`
+template <bool PLAIN>
+__device__ __forceinline__ void pf_store16(_Float16* step, int g, const float v[16], float sc)
+{
+    if (PLAIN) pf_store_plain(step + ((g & 1) * 4 + (g >> 1)) * 8, v, sc);
+    else pf_store_pairs(step + g * 8, v, sc);
+}
+
 // one workgroup per token: max |x'|, then the pairs of x'' = x' * 2^a as fp16.  A thread takes 16 columns at a time; up to
 // kPreHeld such chunks per thread stay in registers between the two passes (rows up to 32768 elements are read once); longer
 // rows are read twice.  The workgroup is no wider than the row needs (pre_threads).
@@ -150,7 +176,7 @@ constexpr int kPreHeld = 2;
 
 // DT: the element type of x (a template parameter, so that the loads of the fast path sit in
 // straight-line code: all of a thread's chunks are requested back to back, then converted).
-template <int DT>
+template <int DT, bool PLAIN>
 __global__ void __launch_bounds__(kPreThreads)
 prefill_prescale_kernel(const void* __restrict__ x, const uint16_t* __restrict__ s_in, int d_in, int lda,
                         float g_t, _Float16* __restrict__ xs, float* __restrict__ tok_scale)
@@ -270,14 +296,14 @@ prefill_prescale_kernel(const void* __restrict__ x, const uint16_t* __restrict__
 #pragma unroll
         for (int k = 0; k < kPreHeld; ++k) {
             const int c = tid + k * threads;
-            if (c < n16) pf_store_pairs(row + (c >> 2) * 64 + (c & 3) * 8, hv[k], sc);
+            if (c < n16) pf_store16<PLAIN>(row + (c >> 2) * 64, c & 3, hv[k], sc);
         }
     } else {
         for (int c = tid; c < n16; c += threads) {
             float v[16];
             pf_load8(x, x_dtype, s_in, base, c * 16, d_in, vec, v);
             pf_load8(x, x_dtype, s_in, base, c * 16 + 8, d_in, vec, v + 8);
-            pf_store_pairs(row + (c >> 2) * 64 + (c & 3) * 8, v, sc);
+            pf_store16<PLAIN>(row + (c >> 2) * 64, c & 3, v, sc);
         }
     }
     if (tid == 0) tok_scale[tok] = 1.0f / (sc * g_t);
@@ -290,6 +316,7 @@ prefill_prescale_kernel(const void* __restrict__ x, const uint16_t* __restrict__
 // 16 consecutive results of gemm 1 (columns n0 .. n0 + 15 of T, n0 a multiple of 16) of token `tok` -> T as gemm 2 reads it:
 // times g, times the rank-wise scale of the three-scale variant where there is one (its own power of two is folded into g);
 // columns beyond the real rank are exact zeros (they are padding of the next reduction).
+template <bool PLAIN>
 __device__ __forceinline__ void store_t16(const GemmArgs& a, int tok, int n0, const float c[16])
 {
     float f[16];
@@ -310,7 +337,7 @@ __device__ __forceinline__ void store_t16(const GemmArgs& a, int tok, int n0, co
     float v[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) v[i] = n0 + i < a.n_real ? c[i] * f[i] : 0.f;
-    pf_store_pairs(a.t_out + (size_t)tok * a.ldt + (n0 >> 6) * 64 + ((n0 >> 4) & 3) * 8, v, 1.0f);
+    pf_store16<PLAIN>(a.t_out + (size_t)tok * a.ldt + (n0 >> 6) * 64, (n0 >> 4) & 3, v, 1.0f);
 }
 
 // A lane's 16 tile bytes as the sparse matrix instruction takes them.  Word v, byte b, bit p = the sign of (row 16 p + j, column
@@ -417,7 +444,7 @@ __device__ __forceinline__ v4f load_scale4(const uint16_t* scale, int n0, int n)
 // the workgroup's part of the reduction (with staging buffers of their own), and hand their
 // accumulators to their partners through LDS before the epilogue.  Such a workgroup fills its CU by itself (two waves per
 // SIMD), and the reduction is halved without partial sums in memory.
-template <int EPI, int TG, int KS>
+template <int EPI, int TG, int KS, bool PLAIN>
 __global__ void __launch_bounds__(64 * kPfWaves * KS) __attribute__((amdgpu_waves_per_eu(2, TG == 4 ? 2 : 4)))
 prefill_gemm_kernel(GemmArgs a)
 {
@@ -534,6 +561,65 @@ prefill_gemm_kernel(GemmArgs a)
 #pragma unroll
         for (int tg = 0; tg < TG; ++tg) PF_READ_B(0, 0, tg);
         const PfConst kc = pf_const();
+        // the reads of the next step beside plane number k of this one
+#define PF_READS(SET, slot, k)                                                                                             \
+    do {                                                                                                                   \
+        if ((k) == 0) w = PF_READ_TILE(slot);                                                                              \
+        if ((k) < TG) PF_READ_B(SET, slot, (k) % TG);                                                                      \
+    } while (0)
+        if constexpr (PLAIN) {
+            // half h of a lane's operand = the columns of words 2 h and 2 h + 1 of its tile: a dense instruction per plane, half and
+            // token group
+            PfBits b0 = {w.x, w.y, 0, 0}, b1 = {w.z, w.w, 0, 0};
+            v4u32 au = pf_signs<0>(b0, kc);
+#define PF_HALF(P, H, SET, NEXT, READS)                                                                                    \
+    do {                                                                                                                   \
+        const v8h aop = __builtin_bit_cast(v8h, au);                                                                       \
+        NEXT;                                                                                                              \
+        READS;                                                                                                             \
+        _Pragma("unroll") for (int tg = 0; tg < TG; ++tg) {                                                                \
+            const v16h b = bop[SET][tg];                                                                                   \
+            const v8h half = (H) ? __builtin_shufflevector(b, b, 8, 9, 10, 11, 12, 13, 14, 15)                             \
+                                 : __builtin_shufflevector(b, b, 0, 1, 2, 3, 4, 5, 6, 7);                                  \
+            acc[P][tg] = __builtin_amdgcn_mfma_f32_16x16x32_f16(aop, half, acc[P][tg], 0, 0, 0);                           \
+        }                                                                                                                  \
+        _Pragma("unroll") for (int i = 0; i < TG; ++i) {                                                                   \
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                                             \
+            __builtin_amdgcn_sched_group_barrier(0x002, 8 / TG, 0);                                                        \
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                                             \
+        }                                                                                                                  \
+        __builtin_amdgcn_sched_barrier(0);                                                                                 \
+    } while (0)
+#define PF_PLANE(P, SET, READS0, READS1)                                                                                   \
+    do {                                                                                                                   \
+        PF_HALF(P, 0, SET, au = pf_signs<P>(b1, kc), READS0);                                                              \
+        if ((P) == 7) { b0 = PfBits{w.x, w.y, 0, 0}; b1 = PfBits{w.z, w.w, 0, 0}; }                                        \
+        PF_HALF(P, 1, SET, au = pf_signs<((P) + 1) % 8>(b0, kc), READS1);                                                  \
+    } while (0)
+#define PF_STEP(SET, SLOT, step)                                                                                           \
+    do {                                                                                                                   \
+        PF_WAIT(2 * kDma);                                                                                                 \
+        const int nx = min((step) + kPfSlots, last);                                                                       \
+        constexpr int NS = ((SLOT) + 1) % kPfSlots, ST = 1 - (SET);                                                        \
+        PF_PLANE(0, SET, PF_READS(ST, NS, 0), PF_REQUEST(SLOT, nx, 0));                                                    \
+        PF_PLANE(1, SET, PF_READS(ST, NS, 1), PF_REQUEST(SLOT, nx, 1));                                                    \
+        PF_PLANE(2, SET, PF_READS(ST, NS, 2), PF_REQUEST(SLOT, nx, 2));                                                    \
+        PF_PLANE(3, SET, PF_READS(ST, NS, 3), );                                                                           \
+        PF_PLANE(4, SET, , );                                                                                              \
+        PF_PLANE(5, SET, , );                                                                                              \
+        PF_PLANE(6, SET, , );                                                                                              \
+        PF_PLANE(7, SET, , );                                                                                              \
+    } while (0)
+            for (int s = 0; s < n_my; s += 4) {
+                PF_STEP(0, 0, s);
+                PF_STEP(1, 1, s + 1);
+                PF_STEP(0, 2, s + 2);
+                PF_STEP(1, 3, s + 3);
+            }
+#undef PF_STEP
+#undef PF_PLANE
+#undef PF_HALF
+        } else {
         PfBits bits = pf_bits(w);
         v4u32 au = pf_signs<0>(bits, kc);
         uint32_t ix0 = pf_index<0>(bits, kc), ix1 = 0, ix2 = 0, ix3 = 0;
@@ -551,12 +637,6 @@ prefill_gemm_kernel(GemmArgs a)
             if (i < 4) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                                  \
         }                                                                                                                  \
         __builtin_amdgcn_sched_barrier(0);                                                                                 \
-    } while (0)
-        // the reads of the next step beside plane number k of this one
-#define PF_READS(SET, slot, k)                                                                                             \
-    do {                                                                                                                   \
-        if ((k) == 0) w = PF_READ_TILE(slot);                                                                              \
-        if ((k) < TG) PF_READ_B(SET, slot, (k) % TG);                                                           \
     } while (0)
 #define PF_STEP(SET, SLOT, step)                                                                                           \
     do {                                                                                                                   \
@@ -580,6 +660,7 @@ prefill_gemm_kernel(GemmArgs a)
         }
 #undef PF_STEP
 #undef PF_PLANE
+        }
 #undef PF_READS
     }
     // nothing on its way into LDS any more, in no wave: the memory changes hands
@@ -668,7 +749,7 @@ prefill_gemm_kernel(GemmArgs a)
                     const v4f r = *(const v4f*)(tr + t * kPfTrStride + col + 4 * q);
                     c[4 * q] = r.x; c[4 * q + 1] = r.y; c[4 * q + 2] = r.z; c[4 * q + 3] = r.w;
                 }
-                store_t16(a, m0 + tg * 16 + t, rb * kTileRows + col, c);
+                store_t16<PLAIN>(a, m0 + tg * 16 + t, rb * kTileRows + col, c);
             }
         } else {
 #pragma unroll
@@ -691,7 +772,7 @@ prefill_gemm_kernel(GemmArgs a)
 
 // sum the split-K partials and apply the epilogue; one thread per four consecutive outputs (y) or 16 columns of T (the
 // columns between the last row block and T's row length are padding of gemm 2's reduction: zeros)
-template <int EPI>
+template <int EPI, bool PLAIN>
 __global__ void __launch_bounds__(256)
 prefill_finalize_kernel(GemmArgs a)
 {
@@ -711,7 +792,7 @@ prefill_finalize_kernel(GemmArgs a)
         float c[16];
 #pragma unroll
         for (int q = 0; q < 4; ++q) { c[4 * q] = c4[q].x; c[4 * q + 1] = c4[q].y; c[4 * q + 2] = c4[q].z; c[4 * q + 3] = c4[q].w; }
-        store_t16(a, tok, n0, c);
+        store_t16<PLAIN>(a, tok, n0, c);
     } else {
         const int n4 = a.n_pad / 4;
         if (idx >= (size_t)a.m_pad * n4) return;
@@ -757,9 +838,12 @@ static int steps_per_split4(int nst, int splits, int ks = 1)
 //  - beside its steps a workgroup takes 9.5 us (64 tokens), 10.5 (eight waves), 6.9 (32 tokens): the first fetch and the epilogue;
 //  - splitting costs the finalize launch (2.8 us) and per part 0.23 us and the write and re-read of one set of fp32
 //    partial sums, 0.29 us per MB.
+// One column at a time (`plain`) the steps take 0.60, 1.05, 0.97, 0.49 and 0.35 us (from 24 of those points, 6 layers), the rest is the same.
 struct GemmTiling { int tg, splits, ks; };
-static GemmTiling choose_tiling(int m_pad, int n_rb, int nst, int n_pad)
+struct StepCost { double alone4, two4, halves4, alone2, each2; };
+static GemmTiling choose_tiling(int m_pad, int n_rb, int nst, int n_pad, bool plain)
 {
+    const StepCost c = plain ? StepCost{0.60, 1.05, 0.97, 0.49, 0.35} : StepCost{0.377, 0.68, 0.654, 0.353, 0.255};
     const int cus = device_cu_count();
     const int n_tiles = (n_rb + kPfWaves - 1) / kPfWaves;
     const double partial_mb = (double)m_pad * n_pad * 4.0 / 1e6;
@@ -769,11 +853,11 @@ static GemmTiling choose_tiling(int m_pad, int n_rb, int nst, int n_pad)
         const int wgs = (m_pad / (16 * tg)) * n_tiles * splits, per = steps_per_split4(nst, splits, ks);
         double cost;
         if (ks == 2) {
-            cost = (wgs + cus - 1) / cus * (per / 2 * 0.654 + 10.5);
+            cost = (wgs + cus - 1) / cus * (per / 2 * c.halves4 + 10.5);
         } else {
             // full rounds of the CUs' slots, then the last, partial one
             const int per_cu = tg == 4 ? 2 : 4, full = wgs / (per_cu * cus), rem = wgs % (per_cu * cus), k = (rem + cus - 1) / cus;
-            const double step_full = tg == 4 ? 0.68 : 4 * 0.255, step_rem = tg == 4 ? (k <= 1 ? 0.377 : 0.68) : std::max(0.353, k * 0.255);
+            const double step_full = tg == 4 ? c.two4 : 4 * c.each2, step_rem = tg == 4 ? (k <= 1 ? c.alone4 : c.two4) : std::max(c.alone2, k * c.each2);
             const double fixed = tg == 4 ? 9.5 : 6.9;
             cost = full * (per * step_full + fixed) + (rem ? per * step_rem + fixed : 0.0);
         }
@@ -788,7 +872,7 @@ static GemmTiling choose_tiling(int m_pad, int n_rb, int nst, int n_pad)
     return best;
 }
 
-static PfLayout pf_layout(int64_t d_out, int64_t d_in, int64_t r, int batch)
+static PfLayout pf_layout(int64_t d_out, int64_t d_in, int64_t r, int batch, bool plain)
 {
     PfLayout L;
     L.m_pad = (int)round_up(batch, kPfTokens);
@@ -796,8 +880,8 @@ static PfLayout pf_layout(int64_t d_out, int64_t d_in, int64_t r, int batch)
     L.k2 = (int)n_steps(r) * 64;
     L.n1_pad = (int)n_rowblocks(r) * kTileRows;
     L.n2_pad = (int)n_rowblocks(d_out) * kTileRows;
-    const GemmTiling t1 = choose_tiling(L.m_pad, (int)n_rowblocks(r), (int)n_steps(d_in), L.n1_pad);
-    const GemmTiling t2 = choose_tiling(L.m_pad, (int)n_rowblocks(d_out), (int)n_steps(r), L.n2_pad);
+    const GemmTiling t1 = choose_tiling(L.m_pad, (int)n_rowblocks(r), (int)n_steps(d_in), L.n1_pad, plain);
+    const GemmTiling t2 = choose_tiling(L.m_pad, (int)n_rowblocks(d_out), (int)n_steps(r), L.n2_pad, plain);
     L.tg1 = t1.tg; L.splits1 = t1.splits; L.ks1 = t1.ks;
     L.tg2 = t2.tg; L.splits2 = t2.splits; L.ks2 = t2.ks;
     if (opt(OPT_PF_TG1) >= 0) L.tg1 = opt(OPT_PF_TG1) == 2 ? 2 : 4;
@@ -824,21 +908,21 @@ static PfLayout pf_layout(int64_t d_out, int64_t d_in, int64_t r, int batch)
     return L;
 }
 
-size_t prefill_workspace_bytes(int64_t d_out, int64_t d_in, int64_t r, int batch)
+size_t prefill_workspace_bytes(int64_t d_out, int64_t d_in, int64_t r, int batch, bool plain)
 {
-    return pf_layout(d_out, d_in, r, batch).total;
+    return pf_layout(d_out, d_in, r, batch, plain).total;
 }
 
-template <int EPI>
+template <int EPI, bool PLAIN>
 static void launch_gemm(const GemmArgs& a, int tg, int ks, hipStream_t s)
 {
     const dim3 grid(a.m_tiles * a.n_tiles, a.splits), block(64 * kPfWaves * ks);
-    if (ks == 2) hipLaunchKernelGGL((prefill_gemm_kernel<EPI, 4, 2>), grid, block, 0, s, a);
-    else if (tg == 4) hipLaunchKernelGGL((prefill_gemm_kernel<EPI, 4, 1>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((prefill_gemm_kernel<EPI, 2, 1>), grid, block, 0, s, a);
+    if (ks == 2) hipLaunchKernelGGL((prefill_gemm_kernel<EPI, 4, 2, PLAIN>), grid, block, 0, s, a);
+    else if (tg == 4) hipLaunchKernelGGL((prefill_gemm_kernel<EPI, 4, 1, PLAIN>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((prefill_gemm_kernel<EPI, 2, 1, PLAIN>), grid, block, 0, s, a);
 }
 
-template <int EPI>
+template <int EPI, bool PLAIN>
 static int run_gemm(const GemmArgs& a, int tg, int ks, hipStream_t s)
 {
     if (ks == 2 && (tg != 4 || a.nst % 8 != 0 || a.steps_per_split % 8 != 0)) {
@@ -846,15 +930,27 @@ static int run_gemm(const GemmArgs& a, int tg, int ks, hipStream_t s)
         return NQ_E_INVALID_ARG;
     }
     if (a.splits > 1) {
-        launch_gemm<EPI_PARTIAL>(a, tg, ks, s);
+        launch_gemm<EPI_PARTIAL, PLAIN>(a, tg, ks, s);
         NQ_HIP(hipGetLastError());
         const size_t total = EPI == EPI_T ? (size_t)a.m_pad * (a.ldt / 16) : (size_t)a.m_pad * (a.n_pad / 4);
-        hipLaunchKernelGGL((prefill_finalize_kernel<EPI>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, a);
+        hipLaunchKernelGGL((prefill_finalize_kernel<EPI, PLAIN>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, a);
     } else {
-        launch_gemm<EPI>(a, tg, ks, s);
+        launch_gemm<EPI, PLAIN>(a, tg, ks, s);
     }
     NQ_HIP(hipGetLastError());
     return NQ_OK;
+}
+
+// A product of a p-bit and a q-bit number has at most p + q bits, p where the other is a power of two, and fp16 holds 11.  Channels
+// whose scale keeps every x of the type exact: of at most 3 significant bits for bf16 (8 bits), powers of two for fp16 and fp32
+// (whose values may be 16-bit ones widened).  From one channel in sixteen on such a layer is taken one column at a time: with
+// fewer, the pairs' rounding is at most 1.6 % more than that of the columns; general fp16 scales have one such channel in 256 or 1024.
+bool prefill_plain(const uint16_t* s_in, int64_t d_in, int x_dtype)
+{
+    const unsigned low = x_dtype == NQ_BF16 ? 0xFFu : 0x3FFu;
+    int64_t exact = 0;
+    for (int64_t i = 0; i < d_in; ++i) exact += (s_in[i] & 0x7FFFu) != 0 && (s_in[i] & low) == 0;
+    return exact * 16 >= d_in;
 }
 
 // width of a pre-scale workgroup: as many threads as the row has chunks of 16 columns for kPreHeld of them each
@@ -864,9 +960,10 @@ static int pre_threads(int lda)
     return std::min(kPreThreads, std::max(64, (need + 63) / 64 * 64));
 }
 
-int launch_prefill(const PrefillArgs& p, hipStream_t s)
+template <bool PLAIN>
+static int launch_prefill_as(const PrefillArgs& p, hipStream_t s)
 {
-    const PfLayout L = pf_layout(p.d_out, p.d_in, p.r, p.batch);
+    const PfLayout L = pf_layout(p.d_out, p.d_in, p.r, p.batch, PLAIN);
     char* ws = (char*)p.workspace;
     _Float16* xs = (_Float16*)(ws + L.off_x);
     _Float16* t = (_Float16*)(ws + L.off_t);
@@ -878,15 +975,13 @@ int launch_prefill(const PrefillArgs& p, hipStream_t s)
     // (with a rank-wise scale, |s_mid| <= 2^mid_exp, T = X''V g s_mid stays within the same bound)
     const float g_t = ldexpf(1.0f, -(lg > 1 ? lg - 1 : 0) - (p.s_mid ? p.mid_exp : 0));
 
+    const dim3 pgrid(p.batch), pblock(pre_threads(L.k1));
     if (p.x_dtype == NQ_F32)
-        hipLaunchKernelGGL(prefill_prescale_kernel<NQ_F32>, dim3(p.batch), dim3(pre_threads(L.k1)), 0, s, p.x, p.s_in, (int)p.d_in,
-                           L.k1, g_t, xs, tok_scale);
+        hipLaunchKernelGGL((prefill_prescale_kernel<NQ_F32, PLAIN>), pgrid, pblock, 0, s, p.x, p.s_in, (int)p.d_in, L.k1, g_t, xs, tok_scale);
     else if (p.x_dtype == NQ_F16)
-        hipLaunchKernelGGL(prefill_prescale_kernel<NQ_F16>, dim3(p.batch), dim3(pre_threads(L.k1)), 0, s, p.x, p.s_in, (int)p.d_in,
-                           L.k1, g_t, xs, tok_scale);
+        hipLaunchKernelGGL((prefill_prescale_kernel<NQ_F16, PLAIN>), pgrid, pblock, 0, s, p.x, p.s_in, (int)p.d_in, L.k1, g_t, xs, tok_scale);
     else
-        hipLaunchKernelGGL(prefill_prescale_kernel<NQ_BF16>, dim3(p.batch), dim3(pre_threads(L.k1)), 0, s, p.x, p.s_in, (int)p.d_in,
-                           L.k1, g_t, xs, tok_scale);
+        hipLaunchKernelGGL((prefill_prescale_kernel<NQ_BF16, PLAIN>), pgrid, pblock, 0, s, p.x, p.s_in, (int)p.d_in, L.k1, g_t, xs, tok_scale);
     NQ_HIP(hipGetLastError());
 
     GemmArgs a{};
@@ -901,7 +996,7 @@ int launch_prefill(const PrefillArgs& p, hipStream_t s)
     a.splits = L.splits1; a.steps_per_split = steps_per_split4(a.nst, a.splits, L.ks1);
     a.n_pad = L.n1_pad;
     a.m_tiles = L.m_pad / (16 * L.tg1);
-    int rc = run_gemm<EPI_T>(a, L.tg1, L.ks1, s);
+    int rc = run_gemm<EPI_T, PLAIN>(a, L.tg1, L.ks1, s);
     if (rc != NQ_OK) return rc;
     // gemm2: y = T U^T
     a.act = t; a.lda = L.k2; a.tiles = p.u_tiles;
@@ -911,7 +1006,12 @@ int launch_prefill(const PrefillArgs& p, hipStream_t s)
     a.splits = L.splits2; a.steps_per_split = steps_per_split4(a.nst, a.splits, L.ks2);
     a.n_pad = L.n2_pad;
     a.m_tiles = L.m_pad / (16 * L.tg2);
-    return run_gemm<EPI_Y>(a, L.tg2, L.ks2, s);
+    return run_gemm<EPI_Y, PLAIN>(a, L.tg2, L.ks2, s);
+}
+
+int launch_prefill(const PrefillArgs& p, hipStream_t s)
+{
+    return p.plain ? launch_prefill_as<true>(p, s) : launch_prefill_as<false>(p, s);
 }
 
 }  // namespace nq

@@ -59,6 +59,34 @@ def test_odd_row_lengths(d_out, d_in, r, batch, x_dtype, y_dtype):
     L.close()
 
 
+@pytest.mark.parametrize("d_out,d_in,r,batch", [(5, 7, 3, 12), (130, 65, 129, 33), (260, 300, 200, 70), (129, 255, 65, 100)])
+@pytest.mark.parametrize("tg,splits,ks", [(None, None, None), (2, 1, 1), (4, 1, 1), (4, 3, 1), (4, 1, 2), (4, 2, 2)])
+@pytest.mark.parametrize("x_dtype", ["f32", "f16", "bf16"])
+def test_exact_scaled_activations_are_not_rounded(nqopt, d_out, d_in, r, batch, tg, splits, ks, x_dtype):
+    """Where s_in leaves s_in (.) x exact in fp16 (powers of two; up to 3 significant bits beside bf16) the first product has no
+    rounding: T is the exact product rounded once to fp16, and y, whose sums fit fp32 here, follows bit for bit.  Sums of two
+    such columns need more than 11 bits."""
+    for name, v in (("pf_tg", tg), ("pf_splits", splits), ("pf_ks", ks)):
+        if v:
+            nqopt.set(name + "1", v)
+            nqopt.set(name + "2", v)
+    rng = np.random.default_rng(8600 + r + batch)
+    s_in = rng.choice([1.0, 1.25, 1.5, 1.75] if x_dtype == "bf16" else [0.25, 0.5, 1.0], d_in).astype(np.float16)
+    top = 255 if x_dtype == "bf16" else 2047
+    x = rng.integers(-top, top + 1, (batch, d_in)).astype(np.float64)
+    x[:, 0] = top                                     # (the token's power of two is then the same for every token)
+    U, V = synth.gen_sign_words(d_out, r, 8701), synth.gen_sign_words(d_in, r, 8702)
+    L = Layer(d_out, d_in, r, x_dtype, data=synth.LayerData(synth.LinearShape("t", d_out, d_in, r), U, V,
+                                                            np.ones(d_out, dtype=np.float16), s_in))
+    t = (x * s_in.astype(np.float64)) @ signs(V, r)
+    T = t.astype(np.float16).astype(np.float64)
+    assert np.abs(t).max() < 65504 and 4 * np.abs(T).sum(1).max() < 2**24
+    xs = (x.astype(np.float32).view(np.uint32) >> 16).astype(np.uint16) if x_dtype == "bf16" else x.astype({"f32": np.float32, "f16": np.float16}[x_dtype])
+    assert np.array_equal(synth.x_as_f64(xs, x_dtype), x)
+    assert np.array_equal(L.forward(xs), (T @ signs(U, r).T).astype(np.float32))
+    L.close()
+
+
 def test_values_at_the_ends_of_the_range():
     """Tokens at the ends of the path's range keep their precision: the per-token power of two is clamped to 2^-100 .. 2^100, and
     x'' has to stay within fp16 with its pair sums (2^16), so max|x'| < 2^115 / 2 (larger tokens give infinities and NaN);
