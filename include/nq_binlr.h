@@ -160,7 +160,9 @@ int nq_binlr_reserved(nq_handle h, int* max_batch, size_t* workspace_bytes);
  * Not re-entrant on one handle (the handle's workspace is shared); different
  * handles may run concurrently on different streams.
  * batch <= 8: streaming kernels (exact integer accumulation); >= 9: dense MFMA path
- * (fp16 operands, fp32 accumulation), unless the layer was created with NQ_FLAG_NO_PREFILL. */
+ * (fp16 operands with a power of two per token, fp32 accumulation; a token with max|s_in (.) x| of
+ * 65504 * 2^100 or more leaves their range and yields infinities or NaN), unless the layer was created
+ * with NQ_FLAG_NO_PREFILL. */
 int nq_binlr_forward(nq_handle h, const void* x, void* y, int batch, void* stream);
 
 /* nq_binlr_forward for callers that cannot allocate device memory or rely on a workspace the

@@ -1,8 +1,8 @@
 // Dense (prefill, batch >= 9) path of  y = s_out (.) (U (V^T (s_in (.) x)))   (Section 3.1 Eq. 1;
 // Appendix E.3, "Binary GEMM Inference"): both contractions run on the fp16 matrix cores of gfx950.
 //
-//   pre   : x'' = s_in (.) x * 2^a_b                  per token b, 2^a_b puts max|x''| in [2^12, 2^13)
-//   gemm1 : T   = (X'' V) * g                         g = power of two so that |T| <= 2^14 always
+//   pre   : x'' = s_in (.) x * 2^a_b                  per token b, 2^a_b puts max|x''| in [2^12, 2^13), clamped for max|x'| >= 2^113
+//   gemm1 : T   = (X'' V) * g                         g = power of two so that |T| <= 2^14 for all data short of the clamp
 //   gemm2 : y   = (T U^T) (.) s_out / (2^a_b * g)     fp32 accumulation throughout
 //
 // A product with signs, two columns at a time, on the SPARSE matrix instruction.  For signs s1, s2 of a pair of columns
@@ -179,7 +179,7 @@ constexpr int kPreHeld = 2;
 template <int DT, bool PLAIN>
 __global__ void __launch_bounds__(kPreThreads)
 prefill_prescale_kernel(const void* __restrict__ x, const uint16_t* __restrict__ s_in, int d_in, int lda,
-                        float g_t, _Float16* __restrict__ xs, float* __restrict__ tok_scale)
+                        float g_t, int a_min, _Float16* __restrict__ xs, float* __restrict__ tok_scale)
 {
     __shared__ float sm[kPreThreads / 64];
     constexpr int x_dtype = DT;
@@ -287,7 +287,7 @@ prefill_prescale_kernel(const void* __restrict__ x, const uint16_t* __restrict__
         int e;
         (void)frexpf(m, &e);
         int a = 13 - e;
-        a = a > 100 ? 100 : (a < -100 ? -100 : a);
+        a = a > 100 ? 100 : (a < a_min ? a_min : a);
         sc = ldexpf(1.0f, a);
     }
     // chunk c = columns 16 (c & 3) .. of step c >> 2
@@ -975,13 +975,18 @@ static int launch_prefill_as(const PrefillArgs& p, hipStream_t s)
     // (with a rank-wise scale, |s_mid| <= 2^mid_exp, T = X''V g s_mid stays within the same bound)
     const float g_t = ldexpf(1.0f, -(lg > 1 ? lg - 1 : 0) - (p.s_mid ? p.mid_exp : 0));
 
+    // The token's power of two is clamped to 2^a_min .. 2^100: from max|x'| = 2^113 on x'' grows with it, up to 2^16 at 2^116 where fp16 and
+    // with it the path's range end.  Sums of pairs are twice that, so they are clamped at 2^-101 (short of that only where the
+    // token's factor 1 / (2^a g) would leave fp32).
+    const bool room = 101 + (lg > 1 ? lg - 1 : 0) + (p.s_mid ? p.mid_exp : 0) <= 127;
+    const int a_min = !PLAIN && room ? -101 : -100;
     const dim3 pgrid(p.batch), pblock(pre_threads(L.k1));
     if (p.x_dtype == NQ_F32)
-        hipLaunchKernelGGL((prefill_prescale_kernel<NQ_F32, PLAIN>), pgrid, pblock, 0, s, p.x, p.s_in, (int)p.d_in, L.k1, g_t, xs, tok_scale);
+        hipLaunchKernelGGL((prefill_prescale_kernel<NQ_F32, PLAIN>), pgrid, pblock, 0, s, p.x, p.s_in, (int)p.d_in, L.k1, g_t, a_min, xs, tok_scale);
     else if (p.x_dtype == NQ_F16)
-        hipLaunchKernelGGL((prefill_prescale_kernel<NQ_F16, PLAIN>), pgrid, pblock, 0, s, p.x, p.s_in, (int)p.d_in, L.k1, g_t, xs, tok_scale);
+        hipLaunchKernelGGL((prefill_prescale_kernel<NQ_F16, PLAIN>), pgrid, pblock, 0, s, p.x, p.s_in, (int)p.d_in, L.k1, g_t, a_min, xs, tok_scale);
     else
-        hipLaunchKernelGGL((prefill_prescale_kernel<NQ_BF16, PLAIN>), pgrid, pblock, 0, s, p.x, p.s_in, (int)p.d_in, L.k1, g_t, xs, tok_scale);
+        hipLaunchKernelGGL((prefill_prescale_kernel<NQ_BF16, PLAIN>), pgrid, pblock, 0, s, p.x, p.s_in, (int)p.d_in, L.k1, g_t, a_min, xs, tok_scale);
     NQ_HIP(hipGetLastError());
 
     GemmArgs a{};

@@ -88,9 +88,8 @@ def test_exact_scaled_activations_are_not_rounded(nqopt, d_out, d_in, r, batch, 
 
 
 def test_values_at_the_ends_of_the_range():
-    """Tokens at the ends of the path's range keep their precision: the per-token power of two is clamped to 2^-100 .. 2^100, and
-    x'' has to stay within fp16 with its pair sums (2^16), so max|x'| < 2^115 / 2 (larger tokens give infinities and NaN);
-    infinities poison their own token only."""
+    """Tokens at the ends of the path's range keep their precision (the per-token power of two is clamped: 2^113 is the first
+    maximum that meets the clamp); infinities poison their own token only."""
     d_out, d_in, r = 200, 300, 90
     L = unit_layer(d_out, d_in, r, "f32", "f32", 8500)
     L.close()
@@ -107,4 +106,25 @@ def test_values_at_the_ends_of_the_range():
             assert not np.isfinite(y[b]).any()
         else:
             assert np.abs(y[b] - ref[b]).max() <= PREFILL_TOL * np.abs(ref[b]).max(), b
+    L.close()
+
+
+@pytest.mark.parametrize("unit", [True, False])
+def test_largest_tokens_that_fp16_operands_hold(unit):
+    """x'' fits fp16 up to max|x'| = 65504 * 2^100, and so do the sums of two columns, which have to be scaled down by one more."""
+    d_out, d_in, r = 200, 300, 90
+    s_in = np.ones(d_in, dtype=np.float16) if unit else synth.gen_scales(d_in, 8601)
+    L = Layer(d_out, d_in, r, "f32", data=synth.LayerData(
+        synth.LinearShape("t", d_out, d_in, r), synth.gen_sign_words(d_out, r, 8602), synth.gen_sign_words(d_in, r, 8603),
+        np.full(d_out, 2.0 ** -14, dtype=np.float16), s_in))
+    x = synth.gen_x(24, d_in, 8604, "f32")
+    for b in range(24):                                   # max|x'| = 2^112.125 .. 2^115.0, 2^115.875, 2^115.99
+        top = 2.0 ** (112 + (b + 1) / 8) if b < 22 else 2.0 ** (115.875 if b == 22 else 115.99)
+        xp = x[b].astype(np.float64) * s_in.astype(np.float64)
+        x[b] = (x[b].astype(np.float64) * top / np.abs(xp).max()).astype(np.float32)
+        x[b, :8] = np.sign(x[b, :8]) * np.abs(x[b].astype(np.float64) * s_in).max() / s_in[:8].astype(np.float64) * 0.999      # pairs of large columns
+    y, ref = L.forward(x), L.oracle(x)
+    assert np.isfinite(y).all()
+    for b in range(24):
+        assert np.abs(y[b] - ref[b]).max() <= PREFILL_TOL * np.abs(ref[b]).max(), b
     L.close()
