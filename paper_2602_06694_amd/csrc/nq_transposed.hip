@@ -12,10 +12,14 @@
 // a byte are the row's remaining three: operand register i of half h is (word_v >> (4h + i)) & 0x01010101, for the columns
 // 16g + 4v + b of word v.  That is 80 vector instructions per tile beside 32 matrix instructions of 16 cycles for 16 tokens.
 //
-// Fixed point with four byte slices (|q| <= 2^30 of the token's maximum), exact int32 sums, joined and scaled in binary64,
-// one rounding to fp32 when a result is stored: the error against binary64 stays that of the one rounding (3.6e-8 of the
-// result's norm on normal data, as with binary64 additions on the vector ALU, which this replaces: a gradient pass of 64
-// tokens through a 4096 x 4096 r = 1024 layer took 235 us in passes of 8 tokens, 16 launches of 2 to 12 us).
+// Fixed point with four byte slices (|q| < 2^31 of the token's maximum), exact int32 sums, joined and scaled in binary64,
+// one rounding to fp32 when a result is stored: the error against binary64 is that of this one rounding (3.6e-8 of the
+// result's norm on normal data, as with binary64 additions on the vector ALU, which this replaces: a product of 64
+// tokens with a 4096 x 4096 r = 1024 layer took 235 us in passes of 8 tokens, 16 launches of 2 to 12 us; four launches of 3 to 9
+// take 21).  The fixed point's own error is crest / 190 of that rounding, crest = the power of two above the token's maximum
+// over the root mean square of its values.  A token of normal gradients times scales has 8 to 16 (the error grows by less than 0.4 %),
+// one large element among 65536 has 256 and more: tokens with a crest above 16 take a fifth slice, 2^39, for which groups
+// of 16 tokens with such a one are read once more.  (Five slices for all: the gradients of that layer 66 -> 72 us.)
 #include <algorithm>
 
 #include "nq_internal.h"
@@ -23,12 +27,13 @@
 
 namespace nq {
 
-constexpr int kTSlices = 4;
+constexpr int kTSlices = 4;             // slices of every token; kTSlices + 1 of a wide one
 constexpr int kTWaves = 8;              // waves of a workgroup share one (64 columns, 16 tokens) result: they split its row blocks
 constexpr int kTTokens = 16;            // tokens of a workgroup: the 16 columns of one matrix instruction, one slice at a time
 // the fixed-point bytes of a group of 16 tokens per 128-row block, [half][slice][token][4 pieces][16]: what one load instruction
 // of the product kernel fetches is 1 KiB in one piece
 constexpr uint32_t kTGroupRbBytes = 2 * kTSlices * 16 * 64;
+constexpr uint32_t kTGroupRbBytes5 = 2 * 16 * 64;       // the fifth slices, in a region of their own: [half][token][4 pieces][16]
 
 // ---------------------------------------------------------------------------------------------
 // scaled input -> fixed point.  One workgroup per token.  A thread owns pieces: piece (s, c) of a token holds, as four words
@@ -38,7 +43,9 @@ struct TQuantArgs {
     const void* in;             // [batch][in_stride] of in_dtype
     const uint16_t* scale;      // fp16 [M] or nullptr
     uint8_t* bq;                // [groups of 16 tokens][n_pieces / 4][slices][16 tokens][4][16]
+    uint8_t* bq5;               // [groups of 16 tokens][n_pieces / 4][16 tokens][4][16]: the fifth slice, of wide tokens only
     QMeta* meta;                // [batch]
+    uint32_t* wide;             // [batch] whether the token has a fifth slice
     int M, in_dtype, in_stride;
     int n_pieces;               // 4 per 64 rows, whole row blocks
 };
@@ -97,30 +104,49 @@ __device__ __forceinline__ void tq_load(const TQuantArgs& a, size_t base, int pc
     }
 }
 
-// q of 16 values -> the four slices of their piece (slices 1 KiB apart); returns sum q
-__device__ __forceinline__ long long tq_store(const double v[16], double inv_step, bool bad, uint8_t* dst)
+// low 32 bits of a binary64
+__device__ __forceinline__ int low_word(double v) { return (int)(uint32_t)__builtin_bit_cast(uint64_t, v); }
+
+// q of 16 values -> the slices of their piece (slices 1 KiB apart); returns sum q.
+// q (WIDE: hi and lo with q = 2^24 hi + lo) is taken from the low bits of a sum with a constant that leaves it no fraction: rounding
+// and converting instructions for binary64 are several times as slow.
+template <bool WIDE>
+__device__ __forceinline__ double tq_store(const double v[16], double inv_step, bool bad, uint8_t* dst, uint8_t* dst5)
 {
+    constexpr int kS = kTSlices + (WIDE ? 1 : 0);
+    constexpr double kLo = 0x1.8p52, kHi = 0x1.8p76;
+    const auto low_word = [](double x) { return (int)(uint32_t)__builtin_bit_cast(uint64_t, x); };
     long long sum = 0;
-    uint32_t w[kTSlices][4];
+    uint32_t w[kS][4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        uint32_t d[kTSlices][4];
+        uint32_t d[kS][4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            int q = bad ? 0 : (int)rint(v[4 * i + k] * inv_step);          // |q| <= 2^30
-            sum += q;
+            int hi = 0, b;
+            if (WIDE) {
+                const double at = fma(v[4 * i + k], inv_step, kHi);
+                hi = low_word(at);                                              // |hi| <= 2^15
+                b = low_word(fma(v[4 * i + k], inv_step, kHi - at) + kLo);      // |lo| <= 2^23
+                sum += ((long long)hi << 24) + b;
+            } else {
+                b = bad ? 0 : low_word(fma(v[4 * i + k], inv_step, kLo));       // |q| < 0.992 * 2^31
+                sum += b;
+            }
+            // the signed bytes from the lowest up (slice kS - 1); WIDE: those of lo, then of hi plus what lo carries
 #pragma unroll
-            for (int s = kTSlices - 1; s >= 0; --s) {                       // slice kTSlices - 1 is the lowest byte
-                d[s][k] = (uint32_t)q;
-                q = (q + 128) >> 8;
+            for (int s = kS - 1; s >= 0; --s) {
+                if (WIDE && s == kS - 4) b += hi;
+                d[s][k] = (uint32_t)b;
+                b = (b + 128) >> 8;
             }
         }
 #pragma unroll
-        for (int s = 0; s < kTSlices; ++s) w[s][i] = pack_low_bytes(d[s][0], d[s][1], d[s][2], d[s][3]);
+        for (int s = 0; s < kS; ++s) w[s][i] = pack_low_bytes(d[s][0], d[s][1], d[s][2], d[s][3]);
     }
 #pragma unroll
-    for (int s = 0; s < kTSlices; ++s) *(uint4*)(dst + s * 1024) = make_uint4(w[s][0], w[s][1], w[s][2], w[s][3]);
-    return sum;
+    for (int s = 0; s < kS; ++s) *(uint4*)(s < kTSlices ? dst + s * 1024 : dst5) = make_uint4(w[s][0], w[s][1], w[s][2], w[s][3]);
+    return (double)sum;                                                         // below 2^44
 }
 
 constexpr int kTQThreads = 512;         // most threads of a workgroup; short vectors take as many as they have pieces
@@ -128,11 +154,11 @@ constexpr int kTQThreads = 512;         // most threads of a workgroup; short ve
 template <int DT>
 __global__ void __launch_bounds__(kTQThreads) quantize_t_kernel(TQuantArgs a)
 {
-    __shared__ double sm_max[kTQThreads / 64], sm_sum[kTQThreads / 64];
+    __shared__ double sm_max[kTQThreads / 64], sm_sum[kTQThreads / 64], sm_sq[kTQThreads / 64];
     __shared__ int sm_bad[kTQThreads / 64];
     const int tok = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, threads = blockDim.x;
     const size_t base = (size_t)tok * a.in_stride;
-    double v[16], m = 0.0;
+    double v[16], m = 0.0, sq = 0.0;
     int bad = 0;
     // (a thread's first piece stays in registers between the two passes; longer vectors re-read the others)
     for (int pc = tid + ((a.n_pieces - 1 - tid) / threads) * threads; pc >= 0; pc -= threads) {
@@ -143,36 +169,48 @@ __global__ void __launch_bounds__(kTQThreads) quantize_t_kernel(TQuantArgs a)
             const double t = fabs(v[i]);
             if (!(t <= 1.0e300)) bad = 1;                   // NaN or infinity
             m = fmax(m, t);
+            sq = fma(v[i], v[i], sq);
         }
     }
-    for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
+    for (int o = 32; o > 0; o >>= 1) {
+        m = fmax(m, __shfl_xor(m, o));
+        sq += __shfl_xor(sq, o);
+    }
     bad = __builtin_amdgcn_ballot_w64(bad != 0) != 0;
-    if ((tid & 63) == 0) { sm_max[wave] = m; sm_bad[wave] = bad; }
+    if ((tid & 63) == 0) { sm_max[wave] = m; sm_bad[wave] = bad; sm_sq[wave] = sq; }
     __syncthreads();
     m = sm_max[0];
     bad = sm_bad[0];
+    sq = sm_sq[0];
 #pragma unroll
-    for (int w = 1; w < threads / 64; ++w) { m = fmax(m, sm_max[w]); bad |= sm_bad[w]; }
-    // step = 2^(e - 30) with m = f 2^e, f in [0.5, 1): |q| <= 2^30
+    for (int w = 1; w < threads / 64; ++w) { m = fmax(m, sm_max[w]); bad |= sm_bad[w]; sq += sm_sq[w]; }
+    // step = 2^(e - 31), 2^(e - 39) wide, with the maximum at most 0.99 * 2^e: q fits its signed bytes, which hold +-0.996 * 2^31
     int e = 0;
-    if (m > 0.0 && !bad) (void)frexp(m, &e);
-    const double step = ldexp(1.0, e - 30), inv_step = ldexp(1.0, 30 - e);
+    if (m > 0.0 && !bad && frexp(m, &e) > 0.99) ++e;
+    const double top = ldexp(1.0, e);
+    const bool wide = m > 0.0 && !bad && (double)a.M * top * top > 256.0 * sq;
+    const double step = ldexp(1.0, e - (wide ? 39 : 31)), inv_step = ldexp(1.0, (wide ? 39 : 31) - e);
     double s = 0.0;
-    uint8_t* const dst = a.bq + (size_t)(tok >> 4) * (a.n_pieces >> 2) * (kTGroupRbBytes / 2) + (tok & 15) * 64;
+    const size_t group = (size_t)(tok >> 4) * (a.n_pieces >> 2);
+    uint8_t* const dst = a.bq + group * (kTGroupRbBytes / 2) + (tok & 15) * 64;
+    uint8_t* const dst5 = a.bq5 + group * (kTGroupRbBytes5 / 2) + (tok & 15) * 64;
     for (int pc = tid; pc < a.n_pieces; pc += threads) {
         if (pc != tid) tq_load<DT>(a, base, pc, v);
-        s += (double)tq_store(v, inv_step, bad != 0, dst + (size_t)(pc >> 2) * (kTGroupRbBytes / 2) + (pc & 3) * 16);
+        uint8_t* const to = dst + (size_t)(pc >> 2) * (kTGroupRbBytes / 2) + (pc & 3) * 16;
+        s += wide ? tq_store<true>(v, inv_step, false, to, dst5 + (size_t)(pc >> 2) * (kTGroupRbBytes5 / 2) + (pc & 3) * 16)
+                  : tq_store<false>(v, inv_step, bad != 0, to, nullptr);
     }
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);        // below 2^46: exact
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);        // below 2^53: exact
     if ((tid & 63) == 0) sm_sum[wave] = s;
     __syncthreads();
     if (tid == 0) {
         double tot = 0.0;
         for (int w = 0; w < threads / 64; ++w) tot += sm_sum[w];
         QMeta mt;
-        mt.two_step = bad ? (double)__builtin_nanf("") : 2.0 * step;
+        mt.two_step = bad ? (double)__builtin_nanf("") : ldexp(1.0, e - 38);       // (the product joins five slices, the fifth of other tokens zero)
         mt.neg_qs = -tot * step;
         a.meta[tok] = mt;
+        a.wide[tok] = wide;
     }
 }
 
@@ -184,7 +222,9 @@ __global__ void __launch_bounds__(kTQThreads) quantize_t_kernel(TQuantArgs a)
 struct TStageArgs {
     const uint32_t* tiles;
     const uint8_t* bq;
+    const uint8_t* bq5;
     const QMeta* meta;
+    const uint32_t* wide;
     const uint16_t* out_scale;      // fp16 [N] or nullptr
     float* out;                     // [batch][out_stride]
     int N, n_steps, n_rb, out_stride, batch;
@@ -206,8 +246,7 @@ template <int NV>
 __global__ void __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) gemm_t_kernel(TStageArgs a)
 {
     constexpr int kRing = 2;                                        // tiles in flight per wave
-    constexpr int kRound = NV == 4 ? 2 : kTSlices;                  // slices whose partial sums pass through LDS at a time
-    __shared__ v4i red[kRound][kTWaves][NV][64];
+    __shared__ v4i red[2][kTWaves][NV][64];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int g = lane >> 4, n = lane & 15;
@@ -221,6 +260,7 @@ __global__ void __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_
     // (what the epilogue needs is requested before the reduction, not behind it)
     const int col = st * kTileCols + 16 * g + 4 * (v0 + wave % NV);
     const double two_step = a.meta[tok].two_step, neg_qs = a.meta[tok].neg_qs;
+    const bool wide = a.wide[tok] != 0;
     float osc[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) osc[k] = a.out_scale ? half_bits_to_float(a.out_scale[col + k < a.N ? col + k : 0]) : 1.0f;
@@ -274,23 +314,56 @@ __global__ void __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_
 #undef NQ_T_ISSUE
 #undef NQ_T_MAC
 
-    // the eight partial sums of every result, through 64 KiB of LDS; wave v of the first NV takes word v0 + v
-    v4i sum[kTSlices];
+    // the eight partial sums of every result, through LDS, two slices joined (a wave has met at most 8192 rows: 2^28); wave v
+    // of the first NV takes word v0 + v
 #pragma unroll
-    for (int s = 0; s < kTSlices; ++s) sum[s] = v4i{0, 0, 0, 0};
+    for (int s = 0; s < 2; ++s)
 #pragma unroll
-    for (int s0 = 0; s0 < kTSlices; s0 += kRound) {
-        if (s0) __syncthreads();
+        for (int v = 0; v < NV; ++v) red[s][wave][v][lane] = (acc[v][2 * s] << 8) + acc[v][2 * s + 1];
+    __syncthreads();
+    double sum[2][4] = {};
+    v4i low = {0, 0, 0, 0};
+    if (wave < NV) {
 #pragma unroll
-        for (int s = 0; s < kRound; ++s)
+        for (int s = 0; s < 2; ++s)
 #pragma unroll
-            for (int v = 0; v < NV; ++v) red[s][wave][v][lane] = acc[v][s0 + s];
+            for (int k = 0; k < kTWaves; k += 4) {          // (four waves' sums stay in 32 bits)
+                const v4i p = (red[s][k][wave][lane] + red[s][k + 1][wave][lane]) + (red[s][k + 2][wave][lane] + red[s][k + 3][wave][lane]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sum[s][i] += (double)p[i];
+            }
+    }
+    if (__builtin_amdgcn_ballot_w64(wide) != 0) {           // (the same in all waves)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) acc[v][0] = v4i{0, 0, 0, 0};
+        const char* const b5_base = (const char*)a.bq5 + (size_t)blockIdx.y * a.n_rb * kTGroupRbBytes5 + 64 * n + 16 * g;
+        for (int r = wave; r < a.n_rb; r += kTWaves) {
+            const vNu wr = *(const __attribute__((address_space(1))) vNu*)(w_base + (size_t)r * w_rb);
+            v4u br[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                br[h] = load_global_v4u(b5_base + (size_t)r * kTGroupRbBytes5, (uint32_t)(h * 1024));
+                if (!wide) br[h] = v4u{0, 0, 0, 0};         // (never written for this token)
+            }
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const uint32_t t = quad_transpose(wr[v], sel2, sel1);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    v4u op;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) op[i] = (t >> (4 * h + i)) & 0x01010101u;
+                    acc[v][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8((v4i)op, (v4i)br[h], acc[v][0], 0, 0, 0);
+                }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < NV; ++v) red[0][wave][v][lane] = acc[v][0];
         __syncthreads();
         if (wave < NV) {
 #pragma unroll
-            for (int s = 0; s < kRound; ++s)
-#pragma unroll
-                for (int k = 0; k < kTWaves; ++k) sum[s0 + s] += red[s][k][wave][lane];
+            for (int k = 0; k < kTWaves; ++k) low += red[0][k][wave][lane];
         }
     }
     if (wave >= NV || t0 + n >= a.batch) return;
@@ -298,10 +371,8 @@ __global__ void __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_
     float r[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        // below 2^46: exact; so is the product with the power of two, and the difference needs at most 48 bits
-        double raw = (double)sum[0][k];
-#pragma unroll
-        for (int s = 1; s < kTSlices; ++s) raw = fma(raw, 256.0, (double)sum[s][k]);
+        // (below 2^47 without the fifth slice, then 2^55: rounded in binary64 at most)
+        const double raw = fma(fma(sum[0][k], 65536.0, sum[1][k]), 256.0, (double)low[k]);
         double val = fma(raw, two_step, neg_qs);
         val *= (double)osc[k];
         r[k] = (float)val;
@@ -320,7 +391,8 @@ static size_t al256(size_t v) { return (v + 255) / 256 * 256; }
 
 size_t gemm_t_scratch_bytes(int64_t M, int batch)
 {
-    return (size_t)((batch + kTTokens - 1) / kTTokens) * n_rowblocks(M) * kTGroupRbBytes + al256((size_t)batch * sizeof(QMeta));
+    return (size_t)((batch + kTTokens - 1) / kTTokens) * n_rowblocks(M) * (kTGroupRbBytes + kTGroupRbBytes5) + al256((size_t)batch * sizeof(QMeta)) +
+           al256((size_t)batch * sizeof(uint32_t));
 }
 
 // A is [M][N] as sign tiles; out[tok][0..N) = out_scale (.) A^T (in_scale (.) in[tok][0..M)).  `scratch`: device,
@@ -330,14 +402,16 @@ int launch_gemm_t(const uint32_t* tiles, int64_t M, int64_t N, const void* in, i
 {
     const int n_rb = (int)n_rowblocks(M);
     uint8_t* bq = (uint8_t*)scratch;
-    QMeta* meta = (QMeta*)(bq + (size_t)((batch + kTTokens - 1) / kTTokens) * n_rb * kTGroupRbBytes);
-    const TQuantArgs q{in, in_scale, bq, meta, (int)M, in_dtype, in_stride, n_rb * 8};
+    uint8_t* bq5 = bq + (size_t)((batch + kTTokens - 1) / kTTokens) * n_rb * kTGroupRbBytes;
+    QMeta* meta = (QMeta*)(bq5 + (size_t)((batch + kTTokens - 1) / kTTokens) * n_rb * kTGroupRbBytes5);
+    uint32_t* wide = (uint32_t*)((char*)meta + al256((size_t)batch * sizeof(QMeta)));
+    const TQuantArgs q{in, in_scale, bq, bq5, meta, wide, (int)M, in_dtype, in_stride, n_rb * 8};
     const dim3 qgrid(batch), qblock(std::min(kTQThreads, (q.n_pieces + 63) / 64 * 64));
     if (in_dtype == NQ_F32) hipLaunchKernelGGL(quantize_t_kernel<NQ_F32>, qgrid, qblock, 0, s, q);
     else if (in_dtype == NQ_F16) hipLaunchKernelGGL(quantize_t_kernel<NQ_F16>, qgrid, qblock, 0, s, q);
     else hipLaunchKernelGGL(quantize_t_kernel<NQ_BF16>, qgrid, qblock, 0, s, q);
     NQ_HIP(hipGetLastError());
-    const TStageArgs t{tiles, bq, meta, out_scale, out, (int)N, (int)n_steps(N), n_rb, out_stride, batch};
+    const TStageArgs t{tiles, bq, bq5, meta, wide, out_scale, out, (int)N, (int)n_steps(N), n_rb, out_stride, batch};
     const int steps = (int)((N + kTileCols - 1) / kTileCols), groups = (batch + kTTokens - 1) / kTTokens;
     // half tiles where whole ones leave more than half of the CUs without a workgroup (16 steps x 4 groups: 8.3 us against 10)
     if (steps * groups <= device_cu_count() / 2)

@@ -47,5 +47,5 @@ def test_exact_and_transposed_products_in_every_split(d_out, d_in, r, batch):
     U, V = (nq.nq_unpack_signs(m, r).astype(np.float64) for m in (d.U_words, d.V_words))
     ref = ((g_np.astype(np.float64) * d.s_out.astype(np.float64)) @ U) @ V.T
     err = np.linalg.norm(w.cpu().numpy() - ref, axis=1) / np.linalg.norm(ref, axis=1)
-    assert err.max() <= 2 * 2.0 ** -24          # two roundings to fp32; the fixed point is 2^-31 of a token's maximum
+    assert err.max() <= 2 * 2.0 ** -24          # two roundings to fp32; the fixed point's is below a tenth of that
     L.close()

@@ -10,7 +10,7 @@ from gpu_util import Layer, to_device
 pytestmark = pytest.mark.gpu
 
 # u = U^T(..) and w = V u are each rounded once to fp32 (relative 2-norm error 2^-24 / sqrt(3) each for values spread over
-# their binade, at most 2^-24); the fixed point behind them is 2^-31 of a token's maximum, below a tenth of that here.
+# their binade, at most 2^-24); the fixed point behind them is below a tenth of that.
 NORM_TOL = 2 * 2.0**-24
 
 
@@ -47,6 +47,47 @@ def test_transposed_products_at_the_edges(d_out, d_in, r, batch, dt):
     for t in range(batch):                   # token by token: each has its own fixed-point step
         assert _norm_err(w[t].cpu().numpy(), ref[t]) <= NORM_TOL, t
         assert _norm_err(dx[t].cpu().numpy(), ref[t] * L.data.s_in.astype(np.float64)) <= NORM_TOL, t
+    L.close()
+
+
+def test_one_large_element_among_many_costs_no_precision():
+    """The fixed point's step follows a token's maximum: one element 2^20 times the others must not cost the sum of the
+    65536 others its precision (a step of 2^-30 of the maximum misses the bound)."""
+    import torch
+    d_out, d_in, r, batch = 65536, 64, 64, 3
+    L = Layer(d_out, d_in, r, "f32", seed=5400)
+    g_np = synth.gen_x(batch, d_out, 5401, "f32")
+    at = [17, 40000, 65535]
+    for t in range(batch):
+        g_np[t, at[t]] = np.float32(2.0**20)
+    w = torch.full((batch, d_in), float("nan"), dtype=torch.float32, device="cuda")
+    nq.nq_binlr_forward_transposed_unscaled(L.h, to_device(g_np, "f32"), w, batch)
+    torch.cuda.synchronize()
+    ref = _reference(L, g_np.astype(np.float64))
+    for t in range(batch):
+        assert _norm_err(w[t].cpu().numpy(), ref[t]) <= NORM_TOL, t
+    L.close()
+
+
+@pytest.mark.parametrize("d_out,d_in,r,batch", [(2100, 300, 70, 5), (300, 130, 64, 19), (1500, 200, 4200, 40)])
+def test_wide_tokens_are_exact_beside_others(d_out, d_in, r, batch):
+    """Two elements of 2^36 that cancel in every column leave sums of small integers, which only a fifth byte slice holds: bit for
+    bit, in tokens with and without such a pair side by side, on half and on whole tiles (the last: 66 steps x 3 groups)."""
+    import torch
+    U_words, V_words = synth.gen_sign_words(d_out, r, 5501), synth.gen_sign_words(d_in, r, 5502)
+    rows = [(3, 131), (0, d_out - 1), (d_out // 2, 17)]
+    for a, b in rows:
+        U_words[b] = U_words[a]
+    ones = lambda n: np.ones(n, dtype=np.float16)
+    L = Layer(d_out, d_in, r, "f32", data=synth.LayerData(synth.LinearShape("t", d_out, d_in, r), U_words, V_words, ones(d_out), ones(d_in)))
+    g_np = np.random.default_rng(5503).integers(-100, 101, (batch, d_out)).astype(np.float32)
+    for t in range(0, batch, 3):
+        a, b = rows[t // 3 % 3]
+        g_np[t, a], g_np[t, b] = 2.0**36, -2.0**36
+    w = torch.full((batch, d_in), float("nan"), dtype=torch.float32, device="cuda")
+    nq.nq_binlr_forward_transposed_unscaled(L.h, to_device(g_np, "f32"), w, batch)
+    torch.cuda.synchronize()
+    assert np.array_equal(w.cpu().numpy(), _reference(L, g_np.astype(np.float64)).astype(np.float32))
     L.close()
 
 
