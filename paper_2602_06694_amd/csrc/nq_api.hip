@@ -4,7 +4,6 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
-#include <memory>
 #include <mutex>
 #include <vector>
 
@@ -407,6 +406,9 @@ static int create_layer(nq_handle* out, int64_t d_out, int64_t d_in, int64_t r, 
     // decode workspace
     const size_t ws_total = carve_workspace(nullptr, nullptr, d_in, r, NQ_DECODE_MAX_BATCH);
 
+    static std::mutex mutex;
+    static int* answer = nullptr;
+    std::unique_lock<std::mutex> lk(mutex, std::defer_lock);
     uint32_t* d_canon = nullptr;
     const size_t canon_u = (size_t)d_out * wpr * 4, canon_v = (size_t)d_in * wpr * 4;
     int rc = NQ_OK;
@@ -432,6 +434,15 @@ static int create_layer(nq_handle* out, int64_t d_out, int64_t d_in, int64_t r, 
         (void)carve_workspace(&h->ws, (char*)h->ws_alloc, d_in, r, NQ_DECODE_MAX_BATCH);
     }
     CREATE_HIP(hipMemset(h->ws_alloc, 0, ws_total));
+    CREATE_HIP(hipMemcpy(h->s_in, s_in_fp16, (size_t)d_in * 2, kind));
+    if (from_device) {
+        // scales on the device are looked at there, beside the rest (copying them to the host took 45 us of a creation of 140): one
+        // word of host memory for the answer, one creation at a time
+        lk.lock();
+        if (!answer) CREATE_HIP(hipHostMalloc((void**)&answer, sizeof(int), hipHostMallocPortable));
+        rc = launch_prefill_plain(h->s_in, d_in, x_dtype, answer);
+        if (rc != NQ_OK) goto done;
+    }
     CREATE_HIP(hipMemcpy(d_canon, V_words, canon_v, kind));
     rc = launch_repack(d_canon, wpr, true, r, d_in, h->vt_tiles, nullptr);
     if (rc != NQ_OK) goto done;
@@ -439,15 +450,9 @@ static int create_layer(nq_handle* out, int64_t d_out, int64_t d_in, int64_t r, 
     CREATE_HIP(hipMemcpy(d_canon, U_words, canon_u, kind));
     rc = launch_repack(d_canon, wpr, false, d_out, r, h->u_tiles, nullptr);
     if (rc != NQ_OK) goto done;
-    CREATE_HIP(hipMemcpy(h->s_in, s_in_fp16, (size_t)d_in * 2, kind));
     CREATE_HIP(hipMemcpy(h->s_out, s_out_fp16, (size_t)d_out * 2, kind));
-    {
-        std::unique_ptr<uint16_t[]> copy(from_device ? new (std::nothrow) uint16_t[d_in] : nullptr);
-        if (from_device && !copy) { rc = fail(NQ_E_HIP, "nq_binlr_create: out of host memory"); goto done; }
-        if (from_device) CREATE_HIP(hipMemcpy(copy.get(), s_in_fp16, (size_t)d_in * 2, hipMemcpyDeviceToHost));
-        h->pf_plain = prefill_plain(from_device ? copy.get() : s_in_fp16, d_in, x_dtype);
-    }
     CREATE_HIP(hipDeviceSynchronize());
+    h->pf_plain = from_device ? *answer != 0 : prefill_plain(s_in_fp16, d_in, x_dtype);
 #undef CREATE_HIP
 done:
     if (d_canon) (void)hipFree(d_canon);

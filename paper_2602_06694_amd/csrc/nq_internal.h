@@ -335,6 +335,7 @@ struct PrefillArgs {
 };
 // whether a layer's s_in (fp16, host) leaves s_in (.) x exact in fp16 on enough channels that rounding pair sums would lose precision
 bool prefill_plain(const uint16_t* s_in, int64_t d_in, int x_dtype);
+int launch_prefill_plain(const uint16_t* d_s_in, int64_t d_in, int x_dtype, int* answer);      // s_in on the device; default stream
 size_t prefill_workspace_bytes(int64_t d_out, int64_t d_in, int64_t r, int batch, bool plain);
 int launch_prefill(const PrefillArgs& a, hipStream_t s);
 

@@ -945,12 +945,37 @@ static int run_gemm(const GemmArgs& a, int tg, int ks, hipStream_t s)
 // whose scale keeps every x of the type exact: of at most 3 significant bits for bf16 (8 bits), powers of two for fp16 and fp32
 // (whose values may be 16-bit ones widened).  From one channel in sixteen on such a layer is taken one column at a time: with
 // fewer, the pairs' rounding is at most 1.6 % more than that of the columns; general fp16 scales have one such channel in 256 or 1024.
+__host__ __device__ static int plain_channel(uint16_t s, int x_dtype)
+{
+    return (s & 0x7FFFu) != 0 && (s & (x_dtype == NQ_BF16 ? 0xFFu : 0x3FFu)) == 0;
+}
+static __host__ __device__ bool plain_layer(int64_t channels, int64_t d_in) { return channels * 16 >= d_in; }
+
 bool prefill_plain(const uint16_t* s_in, int64_t d_in, int x_dtype)
 {
-    const unsigned low = x_dtype == NQ_BF16 ? 0xFFu : 0x3FFu;
-    int64_t exact = 0;
-    for (int64_t i = 0; i < d_in; ++i) exact += (s_in[i] & 0x7FFFu) != 0 && (s_in[i] & low) == 0;
-    return exact * 16 >= d_in;
+    int64_t n = 0;
+    for (int64_t i = 0; i < d_in; ++i) n += plain_channel(s_in[i], x_dtype);
+    return plain_layer(n, d_in);
+}
+
+__global__ void __launch_bounds__(1024) prefill_plain_kernel(const uint16_t* s_in, int d_in, int x_dtype, int* answer)
+{
+    __shared__ int sm[16];
+    int n = 0;
+    for (int i = threadIdx.x; i < d_in; i += 1024) n += plain_channel(s_in[i], x_dtype);
+    for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = n;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int w = 1; w < 16; ++w) n += sm[w];
+    *answer = plain_layer(n, d_in);
+}
+
+int launch_prefill_plain(const uint16_t* d_s_in, int64_t d_in, int x_dtype, int* answer)
+{
+    hipLaunchKernelGGL(prefill_plain_kernel, dim3(1), dim3(1024), 0, nullptr, d_s_in, (int)d_in, x_dtype, answer);
+    NQ_HIP(hipGetLastError());
+    return NQ_OK;
 }
 
 // width of a pre-scale workgroup: as many threads as the row has chunks of 16 columns for kPreHeld of them each

@@ -7,7 +7,7 @@ import pytest
 
 from paper_2602_06694_amd import binding as nq
 from paper_2602_06694_amd import synth
-from gpu_util import Layer, check_rounded, rel_err
+from gpu_util import Layer, check_rounded, new_output, rel_err, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -56,6 +56,27 @@ def test_odd_row_lengths(d_out, d_in, r, batch, x_dtype, y_dtype):
         assert rel_err(y, ref) <= PREFILL_TOL
     else:
         check_rounded(y, ref, y_dtype, PREFILL_TOL)
+    L.close()
+
+
+@pytest.mark.parametrize("d_out,d_in,r,batch", [
+    (1, 1, 1, 9), (5, 7, 3, 12), (130, 9, 17, 33), (127, 15, 64, 64), (128, 16, 65, 65), (129, 63, 127, 63), (64, 65, 129, 31),
+    (513, 257, 200, 100), (640, 1000, 385, 130), (1027, 511, 700, 70), (300, 2047, 520, 257)])
+@pytest.mark.parametrize("tg,splits,ks", [(None, None, None), (2, 1, 1), (4, 1, 1), (4, 3, 1), (4, 1, 2), (4, 2, 2)])
+def test_small_integers_are_exact_in_pairs(nqopt, d_out, d_in, r, batch, tg, splits, ks):
+    """The same with s_in = 3: such layers take pairs (fp32 activations times 3 are not in general exact in fp16)."""
+    for name, v in (("pf_tg", tg), ("pf_splits", splits), ("pf_ks", ks)):
+        if v:
+            nqopt.set(name + "1", v)
+            nqopt.set(name + "2", v)
+    U, V = synth.gen_sign_words(d_out, r, 8801 + r), synth.gen_sign_words(d_in, r, 8802 + r)
+    L = Layer(d_out, d_in, r, "f32", data=synth.LayerData(synth.LinearShape("t", d_out, d_in, r), U, V,
+                                                          np.ones(d_out, dtype=np.float16), np.full(d_in, 3.0, dtype=np.float16)))
+    x = np.random.default_rng(8900 + batch).integers(-1, 2, (batch, d_in))
+    t = 3 * x @ signs(V, r)
+    assert 2 * np.abs(t).max() <= 2048
+    y = L.forward(x.astype(np.float32))
+    assert np.array_equal(y, (t @ signs(U, r).T).astype(np.float32))
     L.close()
 
 
@@ -128,3 +149,27 @@ def test_largest_tokens_that_fp16_operands_hold(unit):
     for b in range(24):
         assert np.abs(y[b] - ref[b]).max() <= PREFILL_TOL * np.abs(ref[b]).max(), b
     L.close()
+
+
+def test_scales_on_the_device_choose_the_same_form():
+    """Layers created from device memory take columns or pairs as those created from host memory do: same bits."""
+    import torch
+    d_out, d_in, r, batch = 130, 1500, 90, 20
+    x = to_device(synth.gen_x(batch, d_in, 9001, "bf16"), "bf16")
+    U, V = synth.gen_sign_words(d_out, r, 9002), synth.gen_sign_words(d_in, r, 9003)
+    general = synth.gen_scales(d_in, 9004)
+    for exact in (0, 93, 94, d_in):                       # powers of two among 1500 scales: 94 are one in sixteen
+        s_in = np.where(general.view(np.uint16) & 0xFF, general, np.float16(0.7)).astype(np.float16)
+        s_in[:exact] = np.float16(0.5)
+        L = Layer(d_out, d_in, r, "bf16", data=synth.LayerData(synth.LinearShape("t", d_out, d_in, r), U, V,
+                                                               synth.gen_scales(d_out, 9005), s_in))
+        dev = [torch.from_numpy(np.ascontiguousarray(a).view(np.int32 if a.dtype == np.uint32 else np.int16).copy()).cuda()
+               for a in (U, V, L.data.s_out, s_in)]
+        h = nq.nq_binlr_create_from_device(d_out, d_in, r, *dev, nq.NQ_BF16, nq.NQ_F32)
+        a, b = new_output(batch, d_out), new_output(batch, d_out)
+        nq.nq_binlr_forward(L.h, x, a, batch)
+        nq.nq_binlr_forward(h, x, b, batch)
+        torch.cuda.synchronize()
+        assert torch.equal(a, b), exact
+        nq.nq_binlr_destroy(h)
+        L.close()
