@@ -144,13 +144,15 @@ int nq_binlr_set_mid_scale(nq_handle h, const uint16_t* s_mid_fp16);
 
 /* Grow the per-layer workspace so that forwards with ANY batch <= max_batch allocate nothing
  * (the dense path's need is not monotone in the batch; the largest need up to max_batch is taken).
- * Also holds, from a max_batch of 9 on, the exact path's workspace for passes of up to max_batch tokens
- * (about 8 MiB at most, or 64 tokens): nq_binlr_forward_exact, nq_binlr_forward_unscaled and
- * NQ_FLAG_NO_PREFILL layers take such passes instead of passes of 8; the results are the same bits.
- * May allocate and synchronise. */
+ * The exact path's passes of more than eight tokens use the same memory: it is made large enough for passes of
+ * max_batch tokens, of as many as fit about 8 MiB (at least 64) where that is less, and nq_binlr_forward_exact,
+ * nq_binlr_forward_unscaled and NQ_FLAG_NO_PREFILL layers then take such passes, up to 512 tokens, instead of
+ * passes of 8; the results are the same bits.  May allocate and synchronise; does neither where the workspace is
+ * already large enough.  A workspace that a call under graph capture has used is kept, beside the grown one,
+ * until the layer is destroyed. */
 int nq_binlr_reserve(nq_handle h, int max_batch);
-/* What has been reserved: the largest batch that allocates nothing, and the bytes of the dense
- * path's workspace held by the layer.  Either pointer may be NULL. */
+/* What has been reserved: the largest batch that allocates nothing, and the bytes of the workspace held
+ * by the layer for batches above 8.  Either pointer may be NULL. */
 int nq_binlr_reserved(nq_handle h, int* max_batch, size_t* workspace_bytes);
 
 /* y = s_out (.) (U (V^T (s_in (.) x))) for `batch` tokens (Eq. 1).
@@ -181,7 +183,7 @@ int nq_binlr_forward(nq_handle h, const void* x, void* y, int batch, void* strea
 int nq_binlr_forward_static(nq_handle h, const void* x, void* y, int batch, void* stream);
 
 /* The same product for ANY batch through the streaming kernels only, in passes of 8 tokens, or of more
- * where nq_binlr_reserve has made room for them (exact integer accumulation of 24-bit fixed-point
+ * where the layer's workspace has room for them (nq_binlr_reserve; exact integer accumulation of 24-bit fixed-point
  * activations: the accuracy of a batch <= 8 forward) -- the per-call way to ask for the
  * exact path above batch 8, where nq_binlr_forward takes the fp16-operand dense path.
  * Pointers, types and stream as in nq_binlr_forward; allocates nothing. */

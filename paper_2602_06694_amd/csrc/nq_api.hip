@@ -354,9 +354,13 @@ static void free_handle(nq_handle h)
     if (!h) return;
     slab_release(h->w_slab, h->w_alloc, h->w_bytes);
     slab_release(h->ws_slab, h->ws_alloc, h->ws_bytes);
-    if (h->pf_alloc && !h->pf_in_xt) (void)hipFree(h->pf_alloc);
+    if (h->pf_alloc) (void)hipFree(h->pf_alloc);
+    while (Retired* const p = h->retired) {
+        h->retired = p->next;
+        (void)hipFree(p->alloc);
+        delete p;
+    }
     if (h->tp_alloc) (void)hipFree(h->tp_alloc);
-    if (h->xt_alloc) (void)hipFree(h->xt_alloc);
     if (h->s_mid) (void)hipFree(h->s_mid);
     delete h;
 }
@@ -543,27 +547,42 @@ extern "C" int nq_binlr_set_mid_scale(nq_handle h, const uint16_t* s_mid_fp16)
     return NQ_OK;
 }
 
-// forgets the dense path's workspace (the device must be idle)
-static int drop_prefill_workspace(nq_handle h)
+static int exact_pass_tokens(nq_handle h) { return pass_tokens(carve_workspace(nullptr, nullptr, h->d_in, h->r, 16) / 16); }
+
+// A call whose launches go into a graph being captured leaves pf_alloc's address in it.
+static void note_capture(nq_handle h, hipStream_t s)
 {
-    void* const p = h->pf_in_xt ? nullptr : h->pf_alloc;    // inside the exact path's allocation it goes with that
-    h->pf_alloc = nullptr;
-    h->pf_bytes = 0;
-    h->pf_in_xt = false;
-    if (p) NQ_HIP(hipFree(p));
-    return NQ_OK;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (h->pf_captured) return;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) (void)hipGetLastError();       // (the launches report it)
+    else if (st != hipStreamCaptureStatusNone) h->pf_captured = true;
 }
 
-// grows the dense path's workspace to `need` bytes (never shrinks it).  Its contents need no initialisation: rows past the batch are
-// computed with and never stored.
+// grows the workspace to `need` bytes (never shrinks it).  Its contents need no initialisation: what lies past the batch is computed
+// with and never stored.
 static int grow_prefill_workspace(nq_handle h, size_t need)
 {
     if (need <= h->pf_bytes) return NQ_OK;
     NQ_HIP(hipDeviceSynchronize());
-    int rc = drop_prefill_workspace(h);
-    if (rc != NQ_OK) return rc;
+    void* const old = h->pf_alloc;
+    const int batch = h->pf_batch;
+    if (old && h->pf_captured) {
+        Retired* const p = new (std::nothrow) Retired{old, h->retired};
+        if (!p) return fail(NQ_E_HIP, "workspace: out of host memory");
+        h->retired = p;
+    }
+    const bool release = old && !h->pf_captured;
+    h->pf_alloc = nullptr;
+    h->pf_bytes = 0;
+    h->pf_batch = 0;
+    h->xt_tokens = 0;
+    h->pf_captured = false;
+    if (release) NQ_HIP(hipFree(old));
     NQ_HIP(hipMalloc(&h->pf_alloc, need));
     h->pf_bytes = need;
+    h->pf_batch = batch;                                       // (what an earlier reservation asked for fits all the more)
+    for (int t = 512; t >= 16 && h->xt_tokens == 0; t -= 16)
+        if (carve_workspace(nullptr, nullptr, h->d_in, h->r, t) <= need) h->xt_tokens = t;
     return NQ_OK;
 }
 
@@ -577,42 +596,20 @@ extern "C" int nq_binlr_reserve(nq_handle h, int max_batch)
     if (!h) return fail(NQ_E_NULL, "nq_binlr_reserve: NULL handle");
     if (max_batch < 1) return fail(NQ_E_INVALID_ARG, "nq_binlr_reserve: max_batch must be >= 1");
     if (max_batch <= NQ_DECODE_MAX_BATCH || (h->flags & NQ_FLAG_DECODE_VALU)) return NQ_OK;   // decode workspace is fixed
-    // the exact path's workspace for passes of more than eight tokens (its calls themselves never allocate)
-    int tokens = std::min(pass_tokens(carve_workspace(nullptr, nullptr, h->d_in, h->r, 16) / 16), (int)round_up(max_batch, 16));
+    // the exact path's passes of more than eight tokens (its calls themselves never allocate)
+    size_t need = carve_workspace(nullptr, nullptr, h->d_in, h->r, (int)std::min<int64_t>(exact_pass_tokens(h), round_up(max_batch, 16)));
     // The dense path's need is not monotone in the batch: smaller batches split the reduction
     // over more workgroups and keep more partial sums.  It depends on the batch only through its
     // padding to whole 64-token tiles, so the maximum over every padding up to max_batch's is taken.
     const bool dense = max_batch >= NQ_PREFILL_MIN_BATCH && !(h->flags & NQ_FLAG_NO_PREFILL);
-    size_t need = 0;
     for (int64_t b = 64; dense; b += 64) {
         const int bb = (int)std::min<int64_t>(b, max_batch);
         need = std::max(need, prefill_workspace_bytes(h->d_out, h->d_in, h->r, bb, h->pf_plain));
         if (b >= max_batch) break;
     }
-    if (h->xt_tokens < tokens) {
-        // both in one allocation (a second one costs as much as the first: 0.2 to 0.4 ms)
-        need = std::max(need, h->pf_bytes);
-        NQ_HIP(hipDeviceSynchronize());
-        int rc = drop_prefill_workspace(h);
-        if (rc != NQ_OK) return rc;
-        void* const old = h->xt_alloc;
-        h->xt_alloc = nullptr;
-        h->xt_tokens = 0;
-        if (old) NQ_HIP(hipFree(old));
-        const size_t xt_bytes = align_up(carve_workspace(nullptr, nullptr, h->d_in, h->r, tokens), 256);
-        NQ_HIP(hipMalloc(&h->xt_alloc, xt_bytes + need));
-        h->xt_tokens = tokens;
-        if (need) {
-            h->pf_alloc = (char*)h->xt_alloc + xt_bytes;
-            h->pf_bytes = need;
-            h->pf_in_xt = true;
-        }
-    } else if (need > h->pf_bytes) {
-        int rc = grow_prefill_workspace(h, need);
-        if (rc != NQ_OK) return rc;
-    }
-    if (!dense) return NQ_OK;
-    h->pf_batch = std::max(h->pf_batch, max_batch);
+    int rc = grow_prefill_workspace(h, need);
+    if (rc != NQ_OK) return rc;
+    if (dense) h->pf_batch = std::max(h->pf_batch, max_batch);
     return NQ_OK;
 }
 
@@ -712,15 +709,18 @@ static int decode_once(nq_handle h, const DecodeWorkspace& w, const void* x, voi
     return launch_stage(nullptr, s2, nullptr, (rb2 + per2 - 1) / per2, w2, per2, batch, s);
 }
 
-// any batch through the exact streaming kernels; `unscaled`: z = U (V^T (s_in (.) x)).  Passes of as many tokens as the workspace
-// of nq_binlr_reserve holds, of eight through the decode workspace where nothing has been reserved (or eight and fewer are left):
+// any batch through the exact streaming kernels; `unscaled`: z = U (V^T (s_in (.) x)).  Passes of as many tokens as the layer's
+// workspace holds, of eight through the decode workspace where it has none (or eight and fewer are left):
 // the same bits either way.  Allocates nothing.
 static int run_in_passes(nq_handle h, const void* x, void* y, int batch, hipStream_t s, bool unscaled)
 {
     const size_t xs = dtype_size(h->x_dtype), ys = dtype_size(h->y_dtype);
     const bool wide = h->xt_tokens > NQ_DECODE_MAX_BATCH && !(h->flags & NQ_FLAG_DECODE_VALU);
     DecodeWorkspace w;
-    if (wide) (void)carve_workspace(&w, (char*)h->xt_alloc, h->d_in, h->r, h->xt_tokens);
+    if (wide) {
+        (void)carve_workspace(&w, (char*)h->pf_alloc, h->d_in, h->r, h->xt_tokens);
+        if (batch > NQ_DECODE_MAX_BATCH) note_capture(h, s);
+    }
     for (int b0 = 0; b0 < batch;) {
         const int left = batch - b0;
         const char* xp = (const char*)x + (size_t)b0 * h->d_in * xs;
@@ -767,6 +767,7 @@ extern "C" int nq_binlr_forward(nq_handle h, const void* x, void* y, int batch, 
     if (batch <= NQ_DECODE_MAX_BATCH) return decode_once(h, h->ws, x, y, batch, s);
     if (batch >= NQ_PREFILL_MIN_BATCH && !(h->flags & (NQ_FLAG_NO_PREFILL | NQ_FLAG_DECODE_VALU))) {
         if ((rc = ensure_prefill_workspace(h, batch)) != NQ_OK) return rc;
+        note_capture(h, s);
         PrefillArgs a;
         a.vt_tiles = h->vt_tiles; a.u_tiles = h->u_tiles; a.s_in = h->s_in; a.s_out = h->s_out;
         a.s_mid = h->s_mid; a.mid_exp = h->mid_exp;

@@ -217,6 +217,8 @@ struct DecodeWorkspace {
 
 // ---- a layer resident on one GPU (the object behind nq_handle) ------------------------------
 struct Slab;
+struct Retired { void* alloc; Retired* next; };       // an allocation kept for the graphs that hold its address
+
 struct nq_binlr_s {
     int64_t d_out, d_in, r;
     int x_dtype, y_dtype;
@@ -237,18 +239,18 @@ struct nq_binlr_s {
     size_t ws_bytes;
     Slab* ws_slab;
     nq::DecodeWorkspace ws;
-    // prefill workspace (grown by reserve)
+    // workspace of the calls with more than eight tokens (grown by reserve and by dense forwards): the dense path and the exact path's
+    // wide passes use the same memory, one call at a time
     void* pf_alloc;
     size_t pf_bytes;
     int pf_batch;
+    int xt_tokens;        // tokens of an exact pass that pf_alloc holds (whole groups of 16; 0: none)
+    bool pf_captured;     // a graph may hold pf_alloc's address: it is kept when the workspace grows
+    struct Retired* retired;        // such earlier allocations, released with the layer
     bool pf_plain;        // the dense path takes its operands one column at a time (prefill_plain)
-    bool pf_in_xt;        // pf_alloc lies inside xt_alloc (nq_binlr_reserve allocates the two together)
     // workspace of the transposed products (allocated by their first call)
     void* tp_alloc;
     int tp_tokens;        // tokens one pass may hold
-    // workspace of the exact path's passes of more than eight tokens (allocated by nq_binlr_reserve)
-    void* xt_alloc;
-    int xt_tokens;
 };
 
 
