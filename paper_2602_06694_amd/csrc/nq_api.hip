@@ -354,13 +354,13 @@ static void free_handle(nq_handle h)
     if (!h) return;
     slab_release(h->w_slab, h->w_alloc, h->w_bytes);
     slab_release(h->ws_slab, h->ws_alloc, h->ws_bytes);
-    if (h->pf_alloc) (void)hipFree(h->pf_alloc);
+    if (h->pf.alloc) (void)hipFree(h->pf.alloc);
+    if (h->tp.alloc) (void)hipFree(h->tp.alloc);
     while (Retired* const p = h->retired) {
         h->retired = p->next;
         (void)hipFree(p->alloc);
         delete p;
     }
-    if (h->tp_alloc) (void)hipFree(h->tp_alloc);
     if (h->s_mid) (void)hipFree(h->s_mid);
     delete h;
 }
@@ -549,37 +549,46 @@ extern "C" int nq_binlr_set_mid_scale(nq_handle h, const uint16_t* s_mid_fp16)
 
 static int exact_pass_tokens(nq_handle h) { return pass_tokens(carve_workspace(nullptr, nullptr, h->d_in, h->r, 16) / 16); }
 
-// A call whose launches go into a graph being captured leaves pf_alloc's address in it.
-static void note_capture(nq_handle h, hipStream_t s)
+static bool capturing(hipStream_t s)
 {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (h->pf_captured) return;
-    if (hipStreamIsCapturing(s, &st) != hipSuccess) (void)hipGetLastError();       // (the launches report it)
-    else if (st != hipStreamCaptureStatusNone) h->pf_captured = true;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();                                   // (the launches report it)
+    return false;
+}
+// A call whose launches go into a graph being captured leaves the workspace's address in it.
+static void note_capture(Workspace& w, hipStream_t s)
+{
+    if (!w.captured && capturing(s)) w.captured = true;
 }
 
-// grows the workspace to `need` bytes (never shrinks it).  Its contents need no initialisation: what lies past the batch is computed
-// with and never stored.
-static int grow_prefill_workspace(nq_handle h, size_t need)
+// Grows a workspace of layer h to `need` bytes (never shrinks it).  Its contents need no initialisation: what lies past the batch is
+// computed with and never stored.
+static int grow_workspace(nq_handle h, Workspace& w, size_t need)
 {
-    if (need <= h->pf_bytes) return NQ_OK;
+    if (need <= w.bytes) return NQ_OK;
     NQ_HIP(hipDeviceSynchronize());
-    void* const old = h->pf_alloc;
-    const int batch = h->pf_batch;
-    if (old && h->pf_captured) {
+    void* const old = w.alloc;
+    const bool keep = old && w.captured;
+    if (keep) {
         Retired* const p = new (std::nothrow) Retired{old, h->retired};
         if (!p) return fail(NQ_E_HIP, "workspace: out of host memory");
         h->retired = p;
     }
-    const bool release = old && !h->pf_captured;
-    h->pf_alloc = nullptr;
-    h->pf_bytes = 0;
-    h->pf_batch = 0;
-    h->xt_tokens = 0;
-    h->pf_captured = false;
-    if (release) NQ_HIP(hipFree(old));
-    NQ_HIP(hipMalloc(&h->pf_alloc, need));
-    h->pf_bytes = need;
+    w = Workspace{nullptr, 0, false};
+    if (old && !keep) NQ_HIP(hipFree(old));
+    NQ_HIP(hipMalloc(&w.alloc, need));
+    w.bytes = need;
+    return NQ_OK;
+}
+
+static int grow_prefill_workspace(nq_handle h, size_t need)
+{
+    if (need <= h->pf.bytes) return NQ_OK;
+    const int batch = h->pf_batch;
+    h->pf_batch = h->xt_tokens = 0;
+    int rc = grow_workspace(h, h->pf, need);
+    if (rc != NQ_OK) return rc;
     h->pf_batch = batch;                                       // (what an earlier reservation asked for fits all the more)
     for (int t = 512; t >= 16 && h->xt_tokens == 0; t -= 16)
         if (carve_workspace(nullptr, nullptr, h->d_in, h->r, t) <= need) h->xt_tokens = t;
@@ -617,7 +626,7 @@ extern "C" int nq_binlr_reserved(nq_handle h, int* max_batch, size_t* workspace_
 {
     if (!h) return fail(NQ_E_NULL, "nq_binlr_reserved: NULL handle");
     if (max_batch) *max_batch = std::max(h->pf_batch, (int)NQ_DECODE_MAX_BATCH);
-    if (workspace_bytes) *workspace_bytes = h->pf_bytes;
+    if (workspace_bytes) *workspace_bytes = h->pf.bytes;
     return NQ_OK;
 }
 
@@ -718,8 +727,8 @@ static int run_in_passes(nq_handle h, const void* x, void* y, int batch, hipStre
     const bool wide = h->xt_tokens > NQ_DECODE_MAX_BATCH && !(h->flags & NQ_FLAG_DECODE_VALU);
     DecodeWorkspace w;
     if (wide) {
-        (void)carve_workspace(&w, (char*)h->pf_alloc, h->d_in, h->r, h->xt_tokens);
-        if (batch > NQ_DECODE_MAX_BATCH) note_capture(h, s);
+        (void)carve_workspace(&w, (char*)h->pf.alloc, h->d_in, h->r, h->xt_tokens);
+        if (batch > NQ_DECODE_MAX_BATCH) note_capture(h->pf, s);
     }
     for (int b0 = 0; b0 < batch;) {
         const int left = batch - b0;
@@ -767,11 +776,11 @@ extern "C" int nq_binlr_forward(nq_handle h, const void* x, void* y, int batch, 
     if (batch <= NQ_DECODE_MAX_BATCH) return decode_once(h, h->ws, x, y, batch, s);
     if (batch >= NQ_PREFILL_MIN_BATCH && !(h->flags & (NQ_FLAG_NO_PREFILL | NQ_FLAG_DECODE_VALU))) {
         if ((rc = ensure_prefill_workspace(h, batch)) != NQ_OK) return rc;
-        note_capture(h, s);
+        note_capture(h->pf, s);
         PrefillArgs a;
         a.vt_tiles = h->vt_tiles; a.u_tiles = h->u_tiles; a.s_in = h->s_in; a.s_out = h->s_out;
         a.s_mid = h->s_mid; a.mid_exp = h->mid_exp;
-        a.x = x; a.y = y; a.workspace = h->pf_alloc;
+        a.x = x; a.y = y; a.workspace = h->pf.alloc;
         a.d_out = h->d_out; a.d_in = h->d_in; a.r = h->r; a.batch = batch; a.x_dtype = h->x_dtype; a.y_dtype = h->y_dtype; a.plain = h->pf_plain;
         return launch_prefill(a, s);
     }
@@ -1196,25 +1205,26 @@ static int transposed_forward(const char* who, nq_handle h, const void* g, float
     int rc = check_xy(who, g, w, (size_t)batch * h->d_out * gs, (size_t)batch * h->d_in * sizeof(float));
     if (rc != NQ_OK) return rc;
     // Workspace of one pass: the intermediate u = s_mid (.) U^T (s_out (.) g) [tokens][r padded], then the fixed-point input of the
-    // larger of the two products.  The first call allocates it, for its own batch (at least 64 tokens) up to one pass, and it
-    // stays at that: a later, larger batch takes more passes.
+    // larger of the two products.  A call allocates it for its own batch (at least 64 tokens) up to one pass, where no earlier one
+    // has; a call under capture makes do with what there is.
     const size_t r_pad = (size_t)n_steps(h->r) * kTileCols;
     auto pass_bytes = [&](int nb, size_t* u_bytes) {
         *u_bytes = align_up((size_t)nb * r_pad * sizeof(float), 256);
         return *u_bytes + std::max(gemm_t_scratch_bytes(h->d_out, nb), gemm_t_scratch_bytes(h->r, nb));
     };
     size_t u_bytes = 0;
-    if (!h->tp_alloc) {
-        const int tokens = std::min(pass_tokens(pass_bytes(16, &u_bytes) / 16), std::max(64, (int)round_up(batch, 16)));
-        NQ_HIP(hipDeviceSynchronize());
-        NQ_HIP(hipMalloc(&h->tp_alloc, pass_bytes(tokens, &u_bytes)));
+    hipStream_t s = (hipStream_t)stream;
+    const int tokens = (int)std::min<int64_t>(pass_tokens(pass_bytes(16, &u_bytes) / 16), std::max<int64_t>(64, round_up(batch, 16)));
+    if (h->tp_tokens < tokens && !(h->tp_tokens > 0 && capturing(s))) {
+        h->tp_tokens = 0;
+        if ((rc = grow_workspace(h, h->tp, pass_bytes(tokens, &u_bytes))) != NQ_OK) return rc;
         h->tp_tokens = tokens;
     }
+    note_capture(h->tp, s);
     const int nb_max = h->tp_tokens;
     (void)pass_bytes(nb_max, &u_bytes);
-    float* u = (float*)h->tp_alloc;
-    void* scratch = (char*)h->tp_alloc + u_bytes;
-    hipStream_t s = (hipStream_t)stream;
+    float* u = (float*)h->tp.alloc;
+    void* scratch = (char*)h->tp.alloc + u_bytes;
     for (int b0 = 0; b0 < batch; b0 += nb_max) {
         const int nb = std::min(nb_max, batch - b0);
         // u = s_mid (.) U^T (s_out (.) g): the tiles of U ([d_out][r]) read along their columns

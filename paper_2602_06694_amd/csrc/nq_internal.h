@@ -219,6 +219,13 @@ struct DecodeWorkspace {
 struct Slab;
 struct Retired { void* alloc; Retired* next; };       // an allocation kept for the graphs that hold its address
 
+// a workspace that grows with the calls that use it
+struct Workspace {
+    void* alloc;
+    size_t bytes;
+    bool captured;        // a graph may hold the address: it is kept when the workspace grows
+};
+
 struct nq_binlr_s {
     int64_t d_out, d_in, r;
     int x_dtype, y_dtype;
@@ -241,16 +248,14 @@ struct nq_binlr_s {
     nq::DecodeWorkspace ws;
     // workspace of the calls with more than eight tokens (grown by reserve and by dense forwards): the dense path and the exact path's
     // wide passes use the same memory, one call at a time
-    void* pf_alloc;
-    size_t pf_bytes;
+    Workspace pf;
     int pf_batch;
-    int xt_tokens;        // tokens of an exact pass that pf_alloc holds (whole groups of 16; 0: none)
-    bool pf_captured;     // a graph may hold pf_alloc's address: it is kept when the workspace grows
-    struct Retired* retired;        // such earlier allocations, released with the layer
+    int xt_tokens;        // tokens of an exact pass that it holds (whole groups of 16; 0: none)
     bool pf_plain;        // the dense path takes its operands one column at a time (prefill_plain)
-    // workspace of the transposed products (allocated by their first call)
-    void* tp_alloc;
+    // workspace of the transposed products (grown by them)
+    Workspace tp;
     int tp_tokens;        // tokens one pass may hold
+    Retired* retired;     // earlier allocations of the two that graphs may hold, released with the layer
 };
 
 

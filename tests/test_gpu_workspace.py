@@ -100,3 +100,49 @@ def test_graphs_captured_before_the_workspace_grew(exact):
     assert all(bool((o == 3.0).all()) for o in others)    # nobody else's memory was written
     del graph
     L.close()
+
+
+def test_the_transposed_products_workspace_follows_the_largest_batch():
+    """A first call with one token must not leave a layer in passes of 64: after a call with 512 it holds what a first call with
+    512 leaves."""
+    import torch
+    d = 4096
+    w = torch.empty((512, d), dtype=torch.float32, device="cuda")
+    g = torch.randn((512, d), device="cuda")
+    warm = Layer(d, d, 1024, "f32", seed=9500)
+    for batch in (1, 512):
+        nq.nq_binlr_backward_input(warm.h, g, w, batch)
+    held = []
+    for batches in ((512,), (1, 512), (512, 1, 64)):
+        L = Layer(d, d, 1024, "f32", data=warm.data)
+        free0 = free_bytes()
+        for batch in batches:
+            nq.nq_binlr_backward_input(L.h, g, w, batch)
+        held.append(free0 - free_bytes())
+        L.close()
+    assert held[0] == held[1] == held[2] and held[0] <= (9 << 20) + SLACK
+    warm.close()
+
+
+def test_transposed_graphs_captured_before_the_workspace_grew():
+    """Captured with more tokens than the workspace has room for (several passes), replayed after it has grown."""
+    import torch
+    d_out, d_in, r, batch = 600, 500, 300, 150
+    L = Layer(d_out, d_in, r, "f32", seed=9600)
+    g = torch.randn((batch, d_out), device="cuda")
+    w, eager = (torch.empty((batch, d_in), dtype=torch.float32, device="cuda") for _ in range(2))
+    nq.nq_binlr_backward_input(L.h, g, w, 1)              # a workspace of 64 tokens
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        nq.nq_binlr_backward_input(L.h, g, w, batch)
+    for rep in range(4):
+        g.copy_(torch.randn((batch, d_out), device="cuda"))
+        nq.nq_binlr_backward_input(L.h, g, eager, batch)  # (the first one grows it)
+        w.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(w, eager), rep
+    del graph
+    L.close()
