@@ -1669,9 +1669,11 @@ scale_grad_kernel(const void* __restrict__ a, const void* __restrict__ b, int ba
 template <int DA>
 static void launch_scale_grad_a(const void* a, const void* b, int b_dtype, int batch, int64_t n, float* out, hipStream_t s)
 {
-    // (a wave for every kSgUnroll tokens, up to kSgWaves)
-    const int waves = std::min(kSgWaves, (batch + kSgUnroll - 1) / kSgUnroll);
-    const dim3 grid((unsigned)((n + 63) / 64)), block(64 * waves);
+    // a wave for every kSgUnroll tokens, up to kSgWaves, and as many as a launch holds (2^32 threads: from 2^28 columns on fewer)
+    const int64_t columns = (n + 63) / 64 * 64;
+    int waves = std::min(kSgWaves, (batch + kSgUnroll - 1) / kSgUnroll);
+    while (waves > 1 && columns * waves >= (int64_t)1 << 32) waves = (waves + 1) / 2;
+    const dim3 grid((unsigned)(columns / 64)), block(64 * waves);
     if (b_dtype == NQ_F32) hipLaunchKernelGGL((scale_grad_kernel<DA, NQ_F32>), grid, block, 0, s, a, b, batch, n, out);
     else if (b_dtype == NQ_F16) hipLaunchKernelGGL((scale_grad_kernel<DA, NQ_F16>), grid, block, 0, s, a, b, batch, n, out);
     else hipLaunchKernelGGL((scale_grad_kernel<DA, NQ_BF16>), grid, block, 0, s, a, b, batch, n, out);

@@ -25,6 +25,26 @@ def test_scale_grad(n, batch, ta, tb):
     assert np.all(np.abs(out.cpu().numpy() - prod.sum(0)) <= 2.0 ** -24 * np.abs(prod.sum(0)) + 2.0 ** -50 * np.abs(prod).sum(0))
 
 
+def test_scale_grad_of_very_many_columns():
+    """2^28 columns at 61 tokens: 16 waves per 64 columns would be 2^32 threads, more than a launch holds."""
+    import torch
+    n, batch = 1 << 28, 61
+    if torch.cuda.mem_get_info()[0] < 40 << 30:
+        pytest.skip("needs 34 GB")
+    a = torch.zeros((batch, n), dtype=torch.bfloat16, device="cuda")
+    at = torch.tensor([0, 63, 64, 12345, 1 << 27, n - 65, n - 1], device="cuda")
+    v = (torch.arange(batch * at.numel(), device="cuda") % 13 - 6).reshape(batch, -1)
+    a[:, at] = v.bfloat16()
+    out = torch.full((n,), float("nan"), dtype=torch.float32, device="cuda")
+    nq.nq_scale_grad(a, nq.NQ_BF16, a, nq.NQ_BF16, batch, n, out)
+    want = (v * v).sum(0).float()
+    assert torch.equal(out[at], want)
+    out[at] = 0.0
+    assert not bool(out.any())
+    del a, out
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("d_out,d_in,r,batch", [
     (600, 70, 40, 40),              # few row blocks: a quarter of a tile's rows each
     (1100, 130, 1000, 128),         # 72 and 64 pairs of row block and token group: half, a quarter
