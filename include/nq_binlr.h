@@ -205,7 +205,7 @@ int nq_binlr_forward_unscaled(nq_handle h, const void* x, void* z, int batch, vo
 /* w = V (s_mid (.) (U^T (s_out (.) g))): the layer's transpose applied to g without the input scale
  * (s_mid only where nq_binlr_set_mid_scale has set one).
  * g: device, [batch, d_out] row-major of the layer's y_dtype;  w: device, [batch, d_in] floats.
- * Any batch, in passes of as many tokens as fit about 8 MiB (64 to 512).  The scaled input is held as fixed point with a power-of-two
+ * Any batch, in passes of as many tokens as fit about 10 MiB (64 to 512).  The scaled input is held as fixed point with a power-of-two
  * step per token (2^-31 of its maximum, 2^-39 where a few large elements stand out), sign products are
  * summed exactly, and each result is rounded once to fp32 (u = U^T(..) between the two products likewise).
  * The first call on a layer allocates its workspace, for one pass of its own batch but at least 64 tokens, and a

@@ -340,12 +340,13 @@ extern "C" int nq_get_option(const char* name, int* value)
 // ---------------------------------------------------------------------------------------------
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// Tokens of one pass of the paths that take any batch in passes: a workspace of about 8 MiB per layer, at least 64 and at
+// Tokens of one pass of the paths that take any batch in passes: a workspace of about `budget` bytes per layer, at least 64 and at
 // most 512 tokens, whole groups of 16.  (A pass is four dependent launches of 4 to 10 us, so the more tokens the better; a model
-// whose layers all take this path holds one such workspace per layer.)
-static int pass_tokens(size_t bytes_per_token)
+// whose layers all take such a path holds one such workspace per layer.)
+constexpr size_t kExactPassBytes = (size_t)8 << 20, kTransposedPassBytes = (size_t)10 << 20;
+static int pass_tokens(size_t bytes_per_token, size_t budget)
 {
-    const size_t fit = ((size_t)8 << 20) / std::max<size_t>(1, bytes_per_token) / 16 * 16;
+    const size_t fit = budget / std::max<size_t>(1, bytes_per_token) / 16 * 16;
     return (int)std::max<size_t>(64, std::min<size_t>(512, fit));
 }
 
@@ -547,7 +548,7 @@ extern "C" int nq_binlr_set_mid_scale(nq_handle h, const uint16_t* s_mid_fp16)
     return NQ_OK;
 }
 
-static int exact_pass_tokens(nq_handle h) { return pass_tokens(carve_workspace(nullptr, nullptr, h->d_in, h->r, 16) / 16); }
+static int exact_pass_tokens(nq_handle h) { return pass_tokens(carve_workspace(nullptr, nullptr, h->d_in, h->r, 16) / 16, kExactPassBytes); }
 
 static bool capturing(hipStream_t s)
 {
@@ -1214,7 +1215,7 @@ static int transposed_forward(const char* who, nq_handle h, const void* g, float
     };
     size_t u_bytes = 0;
     hipStream_t s = (hipStream_t)stream;
-    const int tokens = (int)std::min<int64_t>(pass_tokens(pass_bytes(16, &u_bytes) / 16), std::max<int64_t>(64, round_up(batch, 16)));
+    const int tokens = (int)std::min<int64_t>(pass_tokens(pass_bytes(16, &u_bytes) / 16, kTransposedPassBytes), std::max<int64_t>(64, round_up(batch, 16)));
     if (h->tp_tokens < tokens && !(h->tp_tokens > 0 && capturing(s))) {
         h->tp_tokens = 0;
         if ((rc = grow_workspace(h, h->tp, pass_bytes(tokens, &u_bytes))) != NQ_OK) return rc;
