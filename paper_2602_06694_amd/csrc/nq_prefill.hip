@@ -43,6 +43,9 @@
 
 #include "nq_internal.h"
 
+// M0 among an asm statement's written registers is what is meant here (the warning calls it reserved)
+#pragma clang diagnostic ignored "-Winline-asm"
+
 namespace nq {
 
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
@@ -509,12 +512,13 @@ prefill_gemm_kernel(GemmArgs a)
     const char* const tile_base = (const char*)a.tiles + ((size_t)rb_ld * a.nst + s_begin) * (kTileWords * 4);
     const uint32_t lds_wave = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds_raw + (uint32_t)(grp * kRing + wave * kWaveBytes);
     // (the requests are written out because for the builtin the compiler waits for all of them before every LDS read.  They
-    // have no register result; M0 holds the LDS address and is not used by anything else here.)
+    // have no register result.  M0, which holds the LDS address, is named as written: the compiler sets it before uses of its own, but
+    // may set it once for several.)
 #define PF_DMA1(lds_addr, voff, base)                                                                                      \
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(base) : "memory")
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(base) : "memory", "m0")
 #define PF_DMA2(lds_addr, voff0, voff1, base, OFF0, OFF1)                                                                  \
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3 offset:" OFF0                          \
-                 "\n\tglobal_load_lds_dwordx4 %2, %3 offset:" OFF1 ::"s"(lds_addr), "v"(voff0), "v"(voff1), "s"(base) : "memory")
+                 "\n\tglobal_load_lds_dwordx4 %2, %3 offset:" OFF1 ::"s"(lds_addr), "v"(voff0), "v"(voff1), "s"(base) : "memory", "m0")
     // part k = 0 .. 2 of the requests of step `step` (spread over the planes of the step before: issued together they leave
     // the matrix cores of their SIMD idle for 5 to 9 us in 100)
 #define PF_REQUEST(slot, step, k)                                                                                          \
