@@ -1536,14 +1536,24 @@ int shared_min_batch() { return std::max(1, opt_or(OPT_SHARE_MIN_BATCH, 4)); }
 
 // Waves per row block in launches that do not fill the chip: four, and 16 (eight at batch 6 to 8, whose waves hold two
 // column groups) where the reduction is so long that four waves' shares take longer than adding up 16 of them, and every row block
-// still has a CU of its own.  Measured per forward, four waves against the wider workgroup: 8192 x 28672 r = 3520 (448 steps)
-// batch 2 36.4 -> 32.6, batch 4 35.3 -> 34.3, batch 6 48.4 -> 46.3 us; 4096 x 4096 r = 1024 (64 steps) batch 2 15.9 against
-// 17.7, batch 4 16.1 against 16.7.
+// still has a CU of its own (260 and more: four are faster at every length).  How long that is depends on the batch, whose
+// sums are what is added up, and on the row blocks, whose tiles are what is waited for: the 16 waves' loads of many row blocks keep
+// more of memory busy.  Measured on whole forwards, 1 to 256 row blocks x 96 to 600 steps at every batch from 2 to 8, four waves
+// against the wider workgroup:
+//   batch 2   224 row blocks, 224 steps 42.8 / 41.4 us, 448 steps 57.9 / 49.2;  3 row blocks, 256 steps 22.2 / 22.3, 448 steps 29.5 / 28.7
+//   batch 3   224 and 224 42.6 / 42.1;  28 and 256 24.5 / 24.8, 320 steps 28.3 / 27.8;  3 and 366 26.7 / 27.4
+//   batch 4   112 and 256 35.4 / 35.0;  28 and 320 28.3 / 28.3, 448 steps 33.6 / 33.1;  16 and 448 30.4 / 30.3
+//   batch 5   level or slower up to 448 steps (224 and 384: 55.5 / 56.1)
+//   batch 8   28 and 256 35.8 / 35.6, 448 steps 47.8 / 46.5;  128 steps slower (28.5 / 28.7)
 static int split_width(int n_rb_total, int mean_steps, int batch)
 {
     if (batch == 1) return n_rb_total * 4 >= schedule_full_rowblocks() ? 4 : 16;
-    if (n_rb_total > device_cu_count() || mean_steps < 256) return 4;
-    return batch <= 5 ? 16 : kSplit8Schedule;
+    if (n_rb_total > device_cu_count()) return 4;
+    const int size = n_rb_total >= 96 ? 0 : n_rb_total >= 48 ? 1 : n_rb_total >= 24 ? 2 : n_rb_total > 2 ? 3 : 4;
+    constexpr int never = 1 << 30;
+    constexpr int from[4][5] = {{192, 192, 192, 320, 192}, {192, 256, 320, 448, 192}, {256, 320, 448, 448, 320}, {never, never, never, never, never}};
+    if (batch <= 5) return mean_steps >= from[batch - 2][size] ? 16 : 4;
+    return mean_steps >= 256 ? kSplit8Schedule : 4;
 }
 
 int stage_schedule(int n_rb_total, int mean_steps, int batch)
