@@ -855,6 +855,7 @@ static GemmTiling choose_tiling(int m_pad, int n_rb, int nst, int n_pad, bool pl
     double best_cost = 1e30;
     auto consider = [&](int tg, int splits, int ks) {
         const int wgs = (m_pad / (16 * tg)) * n_tiles * splits, per = steps_per_split4(nst, splits, ks);
+        if ((splits - 1) * per >= nst) return;                 // parts without a step: fewer do the same
         double cost;
         if (ks == 2) {
             cost = (wgs + cus - 1) / cus * (per / 2 * c.halves4 + 10.5);
@@ -868,7 +869,7 @@ static GemmTiling choose_tiling(int m_pad, int n_rb, int nst, int n_pad, bool pl
         if (splits > 1) cost += 2.8 + splits * (0.23 + 0.29 * partial_mb);
         if (cost < best_cost) { best_cost = cost; best = {tg, splits, ks}; }
     };
-    for (int s = 1; s <= 16 && (s == 1 || steps_per_split4(nst, s) >= 4); ++s) {
+    for (int s = 1; s <= 16; ++s) {
         consider(4, s, 1);
         if (nst % 8 == 0) consider(4, s, 2);
         if (s == 1) consider(2, 1, 1);
