@@ -58,3 +58,47 @@ def test_layers_without_the_dense_path_take_the_wide_passes_too():
     assert torch.isnan(b[5]).all() and not torch.isnan(b[[4, 6]]).any()
     assert torch.equal(torch.nan_to_num(a, nan=7.0), torch.nan_to_num(b, nan=7.0))
     L.close()
+
+
+@pytest.mark.parametrize("d_out,d_in,r,batch,x", [
+    (200, 9000, 130, 20, "bf16"),                         # 512 threads hold the row, 1024, and rows that are read twice
+    (130, 20000, 70, 18, "f32"),
+    (70, 65536, 33, 17, "bf16"),
+    (130, 20001, 65, 21, "f16"),                          # rows of odd lengths
+    (70, 40001, 33, 17, "f32"),
+    (64, 300, 9000, 20, "bf16"),                          # the same for the intermediate
+    (64, 70, 40000, 17, "bf16"),
+])
+def test_long_rows_in_wide_passes(d_out, d_in, r, batch, x):
+    import torch
+    L = Layer(d_out, d_in, r, x, seed=6400 + d_in)
+    xd = to_device(synth.gen_x(batch, d_in, 6401, x), x)
+    narrow, wide = new_output(batch, d_out), new_output(batch, d_out)
+    nq.nq_binlr_forward_exact(L.h, xd, narrow, batch)
+    nq.nq_binlr_reserve(L.h, batch)
+    nq.nq_binlr_forward_exact(L.h, xd, wide, batch)
+    torch.cuda.synchronize()
+    assert torch.equal(narrow, wide) and not torch.isnan(wide).any()
+    L.close()
+
+
+def test_accumulators_at_their_extreme_values_in_wide_passes():
+    """Every sign +1, 65535 low bytes at -128, 127 or 127 (of -129) in 17 tokens: the largest int32 sums the format produces."""
+    import torch
+    d_out, d_in, r, batch = 128, nq.NQ_MAX_DIM, 64, 17
+    ones = lambda rows: oracle.pack_signs(np.ones((rows, r), dtype=np.int8))
+    L = Layer(d_out, d_in, r, "f32", data=synth.LayerData(synth.LinearShape("m", d_out, d_in, r), ones(d_out), ones(d_in),
+                                                          np.ones(d_out, dtype=np.float16), np.ones(d_in, dtype=np.float16)))
+    nq.nq_binlr_reserve(L.h, batch)
+    x = np.empty((batch, d_in))
+    for t, low in enumerate(np.resize([128.0, 127.0, -129.0], batch)):
+        row = np.full(d_in, low)
+        row[0] = 2.0 ** 22 - 2.0 ** 16                    # pins the step of the first quantisation at 1
+        s = row.sum()
+        row[1] -= s % max(1.0, 2.0 ** (np.frexp(abs(s))[1] - 22))      # and makes t a multiple of the second's
+        x[t] = row if t % 2 else -row
+    y = new_output(batch, d_out)
+    nq.nq_binlr_forward_exact(L.h, to_device(x.astype(np.float32), "f32"), y, batch)
+    torch.cuda.synchronize()
+    assert np.array_equal(y.cpu().numpy().astype(np.float64), L.oracle(x.astype(np.float32)))
+    L.close()

@@ -173,3 +173,20 @@ def test_scales_on_the_device_choose_the_same_form():
         assert torch.equal(a, b), exact
         nq.nq_binlr_destroy(h)
         L.close()
+
+
+@pytest.mark.parametrize("d_in", [32769, 65536])
+@pytest.mark.parametrize("scale", [1.0, 3.0])             # columns, pairs
+def test_rows_longer_than_the_prescale_holds(d_in, scale):
+    """Rows of more than 32768 elements are read twice by the pre-scale: integers, bit for bit."""
+    d_out, r, batch = 70, 40, 21
+    U, V = synth.gen_sign_words(d_out, r, 9101), synth.gen_sign_words(d_in, r, 9102)
+    L = Layer(d_out, d_in, r, "f32", data=synth.LayerData(synth.LinearShape("t", d_out, d_in, r), U, V,
+                                                          np.ones(d_out, dtype=np.float16), np.full(d_in, scale, dtype=np.float16)))
+    rng = np.random.default_rng(9103 + d_in)
+    x = rng.integers(-1, 2, (batch, d_in)) * (rng.random((batch, d_in)) < 0.03)
+    x[:, -1] = 1                                          # the last, partial chunk
+    t = int(scale) * x @ signs(V, r)
+    assert 2 * np.abs(t).max() <= 2048
+    assert np.array_equal(L.forward(x.astype(np.float32)), (t @ signs(U, r).T).astype(np.float32))
+    L.close()

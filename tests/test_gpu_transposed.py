@@ -3,6 +3,7 @@ edges of their kernels: 64-column steps, 128-row blocks, eight waves per reducti
 import numpy as np
 import pytest
 
+import oracle
 from paper_2602_06694_amd import binding as nq
 from paper_2602_06694_amd import synth
 from gpu_util import Layer, to_device
@@ -88,6 +89,26 @@ def test_wide_tokens_are_exact_beside_others(d_out, d_in, r, batch):
     nq.nq_binlr_forward_transposed_unscaled(L.h, to_device(g_np, "f32"), w, batch)
     torch.cuda.synchronize()
     assert np.array_equal(w.cpu().numpy(), _reference(L, g_np.astype(np.float64)).astype(np.float32))
+    L.close()
+
+
+@pytest.mark.parametrize("d_in", [64, 8200])              # half tiles, whole tiles in the second product
+def test_accumulators_at_their_extreme_values(d_in):
+    """Every sign +1 and 65535 pairs of bytes at -128: the largest joined sums of two slices (below 2^31 over four waves)."""
+    import torch
+    d_out, r, batch = 65536, 64, 17
+    ones = lambda rows: oracle.pack_signs(np.ones((rows, r), dtype=np.int8))
+    L = Layer(d_out, d_in, r, "f32", data=synth.LayerData(synth.LinearShape("m", d_out, d_in, r), ones(d_out), ones(d_in),
+                                                          np.ones(d_out, dtype=np.float16), np.ones(d_in, dtype=np.float16)))
+    g = np.full((batch, d_out), -(128.0 * 256 + 128))
+    g[:, 0] = 2.0**30                                     # (few large elements: five slices)
+    g[1::3] = -2.0**30 * 1.96875                          # (none: four; the two upper slices near their ends)
+    g[2::3] *= -1.0
+    w = torch.full((batch, d_in), float("nan"), dtype=torch.float32, device="cuda")
+    nq.nq_binlr_forward_transposed_unscaled(L.h, to_device(g.astype(np.float32), "f32"), w, batch)
+    torch.cuda.synchronize()
+    u = g.sum(1).astype(np.float32).astype(np.float64)
+    assert np.array_equal(w.cpu().numpy(), np.repeat((r * u).astype(np.float32)[:, None], d_in, axis=1))
     L.close()
 
 
