@@ -447,7 +447,8 @@ def time_single_layer(cfg, reps=200):
 
 def time_transposed():
     """The transposed product w = V (U^T (s_out . g)) from the resident tiles against the forward without output scale,
-    on config 2's layer and on config 5's down layer, batch 1 / 8 / 64 (microseconds per call)."""
+    on config 2's layer and on config 5's down layer, batch 1 / 8 / 64 (microseconds per call); above 8 tokens the forward also without
+    the workspace that nq_binlr_reserve makes for its wide passes, and nq_scale_grad of the forward's side."""
     import torch
     from paper_2602_06694_amd import binding as nq
     from paper_2602_06694_amd import synth
@@ -461,9 +462,16 @@ def time_transposed():
             w = torch.empty((batch, shp.d_in), dtype=torch.float32, device="cuda")
             x = torch.randn((batch, shp.d_in), dtype=torch.float32, device="cuda").to(torch.bfloat16)
             z = torch.empty((batch, shp.d_out), dtype=torch.float32, device="cuda")
+            ds = torch.empty((shp.d_out,), dtype=torch.float32, device="cuda")
+            unscaled = lambda: nq.nq_binlr_forward_unscaled(h, x, z, batch)
             out = {}
+            if batch > nq.NQ_DECODE_MAX_BATCH:
+                prewarm(unscaled, 0.02)
+                out["forward_unscaled_unreserved_us"] = window_stats(timed_windows(unscaled, 20, 5))["median"] * 1e3
+                nq.nq_binlr_reserve(h, batch)
             for name, f in (("transposed_us", lambda: nq.nq_binlr_forward_transposed_unscaled(h, g, w, batch)),
-                            ("forward_unscaled_us", lambda: nq.nq_binlr_forward_unscaled(h, x, z, batch))):
+                            ("forward_unscaled_us", unscaled),
+                            ("scale_grad_us", lambda: nq.nq_scale_grad(g, nq.NQ_F32, z, nq.NQ_F32, batch, shp.d_out, ds))):
                 prewarm(f, 0.02)
                 win = timed_windows(f, 20, 5)
                 out[name] = window_stats(win)["median"] * 1e3
