@@ -127,7 +127,8 @@ int launch_stage_exact(const StageDesc& d, int batch, hipStream_t s)
     const int n_rb = (int)n_rowblocks(d.M), groups = (batch + kXTokens - 1) / kXTokens;
     // whole row blocks where they give every second CU a workgroup; below that halves and quarters of them, until they do (a
     // 4096 x 4096 r = 1024 layer at 64 tokens, 32 and 128 pairs of row block and group: quarters 12.1 -> 7.7 us, halves 6.7 -> 4.7;
-    // with the transposed product's rule the gradients of that layer 70.2 -> 66.1 us)
+    // with the transposed product's rule the gradients of that layer 70.2 -> 66.1 us; of the three forms on 11 layers from 300 x 300
+    // to 28672 x 8192 at 12 to 512 tokens this rule's is the fastest or within 2 % of it)
     int pl = 8;
     while (pl > 2 && n_rb * groups * (8 / pl) <= device_cu_count() / 2) pl /= 2;
     const dim3 grid((unsigned)(n_rb * (8 / pl)), (unsigned)groups), block(64 * kXWaves);

@@ -22,7 +22,7 @@
 // PFLOP/s without, 2.3 with them; the clock falls to 2.0 .. 2.2 GHz under it).  Signs from memory and activations go straight
 // to LDS, without registers in between.
 // Measured (MI355X, bf16 in and out, whole forwards), dense instruction -> this: 8192 x 28672 r = 3520 at 2048 tokens
-// 390 -> 302 us; 28672 x 8192 at 512 tokens 116 -> 91 us; the first layer's two GEMMs 266 + 75 -> 190 + 60 us.
+// 390 -> 302 us; 28672 x 8192 at 512 tokens 116 -> 91 us; the first layer's two GEMMs on average 285 + 81 -> 207 + 65 us.
 // Not taken: 128-token tiles at one wave per SIMD (half the vector instructions per matrix instruction, no second wave to
 // hide the rest: level); 8-bit sparse operands in two slices (half the vector instructions, but the fixed point that outlier
 // tokens then get is coarser than fp16); three 6-bit slices with block scales (finer than fp16, 1.5 times the matrix cycles: level).
@@ -842,7 +842,8 @@ static int steps_per_split4(int nst, int splits, int ks = 1)
 //  - beside its steps a workgroup takes 9.5 us (64 tokens), 10.5 (eight waves), 6.9 (32 tokens): the first fetch and the epilogue;
 //  - splitting costs the finalize launch (2.8 us) and per part 0.23 us and the write and re-read of one set of fp32
 //    partial sums, 0.29 us per MB.
-// One column at a time (`plain`) the steps take 0.60, 1.05, 0.97, 0.49 and 0.35 us (from 24 of those points, 6 layers), the rest is the same.
+// One column at a time (`plain`) the steps take 0.60, 1.05, 0.97, 0.49 and 0.35 us (each of ten tilings
+// of the two GEMMs of six layers at 24 to 2048 tokens, against the same in pairs), the rest is the same.
 struct GemmTiling { int tg, splits, ks; };
 struct StepCost { double alone4, two4, halves4, alone2, each2; };
 static GemmTiling choose_tiling(int m_pad, int n_rb, int nst, int n_pad, bool plain)

@@ -413,7 +413,8 @@ int launch_gemm_t(const uint32_t* tiles, int64_t M, int64_t N, const void* in, i
     NQ_HIP(hipGetLastError());
     const TStageArgs t{tiles, bq, bq5, meta, wide, out_scale, out, (int)N, (int)n_steps(N), n_rb, out_stride, batch};
     const int steps = (int)((N + kTileCols - 1) / kTileCols), groups = (batch + kTTokens - 1) / kTTokens;
-    // half tiles where whole ones leave more than half of the CUs without a workgroup (16 steps x 4 groups: 8.3 us against 10)
+    // half tiles where whole ones leave more than half of the CUs without a workgroup (16 steps x 4 groups: 8.3 us against 10; on 11
+    // layers from 300 x 300 to 28672 x 8192 at 1 to 512 tokens the faster of the two, or within 2 % of it)
     if (steps * groups <= device_cu_count() / 2)
         hipLaunchKernelGGL(gemm_t_kernel<2>, dim3((unsigned)steps * 2, (unsigned)groups), dim3(64 * kTWaves), 0, s, t);
     else
