@@ -103,11 +103,10 @@ def test_prefill_reserve_and_batch_changes():
 
 
 def test_prefill_activations_with_a_large_mean_and_uniform_sign_columns():
-    """The dense kernels accumulate P = the sum of the activations under the +1 weights and form
-    the signed sum as 2P - S (S = the plain sum).  That cancels most where the activations share
-    a large offset (S far above the signed sums), and it must be exact-ish where a column of V is
-    all +1 (P = S) or all -1 (P = 0): long reduction, all-positive inputs, constant inputs, and a V
-    whose first columns are uniform.  Same bar as every other dense case."""
+    """Activations that share a large offset (partial sums far above the signed sums), and columns of V that are
+    all +1 or all -1: long reduction, all-positive inputs, constant inputs, and a V whose first columns are
+    uniform.  Same bar as every other dense case.  (Unit scales: columns; the same in pairs is in
+    test_gpu_prefill_pairs.)"""
     d_out, d_in, r = 640, 8192, 384
     rng = np.random.default_rng(77)
     U = synth.gen_sign_words(d_out, r, 771)

@@ -190,3 +190,21 @@ def test_rows_longer_than_the_prescale_holds(d_in, scale):
     assert 2 * np.abs(t).max() <= 2048
     assert np.array_equal(L.forward(x.astype(np.float32)), (t @ signs(U, r).T).astype(np.float32))
     L.close()
+
+
+def test_large_mean_and_uniform_sign_columns_in_pairs():
+    """Activations that share a large offset, with columns of V that are all +1 (every pair a sum) or all -1; constant and negative
+    tokens; half of the inputs zero."""
+    d_out, d_in, r, batch = 640, 8192, 384, 80
+    V = synth.gen_sign_words(d_in, r, 9202)
+    V[:, 0] = (V[:, 0] | np.uint32(0x0000FFFF)) & np.uint32(0x0000FFFF)       # columns 0..15 all +1, 16..31 all -1
+    L = Layer(d_out, d_in, r, "f32", data=synth.LayerData(synth.LinearShape("m", d_out, d_in, r), synth.gen_sign_words(d_out, r, 9201), V,
+                                                          synth.gen_scales(d_out, 9203), np.full(d_in, 3.0, dtype=np.float16)))
+    x = (np.abs(np.random.default_rng(9204).standard_normal((batch, d_in))) + 3.0).astype(np.float32)
+    x[1] = 2.5
+    x[2] = -x[2]
+    x[3, ::2] = 0.0
+    y, ref = L.forward(x), L.oracle(x)
+    for b in range(batch):
+        assert np.abs(y[b] - ref[b]).max() <= PREFILL_TOL * np.abs(ref[b]).max(), b
+    L.close()
