@@ -695,7 +695,7 @@ static int decode_once(nq_handle h, const DecodeWorkspace& w, const void* x, voi
     StageDesc s2 = make_s2(h, w, y);
     if (unscaled) s2.out_scale = nullptr;
     const int rb1 = (int)n_rowblocks(h->r), rb2 = (int)n_rowblocks(h->d_out);
-    const int w1 = stage_schedule(rb1, s1.n_steps, batch), w2 = stage_schedule(rb2, s2.n_steps, batch);
+    const int w1 = stage_schedule(rb1, s1.n_steps, s1.n_steps, batch), w2 = stage_schedule(rb2, s2.n_steps, s2.n_steps, batch);
     const int per1 = w1 == 1 ? rbs_per_stream_item(rb1, s1.n_steps, rb1, batch) : 1;
     const int per2 = w2 == 1 ? rbs_per_stream_item(rb2, s2.n_steps, rb2, batch) : 1;
     // a lone layer is bound by launch latency: where the quantised input of a stage fits LDS, the
@@ -943,15 +943,15 @@ extern "C" int nq_plan_create(nq_plan* out, const nq_handle* hs, const void* con
             sq += (double)nrb * sd[i].n_steps * sd[i].n_steps;     // mean length seen by a streamed tile
             sm += (double)nrb * sd[i].n_steps;
         }
-        int w = stage_schedule(total_rb, (int)(sq / sm), batch);
+        int max_steps = 0;
+        for (int i = 0; i < n; ++i) max_steps = std::max(max_steps, sd[i].n_steps);
+        int w = stage_schedule(total_rb, (int)(sq / sm), max_steps, batch);
         // A short launch at batch 1 is bound by launch latency, not by bandwidth: the stage then
         // quantises its own input, which saves the quantisation launch -- by the waves of the one- or
         // four-wave kernel where the reductions are short enough for it (measured faster than the
         // 16-wave kernel at every size: 4 layers of 4096x4096 r=1024 11.6 vs 13.0 us, 32 layers 13.8
         // vs 29.5), else by the 16-wave kernel, every workgroup for itself, up to NQ_FUSE_MAX_MB of tiles.
         {
-            int max_steps = 0;
-            for (int i = 0; i < n; ++i) max_steps = std::max(max_steps, sd[i].n_steps);
             const double tile_mb = sm * (kTileWords * 4) / 1.0e6;
             int min_steps = max_steps;
             for (int i = 0; i < n; ++i) min_steps = std::min(min_steps, sd[i].n_steps);

@@ -1545,9 +1545,13 @@ int shared_min_batch() { return std::max(1, opt_or(OPT_SHARE_MIN_BATCH, 4)); }
 //   batch 4   112 and 256 35.4 / 35.0;  28 and 320 28.3 / 28.3, 448 steps 33.6 / 33.1;  16 and 448 30.4 / 30.3
 //   batch 5   level or slower up to 448 steps (224 and 384: 55.5 / 56.1)
 //   batch 8   28 and 256 35.8 / 35.6, 448 steps 47.8 / 46.5;  128 steps slower (28.5 / 28.7)
-static int split_width(int n_rb_total, int mean_steps, int batch)
+// Launches of layers with reductions of different lengths end with their longest ones, which four waves take four times as long
+// for: at batch 2, 96 to 384 row blocks, those keep 16 (stage 1 of 7B-shaped blocks, 64 and 172 steps, 12 to 35 layers as one plan
+// 24.7 to 33.1 -> 24.0 to 31.7 us; 17 layers of 70B-shaped ones 51.0 -> 46.5, from 20 on level).
+static int split_width(int n_rb_total, int mean_steps, int max_steps, int batch)
 {
     if (batch == 1) return n_rb_total * 4 >= schedule_full_rowblocks() ? 4 : 16;
+    if (batch == 2 && max_steps * 4 >= mean_steps * 5 && n_rb_total >= 96 && n_rb_total * 2 <= device_cu_count() * 3) return 16;
     if (n_rb_total > device_cu_count()) return 4;
     const int size = n_rb_total >= 96 ? 0 : n_rb_total >= 48 ? 1 : n_rb_total >= 24 ? 2 : n_rb_total > 2 ? 3 : 4;
     constexpr int never = 1 << 30;
@@ -1556,7 +1560,7 @@ static int split_width(int n_rb_total, int mean_steps, int batch)
     return mean_steps >= 256 ? kSplit8Schedule : 4;
 }
 
-int stage_schedule(int n_rb_total, int mean_steps, int batch)
+int stage_schedule(int n_rb_total, int mean_steps, int max_steps, int batch)
 {
     // row blocks from which a launch counts as filling the chip (NQ_SCHEDULE_FULL overrides it,
     // which lets small inputs exercise the schedules built for large launches)
@@ -1566,7 +1570,7 @@ int stage_schedule(int n_rb_total, int mean_steps, int batch)
     // (batch 1 splits from 33 steps on: stage 2 of the 70B stack, 35 and 55 steps, 452 -> 442 us; pools
     // of 35- and 55-step reductions 64 -> 62 and 91 -> 85 us including the quantisation launch)
     else if (n_rb_total >= full) w = mean_steps >= std::max(1, opt_or(OPT_SPLIT_STEPS, batch == 1 ? 33 : 64)) ? 4 : 1;
-    else w = split_width(n_rb_total, mean_steps, batch);
+    else w = split_width(n_rb_total, mean_steps, max_steps, batch);
     {
         const int fw = opt(OPT_FORCE_W);
         if (fw == 1 || fw == 4 || (fw == 16 && batch <= 5)) w = fw;     // (the shared schedule cannot be forced: it needs a work list)

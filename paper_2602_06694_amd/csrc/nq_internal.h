@@ -271,7 +271,7 @@ int launch_pack_signs(const void* d_signs, int dtype, int64_t rows, int64_t cols
 // single op (descriptor by value) or many (device arrays)
 int launch_quantize(const QuantDesc* d_descs, const QuantDesc& single, int n_ops, int max_chunks, int batch,
                     hipStream_t s, bool grouped = false);
-int stage_schedule(int n_rb_total, int mean_steps, int batch);
+int stage_schedule(int n_rb_total, int mean_steps, int max_steps, int batch);
 int stream_target_steps(int batch);
 int stream_max_rbs(int batch);           // row blocks one stream item may chain (bounded by its LDS output buffer)
 #ifndef NQ_SHARE_WAVES

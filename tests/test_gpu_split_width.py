@@ -29,3 +29,26 @@ def test_waves_per_row_block(nqopt, batch, row_blocks, steps, waves):
     assert torch.equal(y, narrow) and not torch.isnan(y).any()
     nq.nq_plan_destroy(plan)
     L.close()
+
+
+@pytest.mark.parametrize("layers,waves", [(5, 4), (12, 16), (35, 16), (40, 4)])
+def test_waves_of_launches_with_reductions_of_different_lengths(layers, waves):
+    """Layers of 7B-shaped blocks (64 and 172 steps) as one plan at batch 2."""
+    import torch
+    shapes = [synth.llama2_7b_block()[i % 7] for i in range(layers)]
+    hs, xs, ys, lone = [], [], [], []
+    for i, s in enumerate(shapes):
+        hs.append(Layer(s.d_out, s.d_in, s.r, "bf16", seed=9800 + 10 * (i % 7)))
+        xs.append(to_device(synth.gen_x(2, s.d_in, 9801 + i, "bf16"), "bf16"))
+        ys.append(new_output(2, s.d_out))
+        lone.append(new_output(2, s.d_out))
+    plan = nq.nq_plan_create([L.h for L in hs], xs, ys, 2)
+    assert nq.nq_plan_schedules(plan)[0] == waves
+    nq.nq_plan_forward(plan)
+    for L, x, y in zip(hs, xs, lone):
+        nq.nq_binlr_forward(L.h, x, y, 2)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(ys, lone))
+    nq.nq_plan_destroy(plan)
+    for L in hs:
+        L.close()
