@@ -1205,8 +1205,9 @@ static int transposed_forward(const char* who, nq_handle h, const void* g, float
     const size_t gs = dtype_size(h->y_dtype);
     int rc = check_xy(who, g, w, (size_t)batch * h->d_out * gs, (size_t)batch * h->d_in * sizeof(float));
     if (rc != NQ_OK) return rc;
-    // Workspace of one pass: the intermediate u = s_mid (.) U^T (s_out (.) g) [tokens][r padded], then the fixed-point input of the
-    // larger of the two products.  A call allocates it for its own batch (at least 64 tokens) up to one pass, where no earlier one
+    // Workspace of one pass: the intermediate u = s_mid (.) U^T (s_out (.) g) [tokens][r padded], in fp32 or, of few
+    // tokens, as the sums of several shares of the rows in binary64 (gemm_t_parts: room for 64 tokens is enough), then the fixed-point
+    // input of the larger of the two products.  A call allocates it for its own batch (at least 64 tokens) up to one pass, where no earlier one
     // has; a call under capture makes do with what there is.
     const size_t r_pad = (size_t)n_steps(h->r) * kTileCols;
     auto pass_bytes = [&](int nb, size_t* u_bytes) {
@@ -1215,7 +1216,8 @@ static int transposed_forward(const char* who, nq_handle h, const void* g, float
     };
     size_t u_bytes = 0;
     hipStream_t s = (hipStream_t)stream;
-    const int tokens = (int)std::min<int64_t>(pass_tokens(pass_bytes(16, &u_bytes) / 16, kTransposedPassBytes), std::max<int64_t>(64, round_up(batch, 16)));
+    const size_t token_bytes = r_pad * sizeof(float) + std::max(gemm_t_scratch_bytes(h->d_out, 16), gemm_t_scratch_bytes(h->r, 16)) / 16;
+    const int tokens = (int)std::min<int64_t>(pass_tokens(token_bytes, kTransposedPassBytes), std::max<int64_t>(64, round_up(batch, 16)));
     if (h->tp_tokens < tokens && !(h->tp_tokens > 0 && capturing(s))) {
         h->tp_tokens = 0;
         if ((rc = grow_workspace(h, h->tp, pass_bytes(tokens, &u_bytes))) != NQ_OK) return rc;
@@ -1224,17 +1226,17 @@ static int transposed_forward(const char* who, nq_handle h, const void* g, float
     note_capture(h->tp, s);
     const int nb_max = h->tp_tokens;
     (void)pass_bytes(nb_max, &u_bytes);
-    float* u = (float*)h->tp.alloc;
+    void* const u = h->tp.alloc;
     void* scratch = (char*)h->tp.alloc + u_bytes;
     for (int b0 = 0; b0 < batch; b0 += nb_max) {
-        const int nb = std::min(nb_max, batch - b0);
+        const int nb = std::min(nb_max, batch - b0), parts = gemm_t_parts(h->d_out, h->r, nb);
         // u = s_mid (.) U^T (s_out (.) g): the tiles of U ([d_out][r]) read along their columns
-        rc = launch_gemm_t(h->u_tiles, h->d_out, h->r, (const char*)g + (size_t)b0 * h->d_out * gs, h->y_dtype, (int)h->d_out, h->s_out,
-                           h->s_mid, u, (int)r_pad, nb, scratch, s);
+        rc = launch_gemm_t(h->u_tiles, h->d_out, h->r, (const char*)g + (size_t)b0 * h->d_out * gs, h->y_dtype, (int)h->d_out, h->s_out, 1,
+                           h->s_mid, u, (int)r_pad, parts, nb, scratch, s);
         if (rc != NQ_OK) return rc;
-        // w = V u: the tiles of V^T ([r][d_in]) read along their columns
-        rc = launch_gemm_t(h->vt_tiles, h->r, h->d_in, u, NQ_F32, (int)r_pad, nullptr, with_s_in ? h->s_in : nullptr,
-                           w + (size_t)b0 * h->d_in, (int)h->d_in, nb, scratch, s);
+        // w = V u: the tiles of V^T ([r][d_in]) read along their columns (s_mid here where u is still in parts)
+        rc = launch_gemm_t(h->vt_tiles, h->r, h->d_in, u, NQ_F32, (int)r_pad, parts > 1 ? h->s_mid : nullptr, parts,
+                           with_s_in ? h->s_in : nullptr, w + (size_t)b0 * h->d_in, (int)h->d_in, 1, nb, scratch, s);
         if (rc != NQ_OK) return rc;
     }
     return NQ_OK;

@@ -314,8 +314,9 @@ int shared_min_batch();          // smallest batch that takes the shared-input k
 
 // ---- launchers (nq_transposed.hip) -----------------------------------------------------------
 size_t gemm_t_scratch_bytes(int64_t M, int batch);
+int gemm_t_parts(int64_t M, int64_t N, int batch);
 int launch_gemm_t(const uint32_t* tiles, int64_t M, int64_t N, const void* in, int in_dtype, int in_stride, const uint16_t* in_scale,
-                  const uint16_t* out_scale, float* out, int out_stride, int batch, void* scratch, hipStream_t s);
+                  int in_parts, const uint16_t* out_scale, void* out, int out_stride, int parts, int batch, void* scratch, hipStream_t s);
 
 // ---- launchers (nq_exact.hip) ---------------------------------------------------------------
 int launch_stage_exact(const StageDesc& d, int batch, hipStream_t s);

@@ -35,12 +35,18 @@ constexpr int kTTokens = 16;            // tokens of a workgroup: the 16 columns
 constexpr uint32_t kTGroupRbBytes = 2 * kTSlices * 16 * 64;
 constexpr uint32_t kTGroupRbBytes5 = 2 * 16 * 64;       // the fifth slices, in a region of their own: [half][token][4 pieces][16]
 
+// input of the second product where the first one's reduction is dealt out to several workgroups: their sums in binary64, added up,
+// scaled and rounded to fp32 (the intermediate u) while they are read
+constexpr int kTParts = -1, kTMaxParts = 8;
+constexpr int kTPartTokens = 32;        // most parts x tokens
+
 // ---------------------------------------------------------------------------------------------
 // scaled input -> fixed point.  One workgroup per token.  A thread owns pieces: piece (s, c) of a token holds, as four words
 // i of four bytes, rows 64 s + 16 i + 4 c + (0..3) -- the order in which the turned-round tile meets its rows.
 // ---------------------------------------------------------------------------------------------
 struct TQuantArgs {
-    const void* in;             // [batch][in_stride] of in_dtype
+    const void* in;             // [batch][in_stride] of in_dtype; kTParts: [parts][batch][in_stride] binary64 to be added up
+    int parts;
     const uint16_t* scale;      // fp16 [M] or nullptr
     uint8_t* bq;                // [groups of 16 tokens][n_pieces / 4][slices][16 tokens][4][16]
     uint8_t* bq5;               // [groups of 16 tokens][n_pieces / 4][16 tokens][4][16]: the fifth slice, of wide tokens only
@@ -51,14 +57,22 @@ struct TQuantArgs {
 };
 
 // the 16 scaled values of piece `pc`; binary64: an fp32 value times an fp16 scale is exact.  (DT = the type of the input: all of a
-// piece's loads are requested before the first is converted)
+// piece's loads are requested before the first is converted; kTParts: from `u`, LDS)
 template <int DT>
-__device__ __forceinline__ void tq_load(const TQuantArgs& a, size_t base, int pc, double v[16])
+__device__ __forceinline__ void tq_load(const TQuantArgs& a, size_t base, int pc, double v[16], const float* u)
 {
     typedef unsigned int v2u __attribute__((ext_vector_type(2)));
     typedef v4f v4f_any __attribute__((aligned(4)));       // rows of odd lengths: 16 and 8 bytes at the alignment of an element
     typedef v2u v2u_any __attribute__((aligned(2)));
     const int r0 = (pc >> 2) * 64 + 4 * (pc & 3);
+    if (DT == kTParts) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int r = r0 + 16 * (i >> 2) + (i & 3);
+            v[i] = r < a.M ? (double)u[r] : 0.0;
+        }
+        return;
+    }
     if (r0 + 52 <= a.M) {                                   // whole pieces: no branch around a load
         v4f xf[4];
         v2u xh[4], sc[4];
@@ -160,10 +174,26 @@ __global__ void __launch_bounds__(kTQThreads) quantize_t_kernel(TQuantArgs a)
     const size_t base = (size_t)tok * a.in_stride;
     double v[16], m = 0.0, sq = 0.0;
     int bad = 0;
+    extern __shared__ float u[];                            // [M], kTParts only
+    if (DT == kTParts) {
+        typedef const __attribute__((address_space(1))) double* gptr_d;
+        const gptr_d in = (gptr_d)a.in + base;
+        const size_t part = (size_t)gridDim.x * a.in_stride;
+        for (int r = tid; r < a.M; r += threads) {
+            double p[kTMaxParts];                           // (as many loads in flight whatever the count: past it the last is read again)
+#pragma unroll
+            for (int k = 0; k < kTMaxParts; ++k) p[k] = in[(k < a.parts ? k : a.parts - 1) * part + r];
+            double t = p[0];
+#pragma unroll
+            for (int k = 1; k < kTMaxParts; ++k) t += k < a.parts ? p[k] : 0.0;
+            u[r] = (float)(a.scale ? t * (double)half_bits_to_float(a.scale[r]) : t);
+        }
+        __syncthreads();
+    }
     // (a thread's first piece stays in registers between the two passes; longer vectors re-read the others)
     for (int pc = tid + ((a.n_pieces - 1 - tid) / threads) * threads; pc >= 0; pc -= threads) {
         if (pc >= a.n_pieces) break;
-        tq_load<DT>(a, base, pc, v);
+        tq_load<DT>(a, base, pc, v, u);
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const double t = fabs(v[i]);
@@ -195,7 +225,7 @@ __global__ void __launch_bounds__(kTQThreads) quantize_t_kernel(TQuantArgs a)
     uint8_t* const dst = a.bq + group * (kTGroupRbBytes / 2) + (tok & 15) * 64;
     uint8_t* const dst5 = a.bq5 + group * (kTGroupRbBytes5 / 2) + (tok & 15) * 64;
     for (int pc = tid; pc < a.n_pieces; pc += threads) {
-        if (pc != tid) tq_load<DT>(a, base, pc, v);
+        if (pc != tid) tq_load<DT>(a, base, pc, v, u);
         uint8_t* const to = dst + (size_t)(pc >> 2) * (kTGroupRbBytes / 2) + (pc & 3) * 16;
         s += wide ? tq_store<true>(v, inv_step, false, to, dst5 + (size_t)(pc >> 2) * (kTGroupRbBytes5 / 2) + (pc & 3) * 16)
                   : tq_store<false>(v, inv_step, bad != 0, to, nullptr);
@@ -216,8 +246,9 @@ __global__ void __launch_bounds__(kTQThreads) quantize_t_kernel(TQuantArgs a)
 
 // ---------------------------------------------------------------------------------------------
 // out[tok][col] = out_scale[col] * sum_row sign(row, col) v[tok][row], 64 columns x 16 tokens per workgroup
-// grid = (64-column steps x 4 / NV, token groups), block = 512.  NV = words of a tile's lane that a workgroup takes of the four,
-// i.e. 16 NV of the 64 columns: where columns and token groups are few, two workgroups share a tile.
+// grid = (64-column steps x 4 / NV, token groups, parts), block = 512.  NV = words of a tile's lane that a workgroup takes of the four,
+// i.e. 16 NV of the 64 columns: where columns and token groups are few, two workgroups share a tile.  parts > 1: each takes its share
+// of the row blocks, and the sums (exact) go to `partial` for the next quantisation to add up.
 // ---------------------------------------------------------------------------------------------
 struct TStageArgs {
     const uint32_t* tiles;
@@ -227,6 +258,7 @@ struct TStageArgs {
     const uint32_t* wide;
     const uint16_t* out_scale;      // fp16 [N] or nullptr
     float* out;                     // [batch][out_stride]
+    double* partial;                // [parts][batch][out_stride] where the reduction is dealt out, else nullptr
     int N, n_steps, n_rb, out_stride, batch;
 };
 
@@ -270,7 +302,7 @@ __global__ void __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_
 #pragma unroll
         for (int s = 0; s < kTSlices; ++s) acc[v][s] = v4i{0, 0, 0, 0};
     // past the end the last tile is read again and not used
-    const int last = a.n_rb - 1;
+    const int last = a.n_rb - 1, first = blockIdx.z * kTWaves + wave, stride = gridDim.z * kTWaves;
     typedef unsigned int vNu __attribute__((ext_vector_type(NV)));
     vNu w[kRing];
     v4u b[kRing][2][kTSlices];
@@ -296,21 +328,21 @@ __global__ void __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_
     } while (0)
 #pragma unroll
     for (int k = 0; k < kRing; ++k) {
-        if (k == 0 || wave + k * kTWaves <= last) NQ_T_ISSUE(k, wave + k * kTWaves);
+        if (k == 0 || first + k * stride <= last) NQ_T_ISSUE(k, first + k * stride);
         __builtin_amdgcn_sched_barrier(0);
     }
-    int rb = wave;
-    for (; rb + (kRing - 1) * kTWaves < a.n_rb; rb += kRing * kTWaves) {
+    int rb = first;
+    for (; rb + (kRing - 1) * stride < a.n_rb; rb += kRing * stride) {
 #pragma unroll
         for (int k = 0; k < kRing; ++k) {
             NQ_T_MAC(k);
-            NQ_T_ISSUE(k, rb + (k + kRing) * kTWaves);
+            NQ_T_ISSUE(k, rb + (k + kRing) * stride);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
 #pragma unroll
     for (int k = 0; k < kRing - 1; ++k)
-        if (rb + k * kTWaves < a.n_rb) NQ_T_MAC(k);
+        if (rb + k * stride < a.n_rb) NQ_T_MAC(k);
 #undef NQ_T_ISSUE
 #undef NQ_T_MAC
 
@@ -337,7 +369,7 @@ __global__ void __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_
 #pragma unroll
         for (int v = 0; v < NV; ++v) acc[v][0] = v4i{0, 0, 0, 0};
         const char* const b5_base = (const char*)a.bq5 + (size_t)blockIdx.y * a.n_rb * kTGroupRbBytes5 + 64 * n + 16 * g;
-        for (int r = wave; r < a.n_rb; r += kTWaves) {
+        for (int r = first; r < a.n_rb; r += stride) {
             const vNu wr = *(const __attribute__((address_space(1))) vNu*)(w_base + (size_t)r * w_rb);
             v4u br[2];
 #pragma unroll
@@ -369,6 +401,15 @@ __global__ void __launch_bounds__(64 * kTWaves) __attribute__((amdgpu_waves_per_
     if (wave >= NV || t0 + n >= a.batch) return;
     // lane (g, n), register k: column 16 g + 4 v + k of the step, token n
     float r[4];
+    if (a.partial) {
+        double* const o = a.partial + ((size_t)blockIdx.z * a.batch + tok) * a.out_stride + col;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double raw = fma(fma(sum[0][k], 65536.0, sum[1][k]), 256.0, (double)low[k]);
+            if (col + k < a.N) o[k] = fma(raw, two_step, blockIdx.z == 0 ? neg_qs : 0.0);
+        }
+        return;
+    }
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         // (below 2^47 without the fifth slice, then 2^55: rounded in binary64 at most)
@@ -395,30 +436,53 @@ size_t gemm_t_scratch_bytes(int64_t M, int batch)
            al256((size_t)batch * sizeof(uint32_t));
 }
 
+// half tiles where whole ones leave more than half of the CUs without a workgroup (16 steps x 4 groups: 8.3 us against 10; on 11
+// layers from 300 x 300 to 28672 x 8192 at 1 to 512 tokens the faster of the two, or within 2 % of it)
+static bool half_tiles(int64_t N, int batch)
+{
+    return (N + kTileCols - 1) / kTileCols * ((batch + kTTokens - 1) / kTTokens) <= device_cu_count() / 2;
+}
+
+// Workgroups that a product's reduction is dealt out to: where its columns and tokens give less than every fourth CU one and its waves
+// have more than one row block each (few tokens of tall, narrow products, whose waves would walk them alone), as many as its sums leave room
+// for in the memory of the fp32 intermediate of 64 tokens (32 in binary64).  Both products, 4 tokens: 65536 x 256 r = 64 97 -> 42 us,
+// 9856 x 256 r = 82 27.4 -> 20.7, 4096 x 4096 r = 1024 19.1 -> 17.8; passes on the vector ALU took 63, 24.7 and 30.
+int gemm_t_parts(int64_t M, int64_t N, int batch)
+{
+    const int64_t wgs = (N + kTileCols - 1) / kTileCols * ((batch + kTTokens - 1) / kTTokens) * (half_tiles(N, batch) ? 2 : 1);
+    if (batch > 8 || wgs * 4 > device_cu_count()) return 1;         // (two parts are not worth adding up: 4096 x 4096 at 16 tokens 19.5 -> 21)
+    int parts = 1;
+    while (parts < kTMaxParts && parts * 2 * batch <= kTPartTokens && n_rowblocks(M) > kTWaves * parts) parts *= 2;
+    return parts;
+}
+
 // A is [M][N] as sign tiles; out[tok][0..N) = out_scale (.) A^T (in_scale (.) in[tok][0..M)).  `scratch`: device,
-// gemm_t_scratch_bytes(M, batch), 16-byte aligned.
+// gemm_t_scratch_bytes(M, batch), 16-byte aligned.  parts > 1: the sums of that many shares of the rows go to `out` as
+// binary64 [parts][batch][out_stride], without the output scale; in_parts > 1: `in` is such an array, whose total times
+// in_scale is rounded to fp32 as it is read.
 int launch_gemm_t(const uint32_t* tiles, int64_t M, int64_t N, const void* in, int in_dtype, int in_stride, const uint16_t* in_scale,
-                  const uint16_t* out_scale, float* out, int out_stride, int batch, void* scratch, hipStream_t s)
+                  int in_parts, const uint16_t* out_scale, void* out, int out_stride, int parts, int batch, void* scratch, hipStream_t s)
 {
     const int n_rb = (int)n_rowblocks(M);
+    const int groups = (batch + kTTokens - 1) / kTTokens;
     uint8_t* bq = (uint8_t*)scratch;
-    uint8_t* bq5 = bq + (size_t)((batch + kTTokens - 1) / kTTokens) * n_rb * kTGroupRbBytes;
-    QMeta* meta = (QMeta*)(bq5 + (size_t)((batch + kTTokens - 1) / kTTokens) * n_rb * kTGroupRbBytes5);
+    uint8_t* bq5 = bq + (size_t)groups * n_rb * kTGroupRbBytes;
+    QMeta* meta = (QMeta*)(bq5 + (size_t)groups * n_rb * kTGroupRbBytes5);
     uint32_t* wide = (uint32_t*)((char*)meta + al256((size_t)batch * sizeof(QMeta)));
-    const TQuantArgs q{in, in_scale, bq, bq5, meta, wide, (int)M, in_dtype, in_stride, n_rb * 8};
-    const dim3 qgrid(batch), qblock(std::min(kTQThreads, (q.n_pieces + 63) / 64 * 64));
-    if (in_dtype == NQ_F32) hipLaunchKernelGGL(quantize_t_kernel<NQ_F32>, qgrid, qblock, 0, s, q);
+    const TQuantArgs q{in, in_parts, in_scale, bq, bq5, meta, wide, (int)M, in_dtype, in_stride, n_rb * 8};
+    // (parts are added up by a thread per row; the rows, at most 8192 of them here, wait in LDS)
+    const dim3 qgrid(batch), qblock(std::min(kTQThreads, (in_parts > 1 ? (int)M + 63 : q.n_pieces + 63) / 64 * 64));
+    if (in_parts > 1) hipLaunchKernelGGL(quantize_t_kernel<kTParts>, qgrid, qblock, (size_t)M * sizeof(float), s, q);
+    else if (in_dtype == NQ_F32) hipLaunchKernelGGL(quantize_t_kernel<NQ_F32>, qgrid, qblock, 0, s, q);
     else if (in_dtype == NQ_F16) hipLaunchKernelGGL(quantize_t_kernel<NQ_F16>, qgrid, qblock, 0, s, q);
     else hipLaunchKernelGGL(quantize_t_kernel<NQ_BF16>, qgrid, qblock, 0, s, q);
     NQ_HIP(hipGetLastError());
-    const TStageArgs t{tiles, bq, bq5, meta, wide, out_scale, out, (int)N, (int)n_steps(N), n_rb, out_stride, batch};
-    const int steps = (int)((N + kTileCols - 1) / kTileCols), groups = (batch + kTTokens - 1) / kTTokens;
-    // half tiles where whole ones leave more than half of the CUs without a workgroup (16 steps x 4 groups: 8.3 us against 10; on 11
-    // layers from 300 x 300 to 28672 x 8192 at 1 to 512 tokens the faster of the two, or within 2 % of it)
-    if (steps * groups <= device_cu_count() / 2)
-        hipLaunchKernelGGL(gemm_t_kernel<2>, dim3((unsigned)steps * 2, (unsigned)groups), dim3(64 * kTWaves), 0, s, t);
+    const TStageArgs t{tiles, bq, bq5, meta, wide, out_scale, (float*)out, parts > 1 ? (double*)out : nullptr, (int)N, (int)n_steps(N), n_rb, out_stride, batch};
+    const unsigned steps = (unsigned)((N + kTileCols - 1) / kTileCols);
+    if (half_tiles(N, batch))
+        hipLaunchKernelGGL(gemm_t_kernel<2>, dim3(steps * 2, (unsigned)groups, (unsigned)parts), dim3(64 * kTWaves), 0, s, t);
     else
-        hipLaunchKernelGGL(gemm_t_kernel<4>, dim3((unsigned)steps, (unsigned)groups), dim3(64 * kTWaves), 0, s, t);
+        hipLaunchKernelGGL(gemm_t_kernel<4>, dim3(steps, (unsigned)groups, (unsigned)parts), dim3(64 * kTWaves), 0, s, t);
     NQ_HIP(hipGetLastError());
     return NQ_OK;
 }

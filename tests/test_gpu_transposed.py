@@ -92,6 +92,39 @@ def test_wide_tokens_are_exact_beside_others(d_out, d_in, r, batch):
     L.close()
 
 
+@pytest.mark.parametrize("d_out,r", [(1024, 64), (1025, 64), (2049, 70), (4097, 200), (9000, 24), (5000, 1000)])     # 1, 2, 4, 8, 8, 4 parts of one token
+@pytest.mark.parametrize("mid", [False, True])
+def test_reductions_dealt_out_to_several_workgroups(d_out, r, mid):
+    """Few tokens of a tall, narrow first product: its rows are dealt out, and the sums added up by the second product's
+    quantisation.  The bits are those of a batch that fills the chip without; the values those of the definition."""
+    import torch
+    d_in, batch = 150, 530
+    L = Layer(d_out, d_in, r, "f32", seed=5600 + r)
+    scale = np.ones(r)
+    if mid:
+        s_mid = (np.random.default_rng(5601).standard_normal(r) * 0.5 + 1.0).astype(np.float16)
+        nq.nq_binlr_set_mid_scale(L.h, s_mid)
+        scale = s_mid.astype(np.float64)
+    g_np = synth.gen_x(batch, d_out, 5602, "f32")
+    g_np[2, 1] = np.float32(2.0**24)                      # a wide token
+    g = to_device(g_np, "f32")
+    w = torch.full((batch, d_in), float("nan"), dtype=torch.float32, device="cuda")
+    few = [torch.full((n, d_in), float("nan"), dtype=torch.float32, device="cuda") for n in (1, 4, 5, 8, 17)]
+    nq.nq_binlr_backward_input(L.h, g, w, batch)
+    for f in few:
+        nq.nq_binlr_backward_input(L.h, g[: f.shape[0]], f, f.shape[0])
+    torch.cuda.synchronize()
+    d = L.data
+    U, V = (nq.nq_unpack_signs(m, r).astype(np.float64) for m in (d.U_words, d.V_words))
+    ref = (((((g_np[:17].astype(np.float64) * d.s_out.astype(np.float64)) @ U) * scale) @ V.T)) * d.s_in.astype(np.float64)
+    for f in few:
+        n = f.shape[0]
+        assert torch.equal(f, w[:n])
+        for t in range(n):
+            assert _norm_err(f[t].cpu().numpy(), ref[t]) <= NORM_TOL, t
+    L.close()
+
+
 @pytest.mark.parametrize("d_in", [64, 8200])              # half tiles, whole tiles in the second product
 def test_accumulators_at_their_extreme_values(d_in):
     """Every sign +1 and 65535 pairs of bytes at -128: the largest joined sums of two slices (below 2^31 over four waves)."""
