@@ -181,13 +181,13 @@ quantize_kernel(const QuantDesc* __restrict__ descs, QuantDesc single, int batch
         for (int k = 0; k < kQuantHeld; ++k) {
             const int c = tid + k * kQuantThreads;
             if (c < d.n_chunks)
-                local_sum += quantize_chunk16<STREAMED>(hv[k], inv_step, bad, dst + bq_chunk_piece<GROUPED>(tok, c, d.n_chunks), bq_slice_pieces<GROUPED>());
+                local_sum += quantize_chunk16<STREAMED>(hv[k], inv_step, dst + bq_chunk_piece<GROUPED>(tok, c, d.n_chunks), bq_slice_pieces<GROUPED>());
         }
     } else {
         for (int c = tid; c < d.n_chunks; c += kQuantThreads) {
             float v[16];
             load_chunk16<ANY>(d, base, c, vec, v);
-            local_sum += quantize_chunk16<STREAMED>(v, inv_step, bad, dst + bq_chunk_piece<GROUPED>(tok, c, d.n_chunks), bq_slice_pieces<GROUPED>());
+            local_sum += quantize_chunk16<STREAMED>(v, inv_step, dst + bq_chunk_piece<GROUPED>(tok, c, d.n_chunks), bq_slice_pieces<GROUPED>());
         }
     }
     double s = (double)local_sum;               // |sum| < 2^39: exact
@@ -259,7 +259,7 @@ quantize_wave_kernel(const QuantDesc* __restrict__ descs, QuantDesc single, int 
 #pragma unroll
     for (int k = 0; k < H; ++k) {
         const int c = lane + 64 * k;
-        if (c < d.n_chunks) local_sum += quantize_chunk16<STREAMED>(hv[k], inv_step, bad != 0, dst + bq_chunk_piece<GROUPED>(tok, c, d.n_chunks), bq_slice_pieces<GROUPED>());
+        if (c < d.n_chunks) local_sum += quantize_chunk16<STREAMED>(hv[k], inv_step, dst + bq_chunk_piece<GROUPED>(tok, c, d.n_chunks), bq_slice_pieces<GROUPED>());
     }
     double sum = (double)local_sum;
     for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
@@ -1136,7 +1136,7 @@ stage_selfq_kernel(const FusedItem* __restrict__ items, QuantDesc q1, StageDesc 
 #pragma unroll
     for (int c = 0; c < C; ++c)
         if (lane + 64 * c < n_own)
-            local_sum += quantize_chunk16(hv[c], inv_step, bad != 0, (uint4*)my_bq + bq_piece(lane + 64 * c, 0));
+            local_sum += quantize_chunk16(hv[c], inv_step, (uint4*)my_bq + bq_piece(lane + 64 * c, 0));
     double sum = (double)local_sum;
     for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
     QMeta my_meta;
@@ -1308,7 +1308,7 @@ stage_fused_kernel(const FusedItem* __restrict__ items, QuantDesc q1, StageDesc 
     }
     const float inv_step = 1.0f / step;
     long long local_sum = 0;
-    if (mine) local_sum = quantize_chunk16(v, inv_step, bad != 0, (uint4*)lds_bq + bq_piece(tid, 0));
+    if (mine) local_sum = quantize_chunk16(v, inv_step, (uint4*)lds_bq + bq_piece(tid, 0));
     double sum = (double)local_sum;
     for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
     if (lane == 0) red_d[wave] = sum;

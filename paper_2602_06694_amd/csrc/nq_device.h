@@ -20,6 +20,10 @@ __device__ inline float load_as_float(const void* p, int dtype, int64_t idx)
     return bf16_bits_to_float(((const uint16_t*)p)[idx]);
 }
 
+// v times an fp16 scale, rounded once to fp32.  (Written as a fused operation because that takes the fp16 operand, or both, as it is;
+// the zero it adds only turns -0 into +0, which is the same fixed point.)
+__device__ __forceinline__ float times_half(float v, uint16_t s) { return __builtin_fmaf(v, half_bits_to_float(s), 0.0f); }
+
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef const __attribute__((address_space(1))) v4u* gptr_v4u;    // global (not generic) address space
@@ -77,8 +81,8 @@ __device__ inline void load_chunk16(const QuantDesc& d, int64_t base, int c, boo
                 uint32_t w[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    v[8 * q + 2 * i] *= half_bits_to_float((uint16_t)(w[i] & 0xFFFFu));
-                    v[8 * q + 2 * i + 1] *= half_bits_to_float((uint16_t)(w[i] >> 16));
+                    v[8 * q + 2 * i] = times_half(v[8 * q + 2 * i], (uint16_t)(w[i] & 0xFFFFu));
+                    v[8 * q + 2 * i + 1] = times_half(v[8 * q + 2 * i + 1], (uint16_t)(w[i] >> 16));
                 }
             }
         }
@@ -104,29 +108,35 @@ __device__ __forceinline__ uint32_t pack_low_bytes(uint32_t a, uint32_t b, uint3
     return __builtin_amdgcn_perm(cd, ab, 0x05040100u);                 // ab.0, ab.1, cd.0, cd.1
 }
 
-// q = 65536 hi + 256 mid + lo with signed bytes: lo is the (sign-extended) low byte of q,
-// mid that of q1 = (q - lo) / 256 = (q + 128) >> 8, hi = (q1 + 128) >> 8; only the low bytes are kept
+// Four values to fixed point: q = rint(v / step), |q| <= 2^22, as q = 65536 hi + 256 mid + lo with signed bytes: the words of the
+// four hi, mid and lo bytes.  Returns the sum of the four q.
+// Five vector instructions per value instead of eleven: v / step + 1.5 * 2^23 leaves no fraction (one rounding, to nearest even), its bits are
+// a constant plus q, and with 0x8080 added their low three bytes are lo + 128, mid + 128 and hi; the 128s go with one exclusive or per
+// word.  (A token with a non-finite value gets any bytes: its constants make NaN of whatever they sum up to.)
+__device__ __forceinline__ int quantize4(float v0, float v1, float v2, float v3, float inv_step, uint32_t& hi, uint32_t& mid, uint32_t& lo)
+{
+    constexpr float kRound = 12582912.0f;                              // 1.5 * 2^23, bits 0x4b400000
+    constexpr uint32_t kBias = 0x8080u - 0x400000u;
+    const uint32_t a = __builtin_bit_cast(uint32_t, __builtin_fmaf(v0, inv_step, kRound)) + kBias;
+    const uint32_t b = __builtin_bit_cast(uint32_t, __builtin_fmaf(v1, inv_step, kRound)) + kBias;
+    const uint32_t c = __builtin_bit_cast(uint32_t, __builtin_fmaf(v2, inv_step, kRound)) + kBias;
+    const uint32_t d = __builtin_bit_cast(uint32_t, __builtin_fmaf(v3, inv_step, kRound)) + kBias;
+    const uint32_t ab = __builtin_amdgcn_perm(b, a, 0x05010400u);      // bytes: a.0, b.0, a.1, b.1
+    const uint32_t cd = __builtin_amdgcn_perm(d, c, 0x05010400u);
+    lo = __builtin_amdgcn_perm(cd, ab, 0x05040100u) ^ 0x80808080u;
+    mid = __builtin_amdgcn_perm(cd, ab, 0x07060302u) ^ 0x80808080u;
+    hi = __builtin_amdgcn_perm(__builtin_amdgcn_perm(d, c, 0x0c0c0602u), __builtin_amdgcn_perm(b, a, 0x0c0c0602u), 0x05040100u);
+    return (int)(a + b + (c + d) - 4u * (0x4b400000u + kBias));        // (modulo 2^32; the sum itself fits)
+}
+
+// a chunk of 16 values: its pieces go to dst, slices `slice_pieces` pieces apart; returns the sum of its q
 template <bool STREAMED = false>
-__device__ inline long long quantize_chunk16(const float v[16], float inv_step, bool bad, uint4* dst, int slice_pieces = 4)
+__device__ inline int quantize_chunk16(const float v[16], float inv_step, uint4* dst, int slice_pieces = 4)
 {
     uint32_t hi[4], mid[4], lo[4];
     int sum = 0;                                            // |q| <= 2^22, 16 of them: fits
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        uint32_t q0[4], q1[4], q2[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int q = bad ? 0 : (int)rintf(v[4 * w + i] * inv_step);
-            sum += q;
-            const int m = (q + 128) >> 8;
-            q0[i] = (uint32_t)q;
-            q1[i] = (uint32_t)m;
-            q2[i] = (uint32_t)((m + 128) >> 8);
-        }
-        lo[w] = pack_low_bytes(q0[0], q0[1], q0[2], q0[3]);
-        mid[w] = pack_low_bytes(q1[0], q1[1], q1[2], q1[3]);
-        hi[w] = pack_low_bytes(q2[0], q2[1], q2[2], q2[3]);
-    }
+    for (int w = 0; w < 4; ++w) sum += quantize4(v[4 * w], v[4 * w + 1], v[4 * w + 2], v[4 * w + 3], inv_step, hi[w], mid[w], lo[w]);
     // the three slices of a chunk sit 4 pieces apart (see bq_piece): consecutive threads = consecutive
     // chunks of a step fill whole 64-byte lines with each of the three stores
     if (STREAMED) {

@@ -401,13 +401,13 @@ __device__ __forceinline__ void exec_body(const ExecTask* __restrict__ tasks, in
                 for (int c = 0; c < kExecHeld; ++c) {
                     const int ch = tid + c * kExecThreads;
                     if (c < n_c && ch < n_chunks)
-                        local_sum += quantize_chunk16(hv[c], inv_step, bad != 0, (uint4*)lds_bq + bq_piece(ch, 0));
+                        local_sum += quantize_chunk16(hv[c], inv_step, (uint4*)lds_bq + bq_piece(ch, 0));
                 }
             } else {
                 for (int c = 0; c < n_c; ++c) {
                     const int ch = tid + c * kExecThreads;
                     fetch(ch, kExecHeld, hv[0]);            // (pairs this thread has already seen valid)
-                    if (ch < n_chunks) local_sum += quantize_chunk16(hv[0], inv_step, bad != 0, (uint4*)lds_bq + bq_piece(ch, 0));
+                    if (ch < n_chunks) local_sum += quantize_chunk16(hv[0], inv_step, (uint4*)lds_bq + bq_piece(ch, 0));
                 }
             }
             local_sum = wave_sum64(local_sum);
