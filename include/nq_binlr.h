@@ -259,7 +259,8 @@ int nq_plan_forward_timed(nq_plan p, void* stream, float ms[4]);
  * (batch 6..8, long reductions), 32 = short batch-1 launch with reductions of 4097..16384 elements in which every
  * workgroup (16 waves per row block) quantises the input for itself,
  * 33 / 34 = batch-1 launch whose waves quantise their own share of the input (one / four waves per
- * row block; reductions of at most 1024 / 4096 elements). */
+ * row block; reductions of at most 1024 / 4096 elements), 35 = short launch at batch 2..8 in which every workgroup
+ * quantises the input for itself. */
 int nq_plan_schedules(nq_plan p, int w[2]);
 int nq_plan_destroy(nq_plan p);
 

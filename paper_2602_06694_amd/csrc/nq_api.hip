@@ -674,6 +674,17 @@ static int rbs_per_stream_item(int n_rb, int nst, int total_rb, int batch)
     return std::min(per, std::max(1, n_rb));
 }
 
+// One stage of a lone layer with at most as many row blocks as CUs.  More than half as many leave nothing to deal out: with an input too long
+// to quantise along, the schedules of the larger launches.
+static int lone_stage(const QuantDesc& q, const StageDesc& sd, int n_rb, int w, int per, int batch, hipStream_t s)
+{
+    if (lone_selfq(sd.n_steps, n_rb, batch)) return launch_lone_selfq(nullptr, n_rb, q, sd, sd.n_steps, batch, s);
+    const int rc = launch_quantize(nullptr, q, 1, q.n_chunks, batch, s);
+    if (rc != NQ_OK) return rc;
+    if (lone_planes(n_rb) < 8) return launch_lone(nullptr, n_rb, sd, 16, batch, s);
+    return launch_stage(nullptr, sd, nullptr, (n_rb + per - 1) / per, w, per, batch, s);
+}
+
 // one pass of the streaming path for batch <= 8; `unscaled`: without the output scale (z = U t)
 // (`w`: the workspace the kernels use -- the layer's own, or one carved out of the static scratch array)
 static int decode_once(nq_handle h, const DecodeWorkspace& w, const void* x, void* y, int batch, hipStream_t s,
@@ -703,6 +714,12 @@ static int decode_once(nq_handle h, const DecodeWorkspace& w, const void* x, voi
     // (reductions of up to 4096 elements by the waves of the one- or four-wave kernel, longer ones
     // up to 16384 by the 16-wave kernel)
     const bool no_fuse = opt_flag(OPT_NO_FUSE), no_selfq = opt_flag(OPT_NO_SELFQ);
+    // (few row blocks, whatever the batch: nq_lone.hip)
+    if (!no_selfq && opt(OPT_FORCE_W) < 0 && rb1 <= device_cu_count() && rb2 <= device_cu_count()) {
+        if (lone_layer_fits(qt, s1, s2, batch)) return launch_lone_layer(qx, s1, qt, s2, batch, s);
+        if ((rc = lone_stage(qx, s1, rb1, w1, per1, batch, s)) != NQ_OK) return rc;
+        return lone_stage(qt, s2, rb2, w2, per2, batch, s);
+    }
     const int sq1 = no_selfq ? 0 : selfq_width(s1.n_steps, s1.n_steps, batch);
     const int sq2 = no_selfq ? 0 : selfq_width(s2.n_steps, s2.n_steps, batch);
     if (sq1) {
@@ -976,6 +993,16 @@ extern "C" int nq_plan_create(nq_plan* out, const nq_handle* hs, const void* con
                 selfq_fits(w, max_steps, min_steps, batch))
                 w = w == 1 ? kSelfqSchedule1 : kSelfqSchedule4;
         }
+        // The same above batch 1, and 16 waves per workgroup where the input is too long for that (nq_lone.hip; us per plan, before and after):
+        // q, k, v of a 70B-shaped block at batch 4 21.1 -> 15.0, six 4096 x 4096 layers at batch 3 16.9 -> 12.7, twelve 17.5 -> 14.7, all seven
+        // projections of a 7B-shaped block as four plans 76.2 -> 56.5 at batch 4, 103 -> 75 at batch 8.  (At batch 2 more than four layers, and reductions longer than those of
+        // the 7B shapes, would gain too -- 28 row blocks of 192 steps 22.1 -> 13.0 us, five layers 18.3 -> 12.2 -- but keep the widths
+        // that split_width() gives them, which callers are told by nq_plan_schedules.)
+        if ((batch > 2 || (batch == 2 && n <= 4)) && max_steps <= 176 && total_rb <= device_cu_count() && total_rb < schedule_full_rowblocks() &&
+            !opt_flag(OPT_NO_SELFQ) && opt(OPT_FORCE_W) < 0) {
+            if (lone_selfq(max_steps, total_rb, batch)) w = kLoneSchedule;
+            else if (batch > 2 && lone_planes(total_rb) < 8) w = 16;
+        }
         // Option "two_slice_b8": at batch 6..8 the shared-input launches take their input as 16-bit fixed point (the top
         // byte slice stays zero), which puts the eight tokens into ONE group of 16 MFMA columns instead of two.
         if (opt_flag(OPT_TWO_SLICE_B8) && batch >= 6 && (w == kSharedSchedule || w == kSharedResidentSchedule)) {
@@ -1066,7 +1093,8 @@ extern "C" int nq_plan_create(nq_plan* out, const nq_handle* hs, const void* con
     // stages on the fused schedule get items that carry their op's descriptors
     std::vector<FusedItem> fit[2];
     for (int st = 0; st < 2; ++st) {
-        if (sched[st] != kFusedSchedule && sched[st] != kSelfqSchedule1 && sched[st] != kSelfqSchedule4) continue;
+        if (sched[st] != kFusedSchedule && sched[st] != kSelfqSchedule1 && sched[st] != kSelfqSchedule4 && sched[st] != kLoneSchedule && !is_wide_split(sched[st]))
+            continue;
         for (const WorkItem& w : lists[st]) {
             FusedItem f{};
             f.q = st == 0 ? qx[w.op] : qt[w.op];
@@ -1108,12 +1136,17 @@ static int plan_run(nq_plan p, hipStream_t s, bool timed)
     const StageDesc sdummy{};
     int rc;
     // a stage on one of the self-quantising schedules has no quantisation launch
-    auto self_quantising = [](int w) { return w == kFusedSchedule || w == kSelfqSchedule1 || w == kSelfqSchedule4; };
+    auto self_quantising = [](int w) { return w == kFusedSchedule || w == kSelfqSchedule1 || w == kSelfqSchedule4 || w == kLoneSchedule; };
     auto run_stage = [&](int w, const StageDesc* sd, const WorkItem* items, const FusedItem* fitems, int n_items,
                          int max_steps) {
+        // (the same 16 waves per workgroup, each taking some bit planes of a row block: stage 1 of the q, k, v of a 70B-shaped block)
+        if (w == kFusedSchedule && n_items <= device_cu_count() && lone_planes(n_items) < 8 && lone_selfq(max_steps, n_items, p->batch))
+            return launch_lone_selfq(fitems, n_items, qdummy, sdummy, max_steps, p->batch, s);
         if (w == kFusedSchedule) return launch_fused_list(fitems, n_items, max_steps, s);
         if (w == kSelfqSchedule1 || w == kSelfqSchedule4)
             return launch_selfq(fitems, n_items, qdummy, sdummy, w == kSelfqSchedule1 ? 1 : 4, max_steps, s);
+        if (w == kLoneSchedule) return launch_lone_selfq(fitems, n_items, qdummy, sdummy, max_steps, p->batch, s);
+        if (is_wide_split(w)) return launch_lone(fitems, n_items, sdummy, w == kSplit8Schedule ? 8 : 16, p->batch, s);
         return launch_stage(sd, sdummy, items, n_items, w, stream_max_rbs(p->batch), p->batch, s);
     };
     // timed: launch k carries the event pair ev[2k], ev[2k + 1], bound to the kernel itself (see LaunchTiming)
@@ -1165,7 +1198,7 @@ extern "C" int nq_plan_forward_timed(nq_plan p, void* stream, float ms[4])
     int rc = plan_run(p, (hipStream_t)stream, true);
     if (rc != NQ_OK) return rc;
     NQ_HIP(hipEventSynchronize(p->ev[7]));
-    auto self_quantising = [](int w) { return w == kFusedSchedule || w == kSelfqSchedule1 || w == kSelfqSchedule4; };
+    auto self_quantising = [](int w) { return w == kFusedSchedule || w == kSelfqSchedule1 || w == kSelfqSchedule4 || w == kLoneSchedule; };
     ms[0] = ms[2] = 0.f;
     if (!self_quantising(p->w1)) NQ_HIP(hipEventElapsedTime(&ms[0], p->ev[0], p->ev[1]));
     NQ_HIP(hipEventElapsedTime(&ms[1], p->ev[2], p->ev[3]));

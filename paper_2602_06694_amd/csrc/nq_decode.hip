@@ -372,7 +372,7 @@ int launch_pack_signs(const void* d_signs, int dtype, int64_t rows, int64_t cols
 //       consecutive short ones of one op; their tiles are contiguous in memory, so the prefetch
 //       ring keeps running across block boundaries and only the accumulators are flushed there.
 //       For short reductions.
-//   stage_split_kernel<W> : W waves of one workgroup interleave the 64-column steps of ONE row
+//   stage_split_kernel<W> : W waves of one workgroup (four; 16 and eight: stage_lone_kernel, nq_lone.hip) interleave the 64-column steps of ONE row
 //       block and are summed through LDS.  For long reductions, and for launches with too few row
 //       blocks to fill the chip.
 //   stage_shared_kernel : the waves of a workgroup take row blocks of one op and share its quantised input
@@ -1201,9 +1201,8 @@ stage_selfq_kernel(const FusedItem* __restrict__ items, QuantDesc q1, StageDesc 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Fourth schedule, for ONE layer on its own at batch 1 (nq_binlr_forward): a stage and the
-// quantisation of its input in a single launch, so that a forward is two dependent launches
-// instead of four -- a lone layer is bound by launch latency (about 4 us per dependent launch),
+// Fourth schedule, for short launches at batch 1 with more than half as many row blocks as CUs (fewer: nq_lone.hip): a stage and the
+// quantisation of its input in a single launch -- such a launch is bound by latency (about 4 us per dependent launch),
 // not by bandwidth.  One workgroup of 16 waves per row block, as in the split kernel; every
 // workgroup quantises the whole input vector for itself (one chunk of 16 values per thread, kept
 // in registers between the max pass and the quantising pass) into LDS, in the layout of the
@@ -1379,10 +1378,11 @@ static int launch_stream_t(const StageDesc* d_descs, const StageDesc& single, co
     return NQ_OK;
 }
 
-template <int NB, int W>
+template <int NB>
 static int launch_split_t(const StageDesc* d_descs, const StageDesc& single, const WorkItem* d_items, int n_items,
                           int batch, hipStream_t s)
 {
+    constexpr int W = 4;
     size_t lds_bytes = (size_t)W * kEpiRegion * sizeof(int);
     if (n_items < 1) return NQ_OK;
     NQ_LAUNCH((stage_split_kernel<NB, W, (NB == 1 ? kRingDepth : 2 * kRingDepth)>), dim3(n_items), dim3(64 * W), lds_bytes, s, d_descs,
@@ -1623,12 +1623,9 @@ int launch_stage(const StageDesc* d_descs, const StageDesc& single, const WorkIt
         if (nb == 1) return launch_stream_t<1>(d_descs, single, d_items, n_items, rbs_per_item, mx, batch, s);
         return launch_stream_t<2>(d_descs, single, d_items, n_items, rbs_per_item, mx, batch, s);
     }
-    if (nb == 1) {
-        if (w == 4) return launch_split_t<1, 4>(d_descs, single, d_items, n_items, batch, s);
-        return launch_split_t<1, 16>(d_descs, single, d_items, n_items, batch, s);
-    }
-    if (w == kSplit8Schedule) return launch_split_t<2, 8>(d_descs, single, d_items, n_items, batch, s);
-    return launch_split_t<2, 4>(d_descs, single, d_items, n_items, batch, s);
+    if (is_wide_split(w)) return launch_lone(nullptr, n_items, single, w == kSplit8Schedule ? 8 : 16, batch, s);      // (plans: see plan_run)
+    if (nb == 1) return launch_split_t<1>(d_descs, single, d_items, n_items, batch, s);
+    return launch_split_t<2>(d_descs, single, d_items, n_items, batch, s);
 }
 
 // ---------------------------------------------------------------------------------------------

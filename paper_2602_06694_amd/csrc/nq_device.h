@@ -177,4 +177,46 @@ __device__ __forceinline__ void mac_tile(v4i (&acc)[NB][8], const v4u w, const v
     }
 }
 
+// Reductions over a wavefront on the data-parallel-primitive path of the vector unit (no LDS traffic):
+// quad exchanges, mirrored halves of a 16-lane row, then the four rows through scalar registers.
+// The result is the same in every lane.
+template <class T, class Op>
+__device__ __forceinline__ T wave_reduce32(T v, Op op)
+{
+    static_assert(sizeof(T) == 4, "32-bit values");
+    auto dpp = [](T x, auto ctrl) {
+        return __builtin_bit_cast(T, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, true));
+    };
+    v = op(v, dpp(v, std::integral_constant<int, 0xB1>{}));      // quad_perm [1, 0, 3, 2]
+    v = op(v, dpp(v, std::integral_constant<int, 0x4E>{}));      // quad_perm [2, 3, 0, 1]
+    v = op(v, dpp(v, std::integral_constant<int, 0x141>{}));     // row_half_mirror
+    v = op(v, dpp(v, std::integral_constant<int, 0x140>{}));     // row_mirror
+    const int b = __builtin_bit_cast(int, v);
+    const T r0 = __builtin_bit_cast(T, __builtin_amdgcn_readlane(b, 0)), r1 = __builtin_bit_cast(T, __builtin_amdgcn_readlane(b, 16));
+    const T r2 = __builtin_bit_cast(T, __builtin_amdgcn_readlane(b, 32)), r3 = __builtin_bit_cast(T, __builtin_amdgcn_readlane(b, 48));
+    return op(op(r0, r1), op(r2, r3));
+}
+
+// sum of a 64-bit integer over the wavefront (the halves travel separately, the additions are 64-bit)
+__device__ __forceinline__ long long wave_sum64(long long v)
+{
+    auto dpp = [](long long x, auto ctrl) {
+        const int lo = __builtin_amdgcn_mov_dpp((int)(unsigned int)(unsigned long long)x, decltype(ctrl)::value, 0xf, 0xf, true);
+        const int hi = __builtin_amdgcn_mov_dpp((int)(unsigned int)((unsigned long long)x >> 32), decltype(ctrl)::value, 0xf, 0xf, true);
+        return (long long)(((unsigned long long)(unsigned int)hi << 32) | (unsigned int)lo);
+    };
+    v += dpp(v, std::integral_constant<int, 0xB1>{});
+    v += dpp(v, std::integral_constant<int, 0x4E>{});
+    v += dpp(v, std::integral_constant<int, 0x141>{});
+    v += dpp(v, std::integral_constant<int, 0x140>{});
+    long long t = 0;
+#pragma unroll
+    for (int r = 0; r < 64; r += 16) {
+        const unsigned int lo = (unsigned int)__builtin_amdgcn_readlane((int)(unsigned int)(unsigned long long)v, r);
+        const unsigned int hi = (unsigned int)__builtin_amdgcn_readlane((int)(unsigned int)((unsigned long long)v >> 32), r);
+        t += (long long)(((unsigned long long)hi << 32) | lo);
+    }
+    return t;
+}
+
 }  // namespace nq

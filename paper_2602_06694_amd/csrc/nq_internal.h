@@ -286,6 +286,7 @@ constexpr int kSharedResidentSchedule = 9;   // the same kernel with the whole i
 // the two with 16-bit fixed point at batch 6..8: a token takes two MFMA columns, eight tokens one group of 16
 constexpr int kSharedSchedule2 = 10, kSharedResidentSchedule2 = 11;
 constexpr int kSplit8Schedule = 12;      // eight waves per row block (batch 6..8; 1, 4 and 16 stand for themselves)
+inline bool is_wide_split(int w) { return w == 16 || w == kSplit8Schedule; }
 inline bool is_shared_schedule(int w) { return w >= kSharedSchedule && w <= kSharedResidentSchedule2; }
 int shared_per_wave(int nst, int batch); // row blocks per wave of an item of that kernel
 // w = 1: stream kernel (items are runs of rbs_per_item row blocks); w = 4 / 16: split kernel (one row block
@@ -317,6 +318,15 @@ size_t gemm_t_scratch_bytes(int64_t M, int batch);
 int gemm_t_parts(int64_t M, int64_t N, int batch);
 int launch_gemm_t(const uint32_t* tiles, int64_t M, int64_t N, const void* in, int in_dtype, int in_stride, const uint16_t* in_scale,
                   int in_parts, const uint16_t* out_scale, void* out, int out_stride, int parts, int batch, void* scratch, hipStream_t s);
+
+// ---- launchers (nq_lone.hip) ----------------------------------------------------------------
+constexpr int kLoneSchedule = 35;        // plan schedule code: few row blocks, batch 2 to 8, the workgroups quantise the input
+int lone_planes(int n_rb);
+bool lone_selfq(int max_steps, int n_rb, int batch);
+int launch_lone_selfq(const FusedItem* d_items, int n_rb, const QuantDesc& q, const StageDesc& sd, int max_steps, int batch, hipStream_t s);
+int launch_lone(const FusedItem* d_items, int n_rb, const StageDesc& sd, int w, int batch, hipStream_t s);
+bool lone_layer_fits(const QuantDesc& qt, const StageDesc& s1, const StageDesc& s2, int batch);
+int launch_lone_layer(const QuantDesc& qx, const StageDesc& s1, const QuantDesc& qt, const StageDesc& s2, int batch, hipStream_t s);
 
 // ---- launchers (nq_exact.hip) ---------------------------------------------------------------
 int launch_stage_exact(const StageDesc& d, int batch, hipStream_t s);

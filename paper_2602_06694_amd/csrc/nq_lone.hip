@@ -1,0 +1,725 @@
+// Stages of the streaming path (batch <= 8) for launches that are far from filling the chip: a layer on its own, or the few layers of
+// one level of a decoder block (Section 3.1 Eq. 1 as two sign-matrix x vector products, Appendix E.2).  Such a launch is bound by latency:
+// by the host, which takes 2.7 to 3 us per launch, and by the chain  input -> fixed point -> tiles -> sums -> store  of a workgroup.
+//   - The workgroups of a stage quantise its input themselves where it is short (SELFQ): one launch instead of two.
+//   - A row block is dealt out to 8 / PL workgroups by BIT PLANES: each streams the same tiles, multiplies PL of the eight planes (16
+//     rows each) and finishes its own rows, so that nothing has to be added up between workgroups.  They share an XCD and its L2.
+//   - stage_layer_kernel: a small layer in ONE launch, every workgroup computing the whole of t for itself.
+// The arithmetic is that of quantize_kernel and stage_split_kernel (nq_decode.hip) element for element: the same bits.
+//
+// Whole forwards, us per call, against four launches (batch 1: two self-quantising ones of one, four or 16 waves per row block, each with all
+// planes of it); what two launches cost the host alone is 8.8:
+//   4096 x 4096 r = 1024   batch 1 11.1 -> 8.9, 2 15.5 -> 9.1, 4 15.8 -> 10.1, 8 22.8 -> 13.1
+//   5003 x 3001 r = 777    batch 6 25.0 -> 13.3        1024 x 1024 r = 256   batch 1 10.4 -> 8.0 (one launch), 4 13.6 -> 9.0
+//   8192 x 8192 r = 2240   batch 1 16.5 -> 9.8, 4 20.5 -> 13.6, 8 28.6 -> 20.6 (stage 1 after a quantisation launch)
+//   8192 x 28672 r = 3520  batch 1 29.0 -> 15.2, 4 34.3 -> 25.3 (likewise); 28672 x 8192 r = 3520 batch 1 18.2 -> 12.3, 4 22.3 -> 17.8
+#include <algorithm>
+
+#include "nq_internal.h"
+#include "nq_device.h"
+
+namespace nq {
+
+typedef const __attribute__((address_space(4))) QMeta* cptr_meta;
+
+// A "unit" is what a wave quantises at a time: 64 chunks of 16 elements of one token, one per lane; in the one-launch kernel, whose
+// vectors are so short that this would leave most waves idle, 64 groups of four (E = 4).  Up to 32768 elements are quantised by the workgroups of the stage,
+// two units per wave of 16, which is also what LDS holds; at that length a launch of its own takes about as long, and the host one launch more
+// (4096 x 4096 at batch 8 15.0 us without it, 14.8 with; 8192 wide at batch 4 20.4 and 21.0).
+constexpr int kLoneMaxElements = 32768;
+template <int W, int E> constexpr int lone_share_units() { return kLoneMaxElements / (64 * E) / W; }
+constexpr int kLonePlaneInts = 4 * 68;     // a wave's sums of one bit plane in LDS: four row groups of 16 columns x 4 rows, 68 ints apart (banks)
+
+template <int E> __host__ __device__ inline int lone_pieces(int nst) { return (nst + E - 1) / E; }      // units per token
+// fixed point of a token in LDS: [step][chunk][slice][16 bytes], tokens 48 mod 256 bytes apart: the 15 (token, slice) operands of a
+// 16-lane group fall on different banks
+__host__ __device__ inline int lone_tok_bytes(int nst) { return nst * (int)kBqStepBytes + 48; }
+// bit planes whose sums pass through LDS at a time
+constexpr int lone_round(int nb, int pl) { return pl < 4 / nb ? pl : 4 / nb; }
+constexpr int lone_red_ints(int nb, int pl, int w) { return w * nb * lone_round(nb, pl) * kLonePlaneInts; }
+
+// 2^e, -126 <= e <= 127
+__device__ __forceinline__ float exp2_int(int e) { return __builtin_bit_cast(float, (e + 127) << 23); }
+// exponent of the quantisation step of a token whose largest magnitude has the bits `m` (0 for a token of zeros or with a non-finite value):
+// f 2^e with f in [0.5, 1) gives 2^(e - 22), at least the smallest normal number
+constexpr uint32_t kLoneMostBits = 0x7f61b1e6u;            // of 3.0e38: larger ones (infinities and NaNs among them) count as not finite
+__device__ __forceinline__ int step_exponent(uint32_t m)
+{
+    const int se = (int)(m >> 23) - 126 - 22;
+    return m != 0 && m <= kLoneMostBits ? (se < -126 ? -126 : se) : 0;
+}
+
+// What the units of a launch's tokens leave in LDS: the bits of their largest magnitude and the sum of their q
+struct LoneTokens {
+    unsigned long long sum[8];
+    uint32_t max[8];
+};
+
+__device__ __forceinline__ void lone_clear(LoneTokens* lt, int tid)
+{
+    if (tid < 8) {
+        lt->sum[tid] = 0;
+        lt->max[tid] = 0;
+    }
+}
+
+__device__ __forceinline__ QMeta lone_meta(const LoneTokens* lt, int tok)
+{
+    const uint32_t m = lt->max[tok];
+    const float step = exp2_int(step_exponent(m));
+    QMeta mt;
+    mt.two_step = m <= kLoneMostBits ? 2.0 * (double)step : (double)__builtin_nanf("");
+    mt.neg_qs = -(double)(long long)lt->sum[tok] * (double)step;
+    return mt;
+}
+
+// The units of one wave: `n` consecutive ones, so that few tokens end inside its share.  Wave-uniform.
+struct LoneShare {
+    int n, tok, piece;
+};
+template <int W>
+__device__ __forceinline__ LoneShare lone_share(int units, int pieces, int wave)
+{
+    const int per = (units + W - 1) / W, u0 = wave * per;
+    LoneShare sh;
+    sh.n = units - u0 < per ? (units - u0 > 0 ? units - u0 : 0) : per;
+    // (the quotient is exact for the small integers that occur)
+    sh.tok = __builtin_amdgcn_readfirstlane((int)(((float)u0 + 0.5f) * __builtin_amdgcn_rcpf((float)pieces)));
+    sh.piece = u0 - sh.tok * pieces;
+    return sh;
+}
+__device__ __forceinline__ void lone_next(LoneShare& sh, int pieces)
+{
+    if (++sh.piece == pieces) {
+        sh.piece = 0;
+        ++sh.tok;
+    }
+}
+
+// The elements of a lane and their scales as they are in memory: requested for all of a wave's units before the first is looked at.
+template <int E>
+struct LoneRaw {
+    v4u x[E / 4];                                           // 16-bit inputs: the first half
+    unsigned int s[E / 2];
+};
+
+// Elements j0 .. j0 + E - 1 of token row `base`.  Rows lie at the alignment of an element, which global memory takes.  A lane whose elements
+// reach past the row's end requests the row's last E, which lone_value() moves into place (rows shorter than E: one at a time).
+template <int E>
+__device__ __forceinline__ void lone_request(const QuantDesc& d, int64_t base, int j0, LoneRaw<E>& r)
+{
+    typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+    typedef v4u v4u_elem __attribute__((aligned(2)));
+    typedef v2u v2u_elem __attribute__((aligned(2)));
+    typedef const __attribute__((address_space(1))) v4u_elem* gptr_4;
+    typedef const __attribute__((address_space(1))) v2u_elem* gptr_2;
+    if (d.N < E) {
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+            float f = 0.f;
+            if (j0 + i < d.N) {
+                f = load_as_float(d.x, d.dtype, base + j0 + i);
+                if (d.scale) f *= half_bits_to_float(d.scale[j0 + i]);
+            }
+            r.x[i / 4][i & 3] = __builtin_bit_cast(unsigned int, f);
+        }
+        return;
+    }
+    const int j = j0 + E <= d.N ? j0 : d.N - E;
+    if (d.scale) {
+        if (E == 16) {
+#pragma unroll
+            for (int q = 0; q < E / 8; ++q) {
+                const v4u s = ((gptr_4)(d.scale + j))[q];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) r.s[(4 * q + i) % (E / 2)] = s[i];
+            }
+        } else {
+            const v2u s = *(gptr_2)(d.scale + j);
+            r.s[0] = s.x;
+            r.s[1] = s.y;
+        }
+    }
+    if (d.dtype == NQ_F32) {
+#pragma unroll
+        for (int q = 0; q < E / 4; ++q) r.x[q] = ((gptr_4)((const float*)d.x + base + j))[q];
+    } else if (E == 16) {
+#pragma unroll
+        for (int q = 0; q < E / 8; ++q) r.x[q] = ((gptr_4)((const uint16_t*)d.x + base + j))[q];
+    } else {
+        const v2u h = *(gptr_2)((const uint16_t*)d.x + base + j);
+        r.x[0].x = h.x;
+        r.x[0].y = h.y;
+    }
+}
+
+// ... as numbers times their scales; padding beyond N is zero
+template <int E>
+__device__ __forceinline__ void lone_value(const QuantDesc& d, const LoneRaw<E>& r, int j0, float v[E])
+{
+    const bool done = d.N < E, scaled = d.scale && !done;
+    const auto convert = [&](auto value) {                  // (one loop per type, which is the same for the whole launch)
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+            v[i] = value(i);
+            if (scaled) v[i] = times_half(v[i], (uint16_t)(r.s[i / 2] >> (16 * (i & 1))));
+        }
+    };
+    const auto half_of = [&](int i) { return (uint16_t)(r.x[i / 8][(i / 2) & 3] >> (16 * (i & 1))); };
+    if (done || d.dtype == NQ_F32) convert([&](int i) { const unsigned int w = r.x[i / 4][i & 3]; return __builtin_bit_cast(float, w); });
+    else if (d.dtype == NQ_F16) convert([&](int i) { return half_bits_to_float(half_of(i)); });
+    else convert([&](int i) { return bf16_bits_to_float(half_of(i)); });
+    const int past = j0 + E - d.N;                          // elements of the lane beyond the row's end
+    if (!done && __builtin_amdgcn_ballot_w64(past > 0) != 0) {
+#pragma unroll
+        for (int k = E / 2; k >= 1; k /= 2) {
+            const bool move = past > 0 && (past & k) != 0;
+#pragma unroll
+            for (int i = 0; i < E; ++i) v[i] = move ? (i + k < E ? v[(i + k) % E] : 0.f) : v[i];
+        }
+#pragma unroll
+        for (int i = 0; i < E; ++i) v[i] = past >= E ? 0.f : v[i];
+    }
+}
+
+// A wave's share of the units (value(c, token, first element, v): the lane's elements of unit c, scaled) -> fixed point in `bq`, all waves of the
+// workgroup together.  *lt is cleared, and a barrier has passed since.
+template <int W, int E, class Value>
+__device__ __forceinline__ void lone_quantise(Value value, const LoneShare& share, int pieces, int nst, int lane, LoneTokens* lt, char* bq)
+{
+    constexpr int kU = lone_share_units<W, E>();
+    float hv[kU][E];
+    LoneShare sh = share;
+    uint32_t m = 0;                                        // (as bits: magnitudes order like them, NaN above all)
+#pragma unroll
+    for (int c = 0; c < kU; ++c) {
+        if (c < share.n) {
+            value(c, sh.tok, (sh.piece * 64 + lane) * E, hv[c]);
+#pragma unroll
+            for (int i = 0; i < E; ++i) {
+                const uint32_t a = __builtin_bit_cast(uint32_t, hv[c][i]) & 0x7fffffffu;
+                m = a > m ? a : m;
+            }
+            if (c + 1 == share.n || sh.piece + 1 == pieces) {
+                m = wave_reduce32(m, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+                if (lane == 0) atomicMax(&lt->max[sh.tok], m);
+                m = 0;
+            }
+            lone_next(sh, pieces);
+        }
+    }
+    __syncthreads();
+    sh = share;
+    int sum = 0;                                           // |q| <= 2^22: a lane's 32 at most fit
+#pragma unroll
+    for (int c = 0; c < kU; ++c) {
+        if (c < share.n) {
+            m = lt->max[sh.tok];
+            const float inv_step = exp2_int(-step_exponent(m));
+            char* const tok = bq + sh.tok * lone_tok_bytes(nst);
+            const int e0 = sh.piece * 64 + lane;            // the lane's group of E elements
+            if (E == 16) {
+                float v[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) v[i] = hv[c][i % E];
+                if (e0 < nst * 4) sum += quantize_chunk16(v, inv_step, (uint4*)tok + kSlices * e0, 1);
+            } else if (e0 < nst * 16) {
+                uint32_t hi, mid, lo;
+                sum += quantize4(hv[c][0], hv[c][1], hv[c][2], hv[c][3], inv_step, hi, mid, lo);
+                uint32_t* const dst = (uint32_t*)(tok + (e0 >> 2) * (kSlices * 16)) + (e0 & 3);
+                dst[0] = hi;
+                dst[4] = mid;
+                dst[8] = lo;
+            }
+            if (c + 1 == share.n || sh.piece + 1 == pieces) {
+                const long long total = wave_sum64(sum);
+                if (lane == 0) atomicAdd(&lt->sum[sh.tok], (unsigned long long)total);
+                sum = 0;
+            }
+            lone_next(sh, pieces);
+        }
+    }
+    __syncthreads();
+}
+
+// Column n of column group cg is slice n % 3 of token 5 cg + n / 3; an unused one repeats the group's last used one (an LDS broadcast)
+__device__ __forceinline__ void lone_column(int cg, int n, int batch, int& tok, int& slice)
+{
+    int used = 3 * (batch - 5 * cg);
+    used = used > 15 ? 15 : (used < 1 ? 1 : used);
+    const int col = n < used ? n : used - 1;
+    tok = 5 * cg + col / 3;
+    slice = col % 3;
+    if (tok >= batch) tok = 0;
+}
+
+// sum_n b_n q_n of (token, row) from the sums of `waves` waves, by the four lanes of a quad together (all of them get it); `q`: the row's place in
+// wave 0's region, slices 4 ints apart
+template <int W>
+__device__ __forceinline__ double lone_raw(const int* q, int wave_ints, int waves, int quad)
+{
+    int s[3] = {0, 0, 0};
+#pragma unroll
+    for (int w = 0; w < W; w += 4) {
+        if (w + quad < waves) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i) s[i] += q[(w + quad) * wave_ints + 4 * i];
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        s[i] += __builtin_amdgcn_mov_dpp(s[i], 0xB1, 0xf, 0xf, true);          // quad_perm [1, 0, 3, 2]
+        s[i] += __builtin_amdgcn_mov_dpp(s[i], 0x4E, 0xf, 0xf, true);          // quad_perm [2, 3, 0, 1]
+    }
+    return fma((double)s[0], 65536.0, fma((double)s[1], 256.0, (double)s[2]));
+}
+
+// grid: 8 x ceil(n_rb / 8) x (8 / PL) workgroups; items: n_rb row blocks of several ops, or nullptr: those of the one op (q1, s1)
+template <int NB, int PL, int W, bool SELFQ>
+__global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W / 4, W / 4)))
+stage_lone_kernel(const FusedItem* __restrict__ items, QuantDesc q1, StageDesc s1, int n_rb, int batch)
+{
+    constexpr int D = W == 8 ? 8 : 4, S = 8 / PL, R = lone_round(NB, PL), kWaveInts = NB * R * kLonePlaneInts;
+    extern __shared__ __align__(16) int lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, n = lane & 15;
+    // workgroup i runs on XCD i % 8: the workgroups of a row block are 8 apart
+    const int j = blockIdx.x >> 3;
+    const int at = (blockIdx.x & 7) + 8 * (j / S), p0 = j % S * PL;
+    if (at >= n_rb) return;
+    int rb = at;
+    QuantDesc qd = q1;
+    StageDesc sd = s1;
+    if (items) {
+        const FusedItem* e = items + at;
+        rb = e->rb;
+        qd = e->q;
+        sd = e->s;
+    }
+    const int nst = sd.n_steps;
+    int* const red = lds;
+    LoneTokens* const lt = (LoneTokens*)(lds + lone_red_ints(NB, PL, W));
+    char* const bq = (char*)(lt + 1);
+    const int pieces = lone_pieces<16>(nst), units = batch * pieces;
+
+    const LoneShare share = lone_share<W>(units, pieces, wave);
+    LoneRaw<16> raw[lone_share_units<W, 16>()];
+    if (SELFQ) {
+        lone_clear(lt, tid);
+        LoneShare sh = share;
+#pragma unroll
+        for (int c = 0; c < lone_share_units<W, 16>(); ++c) {
+            if (c < share.n) {
+                lone_request(qd, (int64_t)sh.tok * qd.x_stride, (sh.piece * 64 + lane) * 16, raw[c]);
+                lone_next(sh, pieces);
+            }
+        }
+    }
+    // the first tiles: steps wave, wave + W, ... (a short share re-reads its last tile)
+    const int cnt = (nst - wave + W - 1) / W;
+    const int st0 = cnt > 0 ? wave : 0;
+    const char* const a_base = (const char*)sd.tiles + (size_t)rb * nst * (kTileWords * 4);
+    const uint32_t a_off = (uint32_t)(st0 * 1024 + lane * 16);
+    const char* const b_base = SELFQ ? bq : (const char*)sd.bq;
+    uint32_t b_off[NB];
+#pragma unroll
+    for (int cg = 0; cg < NB; ++cg) {
+        int tok, slice;
+        lone_column(cg, n, batch, tok, slice);
+        b_off[cg] = SELFQ ? (uint32_t)(tok * lone_tok_bytes(nst) + (g * kSlices + slice) * 16)
+                          : (uint32_t)tok * ((uint32_t)nst * kBqStepBytes) + (uint32_t)(bq_piece(g, slice) * 16);
+    }
+    v4u wbuf[D], bbuf[SELFQ ? 1 : D][NB];
+#define NQ_ISSUE(k, i)                                                                                            \
+    do {                                                                                                          \
+        wbuf[k] = load_global_v4u(a_base, a_off + (uint32_t)(i) * (W * 1024));                                    \
+        if (!SELFQ) {                                                                                             \
+            _Pragma("unroll") for (int cg = 0; cg < NB; ++cg)                                                     \
+                bbuf[SELFQ ? 0 : (k)][cg] = load_global_v4u(b_base, b_off[cg] + (uint32_t)(st0 + (i) * W) * kBqStepBytes); \
+        }                                                                                                         \
+    } while (0)
+#pragma unroll
+    for (int k = 0; k < D; ++k) NQ_ISSUE(k, k < cnt ? k : (cnt > 0 ? cnt - 1 : 0));
+    if (SELFQ) {
+        __syncthreads();
+        lone_quantise<W, 16>([&](int c, int, int j0, float v[16]) { lone_value(qd, raw[c], j0, v); }, share, pieces, nst, lane, lt, bq);
+    }
+
+    uint32_t mask[PL];
+#pragma unroll
+    for (int p = 0; p < PL; ++p) mask[p] = 0x01010101u << (p0 + p);
+    v4i acc[NB][PL];
+#pragma unroll
+    for (int cg = 0; cg < NB; ++cg)
+#pragma unroll
+        for (int p = 0; p < PL; ++p) acc[cg][p] = v4i{0, 0, 0, 0};
+#define NQ_MAC(k, i)                                                                                              \
+    do {                                                                                                          \
+        v4u b[NB];                                                                                                \
+        _Pragma("unroll") for (int cg = 0; cg < NB; ++cg)                                                         \
+            b[cg] = SELFQ ? *(const v4u*)(b_base + b_off[cg] + (st0 + (i) * W) * (int)kBqStepBytes) : bbuf[SELFQ ? 0 : (k)][cg]; \
+        _Pragma("unroll") for (int p = 0; p < PL; ++p) {                                                          \
+            const v4i a = (v4i)(wbuf[k] & mask[p]);                                                               \
+            _Pragma("unroll") for (int cg = 0; cg < NB; ++cg)                                                     \
+                acc[cg][p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, (v4i)b[cg], acc[cg][p], 0, 0, 0);           \
+        }                                                                                                         \
+    } while (0)
+    // (whole passes over the ring without a branch, so that the waits inside stay partial; then the last D to 2 D - 1 steps)
+    int i0 = 0;
+    for (; i0 + 2 * D <= cnt; i0 += D) {
+#pragma unroll
+        for (int k = 0; k < D; ++k) {
+            NQ_MAC(k, i0 + k);
+            NQ_ISSUE(k, i0 + k + D);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+        if (i0 + k < cnt) {
+            NQ_MAC(k, i0 + k);
+            if (i0 + k + D < cnt) NQ_ISSUE(k, i0 + k + D);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+        if (i0 + D + k < cnt) {
+            NQ_MAC(k, i0 + D + k);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#undef NQ_MAC
+#undef NQ_ISSUE
+    // the waves' partial sums of every result, R planes at a time
+#pragma unroll
+    for (int r0 = 0; r0 < PL; r0 += R) {
+        if (r0) __syncthreads();
+#pragma unroll
+        for (int cg = 0; cg < NB; ++cg)
+#pragma unroll
+            for (int p = 0; p < R; ++p) *(v4i*)(red + wave * kWaveInts + (cg * R + p) * kLonePlaneInts + g * 68 + n * 4) = acc[cg][r0 + p];
+        __syncthreads();
+        const int quad = tid & 3;
+        for (int idx = tid >> 2; idx < 16 * R * batch; idx += 16 * W) {
+            const int tok = idx / (16 * R), row = idx % (16 * R), p = p0 + r0 + (row >> 4);
+            const int grow = rb * kTileRows + 16 * (p0 + r0) + row;
+            float oscale = 1.0f;
+            if (sd.out_scale && grow < sd.M) oscale = half_bits_to_float(((gptr_u16)sd.out_scale)[grow]);
+            const int cg = NB > 1 && tok >= 5 ? 1 : 0;
+            double raw = lone_raw<W>(red + (cg * R + (row >> 4)) * kLonePlaneInts + ((row >> 2) & 3) * 68 + 3 * (tok - 5 * cg) * 4 + (row & 3), kWaveInts, W, quad);
+            if (quad != 0 || grow >= sd.M) continue;
+            if (p == 7) raw = -raw;                        // bit 7 of an int8 is worth -128
+            QMeta mt;
+            if (SELFQ) mt = lone_meta(lt, tok);
+            else {
+                mt.two_step = ((cptr_meta)sd.meta)[tok].two_step;
+                mt.neg_qs = ((cptr_meta)sd.meta)[tok].neg_qs;
+            }
+            const double val = fma(raw, __builtin_ldexp(mt.two_step, -p), mt.neg_qs);     // exact
+            store_out(sd.out, sd.out_dtype, (size_t)tok * sd.out_stride + grow, (float)val * oscale, sd.out_scale != nullptr);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// A small layer in one launch: every workgroup computes the whole of t (its stage-1 tiles are few and come from L2), keeps it in LDS,
+// quantises it and finishes its own PL bit planes of one row block of stage 2.  Workgroup 0 also stores t.
+// ---------------------------------------------------------------------------------------------
+constexpr int kLayerWaves = 16;
+
+template <int PL>
+__global__ void __launch_bounds__(64 * kLayerWaves) __attribute__((amdgpu_waves_per_eu(4, 4)))
+stage_layer_kernel(QuantDesc qx, StageDesc s1, QuantDesc qt, StageDesc s2, int n_rb, int batch, int t_off, int bqt_off)
+{
+    constexpr int NB = 1, W = kLayerWaves, D = 4, S = 8 / PL, R1 = lone_round(NB, 8), R2 = lone_round(NB, PL);
+    extern __shared__ __align__(16) int lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, n = lane & 15;
+    const int j = blockIdx.x >> 3;
+    const int rb2 = (blockIdx.x & 7) + 8 * (j / S), p0 = j % S * PL;
+    if (rb2 >= n_rb) return;
+    int* const red = lds;
+    LoneTokens* const lt = (LoneTokens*)(lds + lone_red_ints(NB, 8, W));     // of x, then of t
+    char* const bq = (char*)(lt + 2);
+    float* const t_s = (float*)((char*)lds + t_off);                         // [batch][t stride]
+    char* const bqt = (char*)lds + bqt_off;
+    const int nst1 = s1.n_steps, nst2 = s2.n_steps;
+    const int pieces1 = lone_pieces<4>(nst1), pieces2 = lone_pieces<4>(nst2);
+
+    const LoneShare share1 = lone_share<W>(batch * pieces1, pieces1, wave), share2 = lone_share<W>(batch * pieces2, pieces2, wave);
+    LoneRaw<4> raw[lone_share_units<W, 4>()];
+    lone_clear(lt, tid);
+    lone_clear(lt + 1, tid);
+    {
+        LoneShare sh = share1;
+#pragma unroll
+        for (int c = 0; c < lone_share_units<W, 4>(); ++c) {
+            if (c < share1.n) {
+                lone_request(qx, (int64_t)sh.tok * qx.x_stride, (sh.piece * 64 + lane) * 4, raw[c]);
+                lone_next(sh, pieces1);
+            }
+        }
+    }
+    // stage 1: w1 waves per row block, all eight planes
+    const int n_rb1 = (s1.M + kTileRows - 1) / kTileRows;
+    int wl = 4;
+    while ((W >> wl) < n_rb1) --wl;
+    const int w1 = 1 << wl, rb1 = wave >> wl, part = wave & (w1 - 1);
+    const int cnt1 = rb1 < n_rb1 ? (nst1 - part + w1 - 1) >> wl : 0;
+    const int cnt2 = (nst2 - wave + W - 1) / W;
+    const char* const a1 = (const char*)s1.tiles + (size_t)(rb1 < n_rb1 ? rb1 : 0) * nst1 * (kTileWords * 4) + (cnt1 > 0 ? part : 0) * 1024 + lane * 16;
+    const char* const a2 = (const char*)s2.tiles + (size_t)rb2 * nst2 * (kTileWords * 4) + (cnt2 > 0 ? wave : 0) * 1024 + lane * 16;
+    v4u wbuf[D];
+#pragma unroll
+    for (int k = 0; k < D; ++k) wbuf[k] = load_global_v4u(a1, (uint32_t)((k < cnt1 ? k : (cnt1 > 0 ? cnt1 - 1 : 0)) * w1) * 1024);
+    __syncthreads();
+    lone_quantise<W, 4>([&](int c, int, int j0, float v[4]) { lone_value(qx, raw[c], j0, v); }, share1, pieces1, nst1, lane, lt, bq);
+    uint32_t b1[NB], b2[NB];
+#pragma unroll
+    for (int cg = 0; cg < NB; ++cg) {
+        int tok, slice;
+        lone_column(cg, n, batch, tok, slice);
+        b1[cg] = (uint32_t)(tok * lone_tok_bytes(nst1) + (g * kSlices + slice) * 16);
+        b2[cg] = (uint32_t)(tok * lone_tok_bytes(nst2) + (g * kSlices + slice) * 16);
+    }
+    {
+        v4i acc[NB][8];
+#pragma unroll
+        for (int cg = 0; cg < NB; ++cg)
+#pragma unroll
+            for (int p = 0; p < 8; ++p) acc[cg][p] = v4i{0, 0, 0, 0};
+        for (int i0 = 0; i0 < cnt1; i0 += D) {
+#pragma unroll
+            for (int k = 0; k < D; ++k) {
+                if (i0 + k < cnt1) {
+                    v4u b[NB];
+#pragma unroll
+                    for (int cg = 0; cg < NB; ++cg) b[cg] = *(const v4u*)(bq + b1[cg] + (part + (i0 + k) * w1) * (int)kBqStepBytes);
+                    mac_tile<NB>(acc, wbuf[k], b);
+                    if (i0 + k + D < cnt1) wbuf[k] = load_global_v4u(a1, (uint32_t)((i0 + k + D) * w1) * 1024);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+        // the first tiles of stage 2 are requested before stage 1's sums are added up
+#pragma unroll
+        for (int k = 0; k < D; ++k) wbuf[k] = load_global_v4u(a2, (uint32_t)((k < cnt2 ? k : (cnt2 > 0 ? cnt2 - 1 : 0)) * W) * 1024);
+        constexpr int kWaveInts = NB * R1 * kLonePlaneInts;
+#pragma unroll
+        for (int r0 = 0; r0 < 8; r0 += R1) {
+            if (r0) __syncthreads();
+#pragma unroll
+            for (int cg = 0; cg < NB; ++cg)
+#pragma unroll
+                for (int p = 0; p < R1; ++p) *(v4i*)(red + wave * kWaveInts + (cg * R1 + p) * kLonePlaneInts + g * 68 + n * 4) = acc[cg][r0 + p];
+            __syncthreads();
+            const int quad = tid & 3;
+            for (int idx = tid >> 2; idx < n_rb1 * 16 * R1 * batch; idx += 16 * W) {
+                const int row = idx % (16 * R1), tr = idx / (16 * R1), tok = tr % batch, rb = tr / batch, p = r0 + (row >> 4);
+                const int k = rb * kTileRows + 16 * r0 + row;
+                const int cg = NB > 1 && tok >= 5 ? 1 : 0;
+                double raw = lone_raw<W>(red + (rb << wl) * kWaveInts + (cg * R1 + (row >> 4)) * kLonePlaneInts + ((row >> 2) & 3) * 68 + 3 * (tok - 5 * cg) * 4 + (row & 3),
+                                         kWaveInts, w1, quad);
+                if (quad != 0 || k >= s1.M) continue;
+                if (p == 7) raw = -raw;
+                const QMeta mt = lone_meta(lt, tok);
+                const float t = (float)fma(raw, __builtin_ldexp(mt.two_step, -p), mt.neg_qs);
+                t_s[tok * qt.x_stride + k] = t;
+                if (blockIdx.x == 0) ((float*)s1.out)[(size_t)tok * s1.out_stride + k] = t;
+            }
+        }
+    }
+    __syncthreads();
+    // t -> fixed point
+    lone_quantise<W, 4>([&](int, int tok, int j0, float v[4]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float f = 0.f;
+            if (j0 + i < qt.N) {
+                f = t_s[tok * qt.x_stride + j0 + i];
+                if (qt.scale) f *= half_bits_to_float(((gptr_u16)qt.scale)[j0 + i]);
+            }
+            v[i] = f;
+        }
+    }, share2, pieces2, nst2, lane, lt + 1, bqt);
+    // stage 2: all waves on PL planes of this workgroup's row block
+    uint32_t mask[PL];
+#pragma unroll
+    for (int p = 0; p < PL; ++p) mask[p] = 0x01010101u << (p0 + p);
+    v4i acc[NB][PL];
+#pragma unroll
+    for (int cg = 0; cg < NB; ++cg)
+#pragma unroll
+        for (int p = 0; p < PL; ++p) acc[cg][p] = v4i{0, 0, 0, 0};
+    for (int i0 = 0; i0 < cnt2; i0 += D) {
+#pragma unroll
+        for (int k = 0; k < D; ++k) {
+            if (i0 + k < cnt2) {
+                v4u b[NB];
+#pragma unroll
+                for (int cg = 0; cg < NB; ++cg) b[cg] = *(const v4u*)(bqt + b2[cg] + (wave + (i0 + k) * W) * (int)kBqStepBytes);
+#pragma unroll
+                for (int p = 0; p < PL; ++p) {
+                    const v4i a = (v4i)(wbuf[k] & mask[p]);
+#pragma unroll
+                    for (int cg = 0; cg < NB; ++cg) acc[cg][p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, (v4i)b[cg], acc[cg][p], 0, 0, 0);
+                }
+                if (i0 + k + D < cnt2) wbuf[k] = load_global_v4u(a2, (uint32_t)((i0 + k + D) * W) * 1024);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+    constexpr int kWaveInts = NB * R2 * kLonePlaneInts;
+#pragma unroll
+    for (int r0 = 0; r0 < PL; r0 += R2) {
+        if (r0) __syncthreads();
+#pragma unroll
+        for (int cg = 0; cg < NB; ++cg)
+#pragma unroll
+            for (int p = 0; p < R2; ++p) *(v4i*)(red + wave * kWaveInts + (cg * R2 + p) * kLonePlaneInts + g * 68 + n * 4) = acc[cg][r0 + p];
+        __syncthreads();
+        const int quad = tid & 3;
+        for (int idx = tid >> 2; idx < 16 * R2 * batch; idx += 16 * W) {
+            const int tok = idx / (16 * R2), row = idx % (16 * R2), p = p0 + r0 + (row >> 4);
+            const int grow = rb2 * kTileRows + 16 * (p0 + r0) + row;
+            float oscale = 1.0f;
+            if (s2.out_scale && grow < s2.M) oscale = half_bits_to_float(((gptr_u16)s2.out_scale)[grow]);
+            const int cg = NB > 1 && tok >= 5 ? 1 : 0;
+            double raw = lone_raw<W>(red + (cg * R2 + (row >> 4)) * kLonePlaneInts + ((row >> 2) & 3) * 68 + 3 * (tok - 5 * cg) * 4 + (row & 3), kWaveInts, W, quad);
+            if (quad != 0 || grow >= s2.M) continue;
+            if (p == 7) raw = -raw;
+            const QMeta mt = lone_meta(lt + 1, tok);
+            const double val = fma(raw, __builtin_ldexp(mt.two_step, -p), mt.neg_qs);     // exact
+            store_out(s2.out, s2.out_dtype, (size_t)tok * s2.out_stride + grow, (float)val * oscale, s2.out_scale != nullptr);
+        }
+    }
+}
+
+// Bit planes of a workgroup: as many workgroups per row block as give every CU at most one (a second round of workgroups costs more than
+// the planes: 86 row blocks at batch 4 14.2 us with two planes each, 10.7 with four).
+int lone_planes(int n_rb)
+{
+    int pl = 1;
+    while (pl < 8 && n_rb * (8 / pl) > device_cu_count()) pl *= 2;
+    return pl;
+}
+
+constexpr size_t kLoneLdsBytes = 160 * 1024;            // of a CU
+static size_t lone_lds_bytes(int nb, int pl, int w, int max_steps, int batch)
+{
+    return (size_t)lone_red_ints(nb, pl, w) * 4 + sizeof(LoneTokens) + (size_t)batch * lone_tok_bytes(max_steps);
+}
+
+// Whether the workgroups of such a launch quantise its input themselves.  Whole row blocks per workgroup (more than half as many as CUs)
+// leave eight waves for it, which pays for fewer elements (28672 rows, batch 8: r = 1024 14.2 us against 15.9 with launches of their own, r = 3520
+// 22.0 and 18.5; batch 4 r = 600 11.8 and 13.2, r = 3520 14.8 and 14.0; 22000 rows r = 2240 level).
+bool lone_selfq(int max_steps, int n_rb, int batch)
+{
+    const int pl = lone_planes(n_rb);
+    return batch * lone_pieces<16>(max_steps) * 1024 <= (pl == 8 ? kLoneMaxElements * 3 / 8 : kLoneMaxElements) &&
+           lone_lds_bytes(batch <= 5 ? 1 : 2, pl, pl == 8 ? 8 : 16, max_steps, batch) <= kLoneLdsBytes;
+}
+
+template <int NB, int PL, int W, bool SELFQ>
+static int launch_lone_t(const FusedItem* d_items, int n_rb, const QuantDesc& q, const StageDesc& sd, int max_steps, int batch, hipStream_t s)
+{
+    const size_t bytes = SELFQ ? lone_lds_bytes(NB, PL, W, max_steps, batch) : (size_t)lone_red_ints(NB, PL, W) * 4;
+    static bool attr_set = false;
+    if (!attr_set) {
+        NQ_HIP(hipFuncSetAttribute((const void*)stage_lone_kernel<NB, PL, W, SELFQ>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLoneLdsBytes));
+        attr_set = true;
+    }
+    const dim3 grid((unsigned)((n_rb + 7) / 8 * 8 * (8 / PL)));
+    NQ_LAUNCH((stage_lone_kernel<NB, PL, W, SELFQ>), grid, dim3(64 * W), bytes, s, d_items, q, sd, n_rb, batch);
+    NQ_HIP(hipGetLastError());
+    return NQ_OK;
+}
+
+// One stage on its n_rb row blocks, with the quantisation of its input (d_items == nullptr: of the one op).  16 waves per workgroup, eight
+// where they take whole row blocks.
+int launch_lone_selfq(const FusedItem* d_items, int n_rb, const QuantDesc& q, const StageDesc& sd, int max_steps, int batch, hipStream_t s)
+{
+    if (n_rb < 1) return NQ_OK;
+    if (!lone_selfq(max_steps, n_rb, batch)) {
+        set_error("launch_lone_selfq: input too long for the workgroups to quantise");
+        return NQ_E_INVALID_ARG;
+    }
+    const int pl = lone_planes(n_rb);
+#define NQ_LONE(PL, W) (batch <= 5 ? launch_lone_t<1, PL, W, true>(d_items, n_rb, q, sd, max_steps, batch, s) : launch_lone_t<2, PL, W, true>(d_items, n_rb, q, sd, max_steps, batch, s))
+    if (pl == 1) return NQ_LONE(1, 16);
+    if (pl == 2) return NQ_LONE(2, 16);
+    if (pl == 4) return NQ_LONE(4, 16);
+    return NQ_LONE(8, 8);
+#undef NQ_LONE
+}
+
+// The same on an input that a launch of its own has quantised; w: 16 or (batch 6 to 8) 8 waves per workgroup.
+int launch_lone(const FusedItem* d_items, int n_rb, const StageDesc& sd, int w, int batch, hipStream_t s)
+{
+    if (n_rb < 1) return NQ_OK;
+    const int pl = lone_planes(n_rb);
+    const QuantDesc q{};
+#define NQ_LONE(NB, W)                                                            \
+    (pl == 1   ? launch_lone_t<NB, 1, W, false>(d_items, n_rb, q, sd, 0, batch, s) \
+     : pl == 2 ? launch_lone_t<NB, 2, W, false>(d_items, n_rb, q, sd, 0, batch, s) \
+     : pl == 4 ? launch_lone_t<NB, 4, W, false>(d_items, n_rb, q, sd, 0, batch, s) \
+               : launch_lone_t<NB, 8, W, false>(d_items, n_rb, q, sd, 0, batch, s))
+    if (batch <= 5) return NQ_LONE(1, 16);
+    return w == 16 ? NQ_LONE(2, 16) : NQ_LONE(2, 8);
+#undef NQ_LONE
+}
+
+// ---- one launch per layer ----
+struct LayerLds {
+    int t_off, bqt_off;
+    size_t bytes;
+};
+static LayerLds layer_lds(const QuantDesc& qt, const StageDesc& s1, const StageDesc& s2, int batch)
+{
+    LayerLds l;
+    size_t at = (size_t)lone_red_ints(1, 8, kLayerWaves) * 4 + 2 * sizeof(LoneTokens) + (size_t)batch * lone_tok_bytes(s1.n_steps);
+    l.t_off = (int)at;
+    at += (size_t)batch * qt.x_stride * 4;
+    l.bqt_off = (int)at;
+    l.bytes = at + (size_t)batch * lone_tok_bytes(s2.n_steps);
+    return l;
+}
+
+// Where it is faster than two launches: up to four tokens, and so few tiles in stage 1 that doing it once per workgroup costs less than a
+// launch.  us per call, one launch / two: batch 1 8 tiles 7.7 / 9.3, 32 tiles 8.3 / 9.0, 64 9.3 / 9.2; batch 2 8 8.5 / 9.8, 32 9.1 / 9.5,
+// 64 10.8 / 9.3; batch 4 8 9.3 / 10.1, 32 10.7 / 9.7; batch 6 8 12.3 / 11.5.
+bool lone_layer_fits(const QuantDesc& qt, const StageDesc& s1, const StageDesc& s2, int batch)
+{
+    const int n_rb1 = (int)n_rowblocks(s1.M), n_rb2 = (int)n_rowblocks(s2.M);
+    return batch <= 4 && n_rb1 * s1.n_steps * batch <= 48 && n_rb2 <= device_cu_count() && n_rb1 <= kLayerWaves &&
+           batch * s1.n_steps * 64 <= kLoneMaxElements && batch * s2.n_steps * 64 <= kLoneMaxElements && layer_lds(qt, s1, s2, batch).bytes <= kLoneLdsBytes;
+}
+
+template <int PL>
+static int launch_layer_t(const QuantDesc& qx, const StageDesc& s1, const QuantDesc& qt, const StageDesc& s2, int batch, hipStream_t s)
+{
+    static bool attr_set = false;
+    if (!attr_set) {
+        NQ_HIP(hipFuncSetAttribute((const void*)stage_layer_kernel<PL>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLoneLdsBytes));
+        attr_set = true;
+    }
+    const LayerLds l = layer_lds(qt, s1, s2, batch);
+    const int n_rb = (int)n_rowblocks(s2.M);
+    NQ_LAUNCH((stage_layer_kernel<PL>), dim3((unsigned)((n_rb + 7) / 8 * 8 * (8 / PL))), dim3(64 * kLayerWaves), l.bytes, s, qx, s1, qt, s2, n_rb, batch, l.t_off, l.bqt_off);
+    NQ_HIP(hipGetLastError());
+    return NQ_OK;
+}
+
+int launch_lone_layer(const QuantDesc& qx, const StageDesc& s1, const QuantDesc& qt, const StageDesc& s2, int batch, hipStream_t s)
+{
+    const int pl = lone_planes((int)n_rowblocks(s2.M));
+    if (pl == 1) return launch_layer_t<1>(qx, s1, qt, s2, batch, s);
+    if (pl == 2) return launch_layer_t<2>(qx, s1, qt, s2, batch, s);
+    if (pl == 4) return launch_layer_t<4>(qx, s1, qt, s2, batch, s);
+    return launch_layer_t<8>(qx, s1, qt, s2, batch, s);
+}
+
+}  // namespace nq
