@@ -79,8 +79,9 @@ typedef struct nq_exec_s*  nq_exec;     /* a fixed list of layers run in depende
 #define NQ_MAX_DIM 65536
 /* Largest batch served by the streaming (decode) kernels in one pass. */
 #define NQ_DECODE_MAX_BATCH 8
-/* Batches at or above this take the dense matrix-core (prefill) path: its cost is flat up to
- * 64 tokens (one token tile) and, measured, never above that of two streaming passes. */
+/* Batches at or above this take the dense matrix-core (prefill) path, whose cost is flat up to 64 tokens (one token
+ * tile), where the exact path would not be the faster one: few tokens and small layers take that (the choice follows from the
+ * layer's sides, its s_in and the batch alone). */
 #define NQ_PREFILL_MIN_BATCH 9
 
 /* ---- packing (Algorithm 1, PackBinary; Fig. 2(c)) -- host only, no GPU needed ---- */
@@ -161,7 +162,8 @@ int nq_binlr_reserved(nq_handle h, int* max_batch, size_t* workspace_bytes);
  * batch <= the reserved batch (otherwise it reserves first, which synchronises).
  * Not re-entrant on one handle (the handle's workspace is shared); different
  * handles may run concurrently on different streams.
- * batch <= 8: streaming kernels (exact integer accumulation); >= 9: dense MFMA path
+ * batch <= 8: streaming kernels (exact integer accumulation); >= 9: the same (nq_binlr_forward_exact) for few tokens and
+ * small layers, where they are faster, else the dense MFMA path
  * (fp16 operands with a power of two per token, fp32 accumulation; a token with max|s_in (.) x| of
  * 65504 * 2^100 or more leaves their range and yields infinities or NaN), unless the layer was created
  * with NQ_FLAG_NO_PREFILL. */
@@ -185,7 +187,7 @@ int nq_binlr_forward_static(nq_handle h, const void* x, void* y, int batch, void
 /* The same product for ANY batch through the streaming kernels only, in passes of 8 tokens, or of more
  * where the layer's workspace has room for them (nq_binlr_reserve; exact integer accumulation of 24-bit fixed-point
  * activations: the accuracy of a batch <= 8 forward) -- the per-call way to ask for the
- * exact path above batch 8, where nq_binlr_forward takes the fp16-operand dense path.
+ * exact path above batch 8, where nq_binlr_forward may take the fp16-operand dense path.
  * Pointers, types and stream as in nq_binlr_forward; allocates nothing. */
 int nq_binlr_forward_exact(nq_handle h, const void* x, void* y, int batch, void* stream);
 

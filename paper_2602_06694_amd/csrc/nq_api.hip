@@ -40,7 +40,7 @@ static const OptEntry kOptTable[OPT_COUNT] = {
     {"pf_splits1", false}, {"pf_splits2", false}, {"pf_tg1", false}, {"pf_tg2", false}, {"pf_ks1", false}, {"pf_ks2", false},
     {"pf_verbose", true}, {"exec_spin_limit_us", false}, {"no_small_layer", true}, {"small_layer_kb", false},
     {"dgemm_tile", false}, {"admm_no_overlap", true}, {"two_slice_b8", true},
-    {"admm_no_prio", true}, {"admm_product_mode", false}, {"admm_inline_svid", true}, {"admm_no_fused_step", true},
+    {"admm_no_prio", true}, {"admm_product_mode", false}, {"admm_inline_svid", true}, {"dense_only", true}, {"admm_no_fused_step", true},
 };
 static int g_opt[OPT_COUNT];
 static std::once_flag g_opt_once;
@@ -736,6 +736,19 @@ static int decode_once(nq_handle h, const DecodeWorkspace& w, const void* x, voi
     return launch_stage(nullptr, s2, nullptr, (rb2 + per2 - 1) / per2, w2, per2, batch, s);
 }
 
+// More than eight tokens in groups of up to eight (nq_lone.hip), or of 16 (nq_exact.hip)?
+static bool dealt_out(const StageDesc& s1, const StageDesc& s2, int batch)
+{
+    return !opt_flag(OPT_NO_SELFQ) && opt(OPT_FORCE_W) < 0 && lone_deals_out((int)n_rowblocks(s1.M), batch) && lone_deals_out((int)n_rowblocks(s2.M), batch);
+}
+static int dealt_out_stage(const QuantDesc& q, const StageDesc& sd, int batch, hipStream_t s)
+{
+    const int n_rb = (int)n_rowblocks(sd.M);
+    if (lone_selfq(sd.n_steps, n_rb, batch)) return launch_lone_selfq(nullptr, n_rb, q, sd, sd.n_steps, batch, s);
+    const int rc = launch_quantize(nullptr, q, 1, q.n_chunks, batch, s);
+    return rc != NQ_OK ? rc : launch_lone(nullptr, n_rb, sd, 16, batch, s);
+}
+
 // any batch through the exact streaming kernels; `unscaled`: z = U (V^T (s_in (.) x)).  Passes of as many tokens as the layer's
 // workspace holds, of eight through the decode workspace where it has none (or eight and fewer are left):
 // the same bits either way.  Allocates nothing.
@@ -756,10 +769,16 @@ static int run_in_passes(nq_handle h, const void* x, void* y, int batch, hipStre
         if (wide && left > NQ_DECODE_MAX_BATCH) {
             nb = std::min(h->xt_tokens, left);
             const QuantDesc qx = make_qx(h, w, xp), qt = make_qt(h, w);
+            const StageDesc s1 = make_s1(h, w);
             StageDesc s2 = make_s2(h, w, yp);
             if (unscaled) s2.out_scale = nullptr;
+            if (dealt_out(s1, s2, nb)) {
+                if ((rc = dealt_out_stage(qx, s1, nb, s)) != NQ_OK || (rc = dealt_out_stage(qt, s2, nb, s)) != NQ_OK) return rc;
+                b0 += nb;
+                continue;
+            }
             if ((rc = launch_quantize(nullptr, qx, 1, qx.n_chunks, nb, s, true)) != NQ_OK) return rc;
-            if ((rc = launch_stage_exact(make_s1(h, w), nb, s)) != NQ_OK) return rc;
+            if ((rc = launch_stage_exact(s1, nb, s)) != NQ_OK) return rc;
             if ((rc = launch_quantize(nullptr, qt, 1, qt.n_chunks, nb, s, true)) != NQ_OK) return rc;
             rc = launch_stage_exact(s2, nb, s);
         } else {
@@ -770,6 +789,24 @@ static int run_in_passes(nq_handle h, const void* x, void* y, int batch, hipStre
         b0 += nb;
     }
     return NQ_OK;
+}
+
+// Whether nq_binlr_forward takes the exact path for more than eight tokens: where its launches are the faster ones, which is so for few
+// tokens and small layers.  The dense path does 64 tokens at a time on two workgroups of four row blocks per CU, so that such calls leave it idle.  In
+// groups of eight always (9 to 128 tokens of the layers that this holds for: 0.55 to 0.95 of the dense path's time); in groups of 16 where one pass
+// holds the batch and its estimate is a tenth below the dense path's (at that line none of 1150 forwards of 50 layers, 256 x 256 to
+// 28672 x 28672 at 9 to 512 tokens, lost more than 4.1 %, and on average they take 0.83 of the dense path's time).  us, dense / exact: 4096 x 4096
+// r = 1024 at 24, 64, 128 tokens 27.5 / 16.0, 28.0 / 20.0, 29.1 / 22.5, past the line at 256 and 512 33.1 / 30.5, 36.2 / 44.0; 28672 x 8192 r = 3520 at 9 and 24
+// 44.5 / 27.4, 45.8 / 35.0, past it at 64 46.3 / 51.3; 1024 x 1024 r = 256 at 24 and 256 17.7 / 10.8, 18.7 / 15.7.
+static bool forward_exact_pays(nq_handle h, int batch)
+{
+    if (opt_flag(OPT_DENSE_ONLY)) return false;
+    for (int o = OPT_PF_SPLITS1; o <= OPT_PF_KS2; ++o)
+        if (opt((Opt)o) >= 0) return false;
+    // (layers that the dense path takes one column at a time: its first product is exact as well, and its results stay the same bits at every batch)
+    if (h->pf_plain || batch > exact_pass_tokens(h)) return false;
+    if (lone_deals_out((int)n_rowblocks(h->r), batch) && lone_deals_out((int)n_rowblocks(h->d_out), batch)) return true;
+    return exact_us(h->d_out, h->d_in, h->r, batch) < 0.9 * prefill_us(h->d_out, h->d_in, h->r, batch);
 }
 
 static int check_xy(const char* who, const void* x, const void* y, size_t x_bytes, size_t y_bytes)
@@ -793,6 +830,10 @@ extern "C" int nq_binlr_forward(nq_handle h, const void* x, void* y, int batch, 
     hipStream_t s = (hipStream_t)stream;
     if (batch <= NQ_DECODE_MAX_BATCH) return decode_once(h, h->ws, x, y, batch, s);
     if (batch >= NQ_PREFILL_MIN_BATCH && !(h->flags & (NQ_FLAG_NO_PREFILL | NQ_FLAG_DECODE_VALU))) {
+        if (forward_exact_pays(h, batch)) {
+            rc = grow_prefill_workspace(h, carve_workspace(nullptr, nullptr, h->d_in, h->r, (int)round_up(batch, 16)));
+            return rc != NQ_OK ? rc : run_in_passes(h, x, y, batch, s, false);
+        }
         if ((rc = ensure_prefill_workspace(h, batch)) != NQ_OK) return rc;
         note_capture(h->pf, s);
         PrefillArgs a;

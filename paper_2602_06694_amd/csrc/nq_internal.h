@@ -139,6 +139,7 @@ enum Opt {
     OPT_ADMM_NO_PRIO,       // flag: the kernels of LB-ADMM's factorisation chain keep the default wave priority
     OPT_ADMM_PRODUCT_MODE,  // 1: LB-ADMM's product with W keeps two workgroups per CU also beside the factorisation (default 0: one)
     OPT_ADMM_INLINE_SVID,   // flag: LB-ADMM runs the SVID of a factor on the caller's stream, before the next factor's update starts
+    OPT_DENSE_ONLY,         // flag: nq_binlr_forward takes the dense path from batch 9 on whatever the exact path would cost
     OPT_ADMM_NO_FUSED_STEP, // flag: LB-ADMM's factorisation launches the trailing update and the next diagonal block one after the other
     OPT_COUNT
 };
@@ -323,6 +324,7 @@ int launch_gemm_t(const uint32_t* tiles, int64_t M, int64_t N, const void* in, i
 constexpr int kLoneSchedule = 35;        // plan schedule code: few row blocks, batch 2 to 8, the workgroups quantise the input
 int lone_planes(int n_rb);
 bool lone_selfq(int max_steps, int n_rb, int batch);
+bool lone_deals_out(int n_rb, int batch);
 int launch_lone_selfq(const FusedItem* d_items, int n_rb, const QuantDesc& q, const StageDesc& sd, int max_steps, int batch, hipStream_t s);
 int launch_lone(const FusedItem* d_items, int n_rb, const StageDesc& sd, int w, int batch, hipStream_t s);
 bool lone_layer_fits(const QuantDesc& qt, const StageDesc& s1, const StageDesc& s2, int batch);
@@ -330,6 +332,7 @@ int launch_lone_layer(const QuantDesc& qx, const StageDesc& s1, const QuantDesc&
 
 // ---- launchers (nq_exact.hip) ---------------------------------------------------------------
 int launch_stage_exact(const StageDesc& d, int batch, hipStream_t s);
+double exact_us(int64_t d_out, int64_t d_in, int64_t r, int batch);      // estimated time of a forward of one pass
 
 // ---- launchers (nq_exec.hip) ---------------------------------------------------------------
 bool small_layer_fits(nq_handle h, int batch);
@@ -356,5 +359,6 @@ bool prefill_plain(const uint16_t* s_in, int64_t d_in, int x_dtype);
 int launch_prefill_plain(const uint16_t* d_s_in, int64_t d_in, int x_dtype, int* answer);      // s_in on the device; default stream
 size_t prefill_workspace_bytes(int64_t d_out, int64_t d_in, int64_t r, int batch, bool plain);
 int launch_prefill(const PrefillArgs& a, hipStream_t s);
+double prefill_us(int64_t d_out, int64_t d_in, int64_t r, int batch);      // estimated time of a forward in pairs
 
 }  // namespace nq

@@ -1,9 +1,10 @@
-// Stages of the streaming path (batch <= 8) for launches that are far from filling the chip: a layer on its own, or the few layers of
+// Stages of the streaming path for launches that are far from filling the chip: a layer on its own, or the few layers of
 // one level of a decoder block (Section 3.1 Eq. 1 as two sign-matrix x vector products, Appendix E.2).  Such a launch is bound by latency:
 // by the host, which takes 2.7 to 3 us per launch, and by the chain  input -> fixed point -> tiles -> sums -> store  of a workgroup.
 //   - The workgroups of a stage quantise its input themselves where it is short (SELFQ): one launch instead of two.
 //   - A row block is dealt out to 8 / PL workgroups by BIT PLANES: each streams the same tiles, multiplies PL of the eight planes (16
 //     rows each) and finishes its own rows, so that nothing has to be added up between workgroups.  They share an XCD and its L2.
+//   - More than eight tokens (batch 9 and more through the exact path) are dealt out in groups of up to eight as well.
 //   - stage_layer_kernel: a small layer in ONE launch, every workgroup computing the whole of t for itself.
 // The arithmetic is that of quantize_kernel and stage_split_kernel (nq_decode.hip) element for element: the same bits.
 //
@@ -274,21 +275,26 @@ __device__ __forceinline__ double lone_raw(const int* q, int wave_ints, int wave
     return fma((double)s[0], 65536.0, fma((double)s[1], 256.0, (double)s[2]));
 }
 
-// grid: 8 x ceil(n_rb / 8) x (8 / PL) workgroups; items: n_rb row blocks of several ops, or nullptr: those of the one op (q1, s1)
+// grid: 8 x ceil(pairs / 8) x (8 / PL) workgroups for the pairs of row block and group of `per` tokens; items: n_rb row blocks of several ops (one
+// group), or nullptr: those of the one op (q1, s1)
 template <int NB, int PL, int W, bool SELFQ>
 __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W / 4, W / 4)))
-stage_lone_kernel(const FusedItem* __restrict__ items, QuantDesc q1, StageDesc s1, int n_rb, int batch)
+stage_lone_kernel(const FusedItem* __restrict__ items, QuantDesc q1, StageDesc s1, int n_rb, int tokens, int per)
 {
     constexpr int D = W == 8 ? 8 : 4, S = 8 / PL, R = lone_round(NB, PL), kWaveInts = NB * R * kLonePlaneInts;
     extern __shared__ __align__(16) int lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, n = lane & 15;
-    // workgroup i runs on XCD i % 8: the workgroups of a row block are 8 apart
+    // workgroup i runs on XCD i % 8: the workgroups of a pair are 8 apart
     const int j = blockIdx.x >> 3;
     const int at = (blockIdx.x & 7) + 8 * (j / S), p0 = j % S * PL;
-    if (at >= n_rb) return;
-    int rb = at;
+    int rb = at, group = 0;
+    if (tokens > per) {
+        group = at / n_rb;
+        rb = at - group * n_rb;
+        if (group * per >= tokens) return;
+    } else if (at >= n_rb) return;
     QuantDesc qd = q1;
     StageDesc sd = s1;
     if (items) {
@@ -298,6 +304,10 @@ stage_lone_kernel(const FusedItem* __restrict__ items, QuantDesc q1, StageDesc s
         sd = e->s;
     }
     const int nst = sd.n_steps;
+    const int64_t first = (int64_t)group * per;             // of the group's tokens
+    const int batch = tokens - (int)first < per ? tokens - (int)first : per;
+    const int64_t out0 = first * sd.out_stride;
+    const char* const bq0 = (const char*)sd.bq + first * nst * kBqStepBytes;
     int* const red = lds;
     LoneTokens* const lt = (LoneTokens*)(lds + lone_red_ints(NB, PL, W));
     char* const bq = (char*)(lt + 1);
@@ -311,7 +321,7 @@ stage_lone_kernel(const FusedItem* __restrict__ items, QuantDesc q1, StageDesc s
 #pragma unroll
         for (int c = 0; c < lone_share_units<W, 16>(); ++c) {
             if (c < share.n) {
-                lone_request(qd, (int64_t)sh.tok * qd.x_stride, (sh.piece * 64 + lane) * 16, raw[c]);
+                lone_request(qd, (first + sh.tok) * qd.x_stride, (sh.piece * 64 + lane) * 16, raw[c]);
                 lone_next(sh, pieces);
             }
         }
@@ -321,7 +331,7 @@ stage_lone_kernel(const FusedItem* __restrict__ items, QuantDesc q1, StageDesc s
     const int st0 = cnt > 0 ? wave : 0;
     const char* const a_base = (const char*)sd.tiles + (size_t)rb * nst * (kTileWords * 4);
     const uint32_t a_off = (uint32_t)(st0 * 1024 + lane * 16);
-    const char* const b_base = SELFQ ? bq : (const char*)sd.bq;
+    const char* const b_base = SELFQ ? bq : bq0;
     uint32_t b_off[NB];
 #pragma unroll
     for (int cg = 0; cg < NB; ++cg) {
@@ -414,11 +424,11 @@ stage_lone_kernel(const FusedItem* __restrict__ items, QuantDesc q1, StageDesc s
             QMeta mt;
             if (SELFQ) mt = lone_meta(lt, tok);
             else {
-                mt.two_step = ((cptr_meta)sd.meta)[tok].two_step;
-                mt.neg_qs = ((cptr_meta)sd.meta)[tok].neg_qs;
+                mt.two_step = ((cptr_meta)sd.meta)[first + tok].two_step;
+                mt.neg_qs = ((cptr_meta)sd.meta)[first + tok].neg_qs;
             }
             const double val = fma(raw, __builtin_ldexp(mt.two_step, -p), mt.neg_qs);     // exact
-            store_out(sd.out, sd.out_dtype, (size_t)tok * sd.out_stride + grow, (float)val * oscale, sd.out_scale != nullptr);
+            store_out(sd.out, sd.out_dtype, (size_t)(out0 + (int64_t)tok * sd.out_stride) + grow, (float)val * oscale, sd.out_scale != nullptr);
         }
     }
 }
@@ -613,27 +623,38 @@ static size_t lone_lds_bytes(int nb, int pl, int w, int max_steps, int batch)
     return (size_t)lone_red_ints(nb, pl, w) * 4 + sizeof(LoneTokens) + (size_t)batch * lone_tok_bytes(max_steps);
 }
 
+// More than eight tokens of one op are dealt out in groups of at most eight, of even sizes.
+static int lone_group(int batch) { return (batch + (batch + 7) / 8 - 1) / ((batch + 7) / 8); }
+static int lone_groups(int batch) { return (batch + 7) / 8; }
+
+// Whether more than eight tokens are faster in groups than in the groups of 16 of nq_exact.hip: where several workgroups share every pair of row block
+// and group, i.e. up to half as many pairs as CUs.  us per forward, here / there: 4096 x 4096 r = 1024 at 9, 24, 32 tokens 11.9 / 18.2, 16.0 / 18.6,
+// 16.3 / 18.7, past the line at 40 and 80 20.7 / 19.6, 31.6 / 21.5; 1024 x 1024 r = 256 at 64 and 128 11.3 / 14.0, 13.2 / 14.7; 8192 x 28672 r = 3520 at 16
+// 38.9 / 42.3, past it at 24 and 40 44.1 / 44.1, 57.3 / 47.7; 8192 x 8192 r = 2240 at 16 23.3 / 24.8, past it at 24 33.2 / 25.7.
+bool lone_deals_out(int n_rb, int batch) { return 2 * n_rb * lone_groups(batch) <= device_cu_count(); }
+
 // Whether the workgroups of such a launch quantise its input themselves.  Whole row blocks per workgroup (more than half as many as CUs)
 // leave eight waves for it, which pays for fewer elements (28672 rows, batch 8: r = 1024 14.2 us against 15.9 with launches of their own, r = 3520
 // 22.0 and 18.5; batch 4 r = 600 11.8 and 13.2, r = 3520 14.8 and 14.0; 22000 rows r = 2240 level).
 bool lone_selfq(int max_steps, int n_rb, int batch)
 {
-    const int pl = lone_planes(n_rb);
-    return batch * lone_pieces<16>(max_steps) * 1024 <= (pl == 8 ? kLoneMaxElements * 3 / 8 : kLoneMaxElements) &&
-           lone_lds_bytes(batch <= 5 ? 1 : 2, pl, pl == 8 ? 8 : 16, max_steps, batch) <= kLoneLdsBytes;
+    const int pl = lone_planes(n_rb * lone_groups(batch)), per = lone_group(batch);
+    return per * lone_pieces<16>(max_steps) * 1024 <= (pl == 8 ? kLoneMaxElements * 3 / 8 : kLoneMaxElements) &&
+           lone_lds_bytes(per <= 5 ? 1 : 2, pl, pl == 8 ? 8 : 16, max_steps, per) <= kLoneLdsBytes;
 }
 
 template <int NB, int PL, int W, bool SELFQ>
-static int launch_lone_t(const FusedItem* d_items, int n_rb, const QuantDesc& q, const StageDesc& sd, int max_steps, int batch, hipStream_t s)
+static int launch_lone_t(const FusedItem* d_items, int n_rb, const QuantDesc& q, const StageDesc& sd, int max_steps, int batch, int per, hipStream_t s)
 {
-    const size_t bytes = SELFQ ? lone_lds_bytes(NB, PL, W, max_steps, batch) : (size_t)lone_red_ints(NB, PL, W) * 4;
+    const size_t bytes = SELFQ ? lone_lds_bytes(NB, PL, W, max_steps, per) : (size_t)lone_red_ints(NB, PL, W) * 4;
     static bool attr_set = false;
     if (!attr_set) {
         NQ_HIP(hipFuncSetAttribute((const void*)stage_lone_kernel<NB, PL, W, SELFQ>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLoneLdsBytes));
         attr_set = true;
     }
-    const dim3 grid((unsigned)((n_rb + 7) / 8 * 8 * (8 / PL)));
-    NQ_LAUNCH((stage_lone_kernel<NB, PL, W, SELFQ>), grid, dim3(64 * W), bytes, s, d_items, q, sd, n_rb, batch);
+    const int pairs = n_rb * ((batch + per - 1) / per);
+    const dim3 grid((unsigned)((pairs + 7) / 8 * 8 * (8 / PL)));
+    NQ_LAUNCH((stage_lone_kernel<NB, PL, W, SELFQ>), grid, dim3(64 * W), bytes, s, d_items, q, sd, n_rb, batch, per);
     NQ_HIP(hipGetLastError());
     return NQ_OK;
 }
@@ -647,8 +668,8 @@ int launch_lone_selfq(const FusedItem* d_items, int n_rb, const QuantDesc& q, co
         set_error("launch_lone_selfq: input too long for the workgroups to quantise");
         return NQ_E_INVALID_ARG;
     }
-    const int pl = lone_planes(n_rb);
-#define NQ_LONE(PL, W) (batch <= 5 ? launch_lone_t<1, PL, W, true>(d_items, n_rb, q, sd, max_steps, batch, s) : launch_lone_t<2, PL, W, true>(d_items, n_rb, q, sd, max_steps, batch, s))
+    const int pl = lone_planes(n_rb * lone_groups(batch)), per = lone_group(batch);
+#define NQ_LONE(PL, W) (per <= 5 ? launch_lone_t<1, PL, W, true>(d_items, n_rb, q, sd, max_steps, batch, per, s) : launch_lone_t<2, PL, W, true>(d_items, n_rb, q, sd, max_steps, batch, per, s))
     if (pl == 1) return NQ_LONE(1, 16);
     if (pl == 2) return NQ_LONE(2, 16);
     if (pl == 4) return NQ_LONE(4, 16);
@@ -656,18 +677,18 @@ int launch_lone_selfq(const FusedItem* d_items, int n_rb, const QuantDesc& q, co
 #undef NQ_LONE
 }
 
-// The same on an input that a launch of its own has quantised; w: 16 or (batch 6 to 8) 8 waves per workgroup.
+// The same on an input that a launch of its own has quantised; w: 16 or (six to eight tokens a group) 8 waves per workgroup.
 int launch_lone(const FusedItem* d_items, int n_rb, const StageDesc& sd, int w, int batch, hipStream_t s)
 {
     if (n_rb < 1) return NQ_OK;
-    const int pl = lone_planes(n_rb);
+    const int pl = lone_planes(n_rb * lone_groups(batch)), per = lone_group(batch);
     const QuantDesc q{};
 #define NQ_LONE(NB, W)                                                            \
-    (pl == 1   ? launch_lone_t<NB, 1, W, false>(d_items, n_rb, q, sd, 0, batch, s) \
-     : pl == 2 ? launch_lone_t<NB, 2, W, false>(d_items, n_rb, q, sd, 0, batch, s) \
-     : pl == 4 ? launch_lone_t<NB, 4, W, false>(d_items, n_rb, q, sd, 0, batch, s) \
-               : launch_lone_t<NB, 8, W, false>(d_items, n_rb, q, sd, 0, batch, s))
-    if (batch <= 5) return NQ_LONE(1, 16);
+    (pl == 1   ? launch_lone_t<NB, 1, W, false>(d_items, n_rb, q, sd, 0, batch, per, s) \
+     : pl == 2 ? launch_lone_t<NB, 2, W, false>(d_items, n_rb, q, sd, 0, batch, per, s) \
+     : pl == 4 ? launch_lone_t<NB, 4, W, false>(d_items, n_rb, q, sd, 0, batch, per, s) \
+               : launch_lone_t<NB, 8, W, false>(d_items, n_rb, q, sd, 0, batch, per, s))
+    if (per <= 5) return NQ_LONE(1, 16);
     return w == 16 ? NQ_LONE(2, 16) : NQ_LONE(2, 8);
 #undef NQ_LONE
 }

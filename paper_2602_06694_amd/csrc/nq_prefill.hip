@@ -844,7 +844,7 @@ static int steps_per_split4(int nst, int splits, int ks = 1)
 //    partial sums, 0.29 us per MB.
 // One column at a time (`plain`) the steps take 0.60, 1.05, 0.97, 0.49 and 0.35 us (each of ten tilings
 // of the two GEMMs of six layers at 24 to 2048 tokens, against the same in pairs), the rest is the same.
-struct GemmTiling { int tg, splits, ks; };
+struct GemmTiling { int tg, splits, ks; double us; };
 struct StepCost { double alone4, two4, halves4, alone2, each2; };
 static GemmTiling choose_tiling(int m_pad, int n_rb, int nst, int n_pad, bool plain)
 {
@@ -852,7 +852,7 @@ static GemmTiling choose_tiling(int m_pad, int n_rb, int nst, int n_pad, bool pl
     const int cus = device_cu_count();
     const int n_tiles = (n_rb + kPfWaves - 1) / kPfWaves;
     const double partial_mb = (double)m_pad * n_pad * 4.0 / 1e6;
-    GemmTiling best = {4, 1, 1};
+    GemmTiling best = {4, 1, 1, 0.0};
     double best_cost = 1e30;
     auto consider = [&](int tg, int splits, int ks) {
         const int wgs = (m_pad / (16 * tg)) * n_tiles * splits, per = steps_per_split4(nst, splits, ks);
@@ -868,7 +868,7 @@ static GemmTiling choose_tiling(int m_pad, int n_rb, int nst, int n_pad, bool pl
             cost = full * (per * step_full + fixed) + (rem ? per * step_rem + fixed : 0.0);
         }
         if (splits > 1) cost += 2.8 + splits * (0.23 + 0.29 * partial_mb);
-        if (cost < best_cost) { best_cost = cost; best = {tg, splits, ks}; }
+        if (cost < best_cost) { best_cost = cost; best = {tg, splits, ks, cost}; }
     };
     for (int s = 1; s <= 16; ++s) {
         consider(4, s, 1);
@@ -912,6 +912,14 @@ static PfLayout pf_layout(int64_t d_out, int64_t d_in, int64_t r, int batch, boo
     o += al256(std::max(p1, p2));
     L.total = o;
     return L;
+}
+
+// The path's time without what the caller's host side adds, as the exact path is costed against it (nq_api.hip).
+double prefill_us(int64_t d_out, int64_t d_in, int64_t r, int batch)
+{
+    const int m_pad = (int)round_up(batch, kPfTokens), rb1 = (int)n_rowblocks(r), rb2 = (int)n_rowblocks(d_out);
+    return 0.94 * (choose_tiling(m_pad, rb1, (int)n_steps(d_in), rb1 * kTileRows, false).us +
+                   choose_tiling(m_pad, rb2, (int)n_steps(r), rb2 * kTileRows, false).us) + 0.67e-6 * batch * (double)(d_in + d_out);
 }
 
 size_t prefill_workspace_bytes(int64_t d_out, int64_t d_in, int64_t r, int batch, bool plain)
