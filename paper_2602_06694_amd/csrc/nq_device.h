@@ -100,6 +100,17 @@ __device__ inline void load_chunk16(const QuantDesc& d, int64_t base, int c, boo
     }
 }
 
+// 2^e, -126 <= e <= 127
+__device__ __forceinline__ float exp2_int(int e) { return __builtin_bit_cast(float, (e + 127) << 23); }
+// exponent of the quantisation step of a token whose largest magnitude has the bits `m` (0 for a token of zeros or with a non-finite value):
+// f 2^e with f in [0.5, 1) gives 2^(e - 22), at least the smallest normal number
+constexpr uint32_t kMostBits = 0x7f61b1e6u;            // of 3.0e38: larger ones (infinities and NaNs among them) count as not finite
+__device__ __forceinline__ int step_exponent(uint32_t m)
+{
+    const int se = (int)(m >> 23) - 126 - 22;
+    return m != 0 && m <= kMostBits ? (se < -126 ? -126 : se) : 0;
+}
+
 // byte 0 of a, b, c, d -> one word (a lowest): three byte-permute instructions
 __device__ __forceinline__ uint32_t pack_low_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d)
 {

@@ -9,15 +9,21 @@
 // task is a run of 128-row blocks of one phase's sign matrix.  Nothing is ever waited for except data:
 //
 //  - every value that crosses from one phase to the next (t of stage 1; y where a later layer of
-//    the same call reads it) is stored as a 64-bit pair (fp32 bits, epoch) with ONE device-scope
-//    store, and read with device-scope loads; a consumer accepts a pair only if it carries the
-//    epoch of this launch, else it reads again.  A pair is written by a single 8-byte store, so it
-//    is seen whole or not at all: no flag, no counter, no fence, no ordering between stores.  The
-//    epoch lives in device memory and is advanced by the last workgroup to leave, so a replay of a
-//    captured launch gets a fresh one.
+//    the same call reads it) is one 32-bit word, stored with ONE device-scope store and read with device-scope
+//    loads.  The word is the fp32 value; the bits of one NaN that no value has (results that are NaN are stored with other bits) mean
+//    "not there yet", and a consumer that meets them reads again: no flag, no counter, no fence, no ordering between
+//    stores.  There are two copies of every such array, for launches of even and odd number: who stores a value in this launch's
+//    copy clears it in the other, which nobody reads before the next launch.  The number lives in device memory and is
+//    advanced by the last workgroup to leave, so a replay of a captured launch takes the copies in turn too.
+//
+// What bounds it: 256 dependent phases of 4.65 us per token of a 7B-shaped stack.  Of those the hand-over is 1.5 to 3.3 us (6 to 10 for 28672
+// values): a store, half a polling period and a read past the L2, and the contention of up to 128 workgroups that all read the whole
+// input.  Then 0.5 to 0.9 us for the fixed point, 0.7 to 1.7 for the products, 0.5 for adding them up and storing.  As pairs of value and launch number, read 16
+// elements per lane (a line per 16-byte request), hand-overs took 2.4 to 5 us (17 of 28672 values); whole row blocks per workgroup,
+// loops over the longest input's groups without an exit and addresses spilled from phase to phase cost another 1.5 us: 1818 -> 1190 us per token.
 //  - every wait is bounded by a wall-clock limit; a workgroup that gives up sets an error word
 //    and leaves, the others see the word (or run into their own limit) and leave too: the grid
-//    always drains.
+//    always drains.  (They clear the other copies of what their tasks would have stored first.)
 //  - a workgroup requests the first sign tiles of its next task BEFORE it waits for that task's
 //    input, so the weights stream while the dependency chain is being walked.
 //
@@ -38,8 +44,9 @@ constexpr int kExecWaves = 8;                      // two per SIMD
 constexpr int kExecThreads = 64 * kExecWaves;
 constexpr int kExecRing = 8;                       // sign tiles a wave keeps in flight
 constexpr int kExecMaxSteps = 512;                 // longest reduction: 32768 elements (96 KiB of LDS as fixed point)
-constexpr int kExecEpiInts = 3 * kTileRows;        // per wave: the three slice columns x 128 rows
-constexpr int kExecHeld = 4;                       // 16-element chunks of the input a thread keeps in registers (4 x 512 threads x 16 = 32768 elements)
+constexpr int kExecEpiInts = 3 * kTileRows + 16;   // per wave: the three slice columns x 128 rows, 16 banks on from wave to wave
+constexpr int kExecWordBytes = 64;                 // the words of the reductions over a workgroup
+constexpr int kExecHeld = 16;                      // groups of four elements of the input that a thread keeps in registers
 
 // One task of one workgroup: a run of row blocks of one stage of one layer, with everything the
 // kernel needs to know about that stage in the record itself -- a workgroup's records are
@@ -47,42 +54,45 @@ constexpr int kExecHeld = 4;                       // 16-element chunks of the i
 // W = 1 << wl waves share a row block, 8 / W row blocks are worked on side by side.
 struct ExecTask {
     const uint32_t* tiles;          // sign tiles of A (V^T or U)
-    const void* in;                 // the input vector: plain elements of in_dtype (in_ll 0), pairs (1), or none: the LDS array (2)
+    const void* in;                 // the input vector: plain elements of in_dtype (in_ll 0), words handed over (1), or none: the LDS array (2)
     const uint16_t* in_scale;       // fp16 [N] or nullptr
     const uint16_t* out_scale;      // fp16 [M rounded up to whole row blocks] or nullptr
     void* out;                      // plain output [M] of out_dtype, or nullptr
-    unsigned long long* out_ll;     // pairs [M] for the stages that read this output in the same launch, or nullptr
+    unsigned int* out_ll;           // words [M] for the stages that read this output in the same launch (the copy of even launches), or nullptr
     int M, N, n_steps, in_dtype, out_dtype, in_ll;
     int rb0, n_rb, wl;
     int out_lds;                    // the (fp32) output also goes to the workgroup's LDS array, for its next task (in_ll == 2)
-    int pad[2];
+    int p0, pl;                     // pl > 0: bit planes p0 .. p0 + pl - 1 (16 rows each) of the one row block, all eight waves on it
 };
 static_assert(sizeof(ExecTask) == 96, "task record");
+static_assert(kExecMaxSteps * 16 <= kExecHeld * kExecThreads, "a thread holds all of its groups");
 
 struct ExecState {                  // device words shared by the launches of one executor
-    unsigned int epoch;             // of the NEXT launch (never 0: a cleared pair is never valid)
+    unsigned int epoch;             // number of the NEXT launch
     unsigned int done;              // workgroups of the running launch that have left
     int error;                      // sticky: a wait ran into its limit
     int pad;
 };
 
-typedef __attribute__((address_space(1))) unsigned long long* gptr_u64;
+typedef __attribute__((address_space(1))) unsigned int* gptr_u32;
 
+constexpr unsigned int kNotThere = 0xffffffffu;    // a NaN of these bits is never stored as a value
 
-__device__ __forceinline__ void ll_store(unsigned long long* p, float v, unsigned int epoch)
+__device__ __forceinline__ void ll_store(unsigned int* p, unsigned int bits)
 {
-    const unsigned long long pair = (unsigned long long)__builtin_bit_cast(unsigned int, v) | ((unsigned long long)epoch << 32);
     // (global, not generic, address space: a flat store would count on both wait counters)
-    __hip_atomic_store((gptr_u64)p, pair, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store((gptr_u32)p, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ unsigned int ll_bits(float v) { return v == v ? __builtin_bit_cast(unsigned int, v) : 0x7fc00000u; }
 
 // ---------------------------------------------------------------------------------------------
 // LDS: [bq_bytes] the task's input as fixed point (layout of the global buffers of the streaming
 // kernels) | [8][3][128] raw sums of the waves | sum of q, largest magnitude, flags
 // ---------------------------------------------------------------------------------------------
-// tasks[ti .. t_end) of this workgroup; state == nullptr: a lone workgroup whose tasks hand over through LDS only
+// tasks[ti .. t_end) of this workgroup; SMALL: a lone workgroup whose tasks hand over through LDS only (state == nullptr)
+template <bool SMALL>
 __device__ __forceinline__ void exec_body(const ExecTask* __restrict__ tasks, int ti, const int t_end,
-                                          ExecState* __restrict__ state, int bq_bytes, unsigned long long spin_ticks)
+                                          ExecState* __restrict__ state, int bq_bytes, size_t copy_words, unsigned long long spin_ticks)
 {
     extern __shared__ __align__(16) int lds[];
     constexpr int D = kExecRing;
@@ -91,22 +101,24 @@ __device__ __forceinline__ void exec_body(const ExecTask* __restrict__ tasks, in
     // reductions over the workgroup go through LDS atomics (one instruction per wave each, no shuffle
     // chains): the sum of the quantised values, the largest magnitude (as the bits of a non-negative
     // float), "a value is not finite", "a wait gave up"
-    unsigned long long* const lds_sum = (unsigned long long*)(lds_epi + kExecWaves * kExecEpiInts);
-    unsigned int* const lds_max = (unsigned int*)(lds_sum + 1);
-    int* const lds_bad = (int*)(lds_max + 1);
-    int* const lds_abort = lds_bad + 1;
-    float* const lds_t = (float*)(lds_sum + 4);             // (past the 32 bytes of words above) an output kept in LDS for the next task of this workgroup
+    // (two sets, of consecutive tasks: a task clears the other's while everybody is between its two barriers)
+    struct Words {
+        unsigned long long sum;
+        unsigned int max;
+    };
+    Words* const words = (Words*)(lds_epi + kExecWaves * kExecEpiInts);
+    int* const lds_abort = (int*)(words + 2);
+    float* const lds_t = (float*)((char*)words + kExecWordBytes);     // an output kept in LDS for the next task of this workgroup
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, n = lane & 15;
     const unsigned int epoch = state ? state->epoch : 0u;   // written by the previous launch (or the host)
+    const size_t now = epoch & 1u ? copy_words : 0, other = copy_words - now;      // this launch's copies and the others, from the even ones
     if (tid == 0) {
         *lds_abort = 0;
-        *lds_sum = 0;
-        *lds_max = 0;
-        *lds_bad = 0;
+        words[0] = words[1] = Words{0, 0};
     }
     __syncthreads();
 
@@ -130,37 +142,43 @@ __device__ __forceinline__ void exec_body(const ExecTask* __restrict__ tasks, in
         a_base = (const char*)(t).tiles +                                                  \
                  (size_t)(act_ ? rb_ : (t).rb0) * nst_ * (kTileWords * 4);                         \
         a_off = (uint32_t)((cnt > 0 ? part : 0) * 1024 + lane * 16);                               \
+        /* (ordinary loads: the workgroups that share a row block share its tiles in their L2) */  \
         _Pragma("unroll") for (int k = 0; k < D; ++k) {                                            \
             const int kk = k < cnt ? k : (cnt > 0 ? cnt - 1 : 0);                                  \
-            wbuf[k] = load_tile_words(a_base, a_off + (uint32_t)kk * (uint32_t)(w_of * 1024));     \
+            wbuf[k] = load_global_v4u(a_base, a_off + (uint32_t)kk * (uint32_t)(w_of * 1024));     \
         }                                                                                          \
         a_off += (uint32_t)(D * w_of * 1024);                                                      \
     } while (0)
 
     // With the first tiles of a task go the scales it will need (static data, usually cold in the caches:
-    // a round trip to memory each): the input scales of the chunk this thread owns -- where the input is
-    // handed over by another stage and fits one chunk per thread -- and the output scales of the rows this
+    // a round trip to memory each): the input scales of the groups this thread owns, where the input is
+    // handed over by another stage, and the output scales of the rows this
     // thread finishes in the task's first group.  All of them are requested before the task's input is
     // waited for and converted only when they are used.
-    v4u sraw[kExecHeld][2];
+    typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+    typedef const __attribute__((address_space(1))) v2u* gptr_v2u;
+    constexpr int kScaled = 8;                              // groups whose scales come ahead: inputs of up to 16384 elements
+    v2u sraw[kScaled];
 #pragma unroll
-    for (int c = 0; c < kExecHeld; ++c) sraw[c][0] = sraw[c][1] = v4u{0, 0, 0, 0};
+    for (int k = 0; k < kScaled; ++k) sraw[k] = v2u{0, 0};
     uint16_t ps[2] = {0, 0};
 #define NQ_PREFETCH_SCALES(t)                                                                      \
     do {                                                                                           \
         const uint16_t* const is_ = (t).in_scale;                                                  \
         const int n_ = (t).N;                                                                      \
-        _Pragma("unroll") for (int c_ = 0; c_ < kExecHeld; ++c_) {                                 \
-            const int j_ = (tid + c_ * kExecThreads) * 16;                                         \
-            if (is_ && (t).in_ll && j_ + 16 <= n_) {                                               \
-                const gptr_v4u sp_ = (gptr_v4u)(is_ + j_);                                         \
-                sraw[c_][0] = sp_[0];                                                              \
-                sraw[c_][1] = sp_[1];                                                              \
+        if (is_ && (t).in_ll == 1) {                                                               \
+            _Pragma("unroll") for (int k_ = 0; k_ < kScaled; ++k_) {                               \
+                if (k_ * kExecThreads + 64 * wave >= 16 * (t).n_steps) break;                      \
+                const int j_ = (k_ * kExecThreads + tid) * 4;                                      \
+                if (j_ + 4 <= n_) sraw[k_] = *(gptr_v2u)(is_ + j_);                                \
             }                                                                                      \
         }                                                                                          \
         const uint16_t* const os_ = (t).out_scale;                                         \
         const int per_ = kExecWaves >> (t).wl;                                                     \
-        _Pragma("unroll") for (int u = 0; u < 2; ++u) {                                            \
+        if ((t).pl > 0) {                                                                          \
+            if (os_ && (tid >> 2) < 16 * (t).pl)                                                   \
+                ps[0] = ((gptr_u16)os_)[(t).rb0 * kTileRows + 16 * (t).p0 + (tid >> 2)];           \
+        } else _Pragma("unroll") for (int u = 0; u < 2; ++u) {                                     \
             const int idx_ = tid + u * kExecThreads;                                               \
             const int rb_ = (t).rb0 + (idx_ >> 7);                                                 \
             if (os_ && idx_ < per_ * kTileRows && rb_ < (t).rb0 + (t).n_rb)                        \
@@ -182,205 +200,268 @@ __device__ __forceinline__ void exec_body(const ExecTask* __restrict__ tasks, in
         const bool more = ti + 1 < t_end;
         if (more) nxt = tasks[ti + 1];
         const int nst = op.n_steps;
-        const int n_chunks = 4 * nst;
+        const int n_groups = 16 * nst;                      // groups of four elements: thread t owns t, t + 512, ... (whole lines per load)
+        Words* const wd = words + (ti & 1);
 
-        // ---- the task's input: load (waiting for this launch's epoch where another stage writes it), scale, quantise ----
-        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)op.in, 0, op.in_ll ? ((op.N + 1) & ~1) * 8 : 0, 0x00020000);   // (whole 16-byte loads; the arrays are padded)
-        QuantDesc qd;
-        qd.x = op.in; qd.scale = op.in_scale; qd.bq = nullptr; qd.meta = nullptr;
-        qd.N = op.N; qd.n_chunks = n_chunks; qd.x_stride = op.N; qd.dtype = op.in_dtype; qd.mag_exp = 22;
+        // ---- the task's input: load (waiting for it where another stage writes it), scale, quantise ----
+        // (whole 16-byte loads; the arrays are padded)
+        const unsigned int* const in_words = (const unsigned int*)op.in + (op.in_ll == 1 ? now : 0);
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)in_words, 0, op.in_ll == 1 ? ((op.N + 3) & ~3) * 4 : 0, 0x00020000);
         const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
         int gave_up = 0;
-        // chunk ch of a paired input -> v; false while a pair of it does not carry this launch's epoch yet
-        auto load_pairs = [&](int ch, float v[16]) {
-            const int j0 = ch * 16;
-            asm volatile("" ::: "memory");                  // another workgroup writes this memory: load again on every call
-            // (device-scope loads, all eight requested before any is looked at; beyond the array the buffer returns zeros)
-            v4u pr[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) pr[q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (j0 + 2 * q) * 8, 0, 16);
-            unsigned int ok = 1u, any = 0u;                 // all pairs of the chunk carry the epoch / at least one does
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int j = j0 + 2 * q;
-                const unsigned int e0 = pr[q][1], e1 = pr[q][3];
-                ok &= (unsigned int)(j >= op.N) | (unsigned int)(e0 == epoch);
-                ok &= (unsigned int)(j + 1 >= op.N) | (unsigned int)(e1 == epoch);
-                any |= (unsigned int)(j < op.N) & (unsigned int)(e0 == epoch);
-                const unsigned int b0 = j < op.N ? pr[q][0] : 0u, b1 = j + 1 < op.N ? pr[q][2] : 0u;
-                v[2 * q] = __builtin_bit_cast(float, b0);
-                v[2 * q + 1] = __builtin_bit_cast(float, b1);
-            }
-            return ok | (any << 1);
-        };
-        // the same, repeated until the whole wave has its chunks (or the time is up: gave_up)
-        auto wait_pairs = [&](int ch, float v[16]) {
+        v4u hv[kExecHeld];                                  // (as bits until they are scaled)
+        // (whole steps of four: whether a wave has a k-th group is the same for all of its lanes)
+        const int wave0 = 64 * wave;
+        int t = tid;
+        asm volatile("" : "+v"(t));                         // (addresses are formed here, not kept from task to task, which spills them)
+        if (!SMALL && op.in_ll == 1) {
+            // Read until everything is there (or the time is up: gave_up).  Inputs of one group per thread are asked for outright; of longer ones the wave polls the first word of its share only (one
+            // transaction per round, all lanes the same address), so that workgroups waiting far ahead of the running phase leave the
+            // memory system alone; then it asks for the groups that are not complete yet, all of them before any is looked at.
+            // (Device-scope loads; beyond the array the buffer returns zeros.)
+            const int mine = wave0 < n_groups ? (n_groups - wave0 + kExecThreads - 1) / kExecThreads : 0;
+            unsigned int todo = (1u << mine) - 1u;
             unsigned int spins = 0;
-            const int j_wave = (ch - lane) * 16;            // first element of this wave's share
-            for (;;) {
-                const unsigned int got = load_pairs(ch, v);
-                if (__builtin_amdgcn_ballot_w64((got & 1u) == 0u) == 0) return;
-                // Not all there yet.  If part of the wave's share is, the producing phase is under way:
-                // the wave asks again at once.  If nothing is, the wave polls its first pair only (one
-                // transaction per round, all lanes the same address) until that one carries this launch's
-                // epoch, so that workgroups waiting far ahead of the running phase leave the memory system alone.
-                bool stop = false;
-                const bool some = __builtin_amdgcn_ballot_w64((got & 2u) != 0u) != 0;
-                for (; !some;) {
-                    typedef unsigned int v2u __attribute__((ext_vector_type(2)));
-                    asm volatile("" ::: "memory");
-                    const v2u pr = __builtin_amdgcn_raw_buffer_load_b64(rsrc, j_wave * 8, 0, 16);
-                    if (j_wave >= op.N || pr.y == epoch) break;
-                    ++spins;
-                    // (the clock and the error word are looked at every 16th round, and on the first: a limit of zero gives up at once)
-                    if ((spins & 15u) == 1u)
-                        stop = __builtin_amdgcn_s_memrealtime() - t0 > spin_ticks ||
-                               __hip_atomic_load(&state->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-                    if (stop) break;
-                    __builtin_amdgcn_s_sleep(8);
+            bool waiting = op.N > 4 * kExecThreads && wave0 * 4 < op.N;
+            while (todo) {
+                asm volatile("" ::: "memory");              // another workgroup writes this memory: load again every time
+                if (waiting) {
+                    waiting = __builtin_amdgcn_raw_buffer_load_b32(rsrc, wave0 * 16, 0, 16) == kNotThere;
+                    if (waiting) {
+                        ++spins;
+                        // (the clock and the error word are looked at every 16th round, and on the first: a limit of zero gives up at once)
+                        if ((spins & 15u) == 1u && (__builtin_amdgcn_s_memrealtime() - t0 > spin_ticks ||
+                                                    __hip_atomic_load(&state->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
+                            gave_up = 1;
+                            break;
+                        }
+                        __builtin_amdgcn_s_sleep(8);
+                        continue;
+                    }
                 }
-                if (stop || __builtin_amdgcn_s_memrealtime() - t0 > spin_ticks) {
+#pragma unroll
+                for (int k = 0; k < kExecHeld; ++k)
+                {
+                    if (k * kExecThreads + wave0 >= n_groups) break;
+                    if (todo & (1u << k)) hv[k] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (k * kExecThreads + t) * 16, 0, 16);
+                }
+#pragma unroll
+                for (int k = 0; k < kExecHeld; ++k) {
+                    if (k * kExecThreads + wave0 >= n_groups) break;
+                    if (todo & (1u << k)) {
+                        const int j = (k * kExecThreads + t) * 4;
+                        bool missing = false;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) missing |= hv[k][i] == kNotThere && j + i < op.N;
+                        if (__builtin_amdgcn_ballot_w64(missing) == 0) todo &= ~(1u << k);
+                    }
+                }
+                if (todo && (__builtin_amdgcn_s_memrealtime() - t0 > spin_ticks ||
+                             ((++spins & 15u) == 0 && __hip_atomic_load(&state->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0))) {
                     gave_up = 1;
-                    return;
+                    break;
                 }
-            }
-        };
-        // v *= the input scale of chunk ch (as the quantiser of the streaming path does: one fp32 product)
-        auto scale_chunk = [&](int ch, float v[16]) {
-            if (!op.in_scale) return;
-            const int j0 = ch * 16;
-            if (j0 + 16 <= op.N) {
-                const gptr_v4u sp = (gptr_v4u)(op.in_scale + j0);
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const v4u u = sp[q];
-                    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        v[8 * q + 2 * i] *= half_bits_to_float((uint16_t)(w[i] & 0xFFFFu));
-                        v[8 * q + 2 * i + 1] *= half_bits_to_float((uint16_t)(w[i] >> 16));
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    if (j0 + i < op.N) v[i] *= half_bits_to_float(((gptr_u16)op.in_scale)[j0 + i]);
-            }
-        };
-        auto max_of = [&](const float v[16], float& m, int& bad) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const float a = fabsf(v[i]);
-                if (!(a <= 3.0e38f)) bad = 1;
-                m = fmaxf(m, a);
-            }
-        };
-        // A thread owns chunks tid, tid + 512, ...; inputs of up to 32768 elements (four chunks per thread: every input
-        // the executor accepts, kExecMaxSteps) stay in registers between the maximum and the rounding; the other
-        // branch, which fetches a longer input twice, is kept for a narrower workgroup.
-        const int n_c = (n_chunks + kExecThreads - 1) / kExecThreads;           // chunks per thread
-        const bool held = n_c <= kExecHeld;
-        if (op.in_ll == 2) __syncthreads();                 // the LDS array of this workgroup's previous task is complete
-        float hv[kExecHeld][16];
-        float m = 0.f;
-        int bad = 0;
-        // chunk ch of the input, scaled, wherever it comes from (c: which of the thread's chunks, for the prefetched scales)
-        auto fetch = [&](int ch, int c, float v[16]) {
-            if (op.in_ll == 0) {
-                if (ch < n_chunks) load_chunk16(qd, 0, ch, true, v);
-                else {
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) v[i] = 0.f;
-                }
-                return;
-            }
-            if (op.in_ll == 1) {
-                wait_pairs(ch, v);                          // (a chunk past the end reads as zeros)
-            } else {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) v[i] = ch * 16 + i < op.N ? lds_t[ch * 16 + i] : 0.f;
-            }
-            if (c < kExecHeld && op.in_scale && ch * 16 + 16 <= op.N) {
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const uint32_t w[4] = {sraw[c][q].x, sraw[c][q].y, sraw[c][q].z, sraw[c][q].w};
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        v[8 * q + 2 * i] *= half_bits_to_float((uint16_t)(w[i] & 0xFFFFu));
-                        v[8 * q + 2 * i + 1] *= half_bits_to_float((uint16_t)(w[i] >> 16));
-                    }
-                }
-            } else {
-                scale_chunk(ch, v);
-            }
-        };
-        // (a wave none of whose lanes owns a chunk goes straight to the barrier)
-        const bool wave_works = tid - lane < n_chunks;
-        if (held) {
-#pragma unroll
-            for (int c = 0; c < kExecHeld; ++c) {
-                if (c < n_c && tid - lane + c * kExecThreads < n_chunks) {
-                    fetch(tid + c * kExecThreads, c, hv[c]);
-                    max_of(hv[c], m, bad);
-                }
+                if (todo && op.N <= 4 * kExecThreads) __builtin_amdgcn_s_sleep(2);
             }
         } else {
-            for (int c = 0; c < n_c && !gave_up; ++c) {
-                fetch(tid + c * kExecThreads, kExecHeld, hv[0]);
-                max_of(hv[0], m, bad);
+            if (SMALL && op.in_ll == 2) __syncthreads();    // the LDS array of this workgroup's previous task is complete
+#pragma unroll
+            for (int k = 0; k < kExecHeld; ++k) {
+                if (k * kExecThreads + wave0 >= n_groups) break;
+                const int j = (k * kExecThreads + t) * 4;
+                {
+                    hv[k] = v4u{0, 0, 0, 0};
+                    if (SMALL && op.in_ll == 2) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) hv[k][i] = j + i < op.N ? __builtin_bit_cast(unsigned int, lds_t[j + i]) : 0u;
+                    } else if (j + 4 <= op.N) {             // (x is 16-byte aligned)
+                        if (op.in_dtype == NQ_F32) {
+                            hv[k] = *(gptr_v4u)((const float*)op.in + j);
+                        } else {
+                            const v2u h = *(gptr_v2u)((const uint16_t*)op.in + j);
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                const uint16_t b = (uint16_t)(h[i / 2] >> (16 * (i & 1)));
+                                hv[k][i] = __builtin_bit_cast(unsigned int, op.in_dtype == NQ_F16 ? half_bits_to_float(b) : bf16_bits_to_float(b));
+                            }
+                        }
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (j + i < op.N) hv[k][i] = __builtin_bit_cast(unsigned int, load_as_float(op.in, op.in_dtype, j + i));
+                    }
+                    if (k < kScaled && op.in_scale && j + 4 <= op.N) sraw[k % kScaled] = *(gptr_v2u)(op.in_scale + j);
+                }
             }
         }
-        if (wave_works) {
-            m = wave_reduce32(m, [](float a, float b) { return fmaxf(a, b); });
-            bad = __builtin_amdgcn_ballot_w64(bad != 0) != 0;
-            if (lane == 0) {                                // one LDS atomic per wave
-                atomicMax(lds_max, __builtin_bit_cast(unsigned int, m));      // m >= 0: its bits order like the value
-                if (bad) atomicOr(lds_bad, 1);
+        if (op.N & 3) {                                     // the one group that the input ends inside of
+#pragma unroll
+            for (int k = 0; k < kExecHeld; ++k) {
+                const int j = (k * kExecThreads + t) * 4;
+                if (j < op.N && j + 4 > op.N) {
+                    uint16_t h[4] = {0, 0, 0, 0};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        if (j + i >= op.N) hv[k][i] = 0;
+                        else if (op.in_scale) h[i] = ((gptr_u16)op.in_scale)[j + i];
+                    }
+                    if (k < kScaled) sraw[k % kScaled] = v2u{(unsigned int)h[0] | (unsigned int)h[1] << 16, (unsigned int)h[2] | (unsigned int)h[3] << 16};
+                    else if (op.in_scale)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) hv[k][i] = __builtin_bit_cast(unsigned int, times_half(__builtin_bit_cast(float, (unsigned int)hv[k][i]), h[i]));
+                }
             }
+        }
+        unsigned int m = 0;                                 // (as bits: magnitudes order like them, NaN above all)
+#pragma unroll
+        for (int k = 0; k < kExecHeld; ++k) {
+            if (k * kExecThreads + wave0 >= n_groups) break;
+            {
+                if (op.in_scale) {
+                    // times the input scale, as the quantiser of the streaming path does: one fp32 product
+                    const int j = (k * kExecThreads + t) * 4;
+                    v2u sc = sraw[k % kScaled];
+                    if (k < kScaled || j + 4 <= op.N) {
+                        if (k >= kScaled) sc = *(gptr_v2u)(op.in_scale + j);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            hv[k][i] = __builtin_bit_cast(unsigned int, times_half(__builtin_bit_cast(float, (unsigned int)hv[k][i]), (uint16_t)(sc[i / 2] >> (16 * (i & 1)))));
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const unsigned int a = hv[k][i] & 0x7fffffffu;
+                    m = a > m ? a : m;
+                }
+            }
+        }
+        // (a wave none of whose lanes owns a group goes straight to the barrier)
+        const bool wave_works = wave0 < n_groups;
+        if (wave_works) {
+            m = wave_reduce32(m, [](unsigned int a, unsigned int b) { return a > b ? a : b; });
+            if (lane == 0) atomicMax(&wd->max, m);          // one LDS atomic per wave
             if (gave_up) *lds_abort = 1;
         }
         __syncthreads();
         if (*lds_abort) break;                              // the whole workgroup leaves (same LDS word for all)
-        m = __builtin_bit_cast(float, *lds_max);
-        bad = *lds_bad;
-        int ex = 0;
-        float step = 1.0f;
-        if (m > 0.f && !bad) {
-            (void)frexpf(m, &ex);
-            int se = ex - 22;
-            se = se < -126 ? -126 : se;
-            step = ldexpf(1.0f, se);
-        }
-        const float inv_step = 1.0f / step;
+        m = wd->max;
+        if (tid == 0) words[(ti + 1) & 1] = Words{0, 0};
+        const float step = exp2_int(step_exponent(m));
         if (wave_works) {
-            long long local_sum = 0;
-            if (held) {
+            const float inv_step = exp2_int(-step_exponent(m));
+            int sum = 0;                                    // |q| <= 2^22: 64 of them fit
+            uint32_t* const first = (uint32_t*)lds_bq + 4 * bq_piece(t >> 2, 0) + (t & 3);
 #pragma unroll
-                for (int c = 0; c < kExecHeld; ++c) {
-                    const int ch = tid + c * kExecThreads;
-                    if (c < n_c && ch < n_chunks)
-                        local_sum += quantize_chunk16(hv[c], inv_step, (uint4*)lds_bq + bq_piece(ch, 0));
-                }
-            } else {
-                for (int c = 0; c < n_c; ++c) {
-                    const int ch = tid + c * kExecThreads;
-                    fetch(ch, kExecHeld, hv[0]);            // (pairs this thread has already seen valid)
-                    if (ch < n_chunks) local_sum += quantize_chunk16(hv[0], inv_step, (uint4*)lds_bq + bq_piece(ch, 0));
+            for (int k = 0; k < kExecHeld; ++k) {
+                if (k * kExecThreads + wave0 >= n_groups) break;
+                {
+                    uint32_t hi, mid, lo;
+                    const v4f v = __builtin_bit_cast(v4f, hv[k]);
+                    sum += quantize4(v[0], v[1], v[2], v[3], inv_step, hi, mid, lo);
+                    uint32_t* const dst = first + k * (kExecThreads / 16) * (int)(kBqStepBytes / 4);
+                    dst[0] = hi;
+                    dst[16] = mid;
+                    dst[32] = lo;
                 }
             }
-            local_sum = wave_sum64(local_sum);
-            if (lane == 0) atomicAdd(lds_sum, (unsigned long long)local_sum);  // |sum| < 2^39: exact, whatever the order
+            const long long total = wave_sum64(sum);
+            if (lane == 0) atomicAdd(&wd->sum, (unsigned long long)total);     // |sum| < 2^39: exact, whatever the order
         }
         __syncthreads();
-        const double tot = (double)(long long)*lds_sum;
-        const double two_step = bad ? (double)__builtin_nanf("") : 2.0 * (double)step;
+        const double tot = (double)(long long)wd->sum;
+        const double two_step = m <= kMostBits ? 2.0 * (double)step : (double)__builtin_nanf("");
         const double neg_qs = -tot * (double)step;
 
         // ---- the task's row blocks, 8 / W at a time ----
         const int per = kExecWaves >> tk.wl;
         const int n_grp = (tk.n_rb + per - 1) / per;
         const uint32_t b_lane = (uint32_t)(bq_piece(g, n < 3 ? n : 0) * 16);     // unused columns re-read slice 0
-        for (int grp = 0; grp < n_grp; ++grp) {
+        // the value and its hand-over: rounded, then scaled in fp32, as the streaming kernels do
+        auto finish = [&](int grow, double val, uint16_t scale) {
+            float f = (float)val;
+            if (op.out_scale) f *= half_bits_to_float(scale);
+            if (op.out_ll) {
+                // what a reader of the stored output would see: the value after its rounding to the output type
+                float h = f;
+                if (op.out_dtype == NQ_BF16) h = bf16_bits_to_float(float_to_bf16_bits(f));
+                else if (op.out_dtype == NQ_F16) h = half_bits_to_float(float_to_f16_bits(f));
+                ll_store(op.out_ll + now + grow, ll_bits(h));
+                op.out_ll[other + grow] = kNotThere;
+            }
+            if (op.out) store_out(op.out, op.out_dtype, (size_t)grow, f, op.out_scale != nullptr);
+            if (op.out_lds) lds_t[grow] = f;
+        };
+        // PL bit planes of one row block, all waves on it
+        v4i acc[1][8];
+        auto run_planes = [&](auto planes) {
+            constexpr int PL = decltype(planes)::value;
+            uint32_t mask[PL];
+#pragma unroll
+            for (int p = 0; p < PL; ++p) mask[p] = 0x01010101u << (tk.p0 + p);
+#pragma unroll
+            for (int p = 0; p < PL; ++p) acc[0][p] = v4i{0, 0, 0, 0};
+            const char* const b_base = lds_bq + b_lane + wave * (int)kBqStepBytes;
+            auto mac = [&](int k, int i) {
+                const v4u b = *(const v4u*)(b_base + i * (kExecWaves * (int)kBqStepBytes));
+#pragma unroll
+                for (int p = 0; p < PL; ++p)
+                    acc[0][p] = __builtin_amdgcn_mfma_i32_16x16x64_i8((v4i)(wbuf[k] & mask[p]), (v4i)b, acc[0][p], 0, 0, 0);
+            };
+            auto issue = [&](int k) {
+                wbuf[k] = load_global_v4u(a_base, a_off);
+                a_off += (uint32_t)(kExecWaves * 1024);
+            };
+            // whole passes over the ring without a branch, so that the waits inside stay partial (few planes: long reductions); then what is left
+            int i0 = 0;
+            if (PL <= 2) {
+                for (; i0 + 2 * D <= cnt; i0 += D) {
+#pragma unroll
+                    for (int k = 0; k < D; ++k) {
+                        mac(k, i0 + k);
+                        issue(k);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            }
+            for (; i0 < cnt; i0 += D) {
+#pragma unroll
+                for (int k = 0; k < D; ++k) {
+                    if (i0 + k < cnt) {
+                        mac(k, i0 + k);
+                        if (i0 + k + D < cnt) issue(k);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            }
+#pragma unroll
+            for (int p = 0; p < PL; ++p)
+                if (n < 3) *((v4i*)(lds_epi + wave * kExecEpiInts + n * kTileRows) + g + 4 * p) = acc[0][p];
+        };
+        if (tk.pl > 0) {
+            if (tk.pl == 1) run_planes(std::integral_constant<int, 1>{});
+            else if (tk.pl == 2) run_planes(std::integral_constant<int, 2>{});
+            else if (tk.pl == 4) run_planes(std::integral_constant<int, 4>{});
+            else run_planes(std::integral_constant<int, 8>{});
+            __syncthreads();
+            // a quad of lanes per row, two waves' sums each
+            const int row = tid >> 2, grow = tk.rb0 * kTileRows + 16 * tk.p0 + row;
+            if (row < 16 * tk.pl) {
+                const int* q = lds_epi + (tid & 3) * kExecEpiInts + row;
+                int s[3];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    s[i] = q[i * kTileRows] + q[4 * kExecEpiInts + i * kTileRows];
+                    s[i] += __builtin_amdgcn_mov_dpp(s[i], 0xB1, 0xf, 0xf, true);          // quad_perm [1, 0, 3, 2]
+                    s[i] += __builtin_amdgcn_mov_dpp(s[i], 0x4E, 0xf, 0xf, true);          // quad_perm [2, 3, 0, 1]
+                }
+                if ((tid & 3) == 0 && grow < op.M) {
+                    const int p = tk.p0 + (row >> 4);
+                    double raw = fma((double)s[0], 65536.0, fma((double)s[1], 256.0, (double)s[2]));
+                    if (p == 7) raw = -raw;                 // bit 7 of an int8 is worth -128
+                    finish(grow, fma(raw, __builtin_ldexp(two_step, -p), neg_qs), ps[0]);         // exact
+                }
+            }
+        } else for (int grp = 0; grp < n_grp; ++grp) {
             // (the output scales of the first group came with the task's first tiles; a later group requests its own now)
             if (grp > 0) {
 #pragma unroll
@@ -392,7 +473,6 @@ __device__ __forceinline__ void exec_body(const ExecTask* __restrict__ tasks, in
                 }
             }
             const uint16_t ps_now[2] = {ps[0], ps[1]};
-            v4i acc[1][8];
 #pragma unroll
             for (int p = 0; p < 8; ++p) acc[0][p] = v4i{0, 0, 0, 0};
             const int last = cnt > 0 ? cnt - 1 : 0;
@@ -423,12 +503,7 @@ __device__ __forceinline__ void exec_body(const ExecTask* __restrict__ tasks, in
             if (grp + 1 < n_grp) NQ_PRIME(tk, grp + 1);
 
             // ---- epilogue: raw sums -> LDS, added over the W waves of a row block, scaled, stored ----
-            __syncthreads();
-            if (tid == 0 && grp == 0) {                     // every thread has read them; the next task starts from zero
-                *lds_sum = 0;
-                *lds_max = 0;
-                *lds_bad = 0;
-            }                                // the regions (and, after the last group, the input) are free
+            if (grp > 0) __syncthreads();                   // (the regions of the group before; those of a task before are free since its successor's barriers)
             if (n < 3) {
                 v4i* dst = (v4i*)(lds_epi + wave * kExecEpiInts + n * kTileRows) + g;
 #pragma unroll
@@ -459,16 +534,7 @@ __device__ __forceinline__ void exec_body(const ExecTask* __restrict__ tasks, in
                     }
                     const double raw = fma((double)h, 65536.0, fma((double)mm, 256.0, (double)l));
                     const double val = fma(raw, __builtin_ldexp(two_step, -(row >> 4)), neg_qs);    // exact
-                    float f = (float)val;                   // (rounded, then scaled in fp32: as the streaming kernels do)
-                    if (op.out_scale) f *= half_bits_to_float(u ? ps_now[1] : ps_now[0]);
-                    if (op.out) store_out(op.out, op.out_dtype, (size_t)grow, f, op.out_scale != nullptr);
-                    if (op.out_lds) lds_t[grow] = f;
-                    if (op.out_ll) {
-                        // what a reader of the stored output would see: the value after its rounding to the output type
-                        if (op.out_dtype == NQ_BF16) f = bf16_bits_to_float(float_to_bf16_bits(f));
-                        else if (op.out_dtype == NQ_F16) f = half_bits_to_float(float_to_f16_bits(f));
-                        ll_store(op.out_ll + grow, f, epoch);
-                    }
+                    finish(grow, val, u ? ps_now[1] : ps_now[0]);
                 }
             }
         }
@@ -485,24 +551,30 @@ __device__ __forceinline__ void exec_body(const ExecTask* __restrict__ tasks, in
 #undef NQ_PRIME
 #undef NQ_PREFETCH_SCALES
 
-    // ---- leave: report a missed deadline; the last workgroup out advances the epoch ----
+    // ---- leave: report a missed deadline; the last workgroup out advances the number ----
+    // (A workgroup that gave up clears what the tasks it did not finish would have cleared: the next launch reads those copies.)
+    for (; ti < t_end; ++ti) {
+        const ExecTask t = tasks[ti];
+        const int row0 = t.rb0 * kTileRows + 16 * t.p0, rows = t.pl > 0 ? 16 * t.pl : t.n_rb * kTileRows;
+        for (int k = tid; k < rows; k += kExecThreads)
+            if (t.out_ll && row0 + k < t.M) t.out_ll[other + row0 + k] = kNotThere;
+    }
     __syncthreads();
     if (tid == 0 && state) {
         if (*lds_abort) __hip_atomic_store(&state->error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const unsigned int left = __hip_atomic_fetch_add(&state->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (left + 1 == gridDim.x) {
             __hip_atomic_store(&state->done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const unsigned int e = epoch + 1;
-            __hip_atomic_store(&state->epoch, e == 0 ? 1u : e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&state->epoch, epoch + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 }
 
 __global__ void __launch_bounds__(kExecThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 exec_kernel(const ExecTask* __restrict__ tasks, const int* __restrict__ task_begin,
-            ExecState* __restrict__ state, int bq_bytes, unsigned long long spin_ticks)
+            ExecState* __restrict__ state, int bq_bytes, size_t copy_words, unsigned long long spin_ticks)
 {
-    exec_body(tasks, task_begin[blockIdx.x], task_begin[blockIdx.x + 1], state, bq_bytes, spin_ticks);
+    exec_body<false>(tasks, task_begin[blockIdx.x], task_begin[blockIdx.x + 1], state, bq_bytes, copy_words, spin_ticks);
 }
 
 // One small layer, both stages, by ONE workgroup in one launch: t stays in LDS between the stages
@@ -514,14 +586,14 @@ struct ExecPair {
 __global__ void __launch_bounds__(kExecThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 exec_small_kernel(ExecPair pair, int bq_bytes)
 {
-    exec_body(pair.t, 0, 2, nullptr, bq_bytes, 0ull);
+    exec_body<true>(pair.t, 0, 2, nullptr, bq_bytes, 0, 0ull);
 }
 
 // ---------------------------------------------------------------------------------------------
 // host: the task lists
 // ---------------------------------------------------------------------------------------------
 struct PlannedTask {
-    int wg, phase, layer, stage, rb0, n_rb, W;
+    int wg, phase, layer, stage, rb0, n_rb, W, p0, pl;
 };
 
 // Levels are run as 2 phases each (stage 1 of every layer of the level, then stage 2).  Inside a
@@ -534,7 +606,7 @@ static void plan_tasks(const int64_t* d_out, const int64_t* d_in, const int64_t*
                        int n_wg, std::vector<PlannedTask>& out)
 {
     out.clear();
-    int start = 0;
+    int start = 0, slot[8] = {};
     for (int i0 = 0; i0 < n;) {
         int i1 = i0;
         while (i1 < n && level_of[i1] == level_of[i0]) ++i1;
@@ -542,6 +614,23 @@ static void plan_tasks(const int64_t* d_out, const int64_t* d_in, const int64_t*
             const int phase = 2 * level_of[i0] + stage;
             std::vector<int> nrb(i1 - i0);
             for (int i = i0; i < i1; ++i) nrb[i - i0] = (int)n_rowblocks(stage == 0 ? r[i] : d_out[i]);
+            // Where every row block finds a workgroup of its own, all of its waves take it; where the row blocks are few, each is dealt out by bit
+            // planes to 8 / pl workgroups, which stream the same tiles and finish 16 pl rows each: on one XCD, whose L2 they share.
+            // (Workgroup w runs on XCD w mod 8; `slot`: the next workgroup of each.)  At most every second workgroup of the grid, because all
+            // of them read the whole input (up to all / three quarters / half / a quarter of it, with time stamps taken: 7B-shaped chain 1462 / 1342 / 1339 /
+            // 1400 us, 70B-shaped block 72 / 71 / 69 / 83).
+            int pl = 1, all = 0;
+            for (int v : nrb) all += v;
+            const int slots = n_wg / 8, deep = (all + 7) / 8;         // workgroups, row blocks per XCD
+            while (pl < 8 && 2 * deep * (8 / pl) > slots) pl *= 2;
+            if (n_wg % 8 == 0 && deep * (8 / pl) <= slots) {
+                int x = 0;
+                for (int i = i0; i < i1; ++i)
+                    for (int rb = 0; rb < nrb[i - i0]; ++rb, x = (x + 1) % 8)
+                        for (int p0 = 0; p0 < 8; p0 += pl, slot[x] = (slot[x] + 1) % slots)
+                            out.push_back(PlannedTask{8 * slot[x] + x, phase, i, stage, rb, 1, kExecWaves, p0, pl});
+                continue;
+            }
             int W = kExecWaves;
             auto runs = [&](int w) {
                 int u = 0;
@@ -562,7 +651,7 @@ static void plan_tasks(const int64_t* d_out, const int64_t* d_in, const int64_t*
                         out.back().rb0 + out.back().n_rb == rb)
                         out.back().n_rb += cnt;                 // the same workgroup goes on with the same layer
                     else
-                        out.push_back(PlannedTask{wg, phase, i, stage, rb, cnt, W});
+                        out.push_back(PlannedTask{wg, phase, i, stage, rb, cnt, W, 0, 0});
                 }
             }
             start = (start + (total + each - 1) / each) % n_wg;
@@ -578,12 +667,12 @@ using namespace nq;
 struct nq_exec_s {
     int n, n_wg, device;
     std::vector<nq_handle> handles;
-    void* alloc;                    // tasks | task_begin | state | pairs
+    void* alloc;                    // tasks | task_begin | state | words handed over, both copies
     ExecTask* tasks;
     int* task_begin;
     ExecState* state;
     int bq_bytes;
-    size_t lds_bytes;
+    size_t lds_bytes, copy_words;
     int n_tasks;
 };
 
@@ -605,6 +694,7 @@ extern "C" int nq_exec_plan_tasks(const int64_t* d_out, const int64_t* d_in, con
     }
     std::vector<PlannedTask> t;
     plan_tasks(d_out, d_in, r, level_of, n, n_workgroups, t);
+    t.erase(std::remove_if(t.begin(), t.end(), [](const PlannedTask& p) { return p.p0 != 0; }), t.end());      // a row block that is dealt out: once
     *n_tasks = (int)t.size();
     if (tasks_out) {
         if ((int)t.size() > capacity) return exec_fail(NQ_E_INVALID_ARG, "nq_exec_plan_tasks: tasks_out too small");
@@ -652,14 +742,14 @@ int launch_small_layer(nq_handle h, const DecodeWorkspace& w, const void* x, voi
     a.tiles = h->vt_tiles; a.in = x; a.in_ll = 0; a.in_scale = h->s_in; a.out_scale = nullptr;
     a.out = w.t; a.out_ll = nullptr; a.out_lds = 1;
     a.M = (int)h->r; a.N = (int)h->d_in; a.n_steps = (int)n_steps(h->d_in); a.in_dtype = h->x_dtype; a.out_dtype = NQ_F32;
-    a.rb0 = 0; a.n_rb = (int)n_rowblocks(h->r); a.wl = wl_for(a.n_rb);
+    a.rb0 = 0; a.n_rb = (int)n_rowblocks(h->r); a.wl = wl_for(a.n_rb); a.pl = 0;
     ExecTask& b = p.t[1];
     b.tiles = h->u_tiles; b.in = nullptr; b.in_ll = 2; b.in_scale = h->s_mid; b.out_scale = unscaled ? nullptr : h->s_out;
     b.out = y; b.out_ll = nullptr; b.out_lds = 0;
     b.M = (int)h->d_out; b.N = (int)h->r; b.n_steps = (int)n_steps(h->r); b.in_dtype = NQ_F32; b.out_dtype = h->y_dtype;
-    b.rb0 = 0; b.n_rb = (int)n_rowblocks(h->d_out); b.wl = wl_for(b.n_rb);
+    b.rb0 = 0; b.n_rb = (int)n_rowblocks(h->d_out); b.wl = wl_for(b.n_rb); b.pl = 0;
     const int bq_bytes = (int)std::max(n_steps(h->d_in), n_steps(h->r)) * (int)kBqStepBytes;
-    const size_t lds_bytes = (size_t)bq_bytes + (size_t)kExecWaves * kExecEpiInts * 4 + 32 + (size_t)round_up(h->r, 16) * 4;
+    const size_t lds_bytes = (size_t)bq_bytes + (size_t)kExecWaves * kExecEpiInts * 4 + kExecWordBytes + (size_t)round_up(h->r, 16) * 4;
     if (!attr_set) {
         NQ_HIP(hipFuncSetAttribute((const void*)exec_small_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
         attr_set = true;
@@ -737,7 +827,7 @@ extern "C" int nq_exec_create(nq_exec* out, const nq_handle* hs, const void* con
         max_steps = std::max(max_steps, (int)std::max(n_steps(d_in[i]), n_steps(r[i])));
     }
     e->bq_bytes = max_steps * (int)kBqStepBytes;
-    e->lds_bytes = (size_t)e->bq_bytes + (size_t)kExecWaves * kExecEpiInts * 4 + 32;
+    e->lds_bytes = (size_t)e->bq_bytes + (size_t)kExecWaves * kExecEpiInts * 4 + kExecWordBytes;
     hipError_t he = hipFuncSetAttribute((const void*)exec_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (he == hipSuccess)
         he = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)exec_kernel, kExecThreads, e->lds_bytes);
@@ -757,20 +847,21 @@ extern "C" int nq_exec_create(nq_exec* out, const nq_handle* hs, const void* con
     auto al = [](size_t v) { return (v + 255) / 256 * 256; };
     const size_t tasks_b = al(sizeof(ExecTask) * planned.size()), begin_b = al(sizeof(int) * begin.size()),
                  state_b = al(sizeof(ExecState));
-    size_t pairs = 0;
+    size_t words = 0;                                      // bytes of one copy
     std::vector<size_t> t_off(n), y_off(n);
     for (int i = 0; i < n; ++i) {
-        t_off[i] = pairs; pairs += al((size_t)hs[i]->r * 8);
-        y_off[i] = pairs; if (consumed[i]) pairs += al((size_t)hs[i]->d_out * 8);
+        t_off[i] = words; words += al((size_t)hs[i]->r * 4);
+        y_off[i] = words; if (consumed[i]) words += al((size_t)hs[i]->d_out * 4);
     }
-    const size_t total = tasks_b + begin_b + state_b + pairs;
+    e->copy_words = words / 4;
+    const size_t total = tasks_b + begin_b + state_b + 2 * words;
     he = hipMalloc(&e->alloc, total);
     if (he != hipSuccess) { delete e; return hip_fail(he, "hipMalloc(executor)", __FILE__, __LINE__); }
     char* c = (char*)e->alloc;
     e->tasks = (ExecTask*)c; c += tasks_b;
     e->task_begin = (int*)c; c += begin_b;
     e->state = (ExecState*)c; c += state_b;
-    char* pair_base = c;
+    char* const word_base = c;
     // the two stages of every layer
     std::vector<ExecTask> ops(2 * n);
     for (int i = 0; i < n; ++i) {
@@ -778,20 +869,20 @@ extern "C" int nq_exec_create(nq_exec* out, const nq_handle* hs, const void* con
         ExecTask& a = ops[2 * i];
         a = ExecTask{};
         a.tiles = h->vt_tiles;
-        a.in = src[i] >= 0 ? (const void*)(pair_base + y_off[src[i]]) : xs[i];
+        a.in = src[i] >= 0 ? (const void*)(word_base + y_off[src[i]]) : xs[i];
         a.in_ll = src[i] >= 0;
         a.in_scale = h->s_in; a.out_scale = nullptr;
         a.out = h->ws.t;                                   // (so that nq_binlr_read_intermediate sees it)
-        a.out_ll = (unsigned long long*)(pair_base + t_off[i]);
+        a.out_ll = (unsigned int*)(word_base + t_off[i]);
         a.M = (int)h->r; a.N = (int)h->d_in; a.n_steps = (int)n_steps(h->d_in);
         a.in_dtype = h->x_dtype; a.out_dtype = NQ_F32;
         ExecTask& b = ops[2 * i + 1];
         b = ExecTask{};
         b.tiles = h->u_tiles;
-        b.in = pair_base + t_off[i]; b.in_ll = 1;
+        b.in = word_base + t_off[i]; b.in_ll = 1;
         b.in_scale = h->s_mid; b.out_scale = h->s_out;
         b.out = ys[i];
-        b.out_ll = consumed[i] ? (unsigned long long*)(pair_base + y_off[i]) : nullptr;
+        b.out_ll = consumed[i] ? (unsigned int*)(word_base + y_off[i]) : nullptr;
         b.M = (int)h->d_out; b.N = (int)h->r; b.n_steps = (int)n_steps(h->r);
         b.in_dtype = NQ_F32; b.out_dtype = h->y_dtype;
     }
@@ -800,12 +891,15 @@ extern "C" int nq_exec_create(nq_exec* out, const nq_handle* hs, const void* con
         tasks[k] = ops[2 * planned[k].layer + planned[k].stage];
         tasks[k].rb0 = planned[k].rb0;
         tasks[k].n_rb = planned[k].n_rb;
+        tasks[k].p0 = planned[k].p0;
+        tasks[k].pl = planned[k].pl;
         int wl = 0;
         while ((1 << wl) < planned[k].W) ++wl;
         tasks[k].wl = wl;
     }
     ExecState st0{1u, 0u, 0, 0};
     he = hipMemset(e->alloc, 0, total);
+    if (he == hipSuccess) he = hipMemset(word_base, 0xff, 2 * words);      // kNotThere
     if (he == hipSuccess) he = hipMemcpy(e->tasks, tasks.data(), sizeof(ExecTask) * tasks.size(), hipMemcpyHostToDevice);
     if (he == hipSuccess) he = hipMemcpy(e->task_begin, begin.data(), sizeof(int) * begin.size(), hipMemcpyHostToDevice);
     if (he == hipSuccess) he = hipMemcpy(e->state, &st0, sizeof st0, hipMemcpyHostToDevice);
@@ -826,7 +920,7 @@ extern "C" int nq_exec_forward(nq_exec e, void* stream)
     const int us = opt(OPT_EXEC_SPIN_LIMIT_US);
     const unsigned long long ticks = us >= 0 ? (unsigned long long)us * 100ull : 200000000ull;
     hipLaunchKernelGGL(exec_kernel, dim3(e->n_wg), dim3(kExecThreads), e->lds_bytes, (hipStream_t)stream, e->tasks,
-                       e->task_begin, e->state, e->bq_bytes, ticks);
+                       e->task_begin, e->state, e->bq_bytes, e->copy_words, ticks);
     NQ_HIP(hipGetLastError());
     return NQ_OK;
 }

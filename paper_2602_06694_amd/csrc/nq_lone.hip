@@ -39,17 +39,6 @@ __host__ __device__ inline int lone_tok_bytes(int nst) { return nst * (int)kBqSt
 constexpr int lone_round(int nb, int pl) { return pl < 4 / nb ? pl : 4 / nb; }
 constexpr int lone_red_ints(int nb, int pl, int w) { return w * nb * lone_round(nb, pl) * kLonePlaneInts; }
 
-// 2^e, -126 <= e <= 127
-__device__ __forceinline__ float exp2_int(int e) { return __builtin_bit_cast(float, (e + 127) << 23); }
-// exponent of the quantisation step of a token whose largest magnitude has the bits `m` (0 for a token of zeros or with a non-finite value):
-// f 2^e with f in [0.5, 1) gives 2^(e - 22), at least the smallest normal number
-constexpr uint32_t kLoneMostBits = 0x7f61b1e6u;            // of 3.0e38: larger ones (infinities and NaNs among them) count as not finite
-__device__ __forceinline__ int step_exponent(uint32_t m)
-{
-    const int se = (int)(m >> 23) - 126 - 22;
-    return m != 0 && m <= kLoneMostBits ? (se < -126 ? -126 : se) : 0;
-}
-
 // What the units of a launch's tokens leave in LDS: the bits of their largest magnitude and the sum of their q
 struct LoneTokens {
     unsigned long long sum[8];
@@ -69,7 +58,7 @@ __device__ __forceinline__ QMeta lone_meta(const LoneTokens* lt, int tok)
     const uint32_t m = lt->max[tok];
     const float step = exp2_int(step_exponent(m));
     QMeta mt;
-    mt.two_step = m <= kLoneMostBits ? 2.0 * (double)step : (double)__builtin_nanf("");
+    mt.two_step = m <= kMostBits ? 2.0 * (double)step : (double)__builtin_nanf("");
     mt.neg_qs = -(double)(long long)lt->sum[tok] * (double)step;
     return mt;
 }
