@@ -300,206 +300,207 @@ __device__ __forceinline__ double readlane_f64(double v, int lane)
     return __hiloint2double(hi, lo);
 }
 
-// NB x NB block (NB = 64; every panel has an LDS buffer of its own, which a 128-wide block would not fit), (NB/4)^2 threads; a thread keeps one 4 x 4 sub-block of the matrix (a) and of the running
-// right-hand side of L X = I (b, starts as the identity) in registers: row group ty = lane mod NB/4, column group tx.
-// The column groups are dealt to the waves in turn (tx = wave + waves x (lane / (NB/4))), so that consecutive panels of
-// four columns belong to different waves, and the elimination is a pipeline over panels without workgroup barriers:
-//   * the wave that owns panel j + 1 applies panel j to that panel's columns only, factorises it on its own -- pivot and
-//     multipliers travel by lane reads, the square root and its reciprocal come from the hardware's reciprocal-square-root
-//     estimate refined by two coupled Newton steps and a residual correction (ten dependent operations; within an ulp
-//     or two) -- publishes the four scaled columns (zero at and above their pivot) and the reciprocal pivots in the
-//     panel's own LDS buffer, and raises the count of published panels;
-//   * every wave, for each panel in order: waits until it is published, lets the threads that hold rows of the panel
-//     finish those rows of X with the panel's 4 x 4 triangle and hand them to their column group by lane shuffles, and
-//     applies the rank-4 update to its blocks right of the panel (a) and below it (b).
-// So the chain of dependent operations per panel is "four columns of one wave" (about 2300 cycles), not that plus a whole
-// rank-4 update and a barrier (4700): the other waves' updates run beside the next panel's factorisation.
-// A wave waits only for panels with a smaller number than any it still has to publish, so the waits end; they also give
-// up after a fixed number of polls (status is then set and the results are meaningless, every thread still finishes).
+// One workgroup of four waves.  The 64 x 64 block and its inverse are kept in LDS as lower 16 x 16 tiles; four rounds of
+//   * waves 0 and 1 eliminate the diagonal tile's 16 columns, one lane per column and its 16 rows in registers.  Beside the tile (lanes 0 to 15)
+//     wave 0 carries the tiles below it, transposed (lanes 16 to 63: the panel comes out of the same row operations), wave 1 the identity
+//     (lanes 16 to 31: the tile's inverse).  A pivot is LDL^T's: what the next one waits for is a lane read, a reciprocal (the hardware's estimate
+//     and two Newton steps), a product and one multiply-add; row i of column j is the multiplier of a row and reaches all lanes as a scalar.  The 16
+//     square roots and their reciprocals follow together, one per lane, and scale rows and columns (within an ulp or two).
+//   * 16 x 16 x 16 products on the matrix cores: the next column of tiles at once, by three waves; the other tiles and the off-diagonal tiles of
+//     the inverse (X_kj = -X_kk sum_p L_kp X_pj) by waves 2 and 3 beside the next elimination.
+// Bound by the 64 dependent pivots.  KERNEL_TIMES
 // H (lower part) is overwritten by L; the block of Linv receives L^-1 with an exactly zero upper part.  A pivot that is
 // not > 0 sets *status (the results are then meaningless, every thread still finishes).
 // pre != nullptr: first  A <- A - P P^T  with P = pre [NB][NB] (leading dimension ldh): the block's own tile of the
 // trailing update of the block column before it, so that the update's other tiles can run beside this kernel's work.
-// lds: potrf_lds_bytes<NB>() bytes.
-template <int NB> constexpr size_t potrf_lds_bytes() { return (size_t)((NB / 4) * 4 * NB + (NB / 4) * 4) * sizeof(double) + 16; }
+// lds: kPotrfLdsBytes bytes.
+constexpr int kTilePitch = 17, kTileDoubles = 16 * kTilePitch;         // operand reads of all three forms are free of bank conflicts
+constexpr int kPitchP = kNB + 1;
+constexpr size_t kPotrfLdsBytes = 2 * 10 * kTileDoubles * sizeof(double);
 
-template <int NB>
 __device__ __forceinline__ void potrf_inv_body(double* H, int ldh, double* Linv, int ldi, int o, int* status, int prio, const double* pre,
                                                double* lds)
 {
     if (prio) __builtin_amdgcn_s_setprio(3);
-    static_assert(NB == 64, "one LDS buffer per panel: 32 KiB at NB = 64");
-    constexpr int G = NB / 4;                      // row groups of a column group = lanes they occupy; also the number of panels
-    constexpr int CGW = 64 / G;                    // column groups per wave
-    constexpr int NW = G / CGW;                    // waves
-    double (*const colL)[4][NB] = (double (*)[4][NB])lds;
-    double (*const dinv)[4] = (double (*)[4])(lds + G * 4 * NB);
-    int& published = *(int*)(lds + G * 4 * NB + G * 4);            // panels whose columns are in LDS
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int local = lane / G;                    // which of the wave's column groups
-    const int tx = wave + NW * local, ty = lane % G;
-    double a[4][4], b[4][4];
+    static_assert(kNB == 64 && kGemmThreads == 256, "four tiles a side, four waves");
+    static_assert(kNB * kPitchP * sizeof(double) <= kPotrfLdsBytes, "P is staged where the tiles go");
+    double* const A = lds;
+    double* const X = lds + 10 * kTileDoubles;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int g = lane >> 4, n = lane & 15;
+    auto tile = [](int i, int j) { return (i * (i + 1) / 2 + j) * kTileDoubles; };
+    {
+        v4d acc[3];
+        int ti[3], tj[3];
 #pragma unroll
-    for (int ii = 0; ii < 4; ++ii)
+        for (int u = 0; u < 3; ++u) {
+            const int t = wave + 4 * u;
+            ti[u] = t < 1 ? 0 : t < 3 ? 1 : t < 6 ? 2 : 3;
+            tj[u] = t - ti[u] * (ti[u] + 1) / 2;
+            if (t < 10)
 #pragma unroll
-        for (int cc = 0; cc < 4; ++cc) {
-            a[ii][cc] = H[(size_t)(o + 4 * ty + ii) * ldh + o + 4 * tx + cc];
-            b[ii][cc] = (4 * ty + ii == 4 * tx + cc) ? 1.0 : 0.0;
+                for (int v = 0; v < 4; ++v) acc[u][v] = H[(size_t)(o + 16 * ti[u] + 4 * v + g) * ldh + o + 16 * tj[u] + n];
         }
-    if (pre) {
-        // P transposed into LDS (where the panels will go): thread t brings 16 entries of row t mod NB
-        static_assert(NB * NB <= G * 4 * NB, "P fits the panel buffers");
-        double* const pT = lds;                    // [NB][NB]: pT[k][row]
-        {
-            const int row = threadIdx.x % NB, k0 = (threadIdx.x / NB) * (NB * NB / (G * G));
+        if (pre) {
+            const int row = threadIdx.x >> 2, k0 = (threadIdx.x & 3) * 16;
             const double* src = pre + (size_t)row * ldh + k0;
 #pragma unroll
-            for (int k = 0; k < NB * NB / (G * G); ++k) pT[(k0 + k) * NB + row] = src[k];
+            for (int k = 0; k < 16; ++k) lds[row * kPitchP + k0 + k] = src[k];
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < 3; ++u) {
+                if (wave + 4 * u < 10) {
+                    const double* const pi = lds + (16 * ti[u] + n) * kPitchP + g;
+                    const double* const pj = lds + (16 * tj[u] + n) * kPitchP + g;
+#pragma unroll
+                    for (int s = 0; s < kNB / 4; ++s) acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(-pi[4 * s], pj[4 * s], acc[u], 0, 0, 0);
+                }
+            }
+            __syncthreads();                       // everybody has read P: the tiles go where it was
         }
-        __syncthreads();
-#pragma unroll 4
-        for (int k = 0; k < NB; ++k) {
-            double pr[4], pc[4];
 #pragma unroll
-            for (int ii = 0; ii < 4; ++ii) pr[ii] = pT[k * NB + 4 * ty + ii];
+        for (int u = 0; u < 3; ++u)
+            if (wave + 4 * u < 10)
 #pragma unroll
-            for (int cc = 0; cc < 4; ++cc) pc[cc] = pT[k * NB + 4 * tx + cc];
-#pragma unroll
-            for (int ii = 0; ii < 4; ++ii)
-#pragma unroll
-                for (int cc = 0; cc < 4; ++cc) a[ii][cc] = fma(-pr[ii], pc[cc], a[ii][cc]);
-        }
-        __syncthreads();                           // everybody has read P: the buffers change hands
+                for (int v = 0; v < 4; ++v) A[tile(ti[u], tj[u]) + (4 * v + g) * kTilePitch + n] = acc[u][v];
     }
-    if (threadIdx.x == 0) published = 0;
     __syncthreads();
     bool bad = false;
 
-    // factorises panel jb (called by every lane of the wave that owns it) and publishes it
-    auto factor_panel = [&](int jb) {
-        const int src = G * (jb / NW) + jb;                // lane of the thread that holds the panel's diagonal block
-        const bool mine = tx == jb;
+    // what waves do on the matrix cores; the operands are read as [row n][depth 4 s + g], or, for an untransposed right factor, [depth][column n]
+    auto load_c = [&](const double* c) {
+        v4d acc;
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-            const int j = 4 * jb + jj;
-            const double piv = readlane_f64(a[jj][jj], src);
-            if (!(piv > 0.0)) bad = true;
-            const double y = __builtin_amdgcn_rsq(piv);
-            double g = piv * y, h = 0.5 * y;
-            double e = fma(-h, g, 0.5);
-            g = fma(g, e, g);
-            h = fma(h, e, h);
-            e = fma(-h, g, 0.5);
-            g = fma(g, e, g);
-            h = fma(h, e, h);
-            e = fma(-g, g, piv);
-            g = fma(e, h, g);
-            const double d = g, inv = 2.0 * h;
-            double l[4];
+        for (int v = 0; v < 4; ++v) acc[v] = c[(4 * v + g) * kTilePitch + n];
+        return acc;
+    };
+    auto store_c = [&](double* c, v4d acc) {
 #pragma unroll
-            for (int ii = 0; ii < 4; ++ii) {
-                const int row = 4 * ty + ii;
-                l[ii] = row > j ? a[ii][jj] * inv : 0.0;
-                if (mine && row >= j) a[ii][jj] = row == j ? d : l[ii];
-            }
+        for (int v = 0; v < 4; ++v) c[(4 * v + g) * kTilePitch + n] = acc[v];
+    };
+    auto sub_aat = [&](int i, int j, int kb) {     // A_ij -= P_i P_j^T
+        const double *pi = A + tile(i, kb) + n * kTilePitch + g, *pj = A + tile(j, kb) + n * kTilePitch + g;
+        v4d acc = load_c(A + tile(i, j));
 #pragma unroll
-            for (int cc = jj + 1; cc < 4; ++cc) {
-                const double lc = readlane_f64(a[cc][jj], src);       // L[4 jb + cc][j]
-                if (mine)
+        for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-pi[4 * s], pj[4 * s], acc, 0, 0, 0);
+        store_c(A + tile(i, j), acc);
+    };
+    auto sum_lx = [&](int k, int j) {              // X_kj <- sum over j <= p < k of L_kp X_pj
+        v4d acc = {0.0, 0.0, 0.0, 0.0};
+        for (int p = j; p < k; ++p) {
+            const double *l = A + tile(k, p) + n * kTilePitch + g, *x = X + tile(p, j) + g * kTilePitch + n;
 #pragma unroll
-                    for (int ii = 0; ii < 4; ++ii) a[ii][cc] = fma(-l[ii], lc, a[ii][cc]);
-            }
-            if (mine)
-#pragma unroll
-                for (int ii = 0; ii < 4; ++ii) colL[jb][jj][4 * ty + ii] = l[ii];
-            if (lane == src) dinv[jb][jj] = inv;
+            for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(l[4 * s], x[4 * s * kTilePitch], acc, 0, 0, 0);
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");         // the columns are in LDS before the count says so
-        if (lane == 0) __hip_atomic_store(&published, jb + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        store_c(X + tile(k, j), acc);
+    };
+    auto finish_x = [&](int k, int j) {            // X_kj <- -X_kk X_kj
+        const double *l = X + tile(k, k) + n * kTilePitch + g, *x = X + tile(k, j) + g * kTilePitch + n;
+        v4d acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-l[4 * s], x[4 * s * kTilePitch], acc, 0, 0, 0);
+        store_c(X + tile(k, j), acc);
     };
 
-    if (wave == 0) factor_panel(0);
-    for (int jb = 0; jb < G; ++jb) {
-        // wait for panel jb (its owner published it one round ago, or just now)
-        for (int spins = 0; __hip_atomic_load(&published, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) <= jb; ++spins) {
-            if (spins > (1 << 22)) {
-                bad = true;
-                break;
+    for (int kb = 0; kb < 4; ++kb) {
+        double v[16], root = 0.0;
+        const int below = kb + g;                  // the panel tile of wave 0's lanes
+        if (wave < 2) {
+            const double* const d = A + tile(kb, kb);
+            const double* const p = A + tile(g > 0 && below < 4 ? below : kb, kb) + n * kTilePitch;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const double dv = d[i >= n ? i * kTilePitch + n : n * kTilePitch + i];
+                const double pv = wave == 0 ? p[i] : (i == n ? 1.0 : 0.0);
+                v[i] = g == 0 ? dv : pv;
             }
-            __builtin_amdgcn_s_sleep(1);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        // the next panel's owner brings that panel's columns up to date first, factorises and publishes them
-        if (jb + 1 < G && wave == (jb + 1) % NW) {
-            if (tx == jb + 1) {
+            double mine = 1.0;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
+            for (int j = 0; j < 16; ++j) {
+                const double piv = readlane_f64(v[j], j);
+                if (!(piv > 0.0)) bad = true;
+                double y = __builtin_amdgcn_rcp(piv);
+                double e = fma(-piv, y, 1.0);
+                y = fma(y, e, y);
+                e = fma(-piv, y, 1.0);
+                y = fma(y, e, y);
+                mine = lane == j ? piv : mine;
+                const double r = lane > j ? -v[j] * y : 0.0;           // (columns that are done stay)
 #pragma unroll
-                    for (int cc = 0; cc < 4; ++cc) {
-                        const double lc = colL[jb][q][4 * tx + cc];
-#pragma unroll
-                        for (int ii = 0; ii < 4; ++ii) a[ii][cc] = fma(-colL[jb][q][4 * ty + ii], lc, a[ii][cc]);
-                    }
-                }
+                for (int i = j + 1; i < 16; ++i) v[i] = fma(readlane_f64(v[i], j), r, v[i]);
             }
-            factor_panel(jb + 1);
+            double y = __builtin_amdgcn_rsq(mine);
+            double h = 0.5 * y;
+            root = mine * y;
+            double e = fma(-h, root, 0.5);
+            root = fma(root, e, root);
+            h = fma(h, e, h);
+            e = fma(-h, root, 0.5);
+            root = fma(root, e, root);
+            h = fma(h, e, h);
+            e = fma(-root, root, mine);
+            root = fma(e, h, root);
+            y = 2.0 * h;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const double row_scale = readlane_f64(y, i);
+                v[i] *= g == 0 ? y : row_scale;
+            }
+            if (wave == 0 && g > 0 && below < 4) {
+                double* const to = A + tile(below, kb) + n * kTilePitch;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) to[i] = v[i];
+            }
+            if (wave == 1 && g == 1) {
+                double* const to = X + tile(kb, kb) + n;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) to[i * kTilePitch] = v[i];
+            }
         }
-        if (ty == jb) {                                    // rows 4 jb .. 4 jb + 3 of X
+        __syncthreads();                           // the panel and X_kk
+        if (wave == 0 && g == 0) {
+            double* const to = A + tile(kb, kb) + n;
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int cc = 0; cc < 4; ++cc) {
-                    double acc = b[q][cc];
-#pragma unroll
-                    for (int p = 0; p < q; ++p) acc = fma(-colL[jb][p][4 * jb + q], b[p][cc], acc);
-                    b[q][cc] = acc * dinv[jb][q];
-                }
+            for (int i = 0; i < 16; ++i)
+                if (i >= n) to[i * kTilePitch] = i == n ? root : v[i];
         }
-        // the rank-4 update: everything it reads is requested first (LDS reads and lane shuffles have a long latency and
-        // there is one wave per SIMD to hide it), then the 128 multiply-adds
-        double lr[4][4], lc[4][4], xs[4][4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-#pragma unroll
-            for (int ii = 0; ii < 4; ++ii) lr[q][ii] = colL[jb][q][4 * ty + ii];
-#pragma unroll
-            for (int cc = 0; cc < 4; ++cc) lc[q][cc] = colL[jb][q][4 * tx + cc];
-#pragma unroll
-            for (int cc = 0; cc < 4; ++cc) xs[q][cc] = __shfl(b[q][cc], (lane & (64 - G)) | jb);
-        }
-        if (tx > jb + 1) {                                 // (column group jb + 1 was brought up to date above)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int cc = 0; cc < 4; ++cc)
-#pragma unroll
-                    for (int ii = 0; ii < 4; ++ii) a[ii][cc] = fma(-lr[q][ii], lc[q][cc], a[ii][cc]);
-        }
-        if (ty > jb) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int ii = 0; ii < 4; ++ii)
-#pragma unroll
-                    for (int cc = 0; cc < 4; ++cc) b[ii][cc] = fma(-lr[q][ii], xs[q][cc], b[ii][cc]);
+        if (kb == 3) break;
+        if (wave < 3 - kb) sub_aat(kb + 1 + wave, kb + 1, kb);
+        __syncthreads();                           // the next column of tiles
+        if (wave == 2) {
+            if (kb > 0) finish_x(kb, 0);
+            sum_lx(kb + 1, 0);
+            if (kb == 0) sub_aat(3, 3, 0);
+        } else if (wave == 3) {
+            if (kb == 0) {
+                sub_aat(2, 2, 0);
+                sub_aat(3, 2, 0);
+            } else if (kb == 1) {
+                sub_aat(3, 3, 1);
+                sum_lx(2, 1);
+            } else {
+                finish_x(2, 1);
+                sum_lx(3, 1);
+                sum_lx(3, 2);
+            }
         }
     }
-#pragma unroll
-    for (int ii = 0; ii < 4; ++ii)
-#pragma unroll
-        for (int cc = 0; cc < 4; ++cc) {
-            const int i = 4 * ty + ii, c = 4 * tx + cc;
-            if (c <= i) H[(size_t)(o + i) * ldh + o + c] = a[ii][cc];
-            Linv[(size_t)(o + i) * ldi + o + c] = (c <= i) ? b[ii][cc] : 0.0;
-        }
+    if (wave < 3) finish_x(3, wave);
+    __syncthreads();
+    // (a wave stores whole rows)
+#pragma unroll 4
+    for (int q = 0; q < kNB / 4; ++q) {
+        const int i = 4 * q + wave, at = tile(i >> 4, g) + (i & 15) * kTilePitch + n;
+        if (lane <= i) H[(size_t)(o + i) * ldh + o + lane] = A[at];
+        Linv[(size_t)(o + i) * ldi + o + lane] = lane <= i ? X[g <= (i >> 4) ? at : 0] : 0.0;
+    }
     if (bad) *status = 1;
 }
 
-template <int NB>
-__global__ __launch_bounds__((NB / 4) * (NB / 4)) void potrf_inv_kernel(double* H, int ldh, double* Linv, int ldi, int o, int* status, int prio)
+__global__ __launch_bounds__(kGemmThreads) void potrf_inv_kernel(double* H, int ldh, double* Linv, int ldi, int o, int* status, int prio)
 {
     extern __shared__ __align__(16) double lds_dyn[];
-    potrf_inv_body<NB>(H, ldh, Linv, ldi, o, status, prio, nullptr, lds_dyn);
+    potrf_inv_body(H, ldh, Linv, ldi, o, status, prio, nullptr, lds_dyn);
 }
 
 // One launch per block column k of the factorisation, after the diagonal block k has been factorised and inverted
@@ -532,7 +533,7 @@ struct StepArgs {
 
 __global__ __launch_bounds__(kGemmThreads, 2) void chol_step_kernel(StepArgs a)
 {
-    static_assert(kGemmThreads == (kNB / 4) * (kNB / 4) && kNB == 64, "both bodies are written for 256 threads and 64-wide blocks");
+    static_assert(kGemmThreads == 256 && kNB == 64, "both bodies are written for 256 threads and 64-wide blocks");
     extern __shared__ __align__(16) double lds_dyn[];
     const int ld = a.ld;
     const double* const X = a.Linv + (size_t)a.o * ld + a.o;
@@ -544,7 +545,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void chol_step_kernel(StepArgs a)
         g.prio = a.prio;
         dgemm_body<64, 64, 4, false, true>(g, 0, 0, 0, lds_dyn);
         __syncthreads();                           // P's first rows are in memory (and LDS is free again)
-        potrf_inv_body<kNB>(a.H, ld, a.Linv, ld, a.o + kNB, a.status, a.prio, L21, lds_dyn);
+        potrf_inv_body(a.H, ld, a.Linv, ld, a.o + kNB, a.status, a.prio, L21, lds_dyn);
         return;
     }
     if ((int)blockIdx.y > a.tiles) {
@@ -889,16 +890,15 @@ static int svid(const AdmmWs& ws, const double* P, int rows, int r, int iters, i
 static int factor_and_invert(const AdmmWs& ws, hipStream_t s, int prio)
 {
     const int rp = ws.rp, rr = ws.rr, q = rr / kNB;
-    static_assert(potrf_lds_bytes<kNB>() <= gemm_lds_bytes<64, 64>(), "the step kernel's LDS is the product's");
     const bool fused = !opt_flag(OPT_ADMM_NO_FUSED_STEP);
-    constexpr size_t potrf_lds = potrf_lds_bytes<kNB>();
-    constexpr size_t step_lds = gemm_lds_bytes<64, 64>();
+    constexpr size_t potrf_lds = kPotrfLdsBytes;
+    constexpr size_t step_lds = std::max(kPotrfLdsBytes, gemm_lds_bytes<64, 64>());
     // where the blocks of L below the diagonal end up: a matrix of their own with the one-launch step (Hinv's buffer,
     // free until the last product below), in place of A21 with separate launches
     const double* const Lb = fused ? ws.Hinv : ws.H;
     // the inverse carried along by the step launches, in two of the buffers of the Gram product's parts (ranks that have them)
     const bool carried = fused && ws.G[0] != nullptr;
-    hipLaunchKernelGGL(potrf_inv_kernel<kNB>, dim3(1), dim3((kNB / 4) * (kNB / 4)), potrf_lds, s, ws.H, rp, ws.Linv, rp, 0, ws.status, prio);
+    hipLaunchKernelGGL(potrf_inv_kernel, dim3(1), dim3(kGemmThreads), potrf_lds, s, ws.H, rp, ws.Linv, rp, 0, ws.status, prio);
     for (int k = 0; k + 1 < q; ++k) {
         const int o = k * kNB;
         const int rem = rr - o - kNB;
@@ -922,7 +922,7 @@ static int factor_and_invert(const AdmmWs& ws, hipStream_t s, int prio)
         u.prio = prio;
         rc = launch_gemm(u, 1, s);
         if (rc != NQ_OK) return rc;
-        hipLaunchKernelGGL(potrf_inv_kernel<kNB>, dim3(1), dim3((kNB / 4) * (kNB / 4)), potrf_lds, s, ws.H, rp, ws.Linv, rp, o + kNB, ws.status, prio);
+        hipLaunchKernelGGL(potrf_inv_kernel, dim3(1), dim3(kGemmThreads), potrf_lds, s, ws.H, rp, ws.Linv, rp, o + kNB, ws.status, prio);
     }
     NQ_HIP(hipGetLastError());
     if (carried && q > 1) {
