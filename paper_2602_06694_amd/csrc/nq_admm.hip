@@ -7,6 +7,7 @@
 #include <math.h>
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 namespace nq {
 
@@ -216,10 +217,17 @@ __device__ __forceinline__ void dgemm_body(const GemmArgs& g, const int bx, cons
 }
 
 template <int BM, int BN, int PF, bool TA, bool TB>
-__global__ __launch_bounds__(kGemmThreads, 2) void dgemm_kernel(GemmArgs g)
+__global__ __launch_bounds__(kGemmThreads, BM == 128 && BN == 128 && PF > 1 ? 1 : 2) void dgemm_kernel(GemmArgs g)
 {
     extern __shared__ __align__(16) double lds_dyn[];
-    dgemm_body<BM, BN, PF, TA, TB>(g, (int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, lds_dyn);
+    int bx = (int)blockIdx.x, by = (int)blockIdx.y;
+    if (BM == BN && g.lower_only && g.M == g.N) {   // tile t of those on and below the diagonal, row by row
+        by = (int)((__builtin_sqrtf(8.0f * (float)bx + 1.0f) - 1.0f) * 0.5f);
+        while (by * (by + 1) / 2 > bx) --by;
+        while ((by + 1) * (by + 2) / 2 <= bx) ++by;
+        bx -= by * (by + 1) / 2;
+    }
+    dgemm_body<BM, BN, PF, TA, TB>(g, bx, by, (int)blockIdx.z, lds_dyn);
 }
 
 template <int BM, int BN> constexpr size_t gemm_lds_bytes()
@@ -244,6 +252,9 @@ template <int BM, int BN, int PF, bool TA, bool TB> static int launch_gemm_varia
     });
     NQ_HIP(attr_err);
     dim3 grid((g.N + BN - 1) / BN, (g.M + BM - 1) / BM, batch);
+    // Of a square matrix' lower half only the tiles that do work are launched: of a grid of all of them XCD k (workgroup mod 8) would get block
+    // column k, and with it 8 - k of 8 tiles (Gram product of r = 1024, 4096 rows: 191 -> 135 us)
+    if (BM == BN && g.lower_only && g.M == g.N) grid = dim3(grid.x * (grid.x + 1) / 2, 1, batch);
     const size_t pad = (size_t)(g.lds_pad < 0 ? 0 : g.lds_pad > kGemmMaxLdsPad ? kGemmMaxLdsPad : g.lds_pad);
     hipLaunchKernelGGL((dgemm_kernel<BM, BN, PF, TA, TB>), grid, dim3(kGemmThreads), lds + pad, s, g);
     NQ_HIP(hipGetLastError());
@@ -269,8 +280,11 @@ static int launch_gemm(const GemmArgs& g, int batch, hipStream_t s)
     };
     int choice = g.tile ? g.tile : opt_or(OPT_DGEMM_TILE, 0);
     if (choice < 1 || choice > 3) choice = tiles(128, 128) >= 512 ? 1 : tiles(128, 64) >= 384 ? 2 : 3;
-    if (choice == 1) return launch_gemm_tile<128, 128, 1>(g, batch, s);
-    if (choice == 2) return launch_gemm_tile<128, 64, 1>(g, batch, s);
+    // Tiles of look-ahead: three for the product that runs with one workgroup per CU, whose waves have nobody to hide their loads (845 -> 800 us beside
+    // the factorisation; four take registers that the factorisation's workgroups need), two for the 128 x 64 tile (4096 x 1024 x 1024
+    // 206 -> 177 us; three 203).
+    if (choice == 1) return g.lds_pad > 0 ? launch_gemm_tile<128, 128, 3>(g, batch, s) : launch_gemm_tile<128, 128, 1>(g, batch, s);
+    if (choice == 2) return launch_gemm_tile<128, 64, 2>(g, batch, s);
     return launch_gemm_tile<64, 64, 4>(g, batch, s);
 }
 
@@ -293,37 +307,51 @@ __host__ __device__ static GemmArgs gemm_args(int ta, int tb, int M, int N, int 
 // ============================================================================================
 constexpr int kNB = 64;        // width of a block column of the factorisation (an earlier 128-wide diagonal-block kernel measured slower than two of 64)
 
-__device__ __forceinline__ double readlane_f64(double v, int lane)
+// the value of lane J of every 16-lane row, in all lanes of the row
+template <int J>
+__device__ __forceinline__ double row_bcast(double v)
 {
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x150 + J, 0xf, 0xf, true);      // row_newbcast
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x150 + J, 0xf, 0xf, true);
     return __hiloint2double(hi, lo);
+}
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void static_for(F f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<N, I + 1>(f);
+    }
 }
 
 // One workgroup of four waves.  The 64 x 64 block and its inverse are kept in LDS as lower 16 x 16 tiles; four rounds of
-//   * waves 0 and 1 eliminate the diagonal tile's 16 columns, one lane per column and its 16 rows in registers.  Beside the tile (lanes 0 to 15)
+//   * waves 0 and 1 eliminate the diagonal tile's 16 columns, one lane per column and its 16 rows in registers.  Beside the tile
 //     wave 0 carries the tiles below it, transposed (lanes 16 to 63: the panel comes out of the same row operations), wave 1 the identity
-//     (lanes 16 to 31: the tile's inverse).  A pivot is LDL^T's: what the next one waits for is a lane read, a reciprocal (the hardware's estimate
-//     and two Newton steps), a product and one multiply-add; row i of column j is the multiplier of a row and reaches all lanes as a scalar.  The 16
+//     (lanes 16 to 31: the tile's inverse).  A pivot is LDL^T's: what the next one waits for is a move between lanes, a reciprocal (the hardware's estimate
+//     and two Newton steps), a product and one multiply-add; the multipliers reach the lanes of a 16-lane row by data-parallel moves from a copy of the tile that every row keeps.  The 16
 //     square roots and their reciprocals follow together, one per lane, and scale rows and columns (within an ulp or two).
 //   * 16 x 16 x 16 products on the matrix cores: the next column of tiles at once, by three waves; the other tiles and the off-diagonal tiles of
 //     the inverse (X_kj = -X_kk sum_p L_kp X_pj) by waves 2 and 3 beside the next elimination.
-// Bound by the 64 dependent pivots.  KERNEL_TIMES
+// Bound by the 64 dependent pivots: of 18 us on its own, 3.5 are loads, 4 x 1.7 eliminations (2.4 with lane reads into
+// scalars, whose use by the next instruction waits), 3 x 1 the products and barriers between them.
 // H (lower part) is overwritten by L; the block of Linv receives L^-1 with an exactly zero upper part.  A pivot that is
 // not > 0 sets *status (the results are then meaningless, every thread still finishes).
-// pre != nullptr: first  A <- A - P P^T  with P = pre [NB][NB] (leading dimension ldh): the block's own tile of the
-// trailing update of the block column before it, so that the update's other tiles can run beside this kernel's work.
+// A21 != nullptr: the block is the first tile of the trailing update of the block column before it, whose inverted diagonal block is X11: first
+//  P = A21 X11^T,  which goes to L21 (both with leading dimension ldh), and  A <- A - P P^T,  so that the update's other tiles can run beside this
+// kernel's work.  Everything is requested at once and P stays in LDS (with the tiles' bodies below: step launch 24 -> 19 us on its own, 58 -> 52 beside the product with W).
 // lds: kPotrfLdsBytes bytes.
+// registers for three waves per SIMD (168), so that such a workgroup fits beside one of the product with W (328): otherwise it waits 800 us for its end
+constexpr int kStepWavesPerEu = 3;
 constexpr int kTilePitch = 17, kTileDoubles = 16 * kTilePitch;         // operand reads of all three forms are free of bank conflicts
 constexpr int kPitchP = kNB + 1;
-constexpr size_t kPotrfLdsBytes = 2 * 10 * kTileDoubles * sizeof(double);
+constexpr size_t kPotrfLdsBytes = (kNB * kPitchP + 10 * kTileDoubles) * sizeof(double);      // P and X11; then the block's tiles and its inverse's
 
-__device__ __forceinline__ void potrf_inv_body(double* H, int ldh, double* Linv, int ldi, int o, int* status, int prio, const double* pre,
-                                               double* lds)
+__device__ __forceinline__ void potrf_inv_body(double* H, int ldh, double* Linv, int ldi, int o, int* status, int prio, const double* A21,
+                                               const double* X11, double* L21, double* lds)
 {
     if (prio) __builtin_amdgcn_s_setprio(3);
     static_assert(kNB == 64 && kGemmThreads == 256, "four tiles a side, four waves");
-    static_assert(kNB * kPitchP * sizeof(double) <= kPotrfLdsBytes, "P is staged where the tiles go");
+    static_assert(20 * kTileDoubles * sizeof(double) <= kPotrfLdsBytes, "the tiles go where P and X11 were");
     double* const A = lds;
     double* const X = lds + 10 * kTileDoubles;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -341,21 +369,57 @@ __device__ __forceinline__ void potrf_inv_body(double* H, int ldh, double* Linv,
 #pragma unroll
                 for (int v = 0; v < 4; ++v) acc[u][v] = H[(size_t)(o + 16 * ti[u] + 4 * v + g) * ldh + o + 16 * tj[u] + n];
         }
-        if (pre) {
-            const int row = threadIdx.x >> 2, k0 = (threadIdx.x & 3) * 16;
-            const double* src = pre + (size_t)row * ldh + k0;
+        if (A21) {
+            double* const P = lds;                 // [64][65]: rows of A21, then of P; a wave's 16 rows are its own
+            double* const XT = lds + kNB * kPitchP;
+            {
+                const int row = threadIdx.x >> 2, c = threadIdx.x & 3;
+                const double *pa = A21 + (size_t)row * ldh + 16 * c, *px = X11 + (size_t)row * ldi + 16 * c;
+                double av[16], xv[16];
 #pragma unroll
-            for (int k = 0; k < 16; ++k) lds[row * kPitchP + k0 + k] = src[k];
-            __syncthreads();
+                for (int k = 0; k < 16; ++k) av[k] = pa[k];
+                if (c <= row >> 4)
 #pragma unroll
-            for (int u = 0; u < 3; ++u) {
-                if (wave + 4 * u < 10) {
-                    const double* const pi = lds + (16 * ti[u] + n) * kPitchP + g;
-                    const double* const pj = lds + (16 * tj[u] + n) * kPitchP + g;
+                    for (int k = 0; k < 16; ++k) xv[k] = px[k];
 #pragma unroll
-                    for (int s = 0; s < kNB / 4; ++s) acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(-pi[4 * s], pj[4 * s], acc[u], 0, 0, 0);
-                }
+                for (int k = 0; k < 16; ++k) P[row * kPitchP + 16 * c + k] = av[k];
+                if (c <= row >> 4)
+#pragma unroll
+                    for (int k = 0; k < 16; ++k) XT[tile(row >> 4, c) + (row & 15) * kTilePitch + k] = xv[k];
             }
+            __syncthreads();
+            double a[16];
+#pragma unroll
+            for (int s = 0; s < 16; ++s) a[s] = P[(16 * wave + n) * kPitchP + 4 * s + g];
+            v4d p[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) p[j] = v4d{0.0, 0.0, 0.0, 0.0};
+            // (depth outside: four independent sums at a time; X11 is lower triangular)
+#pragma unroll
+            for (int s = 0; s < 16; ++s)
+#pragma unroll
+                for (int j = s / 4; j < 4; ++j)
+                    p[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], XT[tile(j, s / 4) + n * kTilePitch + 4 * (s % 4) + g], p[j], 0, 0, 0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    P[(16 * wave + 4 * v + g) * kPitchP + 16 * j + n] = p[j][v];
+                    L21[(size_t)(16 * wave + 4 * v + g) * ldh + 16 * j + n] = p[j][v];
+                }
+            __syncthreads();
+            v4d sum[3];
+#pragma unroll
+            for (int u = 0; u < 3; ++u) sum[u] = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int s = 0; s < kNB / 4; ++s)
+#pragma unroll
+                for (int u = 0; u < 3; ++u)
+                    if (wave + 4 * u < 10)
+                        sum[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(P[(16 * ti[u] + n) * kPitchP + g + 4 * s], P[(16 * tj[u] + n) * kPitchP + g + 4 * s], sum[u], 0, 0, 0);
+#pragma unroll
+            for (int u = 0; u < 3; ++u)
+                if (wave + 4 * u < 10) acc[u] -= sum[u];
             __syncthreads();                       // everybody has read P: the tiles go where it was
         }
 #pragma unroll
@@ -403,32 +467,35 @@ __device__ __forceinline__ void potrf_inv_body(double* H, int ldh, double* Linv,
     };
 
     for (int kb = 0; kb < 4; ++kb) {
-        double v[16], root = 0.0;
+        // d: the diagonal tile's column n, in all four 16-lane rows of the wave (a value of lane j of a row reaches its other lanes by a
+        // data-parallel move); v: the lane's other column
+        double d[16], v[16], root = 0.0;
         const int below = kb + g;                  // the panel tile of wave 0's lanes
         if (wave < 2) {
-            const double* const d = A + tile(kb, kb);
+            const double* const t = A + tile(kb, kb);
             const double* const p = A + tile(g > 0 && below < 4 ? below : kb, kb) + n * kTilePitch;
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const double dv = d[i >= n ? i * kTilePitch + n : n * kTilePitch + i];
-                const double pv = wave == 0 ? p[i] : (i == n ? 1.0 : 0.0);
-                v[i] = g == 0 ? dv : pv;
+                d[i] = t[i >= n ? i * kTilePitch + n : n * kTilePitch + i];
+                v[i] = wave == 0 ? p[i] : (i == n ? 1.0 : 0.0);
             }
             double mine = 1.0;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const double piv = readlane_f64(v[j], j);
+            static_for<16>([&](auto jc) {
+                constexpr int j = decltype(jc)::value;
+                const double piv = row_bcast<j>(d[j]);
                 if (!(piv > 0.0)) bad = true;
                 double y = __builtin_amdgcn_rcp(piv);
-                double e = fma(-piv, y, 1.0);
-                y = fma(y, e, y);
-                e = fma(-piv, y, 1.0);
-                y = fma(y, e, y);
-                mine = lane == j ? piv : mine;
-                const double r = lane > j ? -v[j] * y : 0.0;           // (columns that are done stay)
+                y = fma(y, fma(-piv, y, 1.0), y);
+                y = fma(y, fma(-piv, y, 1.0), y);
+                mine = n == j ? piv : mine;
+                const double rd = n > j ? -d[j] * y : 0.0, rv = -v[j] * y;     // (columns that are done stay)
 #pragma unroll
-                for (int i = j + 1; i < 16; ++i) v[i] = fma(readlane_f64(v[i], j), r, v[i]);
-            }
+                for (int i = j + 1; i < 16; ++i) {
+                    const double m = row_bcast<j>(d[i]);
+                    d[i] = fma(m, rd, d[i]);
+                    v[i] = fma(m, rv, v[i]);
+                }
+            });
             double y = __builtin_amdgcn_rsq(mine);
             double h = 0.5 * y;
             root = mine * y;
@@ -441,11 +508,11 @@ __device__ __forceinline__ void potrf_inv_body(double* H, int ldh, double* Linv,
             e = fma(-root, root, mine);
             root = fma(e, h, root);
             y = 2.0 * h;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const double row_scale = readlane_f64(y, i);
-                v[i] *= g == 0 ? y : row_scale;
-            }
+            static_for<16>([&](auto ic) {
+                constexpr int i = decltype(ic)::value;
+                v[i] *= row_bcast<i>(y);
+                d[i] *= y;
+            });
             if (wave == 0 && g > 0 && below < 4) {
                 double* const to = A + tile(below, kb) + n * kTilePitch;
 #pragma unroll
@@ -462,7 +529,7 @@ __device__ __forceinline__ void potrf_inv_body(double* H, int ldh, double* Linv,
             double* const to = A + tile(kb, kb) + n;
 #pragma unroll
             for (int i = 0; i < 16; ++i)
-                if (i >= n) to[i * kTilePitch] = i == n ? root : v[i];
+                if (i >= n) to[i * kTilePitch] = i == n ? root : d[i];
         }
         if (kb == 3) break;
         if (wave < 3 - kb) sub_aat(kb + 1 + wave, kb + 1, kb);
@@ -497,10 +564,10 @@ __device__ __forceinline__ void potrf_inv_body(double* H, int ldh, double* Linv,
     if (bad) *status = 1;
 }
 
-__global__ __launch_bounds__(kGemmThreads) void potrf_inv_kernel(double* H, int ldh, double* Linv, int ldi, int o, int* status, int prio)
+__global__ __launch_bounds__(kGemmThreads, kStepWavesPerEu) void potrf_inv_kernel(double* H, int ldh, double* Linv, int ldi, int o, int* status, int prio)
 {
     extern __shared__ __align__(16) double lds_dyn[];
-    potrf_inv_body(H, ldh, Linv, ldi, o, status, prio, nullptr, lds_dyn);
+    potrf_inv_body(H, ldh, Linv, ldi, o, status, prio, nullptr, nullptr, nullptr, lds_dyn);
 }
 
 // One launch per block column k of the factorisation, after the diagonal block k has been factorised and inverted
@@ -510,13 +577,15 @@ __global__ __launch_bounds__(kGemmThreads) void potrf_inv_kernel(double* H, int 
 //     block k + 1 in its registers and factorises it (the long pole of the launch);
 //   * workgroup (j, i + 1), j <= i, (i, j) != (0, 0), owns tile (i, j) of the trailing matrix: it forms the rows P_i and
 //     P_j of the panel for itself (three 64 x 64 x 64 products instead of one; they cost little next to the
-//     factorisation beside them), keeps them in its own piece of a scratch matrix -- or, tile (i, 0), stores P_i as
-//     block i of L -- and subtracts  P_i P_j^T  from its tile.
+//     factorisation beside them) and subtracts  P_i P_j^T  from its tile; tile (i, 0) stores P_i as block i of L.
 //   * with `S`, workgroup (i, tiles + 1 + j), j <= k, carries the inverse along: it forms P_i and the block
 //     X_kj = -X_kk S_kj  of row k of L^-1 for itself (the first of the column also stores it) and adds  P_i X_kj  to  S_ij,
 //     the sum of L_ip X_pj over p < i that row k + 1 + i of L^-1 waits for.  As many products as a tile of the trailing matrix takes, in the same
 //     launch, while the diagonal block is factorised: what is left of the inversion afterwards is one row of blocks, where
 //     inverting by halves took eight launches, 185 us for r = 1024.
+// The last two run as one body (step_tile_body): everything is requested at once, a wave owns 16 rows of each product, whose first operand needs only its
+// own rows, and what the other waves need of the first products passes through LDS.  (As three general products through memory, each waiting for its
+// first tiles, they took 24 us, longer than the factorisation.)
 // The panel is NOT written over A21: other workgroups still read A21, so L's blocks below the diagonal go to a matrix
 // of their own (Lb; the diagonal blocks of L stay in H).  A step is then one launch of the factorisation's length
 // where the panel, the update and the factorisation as launches of their own take three.
@@ -524,14 +593,106 @@ struct StepArgs {
     double* H;          // [..][ld]: A21, A22 (read and updated in place), diagonal blocks of L
     double* Lb;         // [..][ld]: L below the diagonal
     double* Linv;       // [..][ld]: the inverted diagonal blocks
-    double* scratch;    // tiles (tiles + 1) / 2 pieces of 2 x 64 x 64
     int ld, o, prio;    // o: first row / column of block column k
     int* status;
     int tiles;          // row blocks below block column k
-    double *S, *xscratch;       // [..][ld] sums behind the rows of L^-1 still to come, and tiles x (k + 1) pieces of 2 x 64 x 64; or nullptr
+    double* S;          // [..][ld] sums behind the rows of L^-1 still to come, or nullptr
 };
 
-__global__ __launch_bounds__(kGemmThreads, 2) void chol_step_kernel(StepArgs a)
+constexpr size_t kStepLdsBytes = 2 * kNB * kPitchP * sizeof(double);       // two blocks; beside the product with W (88 KiB) that still fits a CU
+
+// INV = false: C -= P_i P_j^T with P_j from B = A21_j (the same as P_i where B is nullptr); INV = true: C (+)= P_i Y with Y = -X11 B, B = S_kj, or Y = X11
+// (B nullptr).  P_i = A21_i X11^T.  store_p: where P_i goes, store_y: Y (leading dimension ld), or nullptr.
+template <bool INV>
+__device__ __forceinline__ void step_tile_body(const double* A21i, const double* X11, const double* B, double* C, bool add, double* store_p, double* store_y, int ld,
+                                               double* lds)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int g = lane >> 4, n = lane & 15;
+    auto tile = [](int i, int j) { return (i * (i + 1) / 2 + j) * kTileDoubles; };
+    double* const R0 = lds;                        // X11's lower tiles, then P_i
+    double* const R1 = lds + kNB * kPitchP;        // P_j, or S_kj and then Y
+    const int row = threadIdx.x >> 2, c4 = threadIdx.x & 3;
+    double x[16], b[16], ai[16];
+    v4d acc[4], pi[4], q[4];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) x[k] = X11[(size_t)row * ld + 16 * c4 + k];
+#pragma unroll
+    for (int s = 0; s < 16; ++s) ai[s] = A21i[(size_t)(16 * wave + n) * ld + 4 * s + g];
+    if (B)
+#pragma unroll
+        for (int s = 0; s < 16; ++s) b[s] = INV ? B[(size_t)row * ld + 16 * c4 + s] : B[(size_t)(16 * wave + n) * ld + 4 * s + g];
+    if (c4 <= row >> 4)
+#pragma unroll
+        for (int k = 0; k < 16; ++k) R0[tile(row >> 4, c4) + (row & 15) * kTilePitch + k] = x[k];
+    if (INV)
+#pragma unroll
+        for (int k = 0; k < 16; ++k) R1[row * kPitchP + 16 * c4 + k] = B ? b[k] : x[k];
+    __syncthreads();
+    auto times_xt = [&](const double (&a)[16], v4d (&p)[4]) {      // 16 rows times X11^T, which is upper triangular
+#pragma unroll
+        for (int c = 0; c < 4; ++c) p[c] = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int s = 0; s < 16; ++s)
+#pragma unroll
+            for (int c = s / 4; c < 4; ++c)
+                p[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], R0[tile(c, s / 4) + n * kTilePitch + 4 * (s % 4) + g], p[c], 0, 0, 0);
+    };
+    auto to_rows = [&](double* r, const v4d (&p)[4]) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) r[(16 * wave + 4 * v + g) * kPitchP + 16 * c + n] = p[c][v];
+    };
+    auto to_memory = [&](double* m, const v4d (&p)[4]) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) m[(size_t)(16 * wave + 4 * v + g) * ld + 16 * c + n] = p[c][v];
+    };
+    times_xt(ai, pi);
+    if (!INV) {
+        if (B) {
+            times_xt(b, q);
+            to_rows(R1, q);
+        } else to_rows(R1, pi);
+    } else if (B) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) q[c] = v4d{0.0, 0.0, 0.0, 0.0};
+        for (int t = 0; t <= wave; ++t)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const double xs = -R0[tile(wave, t) + n * kTilePitch + 4 * s + g];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) q[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(xs, R1[(16 * t + 4 * s + g) * kPitchP + 16 * c + n], q[c], 0, 0, 0);
+            }
+    }
+    __syncthreads();                               // X11 (and S_kj) have been read
+    to_rows(R0, pi);
+    if (INV && B) to_rows(R1, q);
+    if (store_p) to_memory(store_p, pi);
+    if (INV && store_y) to_memory(store_y, q);
+    v4d old[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        acc[c] = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int v = 0; v < 4; ++v) old[c][v] = add ? C[(size_t)(16 * wave + 4 * v + g) * ld + 16 * c + n] : 0.0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < 16; ++s) {
+        const double p = R0[(16 * wave + n) * kPitchP + 4 * s + g];
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(p, INV ? R1[(4 * s + g) * kPitchP + 16 * c + n] : R1[(16 * c + n) * kPitchP + 4 * s + g], acc[c], 0, 0, 0);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[c] = INV ? old[c] + acc[c] : old[c] - acc[c];
+    to_memory(C, acc);
+}
+
+__global__ __launch_bounds__(kGemmThreads, kStepWavesPerEu) void chol_step_kernel(StepArgs a)
 {
     static_assert(kGemmThreads == 256 && kNB == 64, "both bodies are written for 256 threads and 64-wide blocks");
     extern __shared__ __align__(16) double lds_dyn[];
@@ -541,55 +702,20 @@ __global__ __launch_bounds__(kGemmThreads, 2) void chol_step_kernel(StepArgs a)
     double* const L21 = a.Lb + (size_t)(a.o + kNB) * ld + a.o;
     if (blockIdx.y == 0) {
         if (blockIdx.x != 0) return;
-        GemmArgs g = gemm_args(0, 1, kNB, kNB, kNB, 1.0, A21, ld, X, ld, 0.0, nullptr, 0, L21, ld);
-        g.prio = a.prio;
-        dgemm_body<64, 64, 4, false, true>(g, 0, 0, 0, lds_dyn);
-        __syncthreads();                           // P's first rows are in memory (and LDS is free again)
-        potrf_inv_body(a.H, ld, a.Linv, ld, a.o + kNB, a.status, a.prio, L21, lds_dyn);
+        potrf_inv_body(a.H, ld, a.Linv, ld, a.o + kNB, a.status, a.prio, A21, X, L21, lds_dyn);
         return;
     }
+    if (a.prio) __builtin_amdgcn_s_setprio(2);
     if ((int)blockIdx.y > a.tiles) {
         const int i = (int)blockIdx.x, j = (int)blockIdx.y - a.tiles - 1, k = a.o / kNB;
-        double* const Pi = a.xscratch + (size_t)(i * (k + 1) + j) * (2 * kNB * kNB);
-        GemmArgs g = gemm_args(0, 1, kNB, kNB, kNB, 1.0, A21 + (size_t)i * kNB * ld, ld, X, ld, 0.0, nullptr, 0, Pi, kNB);
-        g.prio = a.prio;
-        dgemm_body<64, 64, 4, false, true>(g, 0, 0, 0, lds_dyn);
-        const double* Xkj = X;                     // j = k: the diagonal block itself
-        int ldx = ld;
-        if (j < k) {
-            double* const dst = i == 0 ? a.Linv + (size_t)a.o * ld + j * kNB : Pi + kNB * kNB;
-            ldx = i == 0 ? ld : kNB;
-            g = gemm_args(0, 0, kNB, kNB, kNB, -1.0, X, ld, a.S + (size_t)a.o * ld + j * kNB, ld, 0.0, nullptr, 0, dst, ldx);
-            g.prio = a.prio;
-            __syncthreads();
-            dgemm_body<64, 64, 4, false, false>(g, 0, 0, 0, lds_dyn);
-            Xkj = dst;
-        }
-        __syncthreads();                           // this workgroup's P_i and X_kj are in memory
-        double* const Sij = a.S + (size_t)(a.o + (i + 1) * kNB) * ld + j * kNB;
-        g = gemm_args(0, 0, kNB, kNB, kNB, 1.0, Pi, kNB, Xkj, ldx, j == k ? 0.0 : 1.0, Sij, ld, Sij, ld);
-        g.prio = a.prio;
-        dgemm_body<64, 64, 4, false, false>(g, 0, 0, 0, lds_dyn);
+        step_tile_body<true>(A21 + (size_t)i * kNB * ld, X, j < k ? a.S + (size_t)a.o * ld + j * kNB : nullptr, a.S + (size_t)(a.o + (i + 1) * kNB) * ld + j * kNB, j < k,
+                             nullptr, i == 0 && j < k ? a.Linv + (size_t)a.o * ld + j * kNB : nullptr, ld, lds_dyn);
         return;
     }
     const int i = (int)blockIdx.y - 1, j = (int)blockIdx.x;
     if (j > i || i == 0) return;                   // above the diagonal; (0, 0) is the diagonal block's
-    double* const mine = a.scratch + (size_t)(i * (i + 1) / 2 + j) * (2 * kNB * kNB);
-    double* const Pi = j == 0 ? L21 + (size_t)i * kNB * ld : mine;
-    const int ldi = j == 0 ? ld : kNB;
-    double* const Pj = j == i ? Pi : mine + kNB * kNB;
-    const int ldj = j == i ? ldi : kNB;
-    GemmArgs g = gemm_args(0, 1, kNB, kNB, kNB, 1.0, A21 + (size_t)i * kNB * ld, ld, X, ld, 0.0, nullptr, 0, Pi, ldi);
-    g.prio = a.prio;
-    dgemm_body<64, 64, 4, false, true>(g, 0, 0, 0, lds_dyn);
-    if (j != i) {
-        g = gemm_args(0, 1, kNB, kNB, kNB, 1.0, A21 + (size_t)j * kNB * ld, ld, X, ld, 0.0, nullptr, 0, Pj, kNB);
-        dgemm_body<64, 64, 4, false, true>(g, 0, 0, 0, lds_dyn);
-    }
-    __syncthreads();                               // this workgroup's P_i, P_j are in memory
-    double* const Cij = a.H + (size_t)(a.o + kNB + i * kNB) * ld + a.o + kNB + j * kNB;
-    g = gemm_args(0, 1, kNB, kNB, kNB, -1.0, Pi, ldi, Pj, ldj, 1.0, Cij, ld, Cij, ld);
-    dgemm_body<64, 64, 4, false, true>(g, 0, 0, 0, lds_dyn);
+    step_tile_body<false>(A21 + (size_t)i * kNB * ld, X, j < i ? A21 + (size_t)j * kNB * ld : nullptr, a.H + (size_t)(a.o + kNB + i * kNB) * ld + a.o + kNB + j * kNB, true,
+                          j == 0 ? L21 + (size_t)i * kNB * ld : nullptr, nullptr, ld, lds_dyn);
 }
 
 // A += B, both [rows][cols] without padding (the two halves of a product whose reduction was split).
@@ -892,11 +1018,15 @@ static int factor_and_invert(const AdmmWs& ws, hipStream_t s, int prio)
     const int rp = ws.rp, rr = ws.rr, q = rr / kNB;
     const bool fused = !opt_flag(OPT_ADMM_NO_FUSED_STEP);
     constexpr size_t potrf_lds = kPotrfLdsBytes;
-    constexpr size_t step_lds = std::max(kPotrfLdsBytes, gemm_lds_bytes<64, 64>());
+    constexpr size_t step_lds = std::max(kPotrfLdsBytes, kStepLdsBytes);
+    static std::once_flag once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(once, [] { attr_err = hipFuncSetAttribute((const void*)chol_step_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)step_lds); });
+    NQ_HIP(attr_err);
     // where the blocks of L below the diagonal end up: a matrix of their own with the one-launch step (Hinv's buffer,
     // free until the last product below), in place of A21 with separate launches
     const double* const Lb = fused ? ws.Hinv : ws.H;
-    // the inverse carried along by the step launches, in two of the buffers of the Gram product's parts (ranks that have them)
+    // the inverse carried along by the step launches, in one of the buffers of the Gram product's parts (ranks that have them)
     const bool carried = fused && ws.G[0] != nullptr;
     hipLaunchKernelGGL(potrf_inv_kernel, dim3(1), dim3(kGemmThreads), potrf_lds, s, ws.H, rp, ws.Linv, rp, 0, ws.status, prio);
     for (int k = 0; k + 1 < q; ++k) {
@@ -904,7 +1034,7 @@ static int factor_and_invert(const AdmmWs& ws, hipStream_t s, int prio)
         const int rem = rr - o - kNB;
         if (fused) {
             const int tiles = rem / kNB;
-            StepArgs sa{ws.H, ws.Hinv, ws.Linv, ws.T, rp, o, prio, ws.status, tiles, carried ? ws.G[0] : nullptr, carried ? ws.G[1] : nullptr};
+            StepArgs sa{ws.H, ws.Hinv, ws.Linv, rp, o, prio, ws.status, tiles, carried ? ws.G[0] : nullptr};
             hipLaunchKernelGGL(chol_step_kernel, dim3(tiles, tiles + 1 + (carried ? k + 1 : 0)), dim3(kGemmThreads), step_lds, s, sa);
             continue;
         }
@@ -957,13 +1087,13 @@ static int factor_and_invert(const AdmmWs& ws, hipStream_t s, int prio)
     return launch_gemm(h, 1, s);
 }
 
-// A second stream and three events, created once.  Two things run beside the factorisation, which is a chain of small
+// Two more streams and four events, created once.  Two things run beside the factorisation, which is a chain of small
 // launches that leaves most of the chip idle: the product with W (it does not depend on the factorisation), and the
 // SVID of the factor just updated (nothing needs its result before that factor's NEXT update, a whole factor step later;
 // the other factor's update only reads the new factor itself).
 struct SideStream {
-    hipStream_t stream = nullptr;
-    hipEvent_t fork = nullptr, join = nullptr, updated = nullptr;
+    hipStream_t stream = nullptr, svid = nullptr;
+    hipEvent_t fork = nullptr, join = nullptr, updated = nullptr, svid_done = nullptr;
     hipError_t err = hipSuccess;
 };
 
@@ -973,6 +1103,8 @@ static SideStream& side_stream()
     static std::once_flag once;
     std::call_once(once, [] {
         ss.err = hipStreamCreateWithFlags(&ss.stream, hipStreamNonBlocking);
+        if (ss.err == hipSuccess) ss.err = hipStreamCreateWithFlags(&ss.svid, hipStreamNonBlocking);
+        if (ss.err == hipSuccess) ss.err = hipEventCreateWithFlags(&ss.svid_done, hipEventDisableTiming);
         if (ss.err == hipSuccess) ss.err = hipEventCreateWithFlags(&ss.fork, hipEventDisableTiming);
         if (ss.err == hipSuccess) ss.err = hipEventCreateWithFlags(&ss.join, hipEventDisableTiming);
         if (ss.err == hipSuccess) ss.err = hipEventCreateWithFlags(&ss.updated, hipEventDisableTiming);
@@ -995,8 +1127,11 @@ static int issue_pending_svid(const AdmmWs& ws, PendingSvid& pend, int r, int po
     if (!pend.valid) return NQ_OK;
     pend.valid = false;
     SideStream& ss = side_stream();
-    NQ_HIP(hipStreamWaitEvent(ss.stream, ss.updated, 0));
-    return svid(ws, ws.P, pend.rows, r, power_iters, 0, pend.Z, pend.Lambda, pend.D, ss.stream);
+    NQ_HIP(hipStreamWaitEvent(ss.svid, ss.updated, 0));
+    const int rc = svid(ws, ws.P, pend.rows, r, power_iters, 0, pend.Z, pend.Lambda, pend.D, ss.svid);
+    if (rc != NQ_OK) return rc;
+    NQ_HIP(hipEventRecord(ss.svid_done, ss.svid));
+    return NQ_OK;
 }
 
 static int factor_step(const AdmmWs& ws, const double* W, int w_trans, int ldw, int rows, int cols, int r, const double* O, double rho, double lam,
@@ -1035,7 +1170,9 @@ static int factor_step(const AdmmWs& ws, const double* W, int w_trans, int ldw, 
         hipLaunchKernelGGL(add_parts_kernel, dim3((r + 255) / 256, r), dim3(256), 0, s, ws.H, gp, ws.rp, r);
         NQ_HIP(hipGetLastError());
     }
-    rc = issue_pending_svid(ws, pend, r, power_iters);        // the other factor's SVID, to the side stream
+    // (the product below needs this factor's own SVID, the one before the one that is issued here)
+    if (overlap) NQ_HIP(hipStreamWaitEvent(ss.stream, ss.svid_done, 0));
+    rc = issue_pending_svid(ws, pend, r, power_iters);        // the other factor's SVID, to its stream
     if (rc != NQ_OK) return rc;
     // RHS = op(W) O + rho (Z - Lambda), on the side stream (behind the SVID that produced Z and Lambda).  It is let go
     // once the Gram matrix is done: both fill the chip, so side by side neither gains, and the product would only keep
@@ -1065,8 +1202,9 @@ static int factor_step(const AdmmWs& ws, const double* W, int w_trans, int ldw, 
     }
     if (roomy) {
         gr.tile = 1;
-        gr.lds_pad = 16384;
+        gr.lds_pad = 8704;                         // (2 x 80.5 KiB do not fit; what is left takes a workgroup of the factorisation, 65 KiB)
     }
+    if (overlap && w_parts > 1) NQ_HIP(hipStreamWaitEvent(rs, ss.svid_done, 0));      // the second half goes where that SVID reads P
     rc = launch_gemm(gr, w_parts, rs);
     if (rc != NQ_OK) return rc;
     if (w_parts > 1) {
@@ -1076,7 +1214,10 @@ static int factor_step(const AdmmWs& ws, const double* W, int w_trans, int ldw, 
     if (overlap) NQ_HIP(hipEventRecord(ss.join, ss.stream));
     rc = factor_and_invert(ws, s, prio);
     if (rc != NQ_OK) return rc;
-    if (overlap) NQ_HIP(hipStreamWaitEvent(s, ss.join, 0));
+    if (overlap) {
+        NQ_HIP(hipStreamWaitEvent(s, ss.join, 0));
+        NQ_HIP(hipStreamWaitEvent(s, ss.svid_done, 0));       // P is about to be written
+    }
     // X = RHS H^-1,  P = X + Lambda
     GemmArgs gx = gemm_args(0, 0, rows, r, r, 1.0, ws.RHS, r, ws.Hinv, ws.rp, 0.0, nullptr, 0, X, r);
     gx.E = Lambda;
@@ -1085,9 +1226,9 @@ static int factor_step(const AdmmWs& ws, const double* W, int w_trans, int ldw, 
     rc = launch_gemm(gx, 1, s);
     if (rc != NQ_OK) return rc;
     if (!overlap || opt_flag(OPT_ADMM_INLINE_SVID)) return svid(ws, ws.P, rows, r, power_iters, 0, Z, Lambda, D, s);
-    // The SVID goes to the side stream.  What keeps the buffers apart: the side stream runs SVID (reads P; writes Z,
-    // Lambda, D), then the next factor step's product (second half into P, result into RHS), in that order; the
-    // caller's stream writes P and reads RHS and Lambda only after it has waited for that product.
+    // The SVID goes to a stream of its own, so that the next product does not wait for it (four iterations of 4096 x 4096 r = 1024 10.72 -> 10.27 ms).  What keeps
+    // the buffers apart: SVIDs follow one another (they read P; write Z, Lambda, D and the vectors); a factor's product waits for that factor's last SVID, which wrote
+    // its D; the caller's stream writes P, reads RHS and Lambda only after it has waited for that product and for the SVID that still reads P.
     // (Its launches are issued by the next factor step, or by the caller after the last one.)
     NQ_HIP(hipEventRecord(ss.updated, s));
     pend.valid = true;
@@ -1168,8 +1309,7 @@ extern "C" int nq_lb_admm(const double* W, int64_t n, int64_t m, int64_t r, cons
     if (rc != NQ_OK) return rc;
     if (n_iters > 0 && !opt_flag(OPT_ADMM_NO_OVERLAP)) {      // the last SVID may still be running on the side stream
         SideStream& ss = side_stream();
-        NQ_HIP(hipEventRecord(ss.join, ss.stream));
-        NQ_HIP(hipStreamWaitEvent(s, ss.join, 0));
+        NQ_HIP(hipStreamWaitEvent(s, ss.svid_done, 0));
     }
     int status = 0;
     NQ_HIP(hipMemcpyAsync(&status, ws.status, sizeof(int), hipMemcpyDeviceToHost, s));
