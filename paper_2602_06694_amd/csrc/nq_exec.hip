@@ -16,11 +16,11 @@
 //    copy clears it in the other, which nobody reads before the next launch.  The number lives in device memory and is
 //    advanced by the last workgroup to leave, so a replay of a captured launch takes the copies in turn too.
 //
-// What bounds it: 256 dependent phases of 4.65 us per token of a 7B-shaped stack.  Of those the hand-over is 1.5 to 3.3 us (6 to 10 for 28672
+// What bounds it: 256 dependent phases of 4.35 us per token of a 7B-shaped stack.  Of those the hand-over is 1.5 to 3.3 us (6 to 10 for 28672
 // values): a store, half a polling period and a read past the L2, and the contention of up to 128 workgroups that all read the whole
 // input.  Then 0.5 to 0.9 us for the fixed point, 0.7 to 1.7 for the products, 0.5 for adding them up and storing.  As pairs of value and launch number, read 16
 // elements per lane (a line per 16-byte request), hand-overs took 2.4 to 5 us (17 of 28672 values); whole row blocks per workgroup,
-// loops over the longest input's groups without an exit and addresses spilled from phase to phase cost another 1.5 us: 1818 -> 1190 us per token.
+// loops over the longest input's groups without an exit and addresses spilled from phase to phase cost another 1.5 us: 1818 -> 1110 us per token.
 //  - every wait is bounded by a wall-clock limit; a workgroup that gives up sets an error word
 //    and leaves, the others see the word (or run into their own limit) and leave too: the grid
 //    always drains.  (They clear the other copies of what their tasks would have stored first.)
@@ -215,18 +215,20 @@ __device__ __forceinline__ void exec_body(const ExecTask* __restrict__ tasks, in
         int t = tid;
         asm volatile("" : "+v"(t));                         // (addresses are formed here, not kept from task to task, which spills them)
         if (!SMALL && op.in_ll == 1) {
-            // Read until everything is there (or the time is up: gave_up).  Inputs of one group per thread are asked for outright; of longer ones the wave polls the first word of its share only (one
+            // Read until everything is there (or the time is up: gave_up).  First the wave polls the last word of its first groups only (one
             // transaction per round, all lanes the same address), so that workgroups waiting far ahead of the running phase leave the
-            // memory system alone; then it asks for the groups that are not complete yet, all of them before any is looked at.
+            // memory system alone; then it asks for the groups that are not complete yet, all of them before any is looked at.  (7B-shaped chain: 1110 us;
+            // polling the first word 1121, four times as rarely 1143, without polling where a thread has one group 1168.)
             // (Device-scope loads; beyond the array the buffer returns zeros.)
+            const int last = wave0 * 4 + 255 < op.N ? wave0 * 4 + 255 : op.N - 1;
             const int mine = wave0 < n_groups ? (n_groups - wave0 + kExecThreads - 1) / kExecThreads : 0;
             unsigned int todo = (1u << mine) - 1u;
             unsigned int spins = 0;
-            bool waiting = op.N > 4 * kExecThreads && wave0 * 4 < op.N;
+            bool waiting = wave0 * 4 < op.N;
             while (todo) {
                 asm volatile("" ::: "memory");              // another workgroup writes this memory: load again every time
                 if (waiting) {
-                    waiting = __builtin_amdgcn_raw_buffer_load_b32(rsrc, wave0 * 16, 0, 16) == kNotThere;
+                    waiting = __builtin_amdgcn_raw_buffer_load_b32(rsrc, last * 4, 0, 16) == kNotThere;
                     if (waiting) {
                         ++spins;
                         // (the clock and the error word are looked at every 16th round, and on the first: a limit of zero gives up at once)
@@ -235,7 +237,7 @@ __device__ __forceinline__ void exec_body(const ExecTask* __restrict__ tasks, in
                             gave_up = 1;
                             break;
                         }
-                        __builtin_amdgcn_s_sleep(8);
+                        __builtin_amdgcn_s_sleep(2);
                         continue;
                     }
                 }
@@ -261,6 +263,7 @@ __device__ __forceinline__ void exec_body(const ExecTask* __restrict__ tasks, in
                     gave_up = 1;
                     break;
                 }
+                // (inputs of one group per thread, which most workgroups of the grid wait for: a pause; 1264 us without, 1119 with one for all)
                 if (todo && op.N <= 4 * kExecThreads) __builtin_amdgcn_s_sleep(2);
             }
         } else {
@@ -617,8 +620,8 @@ static void plan_tasks(const int64_t* d_out, const int64_t* d_in, const int64_t*
             // Where every row block finds a workgroup of its own, all of its waves take it; where the row blocks are few, each is dealt out by bit
             // planes to 8 / pl workgroups, which stream the same tiles and finish 16 pl rows each: on one XCD, whose L2 they share.
             // (Workgroup w runs on XCD w mod 8; `slot`: the next workgroup of each.)  At most every second workgroup of the grid, because all
-            // of them read the whole input (up to all / three quarters / half / a quarter of it, with time stamps taken: 7B-shaped chain 1462 / 1342 / 1339 /
-            // 1400 us, 70B-shaped block 72 / 71 / 69 / 83).
+            // of them read the whole input (up to three quarters / half / a quarter of it: 7B-shaped chain 1126 / 1110 / 1206 us, a 70B-shaped
+            // block 62 / 61 / 88).
             int pl = 1, all = 0;
             for (int v : nrb) all += v;
             const int slots = n_wg / 8, deep = (all + 7) / 8;         // workgroups, row blocks per XCD
