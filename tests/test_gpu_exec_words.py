@@ -4,6 +4,8 @@ import numpy as np
 import pytest
 
 from paper_2602_06694_amd import binding as nq
+from paper_2602_06694_amd import synth
+from gpu_util import Layer
 from test_gpu_exec import SMALL, Chain
 
 pytestmark = pytest.mark.gpu
@@ -75,3 +77,41 @@ def test_row_blocks_dealt_out(shapes):
         same(c, ref)
     nq.nq_exec_destroy(e)
     c.close()
+
+
+@pytest.mark.parametrize("scale", [np.inf, -np.inf, np.nan])
+def test_a_scale_that_is_not_finite_stays_in_its_own_layer(scale):
+    """Layers whose inputs end inside a step, read from outside and handed over, run by the workgroups that ran a layer with a scale that
+    is not finite further up its own, longer input: a lane past the end of an input has no scale, whatever the task before left in it."""
+    import torch
+    # level 0 has the scale; every later level one layer that reads x and one that reads the level before
+    shapes = [(1024, 512, 1024, -1)]
+    for k in range(1, 9):
+        shapes += [(257 + k, 250 + 5 * k, 1024, -1), (300, 257 + k - 1 if k > 1 else 250, 1024, 2 * k - 3 if k > 1 else -1)]
+    layers, xs, ys, level = [], [], [], []
+    for i, (d_out, d_in, r, src) in enumerate(shapes):
+        lin = synth.LinearShape("t", d_out, d_in, r)
+        s_in = synth.gen_scales(d_in, 13300 + i)
+        if i == 0:
+            s_in[500] = np.float16(scale)
+        data = synth.LayerData(lin, synth.gen_sign_words(d_out, r, 13320 + i), synth.gen_sign_words(d_in, r, 13340 + i), synth.gen_scales(d_out, 13360 + i), s_in)
+        layers.append(Layer(d_out, d_in, r, "f32", data=data))
+        xs.append(torch.from_numpy(synth.gen_x(1, d_in, 13380 + i, "f32")).cuda() if src < 0 else ys[src])
+        ys.append(torch.full((1, d_out), float("nan"), device="cuda"))
+        level.append((i + 1) // 2)
+    for L, x, y in zip(layers, xs, ys):
+        nq.nq_binlr_forward(L.h, x, y, 1)
+    torch.cuda.synchronize()
+    ref = [y.clone() for y in ys]
+    assert torch.isnan(ref[0]).all() and not any(torch.isnan(y).any() for y in ref[1:])
+    e = nq.nq_exec_create([L.h for L in layers], xs, ys, level)
+    for _ in range(3):
+        for y in ys:
+            y.fill_(7.0)
+        nq.nq_exec_forward(e)
+        nq.nq_exec_status(e)
+        wrong = [shapes[i] for i, (a, b) in enumerate(zip(ys, ref)) if i and not torch.equal(a, b)]
+        assert not wrong and torch.isnan(ys[0]).all(), wrong
+    nq.nq_exec_destroy(e)
+    for L in layers:
+        L.close()
