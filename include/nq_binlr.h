@@ -294,10 +294,16 @@ int nq_exec_status(nq_exec e, void* stream);
 /* Debug: workgroups of the launch, tasks in their lists, LDS bytes per workgroup.  Pointers may be NULL. */
 int nq_exec_info(nq_exec e, int* n_workgroups, int* n_tasks, size_t* lds_bytes);
 int nq_exec_destroy(nq_exec e);
-/* Host only (no GPU needed): the task lists nq_exec_create would build for layers of these shapes on
- * n_workgroups workgroups.  tasks_out: host, capacity x 7 int32 -- workgroup, phase (2 level + stage),
- * layer, stage (0: t = V^T x', 1: y = U t), first row block, row blocks, waves per row block -- in
- * phase order; NULL to only count.  *n_tasks = number of tasks. */
+/* Host only (no GPU needed): the task lists nq_exec_create builds for layers of these shapes on
+ * n_workgroups workgroups.  tasks_out: host, capacity x 9 int32 -- workgroup, phase (2 level + stage),
+ * layer, stage (0: t = V^T x', 1: y = U t), first row block, row blocks, waves per row block, first bit plane, bit
+ * planes (16 rows of the one row block each; 0: whole row blocks) -- in phase order; NULL to only count.
+ * *n_tasks = number of tasks. */
+int nq_exec_plan_lists(const int64_t* d_out, const int64_t* d_in, const int64_t* r, const int* level_of, int n,
+                       int n_workgroups, int32_t* tasks_out, int capacity, int* n_tasks);
+/* The same in records of 7 int32, without the planes: a row block that is dealt out to several workgroups by bit
+ * planes is listed once, with the workgroup that has its first ones (which row blocks a phase has and where they begin;
+ * not every task that runs). */
 int nq_exec_plan_tasks(const int64_t* d_out, const int64_t* d_in, const int64_t* r, const int* level_of, int n,
                        int n_workgroups, int32_t* tasks_out, int capacity, int* n_tasks);
 

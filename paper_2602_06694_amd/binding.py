@@ -84,7 +84,8 @@ def lib() -> ctypes.CDLL:
         L.nq_exec_status.argtypes = [vp, vp]; L.nq_exec_status.restype = ci
         L.nq_exec_info.argtypes = [vp, ctypes.POINTER(ci), ctypes.POINTER(ci), ctypes.POINTER(ctypes.c_size_t)]; L.nq_exec_info.restype = ci
         L.nq_exec_destroy.argtypes = [vp]; L.nq_exec_destroy.restype = ci
-        L.nq_exec_plan_tasks.argtypes = [vp, vp, vp, vp, ci, ci, vp, ci, ctypes.POINTER(ci)]; L.nq_exec_plan_tasks.restype = ci
+        for f in (L.nq_exec_plan_tasks, L.nq_exec_plan_lists):
+            f.argtypes = [vp, vp, vp, vp, ci, ci, vp, ci, ctypes.POINTER(ci)]; f.restype = ci
         L.nq_debug_slab_count.argtypes = []; L.nq_debug_slab_count.restype = ci
         dbl, szp = ctypes.c_double, ctypes.POINTER(ctypes.c_size_t)
         L.nq_lb_admm_workspace_bytes.argtypes = [i64, i64, i64, szp]; L.nq_lb_admm_workspace_bytes.restype = ci
@@ -343,19 +344,29 @@ def nq_exec_destroy(e: Optional[int]) -> None:
     _check(lib().nq_exec_destroy(e))
 
 
-def nq_exec_plan_tasks(d_out: Sequence[int], d_in: Sequence[int], r: Sequence[int], level_of: Sequence[int],
-                       n_workgroups: int) -> np.ndarray:
-    """Host only: int32 [n_tasks, 7] = workgroup, phase, layer, stage, first row block, row blocks, waves per row block."""
+def _exec_plan(call, words: int, d_out, d_in, r, level_of, n_workgroups: int) -> np.ndarray:
     n = len(d_out)
     a = [np.ascontiguousarray(v, dtype=np.int64) for v in (d_out, d_in, r)]
     lv = np.ascontiguousarray(level_of, dtype=np.int32)
     cnt = ctypes.c_int()
-    _check(lib().nq_exec_plan_tasks(_np_ptr(a[0]), _np_ptr(a[1]), _np_ptr(a[2]), _np_ptr(lv), n, n_workgroups, None, 0,
-                                    ctypes.byref(cnt)))
-    out = np.zeros((cnt.value, 7), dtype=np.int32)
-    _check(lib().nq_exec_plan_tasks(_np_ptr(a[0]), _np_ptr(a[1]), _np_ptr(a[2]), _np_ptr(lv), n, n_workgroups, _np_ptr(out),
-                                    cnt.value, ctypes.byref(cnt)))
+    _check(call(_np_ptr(a[0]), _np_ptr(a[1]), _np_ptr(a[2]), _np_ptr(lv), n, n_workgroups, None, 0, ctypes.byref(cnt)))
+    out = np.zeros((cnt.value, words), dtype=np.int32)
+    _check(call(_np_ptr(a[0]), _np_ptr(a[1]), _np_ptr(a[2]), _np_ptr(lv), n, n_workgroups, _np_ptr(out), cnt.value, ctypes.byref(cnt)))
     return out
+
+
+def nq_exec_plan_lists(d_out: Sequence[int], d_in: Sequence[int], r: Sequence[int], level_of: Sequence[int],
+                       n_workgroups: int) -> np.ndarray:
+    """Host only: int32 [n_tasks, 9] = workgroup, phase, layer, stage, first row block, row blocks, waves per row block, first bit plane,
+    bit planes (0: whole row blocks): the lists that nq_exec_create builds."""
+    return _exec_plan(lib().nq_exec_plan_lists, 9, d_out, d_in, r, level_of, n_workgroups)
+
+
+def nq_exec_plan_tasks(d_out: Sequence[int], d_in: Sequence[int], r: Sequence[int], level_of: Sequence[int],
+                       n_workgroups: int) -> np.ndarray:
+    """Host only: int32 [n_tasks, 7] = workgroup, phase, layer, stage, first row block, row blocks, waves per row block; a row block
+    that is dealt out by bit planes once."""
+    return _exec_plan(lib().nq_exec_plan_tasks, 7, d_out, d_in, r, level_of, n_workgroups)
 
 
 def nq_plan_forward(p: int, stream=None) -> None:

@@ -32,6 +32,7 @@
 // nq_binlr_forward calls.
 #include <algorithm>
 #include <mutex>
+#include <string>
 #include <type_traits>
 #include <vector>
 
@@ -690,28 +691,43 @@ static int exec_fail(int code, const char* msg)
     return code;
 }
 
-extern "C" int nq_exec_plan_tasks(const int64_t* d_out, const int64_t* d_in, const int64_t* r, const int* level_of, int n,
-                                  int n_workgroups, int32_t* tasks_out, int capacity, int* n_tasks)
+// the lists as records of 9 (with the bit planes) or of 7 words
+static int plan_records(const char* who, const int64_t* d_out, const int64_t* d_in, const int64_t* r, const int* level_of, int n,
+                        int n_workgroups, int record, int32_t* tasks_out, int capacity, int* n_tasks)
 {
-    if (!d_out || !d_in || !r || !level_of || !n_tasks) return exec_fail(NQ_E_NULL, "nq_exec_plan_tasks: NULL pointer");
-    if (n < 1 || n_workgroups < 1) return exec_fail(NQ_E_INVALID_ARG, "nq_exec_plan_tasks: n and n_workgroups must be >= 1");
+    const std::string w(who);
+    if (!d_out || !d_in || !r || !level_of || !n_tasks) return exec_fail(NQ_E_NULL, (w + ": NULL pointer").c_str());
+    if (n < 1 || n_workgroups < 1) return exec_fail(NQ_E_INVALID_ARG, (w + ": n and n_workgroups must be >= 1").c_str());
     for (int i = 0; i < n; ++i) {
-        if (d_out[i] < 1 || d_in[i] < 1 || r[i] < 1) return exec_fail(NQ_E_SHAPE, "nq_exec_plan_tasks: dimensions must be >= 1");
+        if (d_out[i] < 1 || d_in[i] < 1 || r[i] < 1) return exec_fail(NQ_E_SHAPE, (w + ": dimensions must be >= 1").c_str());
         if (level_of[i] < 0 || (i > 0 && level_of[i] < level_of[i - 1]))
-            return exec_fail(NQ_E_INVALID_ARG, "nq_exec_plan_tasks: levels must be >= 0 and listed in order");
+            return exec_fail(NQ_E_INVALID_ARG, (w + ": levels must be >= 0 and listed in order").c_str());
     }
     std::vector<PlannedTask> t;
     plan_tasks(d_out, d_in, r, level_of, n, n_workgroups, t);
-    t.erase(std::remove_if(t.begin(), t.end(), [](const PlannedTask& p) { return p.p0 != 0; }), t.end());      // a row block that is dealt out: once
+    // (7 words cannot tell the planes of a row block apart: it is listed once)
+    if (record == 7) t.erase(std::remove_if(t.begin(), t.end(), [](const PlannedTask& p) { return p.p0 != 0; }), t.end());
     *n_tasks = (int)t.size();
     if (tasks_out) {
-        if ((int)t.size() > capacity) return exec_fail(NQ_E_INVALID_ARG, "nq_exec_plan_tasks: tasks_out too small");
+        if ((int)t.size() > capacity) return exec_fail(NQ_E_INVALID_ARG, (w + ": tasks_out too small").c_str());
         for (size_t k = 0; k < t.size(); ++k) {
-            int32_t* o = tasks_out + 7 * k;
-            o[0] = t[k].wg; o[1] = t[k].phase; o[2] = t[k].layer; o[3] = t[k].stage; o[4] = t[k].rb0; o[5] = t[k].n_rb; o[6] = t[k].W;
+            const int32_t rec[9] = {t[k].wg, t[k].phase, t[k].layer, t[k].stage, t[k].rb0, t[k].n_rb, t[k].W, t[k].p0, t[k].pl};
+            std::copy(rec, rec + record, tasks_out + record * k);
         }
     }
     return NQ_OK;
+}
+
+extern "C" int nq_exec_plan_tasks(const int64_t* d_out, const int64_t* d_in, const int64_t* r, const int* level_of, int n,
+                                  int n_workgroups, int32_t* tasks_out, int capacity, int* n_tasks)
+{
+    return plan_records("nq_exec_plan_tasks", d_out, d_in, r, level_of, n, n_workgroups, 7, tasks_out, capacity, n_tasks);
+}
+
+extern "C" int nq_exec_plan_lists(const int64_t* d_out, const int64_t* d_in, const int64_t* r, const int* level_of, int n,
+                                  int n_workgroups, int32_t* tasks_out, int capacity, int* n_tasks)
+{
+    return plan_records("nq_exec_plan_lists", d_out, d_in, r, level_of, n, n_workgroups, 9, tasks_out, capacity, n_tasks);
 }
 
 // ---------------------------------------------------------------------------------------------

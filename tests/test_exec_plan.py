@@ -76,6 +76,40 @@ def test_task_lists_cover_everything_once_and_drain(which, n_blocks, n_wg):
     assert simulate(tasks, n_wg, src, max_rounds=len(tasks) + 1) == 0
 
 
+@pytest.mark.parametrize("which,n_blocks,n_wg", [("7b", 3, 256), ("70b", 2, 256), ("7b", 2, 512), ("70b", 1, 304), ("70b", 1, 64), ("7b", 1, 8), ("7b", 1, 7)])
+def test_lists_with_bit_planes(which, n_blocks, n_wg):
+    """The complete lists: every bit plane of every row block once, the planes of a row block on different workgroups of one XCD (workgroup
+    mod 8), no workgroup with two dealt-out tasks of a phase, phase order, and the model grid drains -- and does not where one task of a
+    dealt-out row block never runs."""
+    block = synth.llama2_7b_block() if which == "7b" else synth.llama2_70b_block()
+    d_out, d_in, r, level, src = block_spec(block, n_blocks)
+    tasks = nq.nq_exec_plan_lists(d_out, d_in, r, level, n_wg).tolist()
+    seen, on, last, phases = {}, {}, {}, set()
+    for wg, phase, layer, stage, rb0, n, W, p0, pl in tasks:
+        assert 0 <= wg < n_wg and phase == 2 * level[layer] + stage and phase >= last.get(wg, -1)
+        last[wg] = phase
+        if pl:
+            assert n == 1 and W == 8 and pl in (1, 2, 4, 8) and p0 % pl == 0 and p0 + pl <= 8
+            assert (phase, wg) not in phases
+            phases.add((phase, wg))
+            on.setdefault((layer, stage, rb0), []).append(wg)
+        for rb in range(rb0, rb0 + n):
+            for p in range(p0, p0 + pl) if pl else range(8):
+                seen[(layer, stage, rb, p)] = seen.get((layer, stage, rb, p), 0) + 1
+    want = {(i, st, rb, p) for i in range(len(d_out)) for st in (0, 1) for rb in range(((r[i] if st == 0 else d_out[i]) + 127) // 128) for p in range(8)}
+    assert set(seen) == want and set(seen.values()) == {1}
+    for wgs in on.values():
+        assert len(set(wgs)) == len(wgs) and len({w % 8 for w in wgs}) == 1
+    assert (max(len(w) for w in on.values()) > 1) if n_wg >= 256 else True
+    short = [t[:7] for t in tasks]
+    assert simulate(short, n_wg, src, max_rounds=len(tasks) + 1) == 0
+    # (the stages behind it are left over)
+    gone = next(k for k, t in enumerate(tasks) if t[2] == 3 and t[3] == 0)
+    assert simulate(short[:gone] + short[gone + 1:], n_wg, src, max_rounds=10 * len(tasks), planned=short) > 0
+    # and the records without planes are the same lists with a dealt-out row block once
+    assert nq.nq_exec_plan_tasks(d_out, d_in, r, level, n_wg).tolist() == [t[:7] for t in tasks if t[7] == 0]
+
+
 def test_model_reports_a_stuck_grid_after_bounded_rounds():
     """The model's waits are bounded like the kernel's: lists that break the phase order (one workgroup's
     list reversed), or a producer that never shows up, end with tasks left over, not in an endless loop."""

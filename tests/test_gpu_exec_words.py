@@ -115,3 +115,14 @@ def test_a_scale_that_is_not_finite_stays_in_its_own_layer(scale):
     nq.nq_exec_destroy(e)
     for L in layers:
         L.close()
+
+
+@pytest.mark.parametrize("shapes", [SMALL, [(5123, 70, 300)] * 3 + [(9001, 5123, 259), (16901, 9001, 2051), (16901, 9001, 2051), (70, 16901, 18)]])
+def test_the_planner_lists_what_the_executor_runs(shapes):
+    c = Chain(shapes, 2, seed=13400)
+    e = c.executor()
+    n_wg, n_tasks, _ = nq.nq_exec_info(e)
+    lists = nq.nq_exec_plan_lists([L.d_out for L in c.layers], [L.d_in for L in c.layers], [L.r for L in c.layers], c.level, n_wg)
+    assert len(lists) == n_tasks and (lists[:, 8] > 0).any()
+    nq.nq_exec_destroy(e)
+    c.close()
