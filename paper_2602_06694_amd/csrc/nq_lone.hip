@@ -622,14 +622,17 @@ static int lone_groups(int batch) { return (batch + 7) / 8; }
 // 38.9 / 42.3, past it at 24 and 40 44.1 / 44.1, 57.3 / 47.7; 8192 x 8192 r = 2240 at 16 23.3 / 24.8, past it at 24 33.2 / 25.7.
 bool lone_deals_out(int n_rb, int batch) { return 2 * n_rb * lone_groups(batch) <= device_cu_count(); }
 
-// Whether the workgroups of such a launch quantise its input themselves.  Whole row blocks per workgroup (more than half as many as CUs)
-// leave eight waves for it, which pays for fewer elements (28672 rows, batch 8: r = 1024 14.2 us against 15.9 with launches of their own, r = 3520
-// 22.0 and 18.5; batch 4 r = 600 11.8 and 13.2, r = 3520 14.8 and 14.0; 22000 rows r = 2240 level).
+// Whether the workgroups of such a launch quantise its input themselves.  Where several share a row block, up to what 16 waves hold.  Whole row
+// blocks per workgroup (more than half as many as CUs) leave eight waves for it, two to a SIMD, which pays for one or two tokens and for short
+// inputs of more; past that the launch of its own is the faster one.  us per plan, with a launch of its own / along, stage 2 of 224 row blocks: batch 2 r = 2048 12.1 / 11.2, r = 6144 16.8 / 14.4;
+// batch 3 r = 1024 11.4 / 11.2, r = 2048 12.0 / 12.1, past the line r = 4096 13.3 / 14.4; batch 4 r = 1024 11.5 / 11.6, past it r = 2048 12.2 / 12.6; batch 5 r = 1024
+// 12.3 / 12.8, past it r = 2048 12.9 / 14.3; batch 8 r = 1024 15.1 / 15.6, but stage 1 of as many of three layers, d_in = 1024, batch 5 to 8, 0.97 to 0.99 of the time.
+// (132 to 256 row blocks and lone forwards alike.)
 bool lone_selfq(int max_steps, int n_rb, int batch)
 {
-    const int pl = lone_planes(n_rb * lone_groups(batch)), per = lone_group(batch);
-    return per * lone_pieces<16>(max_steps) * 1024 <= (pl == 8 ? kLoneMaxElements * 3 / 8 : kLoneMaxElements) &&
-           lone_lds_bytes(per <= 5 ? 1 : 2, pl, pl == 8 ? 8 : 16, max_steps, per) <= kLoneLdsBytes;
+    const int pl = lone_planes(n_rb * lone_groups(batch)), per = lone_group(batch), pieces = lone_pieces<16>(max_steps);
+    const int most = pl < 8 ? kLoneMaxElements / 1024 / per : per <= 2 ? 12 / per : per == 3 ? 2 : 1;
+    return pieces <= most && lone_lds_bytes(per <= 5 ? 1 : 2, pl, pl == 8 ? 8 : 16, max_steps, per) <= kLoneLdsBytes;
 }
 
 template <int NB, int PL, int W, bool SELFQ>

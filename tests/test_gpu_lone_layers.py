@@ -86,3 +86,25 @@ def test_plans(nqopt, layers, batch, codes):
     nq.nq_plan_destroy(plan)
     for L in hs:
         L.close()
+
+
+@pytest.mark.parametrize("batch,steps,own", [(1, 192, False), (2, 96, False), (2, 97, True), (3, 32, False), (3, 33, True), (4, 16, False), (4, 17, True), (5, 32, True), (8, 16, False), (8, 17, True)])
+def test_inputs_quantised_along_by_workgroups_of_whole_row_blocks(nqopt, batch, steps, own):
+    """132 row blocks, each with a workgroup of its own: where the stage quantises its input along (no launch and no time for it) and where a launch does."""
+    import torch
+    L = Layer(132 * 128 - 5, 70, 64 * steps - 3, "f32", seed=11700 + steps)
+    x = to_device(synth.gen_x(batch, 70, 11701, "f32"), "f32")
+    y, lone, narrow = (new_output(batch, L.d_out) for _ in range(3))
+    plan = nq.nq_plan_create([L.h], [x], [y], batch)
+    ms = nq.nq_plan_forward_timed(plan)
+    nq.nq_binlr_forward(L.h, x, lone, batch)
+    for o in ("no_selfq", "no_fuse"):
+        nqopt.set(o, 1)
+    nqopt.set("force_w", 4)
+    nq.nq_binlr_forward(L.h, x, narrow, batch)
+    torch.cuda.synchronize()
+    assert torch.equal(y, lone) and torch.equal(y, narrow) and not torch.isnan(y).any()
+    if batch > 1:
+        assert (ms[2] > 0) == own, ms
+    nq.nq_plan_destroy(plan)
+    L.close()
