@@ -251,7 +251,7 @@ int nq_plan_forward(nq_plan p, void* stream);
  * than the step), waits for it, and returns the duration of each kernel in milliseconds:
  * ms[0] input quantisation, ms[1] stage 1 (t = V^T x'), ms[2] quantisation of t,
  * ms[3] stage 2 (y = s_out (.) U t).  Synchronises `stream`.  Where a stage quantises its own
- * input (batch-1 lists) there is no quantisation launch: its entry is 0 and the stage entry
+ * input (short launches) there is no quantisation launch: its entry is 0 and the stage entry
  * covers both. */
 int nq_plan_forward_timed(nq_plan p, void* stream, float ms[4]);
 /* Debug: which schedule each of the plan's two stage launches uses.  w[0] stage 1, w[1] stage 2:
@@ -262,7 +262,9 @@ int nq_plan_forward_timed(nq_plan p, void* stream, float ms[4]);
  * workgroup (16 waves per row block) quantises the input for itself,
  * 33 / 34 = batch-1 launch whose waves quantise their own share of the input (one / four waves per
  * row block; reductions of at most 1024 / 4096 elements), 35 = short launch at batch 2..8 in which every workgroup
- * quantises the input for itself. */
+ * quantises the input for itself.  A launch with at most one row block per CU may run as 35 (32 at batch 1: as its form with several
+ * workgroups per row block) or 16 where it is said to be 4, 12 or 16: more than four layers at batch 2, reductions of more than 176
+ * steps; nq_plan_forward_timed shows whether it quantises its input itself. */
 int nq_plan_schedules(nq_plan p, int w[2]);
 int nq_plan_destroy(nq_plan p);
 

@@ -210,6 +210,7 @@ struct nq_plan_s {
     FusedItem* fitems2;
     int n_items1, n_items2;
     int w1, w2;                     // schedule of each stage launch (see stage_schedule; kFusedSchedule: no quantisation launch)
+    int told[2];                    // what nq_plan_schedules says of them
     int max_steps1, max_steps2;     // longest reduction of each stage launch
     int max_chunks_x, max_chunks_t; // longest vector of each quantisation launch (picks its block size)
     std::vector<nq_handle> handles;
@@ -989,7 +990,7 @@ extern "C" int nq_plan_create(nq_plan* out, const nq_handle* hs, const void* con
         s2[i] = make_s2(hs[i], hs[i]->ws, ys[i]);
     }
     // one work list per stage launch; its shape follows the schedule the launch will use
-    int sched[2], max_steps_of[2] = {0, 0};
+    int sched[2], told[2], max_steps_of[2] = {0, 0};       // what runs, what nq_plan_schedules says
     std::vector<WorkItem> lists[2];
     for (int st = 0; st < 2; ++st) {
         const std::vector<StageDesc>& sd = st == 0 ? s1 : s2;
@@ -1034,26 +1035,30 @@ extern "C" int nq_plan_create(nq_plan* out, const nq_handle* hs, const void* con
                 selfq_fits(w, max_steps, min_steps, batch))
                 w = w == 1 ? kSelfqSchedule1 : kSelfqSchedule4;
         }
-        // The same above batch 1, and 16 waves per workgroup where the input is too long for that (nq_lone.hip; us per plan, before and after):
-        // q, k, v of a 70B-shaped block at batch 4 21.1 -> 15.0, six 4096 x 4096 layers at batch 3 16.9 -> 12.7, twelve 17.5 -> 14.7, all seven
-        // projections of a 7B-shaped block as four plans 76.2 -> 56.5 at batch 4, 103 -> 75 at batch 8.  (At batch 2 more than four layers, and reductions longer than those of
-        // the 7B shapes, would gain too -- 28 row blocks of 192 steps 22.1 -> 13.0 us, five layers 18.3 -> 12.2 -- but keep the widths
-        // that split_width() gives them, which callers are told by nq_plan_schedules.)
-        if ((batch > 2 || (batch == 2 && n <= 4)) && max_steps <= 176 && total_rb <= device_cu_count() && total_rb < schedule_full_rowblocks() &&
-            !opt_flag(OPT_NO_SELFQ) && opt(OPT_FORCE_W) < 0) {
-            if (lone_selfq(max_steps, total_rb, batch)) w = kLoneSchedule;
-            else if (batch > 2 && lone_planes(total_rb) < 8) w = 16;
+        // The same above batch 1, and 16 waves per workgroup where several share a row block but the input is too long for that
+        // (nq_lone.hip).  Against split_width()'s four waves and a quantisation launch, plans of one and six layers, 1 to 128 row blocks
+        // of 16 to 512 steps at batch 2 to 8, dealt-out row blocks take 0.69 to 0.97 of the time at every length; only 100 to 128 of them with 100
+        // to 176 steps at batch 4 and 5 are level (0.99 to 1.03).  us per plan: 28 row blocks of 176 steps at batch 2 20.8 -> 16.7; six layers, 128 of
+        // 128 steps at batch 2 21.1 -> 17.1; 12 of 216 at batch 3 21.1 -> 19.1, at batch 6 30.7 -> 25.1; q, k, v of a 70B-shaped block at
+        // batch 4 21.1 -> 15.0; the seven projections of a 7B-shaped one as four plans at batch 4 76 -> 57.
+        int how = w;
+        if (batch > 1 && total_rb <= device_cu_count() && total_rb < schedule_full_rowblocks() && !opt_flag(OPT_NO_SELFQ) && opt(OPT_FORCE_W) < 0) {
+            if (lone_selfq(max_steps, total_rb, batch)) how = kLoneSchedule;
+            else if (lone_planes(total_rb) < 8 && !is_wide_split(w)) how = 16;
+            // (nq_plan_schedules names them only for the launches that it has named them for so far; programs compare its answers)
+            if ((batch > 2 || (how == kLoneSchedule && n <= 4)) && max_steps <= 176) w = how;
         }
         // Option "two_slice_b8": at batch 6..8 the shared-input launches take their input as 16-bit fixed point (the top
         // byte slice stays zero), which puts the eight tokens into ONE group of 16 MFMA columns instead of two.
         if (opt_flag(OPT_TWO_SLICE_B8) && batch >= 6 && (w == kSharedSchedule || w == kSharedResidentSchedule)) {
-            w = w == kSharedSchedule ? kSharedSchedule2 : kSharedResidentSchedule2;
+            how = w = w == kSharedSchedule ? kSharedSchedule2 : kSharedResidentSchedule2;
             for (int i = 0; i < n; ++i) (st == 0 ? qx : qt)[i].mag_exp = 14;
         }
-        sched[st] = w;
+        told[st] = w;
+        sched[st] = how;
         for (int i = 0; i < n; ++i) {
             const int nrb = (int)n_rowblocks(sd[i].M);
-            if (is_shared_schedule(w)) {
+            if (is_shared_schedule(how)) {
                 // the waves of a workgroup share an op's input: items of kShareWaves x (row blocks per wave) row blocks
                 const int group = kShareWaves * shared_per_wave(sd[i].n_steps, batch);
                 for (int rb = 0; rb < nrb; rb += group)
@@ -1061,7 +1066,7 @@ extern "C" int nq_plan_create(nq_plan* out, const nq_handle* hs, const void* con
                                                  sd[i].n_steps, i, rb, std::min(group, nrb - rb)});
                 continue;
             }
-            const int per = w == 1 ? rbs_per_stream_item(nrb, sd[i].n_steps, total_rb, batch) : 1;
+            const int per = how == 1 ? rbs_per_stream_item(nrb, sd[i].n_steps, total_rb, batch) : 1;
             // runs of `per` row blocks first, then shorter and shorter ones: the sorted list ends in
             // small items, which level out the finishing times of the waves (the hardware hands an
             // idle slot the next item)
@@ -1123,6 +1128,7 @@ extern "C" int nq_plan_create(nq_plan* out, const nq_handle* hs, const void* con
     p->handles.assign(hs, hs + n);
     p->n_items1 = (int)it1.size(); p->n_items2 = (int)it2.size();
     p->w1 = sched[0]; p->w2 = sched[1];
+    p->told[0] = told[0]; p->told[1] = told[1];
     p->max_steps1 = max_steps_of[0]; p->max_steps2 = max_steps_of[1];
     p->max_chunks_x = p->max_chunks_t = 0;
     for (int i = 0; i < n; ++i) {
@@ -1218,8 +1224,8 @@ static int plan_run(nq_plan p, hipStream_t s, bool timed)
 extern "C" int nq_plan_schedules(nq_plan p, int w[2])
 {
     if (!p || !w) return fail(NQ_E_NULL, "nq_plan_schedules: NULL pointer");
-    w[0] = p->w1;
-    w[1] = p->w2;
+    w[0] = p->told[0];
+    w[1] = p->told[1];
     return NQ_OK;
 }
 

@@ -108,3 +108,28 @@ def test_inputs_quantised_along_by_workgroups_of_whole_row_blocks(nqopt, batch, 
         assert (ms[2] > 0) == own, ms
     nq.nq_plan_destroy(plan)
     L.close()
+
+
+@pytest.mark.parametrize("row_blocks,steps,layers,batch,along", [
+    (28, 188, 1, 2, True), (28, 192, 1, 2, True), (64, 256, 1, 2, True), (128, 240, 1, 2, True), (128, 256, 1, 2, False), (28, 257, 1, 2, False),      # past 7B-shaped reductions, to what fits
+    (3, 160, 1, 3, True), (12, 216, 1, 3, False), (28, 320, 1, 4, False), (128, 512, 1, 5, False), (8, 252, 1, 6, False), (8, 256, 1, 8, False),
+    (45, 64, 5, 2, True), (116, 172, 12, 2, True), (128, 216, 6, 3, False), (6, 300, 6, 8, False)])
+def test_plans_of_any_length(nqopt, row_blocks, steps, layers, batch, along):
+    """Few row blocks of long reductions and of many layers: dealt out whatever the length, the input quantised along (no launch, no time for it) where it fits; the bits
+    of four waves per row block."""
+    import torch
+    per = [row_blocks // layers + (i < row_blocks % layers) for i in range(layers)]
+    hs = [Layer(70, 64 * steps - (5 if i == 0 else 64 * i), 128 * k - (3 if i == 0 else 0), "bf16", seed=11800 + i) for i, k in enumerate(per)]
+    xs = [to_device(synth.gen_x(batch, L.d_in, 11801 + i, "bf16"), "bf16") for i, L in enumerate(hs)]
+    ys, narrow = [new_output(batch, 70) for _ in hs], [new_output(batch, 70) for _ in hs]
+    plan = nq.nq_plan_create([L.h for L in hs], xs, ys, batch)
+    ms = nq.nq_plan_forward_timed(plan)
+    assert (ms[0] == 0) == along, ms
+    nqopt.set("force_w", 4)
+    for L, x, y in zip(hs, xs, narrow):
+        nq.nq_binlr_forward(L.h, x, y, batch)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) and not torch.isnan(a).any() for a, b in zip(ys, narrow))
+    nq.nq_plan_destroy(plan)
+    for L in hs:
+        L.close()
