@@ -737,14 +737,15 @@ static int decode_once(nq_handle h, const DecodeWorkspace& w, const void* x, voi
     return launch_stage(nullptr, s2, nullptr, (rb2 + per2 - 1) / per2, w2, per2, batch, s);
 }
 
-// More than eight tokens in groups of up to eight (nq_lone.hip), or of 16 (nq_exact.hip)?
-static bool dealt_out(const StageDesc& s1, const StageDesc& s2, int batch)
-{
-    return !opt_flag(OPT_NO_SELFQ) && opt(OPT_FORCE_W) < 0 && lone_deals_out((int)n_rowblocks(s1.M), batch) && lone_deals_out((int)n_rowblocks(s2.M), batch);
-}
-static int dealt_out_stage(const QuantDesc& q, const StageDesc& sd, int batch, hipStream_t s)
+// One stage of a pass of more than eight tokens: in groups of up to eight (nq_lone.hip), or of 16 (nq_exact.hip).
+static int exact_stage(const QuantDesc& q, const StageDesc& sd, int batch, hipStream_t s)
 {
     const int n_rb = (int)n_rowblocks(sd.M);
+    const bool whole = (size_t)q.x_stride * dtype_size(q.dtype) % 16 == 0 && q.N % 16 == 0;
+    if (opt_flag(OPT_NO_SELFQ) || opt(OPT_FORCE_W) >= 0 || !lone_deals_out(n_rb, sd.n_steps, whole, batch)) {
+        const int rc = launch_quantize(nullptr, q, 1, q.n_chunks, batch, s, true);
+        return rc != NQ_OK ? rc : launch_stage_exact(sd, batch, s);
+    }
     if (lone_selfq(sd.n_steps, n_rb, batch)) return launch_lone_selfq(nullptr, n_rb, q, sd, sd.n_steps, batch, s);
     const int rc = launch_quantize(nullptr, q, 1, q.n_chunks, batch, s);
     return rc != NQ_OK ? rc : launch_lone(nullptr, n_rb, sd, 16, batch, s);
@@ -769,19 +770,10 @@ static int run_in_passes(nq_handle h, const void* x, void* y, int batch, hipStre
         int rc, nb;
         if (wide && left > NQ_DECODE_MAX_BATCH) {
             nb = std::min(h->xt_tokens, left);
-            const QuantDesc qx = make_qx(h, w, xp), qt = make_qt(h, w);
-            const StageDesc s1 = make_s1(h, w);
             StageDesc s2 = make_s2(h, w, yp);
             if (unscaled) s2.out_scale = nullptr;
-            if (dealt_out(s1, s2, nb)) {
-                if ((rc = dealt_out_stage(qx, s1, nb, s)) != NQ_OK || (rc = dealt_out_stage(qt, s2, nb, s)) != NQ_OK) return rc;
-                b0 += nb;
-                continue;
-            }
-            if ((rc = launch_quantize(nullptr, qx, 1, qx.n_chunks, nb, s, true)) != NQ_OK) return rc;
-            if ((rc = launch_stage_exact(s1, nb, s)) != NQ_OK) return rc;
-            if ((rc = launch_quantize(nullptr, qt, 1, qt.n_chunks, nb, s, true)) != NQ_OK) return rc;
-            rc = launch_stage_exact(s2, nb, s);
+            rc = exact_stage(make_qx(h, w, xp), make_s1(h, w), nb, s);
+            if (rc == NQ_OK) rc = exact_stage(make_qt(h, w), s2, nb, s);
         } else {
             nb = std::min(NQ_DECODE_MAX_BATCH, left);
             rc = decode_once(h, h->ws, xp, yp, nb, s, unscaled);
@@ -793,8 +785,10 @@ static int run_in_passes(nq_handle h, const void* x, void* y, int batch, hipStre
 }
 
 // Whether nq_binlr_forward takes the exact path for more than eight tokens: where its launches are the faster ones, which is so for few
-// tokens and small layers.  The dense path does 64 tokens at a time on two workgroups of four row blocks per CU, so that such calls leave it idle.  In
-// groups of eight always (9 to 128 tokens of the layers that this holds for: 0.55 to 0.95 of the dense path's time); in groups of 16 where one pass
+// tokens and small layers.  The dense path does 64 tokens at a time on two workgroups of four row blocks per CU, so that such calls leave it idle.  Where both
+// stages have at most half as many pairs of row block and group of eight tokens as CUs: 0.55 to 0.99 of the dense path's time (456 forwards, 128 x 128 to 1024 x 65536 at
+// 32 to 512 tokens), but for reductions of more than 32768 elements in groups of more than five tokens (65536 long: 9 tokens 44 us against 50, 16 59 against 51) and
+// more than 256 tokens of four steps and fewer (256 x 256 r = 250, 512 tokens 15.1 against 13.8).  Those and larger layers where one pass
 // holds the batch and its estimate is a tenth below the dense path's (at that line none of 1150 forwards of 50 layers, 256 x 256 to
 // 28672 x 28672 at 9 to 512 tokens, lost more than 4.1 %, and on average they take 0.83 of the dense path's time).  us, dense / exact: 4096 x 4096
 // r = 1024 at 24, 64, 128 tokens 27.5 / 16.0, 28.0 / 20.0, 29.1 / 22.5, past the line at 256 and 512 33.1 / 30.5, 36.2 / 44.0; 28672 x 8192 r = 3520 at 9 and 24
@@ -806,7 +800,9 @@ static bool forward_exact_pays(nq_handle h, int batch)
         if (opt((Opt)o) >= 0) return false;
     // (layers that the dense path takes one column at a time: its first product is exact as well, and its results stay the same bits at every batch)
     if (h->pf_plain || batch > exact_pass_tokens(h)) return false;
-    if (lone_deals_out((int)n_rowblocks(h->r), batch) && lone_deals_out((int)n_rowblocks(h->d_out), batch)) return true;
+    const int64_t longest = std::max(n_steps(h->d_in), n_steps(h->r));
+    const int rbs = (int)n_rowblocks(std::max(h->r, h->d_out));
+    if (lone_shared_pairs(rbs, batch) && (longest <= 512 || batch <= 10) && (batch <= 256 || longest > 4 || lone_shared_pairs(2 * rbs, batch))) return true;
     return exact_us(h->d_out, h->d_in, h->r, batch) < 0.9 * prefill_us(h->d_out, h->d_in, h->r, batch);
 }
 

@@ -616,12 +616,6 @@ static size_t lone_lds_bytes(int nb, int pl, int w, int max_steps, int batch)
 static int lone_group(int batch) { return (batch + (batch + 7) / 8 - 1) / ((batch + 7) / 8); }
 static int lone_groups(int batch) { return (batch + 7) / 8; }
 
-// Whether more than eight tokens are faster in groups than in the groups of 16 of nq_exact.hip: where several workgroups share every pair of row block
-// and group, i.e. up to half as many pairs as CUs.  us per forward, here / there: 4096 x 4096 r = 1024 at 9, 24, 32 tokens 11.9 / 18.2, 16.0 / 18.6,
-// 16.3 / 18.7, past the line at 40 and 80 20.7 / 19.6, 31.6 / 21.5; 1024 x 1024 r = 256 at 64 and 128 11.3 / 14.0, 13.2 / 14.7; 8192 x 28672 r = 3520 at 16
-// 38.9 / 42.3, past it at 24 and 40 44.1 / 44.1, 57.3 / 47.7; 8192 x 8192 r = 2240 at 16 23.3 / 24.8, past it at 24 33.2 / 25.7.
-bool lone_deals_out(int n_rb, int batch) { return 2 * n_rb * lone_groups(batch) <= device_cu_count(); }
-
 // Whether the workgroups of such a launch quantise its input themselves.  Where several share a row block, up to what 16 waves hold.  Whole row
 // blocks per workgroup (more than half as many as CUs) leave eight waves for it, two to a SIMD, which pays for one or two tokens and for short
 // inputs of more; past that the launch of its own is the faster one.  us per plan, with a launch of its own / along, stage 2 of 224 row blocks: batch 2 r = 2048 12.1 / 11.2, r = 6144 16.8 / 14.4;
@@ -633,6 +627,23 @@ bool lone_selfq(int max_steps, int n_rb, int batch)
     const int pl = lone_planes(n_rb * lone_groups(batch)), per = lone_group(batch), pieces = lone_pieces<16>(max_steps);
     const int most = pl < 8 ? kLoneMaxElements / 1024 / per : per <= 2 ? 12 / per : per == 3 ? 2 : 1;
     return pieces <= most && lone_lds_bytes(per <= 5 ? 1 : 2, pl, pl == 8 ? 8 : 16, max_steps, per) <= kLoneLdsBytes;
+}
+
+// Up to half as many pairs of row block and group of eight tokens as CUs: several workgroups share every pair.
+bool lone_shared_pairs(int n_rb, int batch) { return 2 * n_rb * lone_groups(batch) <= device_cu_count(); }
+
+// Whether a stage of more than eight tokens is faster in such groups than in the groups of 16 of nq_exact.hip.  Always up to a quarter as many pairs as CUs, where
+// four and eight workgroups share each.  Two workgroups per pair take 7.75 us up to 16 steps with the input quantised along, 9.1 up to 32, 10.9 at 47; a quantisation launch and
+// groups of 16 take 3.5 to 4.8 and 3.7 to 4.4 up to 24 steps, 6.5 to 7.6 beyond (rows that do not start 16-byte aligned or end inside 16 elements two to three
+// more, and so do more than 128 tokens; at 24 tokens, where half a group of 16 is empty, the two are level and one launch is less).  Forwards, groups of eight in both stages / of 16, us: 1536 x 1536 r = 1536, 64 tokens 18.2 / 15.8; 2048 x 2048 r = 2048, 64 18.4 / 19.3;
+// 2000 x 3000 r = 1900, 64 20.5 / 22.7; 640 x 300 r = 600, 128 15.6 / 17.5; 256 x 512 r = 256, 512 15.6 / 14.7; 256 x 2048 r = 256, 512 16.7 / 20.9.  With
+// a quantisation launch in both forms the line lies between: 1024 x 4096 r = 1024, 96 20.1 / 19.4; 512 x 4096 r = 384, 256 20.6 / 21.6; 768 x 8192 r = 700, 96
+// 24.0 / 25.0; 1024 x 32768 r = 1024, 96 42.0 / 45.7.
+bool lone_deals_out(int n_rb, int steps, bool whole, int batch)
+{
+    if (!lone_shared_pairs(n_rb, batch)) return false;
+    if (4 * n_rb * lone_groups(batch) <= device_cu_count() || steps >= 128 || (batch > 128 && steps > 8)) return true;
+    return lone_selfq(steps, n_rb, batch) && (!whole || steps > 24 || (batch <= 24 && steps > 8));
 }
 
 template <int NB, int PL, int W, bool SELFQ>

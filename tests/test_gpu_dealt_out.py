@@ -66,3 +66,48 @@ def test_forward_on_either_path(nqopt, shape, x_dtype):
         assert rel_err(exact.cpu().numpy(), ref) <= DECODE_TOL
         assert rel_err(dense.cpu().numpy(), ref) <= DENSE_TOL
         L.close()
+
+
+@pytest.mark.parametrize("shape,x_dtype,batches", [
+    ((1536, 1536, 1536), "bf16", (41, 48, 80)),                   # two workgroups per pair: groups of 16 in both stages
+    ((2000, 3000, 1900), "f16", (33, 64)),                        # of eight in both
+    ((1280, 8200, 1280), "bf16", (56, 96)), ((1030, 700, 1024), "f32", (72, 120)),      # of eight in the first only
+    ((2048, 512, 1800), "bf16", (40, 64)),                        # in the second only
+    ((250, 640, 256), "f16", (257, 320, 512)),
+])
+def test_each_stage_has_a_form_of_its_own(nqopt, shape, x_dtype, batches):
+    import torch
+    L = Layer(*shape, x_dtype, seed=12300 + shape[1])
+    nq.nq_binlr_reserve(L.h, max(batches))
+    nq.nq_binlr_set_mid_scale(L.h, synth.gen_scales(shape[2], 12301))
+    for batch in batches:
+        xd = to_device(synth.gen_x(batch, shape[1], 12310 + batch, x_dtype), x_dtype)
+        a, b = new_output(batch, shape[0]), new_output(batch, shape[0])
+        nq.nq_binlr_forward_exact(L.h, xd, a, batch)
+        nqopt.set("no_selfq", 1)
+        nq.nq_binlr_forward_exact(L.h, xd, b, batch)
+        nqopt.unset("no_selfq")
+        torch.cuda.synchronize()
+        assert torch.equal(a, b) and not torch.isnan(a).any(), batch
+    L.close()
+
+
+@pytest.mark.parametrize("shape,batch,takes_exact", [
+    ((256, 32768, 100), 24, True), ((256, 65536, 100), 9, True), ((256, 65536, 100), 16, False), ((130, 50000, 64), 64, False),
+    ((128, 128, 128), 512, True), ((256, 256, 250), 256, True), ((256, 256, 250), 320, False), ((256, 512, 250), 320, True),
+])
+def test_forward_takes_the_faster_path_of_small_layers(nqopt, shape, batch, takes_exact):
+    """Many tokens of a few row blocks and reductions longer than 32768: the bits of the path that was measured to be the faster one."""
+    import torch
+    L = Layer(*shape, "bf16", seed=12400 + shape[1])
+    nq.nq_binlr_reserve(L.h, batch)
+    xd = to_device(synth.gen_x(batch, shape[1], 12410 + batch, "bf16"), "bf16")
+    y, exact, dense = (new_output(batch, shape[0]) for _ in range(3))
+    nq.nq_binlr_forward(L.h, xd, y, batch)
+    nq.nq_binlr_forward_exact(L.h, xd, exact, batch)
+    nqopt.set("dense_only", 1)
+    nq.nq_binlr_forward(L.h, xd, dense, batch)
+    torch.cuda.synchronize()
+    assert not torch.equal(exact, dense)
+    assert torch.equal(y, exact if takes_exact else dense)
+    L.close()
