@@ -1410,7 +1410,6 @@ int shared_per_wave(int nst, int batch)
 template <int NB, bool RESIDENT, int SL = 3>
 static int launch_shared_t(const StageDesc* d_descs, const WorkItem* d_items, int n_items, int batch, hipStream_t s)
 {
-    static bool attr_set = false;
     const int per_max = shared_max_per(batch);
     const size_t lds_bytes = (size_t)2 * batch * kShareTokStride + (size_t)kShareWaves * kEpiRegion * 4 +
                              (size_t)kShareWaves * per_max * kTileRows * batch * 4;
@@ -1419,11 +1418,7 @@ static int launch_shared_t(const StageDesc* d_descs, const WorkItem* d_items, in
         return NQ_E_INVALID_ARG;
     }
     if (n_items < 1) return NQ_OK;
-    if (!attr_set) {
-        NQ_HIP(hipFuncSetAttribute((const void*)stage_shared_kernel<NB, RESIDENT, SL>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   160 * 1024));
-        attr_set = true;
-    }
+    NQ_ALLOW_LDS((stage_shared_kernel<NB, RESIDENT, SL>), 160 * 1024);
     NQ_LAUNCH((stage_shared_kernel<NB, RESIDENT, SL>), dim3(n_items), dim3(64 * kShareWaves), lds_bytes, s, d_descs, d_items,
                        n_items, per_max, batch);
     NQ_HIP(hipGetLastError());
@@ -1435,12 +1430,8 @@ bool fused_fits(int nst, int batch) { return batch == 1 && nst * 4 <= 64 * kFuse
 
 static int fused_set_attr()
 {
-    static bool attr_set = false;
-    if (!attr_set) {
-        NQ_HIP(hipFuncSetAttribute((const void*)stage_fused_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024));
-        NQ_HIP(hipFuncSetAttribute((const void*)stage_fused_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024));
-        attr_set = true;
-    }
+    NQ_ALLOW_LDS(stage_fused_kernel<false>, 128 * 1024);
+    NQ_ALLOW_LDS(stage_fused_kernel<true>, 128 * 1024);
     return NQ_OK;
 }
 

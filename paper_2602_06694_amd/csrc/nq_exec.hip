@@ -752,7 +752,6 @@ bool small_layer_fits(nq_handle h, int batch)
 
 int launch_small_layer(nq_handle h, const DecodeWorkspace& w, const void* x, void* y, bool unscaled, hipStream_t s)
 {
-    static bool attr_set = false;
     ExecPair p{};
     // waves per row block: as many as leave every row block of the stage a place in ONE round (else one wave each, several rounds)
     auto wl_for = [](int64_t n_rb) {
@@ -774,10 +773,7 @@ int launch_small_layer(nq_handle h, const DecodeWorkspace& w, const void* x, voi
     b.rb0 = 0; b.n_rb = (int)n_rowblocks(h->d_out); b.wl = wl_for(b.n_rb); b.pl = 0;
     const int bq_bytes = (int)std::max(n_steps(h->d_in), n_steps(h->r)) * (int)kBqStepBytes;
     const size_t lds_bytes = (size_t)bq_bytes + (size_t)kExecWaves * kExecEpiInts * 4 + kExecWordBytes + (size_t)round_up(h->r, 16) * 4;
-    if (!attr_set) {
-        NQ_HIP(hipFuncSetAttribute((const void*)exec_small_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
-        attr_set = true;
-    }
+    NQ_ALLOW_LDS(exec_small_kernel, 160 * 1024);
     hipLaunchKernelGGL(exec_small_kernel, dim3(1), dim3(kExecThreads), lds_bytes, s, p, bq_bytes);
     NQ_HIP(hipGetLastError());
     return NQ_OK;

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 #include <stdint.h>
+#include <mutex>
 #include <string>
 #include "nq_binlr.h"
 
@@ -171,6 +172,14 @@ int hip_fail(hipError_t e, const char* what, const char* file, int line);
     do {                                                                    \
         hipError_t e__ = (call);                                            \
         if (e__ != hipSuccess) return ::nq::hip_fail(e__, #call, __FILE__, __LINE__); \
+    } while (0)
+// the most dynamic LDS a kernel may ask for, set by whichever thread comes first
+#define NQ_ALLOW_LDS(kernel, bytes)                                         \
+    do {                                                                    \
+        static std::once_flag once__;                                       \
+        static hipError_t set__ = hipSuccess;                               \
+        std::call_once(once__, [] { set__ = hipFuncSetAttribute((const void*)(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(bytes)); }); \
+        if (set__ != hipSuccess) return ::nq::hip_fail(set__, "hipFuncSetAttribute", __FILE__, __LINE__); \
     } while (0)
 
 // ---- output conversion (device code) ---------------------------------------------------------

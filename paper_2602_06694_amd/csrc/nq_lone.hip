@@ -650,11 +650,7 @@ template <int NB, int PL, int W, bool SELFQ>
 static int launch_lone_t(const FusedItem* d_items, int n_rb, const QuantDesc& q, const StageDesc& sd, int max_steps, int batch, int per, hipStream_t s)
 {
     const size_t bytes = SELFQ ? lone_lds_bytes(NB, PL, W, max_steps, per) : (size_t)lone_red_ints(NB, PL, W) * 4;
-    static bool attr_set = false;
-    if (!attr_set) {
-        NQ_HIP(hipFuncSetAttribute((const void*)stage_lone_kernel<NB, PL, W, SELFQ>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLoneLdsBytes));
-        attr_set = true;
-    }
+    NQ_ALLOW_LDS((stage_lone_kernel<NB, PL, W, SELFQ>), kLoneLdsBytes);
     const int pairs = n_rb * ((batch + per - 1) / per);
     const dim3 grid((unsigned)((pairs + 7) / 8 * 8 * (8 / PL)));
     NQ_LAUNCH((stage_lone_kernel<NB, PL, W, SELFQ>), grid, dim3(64 * W), bytes, s, d_items, q, sd, n_rb, batch, per);
@@ -725,11 +721,7 @@ bool lone_layer_fits(const QuantDesc& qt, const StageDesc& s1, const StageDesc& 
 template <int PL>
 static int launch_layer_t(const QuantDesc& qx, const StageDesc& s1, const QuantDesc& qt, const StageDesc& s2, int batch, hipStream_t s)
 {
-    static bool attr_set = false;
-    if (!attr_set) {
-        NQ_HIP(hipFuncSetAttribute((const void*)stage_layer_kernel<PL>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLoneLdsBytes));
-        attr_set = true;
-    }
+    NQ_ALLOW_LDS((stage_layer_kernel<PL>), kLoneLdsBytes);
     const LayerLds l = layer_lds(qt, s1, s2, batch);
     const int n_rb = (int)n_rowblocks(s2.M);
     NQ_LAUNCH((stage_layer_kernel<PL>), dim3((unsigned)((n_rb + 7) / 8 * 8 * (8 / PL))), dim3(64 * kLayerWaves), l.bytes, s, qx, s1, qt, s2, n_rb, batch, l.t_off, l.bqt_off);
