@@ -96,6 +96,15 @@ class Layer:
                                          synth.x_as_f64(x_np, self.x_dtype), rows)
 
 
+def exact_forward(L: "Layer", x_np: np.ndarray) -> np.ndarray:
+    """The same forward through the exact path: what a result of the dense one, whose operands are rounded to fp16, must differ from."""
+    import torch
+    y = new_output(x_np.shape[0], L.d_out, L.y_dtype)
+    nq.nq_binlr_forward_exact(L.h, to_device(x_np, L.x_dtype), y, x_np.shape[0])
+    torch.cuda.synchronize()
+    return output_to_numpy(y)
+
+
 def rel_err(y: np.ndarray, ref: np.ndarray) -> float:
     assert y.shape == ref.shape, (y.shape, ref.shape)
     assert np.isfinite(y).all(), "non-finite output"

@@ -6,7 +6,7 @@ import pytest
 import oracle
 from paper_2602_06694_amd import binding as nq
 from paper_2602_06694_amd import synth
-from gpu_util import DECODE_TOL, Layer, rel_err, to_device
+from gpu_util import DECODE_TOL, Layer, exact_forward, rel_err, to_device
 
 pytestmark = pytest.mark.gpu
 PREFILL_TOL = 7e-4
@@ -107,17 +107,20 @@ def test_plans_and_every_schedule(nqopt):
 
 
 @pytest.mark.parametrize("shape,batch", [((1024, 2048, 512), 64), ((300, 1100, 1030), 40), ((4096, 1024, 3520), 130)])
-def test_dense_path_matches_oracle(shape, batch):
+def test_dense_path_matches_oracle(nqopt, shape, batch):
     """Batches that take the dense matrix-core path; scales up to 16 and down to 1/64 exercise the
     power of two that keeps the fp16 intermediate in range."""
+    nqopt.set("dense_only", 1)
     d_out, d_in, r = shape
     L = Layer(d_out, d_in, r, "bf16", seed=2900 + r)
     x = synth.gen_x(batch, d_in, 2950 + batch, "bf16")
     for gain in (1.0, 16.0, 1.0 / 64):
         s_mid = (mid_scales(r, 2960 + r).astype(np.float32) * gain).astype(np.float16)
         nq.nq_binlr_set_mid_scale(L.h, s_mid)
-        err = rel_err(L.forward(x), mid_oracle(L, s_mid, x))
+        y = L.forward(x)
+        err = rel_err(y, mid_oracle(L, s_mid, x))
         assert err <= PREFILL_TOL, (shape, batch, gain, err)
+        assert not np.array_equal(y, exact_forward(L, x))
     L.close()
 
 

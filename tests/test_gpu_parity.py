@@ -516,6 +516,7 @@ def test_sixteen_bit_outputs_every_path(y_dtype, nqopt):
     x = synth.gen_x(20, shape[1], 530, "bf16")
     check_rounded(Lc.forward(x), Lc.oracle(x), y_dtype, DECODE_TOL)
     Lc.close()
+    nqopt.set("dense_only", 1)
     for batch in (9, 64, 130):
         x = synth.gen_x(batch, shape[1], 520 + batch, "bf16")
         check_rounded(L.forward(x), L.oracle(x), y_dtype, PREFILL_TOL)
@@ -524,6 +525,7 @@ def test_sixteen_bit_outputs_every_path(y_dtype, nqopt):
     Ln = Layer(96, 2048, 1024, "bf16", seed=530, y_dtype=y_dtype)
     x = synth.gen_x(64, 2048, 531, "bf16")
     check_rounded(Ln.forward(x), Ln.oracle(x), y_dtype, PREFILL_TOL)
+    nqopt.unset("dense_only")
     Ln.close()
     Lv = Layer(*shape, "f32", seed=540, y_dtype=y_dtype, flags=nq.NQ_FLAG_DECODE_VALU)
     x = synth.gen_x(2, shape[1], 541, "f32")
@@ -938,14 +940,15 @@ def test_library_used_before_torch_touches_the_gpu_leaves_torch_working():
     assert res.returncode == 0 and "order ok" in res.stdout, res.stderr[-2000:]
 
 
-def test_different_layers_run_side_by_side_on_two_streams():
+def test_different_layers_run_side_by_side_on_two_streams(nqopt):
     """The header promises that forwards of DIFFERENT layers may run at the same time (a layer owns its
     workspace; nothing is shared between layers).  Two layers, two streams of the default priority, many forwards
-    issued alternately without waiting, on every path (streaming with and without a quantisation launch, dense):
+    issued alternately without waiting, on every path (streaming with and without a quantisation launch, more than eight tokens of it, dense):
     each output must be what the same call gives alone, bit for bit, and match the oracle."""
     import torch
     specs = [(1536, 4096, 1024, "bf16"), (1100, 11008, 700, "bf16")]
-    for batch in (1, 8, 70):
+    for batch, dense in ((1, 0), (8, 0), (70, 0), (70, 1)):
+        nqopt.set("dense_only", dense)
         layers = [Layer(*s, seed=6400 + 10 * i) for i, s in enumerate(specs)]
         xs_np = [synth.gen_x(batch, L.d_in, 6450 + i, L.x_dtype) for i, L in enumerate(layers)]
         alone = [L.forward(x) for L, x in zip(layers, xs_np)]

@@ -4,12 +4,18 @@ import pytest
 
 from paper_2602_06694_amd import binding as nq
 from paper_2602_06694_amd import synth
-from gpu_util import BAR, Layer, rel_err, to_device
+from gpu_util import BAR, Layer, exact_forward, rel_err, to_device
 
 pytestmark = pytest.mark.gpu
 
 # x' and t pass through fp16 (11-bit significands, per-token power-of-two guards): a few 1e-4
 PREFILL_TOL = 7e-4
+
+
+@pytest.fixture(autouse=True)
+def dense_path(nqopt):
+    """Small layers take the exact path where it is the faster one; what is tested here is the dense one."""
+    nqopt.set("dense_only", 1)
 
 
 @pytest.mark.parametrize("shape", [(300, 200, 100), (129, 65, 33), (1024, 1024, 256), (640, 1500, 257), (1, 1, 1),
@@ -24,6 +30,7 @@ def test_prefill_small_shapes(shape, x_dtype):
         ref = L.oracle(x)
         err = rel_err(y, ref)
         assert err <= PREFILL_TOL and err <= BAR, (shape, x_dtype, batch, err)
+        assert d_in == 1 or not np.array_equal(y, exact_forward(L, x)), (shape, x_dtype, batch)
     L.close()
 
 
@@ -62,6 +69,7 @@ def test_prefill_matches_streaming_path():
     ref = La.oracle(x)
     assert rel_err(ya, ref) <= PREFILL_TOL
     assert rel_err(yb, ref) <= 1e-5
+    assert not np.array_equal(ya, yb)
     La.close()
     Lb.close()
 
@@ -74,6 +82,7 @@ def test_prefill_tokens_of_very_different_magnitude_and_nan():
     y, ref = L.forward(x), L.oracle(x)
     for b in range(128):
         assert np.abs(y[b] - ref[b]).max() <= PREFILL_TOL * np.abs(ref[b]).max(), b
+    assert not np.array_equal(y, exact_forward(L, x))
     x[5, 7] = np.nan
     x[9] = 0.0
     import torch
@@ -91,7 +100,9 @@ def test_prefill_tokens_of_very_different_magnitude_and_nan():
     L.close()
 
 
-def test_prefill_reserve_and_batch_changes():
+@pytest.mark.parametrize("dense", [True, False])
+def test_prefill_reserve_and_batch_changes(nqopt, dense):
+    nqopt.set("dense_only", int(dense))
     d_out, d_in, r = 700, 300, 130
     L = Layer(d_out, d_in, r, "bf16", seed=21)
     nq.nq_binlr_reserve(L.h, 512)
@@ -156,11 +167,13 @@ def test_prefill_eight_wave_workgroups_by_default(nqopt):
     L.close()
 
 
-def test_reserve_covers_every_batch_up_to_the_reserved_one():
+@pytest.mark.parametrize("dense", [True, False])
+def test_reserve_covers_every_batch_up_to_the_reserved_one(nqopt, dense):
     """The dense path's workspace need is not monotone in the batch (small batches split the reduction
     and keep partial sums).  After nq_binlr_reserve(h, 2048) a forward at ANY batch <= 2048 must leave
     the workspace as it is (no reallocation, hence no synchronisation on the stream)."""
     import torch
+    nqopt.set("dense_only", int(dense))
     for shape in [(2048, 7168, 880), (7168, 2048, 880)]:     # the 70B MLP shapes at a quarter of their size
         L = Layer(*shape, "bf16", seed=5200)
         nq.nq_binlr_reserve(L.h, 2048)

@@ -7,12 +7,18 @@ import pytest
 
 from paper_2602_06694_amd import binding as nq
 from paper_2602_06694_amd import synth
-from gpu_util import Layer, check_rounded, new_output, rel_err, to_device
+from gpu_util import Layer, check_rounded, exact_forward, new_output, rel_err, to_device
 
 pytestmark = pytest.mark.gpu
 
 # x'' and T are rounded to fp16 (2^-11 relative each, as pair sums and differences; random signs): a few 1e-4 of the largest output
 PREFILL_TOL = 7e-4
+
+
+@pytest.fixture(autouse=True)
+def dense_path(nqopt):
+    """Small layers take the exact path where it is the faster one; what is tested here is the dense one."""
+    nqopt.set("dense_only", 1)
 
 
 def unit_layer(d_out, d_in, r, x_dtype, y_dtype, seed):
@@ -51,7 +57,7 @@ def test_odd_row_lengths(d_out, d_in, r, batch, x_dtype, y_dtype):
     L = Layer(d_out, d_in, r, x_dtype, seed=8300 + r, y_dtype=y_dtype)
     x = synth.gen_x(batch, d_in, 8400 + batch, x_dtype)
     y, ref = L.forward(x), L.oracle(x)
-    assert np.isfinite(y).all()
+    assert np.isfinite(y).all() and not np.array_equal(y, exact_forward(L, x))
     if y_dtype == "f32":
         assert rel_err(y, ref) <= PREFILL_TOL
     else:
@@ -145,7 +151,7 @@ def test_largest_tokens_that_fp16_operands_hold(unit):
         x[b] = (x[b].astype(np.float64) * top / np.abs(xp).max()).astype(np.float32)
         x[b, :8] = np.sign(x[b, :8]) * np.abs(x[b].astype(np.float64) * s_in).max() / s_in[:8].astype(np.float64) * 0.999      # pairs of large columns
     y, ref = L.forward(x), L.oracle(x)
-    assert np.isfinite(y).all()
+    assert np.isfinite(y).all() and not np.array_equal(y, exact_forward(L, x))
     for b in range(24):
         assert np.abs(y[b] - ref[b]).max() <= PREFILL_TOL * np.abs(ref[b]).max(), b
     L.close()
@@ -205,6 +211,7 @@ def test_large_mean_and_uniform_sign_columns_in_pairs():
     x[2] = -x[2]
     x[3, ::2] = 0.0
     y, ref = L.forward(x), L.oracle(x)
+    assert not np.array_equal(y, exact_forward(L, x))
     for b in range(batch):
         assert np.abs(y[b] - ref[b]).max() <= PREFILL_TOL * np.abs(ref[b]).max(), b
     L.close()

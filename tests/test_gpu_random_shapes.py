@@ -1,5 +1,5 @@
 """Seeded random shapes, batches and storage types through the forward entry points against the fp64 oracle: single
-calls on both paths (streaming up to batch 8, dense above), plans with random tuning options against single calls bit
+calls on both paths (streaming up to batch 8; above, the one that the library takes and the dense one), plans with random tuning options against single calls bit
 for bit, and chains of decoder-shaped blocks through the executor.  The fixed-shape tests cover the cases that were
 thought of; this one covers ragged combinations nobody listed."""
 import numpy as np
@@ -41,7 +41,7 @@ def random_shape(g):
     return int(g.integers(1, 600)), int(g.integers(3000, 12000)), int(g.integers(1, 600))
 
 
-def test_single_calls_on_random_shapes():
+def test_single_calls_on_random_shapes(nqopt):
     g = np.random.default_rng(20260628)
     for c in range(400):
         d_out, d_in, r = random_shape(g)
@@ -51,12 +51,15 @@ def test_single_calls_on_random_shapes():
         print(f"case {c}: {d_out}x{d_in} r={r} B={batch} x={x_dtype} y={y_dtype}", flush=True)
         L = Layer(d_out, d_in, r, x_dtype, seed=7000 + c, y_dtype=y_dtype)
         x = synth.gen_x(batch, d_in, 9000 + c, x_dtype)
-        y = L.forward(x)
         tol = DECODE_TOL if batch <= 8 else DENSE_TOL
-        if y_dtype == "f32":
-            close_enough(y, L, x, tol)
-        else:
-            check_rounded(y, L.oracle(x), y_dtype, 4 * tol)
+        for dense in (0, 1) if batch > 8 else (0,):
+            nqopt.set("dense_only", dense)
+            y = L.forward(x)
+            if y_dtype == "f32":
+                close_enough(y, L, x, tol)
+            else:
+                check_rounded(y, L.oracle(x), y_dtype, 4 * tol)
+        nqopt.unset("dense_only")
         L.close()
 
 

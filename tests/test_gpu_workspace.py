@@ -73,12 +73,14 @@ def test_reservations_without_the_dense_path():
     L.close()
 
 
-@pytest.mark.parametrize("exact", [False, True])
-def test_graphs_captured_before_the_workspace_grew(exact):
+@pytest.mark.parametrize("path", ["dense", "exact", "forward"])
+def test_graphs_captured_before_the_workspace_grew(nqopt, path):
     import torch
+    if path == "dense":
+        nqopt.set("dense_only", 1)
     d_out, d_in, r, batch = 600, 1000, 300, 40
     L = Layer(d_out, d_in, r, "bf16", seed=9400)
-    call = nq.nq_binlr_forward_exact if exact else nq.nq_binlr_forward
+    call = nq.nq_binlr_forward_exact if path == "exact" else nq.nq_binlr_forward
     x, y, eager = to_device(synth.gen_x(batch, d_in, 9401, "bf16"), "bf16"), new_output(batch, d_out), new_output(batch, d_out)
     big_x, big_y = to_device(synth.gen_x(2048, d_in, 9402, "bf16"), "bf16"), new_output(2048, d_out)
     nq.nq_binlr_reserve(L.h, batch)
@@ -98,6 +100,10 @@ def test_graphs_captured_before_the_workspace_grew(exact):
         torch.cuda.synchronize()
         assert torch.equal(y, eager), rep
     assert all(bool((o == 3.0).all()) for o in others)    # nobody else's memory was written
+    if path == "dense":
+        nq.nq_binlr_forward_exact(L.h, x, eager, batch)
+        torch.cuda.synchronize()
+        assert not torch.equal(y, eager)
     del graph
     L.close()
 
