@@ -338,7 +338,7 @@ __device__ __forceinline__ void static_for(F f)
 // not > 0 sets *status (the results are then meaningless, every thread still finishes).
 // A21 != nullptr: the block is the first tile of the trailing update of the block column before it, whose inverted diagonal block is X11: first
 //  P = A21 X11^T,  which goes to L21 (both with leading dimension ldh), and  A <- A - P P^T,  so that the update's other tiles can run beside this
-// kernel's work.  Everything is requested at once and P stays in LDS (with the tiles' bodies below: step launch 24 -> 19 us on its own, 58 -> 52 beside the product with W).
+// kernel's work.  Everything is requested at once and P stays in LDS (with the tiles' bodies below: step launch 24 -> 19 us on its own, 52 beside the product with W).
 // lds: kPotrfLdsBytes bytes.
 // registers for three waves per SIMD (168), so that such a workgroup fits beside one of the product with W (328): otherwise it waits 800 us for its end
 constexpr int kStepWavesPerEu = 3;
@@ -599,7 +599,7 @@ struct StepArgs {
     double* S;          // [..][ld] sums behind the rows of L^-1 still to come, or nullptr
 };
 
-constexpr size_t kStepLdsBytes = 2 * kNB * kPitchP * sizeof(double);       // two blocks; beside the product with W (88 KiB) that still fits a CU
+constexpr size_t kStepLdsBytes = 2 * kNB * kPitchP * sizeof(double);       // two blocks, 65 KiB; beside the product with W (80.5) that still fits a CU
 
 // INV = false: C -= P_i P_j^T with P_j from B = A21_j (the same as P_i where B is nullptr); INV = true: C (+)= P_i Y with Y = -X11 B, B = S_kj, or Y = X11
 // (B nullptr).  P_i = A21_i X11^T.  store_p: where P_i goes, store_y: Y (leading dimension ld), or nullptr.

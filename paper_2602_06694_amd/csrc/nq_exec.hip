@@ -16,11 +16,11 @@
 //    copy clears it in the other, which nobody reads before the next launch.  The number lives in device memory and is
 //    advanced by the last workgroup to leave, so a replay of a captured launch takes the copies in turn too.
 //
-// What bounds it: 256 dependent phases of 4.35 us per token of a 7B-shaped stack.  Of those the hand-over is 1.5 to 3.3 us (6 to 10 for 28672
-// values): a store, half a polling period and a read past the L2, and the contention of up to 128 workgroups that all read the whole
-// input.  Then 0.5 to 0.9 us for the fixed point, 0.7 to 1.7 for the products, 0.5 for adding them up and storing.  As pairs of value and launch number, read 16
-// elements per lane (a line per 16-byte request), hand-overs took 2.4 to 5 us (17 of 28672 values); whole row blocks per workgroup,
-// loops over the longest input's groups without an exit and addresses spilled from phase to phase cost another 1.5 us: 1818 -> 1110 us per token.
+// What bounds it: 256 dependent phases of 4.25 us per token of a 7B-shaped stack.  Of those the hand-over, from the last store to the last workgroup that has its
+// input, is 1.3 to 2.7 us (a store, half a polling period and a read past the L2; 3.3 where 86 workgroups store, 4.8 where 104 read 11008 values, 6 for 28672), the
+// fixed point 0.4 to 0.7 (0.8, 1.6), the products 0.7 to 1.9 (a long reduction or many rows: 2.9 to 5.5), adding them up and storing 0.3 to 0.45.  As pairs of value and
+// launch number, read 16 elements per lane (a line per 16-byte request), hand-overs took 2.4 to 5 us (17 of 28672 values); whole row blocks per workgroup,
+// loops over the longest input's groups without an exit and addresses spilled from phase to phase cost another 1.5 us: 1818 -> 1089 us per token.
 //  - every wait is bounded by a wall-clock limit; a workgroup that gives up sets an error word
 //    and leaves, the others see the word (or run into their own limit) and leave too: the grid
 //    always drains.  (They clear the other copies of what their tasks would have stored first.)
