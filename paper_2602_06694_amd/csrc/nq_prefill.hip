@@ -696,7 +696,12 @@ prefill_gemm_kernel(GemmArgs a)
             for (int tl = 0; tl < 2; ++tl) {
 #pragma unroll
                 for (int p = 0; p < 8; ++p) acc[p][2 * round + tl] += *(const v4f*)(xr + ((tl * 8 + p) * 64 + lane) * 4);
-                __builtin_amdgcn_sched_barrier(0);          // (eight reads in flight, not sixteen: registers)
+                // (eight reads in flight, not sixteen: registers)
+                // The sums are complete before the barrier: only waves of the first part use them further on, and left to itself the compiler
+                // moves the last round's reads past the barrier into the code of those, where the epilogue's regions of other waves
+                // may already have been written over what is read.
+#pragma unroll
+                for (int p = 0; p < 8; ++p) asm volatile("" : "+v"(acc[p][2 * round + tl]));
             }
             __syncthreads();
         }
