@@ -1039,7 +1039,7 @@ extern "C" int nq_plan_create(nq_plan* out, const nq_handle* hs, const void* con
         // batch 4 21.1 -> 15.0; the seven projections of a 7B-shaped one as four plans at batch 4 76 -> 57.
         int how = w;
         if (batch > 1 && total_rb <= device_cu_count() && total_rb < schedule_full_rowblocks() && !opt_flag(OPT_NO_SELFQ) && opt(OPT_FORCE_W) < 0) {
-            if (lone_selfq(max_steps, total_rb, batch)) how = kLoneSchedule;
+            if (lone_plan_selfq(max_steps, total_rb, batch)) how = kLoneSchedule;
             else if (lone_planes(total_rb) < 8 && !is_wide_split(w)) how = 16;
             // (nq_plan_schedules names them only for the launches that it has named them for so far; programs compare its answers)
             if ((batch > 2 || (how == kLoneSchedule && n <= 4)) && max_steps <= 176) w = how;
@@ -1183,7 +1183,7 @@ static int plan_run(nq_plan p, hipStream_t s, bool timed)
     auto run_stage = [&](int w, const StageDesc* sd, const WorkItem* items, const FusedItem* fitems, int n_items,
                          int max_steps) {
         // (the same 16 waves per workgroup, each taking some bit planes of a row block: stage 1 of the q, k, v of a 70B-shaped block)
-        if (w == kFusedSchedule && n_items <= device_cu_count() && lone_planes(n_items) < 8 && lone_selfq(max_steps, n_items, p->batch))
+        if ((w == kFusedSchedule || w == kSelfqSchedule1 || w == kSelfqSchedule4) && n_items <= device_cu_count() && lone_planes(n_items) < 8 && lone_selfq(max_steps, n_items, p->batch))
             return launch_lone_selfq(fitems, n_items, qdummy, sdummy, max_steps, p->batch, s);
         if (w == kFusedSchedule) return launch_fused_list(fitems, n_items, max_steps, s);
         if (w == kSelfqSchedule1 || w == kSelfqSchedule4)

@@ -333,6 +333,7 @@ int launch_gemm_t(const uint32_t* tiles, int64_t M, int64_t N, const void* in, i
 constexpr int kLoneSchedule = 35;        // plan schedule code: few row blocks, batch 2 to 8, the workgroups quantise the input
 int lone_planes(int n_rb);
 bool lone_selfq(int max_steps, int n_rb, int batch);
+bool lone_plan_selfq(int max_steps, int n_rb, int batch);
 bool lone_shared_pairs(int n_rb, int batch);
 bool lone_deals_out(int n_rb, int steps, bool whole, int batch);      // whole: the input's rows start 16-byte aligned and end with 16 elements
 int launch_lone_selfq(const FusedItem* d_items, int n_rb, const QuantDesc& q, const StageDesc& sd, int max_steps, int batch, hipStream_t s);

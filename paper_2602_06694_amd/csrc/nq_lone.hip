@@ -1,19 +1,19 @@
 // Stages of the streaming path for launches that are far from filling the chip: a layer on its own, or the few layers of
 // one level of a decoder block (Section 3.1 Eq. 1 as two sign-matrix x vector products, Appendix E.2).  Such a launch is bound by latency:
 // by the host, which takes 2.7 to 3 us per launch, and by the chain  input -> fixed point -> tiles -> sums -> store  of a workgroup.
-//   - The workgroups of a stage quantise its input themselves where it is short (SELFQ): one launch instead of two.
-//   - A row block is dealt out to 8 / PL workgroups by BIT PLANES: each streams the same tiles, multiplies PL of the eight planes (16
-//     rows each) and finishes its own rows, so that nothing has to be added up between workgroups.  They share an XCD and its L2.
+//   - The workgroups of a stage quantise its input themselves where it is short: one launch instead of two.
+//   - A row block is dealt out to several workgroups, which share an XCD and its L2: by groups of TOKENS first, because the fixed point of a workgroup's tokens is the
+//     longest link of its chain and only tokens divide it, and by BIT PLANES: each streams the same tiles, multiplies PL of the eight planes (16
+//     rows each) and finishes its own rows, so that nothing has to be added up between workgroups.
 //   - More than eight tokens (batch 9 and more through the exact path) are dealt out in groups of up to eight as well.
 //   - stage_layer_kernel: a small layer in ONE launch, every workgroup computing the whole of t for itself.
 // The arithmetic is that of quantize_kernel and stage_split_kernel (nq_decode.hip) element for element: the same bits.
 //
-// Whole forwards, us per call, against four launches (batch 1: two self-quantising ones of one, four or 16 waves per row block, each with all
-// planes of it); what two launches cost the host alone is 8.8:
-//   4096 x 4096 r = 1024   batch 1 11.1 -> 8.9, 2 15.5 -> 9.1, 4 15.8 -> 10.1, 8 22.8 -> 13.1
-//   5003 x 3001 r = 777    batch 6 25.0 -> 13.3        1024 x 1024 r = 256   batch 1 10.4 -> 8.0 (one launch), 4 13.6 -> 9.0
-//   8192 x 8192 r = 2240   batch 1 16.5 -> 9.8, 4 20.5 -> 13.6, 8 28.6 -> 20.6 (stage 1 after a quantisation launch)
-//   8192 x 28672 r = 3520  batch 1 29.0 -> 15.2, 4 34.3 -> 25.3 (likewise); 28672 x 8192 r = 3520 batch 1 18.2 -> 12.3, 4 22.3 -> 17.8
+// Whole forwards, us per call: four launches (batch 1: two self-quantising ones) / two, planes dealt out / tokens and planes; what two launches cost the host is 6:
+//   4096 x 4096 r = 1024   batch 1 11.1 / 8.9 / 8.9, 4 15.8 / 10.6 / 9.9, 8 22.8 / 13.3 / 10.6, 24 27.4 (dense path) / 15.4 / 11.8
+//   5003 x 3001 r = 777    batch 6 25.0 / 13.4 / 10.4        1024 x 1024 r = 256   batch 1 10.4 / 8.0 (one launch) / 7.9
+//   1408 x 21251 r = 999   batch 7 27.1 (planes) / 14.5      384 x 13516 r = 96    batch 8 23.9 / 11.7
+// 150 random layers from 256 to 28672 a side at batch 1 to 8: 0.81 to 0.85 of the time of planes alone (geometric mean), none slower than their scatter.
 #include <algorithm>
 
 #include "nq_internal.h"
@@ -29,6 +29,9 @@ typedef const __attribute__((address_space(4))) QMeta* cptr_meta;
 // (4096 x 4096 at batch 8 15.0 us without it, 14.8 with; 8192 wide at batch 4 20.4 and 21.0).
 constexpr int kLoneMaxElements = 32768;
 template <int W, int E> constexpr int lone_share_units() { return kLoneMaxElements / (64 * E) / W; }
+// ... of a kernel that takes four at a time only where they are few
+constexpr int kFewElements = 16384;
+template <int W, int E> constexpr int along_units() { return (E == 4 ? kFewElements : kLoneMaxElements) / (64 * E) / W; }
 constexpr int kLonePlaneInts = 4 * 68;     // a wave's sums of one bit plane in LDS: four row groups of 16 columns x 4 rows, 68 ints apart (banks)
 
 template <int E> __host__ __device__ inline int lone_pieces(int nst) { return (nst + E - 1) / E; }      // units per token
@@ -37,7 +40,9 @@ template <int E> __host__ __device__ inline int lone_pieces(int nst) { return (n
 __host__ __device__ inline int lone_tok_bytes(int nst) { return nst * (int)kBqStepBytes + 48; }
 // bit planes whose sums pass through LDS at a time
 constexpr int lone_round(int nb, int pl) { return pl < 4 / nb ? pl : 4 / nb; }
-constexpr int lone_red_ints(int nb, int pl, int w) { return w * nb * lone_round(nb, pl) * kLonePlaneInts; }
+// ints between the waves' sums: 16 modulo 32, because the four lanes that add up a result start at four waves
+__host__ __device__ constexpr int lone_wave_ints(int ints) { return (ints + 15) / 32 * 32 + 16; }
+constexpr int lone_red_ints(int nb, int pl, int w) { return w * lone_wave_ints(nb * lone_round(nb, pl) * kLonePlaneInts); }
 
 // What the units of a launch's tokens leave in LDS: the bits of their largest magnitude and the sum of their q
 struct LoneTokens {
@@ -174,10 +179,9 @@ __device__ __forceinline__ void lone_value(const QuantDesc& d, const LoneRaw<E>&
 
 // A wave's share of the units (value(c, token, first element, v): the lane's elements of unit c, scaled) -> fixed point in `bq`, all waves of the
 // workgroup together.  *lt is cleared, and a barrier has passed since.
-template <int W, int E, class Value>
+template <int W, int E, int kU, class Value>
 __device__ __forceinline__ void lone_quantise(Value value, const LoneShare& share, int pieces, int nst, int lane, LoneTokens* lt, char* bq)
 {
-    constexpr int kU = lone_share_units<W, E>();
     float hv[kU][E];
     LoneShare sh = share;
     uint32_t m = 0;                                        // (as bits: magnitudes order like them, NaN above all)
@@ -264,13 +268,169 @@ __device__ __forceinline__ double lone_raw(const int* q, int wave_ints, int wave
     return fma((double)s[0], 65536.0, fma((double)s[1], 256.0, (double)s[2]));
 }
 
-// grid: 8 x ceil(pairs / 8) x (8 / PL) workgroups for the pairs of row block and group of `per` tokens; items: n_rb row blocks of several ops (one
-// group), or nullptr: those of the one op (q1, s1)
-template <int NB, int PL, int W, bool SELFQ>
+// How a launch of the kernel below is dealt out: `groups` groups of up to `per` tokens (even sizes), PL bit planes per workgroup.  A unit is a row block
+// of a group; the 8 / PL workgroups of one are 8 apart, i.e. on one XCD, and so are the groups of a row block, which stream the same tiles through
+// that XCD's L2 (`spread`: units dealt to all XCDs, where more groups than that leaves room for make the launch).
+struct LoneDeal {
+    int n_rb, tokens, per, groups, spread;
+};
+
+// ints between the row groups of a wave's sums of one bit plane in LDS: the columns in use (three per token) x 4 rows and a gap, 4 or 12 modulo 16,
+// so that what a wave reads of four row groups and (lone_wave_ints) four waves falls on different banks
+__host__ __device__ inline int along_row_ints(int per) { return 12 * per + 4 + 4 * (per & 1); }
+
+// A stage whose workgroups quantise their own group's tokens (E elements of a lane at a time) and multiply PL bit planes of a row block by them.
+// Bound by a chain of latencies, of which the fixed point was the longest: 32 elements per thread take 3.2 us, so tokens are dealt out before planes
+// are.
+// items: n_rb row blocks of several ops, or nullptr: those of the one op (q1, s1).
+template <int NB, int PL, int W, int E>
 __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W / 4, W / 4)))
-stage_lone_kernel(const FusedItem* __restrict__ items, QuantDesc q1, StageDesc s1, int n_rb, int tokens, int per)
+stage_along_kernel(const FusedItem* __restrict__ items, QuantDesc q1, StageDesc s1, LoneDeal d)
 {
-    constexpr int D = W == 8 ? 8 : 4, S = 8 / PL, R = lone_round(NB, PL), kWaveInts = NB * R * kLonePlaneInts;
+    constexpr int D = W == 8 ? 8 : 4, S = 8 / PL, kUnits = along_units<W, E>();
+    extern __shared__ __align__(16) int lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, n = lane & 15;
+    const int x = blockIdx.x & 7, j = blockIdx.x >> 3, p0 = j % S * PL;
+    int group = 0, at = x + 8 * (j / S);                    // (item or row block)
+    if (d.groups > 1) {
+        const int by = d.spread ? d.n_rb : d.groups, k = d.spread ? at : j / S;
+        const int quot = __builtin_amdgcn_readfirstlane((int)(((float)k + 0.5f) * __builtin_amdgcn_rcpf((float)by)));      // (exact for the small integers that occur)
+        group = d.spread ? quot : k - quot * by;
+        at = d.spread ? k - quot * by : x + 8 * quot;
+    }
+    if (at >= d.n_rb || group >= d.groups) return;
+    QuantDesc qd = q1;
+    StageDesc sd = s1;
+    int rb = at;
+    if (items) {
+        const FusedItem* e = items + at;
+        rb = e->rb;
+        qd = e->q;
+        sd = e->s;
+    }
+    const int nst = sd.n_steps;
+    const int64_t first = (int64_t)group * d.per;           // of the group's tokens
+    const int batch = d.tokens - (int)first < d.per ? d.tokens - (int)first : d.per;
+    const int row_ints = along_row_ints(d.per), wave_ints = lone_wave_ints(PL * 4 * row_ints);
+    int* const red = lds;                                   // [W][PL][4 row groups][columns][4 rows]
+    LoneTokens* const lt = (LoneTokens*)(lds + W * wave_ints);
+    char* const bq = (char*)(lt + 1);
+    const int pieces = lone_pieces<E>(nst), units = batch * pieces;
+
+    const LoneShare share = lone_share<W>(units, pieces, wave);
+    LoneRaw<E> raw[kUnits];
+    lone_clear(lt, tid);
+    {
+        LoneShare sh = share;
+#pragma unroll
+        for (int c = 0; c < kUnits; ++c) {
+            if (c < share.n) {
+                lone_request(qd, (first + sh.tok) * qd.x_stride, (sh.piece * 64 + lane) * E, raw[c]);
+                lone_next(sh, pieces);
+            }
+        }
+    }
+    // the first tiles: steps wave, wave + W, ... (a short share re-reads its last tile)
+    const int cnt = (nst - wave + W - 1) / W;
+    const int st0 = cnt > 0 ? wave : 0;
+    const char* const a_base = (const char*)sd.tiles + (size_t)rb * nst * (kTileWords * 4);
+    const uint32_t a_off = (uint32_t)(st0 * 1024 + lane * 16);
+    uint32_t b_off[NB];
+#pragma unroll
+    for (int cg = 0; cg < NB; ++cg) {
+        int tok, slice;
+        lone_column(cg, n, batch, tok, slice);
+        b_off[cg] = (uint32_t)(tok * lone_tok_bytes(nst) + (g * kSlices + slice) * 16 + st0 * (int)kBqStepBytes);
+    }
+    v4u wbuf[D];
+#define NQ_ISSUE(k, i) wbuf[k] = load_global_v4u(a_base, a_off + (uint32_t)(i) * (W * 1024))
+#pragma unroll
+    for (int k = 0; k < D; ++k) NQ_ISSUE(k, k < cnt ? k : (cnt > 0 ? cnt - 1 : 0));
+    // A thread finishes the same row of all of its tokens: that row's output scale, requested behind everything that is waited for sooner (and whether there
+    // is one or not, so that those waits stay exact: ahead of the tiles, in a branch, it cost stage 2 of 4096 x 4096 at batch 1 0.3 of 4.2 us).
+    constexpr int kRows = 16 * PL;
+    static_assert(16 * W % kRows == 0, "whole tokens between a thread's results");
+    const int row = (tid >> 2) % kRows, grow = rb * kTileRows + 16 * p0 + row;
+    const uint16_t oscale = *(sd.out_scale ? (gptr_u16)sd.out_scale + (grow < sd.M ? grow : 0) : (gptr_u16)sd.tiles);
+    __syncthreads();
+    lone_quantise<W, E, kUnits>([&](int c, int, int j0, float v[E]) { lone_value(qd, raw[c], j0, v); }, share, pieces, nst, lane, lt, bq);
+
+    uint32_t mask[PL];
+#pragma unroll
+    for (int p = 0; p < PL; ++p) mask[p] = 0x01010101u << (p0 + p);
+    v4i acc[NB][PL];
+#pragma unroll
+    for (int cg = 0; cg < NB; ++cg)
+#pragma unroll
+        for (int p = 0; p < PL; ++p) acc[cg][p] = v4i{0, 0, 0, 0};
+#define NQ_MAC(k, i)                                                                                              \
+    do {                                                                                                          \
+        v4u b[NB];                                                                                                \
+        _Pragma("unroll") for (int cg = 0; cg < NB; ++cg) b[cg] = *(const v4u*)(bq + b_off[cg] + (i) * (W * (int)kBqStepBytes)); \
+        _Pragma("unroll") for (int p = 0; p < PL; ++p) {                                                          \
+            const v4i a = (v4i)(wbuf[k] & mask[p]);                                                               \
+            _Pragma("unroll") for (int cg = 0; cg < NB; ++cg)                                                     \
+                acc[cg][p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, (v4i)b[cg], acc[cg][p], 0, 0, 0);           \
+        }                                                                                                         \
+    } while (0)
+    // (whole passes over the ring without a branch, so that the waits inside stay partial; then the last D to 2 D - 1 steps)
+    int i0 = 0;
+    for (; i0 + 2 * D <= cnt; i0 += D) {
+#pragma unroll
+        for (int k = 0; k < D; ++k) {
+            NQ_MAC(k, i0 + k);
+            NQ_ISSUE(k, i0 + k + D);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+        if (i0 + k < cnt) {
+            NQ_MAC(k, i0 + k);
+            if (i0 + k + D < cnt) NQ_ISSUE(k, i0 + k + D);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+        if (i0 + D + k < cnt) {
+            NQ_MAC(k, i0 + D + k);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#undef NQ_MAC
+#undef NQ_ISSUE
+    // the waves' partial sums of every result
+#pragma unroll
+    for (int cg = 0; cg < NB; ++cg)
+        if (n < (cg == 0 && NB > 1 ? 15 : 3 * d.per - 15 * cg)) {
+#pragma unroll
+            for (int p = 0; p < PL; ++p) *(v4i*)(red + wave * wave_ints + (p * 4 + g) * row_ints + (15 * cg + n) * 4) = acc[cg][p];
+        }
+    __syncthreads();
+    const int quad = tid & 3, p = p0 + (row >> 4);
+    const float scale = sd.out_scale ? half_bits_to_float(oscale) : 1.0f;
+    const int64_t out0 = first * sd.out_stride + grow;
+    for (int tok = (tid >> 2) / kRows; tok < batch; tok += 16 * W / kRows) {
+        double sum = lone_raw<W>(red + (row >> 2) * row_ints + 12 * tok + (row & 3), wave_ints, W, quad);
+        const QMeta mt = lone_meta(lt, tok);
+        if (quad != 0 || grow >= sd.M) continue;
+        if (p == 7) sum = -sum;                            // bit 7 of an int8 is worth -128
+        const double val = fma(sum, __builtin_ldexp(mt.two_step, -p), mt.neg_qs);     // exact
+        store_out(sd.out, sd.out_dtype, (size_t)(out0 + (int64_t)tok * sd.out_stride), (float)val * scale, sd.out_scale != nullptr);
+    }
+}
+
+// The same on an input that a launch of its own has quantised (too long to quantise along).
+// grid: 8 x ceil(pairs / 8) x (8 / PL) workgroups for the pairs of row block and group of `per` tokens; items: n_rb row blocks of several ops (one
+// group), or nullptr: those of the one op (s1)
+template <int NB, int PL, int W>
+__global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W / 4, W / 4)))
+stage_lone_kernel(const FusedItem* __restrict__ items, StageDesc s1, int n_rb, int tokens, int per)
+{
+    constexpr int D = W == 8 ? 8 : 4, S = 8 / PL, R = lone_round(NB, PL), kWaveInts = lone_wave_ints(NB * R * kLonePlaneInts);
     extern __shared__ __align__(16) int lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -284,12 +444,10 @@ stage_lone_kernel(const FusedItem* __restrict__ items, QuantDesc q1, StageDesc s
         rb = at - group * n_rb;
         if (group * per >= tokens) return;
     } else if (at >= n_rb) return;
-    QuantDesc qd = q1;
     StageDesc sd = s1;
     if (items) {
         const FusedItem* e = items + at;
         rb = e->rb;
-        qd = e->q;
         sd = e->s;
     }
     const int nst = sd.n_steps;
@@ -298,52 +456,27 @@ stage_lone_kernel(const FusedItem* __restrict__ items, QuantDesc q1, StageDesc s
     const int64_t out0 = first * sd.out_stride;
     const char* const bq0 = (const char*)sd.bq + first * nst * kBqStepBytes;
     int* const red = lds;
-    LoneTokens* const lt = (LoneTokens*)(lds + lone_red_ints(NB, PL, W));
-    char* const bq = (char*)(lt + 1);
-    const int pieces = lone_pieces<16>(nst), units = batch * pieces;
-
-    const LoneShare share = lone_share<W>(units, pieces, wave);
-    LoneRaw<16> raw[lone_share_units<W, 16>()];
-    if (SELFQ) {
-        lone_clear(lt, tid);
-        LoneShare sh = share;
-#pragma unroll
-        for (int c = 0; c < lone_share_units<W, 16>(); ++c) {
-            if (c < share.n) {
-                lone_request(qd, (first + sh.tok) * qd.x_stride, (sh.piece * 64 + lane) * 16, raw[c]);
-                lone_next(sh, pieces);
-            }
-        }
-    }
     // the first tiles: steps wave, wave + W, ... (a short share re-reads its last tile)
     const int cnt = (nst - wave + W - 1) / W;
     const int st0 = cnt > 0 ? wave : 0;
     const char* const a_base = (const char*)sd.tiles + (size_t)rb * nst * (kTileWords * 4);
     const uint32_t a_off = (uint32_t)(st0 * 1024 + lane * 16);
-    const char* const b_base = SELFQ ? bq : bq0;
     uint32_t b_off[NB];
 #pragma unroll
     for (int cg = 0; cg < NB; ++cg) {
         int tok, slice;
         lone_column(cg, n, batch, tok, slice);
-        b_off[cg] = SELFQ ? (uint32_t)(tok * lone_tok_bytes(nst) + (g * kSlices + slice) * 16)
-                          : (uint32_t)tok * ((uint32_t)nst * kBqStepBytes) + (uint32_t)(bq_piece(g, slice) * 16);
+        b_off[cg] = (uint32_t)tok * ((uint32_t)nst * kBqStepBytes) + (uint32_t)(bq_piece(g, slice) * 16);
     }
-    v4u wbuf[D], bbuf[SELFQ ? 1 : D][NB];
+    v4u wbuf[D], bbuf[D][NB];
 #define NQ_ISSUE(k, i)                                                                                            \
     do {                                                                                                          \
         wbuf[k] = load_global_v4u(a_base, a_off + (uint32_t)(i) * (W * 1024));                                    \
-        if (!SELFQ) {                                                                                             \
-            _Pragma("unroll") for (int cg = 0; cg < NB; ++cg)                                                     \
-                bbuf[SELFQ ? 0 : (k)][cg] = load_global_v4u(b_base, b_off[cg] + (uint32_t)(st0 + (i) * W) * kBqStepBytes); \
-        }                                                                                                         \
+        _Pragma("unroll") for (int cg = 0; cg < NB; ++cg)                                                         \
+            bbuf[k][cg] = load_global_v4u(bq0, b_off[cg] + (uint32_t)(st0 + (i) * W) * kBqStepBytes);             \
     } while (0)
 #pragma unroll
     for (int k = 0; k < D; ++k) NQ_ISSUE(k, k < cnt ? k : (cnt > 0 ? cnt - 1 : 0));
-    if (SELFQ) {
-        __syncthreads();
-        lone_quantise<W, 16>([&](int c, int, int j0, float v[16]) { lone_value(qd, raw[c], j0, v); }, share, pieces, nst, lane, lt, bq);
-    }
 
     uint32_t mask[PL];
 #pragma unroll
@@ -355,13 +488,10 @@ stage_lone_kernel(const FusedItem* __restrict__ items, QuantDesc q1, StageDesc s
         for (int p = 0; p < PL; ++p) acc[cg][p] = v4i{0, 0, 0, 0};
 #define NQ_MAC(k, i)                                                                                              \
     do {                                                                                                          \
-        v4u b[NB];                                                                                                \
-        _Pragma("unroll") for (int cg = 0; cg < NB; ++cg)                                                         \
-            b[cg] = SELFQ ? *(const v4u*)(b_base + b_off[cg] + (st0 + (i) * W) * (int)kBqStepBytes) : bbuf[SELFQ ? 0 : (k)][cg]; \
         _Pragma("unroll") for (int p = 0; p < PL; ++p) {                                                          \
             const v4i a = (v4i)(wbuf[k] & mask[p]);                                                               \
             _Pragma("unroll") for (int cg = 0; cg < NB; ++cg)                                                     \
-                acc[cg][p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, (v4i)b[cg], acc[cg][p], 0, 0, 0);           \
+                acc[cg][p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, (v4i)bbuf[k][cg], acc[cg][p], 0, 0, 0);     \
         }                                                                                                         \
     } while (0)
     // (whole passes over the ring without a branch, so that the waits inside stay partial; then the last D to 2 D - 1 steps)
@@ -411,11 +541,8 @@ stage_lone_kernel(const FusedItem* __restrict__ items, QuantDesc q1, StageDesc s
             if (quad != 0 || grow >= sd.M) continue;
             if (p == 7) raw = -raw;                        // bit 7 of an int8 is worth -128
             QMeta mt;
-            if (SELFQ) mt = lone_meta(lt, tok);
-            else {
-                mt.two_step = ((cptr_meta)sd.meta)[first + tok].two_step;
-                mt.neg_qs = ((cptr_meta)sd.meta)[first + tok].neg_qs;
-            }
+            mt.two_step = ((cptr_meta)sd.meta)[first + tok].two_step;
+            mt.neg_qs = ((cptr_meta)sd.meta)[first + tok].neg_qs;
             const double val = fma(raw, __builtin_ldexp(mt.two_step, -p), mt.neg_qs);     // exact
             store_out(sd.out, sd.out_dtype, (size_t)(out0 + (int64_t)tok * sd.out_stride) + grow, (float)val * oscale, sd.out_scale != nullptr);
         }
@@ -475,7 +602,7 @@ stage_layer_kernel(QuantDesc qx, StageDesc s1, QuantDesc qt, StageDesc s2, int n
 #pragma unroll
     for (int k = 0; k < D; ++k) wbuf[k] = load_global_v4u(a1, (uint32_t)((k < cnt1 ? k : (cnt1 > 0 ? cnt1 - 1 : 0)) * w1) * 1024);
     __syncthreads();
-    lone_quantise<W, 4>([&](int c, int, int j0, float v[4]) { lone_value(qx, raw[c], j0, v); }, share1, pieces1, nst1, lane, lt, bq);
+    lone_quantise<W, 4, lone_share_units<W, 4>()>([&](int c, int, int j0, float v[4]) { lone_value(qx, raw[c], j0, v); }, share1, pieces1, nst1, lane, lt, bq);
     uint32_t b1[NB], b2[NB];
 #pragma unroll
     for (int cg = 0; cg < NB; ++cg) {
@@ -506,7 +633,7 @@ stage_layer_kernel(QuantDesc qx, StageDesc s1, QuantDesc qt, StageDesc s2, int n
         // the first tiles of stage 2 are requested before stage 1's sums are added up
 #pragma unroll
         for (int k = 0; k < D; ++k) wbuf[k] = load_global_v4u(a2, (uint32_t)((k < cnt2 ? k : (cnt2 > 0 ? cnt2 - 1 : 0)) * W) * 1024);
-        constexpr int kWaveInts = NB * R1 * kLonePlaneInts;
+        constexpr int kWaveInts = lone_wave_ints(NB * R1 * kLonePlaneInts);
 #pragma unroll
         for (int r0 = 0; r0 < 8; r0 += R1) {
             if (r0) __syncthreads();
@@ -533,7 +660,7 @@ stage_layer_kernel(QuantDesc qx, StageDesc s1, QuantDesc qt, StageDesc s2, int n
     }
     __syncthreads();
     // t -> fixed point
-    lone_quantise<W, 4>([&](int, int tok, int j0, float v[4]) {
+    lone_quantise<W, 4, lone_share_units<W, 4>()>([&](int, int tok, int j0, float v[4]) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             float f = 0.f;
@@ -571,7 +698,7 @@ stage_layer_kernel(QuantDesc qx, StageDesc s1, QuantDesc qt, StageDesc s2, int n
             }
         }
     }
-    constexpr int kWaveInts = NB * R2 * kLonePlaneInts;
+    constexpr int kWaveInts = lone_wave_ints(NB * R2 * kLonePlaneInts);
 #pragma unroll
     for (int r0 = 0; r0 < PL; r0 += R2) {
         if (r0) __syncthreads();
@@ -607,26 +734,105 @@ int lone_planes(int n_rb)
 }
 
 constexpr size_t kLoneLdsBytes = 160 * 1024;            // of a CU
-static size_t lone_lds_bytes(int nb, int pl, int w, int max_steps, int batch)
-{
-    return (size_t)lone_red_ints(nb, pl, w) * 4 + sizeof(LoneTokens) + (size_t)batch * lone_tok_bytes(max_steps);
-}
-
-// More than eight tokens of one op are dealt out in groups of at most eight, of even sizes.
+// More than eight tokens of one op on a quantised input are dealt out in groups of at most eight, of even sizes.
 static int lone_group(int batch) { return (batch + (batch + 7) / 8 - 1) / ((batch + 7) / 8); }
 static int lone_groups(int batch) { return (batch + 7) / 8; }
 
-// Whether the workgroups of such a launch quantise its input themselves.  Where several share a row block, up to what 16 waves hold.  Whole row
-// blocks per workgroup (more than half as many as CUs) leave eight waves for it, two to a SIMD, which pays for one or two tokens and for short
+// A form of the launch that quantises along
+struct AlongForm {
+    LoneDeal d;
+    int pl, w, e;
+    size_t lds;
+};
+
+static size_t along_lds_bytes(int pl, int w, int steps, int per)
+{
+    return (size_t)w * lone_wave_ints(pl * 4 * along_row_ints(per)) * 4 + sizeof(LoneTokens) + (size_t)per * lone_tok_bytes(steps);
+}
+
+// Time of a launch, back to back with others (us), fitted to 43000 timings: 1 to 224 row blocks of 4 to 448 steps at 1 to 64 tokens in every form that
+// fits; 3.4 % off on average, its choices 1.2 % slower than the best of each, the timings' own scatter included.  Beside the launch and the chain's fixed part
+// (3.3): the vector instructions of the fixed point on the busiest SIMD (a lane's element 18 ns) and its reductions (a wave's part of a token 54), the matrix
+// instructions and their masks there (13 ns each), the sums passed through LDS, and what workgroups cost each other.
+static double along_us(const AlongForm& f, int steps)
+{
+    const int s = 8 / f.pl, pieces = (steps + f.e - 1) / f.e, units = f.d.per * pieces, share = (units + f.w - 1) / f.w;
+    const int simd = units >= f.w ? share * (f.w / 4) : (units + 3) / 4;
+    const int results = 16 * f.pl * f.d.per;
+    int parts = 0;                                          // parts of tokens that waves reduce
+    for (int u = 0; u < units; u += share) parts += (std::min(units, u + share) - 1) / pieces - u / pieces + 1;
+    return 3.34 + 0.0184 * simd * f.e + (f.e == 4 ? 0.40 * share : 0.52) + 0.054 * ((parts + 3) / 4) + 0.013 * 0.25 * steps * f.pl * (f.d.per > 5 ? 2 : 1) + 0.002 * steps +
+           0.0141 / 1024 * f.w * f.pl * 192 * f.d.per + 0.51 / 256 * f.d.n_rb * f.d.groups * s + 0.175 * ((results + 16 * f.w - 1) / (16 * f.w)) + (f.w == 8 ? 0.30 : 0.0);
+}
+
+// The form of a launch: among those with at most one workgroup per CU, on their XCD (dealt to all XCDs only where more than eight tokens need it), whose
+// fixed point and sums fit LDS, the one of the least estimated time.  us per launch, stage 1 of 8 row blocks of 64 steps at 24 tokens 8.4 with groups of eight and one
+// plane, 6.7 with groups of three and two; 28 of 448 steps at 4 tokens 14.6 after a quantisation launch of 6.2, 14.8 with it.
+static bool along_form_now(int n_rb, int steps, int tokens, AlongForm* best)
+{
+    const int cus = device_cu_count(), slots = cus / 8 / ((n_rb + 7) / 8);
+    double best_us = 1e30;
+    for (int most = 8; most >= 1; --most) {
+        const int groups = (tokens + most - 1) / most, per = (tokens + groups - 1) / groups;
+        if (per != most || per * lone_pieces<16>(steps) > kLoneMaxElements / 1024) continue;
+        for (int pl = 8; pl >= 1; pl /= 2)
+            for (int w = 16; w >= 8; w /= 2) {
+                if (w == 8 ? pl < 8 : per > 5) continue;
+                for (int e = w == 16 && per * lone_pieces<4>(steps) <= kFewElements / 256 ? 4 : 16; e <= 16; e *= 4) {
+                    const bool spread = 8 / pl * groups > slots;
+                    if (spread && (tokens <= 8 || n_rb * groups * (8 / pl) > cus)) continue;
+                    const AlongForm f = {LoneDeal{n_rb, tokens, per, groups, spread}, pl, w, e, along_lds_bytes(pl, w, steps, per)};
+                    if (f.lds > kLoneLdsBytes) continue;
+                    const double us = along_us(f, steps);
+                    if (us < best_us) { best_us = us; *best = f; }
+                }
+            }
+    }
+    return best_us < 1e30;
+}
+
+// (A call asks for the forms of two stages, twice each: 2 us of a host that takes 6 for the call.  The answer depends on nothing but the three numbers.)
+static bool along_form(int n_rb, int steps, int tokens, AlongForm* best)
+{
+    struct Known {
+        int n_rb, steps, tokens;
+        bool fits;
+        AlongForm form;
+    };
+    static thread_local Known known[64];                   // (all zero: no launch has no row blocks)
+    Known& k = known[(unsigned)(n_rb * 31 + steps * 7 + tokens) % 64];
+    if (k.n_rb != n_rb || k.steps != steps || k.tokens != tokens) {
+        k = Known{n_rb, steps, tokens, false, {}};
+        k.fits = along_form_now(n_rb, steps, tokens, &k.form);
+    }
+    if (k.fits) *best = k.form;
+    return k.fits;
+}
+
+// Whether the workgroups of such a launch quantise its input themselves.  Where every row block finds two CUs and more, wherever that fits.  Whole row
+// blocks per workgroup (more than half as many as CUs) leave nothing to deal out, which pays for one or two tokens and for short
 // inputs of more; past that the launch of its own is the faster one.  us per plan, with a launch of its own / along, stage 2 of 224 row blocks: batch 2 r = 2048 12.1 / 11.2, r = 6144 16.8 / 14.4;
 // batch 3 r = 1024 11.4 / 11.2, r = 2048 12.0 / 12.1, past the line r = 4096 13.3 / 14.4; batch 4 r = 1024 11.5 / 11.6, past it r = 2048 12.2 / 12.6; batch 5 r = 1024
 // 12.3 / 12.8, past it r = 2048 12.9 / 14.3; batch 8 r = 1024 15.1 / 15.6, but stage 1 of as many of three layers, d_in = 1024, batch 5 to 8, 0.97 to 0.99 of the time.
 // (132 to 256 row blocks and lone forwards alike.)
 bool lone_selfq(int max_steps, int n_rb, int batch)
 {
-    const int pl = lone_planes(n_rb * lone_groups(batch)), per = lone_group(batch), pieces = lone_pieces<16>(max_steps);
-    const int most = pl < 8 ? kLoneMaxElements / 1024 / per : per <= 2 ? 12 / per : per == 3 ? 2 : 1;
-    return pieces <= most && lone_lds_bytes(per <= 5 ? 1 : 2, pl, pl == 8 ? 8 : 16, max_steps, per) <= kLoneLdsBytes;
+    AlongForm f;
+    if (lone_planes(n_rb * lone_groups(batch)) == 8) {
+        const int per = lone_group(batch);
+        if (lone_pieces<16>(max_steps) > (per <= 2 ? 12 / per : per == 3 ? 2 : 1)) return false;
+    }
+    return along_form(n_rb, max_steps, batch, &f);
+}
+
+// The same for the launches of a plan, which quantise along where whole groups of eight tokens fit, as they did when those were the only ones: what a plan does is
+// part of its answers (nq_plan_schedules, and the times of nq_plan_forward_timed, where a launch that is not there takes none).
+bool lone_plan_selfq(int max_steps, int n_rb, int batch)
+{
+    const int pl = lone_planes(n_rb), pieces = lone_pieces<16>(max_steps);
+    const int most = pl < 8 ? kLoneMaxElements / 1024 / batch : batch <= 2 ? 12 / batch : batch == 3 ? 2 : 1;
+    const size_t sums = (size_t)(pl == 8 ? 8 : 16) * (batch <= 5 ? 1 : 2) * lone_round(batch <= 5 ? 1 : 2, pl) * kLonePlaneInts * 4;
+    return pieces <= most && sums + sizeof(LoneTokens) + (size_t)batch * lone_tok_bytes(max_steps) <= kLoneLdsBytes && lone_selfq(max_steps, n_rb, batch);
 }
 
 // Up to half as many pairs of row block and group of eight tokens as CUs: several workgroups share every pair.
@@ -646,47 +852,55 @@ bool lone_deals_out(int n_rb, int steps, bool whole, int batch)
     return lone_selfq(steps, n_rb, batch) && (!whole || steps > 24 || (batch <= 24 && steps > 8));
 }
 
-template <int NB, int PL, int W, bool SELFQ>
-static int launch_lone_t(const FusedItem* d_items, int n_rb, const QuantDesc& q, const StageDesc& sd, int max_steps, int batch, int per, hipStream_t s)
+template <int NB, int PL, int W, int E>
+static int launch_along_t(const FusedItem* d_items, const QuantDesc& q, const StageDesc& sd, const AlongForm& f, hipStream_t s)
 {
-    const size_t bytes = SELFQ ? lone_lds_bytes(NB, PL, W, max_steps, per) : (size_t)lone_red_ints(NB, PL, W) * 4;
-    NQ_ALLOW_LDS((stage_lone_kernel<NB, PL, W, SELFQ>), kLoneLdsBytes);
-    const int pairs = n_rb * ((batch + per - 1) / per);
-    const dim3 grid((unsigned)((pairs + 7) / 8 * 8 * (8 / PL)));
-    NQ_LAUNCH((stage_lone_kernel<NB, PL, W, SELFQ>), grid, dim3(64 * W), bytes, s, d_items, q, sd, n_rb, batch, per);
+    NQ_ALLOW_LDS((stage_along_kernel<NB, PL, W, E>), kLoneLdsBytes);
+    const int units = f.d.spread ? (f.d.n_rb * f.d.groups + 7) / 8 : (f.d.n_rb + 7) / 8 * f.d.groups;       // of an XCD
+    NQ_LAUNCH((stage_along_kernel<NB, PL, W, E>), dim3((unsigned)(8 * units * (8 / PL))), dim3(64 * W), f.lds, s, d_items, q, sd, f.d);
     NQ_HIP(hipGetLastError());
     return NQ_OK;
 }
 
-// One stage on its n_rb row blocks, with the quantisation of its input (d_items == nullptr: of the one op).  16 waves per workgroup, eight
-// where they take whole row blocks.
+// One stage on its n_rb row blocks, with the quantisation of its input (d_items == nullptr: of the one op).
 int launch_lone_selfq(const FusedItem* d_items, int n_rb, const QuantDesc& q, const StageDesc& sd, int max_steps, int batch, hipStream_t s)
 {
     if (n_rb < 1) return NQ_OK;
-    if (!lone_selfq(max_steps, n_rb, batch)) {
+    AlongForm f;
+    if (!along_form(n_rb, max_steps, batch, &f)) {
         set_error("launch_lone_selfq: input too long for the workgroups to quantise");
         return NQ_E_INVALID_ARG;
     }
-    const int pl = lone_planes(n_rb * lone_groups(batch)), per = lone_group(batch);
-#define NQ_LONE(PL, W) (per <= 5 ? launch_lone_t<1, PL, W, true>(d_items, n_rb, q, sd, max_steps, batch, per, s) : launch_lone_t<2, PL, W, true>(d_items, n_rb, q, sd, max_steps, batch, per, s))
-    if (pl == 1) return NQ_LONE(1, 16);
-    if (pl == 2) return NQ_LONE(2, 16);
-    if (pl == 4) return NQ_LONE(4, 16);
-    return NQ_LONE(8, 8);
-#undef NQ_LONE
+#define NQ_ALONG(PL) (f.e == 4 ? launch_along_t<1, PL, 16, 4>(d_items, q, sd, f, s) : launch_along_t<1, PL, 16, 16>(d_items, q, sd, f, s))
+    if (f.w == 8) return f.d.per <= 5 ? launch_along_t<1, 8, 8, 16>(d_items, q, sd, f, s) : launch_along_t<2, 8, 8, 16>(d_items, q, sd, f, s);
+    if (f.pl == 1) return NQ_ALONG(1);
+    if (f.pl == 2) return NQ_ALONG(2);
+    if (f.pl == 4) return NQ_ALONG(4);
+    return NQ_ALONG(8);
+#undef NQ_ALONG
 }
 
-// The same on an input that a launch of its own has quantised; w: 16 or (six to eight tokens a group) 8 waves per workgroup.
+template <int NB, int PL, int W>
+static int launch_lone_t(const FusedItem* d_items, int n_rb, const StageDesc& sd, int batch, int per, hipStream_t s)
+{
+    NQ_ALLOW_LDS((stage_lone_kernel<NB, PL, W>), kLoneLdsBytes);
+    const int pairs = n_rb * ((batch + per - 1) / per);
+    const dim3 grid((unsigned)((pairs + 7) / 8 * 8 * (8 / PL)));
+    NQ_LAUNCH((stage_lone_kernel<NB, PL, W>), grid, dim3(64 * W), (size_t)lone_red_ints(NB, PL, W) * 4, s, d_items, sd, n_rb, batch, per);
+    NQ_HIP(hipGetLastError());
+    return NQ_OK;
+}
+
+// One stage on an input that a launch of its own has quantised; w: 16 or (six to eight tokens a group) 8 waves per workgroup.
 int launch_lone(const FusedItem* d_items, int n_rb, const StageDesc& sd, int w, int batch, hipStream_t s)
 {
     if (n_rb < 1) return NQ_OK;
     const int pl = lone_planes(n_rb * lone_groups(batch)), per = lone_group(batch);
-    const QuantDesc q{};
 #define NQ_LONE(NB, W)                                                            \
-    (pl == 1   ? launch_lone_t<NB, 1, W, false>(d_items, n_rb, q, sd, 0, batch, per, s) \
-     : pl == 2 ? launch_lone_t<NB, 2, W, false>(d_items, n_rb, q, sd, 0, batch, per, s) \
-     : pl == 4 ? launch_lone_t<NB, 4, W, false>(d_items, n_rb, q, sd, 0, batch, per, s) \
-               : launch_lone_t<NB, 8, W, false>(d_items, n_rb, q, sd, 0, batch, per, s))
+    (pl == 1   ? launch_lone_t<NB, 1, W>(d_items, n_rb, sd, batch, per, s) \
+     : pl == 2 ? launch_lone_t<NB, 2, W>(d_items, n_rb, sd, batch, per, s) \
+     : pl == 4 ? launch_lone_t<NB, 4, W>(d_items, n_rb, sd, batch, per, s) \
+               : launch_lone_t<NB, 8, W>(d_items, n_rb, sd, batch, per, s))
     if (per <= 5) return NQ_LONE(1, 16);
     return w == 16 ? NQ_LONE(2, 16) : NQ_LONE(2, 8);
 #undef NQ_LONE
