@@ -44,26 +44,28 @@ struct GemmArgs {
 constexpr int kGemmThreads = 256;
 constexpr int kBK = 16;        // reduction depth of one LDS tile = four 16x16x4 matrix instructions
 
-// A workgroup of four waves (2 x 2) owns a BM x BN tile of C; each wave (BM/2) x (BN/2) of it as
+// A workgroup of four or eight waves (2 x 2, 2 x 4) owns a BM x BN tile of C; each wave (BM/2) x (BN/2 or BN/4) of it as
 // 16 x 16 accumulator tiles.  v_mfma_f64_16x16x4_f64: lane l supplies A[l & 15][l >> 4] and B[l >> 4][l & 15],
 // and holds C[4 v + (l >> 4)][l & 15] in element v of its four accumulators.  Operand tiles go through LDS, double
 // buffered: the global loads of tile kt + 1 are in flight while tile kt is multiplied.  The LDS layout of an
 // operand follows the memory layout of its source, so that both the staging stores and the operand reads are
 // free of bank conflicts: a source that is contiguous along the reduction (A stored [M][K], B stored [N][K]) is kept
 // as [i][k] with a row pitch of 17 doubles, one that is contiguous along the tile's rows or columns as [k][i] with
-// a pitch of BM + 16.  Two workgroups fit a CU (registers and LDS), so one's staging overlaps the other's products.
-// PF: tiles held in registers ahead of the one being multiplied (1 for the large tiles; 4 for the 64 x 64 tile, whose
+// a pitch of BM + 16.  Two workgroups fit a CU (registers and LDS; a 128 x 128 one has its eight waves for that), so one's staging overlaps the other's products.
+// PF: tiles held in registers ahead of the one being multiplied (4 for the 64 x 64 tile, whose
 // launches are mostly short reductions that would otherwise wait a full memory latency per 16 columns).
+// Bound: binary64 matrix cores, 66 to 68 of 77.7 TFLOP/s on large products (49 to 62 before the fetches lost their branches and 128 wide tiles their second wave per SIMD).
 // TA, TB: the transpose flags as compile-time constants (LDS offsets become immediates of the LDS instructions).
-template <int BM, int BN, int PF, bool TA, bool TB>
+template <int BM, int BN, int PF, bool TA, bool TB, int WAVES>
 __device__ __forceinline__ void dgemm_body(const GemmArgs& g, const int bx, const int by, const int bz, double* lds_gemm)
 {
     constexpr int PK = kBK + 1;
     constexpr int PA = BM + 16, PB = BN + 16;
     constexpr int SA = BM * PK > kBK * PA ? BM * PK : kBK * PA;
     constexpr int SB = BN * PK > kBK * PB ? BN * PK : kBK * PB;
-    constexpr int TM = BM / 32, TN = BN / 32;
-    constexpr int LA = BM * kBK / kGemmThreads, LB = BN * kBK / kGemmThreads;
+    constexpr int WN = WAVES / 2;          // waves side by side
+    constexpr int TM = BM / 32, TN = BN / 16 / WN;
+    constexpr int kThreads = 64 * WAVES, LA = BM * kBK / kThreads, LB = BN * kBK / kThreads;
     double* As = lds_gemm;                 // [2][SA]
     double* Bs = lds_gemm + 2 * SA;        // [2][SB]
 
@@ -77,70 +79,48 @@ __device__ __forceinline__ void dgemm_body(const GemmArgs& g, const int bx, cons
     const int zb = g.k_parts > 1 ? 0 : bz;
     const int k_begin = g.k_from_max ? ((i0 > j0 ? i0 : j0) / kBK) * kBK : part * g.k_per_part;
     const int k_end = g.k_parts > 1 && k_begin + g.k_per_part < g.K ? k_begin + g.k_per_part : g.K;
-    const int n_kt = k_end > k_begin ? (k_end - k_begin + kBK - 1) / kBK : 0;
-    const int wm0 = (wave >> 1) * (BM / 2), wn0 = (wave & 1) * (BN / 2);
+    const int n_full = k_end > k_begin ? (k_end - k_begin) / kBK : 0, k_rest = k_end > k_begin ? (k_end - k_begin) % kBK : 0;      // whole tiles and what is left
+    const int wm0 = wave / WN * (BM / 2), wn0 = wave % WN * (BN / WN);
     constexpr bool ta = TA, tb = TB;
-    // a tile that lies inside the matrix needs no masking of rows or columns
-    const bool interior = i0 + BM <= g.M && j0 + BN <= g.N;
-
-    // What a thread fetches does not change from tile to tile except for the reduction offset: the pointers (rows and
-    // columns beyond the matrix are clamped to its last one and their values replaced by zero), the element's depth
-    // inside a tile and its place in LDS are set up once; the loop only advances the pointers.  Tiles are fetched in
-    // ascending order, one call per tile.
+    // What a thread fetches does not change from tile to tile except for the reduction offset: the pointers (rows and columns beyond the matrix are
+    // clamped to its last one: they only reach results that are not stored), the element's depth inside a tile and its place in LDS are set up once; the loop only
+    // advances the pointers.  Whole tiles are fetched without a branch, past the last one that one again: with masks and conditions around the loads the compiler
+    // waited for all of them before the products that they are meant to run beside.
     double ra[PF][LA], rb[PF][LB];
     const double* pa[LA];
     const double* pb[LB];
-    bool va[LA], vb[LB];
     int ka[LA], kb[LB], sa[LA], sb[LB];
     const size_t step_a = ta ? (size_t)kBK * g.lda : kBK, step_b = tb ? kBK : (size_t)kBK * g.ldb;
 #pragma unroll
     for (int p = 0; p < LA; ++p) {
-        const int idx = p * kGemmThreads + tid;
+        const int idx = p * kThreads + tid;
         const int i = ta ? idx % BM : idx / kBK, k = ta ? idx / BM : idx % kBK;
         const int gi = i0 + i < g.M ? i0 + i : g.M - 1;
-        va[p] = i0 + i < g.M;
         ka[p] = k;
         sa[p] = ta ? k * PA + i : i * PK + k;
         pa[p] = ta ? A + (size_t)(k_begin + k) * g.lda + gi : A + (size_t)gi * g.lda + k_begin + k;
     }
 #pragma unroll
     for (int p = 0; p < LB; ++p) {
-        const int idx = p * kGemmThreads + tid;
+        const int idx = p * kThreads + tid;
         const int j = tb ? idx / kBK : idx % BN, k = tb ? idx % kBK : idx / BN;
         const int gj = j0 + j < g.N ? j0 + j : g.N - 1;
-        vb[p] = j0 + j < g.N;
         kb[p] = k;
         sb[p] = tb ? j * PK + k : k * PB + j;
         pb[p] = tb ? B + (size_t)gj * g.ldb + k_begin + k : B + (size_t)(k_begin + k) * g.ldb + gj;
     }
-    auto fetch = [&](int kt, double (&ra)[LA], double (&rb)[LB]) {
-        const int krem = k_end - (k_begin + kt * kBK);        // depth left, >= 1
-        if (krem >= kBK && interior) {
+    int left = n_full - 1;                 // whole tiles behind the one that the pointers are at
+    auto fetch = [&](double (&ra)[LA], double (&rb)[LB]) {
 #pragma unroll
-            for (int p = 0; p < LA; ++p) ra[p] = *pa[p];
+        for (int p = 0; p < LA; ++p) ra[p] = *pa[p];
 #pragma unroll
-            for (int p = 0; p < LB; ++p) rb[p] = *pb[p];
-        } else if (krem >= kBK) {                             // a whole tile: every address is inside the matrix
+        for (int p = 0; p < LB; ++p) rb[p] = *pb[p];
+        const size_t da = left > 0 ? step_a : 0, db = left > 0 ? step_b : 0;
+        --left;
 #pragma unroll
-            for (int p = 0; p < LA; ++p) {
-                const double v = *pa[p];
-                ra[p] = va[p] ? v : 0.0;
-            }
+        for (int p = 0; p < LA; ++p) pa[p] += da;
 #pragma unroll
-            for (int p = 0; p < LB; ++p) {
-                const double v = *pb[p];
-                rb[p] = vb[p] ? v : 0.0;
-            }
-        } else {                                              // the ragged last tile
-#pragma unroll
-            for (int p = 0; p < LA; ++p) ra[p] = (va[p] && ka[p] < krem) ? *pa[p] : 0.0;
-#pragma unroll
-            for (int p = 0; p < LB; ++p) rb[p] = (vb[p] && kb[p] < krem) ? *pb[p] : 0.0;
-        }
-#pragma unroll
-        for (int p = 0; p < LA; ++p) pa[p] += step_a;
-#pragma unroll
-        for (int p = 0; p < LB; ++p) pb[p] += step_b;
+        for (int p = 0; p < LB; ++p) pb[p] += db;
     };
     auto stash = [&](int buf, const double (&ra)[LA], const double (&rb)[LB]) {
 #pragma unroll
@@ -160,39 +140,70 @@ __device__ __forceinline__ void dgemm_body(const GemmArgs& g, const int bx, cons
     constexpr int a_dk = ta ? 4 * PA : 4, a_dt = ta ? 16 : 16 * PK;
     const int b_off = tb ? (wn0 + (lane & 15)) * PK + (lane >> 4) : (lane >> 4) * PB + wn0 + (lane & 15);
     constexpr int b_dk = tb ? 4 : 4 * PB, b_dt = tb ? 16 * PK : 16;
+    auto multiply = [&](int buf) {
+        const double* Ab = As + buf * SA + a_off;
+        const double* Bb = Bs + buf * SB + b_off;
+        // Where a wave has few products per column of operands, the next four columns' are on their way while these are multiplied; 128 x 128 tiles have
+        // enough of them, and the compiler's own order leaves their fetches more room (4096 x 1024 x 4096 526 us, so ordered 562; 128 x 64 533 and 601 (transposed) -> 521 and 512).
+        constexpr bool kAhead = BN < 128;
+        double a[2][TM], b[2][TN];
+        auto read = [&](int k4) {
+#pragma unroll
+            for (int t = 0; t < TM; ++t) a[k4 & 1][t] = Ab[k4 * a_dk + t * a_dt];
+#pragma unroll
+            for (int t = 0; t < TN; ++t) b[k4 & 1][t] = Bb[k4 * b_dk + t * b_dt];
+        };
+        if (kAhead) read(0);
+#pragma unroll
+        for (int k4 = 0; k4 < kBK / 4; ++k4) {
+            if (!kAhead) read(k4);
+            else if (k4 + 1 < kBK / 4) read(k4 + 1);
+            if (kAhead) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                for (int tn = 0; tn < TN; ++tn)
+                    acc[tm][tn] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[k4 & 1][tm], b[k4 & 1][tn], acc[tm][tn], 0, 0, 0);
+            if (kAhead) __builtin_amdgcn_sched_barrier(0);
+        }
+    };
 
+    if (n_full > 0) {
 #pragma unroll
-    for (int t = 0; t < PF; ++t)
-        if (t < n_kt) fetch(t, ra[t], rb[t]);
-    if (n_kt > 0) stash(0, ra[0], rb[0]);
-    __syncthreads();
-    for (int kt0 = 0; kt0 < n_kt; kt0 += PF) {
+        for (int t = 0; t < PF; ++t) fetch(ra[t], rb[t]);
+        stash(0, ra[0], rb[0]);
+        __syncthreads();
+        int kt0 = 0;
+        for (; kt0 + PF <= n_full; kt0 += PF) {
+            // slot sl went to LDS one tile ago: refill it with the tile PF ahead, multiply tile kt, then stage tile kt + 1
 #pragma unroll
-        for (int sl = 0; sl < PF; ++sl) {
-            const int kt = kt0 + sl;
-            if (kt < n_kt) {
-                const int buf = kt & 1;
-                // slot sl went to LDS one tile ago: refill it with the tile PF ahead, multiply tile kt, then stage tile kt + 1
-                if (kt + PF < n_kt) fetch(kt + PF, ra[sl], rb[sl]);
-                const double* Ab = As + buf * SA + a_off;
-                const double* Bb = Bs + buf * SB + b_off;
-#pragma unroll
-                for (int k4 = 0; k4 < kBK / 4; ++k4) {
-                    double a[TM], b[TN];
-#pragma unroll
-                    for (int t = 0; t < TM; ++t) a[t] = Ab[k4 * a_dk + t * a_dt];
-#pragma unroll
-                    for (int t = 0; t < TN; ++t) b[t] = Bb[k4 * b_dk + t * b_dt];
-#pragma unroll
-                    for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-                        for (int tn = 0; tn < TN; ++tn)
-                            acc[tm][tn] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[tm], b[tn], acc[tm][tn], 0, 0, 0);
-                }
-                if (kt + 1 < n_kt) stash(buf ^ 1, ra[(sl + 1) % PF], rb[(sl + 1) % PF]);
+            for (int sl = 0; sl < PF; ++sl) {
+                const int buf = (kt0 + sl) & 1;
+                fetch(ra[sl], rb[sl]);
+                multiply(buf);
+                stash(buf ^ 1, ra[(sl + 1) % PF], rb[(sl + 1) % PF]);
                 __syncthreads();
             }
         }
+#pragma unroll
+        for (int sl = 0; sl + 1 < PF; ++sl) {
+            if (kt0 + sl < n_full) {
+                const int buf = (kt0 + sl) & 1;
+                multiply(buf);
+                stash(buf ^ 1, ra[sl + 1], rb[sl + 1]);
+                __syncthreads();
+            }
+        }
+    }
+    if (k_rest > 0) {                      // the ragged last tile
+        const size_t da = n_full > 0 ? step_a : 0, db = n_full > 0 ? step_b : 0;
+#pragma unroll
+        for (int p = 0; p < LA; ++p) ra[0][p] = ka[p] < k_rest ? pa[p][da] : 0.0;
+#pragma unroll
+        for (int p = 0; p < LB; ++p) rb[0][p] = kb[p] < k_rest ? pb[p][db] : 0.0;
+        stash(0, ra[0], rb[0]);
+        __syncthreads();
+        multiply(0);
     }
 
     const bool first = part == 0;
@@ -216,8 +227,8 @@ __device__ __forceinline__ void dgemm_body(const GemmArgs& g, const int bx, cons
             }
 }
 
-template <int BM, int BN, int PF, bool TA, bool TB>
-__global__ __launch_bounds__(kGemmThreads, BM == 128 && BN == 128 && PF > 1 ? 1 : 2) void dgemm_kernel(GemmArgs g)
+template <int BM, int BN, int PF, bool TA, bool TB, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, BM == 128 && BN == 128 ? 3 : 2) void dgemm_kernel(GemmArgs g)
 {
     extern __shared__ __align__(16) double lds_dyn[];
     int bx = (int)blockIdx.x, by = (int)blockIdx.y;
@@ -227,7 +238,7 @@ __global__ __launch_bounds__(kGemmThreads, BM == 128 && BN == 128 && PF > 1 ? 1 
         while ((by + 1) * (by + 2) / 2 <= bx) ++by;
         bx -= by * (by + 1) / 2;
     }
-    dgemm_body<BM, BN, PF, TA, TB>(g, bx, by, (int)blockIdx.z, lds_dyn);
+    dgemm_body<BM, BN, PF, TA, TB, WAVES>(g, bx, by, (int)blockIdx.z, lds_dyn);
 }
 
 template <int BM, int BN> constexpr size_t gemm_lds_bytes()
@@ -240,14 +251,14 @@ template <int BM, int BN> constexpr size_t gemm_lds_bytes()
 
 constexpr int kGemmMaxLdsPad = 32768;
 
-template <int BM, int BN, int PF, bool TA, bool TB> static int launch_gemm_variant(const GemmArgs& g, int batch, hipStream_t s)
+template <int BM, int BN, int PF, bool TA, bool TB, int WAVES> static int launch_gemm_variant(const GemmArgs& g, int batch, hipStream_t s)
 {
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     constexpr size_t lds = gemm_lds_bytes<BM, BN>();
     std::call_once(once, [] {
         if (lds + kGemmMaxLdsPad > 65536)
-            attr_err = hipFuncSetAttribute((const void*)dgemm_kernel<BM, BN, PF, TA, TB>, hipFuncAttributeMaxDynamicSharedMemorySize,
+            attr_err = hipFuncSetAttribute((const void*)dgemm_kernel<BM, BN, PF, TA, TB, WAVES>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)(lds + kGemmMaxLdsPad));
     });
     NQ_HIP(attr_err);
@@ -256,19 +267,21 @@ template <int BM, int BN, int PF, bool TA, bool TB> static int launch_gemm_varia
     // column k, and with it 8 - k of 8 tiles (Gram product of r = 1024, 4096 rows: 191 -> 135 us)
     if (BM == BN && g.lower_only && g.M == g.N) grid = dim3(grid.x * (grid.x + 1) / 2, 1, batch);
     const size_t pad = (size_t)(g.lds_pad < 0 ? 0 : g.lds_pad > kGemmMaxLdsPad ? kGemmMaxLdsPad : g.lds_pad);
-    hipLaunchKernelGGL((dgemm_kernel<BM, BN, PF, TA, TB>), grid, dim3(kGemmThreads), lds + pad, s, g);
+    hipLaunchKernelGGL((dgemm_kernel<BM, BN, PF, TA, TB, WAVES>), grid, dim3(64 * WAVES), lds + pad, s, g);
     NQ_HIP(hipGetLastError());
     return NQ_OK;
 }
 
-template <int BM, int BN, int PF> static int launch_gemm_tile(const GemmArgs& g, int batch, hipStream_t s)
+template <int BM, int BN, int PF, int WAVES = 4> static int launch_gemm_tile(const GemmArgs& g, int batch, hipStream_t s)
 {
-    if (g.trans_a) return g.trans_b ? launch_gemm_variant<BM, BN, PF, true, true>(g, batch, s) : launch_gemm_variant<BM, BN, PF, true, false>(g, batch, s);
-    return g.trans_b ? launch_gemm_variant<BM, BN, PF, false, true>(g, batch, s) : launch_gemm_variant<BM, BN, PF, false, false>(g, batch, s);
+    if (g.trans_a) return g.trans_b ? launch_gemm_variant<BM, BN, PF, true, true, WAVES>(g, batch, s) : launch_gemm_variant<BM, BN, PF, true, false, WAVES>(g, batch, s);
+    return g.trans_b ? launch_gemm_variant<BM, BN, PF, false, true, WAVES>(g, batch, s) : launch_gemm_variant<BM, BN, PF, false, false, WAVES>(g, batch, s);
 }
 
-// Tile choice: the largest tile that still gives every CU two workgroups; the option "dgemm_tile" (1: 128 x 128,
-// 2: 128 x 64, 3: 64 x 64) overrides it.
+// Tile choice: 128 x 64 by eight waves or 64 x 64 by four, whichever gives the fullest CU less to do (in halves of a 128 x 64 tile; a 64 x 64 tile's half takes 1.06 of it; a
+// 128 x 64 workgroup alone on its CU 1.15).  us, 128 x 64 / 64 x 64: 4096 x 1024 x 4096 514 / 550, x 1024 134 / 146, 4096^3 2019 / 2043, past the line
+// 2048 x 1024 x 4096 307 / 275, 3072 x 1024 x 2048 (384 tiles) 256 / 201, 1024 x 1024 x 4096 302 / 192.  The option "dgemm_tile" (1: 128 x 128, 2: 128 x 64, 3: 64 x 64) overrides it.
+// Four waves on 128 x 128 and 128 x 64 tiles, fetched under conditions, took 549 us for the first (569 transposed), 2346 for 4096^3, and 64 x 64 ones 300 for the last.
 static int launch_gemm(const GemmArgs& g, int batch, hipStream_t s)
 {
     if (g.M < 1 || g.N < 1 || batch < 1) return NQ_OK;
@@ -279,12 +292,13 @@ static int launch_gemm(const GemmArgs& g, int batch, hipStream_t s)
         return n * batch;
     };
     int choice = g.tile ? g.tile : opt_or(OPT_DGEMM_TILE, 0);
-    if (choice < 1 || choice > 3) choice = tiles(128, 128) >= 512 ? 1 : tiles(128, 64) >= 384 ? 2 : 3;
-    // Tiles of look-ahead: three for the product that runs with one workgroup per CU, whose waves have nobody to hide their loads (845 -> 800 us beside
-    // the factorisation; four take registers that the factorisation's workgroups need), two for the 128 x 64 tile (4096 x 1024 x 1024
-    // 206 -> 177 us; three 203).
-    if (choice == 1) return g.lds_pad > 0 ? launch_gemm_tile<128, 128, 3>(g, batch, s) : launch_gemm_tile<128, 128, 1>(g, batch, s);
-    if (choice == 2) return launch_gemm_tile<128, 64, 2>(g, batch, s);
+    if (choice < 1 || choice > 3) {
+        const int cus = device_cu_count();
+        const long long wide = (tiles(128, 64) + cus - 1) / cus, narrow = (tiles(64, 64) + cus - 1) / cus;
+        choice = (wide == 1 ? 2.3 : 2.0 * wide) <= 1.06 * narrow ? 2 : 3;
+    }
+    if (choice == 1) return launch_gemm_tile<128, 128, 2, 8>(g, batch, s);
+    if (choice == 2) return launch_gemm_tile<128, 64, 2, 8>(g, batch, s);
     return launch_gemm_tile<64, 64, 4>(g, batch, s);
 }
 
@@ -340,7 +354,7 @@ __device__ __forceinline__ void static_for(F f)
 //  P = A21 X11^T,  which goes to L21 (both with leading dimension ldh), and  A <- A - P P^T,  so that the update's other tiles can run beside this
 // kernel's work.  Everything is requested at once and P stays in LDS (with the tiles' bodies below: step launch 24 -> 19 us on its own, 52 beside the product with W).
 // lds: kPotrfLdsBytes bytes.
-// registers for three waves per SIMD (168), so that such a workgroup fits beside one of the product with W (328): otherwise it waits 800 us for its end
+// registers for three waves per SIMD (168), so that such a workgroup fits beside one of the product with W (two waves of 144): otherwise it waits for its end
 constexpr int kStepWavesPerEu = 3;
 constexpr int kTilePitch = 17, kTileDoubles = 16 * kTilePitch;         // operand reads of all three forms are free of bank conflicts
 constexpr int kPitchP = kNB + 1;
@@ -716,12 +730,6 @@ __global__ __launch_bounds__(kGemmThreads, kStepWavesPerEu) void chol_step_kerne
     if (j > i || i == 0) return;                   // above the diagonal; (0, 0) is the diagonal block's
     step_tile_body<false>(A21 + (size_t)i * kNB * ld, X, j < i ? A21 + (size_t)j * kNB * ld : nullptr, a.H + (size_t)(a.o + kNB + i * kNB) * ld + a.o + kNB + j * kNB, true,
                           j == 0 ? L21 + (size_t)i * kNB * ld : nullptr, nullptr, ld, lds_dyn);
-}
-
-// A += B, both [rows][cols] without padding (the two halves of a product whose reduction was split).
-__global__ void add_half_kernel(double* A, const double* B, size_t count)
-{
-    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < count; e += (size_t)gridDim.x * blockDim.x) A[e] += B[e];
 }
 
 // A += the other parts, in their order, on the leading r x r part of [rp][rp] matrices (the partial Gram products of a
@@ -1184,33 +1192,19 @@ static int factor_step(const AdmmWs& ws, const double* W, int w_trans, int ldw, 
         NQ_HIP(hipStreamWaitEvent(ss.stream, ss.fork, 0));
     }
     GemmArgs gr = gemm_args(w_trans, 0, rows, r, cols, 1.0, W, ldw, O, r, rho, D, r, ws.RHS, r);
-    // On its own (everything on one stream) the product wants the 128 x 128 tile with two workgroups per CU: where the
-    // output has fewer tiles than that, the reduction is cut in two halves (the second into P's buffer, which is free
-    // until the solve) and the halves are added.
-    // Beside the factorisation it is the other way round: the product has the whole factorisation to finish in, and what
-    // matters is that the factorisation's small launches find room at once -- with two 128 x 128 workgroups on a CU
-    // (2 x 72 KiB of LDS) a 64 x 64 workgroup (40 KiB) has to wait until one of them has finished its whole reduction
+    // Beside the factorisation the product has the whole factorisation to finish in, and what
+    // matters is that the factorisation's small launches find room at once -- with two workgroups of the product
+    // on a CU (2 x 72 KiB of LDS) one of the chain (65 KiB) has to wait until one of them has finished its whole reduction
     // (measured: a panel update of 15 workgroups took 470-570 us instead of 8).  So the product then runs with at
-    // most ONE workgroup per CU (its LDS request is padded past half a CU's) and without the cut.
+    // most ONE workgroup per CU (its LDS request is padded past half a CU's), of eight waves: 585 us beside the chain, 526 alone, where
+    // one of four took 800 and 720.
     const long long t128 = (long long)((rows + 127) / 128) * ((r + 127) / 128);
-    const bool roomy = overlap && opt_or(OPT_ADMM_PRODUCT_MODE, 0) != 1 && t128 >= 64;
-    const int w_parts = !roomy && t128 < 512 && 2 * t128 >= 384 && cols >= 1024 ? 2 : 1;
-    if (w_parts > 1) {
-        gr.k_parts = 2;
-        gr.k_per_part = ((cols + 1) / 2 + kBK - 1) / kBK * kBK;
-        gr.Cp[0] = ws.RHS; gr.Cp[1] = ws.P;
-    }
-    if (roomy) {
+    if (overlap && opt_or(OPT_ADMM_PRODUCT_MODE, 0) != 1 && t128 >= 64) {
         gr.tile = 1;
         gr.lds_pad = 8704;                         // (2 x 80.5 KiB do not fit; what is left takes a workgroup of the factorisation, 65 KiB)
     }
-    if (overlap && w_parts > 1) NQ_HIP(hipStreamWaitEvent(rs, ss.svid_done, 0));      // the second half goes where that SVID reads P
-    rc = launch_gemm(gr, w_parts, rs);
+    rc = launch_gemm(gr, 1, rs);
     if (rc != NQ_OK) return rc;
-    if (w_parts > 1) {
-        hipLaunchKernelGGL(add_half_kernel, dim3(1024), dim3(256), 0, rs, ws.RHS, (const double*)ws.P, (size_t)rows * r);
-        NQ_HIP(hipGetLastError());
-    }
     if (overlap) NQ_HIP(hipEventRecord(ss.join, ss.stream));
     rc = factor_and_invert(ws, s, prio);
     if (rc != NQ_OK) return rc;
