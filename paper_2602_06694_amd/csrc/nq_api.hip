@@ -610,10 +610,10 @@ extern "C" int nq_binlr_reserve(nq_handle h, int max_batch)
     // the exact path's passes of more than eight tokens (its calls themselves never allocate)
     size_t need = carve_workspace(nullptr, nullptr, h->d_in, h->r, (int)std::min<int64_t>(exact_pass_tokens(h), round_up(max_batch, 16)));
     // The dense path's need is not monotone in the batch: smaller batches split the reduction
-    // over more workgroups and keep more partial sums.  It depends on the batch only through its
-    // padding to whole 64-token tiles, so the maximum over every padding up to max_batch's is taken.
+    // over more workgroups and keep more partial sums.  It depends on the batch only through the
+    // number of its 32-token tiles, so the maximum over every such number up to max_batch's is taken.
     const bool dense = max_batch >= NQ_PREFILL_MIN_BATCH && !(h->flags & NQ_FLAG_NO_PREFILL);
-    for (int64_t b = 64; dense; b += 64) {
+    for (int64_t b = 32; dense; b += 32) {
         const int bb = (int)std::min<int64_t>(b, max_batch);
         need = std::max(need, prefill_workspace_bytes(h->d_out, h->d_in, h->r, bb, h->pf_plain));
         if (b >= max_batch) break;

@@ -81,6 +81,7 @@ struct GemmArgs {
     int batch;                 // real tokens
     int splits, steps_per_split;
     int n_pad, m_pad;
+    int m_rows;                // tokens of the tiles that are launched (at most m_pad)
 };
 
 __device__ __forceinline__ float h2f(uint16_t h) { return (float)__builtin_bit_cast(_Float16, h); }
@@ -788,7 +789,7 @@ prefill_finalize_kernel(GemmArgs a)
     const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (EPI == EPI_T) {
         const int n16 = a.ldt / 16;
-        if (idx >= (size_t)a.m_pad * n16) return;
+        if (idx >= (size_t)a.m_rows * n16) return;
         const int tok = (int)(idx / n16), n0 = (int)(idx % n16) * 16;
         v4f c4[4] = {};
         if (n0 < a.n_pad) {
@@ -804,7 +805,7 @@ prefill_finalize_kernel(GemmArgs a)
         store_t16<PLAIN>(a, tok, n0, c);
     } else {
         const int n4 = a.n_pad / 4;
-        if (idx >= (size_t)a.m_pad * n4) return;
+        if (idx >= (size_t)a.m_rows * n4) return;
         const int tok = (int)(idx / n4), n0 = (int)(idx % n4) * 4;
         v4f c = {0.f, 0.f, 0.f, 0.f};
         for (int s = 0; s < a.splits; ++s) c += *(const v4f*)(a.partial + ((size_t)s * a.m_pad + tok) * a.n_pad + n0);
@@ -847,20 +848,24 @@ static int steps_per_split4(int nst, int splits, int ks = 1)
 //  - beside its steps a workgroup takes 9.5 us (64 tokens), 10.5 (eight waves), 6.9 (32 tokens): the first fetch and the epilogue;
 //  - splitting costs the finalize launch (2.8 us) and per part 0.23 us and the write and re-read of one set of fp32
 //    partial sums, 0.29 us per MB.
+// Tiles are counted over the tokens that are there: 32-token tiles leave out the half of a last 64 that holds none (its rows of T stay unwritten and are only read
+// for tokens that are not stored), and either tile is split.  us per forward, 64-token tiles alone split and 32-token ones in pairs / so: 11005 x 4095 r = 1663 at 333 tokens 45.9 / 38.7,
+// 5000 x 5000 r = 1300 at 800 47.5 / 41.9, 4096 x 11008 r = 1664 at 150 41.1 / 38.7, 3262 x 4081 r = 820 at 137 31.9 / 29.9; 40 layers from 600 to 28672 a side at 60 to 2048
+// tokens on average 0.7 % slower than the best tiling of each GEMM.
 // One column at a time (`plain`) the steps take 0.60, 1.05, 0.97, 0.49 and 0.35 us (each of ten tilings
 // of the two GEMMs of six layers at 24 to 2048 tokens, against the same in pairs), the rest is the same.
 struct GemmTiling { int tg, splits, ks; double us; };
 struct StepCost { double alone4, two4, halves4, alone2, each2; };
-static GemmTiling choose_tiling(int m_pad, int n_rb, int nst, int n_pad, bool plain)
+static GemmTiling choose_tiling(int batch, int n_rb, int nst, int n_pad, bool plain)
 {
     const StepCost c = plain ? StepCost{0.60, 1.05, 0.97, 0.49, 0.35} : StepCost{0.377, 0.68, 0.654, 0.353, 0.255};
     const int cus = device_cu_count();
     const int n_tiles = (n_rb + kPfWaves - 1) / kPfWaves;
-    const double partial_mb = (double)m_pad * n_pad * 4.0 / 1e6;
+    const double partial_mb = (double)round_up(batch, kPfTokens) * n_pad * 4.0 / 1e6;
     GemmTiling best = {4, 1, 1, 0.0};
     double best_cost = 1e30;
     auto consider = [&](int tg, int splits, int ks) {
-        const int wgs = (m_pad / (16 * tg)) * n_tiles * splits, per = steps_per_split4(nst, splits, ks);
+        const int wgs = (batch + 16 * tg - 1) / (16 * tg) * n_tiles * splits, per = steps_per_split4(nst, splits, ks);
         if ((splits - 1) * per >= nst) return;                 // parts without a step: fewer do the same
         double cost;
         if (ks == 2) {
@@ -878,7 +883,7 @@ static GemmTiling choose_tiling(int m_pad, int n_rb, int nst, int n_pad, bool pl
     for (int s = 1; s <= 16; ++s) {
         consider(4, s, 1);
         if (nst % 8 == 0) consider(4, s, 2);
-        if (s == 1) consider(2, 1, 1);
+        consider(2, s, 1);
     }
     return best;
 }
@@ -891,8 +896,8 @@ static PfLayout pf_layout(int64_t d_out, int64_t d_in, int64_t r, int batch, boo
     L.k2 = (int)n_steps(r) * 64;
     L.n1_pad = (int)n_rowblocks(r) * kTileRows;
     L.n2_pad = (int)n_rowblocks(d_out) * kTileRows;
-    const GemmTiling t1 = choose_tiling(L.m_pad, (int)n_rowblocks(r), (int)n_steps(d_in), L.n1_pad, plain);
-    const GemmTiling t2 = choose_tiling(L.m_pad, (int)n_rowblocks(d_out), (int)n_steps(r), L.n2_pad, plain);
+    const GemmTiling t1 = choose_tiling(batch, (int)n_rowblocks(r), (int)n_steps(d_in), L.n1_pad, plain);
+    const GemmTiling t2 = choose_tiling(batch, (int)n_rowblocks(d_out), (int)n_steps(r), L.n2_pad, plain);
     L.tg1 = t1.tg; L.splits1 = t1.splits; L.ks1 = t1.ks;
     L.tg2 = t2.tg; L.splits2 = t2.splits; L.ks2 = t2.ks;
     if (opt(OPT_PF_TG1) >= 0) L.tg1 = opt(OPT_PF_TG1) == 2 ? 2 : 4;
@@ -922,9 +927,10 @@ static PfLayout pf_layout(int64_t d_out, int64_t d_in, int64_t r, int batch, boo
 // The path's time without what the caller's host side adds, as the exact path is costed against it (nq_api.hip).
 double prefill_us(int64_t d_out, int64_t d_in, int64_t r, int batch)
 {
-    const int m_pad = (int)round_up(batch, kPfTokens), rb1 = (int)n_rowblocks(r), rb2 = (int)n_rowblocks(d_out);
-    return 0.94 * (choose_tiling(m_pad, rb1, (int)n_steps(d_in), rb1 * kTileRows, false).us +
-                   choose_tiling(m_pad, rb2, (int)n_steps(r), rb2 * kTileRows, false).us) + 0.67e-6 * batch * (double)(d_in + d_out);
+    // (whole 64-token tiles, as the choice between the paths was fitted: which calls are exact does not depend on how a last tile is cut)
+    const int rb1 = (int)n_rowblocks(r), rb2 = (int)n_rowblocks(d_out), whole = (int)round_up(batch, kPfTokens);
+    return 0.94 * (choose_tiling(whole, rb1, (int)n_steps(d_in), rb1 * kTileRows, false).us +
+                   choose_tiling(whole, rb2, (int)n_steps(r), rb2 * kTileRows, false).us) + 0.67e-6 * batch * (double)(d_in + d_out);
 }
 
 size_t prefill_workspace_bytes(int64_t d_out, int64_t d_in, int64_t r, int batch, bool plain)
@@ -951,7 +957,7 @@ static int run_gemm(const GemmArgs& a, int tg, int ks, hipStream_t s)
     if (a.splits > 1) {
         launch_gemm<EPI_PARTIAL, PLAIN>(a, tg, ks, s);
         NQ_HIP(hipGetLastError());
-        const size_t total = EPI == EPI_T ? (size_t)a.m_pad * (a.ldt / 16) : (size_t)a.m_pad * (a.n_pad / 4);
+        const size_t total = EPI == EPI_T ? (size_t)a.m_rows * (a.ldt / 16) : (size_t)a.m_rows * (a.n_pad / 4);
         hipLaunchKernelGGL((prefill_finalize_kernel<EPI, PLAIN>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, a);
     } else {
         launch_gemm<EPI, PLAIN>(a, tg, ks, s);
@@ -1044,7 +1050,8 @@ static int launch_prefill_as(const PrefillArgs& p, hipStream_t s)
     a.n_tiles = (a.n_rb + kPfWaves - 1) / kPfWaves;
     a.splits = L.splits1; a.steps_per_split = steps_per_split4(a.nst, a.splits, L.ks1);
     a.n_pad = L.n1_pad;
-    a.m_tiles = L.m_pad / (16 * L.tg1);
+    a.m_tiles = (p.batch + 16 * L.tg1 - 1) / (16 * L.tg1);
+    a.m_rows = a.m_tiles * 16 * L.tg1;
     int rc = run_gemm<EPI_T, PLAIN>(a, L.tg1, L.ks1, s);
     if (rc != NQ_OK) return rc;
     // gemm2: y = T U^T
@@ -1054,7 +1061,8 @@ static int launch_prefill_as(const PrefillArgs& p, hipStream_t s)
     a.n_tiles = (a.n_rb + kPfWaves - 1) / kPfWaves;
     a.splits = L.splits2; a.steps_per_split = steps_per_split4(a.nst, a.splits, L.ks2);
     a.n_pad = L.n2_pad;
-    a.m_tiles = L.m_pad / (16 * L.tg2);
+    a.m_tiles = (p.batch + 16 * L.tg2 - 1) / (16 * L.tg2);
+    a.m_rows = a.m_tiles * 16 * L.tg2;
     return run_gemm<EPI_Y, PLAIN>(a, L.tg2, L.ks2, s);
 }
 
