@@ -41,8 +41,10 @@ constexpr int kTParts = -1, kTMaxParts = 8;
 constexpr int kTPartTokens = 32;        // most parts x tokens
 
 // ---------------------------------------------------------------------------------------------
-// scaled input -> fixed point.  One workgroup per token.  A thread owns pieces: piece (s, c) of a token holds, as four words
-// i of four bytes, rows 64 s + 16 i + 4 c + (0..3) -- the order in which the turned-round tile meets its rows.
+// scaled input -> fixed point.  One workgroup per token, as many threads as the token has groups of four rows (1024 at most): bound by latency, so a thread has
+// little to do in turn.  Group q of 64 rows is word q >> 2 of piece q & 3 of those rows' four 16-byte pieces: piece (s, c) of a token holds, as four words
+// i of four bytes, rows 64 s + 16 i + 4 c + (0..3) -- the order in which the turned-round tile meets its rows.  Launches of 64 tokens, 4096 rows 5.2 us (with 16 rows
+// per thread and reductions through LDS permutes 5.6), 1024 rows 3.5 (4.0), 2500 rows 3.4 (5.5).
 // ---------------------------------------------------------------------------------------------
 struct TQuantArgs {
     const void* in;             // [batch][in_stride] of in_dtype; kTParts: [parts][batch][in_stride] binary64 to be added up
@@ -56,64 +58,39 @@ struct TQuantArgs {
     int n_pieces;               // 4 per 64 rows, whole row blocks
 };
 
-// the 16 scaled values of piece `pc`; binary64: an fp32 value times an fp16 scale is exact.  (DT = the type of the input: all of a
-// piece's loads are requested before the first is converted; kTParts: from `u`, LDS)
+// the four scaled values of rows r0 .. r0 + 3 (rows past M are padding: zeros); binary64: an fp32 value times an fp16 scale is exact.  (DT = the type of the
+// input; kTParts: from `u`, LDS)
 template <int DT>
-__device__ __forceinline__ void tq_load(const TQuantArgs& a, size_t base, int pc, double v[16], const float* u)
+__device__ __forceinline__ void tq_load(const TQuantArgs& a, size_t base, int r0, double v[4], const float* u)
 {
     typedef unsigned int v2u __attribute__((ext_vector_type(2)));
     typedef v4f v4f_any __attribute__((aligned(4)));       // rows of odd lengths: 16 and 8 bytes at the alignment of an element
     typedef v2u v2u_any __attribute__((aligned(2)));
-    const int r0 = (pc >> 2) * 64 + 4 * (pc & 3);
     if (DT == kTParts) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int r = r0 + 16 * (i >> 2) + (i & 3);
-            v[i] = r < a.M ? (double)u[r] : 0.0;
-        }
+        for (int k = 0; k < 4; ++k) v[k] = r0 + k < a.M ? (double)u[r0 + k] : 0.0;
         return;
     }
-    if (r0 + 52 <= a.M) {                                   // whole pieces: no branch around a load
-        v4f xf[4];
-        v2u xh[4], sc[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int r = r0 + 16 * i;
-            if (DT == NQ_F32) xf[i] = *(const __attribute__((address_space(1))) v4f_any*)((const float*)a.in + base + r);
-            else xh[i] = *(const __attribute__((address_space(1))) v2u_any*)((const uint16_t*)a.in + base + r);
-            if (a.scale) sc[i] = *(const __attribute__((address_space(1))) v2u*)(a.scale + r);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float f[4];
-            if (DT == NQ_F32) {
-                f[0] = xf[i].x; f[1] = xf[i].y; f[2] = xf[i].z; f[3] = xf[i].w;
-            } else {
-                const uint16_t h[4] = {(uint16_t)(xh[i].x & 0xFFFFu), (uint16_t)(xh[i].x >> 16), (uint16_t)(xh[i].y & 0xFFFFu), (uint16_t)(xh[i].y >> 16)};
-#pragma unroll
-                for (int k = 0; k < 4; ++k) f[k] = DT == NQ_F16 ? half_bits_to_float(h[k]) : bf16_bits_to_float(h[k]);
-            }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) v[4 * i + k] = (double)f[k];
-            if (a.scale) {
-                v[4 * i] *= (double)half_bits_to_float((uint16_t)(sc[i].x & 0xFFFFu));
-                v[4 * i + 1] *= (double)half_bits_to_float((uint16_t)(sc[i].x >> 16));
-                v[4 * i + 2] *= (double)half_bits_to_float((uint16_t)(sc[i].y & 0xFFFFu));
-                v[4 * i + 3] *= (double)half_bits_to_float((uint16_t)(sc[i].y >> 16));
-            }
-        }
-        return;
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    if (r0 + 4 <= a.M) {
+        v4f xf;
+        v2u xh, sc;
+        if (DT == NQ_F32) xf = *(const __attribute__((address_space(1))) v4f_any*)((const float*)a.in + base + r0);
+        else xh = *(const __attribute__((address_space(1))) v2u_any*)((const uint16_t*)a.in + base + r0);
+        if (a.scale) sc = *(const __attribute__((address_space(1))) v2u*)(a.scale + r0);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int r = r0 + 16 * i + k;
-            v[4 * i + k] = 0.0;                             // rows beyond M are padding: zeros
-            if (r < a.M) {
-                v[4 * i + k] = (double)load_as_float(a.in, DT, (int64_t)(base + r));
-                if (a.scale) v[4 * i + k] *= (double)half_bits_to_float(a.scale[r]);
-            }
+            const uint16_t h = (uint16_t)(xh[k >> 1] >> (16 * (k & 1)));
+            v[k] = (double)(DT == NQ_F32 ? xf[k] : DT == NQ_F16 ? half_bits_to_float(h) : bf16_bits_to_float(h));
+            if (a.scale) v[k] *= (double)half_bits_to_float((uint16_t)(sc[k >> 1] >> (16 * (k & 1))));
+        }
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        v[k] = 0.0;
+        if (r0 + k < a.M) {
+            v[k] = (double)load_as_float(a.in, DT, (int64_t)(base + r0 + k));
+            if (a.scale) v[k] *= (double)half_bits_to_float(a.scale[r0 + k]);
         }
     }
 }
@@ -121,49 +98,69 @@ __device__ __forceinline__ void tq_load(const TQuantArgs& a, size_t base, int pc
 // low 32 bits of a binary64
 __device__ __forceinline__ int low_word(double v) { return (int)(uint32_t)__builtin_bit_cast(uint64_t, v); }
 
-// q of 16 values -> the slices of their piece (slices 1 KiB apart); returns sum q.
+// q of four values -> their word of every slice (slices 1 KiB apart); returns sum q.
 // q (WIDE: hi and lo with q = 2^24 hi + lo) is taken from the low bits of a sum with a constant that leaves it no fraction: rounding
 // and converting instructions for binary64 are several times as slow.
 template <bool WIDE>
-__device__ __forceinline__ double tq_store(const double v[16], double inv_step, bool bad, uint8_t* dst, uint8_t* dst5)
+__device__ __forceinline__ double tq_store(const double v[4], double inv_step, bool bad, uint8_t* dst, uint8_t* dst5)
 {
     constexpr int kS = kTSlices + (WIDE ? 1 : 0);
     constexpr double kLo = 0x1.8p52, kHi = 0x1.8p76;
-    const auto low_word = [](double x) { return (int)(uint32_t)__builtin_bit_cast(uint64_t, x); };
     long long sum = 0;
-    uint32_t w[kS][4];
+    uint32_t d[kS][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        uint32_t d[kS][4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            int hi = 0, b;
-            if (WIDE) {
-                const double at = fma(v[4 * i + k], inv_step, kHi);
-                hi = low_word(at);                                              // |hi| <= 2^15
-                b = low_word(fma(v[4 * i + k], inv_step, kHi - at) + kLo);      // |lo| <= 2^23
-                sum += ((long long)hi << 24) + b;
-            } else {
-                b = bad ? 0 : low_word(fma(v[4 * i + k], inv_step, kLo));       // |q| < 0.992 * 2^31
-                sum += b;
-            }
-            // the signed bytes from the lowest up (slice kS - 1); WIDE: those of lo, then of hi plus what lo carries
-#pragma unroll
-            for (int s = kS - 1; s >= 0; --s) {
-                if (WIDE && s == kS - 4) b += hi;
-                d[s][k] = (uint32_t)b;
-                b = (b + 128) >> 8;
-            }
+    for (int k = 0; k < 4; ++k) {
+        int hi = 0, b;
+        if (WIDE) {
+            const double at = fma(v[k], inv_step, kHi);
+            hi = low_word(at);                                              // |hi| <= 2^15
+            b = low_word(fma(v[k], inv_step, kHi - at) + kLo);              // |lo| <= 2^23
+            sum += ((long long)hi << 24) + b;
+        } else {
+            b = bad ? 0 : low_word(fma(v[k], inv_step, kLo));               // |q| < 0.992 * 2^31
+            sum += b;
         }
+        // the signed bytes from the lowest up (slice kS - 1); WIDE: those of lo, then of hi plus what lo carries
 #pragma unroll
-        for (int s = 0; s < kS; ++s) w[s][i] = pack_low_bytes(d[s][0], d[s][1], d[s][2], d[s][3]);
+        for (int s = kS - 1; s >= 0; --s) {
+            if (WIDE && s == kS - 4) b += hi;
+            d[s][k] = (uint32_t)b;
+            b = (b + 128) >> 8;
+        }
     }
 #pragma unroll
-    for (int s = 0; s < kS; ++s) *(uint4*)(s < kTSlices ? dst + s * 1024 : dst5) = make_uint4(w[s][0], w[s][1], w[s][2], w[s][3]);
-    return (double)sum;                                                         // below 2^44
+    for (int s = 0; s < kS; ++s) *(uint32_t*)(s < kTSlices ? dst + s * 1024 : dst5) = pack_low_bytes(d[s][0], d[s][1], d[s][2], d[s][3]);
+    return (double)sum;                                                         // below 2^42
 }
 
-constexpr int kTQThreads = 512;         // most threads of a workgroup; short vectors take as many as they have pieces
+// op over each 16-lane row of the wavefront by data-parallel moves, the same in all lanes of a row; over the whole wavefront
+template <class Op>
+__device__ __forceinline__ double row_reduce_f64(double v, Op op)
+{
+    auto dpp = [](double x, auto ctrl) {
+        const uint64_t b = __builtin_bit_cast(uint64_t, x);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)b, decltype(ctrl)::value, 0xf, 0xf, true);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), decltype(ctrl)::value, 0xf, 0xf, true);
+        return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+    };
+    v = op(v, dpp(v, std::integral_constant<int, 0xB1>{}));      // quad_perm [1, 0, 3, 2]
+    v = op(v, dpp(v, std::integral_constant<int, 0x4E>{}));      // quad_perm [2, 3, 0, 1]
+    v = op(v, dpp(v, std::integral_constant<int, 0x141>{}));     // row_half_mirror
+    return op(v, dpp(v, std::integral_constant<int, 0x140>{})); // row_mirror
+}
+template <class Op>
+__device__ __forceinline__ double wave_reduce_f64(double v, Op op)
+{
+    auto lane = [](double x, int l) {
+        const uint64_t b = __builtin_bit_cast(uint64_t, x);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l), hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
+        return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+    };
+    v = row_reduce_f64(v, op);
+    return op(op(lane(v, 0), lane(v, 16)), op(lane(v, 32), lane(v, 48)));
+}
+
+constexpr int kTQThreads = 1024;        // most threads of a workgroup
 
 template <int DT>
 __global__ void __launch_bounds__(kTQThreads) quantize_t_kernel(TQuantArgs a)
@@ -171,8 +168,9 @@ __global__ void __launch_bounds__(kTQThreads) quantize_t_kernel(TQuantArgs a)
     __shared__ double sm_max[kTQThreads / 64], sm_sum[kTQThreads / 64], sm_sq[kTQThreads / 64];
     __shared__ int sm_bad[kTQThreads / 64];
     const int tok = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, threads = blockDim.x;
+    const int groups = a.n_pieces * 4;                      // of four rows
     const size_t base = (size_t)tok * a.in_stride;
-    double v[16], m = 0.0, sq = 0.0;
+    double v[4], m = 0.0, sq = 0.0;
     int bad = 0;
     extern __shared__ float u[];                            // [M], kTParts only
     if (DT == kTParts) {
@@ -190,30 +188,30 @@ __global__ void __launch_bounds__(kTQThreads) quantize_t_kernel(TQuantArgs a)
         }
         __syncthreads();
     }
-    // (a thread's first piece stays in registers between the two passes; longer vectors re-read the others)
-    for (int pc = tid + ((a.n_pieces - 1 - tid) / threads) * threads; pc >= 0; pc -= threads) {
-        if (pc >= a.n_pieces) break;
-        tq_load<DT>(a, base, pc, v, u);
+    // (a thread's first group stays in registers between the two passes; longer vectors re-read the others)
+    for (int gr = tid + ((groups - 1 - tid) / threads) * threads; gr >= 0; gr -= threads) {
+        if (gr >= groups) break;
+        tq_load<DT>(a, base, 4 * gr, v, u);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const double t = fabs(v[i]);
+        for (int k = 0; k < 4; ++k) {
+            const double t = fabs(v[k]);
             if (!(t <= 1.0e300)) bad = 1;                   // NaN or infinity
             m = fmax(m, t);
-            sq = fma(v[i], v[i], sq);
+            sq = fma(v[k], v[k], sq);
         }
     }
-    for (int o = 32; o > 0; o >>= 1) {
-        m = fmax(m, __shfl_xor(m, o));
-        sq += __shfl_xor(sq, o);
-    }
+    const auto most = [](double x, double y) { return fmax(x, y); };
+    const auto plus = [](double x, double y) { return x + y; };
+    m = wave_reduce_f64(m, most);
+    sq = wave_reduce_f64(sq, plus);
     bad = __builtin_amdgcn_ballot_w64(bad != 0) != 0;
     if ((tid & 63) == 0) { sm_max[wave] = m; sm_bad[wave] = bad; sm_sq[wave] = sq; }
     __syncthreads();
-    m = sm_max[0];
-    bad = sm_bad[0];
-    sq = sm_sq[0];
-#pragma unroll
-    for (int w = 1; w < threads / 64; ++w) { m = fmax(m, sm_max[w]); bad |= sm_bad[w]; sq += sm_sq[w]; }
+    // (lane l of every row looks at wave l's)
+    const int other = (tid & 15) < threads / 64 ? tid & 15 : -1, other0 = other < 0 ? 0 : other;
+    m = row_reduce_f64(sm_max[other0], most);
+    bad = __builtin_amdgcn_ballot_w64(sm_bad[other0] != 0) != 0;
+    sq = row_reduce_f64(other < 0 ? 0.0 : sm_sq[other0], plus);
     // step = 2^(e - 31), 2^(e - 39) wide, with the maximum at most 0.99 * 2^e: q fits its signed bytes, which hold +-0.996 * 2^31
     int e = 0;
     if (m > 0.0 && !bad && frexp(m, &e) > 0.99) ++e;
@@ -224,18 +222,18 @@ __global__ void __launch_bounds__(kTQThreads) quantize_t_kernel(TQuantArgs a)
     const size_t group = (size_t)(tok >> 4) * (a.n_pieces >> 2);
     uint8_t* const dst = a.bq + group * (kTGroupRbBytes / 2) + (tok & 15) * 64;
     uint8_t* const dst5 = a.bq5 + group * (kTGroupRbBytes5 / 2) + (tok & 15) * 64;
-    for (int pc = tid; pc < a.n_pieces; pc += threads) {
-        if (pc != tid) tq_load<DT>(a, base, pc, v, u);
-        uint8_t* const to = dst + (size_t)(pc >> 2) * (kTGroupRbBytes / 2) + (pc & 3) * 16;
-        s += wide ? tq_store<true>(v, inv_step, false, to, dst5 + (size_t)(pc >> 2) * (kTGroupRbBytes5 / 2) + (pc & 3) * 16)
-                  : tq_store<false>(v, inv_step, bad != 0, to, nullptr);
+    for (int gr = tid; gr < groups; gr += threads) {
+        if (gr != tid) tq_load<DT>(a, base, 4 * gr, v, u);
+        const int q = gr & 15, at = (q & 3) * 16 + (q >> 2) * 4;
+        uint8_t* const to = dst + (size_t)(gr >> 4) * (kTGroupRbBytes / 2) + at;
+        s += wide ? tq_store<true>(v, inv_step, false, to, dst5 + (size_t)(gr >> 4) * (kTGroupRbBytes5 / 2) + at) : tq_store<false>(v, inv_step, bad != 0, to, nullptr);
     }
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);        // below 2^53: exact
+    s = wave_reduce_f64(s, plus);                           // below 2^53: exact
     if ((tid & 63) == 0) sm_sum[wave] = s;
     __syncthreads();
-    if (tid == 0) {
-        double tot = 0.0;
-        for (int w = 0; w < threads / 64; ++w) tot += sm_sum[w];
+    if (tid < 16) {
+        const double tot = row_reduce_f64(other < 0 ? 0.0 : sm_sum[other0], plus);
+        if (tid != 0) return;
         QMeta mt;
         mt.two_step = bad ? (double)__builtin_nanf("") : ldexp(1.0, e - 38);       // (the product joins five slices, the fifth of other tokens zero)
         mt.neg_qs = -tot * step;
@@ -471,7 +469,7 @@ int launch_gemm_t(const uint32_t* tiles, int64_t M, int64_t N, const void* in, i
     uint32_t* wide = (uint32_t*)((char*)meta + al256((size_t)batch * sizeof(QMeta)));
     const TQuantArgs q{in, in_parts, in_scale, bq, bq5, meta, wide, (int)M, in_dtype, in_stride, n_rb * 8};
     // (parts are added up by a thread per row; the rows, at most 8192 of them here, wait in LDS)
-    const dim3 qgrid(batch), qblock(std::min(kTQThreads, (in_parts > 1 ? (int)M + 63 : q.n_pieces + 63) / 64 * 64));
+    const dim3 qgrid(batch), qblock(std::min(kTQThreads, (in_parts > 1 ? (int)M + 63 : q.n_pieces * 4 + 63) / 64 * 64));
     if (in_parts > 1) hipLaunchKernelGGL(quantize_t_kernel<kTParts>, qgrid, qblock, (size_t)M * sizeof(float), s, q);
     else if (in_dtype == NQ_F32) hipLaunchKernelGGL(quantize_t_kernel<NQ_F32>, qgrid, qblock, 0, s, q);
     else if (in_dtype == NQ_F16) hipLaunchKernelGGL(quantize_t_kernel<NQ_F16>, qgrid, qblock, 0, s, q);
