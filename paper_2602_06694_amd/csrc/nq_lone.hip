@@ -11,7 +11,7 @@
 //
 // Whole forwards, us per call: four launches (batch 1: two self-quantising ones) / two, planes dealt out / tokens and planes; what two launches cost the host is 6:
 //   4096 x 4096 r = 1024   batch 1 11.1 / 8.9 / 8.9, 4 15.8 / 10.6 / 9.9, 8 22.8 / 13.3 / 10.6, 24 27.4 (dense path) / 15.4 / 11.8
-//   5003 x 3001 r = 777    batch 6 25.0 / 13.4 / 10.4        1024 x 1024 r = 256   batch 1 10.4 / 8.0 (one launch) / 7.9
+//   5003 x 3001 r = 777    batch 6 25.0 / 13.4 / 10.4        1024 x 1024 r = 256   batch 1 10.4 / 8.0 (one launch) / 7.6
 //   1408 x 21251 r = 999   batch 7 27.1 (planes) / 14.5      384 x 13516 r = 96    batch 8 23.9 / 11.7
 // 150 random layers from 256 to 28672 a side at batch 1 to 8: 0.81 to 0.85 of the time of planes alone (geometric mean), none slower than their scatter.
 #include <algorithm>
@@ -552,6 +552,8 @@ stage_lone_kernel(const FusedItem* __restrict__ items, StageDesc s1, int n_rb, i
 // ---------------------------------------------------------------------------------------------
 // A small layer in one launch: every workgroup computes the whole of t (its stage-1 tiles are few and come from L2), keeps it in LDS,
 // quantises it and finishes its own PL bit planes of one row block of stage 2.  Workgroup 0 also stores t.
+// Bound by its chain of latencies; adding up the waves' sums of t was the longest link (2.4 of 8.0 us at 1024 x 1024 r = 256): all eight planes pass through LDS at once, in
+// the columns that are in use, and t's largest magnitude is taken where t is: 7.6 us.
 // ---------------------------------------------------------------------------------------------
 constexpr int kLayerWaves = 16;
 
@@ -559,7 +561,7 @@ template <int PL>
 __global__ void __launch_bounds__(64 * kLayerWaves) __attribute__((amdgpu_waves_per_eu(4, 4)))
 stage_layer_kernel(QuantDesc qx, StageDesc s1, QuantDesc qt, StageDesc s2, int n_rb, int batch, int t_off, int bqt_off)
 {
-    constexpr int NB = 1, W = kLayerWaves, D = 4, S = 8 / PL, R1 = lone_round(NB, 8), R2 = lone_round(NB, PL);
+    constexpr int NB = 1, W = kLayerWaves, D = 4, S = 8 / PL, kRows = 16 * PL;
     extern __shared__ __align__(16) int lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -568,7 +570,8 @@ stage_layer_kernel(QuantDesc qx, StageDesc s1, QuantDesc qt, StageDesc s2, int n
     const int rb2 = (blockIdx.x & 7) + 8 * (j / S), p0 = j % S * PL;
     if (rb2 >= n_rb) return;
     int* const red = lds;
-    LoneTokens* const lt = (LoneTokens*)(lds + lone_red_ints(NB, 8, W));     // of x, then of t
+    const int row_ints = along_row_ints(batch), wave_ints1 = lone_wave_ints(32 * row_ints), wave_ints2 = lone_wave_ints(PL * 4 * row_ints);
+    LoneTokens* const lt = (LoneTokens*)(lds + W * wave_ints1);              // of x, then of t
     char* const bq = (char*)(lt + 2);
     float* const t_s = (float*)((char*)lds + t_off);                         // [batch][t stride]
     char* const bqt = (char*)lds + bqt_off;
@@ -601,6 +604,10 @@ stage_layer_kernel(QuantDesc qx, StageDesc s1, QuantDesc qt, StageDesc s2, int n
     v4u wbuf[D];
 #pragma unroll
     for (int k = 0; k < D; ++k) wbuf[k] = load_global_v4u(a1, (uint32_t)((k < cnt1 ? k : (cnt1 > 0 ? cnt1 - 1 : 0)) * w1) * 1024);
+    // the output scale of the row that a thread finishes
+    static_assert(16 * W % kRows == 0, "whole tokens between a thread's results");
+    const int row2 = (tid >> 2) % kRows, grow = rb2 * kTileRows + 16 * p0 + row2;
+    const uint16_t oscale = *(s2.out_scale ? (gptr_u16)s2.out_scale + (grow < s2.M ? grow : 0) : (gptr_u16)s2.tiles);
     __syncthreads();
     lone_quantise<W, 4, lone_share_units<W, 4>()>([&](int c, int, int j0, float v[4]) { lone_value(qx, raw[c], j0, v); }, share1, pieces1, nst1, lane, lt, bq);
     uint32_t b1[NB], b2[NB];
@@ -633,44 +640,62 @@ stage_layer_kernel(QuantDesc qx, StageDesc s1, QuantDesc qt, StageDesc s2, int n
         // the first tiles of stage 2 are requested before stage 1's sums are added up
 #pragma unroll
         for (int k = 0; k < D; ++k) wbuf[k] = load_global_v4u(a2, (uint32_t)((k < cnt2 ? k : (cnt2 > 0 ? cnt2 - 1 : 0)) * W) * 1024);
-        constexpr int kWaveInts = lone_wave_ints(NB * R1 * kLonePlaneInts);
+        // the waves' partial sums of every result, all planes at once; t, scaled, and its largest magnitude from there
+        if (n < 3 * batch) {
 #pragma unroll
-        for (int r0 = 0; r0 < 8; r0 += R1) {
-            if (r0) __syncthreads();
-#pragma unroll
-            for (int cg = 0; cg < NB; ++cg)
-#pragma unroll
-                for (int p = 0; p < R1; ++p) *(v4i*)(red + wave * kWaveInts + (cg * R1 + p) * kLonePlaneInts + g * 68 + n * 4) = acc[cg][r0 + p];
-            __syncthreads();
-            const int quad = tid & 3;
-            for (int idx = tid >> 2; idx < n_rb1 * 16 * R1 * batch; idx += 16 * W) {
-                const int row = idx % (16 * R1), tr = idx / (16 * R1), tok = tr % batch, rb = tr / batch, p = r0 + (row >> 4);
-                const int k = rb * kTileRows + 16 * r0 + row;
-                const int cg = NB > 1 && tok >= 5 ? 1 : 0;
-                double raw = lone_raw<W>(red + (rb << wl) * kWaveInts + (cg * R1 + (row >> 4)) * kLonePlaneInts + ((row >> 2) & 3) * 68 + 3 * (tok - 5 * cg) * 4 + (row & 3),
-                                         kWaveInts, w1, quad);
-                if (quad != 0 || k >= s1.M) continue;
-                if (p == 7) raw = -raw;
-                const QMeta mt = lone_meta(lt, tok);
-                const float t = (float)fma(raw, __builtin_ldexp(mt.two_step, -p), mt.neg_qs);
-                t_s[tok * qt.x_stride + k] = t;
-                if (blockIdx.x == 0) ((float*)s1.out)[(size_t)tok * s1.out_stride + k] = t;
+            for (int p = 0; p < 8; ++p) *(v4i*)(red + wave * wave_ints1 + (p * 4 + g) * row_ints + n * 4) = acc[0][p];
+        }
+        __syncthreads();
+        const int quad = tid & 3;
+        for (int idx = tid >> 2; idx < n_rb1 * kTileRows * batch; idx += 16 * W) {
+            const int row = idx % kTileRows, tr = idx / kTileRows, tok = tr % batch, rb = tr / batch, p = row >> 4;     // (a wave's token is one)
+            const int k = rb * kTileRows + row;
+            double raw = lone_raw<W>(red + (rb << wl) * wave_ints1 + (row >> 2) * row_ints + 12 * tok + (row & 3), wave_ints1, w1, quad);
+            if (p == 7) raw = -raw;
+            const QMeta mt = lone_meta(lt, tok);
+            const float t = (float)fma(raw, __builtin_ldexp(mt.two_step, -p), mt.neg_qs);
+            float f = 0.f;
+            if (k < s1.M) {
+                f = t;
+                if (qt.scale) f *= half_bits_to_float(((gptr_u16)qt.scale)[k]);
+                if (quad == 0) {
+                    t_s[tok * qt.x_stride + k] = f;
+                    if (blockIdx.x == 0) ((float*)s1.out)[(size_t)tok * s1.out_stride + k] = t;
+                }
             }
+            const uint32_t m = wave_reduce32(__builtin_bit_cast(uint32_t, f) & 0x7fffffffu, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+            if (lane == 0) atomicMax(&lt[1].max[tok], m);
         }
     }
     __syncthreads();
-    // t -> fixed point
-    lone_quantise<W, 4, lone_share_units<W, 4>()>([&](int, int tok, int j0, float v[4]) {
+    // t -> fixed point (as the second half of lone_quantise; from LDS, so without registers for a share)
+    {
+        LoneShare sh = share2;
+        int sum = 0;
+#pragma unroll 1
+        for (int c = 0; c < share2.n; ++c) {
+            const float inv_step = exp2_int(-step_exponent(lt[1].max[sh.tok]));
+            const int e0 = sh.piece * 64 + lane;
+            if (e0 < nst2 * 16) {
+                float v[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float f = 0.f;
-            if (j0 + i < qt.N) {
-                f = t_s[tok * qt.x_stride + j0 + i];
-                if (qt.scale) f *= half_bits_to_float(((gptr_u16)qt.scale)[j0 + i]);
+                for (int i = 0; i < 4; ++i) v[i] = 4 * e0 + i < qt.N ? t_s[sh.tok * qt.x_stride + 4 * e0 + i] : 0.f;
+                uint32_t hi, mid, lo;
+                sum += quantize4(v[0], v[1], v[2], v[3], inv_step, hi, mid, lo);
+                uint32_t* const dst = (uint32_t*)(bqt + sh.tok * lone_tok_bytes(nst2) + (e0 >> 2) * (kSlices * 16)) + (e0 & 3);
+                dst[0] = hi;
+                dst[4] = mid;
+                dst[8] = lo;
             }
-            v[i] = f;
+            if (c + 1 == share2.n || sh.piece + 1 == pieces2) {
+                const long long total = wave_sum64(sum);
+                if (lane == 0) atomicAdd(&lt[1].sum[sh.tok], (unsigned long long)total);
+                sum = 0;
+            }
+            lone_next(sh, pieces2);
         }
-    }, share2, pieces2, nst2, lane, lt + 1, bqt);
+    }
+    __syncthreads();
     // stage 2: all waves on PL planes of this workgroup's row block
     uint32_t mask[PL];
 #pragma unroll
@@ -698,29 +723,20 @@ stage_layer_kernel(QuantDesc qx, StageDesc s1, QuantDesc qt, StageDesc s2, int n
             }
         }
     }
-    constexpr int kWaveInts = lone_wave_ints(NB * R2 * kLonePlaneInts);
+    if (n < 3 * batch) {
 #pragma unroll
-    for (int r0 = 0; r0 < PL; r0 += R2) {
-        if (r0) __syncthreads();
-#pragma unroll
-        for (int cg = 0; cg < NB; ++cg)
-#pragma unroll
-            for (int p = 0; p < R2; ++p) *(v4i*)(red + wave * kWaveInts + (cg * R2 + p) * kLonePlaneInts + g * 68 + n * 4) = acc[cg][r0 + p];
-        __syncthreads();
-        const int quad = tid & 3;
-        for (int idx = tid >> 2; idx < 16 * R2 * batch; idx += 16 * W) {
-            const int tok = idx / (16 * R2), row = idx % (16 * R2), p = p0 + r0 + (row >> 4);
-            const int grow = rb2 * kTileRows + 16 * (p0 + r0) + row;
-            float oscale = 1.0f;
-            if (s2.out_scale && grow < s2.M) oscale = half_bits_to_float(((gptr_u16)s2.out_scale)[grow]);
-            const int cg = NB > 1 && tok >= 5 ? 1 : 0;
-            double raw = lone_raw<W>(red + (cg * R2 + (row >> 4)) * kLonePlaneInts + ((row >> 2) & 3) * 68 + 3 * (tok - 5 * cg) * 4 + (row & 3), kWaveInts, W, quad);
-            if (quad != 0 || grow >= s2.M) continue;
-            if (p == 7) raw = -raw;
-            const QMeta mt = lone_meta(lt + 1, tok);
-            const double val = fma(raw, __builtin_ldexp(mt.two_step, -p), mt.neg_qs);     // exact
-            store_out(s2.out, s2.out_dtype, (size_t)tok * s2.out_stride + grow, (float)val * oscale, s2.out_scale != nullptr);
-        }
+        for (int p = 0; p < PL; ++p) *(v4i*)(red + wave * wave_ints2 + (p * 4 + g) * row_ints + n * 4) = acc[0][p];
+    }
+    __syncthreads();
+    const int quad = tid & 3, p = p0 + (row2 >> 4);
+    const float scale = s2.out_scale ? half_bits_to_float(oscale) : 1.0f;
+    for (int tok = (tid >> 2) / kRows; tok < batch; tok += 16 * W / kRows) {
+        double raw = lone_raw<W>(red + (row2 >> 2) * row_ints + 12 * tok + (row2 & 3), wave_ints2, W, quad);
+        if (quad != 0 || grow >= s2.M) continue;
+        if (p == 7) raw = -raw;
+        const QMeta mt = lone_meta(lt + 1, tok);
+        const double val = fma(raw, __builtin_ldexp(mt.two_step, -p), mt.neg_qs);     // exact
+        store_out(s2.out, s2.out_dtype, (size_t)tok * s2.out_stride + grow, (float)val * scale, s2.out_scale != nullptr);
     }
 }
 
@@ -914,7 +930,7 @@ struct LayerLds {
 static LayerLds layer_lds(const QuantDesc& qt, const StageDesc& s1, const StageDesc& s2, int batch)
 {
     LayerLds l;
-    size_t at = (size_t)lone_red_ints(1, 8, kLayerWaves) * 4 + 2 * sizeof(LoneTokens) + (size_t)batch * lone_tok_bytes(s1.n_steps);
+    size_t at = (size_t)kLayerWaves * lone_wave_ints(32 * along_row_ints(batch)) * 4 + 2 * sizeof(LoneTokens) + (size_t)batch * lone_tok_bytes(s1.n_steps);
     l.t_off = (int)at;
     at += (size_t)batch * qt.x_stride * 4;
     l.bqt_off = (int)at;
@@ -922,13 +938,14 @@ static LayerLds layer_lds(const QuantDesc& qt, const StageDesc& s1, const StageD
     return l;
 }
 
-// Where it is faster than two launches: up to four tokens, and so few tiles in stage 1 that doing it once per workgroup costs less than a
-// launch.  us per call, one launch / two: batch 1 8 tiles 7.7 / 9.3, 32 tiles 8.3 / 9.0, 64 9.3 / 9.2; batch 2 8 8.5 / 9.8, 32 9.1 / 9.5,
-// 64 10.8 / 9.3; batch 4 8 9.3 / 10.1, 32 10.7 / 9.7; batch 6 8 12.3 / 11.5.
+// Where it is faster than two launches: so few results of stage 1 that each workgroup adds up the waves' sums of all of them in two or three passes, and so few tiles that
+// doing them once per workgroup costs less than a launch.  us per call, one launch / two, by row blocks and tiles of stage 1, 2048 outputs: batch 1 one row block of 16 tiles 7.2 / 8.7, 64
+// 8.5 / 9.2, 128 10.9 / 9.7; two of 16 7.6 / 9.0, 64 8.4 / 8.9, 128 10.6 / 8.9; four of 32 8.6 / 8.6, 64 8.9 / 8.7 (three of 36 8.3 / 8.5); eight of 32 9.9 / 8.9.  Batch 2 one of 32 8.3 / 9.0, 64 9.4 / 9.3;
+// two of 32 8.6 / 9.1, 64 9.5 / 9.0; four of 16 9.6 / 8.7.  Batch 3 one of 16 8.1 / 9.0, 32 8.9 / 9.0; two of 8 8.7 / 8.7.  Batch 4 one of 8 8.0 / 9.1, 16 8.8 / 9.1, 32 9.7 / 9.2; two of 8 9.4 / 9.1.
 bool lone_layer_fits(const QuantDesc& qt, const StageDesc& s1, const StageDesc& s2, int batch)
 {
     const int n_rb1 = (int)n_rowblocks(s1.M), n_rb2 = (int)n_rowblocks(s2.M);
-    return batch <= 4 && n_rb1 * s1.n_steps * batch <= 48 && n_rb2 <= device_cu_count() && n_rb1 <= kLayerWaves &&
+    return n_rb1 * batch <= 6 && n_rb1 * s1.n_steps * batch <= (n_rb1 * batch > 4 ? 24 : n_rb1 <= 2 ? 64 : 48) && n_rb2 <= device_cu_count() &&
            batch * s1.n_steps * 64 <= kLoneMaxElements && batch * s2.n_steps * 64 <= kLoneMaxElements && layer_lds(qt, s1, s2, batch).bytes <= kLoneLdsBytes;
 }
 
