@@ -856,7 +856,8 @@ static int steps_per_split4(int nst, int splits, int ks = 1)
 // of the two GEMMs of six layers at 24 to 2048 tokens, against the same in pairs), the rest is the same.
 struct GemmTiling { int tg, splits, ks; double us; };
 struct StepCost { double alone4, two4, halves4, alone2, each2; };
-static GemmTiling choose_tiling(int batch, int n_rb, int nst, int n_pad, bool plain)
+// most32: into how many parts the reduction of 32-token tiles may be split
+static GemmTiling choose_tiling(int batch, int n_rb, int nst, int n_pad, bool plain, int most32 = 16)
 {
     const StepCost c = plain ? StepCost{0.60, 1.05, 0.97, 0.49, 0.35} : StepCost{0.377, 0.68, 0.654, 0.353, 0.255};
     const int cus = device_cu_count();
@@ -883,7 +884,7 @@ static GemmTiling choose_tiling(int batch, int n_rb, int nst, int n_pad, bool pl
     for (int s = 1; s <= 16; ++s) {
         consider(4, s, 1);
         if (nst % 8 == 0) consider(4, s, 2);
-        consider(2, s, 1);
+        if (s <= most32) consider(2, s, 1);
     }
     return best;
 }
@@ -927,10 +928,10 @@ static PfLayout pf_layout(int64_t d_out, int64_t d_in, int64_t r, int batch, boo
 // The path's time without what the caller's host side adds, as the exact path is costed against it (nq_api.hip).
 double prefill_us(int64_t d_out, int64_t d_in, int64_t r, int batch)
 {
-    // (whole 64-token tiles, as the choice between the paths was fitted: which calls are exact does not depend on how a last tile is cut)
+    // (whole 64-token tiles, and the tilings among which the choice between the paths was fitted: a call that is exact stays so whatever is gained here)
     const int rb1 = (int)n_rowblocks(r), rb2 = (int)n_rowblocks(d_out), whole = (int)round_up(batch, kPfTokens);
-    return 0.94 * (choose_tiling(whole, rb1, (int)n_steps(d_in), rb1 * kTileRows, false).us +
-                   choose_tiling(whole, rb2, (int)n_steps(r), rb2 * kTileRows, false).us) + 0.67e-6 * batch * (double)(d_in + d_out);
+    return 0.94 * (choose_tiling(whole, rb1, (int)n_steps(d_in), rb1 * kTileRows, false, 1).us +
+                   choose_tiling(whole, rb2, (int)n_steps(r), rb2 * kTileRows, false, 1).us) + 0.67e-6 * batch * (double)(d_in + d_out);
 }
 
 size_t prefill_workspace_bytes(int64_t d_out, int64_t d_in, int64_t r, int batch, bool plain)

@@ -46,3 +46,16 @@ def test_a_reservation_covers_every_number_of_tiles(nqopt):
         nq.nq_binlr_forward(L.h, x, new_output(batch, 640), batch)
         assert nq.nq_binlr_reserved(L.h)[1] == size, batch
     L.close()
+
+
+@pytest.mark.parametrize("shape,batch", [((548, 3214, 192), 207), ((2011, 9600, 997), 149), ((1408, 10245, 1152), 183), ((1330, 5535, 448), 223)])
+def test_calls_on_the_exact_path_stay_there(nqopt, shape, batch):
+    """Calls just inside the line between the two paths, where 32-token tiles in parts bring the dense path's time below the estimate that the line was fitted to."""
+    L = Layer(*shape, "f16", seed=13300 + shape[0])
+    nq.nq_binlr_reserve(L.h, batch)
+    x = to_device(synth.gen_x(batch, shape[1], 13301, "f16"), "f16")
+    y, exact = new_output(batch, shape[0]), new_output(batch, shape[0])
+    nq.nq_binlr_forward(L.h, x, y, batch)
+    nq.nq_binlr_forward_exact(L.h, x, exact, batch)
+    assert np.array_equal(y.cpu().numpy(), exact.cpu().numpy())
+    L.close()
