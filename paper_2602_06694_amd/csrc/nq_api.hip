@@ -682,7 +682,7 @@ static int lone_stage(const QuantDesc& q, const StageDesc& sd, int n_rb, int w, 
     if (lone_selfq(sd.n_steps, n_rb, batch)) return launch_lone_selfq(nullptr, n_rb, q, sd, sd.n_steps, batch, s);
     const int rc = launch_quantize(nullptr, q, 1, q.n_chunks, batch, s);
     if (rc != NQ_OK) return rc;
-    if (lone_planes(n_rb) < 8) return launch_lone(nullptr, n_rb, sd, 16, batch, s);
+    if (lone_planes(n_rb) < 8) return launch_lone(nullptr, n_rb, sd, sd.n_steps, batch, s);
     return launch_stage(nullptr, sd, nullptr, (n_rb + per - 1) / per, w, per, batch, s);
 }
 
@@ -748,7 +748,7 @@ static int exact_stage(const QuantDesc& q, const StageDesc& sd, int batch, hipSt
     }
     if (lone_selfq(sd.n_steps, n_rb, batch)) return launch_lone_selfq(nullptr, n_rb, q, sd, sd.n_steps, batch, s);
     const int rc = launch_quantize(nullptr, q, 1, q.n_chunks, batch, s);
-    return rc != NQ_OK ? rc : launch_lone(nullptr, n_rb, sd, 16, batch, s);
+    return rc != NQ_OK ? rc : launch_lone(nullptr, n_rb, sd, sd.n_steps, batch, s);
 }
 
 // any batch through the exact streaming kernels; `unscaled`: z = U (V^T (s_in (.) x)).  Passes of as many tokens as the layer's
@@ -1189,7 +1189,7 @@ static int plan_run(nq_plan p, hipStream_t s, bool timed)
         if (w == kSelfqSchedule1 || w == kSelfqSchedule4)
             return launch_selfq(fitems, n_items, qdummy, sdummy, w == kSelfqSchedule1 ? 1 : 4, max_steps, s);
         if (w == kLoneSchedule) return launch_lone_selfq(fitems, n_items, qdummy, sdummy, max_steps, p->batch, s);
-        if (is_wide_split(w)) return launch_lone(fitems, n_items, sdummy, w == kSplit8Schedule ? 8 : 16, p->batch, s);
+        if (is_wide_split(w)) return launch_lone(fitems, n_items, sdummy, max_steps, p->batch, s);
         return launch_stage(sd, sdummy, items, n_items, w, stream_max_rbs(p->batch), p->batch, s);
     };
     // timed: launch k carries the event pair ev[2k], ev[2k + 1], bound to the kernel itself (see LaunchTiming)

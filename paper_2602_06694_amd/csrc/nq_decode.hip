@@ -1614,7 +1614,7 @@ int launch_stage(const StageDesc* d_descs, const StageDesc& single, const WorkIt
         if (nb == 1) return launch_stream_t<1>(d_descs, single, d_items, n_items, rbs_per_item, mx, batch, s);
         return launch_stream_t<2>(d_descs, single, d_items, n_items, rbs_per_item, mx, batch, s);
     }
-    if (is_wide_split(w)) return launch_lone(nullptr, n_items, single, w == kSplit8Schedule ? 8 : 16, batch, s);      // (plans: see plan_run)
+    if (is_wide_split(w)) return launch_lone(nullptr, n_items, single, single.n_steps, batch, s);      // (plans: see plan_run)
     if (nb == 1) return launch_split_t<1>(d_descs, single, d_items, n_items, batch, s);
     return launch_split_t<2>(d_descs, single, d_items, n_items, batch, s);
 }

@@ -337,7 +337,7 @@ bool lone_plan_selfq(int max_steps, int n_rb, int batch);
 bool lone_shared_pairs(int n_rb, int batch);
 bool lone_deals_out(int n_rb, int steps, bool whole, int batch);      // whole: the input's rows start 16-byte aligned and end with 16 elements
 int launch_lone_selfq(const FusedItem* d_items, int n_rb, const QuantDesc& q, const StageDesc& sd, int max_steps, int batch, hipStream_t s);
-int launch_lone(const FusedItem* d_items, int n_rb, const StageDesc& sd, int w, int batch, hipStream_t s);
+int launch_lone(const FusedItem* d_items, int n_rb, const StageDesc& sd, int max_steps, int batch, hipStream_t s);
 bool lone_layer_fits(const QuantDesc& qt, const StageDesc& s1, const StageDesc& s2, int batch);
 int launch_lone_layer(const QuantDesc& qx, const StageDesc& s1, const QuantDesc& qt, const StageDesc& s2, int batch, hipStream_t s);
 

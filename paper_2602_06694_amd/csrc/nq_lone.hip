@@ -38,11 +38,8 @@ template <int E> __host__ __device__ inline int lone_pieces(int nst) { return (n
 // fixed point of a token in LDS: [step][chunk][slice][16 bytes], tokens 48 mod 256 bytes apart: the 15 (token, slice) operands of a
 // 16-lane group fall on different banks
 __host__ __device__ inline int lone_tok_bytes(int nst) { return nst * (int)kBqStepBytes + 48; }
-// bit planes whose sums pass through LDS at a time
-constexpr int lone_round(int nb, int pl) { return pl < 4 / nb ? pl : 4 / nb; }
 // ints between the waves' sums: 16 modulo 32, because the four lanes that add up a result start at four waves
 __host__ __device__ constexpr int lone_wave_ints(int ints) { return (ints + 15) / 32 * 32 + 16; }
-constexpr int lone_red_ints(int nb, int pl, int w) { return w * lone_wave_ints(nb * lone_round(nb, pl) * kLonePlaneInts); }
 
 // What the units of a launch's tokens leave in LDS: the bits of their largest magnitude and the sum of their q
 struct LoneTokens {
@@ -275,6 +272,21 @@ struct LoneDeal {
     int n_rb, tokens, per, groups, spread;
 };
 
+// ... the unit of workgroup k of XCD x (planes aside): a group of tokens and a place among the row blocks or items; false: none
+__device__ __forceinline__ bool lone_place(const LoneDeal& d, int x, int k, int& group, int& at)
+{
+    group = 0;
+    at = x + 8 * k;
+    if (d.groups > 1) {
+        const int by = d.spread ? d.n_rb : d.groups;
+        if (d.spread) k = at;
+        const int quot = __builtin_amdgcn_readfirstlane((int)(((float)k + 0.5f) * __builtin_amdgcn_rcpf((float)by)));      // (exact for the small integers that occur)
+        group = d.spread ? quot : k - quot * by;
+        at = d.spread ? k - quot * by : x + 8 * quot;
+    }
+    return at < d.n_rb && group < d.groups;
+}
+
 // ints between the row groups of a wave's sums of one bit plane in LDS: the columns in use (three per token) x 4 rows and a gap, 4 or 12 modulo 16,
 // so that what a wave reads of four row groups and (lone_wave_ints) four waves falls on different banks
 __host__ __device__ inline int along_row_ints(int per) { return 12 * per + 4 + 4 * (per & 1); }
@@ -293,14 +305,8 @@ stage_along_kernel(const FusedItem* __restrict__ items, QuantDesc q1, StageDesc 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, n = lane & 15;
     const int x = blockIdx.x & 7, j = blockIdx.x >> 3, p0 = j % S * PL;
-    int group = 0, at = x + 8 * (j / S);                    // (item or row block)
-    if (d.groups > 1) {
-        const int by = d.spread ? d.n_rb : d.groups, k = d.spread ? at : j / S;
-        const int quot = __builtin_amdgcn_readfirstlane((int)(((float)k + 0.5f) * __builtin_amdgcn_rcpf((float)by)));      // (exact for the small integers that occur)
-        group = d.spread ? quot : k - quot * by;
-        at = d.spread ? k - quot * by : x + 8 * quot;
-    }
-    if (at >= d.n_rb || group >= d.groups) return;
+    int group, at;
+    if (!lone_place(d, x, j / S, group, at)) return;
     QuantDesc qd = q1;
     StageDesc sd = s1;
     int rb = at;
@@ -423,39 +429,32 @@ stage_along_kernel(const FusedItem* __restrict__ items, QuantDesc q1, StageDesc 
     }
 }
 
-// The same on an input that a launch of its own has quantised (too long to quantise along).
-// grid: 8 x ceil(pairs / 8) x (8 / PL) workgroups for the pairs of row block and group of `per` tokens; items: n_rb row blocks of several ops (one
-// group), or nullptr: those of the one op (s1)
+// The same on an input that a launch of its own has quantised (too long to quantise along), dealt out alike.
 template <int NB, int PL, int W>
 __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W / 4, W / 4)))
-stage_lone_kernel(const FusedItem* __restrict__ items, StageDesc s1, int n_rb, int tokens, int per)
+stage_lone_kernel(const FusedItem* __restrict__ items, StageDesc s1, LoneDeal d)
 {
-    constexpr int D = W == 8 ? 8 : 4, S = 8 / PL, R = lone_round(NB, PL), kWaveInts = lone_wave_ints(NB * R * kLonePlaneInts);
+    constexpr int D = W == 8 ? 8 : 4, S = 8 / PL, kRows = 16 * PL;
     extern __shared__ __align__(16) int lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, n = lane & 15;
-    // workgroup i runs on XCD i % 8: the workgroups of a pair are 8 apart
-    const int j = blockIdx.x >> 3;
-    const int at = (blockIdx.x & 7) + 8 * (j / S), p0 = j % S * PL;
-    int rb = at, group = 0;
-    if (tokens > per) {
-        group = at / n_rb;
-        rb = at - group * n_rb;
-        if (group * per >= tokens) return;
-    } else if (at >= n_rb) return;
+    const int x = blockIdx.x & 7, j = blockIdx.x >> 3, p0 = j % S * PL;
+    int group, at;
+    if (!lone_place(d, x, j / S, group, at)) return;
     StageDesc sd = s1;
+    int rb = at;
     if (items) {
         const FusedItem* e = items + at;
         rb = e->rb;
         sd = e->s;
     }
     const int nst = sd.n_steps;
-    const int64_t first = (int64_t)group * per;             // of the group's tokens
-    const int batch = tokens - (int)first < per ? tokens - (int)first : per;
-    const int64_t out0 = first * sd.out_stride;
+    const int64_t first = (int64_t)group * d.per;           // of the group's tokens
+    const int batch = d.tokens - (int)first < d.per ? d.tokens - (int)first : d.per;
+    const int row_ints = along_row_ints(d.per), wave_ints = lone_wave_ints(PL * 4 * row_ints);
     const char* const bq0 = (const char*)sd.bq + first * nst * kBqStepBytes;
-    int* const red = lds;
+    int* const red = lds;                                   // [W][PL][4 row groups][columns][4 rows]
     // the first tiles: steps wave, wave + W, ... (a short share re-reads its last tile)
     const int cnt = (nst - wave + W - 1) / W;
     const int st0 = cnt > 0 ? wave : 0;
@@ -477,6 +476,14 @@ stage_lone_kernel(const FusedItem* __restrict__ items, StageDesc s1, int n_rb, i
     } while (0)
 #pragma unroll
     for (int k = 0; k < D; ++k) NQ_ISSUE(k, k < cnt ? k : (cnt > 0 ? cnt - 1 : 0));
+    static_assert(16 * W % kRows == 0, "whole tokens between a thread's results");
+    const int row = (tid >> 2) % kRows, grow = rb * kTileRows + 16 * p0 + row, tok0 = wave * 16 / kRows;       // (a wave's 16 results are one token's)
+    const uint16_t oscale = *(sd.out_scale ? (gptr_u16)sd.out_scale + (grow < sd.M ? grow : 0) : (gptr_u16)sd.tiles);
+    const auto token_meta = [&](int tok) {
+        const cptr_meta m = (cptr_meta)sd.meta + first + (tok < batch ? tok : 0);
+        return QMeta{m->two_step, m->neg_qs};
+    };
+    QMeta meta = token_meta(tok0);
 
     uint32_t mask[PL];
 #pragma unroll
@@ -521,31 +528,25 @@ stage_lone_kernel(const FusedItem* __restrict__ items, StageDesc s1, int n_rb, i
     }
 #undef NQ_MAC
 #undef NQ_ISSUE
-    // the waves' partial sums of every result, R planes at a time
+    // the waves' partial sums of every result
 #pragma unroll
-    for (int r0 = 0; r0 < PL; r0 += R) {
-        if (r0) __syncthreads();
+    for (int cg = 0; cg < NB; ++cg)
+        if (n < (cg == 0 && NB > 1 ? 15 : 3 * d.per - 15 * cg)) {
 #pragma unroll
-        for (int cg = 0; cg < NB; ++cg)
-#pragma unroll
-            for (int p = 0; p < R; ++p) *(v4i*)(red + wave * kWaveInts + (cg * R + p) * kLonePlaneInts + g * 68 + n * 4) = acc[cg][r0 + p];
-        __syncthreads();
-        const int quad = tid & 3;
-        for (int idx = tid >> 2; idx < 16 * R * batch; idx += 16 * W) {
-            const int tok = idx / (16 * R), row = idx % (16 * R), p = p0 + r0 + (row >> 4);
-            const int grow = rb * kTileRows + 16 * (p0 + r0) + row;
-            float oscale = 1.0f;
-            if (sd.out_scale && grow < sd.M) oscale = half_bits_to_float(((gptr_u16)sd.out_scale)[grow]);
-            const int cg = NB > 1 && tok >= 5 ? 1 : 0;
-            double raw = lone_raw<W>(red + (cg * R + (row >> 4)) * kLonePlaneInts + ((row >> 2) & 3) * 68 + 3 * (tok - 5 * cg) * 4 + (row & 3), kWaveInts, W, quad);
-            if (quad != 0 || grow >= sd.M) continue;
-            if (p == 7) raw = -raw;                        // bit 7 of an int8 is worth -128
-            QMeta mt;
-            mt.two_step = ((cptr_meta)sd.meta)[first + tok].two_step;
-            mt.neg_qs = ((cptr_meta)sd.meta)[first + tok].neg_qs;
-            const double val = fma(raw, __builtin_ldexp(mt.two_step, -p), mt.neg_qs);     // exact
-            store_out(sd.out, sd.out_dtype, (size_t)(out0 + (int64_t)tok * sd.out_stride) + grow, (float)val * oscale, sd.out_scale != nullptr);
+            for (int p = 0; p < PL; ++p) *(v4i*)(red + wave * wave_ints + (p * 4 + g) * row_ints + (15 * cg + n) * 4) = acc[cg][p];
         }
+    __syncthreads();
+    const int quad = tid & 3, p = p0 + (row >> 4);
+    const float scale = sd.out_scale ? half_bits_to_float(oscale) : 1.0f;
+    const int64_t out0 = first * sd.out_stride + grow;
+    for (int tok = tok0; tok < batch; tok += 16 * W / kRows) {
+        const QMeta mt = meta;
+        meta = token_meta(tok + 16 * W / kRows);
+        double sum = lone_raw<W>(red + (row >> 2) * row_ints + 12 * tok + (row & 3), wave_ints, W, quad);
+        if (quad != 0 || grow >= sd.M) continue;
+        if (p == 7) sum = -sum;                            // bit 7 of an int8 is worth -128
+        const double val = fma(sum, __builtin_ldexp(mt.two_step, -p), mt.neg_qs);     // exact
+        store_out(sd.out, sd.out_dtype, (size_t)(out0 + (int64_t)tok * sd.out_stride), (float)val * scale, sd.out_scale != nullptr);
     }
 }
 
@@ -847,25 +848,23 @@ bool lone_plan_selfq(int max_steps, int n_rb, int batch)
 {
     const int pl = lone_planes(n_rb), pieces = lone_pieces<16>(max_steps);
     const int most = pl < 8 ? kLoneMaxElements / 1024 / batch : batch <= 2 ? 12 / batch : batch == 3 ? 2 : 1;
-    const size_t sums = (size_t)(pl == 8 ? 8 : 16) * (batch <= 5 ? 1 : 2) * lone_round(batch <= 5 ? 1 : 2, pl) * kLonePlaneInts * 4;
+    const int nb = batch <= 5 ? 1 : 2;
+    const size_t sums = (size_t)(pl == 8 ? 8 : 16) * nb * std::min(pl, 4 / nb) * kLonePlaneInts * 4;
     return pieces <= most && sums + sizeof(LoneTokens) + (size_t)batch * lone_tok_bytes(max_steps) <= kLoneLdsBytes && lone_selfq(max_steps, n_rb, batch);
 }
 
 // Up to half as many pairs of row block and group of eight tokens as CUs: several workgroups share every pair.
 bool lone_shared_pairs(int n_rb, int batch) { return 2 * n_rb * lone_groups(batch) <= device_cu_count(); }
 
-// Whether a stage of more than eight tokens is faster in such groups than in the groups of 16 of nq_exact.hip.  Always up to a quarter as many pairs as CUs, where
-// four and eight workgroups share each.  Two workgroups per pair take 7.75 us up to 16 steps with the input quantised along, 9.1 up to 32, 10.9 at 47; a quantisation launch and
-// groups of 16 take 3.5 to 4.8 and 3.7 to 4.4 up to 24 steps, 6.5 to 7.6 beyond (rows that do not start 16-byte aligned or end inside 16 elements two to three
-// more, and so do more than 128 tokens; at 24 tokens, where half a group of 16 is empty, the two are level and one launch is less).  Forwards, groups of eight in both stages / of 16, us: 1536 x 1536 r = 1536, 64 tokens 18.2 / 15.8; 2048 x 2048 r = 2048, 64 18.4 / 19.3;
-// 2000 x 3000 r = 1900, 64 20.5 / 22.7; 640 x 300 r = 600, 128 15.6 / 17.5; 256 x 512 r = 256, 512 15.6 / 14.7; 256 x 2048 r = 256, 512 16.7 / 20.9.  With
-// a quantisation launch in both forms the line lies between: 1024 x 4096 r = 1024, 96 20.1 / 19.4; 512 x 4096 r = 384, 256 20.6 / 21.6; 768 x 8192 r = 700, 96
-// 24.0 / 25.0; 1024 x 32768 r = 1024, 96 42.0 / 45.7.
+// Whether a stage of more than eight tokens is faster dealt out here than in the groups of 16 of nq_exact.hip: where two workgroups or more share a pair, and up to one pair per
+// CU and 64 steps where rows do not start 16-byte aligned or end inside 16 elements, which the quantisation launch in front of the groups of 16 takes two to three us longer for.  us per stage
+// with its input's fixed point, groups of 16 / dealt out, by pairs (row blocks, steps, tokens): 2 (1, 7, 15) 6.6 / 4.2; 20 (5, 48, 30) 9.3 / 5.7; 32 (2, 162, 127) 20.5 / 9.6; 60 (10, 4, 48)
+// 6.5 / 5.0; 84 (6, 199, 107) 22.5 / 18.6; 120 (40, 26, 22) 9.1 / 7.1; past it 144 (72, 4, 16) 6.9 / 7.2, 165 (5, 23, 258) 9.8 / 11.3, 225 (15, 127, 114) 19.0 / 19.4; ragged rows
+// 40 (4, 9, 78) 9.6 / 5.1, 128 (16, 34, 64) 12.2 / 8.2, 140 (5, 11, 217) 10.7 / 6.7, 236 (118, 44, 10) 12.8 / 11.8, past it 290 (5, 5, 459) 11.1 / 18.3, 207 (9, 161, 183)
+// 18 / 20.
 bool lone_deals_out(int n_rb, int steps, bool whole, int batch)
 {
-    if (!lone_shared_pairs(n_rb, batch)) return false;
-    if (4 * n_rb * lone_groups(batch) <= device_cu_count() || steps >= 128 || (batch > 128 && steps > 8)) return true;
-    return lone_selfq(steps, n_rb, batch) && (!whole || steps > 24 || (batch <= 24 && steps > 8));
+    return lone_shared_pairs(n_rb, batch) || (!whole && steps <= 64 && n_rb * lone_groups(batch) <= device_cu_count());
 }
 
 template <int NB, int PL, int W, int E>
@@ -896,29 +895,87 @@ int launch_lone_selfq(const FusedItem* d_items, int n_rb, const QuantDesc& q, co
 #undef NQ_ALONG
 }
 
+// A form of the launch on a quantised input
+struct LoneForm {
+    LoneDeal d;
+    int pl, w;
+    size_t lds;
+};
+
+// (six to eight tokens of whole row blocks take eight waves: the registers of sixteen and their sums in LDS are not enough)
+static LoneForm lone_form_of(int n_rb, int tokens, int groups, bool spread, int pl)
+{
+    const int per = (tokens + groups - 1) / groups, w = per > 5 && pl == 8 ? 8 : 16;
+    return {LoneDeal{n_rb, tokens, per, groups, spread}, pl, w, (size_t)w * lone_wave_ints(pl * 4 * along_row_ints(per)) * 4};
+}
+
+// Time of a launch, back to back with others (us), fitted to 12500 timings: 2 to 100 row blocks of 16 to 448 steps at 1 to 48 tokens in every form of at most one workgroup per
+// CU; 5 % off on average, its choices 0.5 % slower than the best of each.  Beside the launch and the chain's fixed part: tiles, fixed point and matrix instructions (past
+// 64 steps the rings run dry and the L2 shows: both cost more), the sums through LDS, and what workgroups cost each other.
+static double lone_us(const LoneForm& f, int steps)
+{
+    const int nb = f.d.per <= 5 ? 1 : 2, far = std::max(0, steps - 64), passes = (f.pl * f.d.per + f.w - 1) / f.w;
+    const double full = (double)f.d.n_rb * f.d.groups * (8 / f.pl) / 256;
+    return 3.11 + 0.0038 * steps + (0.0048 + 0.0023 * f.d.per) * far + 0.00105 * steps * f.pl * nb + 0.0091 / 1024 * f.w * f.pl * 192 * f.d.per +
+           full * (0.23 + (0.0012 + 0.0004 * f.d.per) * far) + 0.035 * f.d.per + 0.67 * (nb - 1) + 0.09 * passes + (f.w == 8 ? 0.24 : 0.0);
+}
+
+// Tokens are dealt out as in along_form_now, and for the same reason two and more groups on one XCD are level with groups on all: us per launch, all tokens in a
+// workgroup / dealt out, 28 row blocks of 448 steps at 8 tokens 18.3 / 10.6, at 4 12.2 / 9.9; 8 of 64 at 8 tokens 4.9 / 3.7, at 4 3.9 / 3.6; 100 of 172 at 8 9.7 / 8.5, at 4 6.8
+// (nothing to deal).  More row blocks than half the CUs: whole ones, eight tokens at a time.
+static LoneForm lone_form_now(int n_rb, int steps, int tokens)
+{
+    const int cus = device_cu_count(), slots = cus / 8 / ((n_rb + 7) / 8);
+    LoneForm best = lone_form_of(n_rb, tokens, lone_groups(tokens), tokens > 8, lone_planes(n_rb * lone_groups(tokens)));
+    double best_us = lone_us(best, steps);
+    for (int most = 8; most >= 1; --most) {
+        const int groups = (tokens + most - 1) / most, per = (tokens + groups - 1) / groups;
+        if (per != most) continue;
+        for (int pl = 8; pl >= 1; pl /= 2) {
+            const bool spread = 8 / pl * groups > slots;
+            if (n_rb * groups * (8 / pl) > cus) continue;
+            const LoneForm f = lone_form_of(n_rb, tokens, groups, spread, pl);
+            const double us = lone_us(f, steps);
+            if (us < best_us) { best_us = us; best = f; }
+        }
+    }
+    return best;
+}
+
+// (remembered as along_form's)
+static LoneForm lone_form(int n_rb, int steps, int tokens)
+{
+    struct Known {
+        int n_rb, steps, tokens;
+        LoneForm form;
+    };
+    static thread_local Known known[64];
+    Known& k = known[(unsigned)(n_rb * 31 + steps * 7 + tokens) % 64];
+    if (k.n_rb != n_rb || k.steps != steps || k.tokens != tokens) k = Known{n_rb, steps, tokens, lone_form_now(n_rb, steps, tokens)};
+    return k.form;
+}
+
 template <int NB, int PL, int W>
-static int launch_lone_t(const FusedItem* d_items, int n_rb, const StageDesc& sd, int batch, int per, hipStream_t s)
+static int launch_lone_t(const FusedItem* d_items, const StageDesc& sd, const LoneForm& f, hipStream_t s)
 {
     NQ_ALLOW_LDS((stage_lone_kernel<NB, PL, W>), kLoneLdsBytes);
-    const int pairs = n_rb * ((batch + per - 1) / per);
-    const dim3 grid((unsigned)((pairs + 7) / 8 * 8 * (8 / PL)));
-    NQ_LAUNCH((stage_lone_kernel<NB, PL, W>), grid, dim3(64 * W), (size_t)lone_red_ints(NB, PL, W) * 4, s, d_items, sd, n_rb, batch, per);
+    const int units = f.d.spread ? (f.d.n_rb * f.d.groups + 7) / 8 : (f.d.n_rb + 7) / 8 * f.d.groups;       // of an XCD
+    NQ_LAUNCH((stage_lone_kernel<NB, PL, W>), dim3((unsigned)(8 * units * (8 / PL))), dim3(64 * W), f.lds, s, d_items, sd, f.d);
     NQ_HIP(hipGetLastError());
     return NQ_OK;
 }
 
-// One stage on an input that a launch of its own has quantised; w: 16 or (six to eight tokens a group) 8 waves per workgroup.
-int launch_lone(const FusedItem* d_items, int n_rb, const StageDesc& sd, int w, int batch, hipStream_t s)
+// One stage on an input that a launch of its own has quantised.
+int launch_lone(const FusedItem* d_items, int n_rb, const StageDesc& sd, int max_steps, int batch, hipStream_t s)
 {
     if (n_rb < 1) return NQ_OK;
-    const int pl = lone_planes(n_rb * lone_groups(batch)), per = lone_group(batch);
-#define NQ_LONE(NB, W)                                                            \
-    (pl == 1   ? launch_lone_t<NB, 1, W>(d_items, n_rb, sd, batch, per, s) \
-     : pl == 2 ? launch_lone_t<NB, 2, W>(d_items, n_rb, sd, batch, per, s) \
-     : pl == 4 ? launch_lone_t<NB, 4, W>(d_items, n_rb, sd, batch, per, s) \
-               : launch_lone_t<NB, 8, W>(d_items, n_rb, sd, batch, per, s))
-    if (per <= 5) return NQ_LONE(1, 16);
-    return w == 16 ? NQ_LONE(2, 16) : NQ_LONE(2, 8);
+    const LoneForm f = lone_form(n_rb, max_steps, batch);
+#define NQ_LONE(NB)                                                   \
+    (f.pl == 1   ? launch_lone_t<NB, 1, 16>(d_items, sd, f, s) \
+     : f.pl == 2 ? launch_lone_t<NB, 2, 16>(d_items, sd, f, s) \
+     : f.pl == 4 ? launch_lone_t<NB, 4, 16>(d_items, sd, f, s) \
+                 : launch_lone_t<NB, 8, NB == 1 ? 16 : 8>(d_items, sd, f, s))
+    return f.d.per <= 5 ? NQ_LONE(1) : NQ_LONE(2);
 #undef NQ_LONE
 }
 
