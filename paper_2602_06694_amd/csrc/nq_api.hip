@@ -791,8 +791,8 @@ static int run_in_passes(nq_handle h, const void* x, void* y, int batch, hipStre
 // more than 256 tokens of four steps and fewer (256 x 256 r = 250, 512 tokens 15.1 against 13.8).  Those and larger layers where one pass
 // holds the batch and its estimate is a tenth below the dense path's (at that line none of 1150 forwards of 50 layers, 256 x 256 to
 // 28672 x 28672 at 9 to 512 tokens, lost more than 4.1 %, and on average they take 0.83 of the dense path's time).  us, dense / exact: 4096 x 4096
-// r = 1024 at 24, 64, 128 tokens 27.5 / 16.0, 28.0 / 20.0, 29.1 / 22.5, past the line at 256 and 512 33.1 / 30.5, 36.2 / 44.0; 28672 x 8192 r = 3520 at 9 and 24
-// 44.5 / 27.4, 45.8 / 35.0, past it at 64 46.3 / 51.3; 1024 x 1024 r = 256 at 24 and 256 17.7 / 10.8, 18.7 / 15.7.
+// r = 1024 at 24, 64, 128 tokens 27.5 / 11.9, 28.0 / 15.5, 29.1 / 18.8, past the line at 256 and 512 33.1 / 30.5, 36.2 / 44.0; 28672 x 8192 r = 3520 at 9 and 24
+// 44.5 / 20.9, 45.8 / 31.2, past it at 64 46.3 / 51.3; 1024 x 1024 r = 256 at 24 and 256 17.7 / 9.3, 18.7 / 13.9.
 static bool forward_exact_pays(nq_handle h, int batch)
 {
     if (opt_flag(OPT_DENSE_ONLY)) return false;
@@ -803,7 +803,13 @@ static bool forward_exact_pays(nq_handle h, int batch)
     const int64_t longest = std::max(n_steps(h->d_in), n_steps(h->r));
     const int rbs = (int)n_rowblocks(std::max(h->r, h->d_out));
     if (lone_shared_pairs(rbs, batch) && (longest <= 512 || batch <= 10) && (batch <= 256 || longest > 4 || lone_shared_pairs(2 * rbs, batch))) return true;
-    return exact_us(h->d_out, h->d_in, h->r, batch) < 0.9 * prefill_us(h->d_out, h->d_in, h->r, batch);
+    if (exact_us(h->d_out, h->d_in, h->r, batch) < 0.9 * prefill_us(h->d_out, h->d_in, h->r, batch)) return true;
+    // Others where one stage at least is dealt out and the estimates of both paths as they are now lie an eighth apart (of 412 forwards, 200 x 200 to 16384 x 16384 at
+    // 9 to 512 tokens, none that this line moved was the slower one).  us, dense / exact: 1220 x 389 r = 149 at 108 tokens 17.7 / 11.9, 942 x 477 r = 213 at 221 18.3 / 14.1,
+    // 3341 x 388 r = 258 at 75 18.7 / 14.6, 8712 x 1167 r = 837 at 60 25.0 / 20.2; past it 384 x 128 r = 128 at 433 14.0 / 13.0, 2503 x 702 r = 188 at 229 19.8 / 19.8.
+    return (longest <= 512 || batch <= 10) && (batch <= 256 || longest > 4) &&
+           (lone_shared_pairs((int)n_rowblocks(h->r), batch) || lone_shared_pairs((int)n_rowblocks(h->d_out), batch)) &&
+           exact_now_us(h->d_out, h->d_in, h->r, batch) < 0.87 * prefill_now_us(h->d_out, h->d_in, h->r, batch);
 }
 
 static int check_xy(const char* who, const void* x, const void* y, size_t x_bytes, size_t y_bytes)

@@ -145,6 +145,17 @@ double exact_us(int64_t d_out, int64_t d_in, int64_t r, int batch)
     return 7.0 + exact_stage_us(r, d_in, batch) + exact_stage_us(d_out, r, batch) + 2.14e-6 * batch * (double)(d_in + 3 * r);
 }
 
+// The path's time with stages dealt out where they are (nq_lone.hip): a stage in groups of 16 with its quantisation launch, or dealt out with its input's fixed point
+double exact_now_us(int64_t d_out, int64_t d_in, int64_t r, int batch)
+{
+    const auto stage = [&](int64_t M, int64_t N) {
+        const int n_rb = (int)n_rowblocks(M), steps = (int)n_steps(N);
+        if (lone_deals_out(n_rb, steps, N % 16 == 0, batch)) return lone_stage_us(n_rb, steps, batch);
+        return 3.5 + exact_stage_us(M, N, batch) + 2.14e-6 * batch * (double)N;
+    };
+    return stage(r, d_in) + stage(d_out, r);
+}
+
 int launch_stage_exact(const StageDesc& d, int batch, hipStream_t s)
 {
     const int n_rb = (int)n_rowblocks(d.M), groups = (batch + kXTokens - 1) / kXTokens;

@@ -336,6 +336,7 @@ bool lone_selfq(int max_steps, int n_rb, int batch);
 bool lone_plan_selfq(int max_steps, int n_rb, int batch);
 bool lone_shared_pairs(int n_rb, int batch);
 bool lone_deals_out(int n_rb, int steps, bool whole, int batch);      // whole: the input's rows start 16-byte aligned and end with 16 elements
+double lone_stage_us(int n_rb, int steps, int tokens);
 int launch_lone_selfq(const FusedItem* d_items, int n_rb, const QuantDesc& q, const StageDesc& sd, int max_steps, int batch, hipStream_t s);
 int launch_lone(const FusedItem* d_items, int n_rb, const StageDesc& sd, int max_steps, int batch, hipStream_t s);
 bool lone_layer_fits(const QuantDesc& qt, const StageDesc& s1, const StageDesc& s2, int batch);
@@ -343,6 +344,7 @@ int launch_lone_layer(const QuantDesc& qx, const StageDesc& s1, const QuantDesc&
 
 // ---- launchers (nq_exact.hip) ---------------------------------------------------------------
 int launch_stage_exact(const StageDesc& d, int batch, hipStream_t s);
+double exact_now_us(int64_t d_out, int64_t d_in, int64_t r, int batch);
 double exact_us(int64_t d_out, int64_t d_in, int64_t r, int batch);      // estimated time of a forward of one pass
 
 // ---- launchers (nq_exec.hip) ---------------------------------------------------------------
@@ -370,6 +372,7 @@ bool prefill_plain(const uint16_t* s_in, int64_t d_in, int x_dtype);
 int launch_prefill_plain(const uint16_t* d_s_in, int64_t d_in, int x_dtype, int* answer);      // s_in on the device; default stream
 size_t prefill_workspace_bytes(int64_t d_out, int64_t d_in, int64_t r, int batch, bool plain);
 int launch_prefill(const PrefillArgs& a, hipStream_t s);
+double prefill_now_us(int64_t d_out, int64_t d_in, int64_t r, int batch);
 double prefill_us(int64_t d_out, int64_t d_in, int64_t r, int batch);      // estimated time of a forward in pairs
 
 }  // namespace nq

@@ -979,6 +979,14 @@ int launch_lone(const FusedItem* d_items, int n_rb, const StageDesc& sd, int max
 #undef NQ_LONE
 }
 
+// Time of a stage dealt out, with its input's fixed point (a quantisation launch where the workgroups do not take it along: 3.5 us and 2.1 us per million elements)
+double lone_stage_us(int n_rb, int steps, int tokens)
+{
+    AlongForm f;
+    if (lone_selfq(steps, n_rb, tokens) && along_form(n_rb, steps, tokens, &f)) return along_us(f, steps);
+    return 3.5 + 2.1e-6 * 64.0 * steps * tokens + lone_us(lone_form(n_rb, steps, tokens), steps);
+}
+
 // ---- one launch per layer ----
 struct LayerLds {
     int t_off, bqt_off;

@@ -879,6 +879,7 @@ static GemmTiling choose_tiling(int batch, int n_rb, int nst, int n_pad, bool pl
             cost = full * (per * step_full + fixed) + (rem ? per * step_rem + fixed : 0.0);
         }
         if (splits > 1) cost += 2.8 + splits * (0.23 + 0.29 * partial_mb);
+        if (tg == 2 && splits > 1) cost += 1.5;                // (what such a choice has to be estimated to gain: short GEMMs were up to 3 % slower)
         if (cost < best_cost) { best_cost = cost; best = {tg, splits, ks, cost}; }
     };
     for (int s = 1; s <= 16; ++s) {
@@ -923,6 +924,14 @@ static PfLayout pf_layout(int64_t d_out, int64_t d_in, int64_t r, int batch, boo
     o += al256(std::max(p1, p2));
     L.total = o;
     return L;
+}
+
+// The path's time on the tilings that it takes
+double prefill_now_us(int64_t d_out, int64_t d_in, int64_t r, int batch)
+{
+    const int rb1 = (int)n_rowblocks(r), rb2 = (int)n_rowblocks(d_out);
+    return 0.94 * (choose_tiling(batch, rb1, (int)n_steps(d_in), rb1 * kTileRows, false).us + choose_tiling(batch, rb2, (int)n_steps(r), rb2 * kTileRows, false).us) +
+           0.67e-6 * batch * (double)(d_in + d_out);
 }
 
 // The path's time without what the caller's host side adds, as the exact path is costed against it (nq_api.hip).

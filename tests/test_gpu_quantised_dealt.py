@@ -56,3 +56,17 @@ def test_more_than_eight_tokens(nqopt, shape, batches):
         assert np.array_equal(got, plain(nqopt, L, xd, batch)), (shape, batch)
         assert rel_err(got, L.oracle(x)) <= TOL, (shape, batch)
     L.close()
+
+
+@pytest.mark.parametrize("shape,batch,exact_pays", [((1220, 389, 149), 108, True), ((942, 477, 213), 221, True), ((3341, 388, 258), 75, True), ((8712, 1167, 837), 60, True),
+                                                    ((2503, 702, 188), 229, False), ((256, 250, 250), 330, False)])
+def test_forward_on_the_faster_path(nqopt, shape, batch, exact_pays):
+    """More pairs of row block and group than are shared in one stage, not in the other: the bits of the path that was measured to be the faster one."""
+    L = Layer(*shape, "bf16", seed=12900 + shape[0])
+    nq.nq_binlr_reserve(L.h, batch)
+    xd = to_device(synth.gen_x(batch, shape[1], 12901, "bf16"), "bf16")
+    y, exact = new_output(batch, shape[0]), new_output(batch, shape[0])
+    nq.nq_binlr_forward(L.h, xd, y, batch)
+    nq.nq_binlr_forward_exact(L.h, xd, exact, batch)
+    assert np.array_equal(y.cpu().numpy(), exact.cpu().numpy()) == exact_pays
+    L.close()
