@@ -295,7 +295,7 @@ constexpr int kSharedSchedule = 8;       // stage_schedule()'s value for the wor
 constexpr int kSharedResidentSchedule = 9;   // the same kernel with the whole input resident in LDS (reductions <= 16 steps)
 // the two with 16-bit fixed point at batch 6..8: a token takes two MFMA columns, eight tokens one group of 16
 constexpr int kSharedSchedule2 = 10, kSharedResidentSchedule2 = 11;
-constexpr int kSplit8Schedule = 12;      // eight waves per row block (batch 6..8; 1, 4 and 16 stand for themselves)
+constexpr int kSplit8Schedule = 12;      // few row blocks of long reductions at batch 6..8: as 16, dealt out by nq_lone.hip (1 and 4 are waves per row block)
 inline bool is_wide_split(int w) { return w == 16 || w == kSplit8Schedule; }
 inline bool is_shared_schedule(int w) { return w >= kSharedSchedule && w <= kSharedResidentSchedule2; }
 int shared_per_wave(int nst, int batch); // row blocks per wave of an item of that kernel
