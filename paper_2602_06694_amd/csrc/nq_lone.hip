@@ -902,7 +902,8 @@ struct LoneForm {
     size_t lds;
 };
 
-// (six to eight tokens of whole row blocks take eight waves: the registers of sixteen and their sums in LDS are not enough)
+// (six to eight tokens take whole row blocks of eight waves: the registers of sixteen and their sums in LDS are not enough, and fewer planes of two column groups are never the
+// faster form: estimated slower than groups of five tokens or fewer at 1 to 600 row blocks, 4 to 1024 steps, 1 to 512 tokens)
 static LoneForm lone_form_of(int n_rb, int tokens, int groups, bool spread, int pl)
 {
     const int per = (tokens + groups - 1) / groups, w = per > 5 && pl == 8 ? 8 : 16;
@@ -926,18 +927,20 @@ static double lone_us(const LoneForm& f, int steps)
 static LoneForm lone_form_now(int n_rb, int steps, int tokens)
 {
     const int cus = device_cu_count(), slots = cus / 8 / ((n_rb + 7) / 8);
-    LoneForm best = lone_form_of(n_rb, tokens, lone_groups(tokens), tokens > 8, lone_planes(n_rb * lone_groups(tokens)));
-    double best_us = lone_us(best, steps);
+    LoneForm best{};
+    double best_us = 1e30;
+    auto consider = [&](int groups, bool spread, int pl) {
+        const LoneForm f = lone_form_of(n_rb, tokens, groups, spread, pl);
+        if (f.d.per > 5 && pl < 8) return;
+        const double us = lone_us(f, steps);
+        if (us < best_us) { best_us = us; best = f; }
+    };
+    consider(lone_groups(tokens), tokens > 8, lone_planes(n_rb * lone_groups(tokens)));
     for (int most = 8; most >= 1; --most) {
         const int groups = (tokens + most - 1) / most, per = (tokens + groups - 1) / groups;
         if (per != most) continue;
-        for (int pl = 8; pl >= 1; pl /= 2) {
-            const bool spread = 8 / pl * groups > slots;
-            if (n_rb * groups * (8 / pl) > cus) continue;
-            const LoneForm f = lone_form_of(n_rb, tokens, groups, spread, pl);
-            const double us = lone_us(f, steps);
-            if (us < best_us) { best_us = us; best = f; }
-        }
+        for (int pl = 8; pl >= 1; pl /= 2)
+            if (n_rb * groups * (8 / pl) <= cus) consider(groups, 8 / pl * groups > slots, pl);
     }
     return best;
 }
@@ -970,13 +973,11 @@ int launch_lone(const FusedItem* d_items, int n_rb, const StageDesc& sd, int max
 {
     if (n_rb < 1) return NQ_OK;
     const LoneForm f = lone_form(n_rb, max_steps, batch);
-#define NQ_LONE(NB)                                                   \
-    (f.pl == 1   ? launch_lone_t<NB, 1, 16>(d_items, sd, f, s) \
-     : f.pl == 2 ? launch_lone_t<NB, 2, 16>(d_items, sd, f, s) \
-     : f.pl == 4 ? launch_lone_t<NB, 4, 16>(d_items, sd, f, s) \
-                 : launch_lone_t<NB, 8, NB == 1 ? 16 : 8>(d_items, sd, f, s))
-    return f.d.per <= 5 ? NQ_LONE(1) : NQ_LONE(2);
-#undef NQ_LONE
+    if (f.w == 8) return launch_lone_t<2, 8, 8>(d_items, sd, f, s);
+    if (f.pl == 1) return launch_lone_t<1, 1, 16>(d_items, sd, f, s);
+    if (f.pl == 2) return launch_lone_t<1, 2, 16>(d_items, sd, f, s);
+    if (f.pl == 4) return launch_lone_t<1, 4, 16>(d_items, sd, f, s);
+    return launch_lone_t<1, 8, 16>(d_items, sd, f, s);
 }
 
 // Time of a stage dealt out, with its input's fixed point (a quantisation launch where the workgroups do not take it along: 3.5 us and 2.1 us per million elements)
