@@ -142,6 +142,8 @@ enum Opt {
     OPT_ADMM_INLINE_SVID,   // flag: LB-ADMM runs the SVID of a factor on the caller's stream, before the next factor's update starts
     OPT_DENSE_ONLY,         // flag: nq_binlr_forward takes the dense path from batch 9 on whatever the exact path would cost
     OPT_ADMM_NO_FUSED_STEP, // flag: LB-ADMM's factorisation launches the trailing update and the next diagonal block one after the other
+    OPT_LONE_FORM,          // form of the launches of few row blocks that deal out tokens and bit planes, 100 x tokens of a group + 10 x planes of a workgroup + kind (0 / 1 / 2: input
+                            // quantised along by 16 waves, 16 / 4 elements of a lane at a time, or by eight; 3 / 4: on a quantised input by 16 / 8); launches that it does not fit are refused
     OPT_COUNT
 };
 int opt(Opt o);                                        // -1 when unset

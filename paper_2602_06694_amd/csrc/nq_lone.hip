@@ -787,7 +787,7 @@ static double along_us(const AlongForm& f, int steps)
 // plane, 6.7 with groups of three and two; 28 of 448 steps at 4 tokens 14.6 after a quantisation launch of 6.2, 14.8 with it.
 static bool along_form_now(int n_rb, int steps, int tokens, AlongForm* best)
 {
-    const int cus = device_cu_count(), slots = cus / 8 / ((n_rb + 7) / 8);
+    const int cus = device_cu_count(), slots = cus / 8 / ((n_rb + 7) / 8), asked = opt(OPT_LONE_FORM);
     double best_us = 1e30;
     for (int most = 8; most >= 1; --most) {
         const int groups = (tokens + most - 1) / most, per = (tokens + groups - 1) / groups;
@@ -797,7 +797,7 @@ static bool along_form_now(int n_rb, int steps, int tokens, AlongForm* best)
                 if (w == 8 ? pl < 8 : per > 5) continue;
                 for (int e = w == 16 && per * lone_pieces<4>(steps) <= kFewElements / 256 ? 4 : 16; e <= 16; e *= 4) {
                     const bool spread = 8 / pl * groups > slots;
-                    if (spread && (tokens <= 8 || n_rb * groups * (8 / pl) > cus)) continue;
+                    if (asked >= 0 ? asked != 100 * per + 10 * pl + (w == 8 ? 2 : e == 4 ? 1 : 0) : spread && (tokens <= 8 || n_rb * groups * (8 / pl) > cus)) continue;
                     const AlongForm f = {LoneDeal{n_rb, tokens, per, groups, spread}, pl, w, e, along_lds_bytes(pl, w, steps, per)};
                     if (f.lds > kLoneLdsBytes) continue;
                     const double us = along_us(f, steps);
@@ -811,6 +811,7 @@ static bool along_form_now(int n_rb, int steps, int tokens, AlongForm* best)
 // (A call asks for the forms of two stages, twice each: 2 us of a host that takes 6 for the call.  The answer depends on nothing but the three numbers.)
 static bool along_form(int n_rb, int steps, int tokens, AlongForm* best)
 {
+    if (opt(OPT_LONE_FORM) >= 0) return along_form_now(n_rb, steps, tokens, best);
     struct Known {
         int n_rb, steps, tokens;
         bool fits;
@@ -835,6 +836,7 @@ static bool along_form(int n_rb, int steps, int tokens, AlongForm* best)
 bool lone_selfq(int max_steps, int n_rb, int batch)
 {
     AlongForm f;
+    if (opt(OPT_LONE_FORM) >= 0) return opt(OPT_LONE_FORM) % 10 < 3;
     if (lone_planes(n_rb * lone_groups(batch)) == 8) {
         const int per = lone_group(batch);
         if (lone_pieces<16>(max_steps) > (per <= 2 ? 12 / per : per == 3 ? 2 : 1)) return false;
@@ -883,7 +885,7 @@ int launch_lone_selfq(const FusedItem* d_items, int n_rb, const QuantDesc& q, co
     if (n_rb < 1) return NQ_OK;
     AlongForm f;
     if (!along_form(n_rb, max_steps, batch, &f)) {
-        set_error("launch_lone_selfq: input too long for the workgroups to quantise");
+        set_error("launch_lone_selfq: input too long for the workgroups to quantise, or not in the form that was asked for");
         return NQ_E_INVALID_ARG;
     }
 #define NQ_ALONG(PL) (f.e == 4 ? launch_along_t<1, PL, 16, 4>(d_items, q, sd, f, s) : launch_along_t<1, PL, 16, 16>(d_items, q, sd, f, s))
@@ -924,38 +926,43 @@ static double lone_us(const LoneForm& f, int steps)
 // Tokens are dealt out as in along_form_now, and for the same reason two and more groups on one XCD are level with groups on all: us per launch, all tokens in a
 // workgroup / dealt out, 28 row blocks of 448 steps at 8 tokens 18.3 / 10.6, at 4 12.2 / 9.9; 8 of 64 at 8 tokens 4.9 / 3.7, at 4 3.9 / 3.6; 100 of 172 at 8 9.7 / 8.5, at 4 6.8
 // (nothing to deal).  More row blocks than half the CUs: whole ones, eight tokens at a time.
-static LoneForm lone_form_now(int n_rb, int steps, int tokens)
+static bool lone_form_now(int n_rb, int steps, int tokens, LoneForm* best)
 {
-    const int cus = device_cu_count(), slots = cus / 8 / ((n_rb + 7) / 8);
-    LoneForm best{};
+    const int cus = device_cu_count(), slots = cus / 8 / ((n_rb + 7) / 8), asked = opt(OPT_LONE_FORM);
     double best_us = 1e30;
     auto consider = [&](int groups, bool spread, int pl) {
         const LoneForm f = lone_form_of(n_rb, tokens, groups, spread, pl);
         if (f.d.per > 5 && pl < 8) return;
+        if (asked >= 0 && asked != 100 * f.d.per + 10 * pl + (f.w == 8 ? 4 : 3)) return;
         const double us = lone_us(f, steps);
-        if (us < best_us) { best_us = us; best = f; }
+        if (us < best_us) { best_us = us; *best = f; }
     };
     consider(lone_groups(tokens), tokens > 8, lone_planes(n_rb * lone_groups(tokens)));
     for (int most = 8; most >= 1; --most) {
         const int groups = (tokens + most - 1) / most, per = (tokens + groups - 1) / groups;
         if (per != most) continue;
         for (int pl = 8; pl >= 1; pl /= 2)
-            if (n_rb * groups * (8 / pl) <= cus) consider(groups, 8 / pl * groups > slots, pl);
+            if (asked >= 0 || n_rb * groups * (8 / pl) <= cus) consider(groups, 8 / pl * groups > slots, pl);
     }
-    return best;
+    return best_us < 1e30;
 }
 
 // (remembered as along_form's)
-static LoneForm lone_form(int n_rb, int steps, int tokens)
+static bool lone_form(int n_rb, int steps, int tokens, LoneForm* best)
 {
+    if (opt(OPT_LONE_FORM) >= 0) return lone_form_now(n_rb, steps, tokens, best);
     struct Known {
         int n_rb, steps, tokens;
         LoneForm form;
     };
     static thread_local Known known[64];
     Known& k = known[(unsigned)(n_rb * 31 + steps * 7 + tokens) % 64];
-    if (k.n_rb != n_rb || k.steps != steps || k.tokens != tokens) k = Known{n_rb, steps, tokens, lone_form_now(n_rb, steps, tokens)};
-    return k.form;
+    if (k.n_rb != n_rb || k.steps != steps || k.tokens != tokens) {
+        k = Known{n_rb, steps, tokens, {}};
+        (void)lone_form_now(n_rb, steps, tokens, &k.form);
+    }
+    *best = k.form;
+    return true;
 }
 
 template <int NB, int PL, int W>
@@ -972,7 +979,11 @@ static int launch_lone_t(const FusedItem* d_items, const StageDesc& sd, const Lo
 int launch_lone(const FusedItem* d_items, int n_rb, const StageDesc& sd, int max_steps, int batch, hipStream_t s)
 {
     if (n_rb < 1) return NQ_OK;
-    const LoneForm f = lone_form(n_rb, max_steps, batch);
+    LoneForm f;
+    if (!lone_form(n_rb, max_steps, batch, &f)) {
+        set_error("launch_lone: no launch in the form that was asked for");
+        return NQ_E_INVALID_ARG;
+    }
     if (f.w == 8) return launch_lone_t<2, 8, 8>(d_items, sd, f, s);
     if (f.pl == 1) return launch_lone_t<1, 1, 16>(d_items, sd, f, s);
     if (f.pl == 2) return launch_lone_t<1, 2, 16>(d_items, sd, f, s);
@@ -985,7 +996,8 @@ double lone_stage_us(int n_rb, int steps, int tokens)
 {
     AlongForm f;
     if (lone_selfq(steps, n_rb, tokens) && along_form(n_rb, steps, tokens, &f)) return along_us(f, steps);
-    return 3.5 + 2.1e-6 * 64.0 * steps * tokens + lone_us(lone_form(n_rb, steps, tokens), steps);
+    LoneForm l;
+    return 3.5 + 2.1e-6 * 64.0 * steps * tokens + (lone_form(n_rb, steps, tokens, &l) ? lone_us(l, steps) : 0.0);
 }
 
 // ---- one launch per layer ----

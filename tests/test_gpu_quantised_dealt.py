@@ -1,6 +1,6 @@
-"""The stage kernel of few row blocks on an input that a launch of its own has quantised (too long to quantise along), at the edges of its forms: tokens in groups of
-one to eight, one to eight bit planes per workgroup, groups on one XCD or on all, several layers of unequal lengths in a launch.  Outputs against lone calls by the
-launches that deal nothing out, bit for bit (the arithmetic is exact up to the same roundings), and against the oracle."""
+"""The stage kernel of few row blocks on an input that a launch of its own has quantised (too long to quantise along), in the forms that its rule takes: groups of tokens and bit
+planes dealt out, whole row blocks of six to eight tokens, groups on one XCD or on all, several layers of unequal lengths in a launch (test_gpu_lone_forms.py has every compiled
+form).  Outputs against lone calls by the launches that deal nothing out, bit for bit (the arithmetic is exact up to the same roundings), and against the oracle."""
 import numpy as np
 import pytest
 
@@ -26,6 +26,7 @@ def plain(nqopt, L, x, batch):
     ([(130, 17000, 100)], (2, 4, 5, 6, 8)), ([(260, 33000, 1025)], (1, 3, 4, 7, 8)),                    # one and nine row blocks of a long reduction
     ([(300, 12000, 4200)], (3, 4, 5, 8)), ([(200, 20000, 8300), (64, 300, 20)], (2, 5, 6)),             # 33 and 66
     ([(500, 9088, 480), (129, 64, 3), (640, 5000, 1000)], (4, 7, 8)),                                   # unequal lengths
+    ([(60, 16400, 129 * 128 + 5)], (6, 8)),                                                             # 130: whole row blocks, eight waves on two column groups
 ])
 def test_plans(nqopt, shapes, batches):
     hs = [Layer(*s, "f16", seed=12700 + i) for i, s in enumerate(shapes)]
@@ -44,7 +45,8 @@ def test_plans(nqopt, shapes, batches):
         L.close()
 
 
-@pytest.mark.parametrize("shape,batches", [((260, 40000, 130), (9, 17, 24, 65)), ((140, 16000, 700), (10, 33, 40)), ((100, 9000, 2040), (9, 15, 16))])
+@pytest.mark.parametrize("shape,batches", [((260, 40000, 130), (9, 17, 24, 65)), ((140, 16000, 700), (10, 33, 40)), ((100, 9000, 2040), (9, 15, 16)),
+                                           ((90, 2555, 99 * 128 + 7), (12, 13, 16))])       # ragged rows, 100 row blocks: whole ones on all XCDs, eight waves
 def test_more_than_eight_tokens(nqopt, shape, batches):
     L = Layer(*shape, "bf16", seed=12800 + shape[1])
     nq.nq_binlr_reserve(L.h, max(batches))
