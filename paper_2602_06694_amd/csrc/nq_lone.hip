@@ -556,7 +556,7 @@ stage_lone_kernel(const FusedItem* __restrict__ items, StageDesc s1, LoneDeal d)
 // Bound by its chain of latencies; adding up the waves' sums of t was the longest link (2.4 of 8.0 us at 1024 x 1024 r = 256): all eight planes pass through LDS at once, in
 // the columns that are in use, and t's largest magnitude is taken where t is: 7.6 us.
 // ---------------------------------------------------------------------------------------------
-constexpr int kLayerWaves = 16;
+constexpr int kLayerWaves = 16, kLayerTokens = 5;       // tokens: one column group of 15 columns, three per token, is all that the kernel has
 
 template <int PL>
 __global__ void __launch_bounds__(64 * kLayerWaves) __attribute__((amdgpu_waves_per_eu(4, 4)))
@@ -1019,11 +1019,12 @@ static LayerLds layer_lds(const QuantDesc& qt, const StageDesc& s1, const StageD
 // Where it is faster than two launches: so few results of stage 1 that each workgroup adds up the waves' sums of all of them in two or three passes, and so few tiles that
 // doing them once per workgroup costs less than a launch.  us per call, one launch / two, by row blocks and tiles of stage 1, 2048 outputs: batch 1 one row block of 16 tiles 7.2 / 8.7, 64
 // 8.5 / 9.2, 128 10.9 / 9.7; two of 16 7.6 / 9.0, 64 8.4 / 8.9, 128 10.6 / 8.9; four of 32 8.6 / 8.6, 64 8.9 / 8.7 (three of 36 8.3 / 8.5); eight of 32 9.9 / 8.9.  Batch 2 one of 32 8.3 / 9.0, 64 9.4 / 9.3;
-// two of 32 8.6 / 9.1, 64 9.5 / 9.0; four of 16 9.6 / 8.7.  Batch 3 one of 16 8.1 / 9.0, 32 8.9 / 9.0; two of 8 8.7 / 8.7.  Batch 4 one of 8 8.0 / 9.1, 16 8.8 / 9.1, 32 9.7 / 9.2; two of 8 9.4 / 9.1.
+// two of 32 8.6 / 9.1, 64 9.5 / 9.0; four of 16 9.6 / 8.7.  Batch 3 one of 16 8.1 / 9.0, 32 8.9 / 9.0; two of 8 8.7 / 8.7.  Batch 4 one of 8 8.0 / 9.1, 16 8.8 / 9.1, 32 9.7 / 9.2; two of 8 9.4 / 9.1.  Batch 5 one of 4, 64 outputs
+// 7.6 / 9.2, 2048 8.0 / 9.9, 32000 9.7 / 12.7.
 bool lone_layer_fits(const QuantDesc& qt, const StageDesc& s1, const StageDesc& s2, int batch)
 {
     const int n_rb1 = (int)n_rowblocks(s1.M), n_rb2 = (int)n_rowblocks(s2.M);
-    return n_rb1 * batch <= 6 && n_rb1 * s1.n_steps * batch <= (n_rb1 * batch > 4 ? 24 : n_rb1 <= 2 ? 64 : 48) && n_rb2 <= device_cu_count() &&
+    return batch <= kLayerTokens && n_rb1 * batch <= 6 && n_rb1 * s1.n_steps * batch <= (n_rb1 * batch > 4 ? 24 : n_rb1 <= 2 ? 64 : 48) && n_rb2 <= device_cu_count() &&
            batch * s1.n_steps * 64 <= kLoneMaxElements && batch * s2.n_steps * 64 <= kLoneMaxElements && layer_lds(qt, s1, s2, batch).bytes <= kLoneLdsBytes;
 }
 
