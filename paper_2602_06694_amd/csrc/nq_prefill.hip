@@ -827,6 +827,7 @@ struct PfLayout {
     int splits1, splits2;
     int tg1, tg2;             // token groups of 16 per workgroup tile of the two GEMMs (4 or 2)
     int ks1, ks2;             // parts of the reduction taken inside a workgroup (1 or 2)
+    int m_tiles1, m_tiles2;   // token tiles launched
     size_t off_x, off_t, off_scale, off_partial, total;
 };
 
@@ -890,6 +891,16 @@ static GemmTiling choose_tiling(int batch, int n_rb, int nst, int n_pad, bool pl
     return best;
 }
 
+// Token tiles of a launch.  A token tile's workgroups have an XCD of their own where the tiles are a multiple of eight, and its activations then come into one L2: seven tiles (15, 23, ..) of
+// 32 tokens that leave every workgroup its CU take an eighth without tokens along.  us per forward, 7 / 8 tiles in both GEMMs: 2796 x 166 r = 78 at 196 tokens 15.4 / 14.9,
+// 15 / 16: 2722 x 431 r = 207 at 461 18.6 / 18.0; 57 short forwards of seven and 8 k + 7 tiles 0.982 of the time on average, none above 1.014.  Past the line work counts: 17245 x 497
+// r = 94 at 458 20.1 / 21.7; in parts (of which there are more than CUs soon) nothing is gained.
+static int token_tiles(int batch, int tg, int splits, int n_rb)
+{
+    const int n = (batch + 16 * tg - 1) / (16 * tg), n_tiles = (n_rb + kPfWaves - 1) / kPfWaves;
+    return tg == 2 && n % 8 == 7 && splits == 1 && (n + 1) * n_tiles <= device_cu_count() ? n + 1 : n;
+}
+
 static PfLayout pf_layout(int64_t d_out, int64_t d_in, int64_t r, int batch, bool plain)
 {
     PfLayout L;
@@ -911,9 +922,11 @@ static PfLayout pf_layout(int64_t d_out, int64_t d_in, int64_t r, int batch, boo
     // the in-workgroup split needs 64-token tiles and a reduction of whole groups of eight steps
     if (L.tg1 != 4 || n_steps(d_in) % 8 != 0) L.ks1 = 1;
     if (L.tg2 != 4 || n_steps(r) % 8 != 0) L.ks2 = 1;
+    L.m_tiles1 = token_tiles(batch, L.tg1, L.splits1, (int)n_rowblocks(r));
+    L.m_tiles2 = token_tiles(batch, L.tg2, L.splits2, (int)n_rowblocks(d_out));
     if (opt_flag(OPT_PF_VERBOSE))
-        fprintf(stderr, "prefill tiling B=%d: gemm1 tg=%d splits=%d ks=%d, gemm2 tg=%d splits=%d ks=%d\n", batch, L.tg1, L.splits1,
-                L.ks1, L.tg2, L.splits2, L.ks2);
+        fprintf(stderr, "prefill tiling B=%d: gemm1 tg=%d tiles=%d splits=%d ks=%d, gemm2 tg=%d tiles=%d splits=%d ks=%d\n", batch, L.tg1, L.m_tiles1, L.splits1,
+                L.ks1, L.tg2, L.m_tiles2, L.splits2, L.ks2);
     size_t o = 0;
     L.off_x = o; o += al256((size_t)L.m_pad * L.k1 * 2);
     L.off_t = o; o += al256((size_t)L.m_pad * L.k2 * 2);
@@ -1060,7 +1073,7 @@ static int launch_prefill_as(const PrefillArgs& p, hipStream_t s)
     a.n_tiles = (a.n_rb + kPfWaves - 1) / kPfWaves;
     a.splits = L.splits1; a.steps_per_split = steps_per_split4(a.nst, a.splits, L.ks1);
     a.n_pad = L.n1_pad;
-    a.m_tiles = (p.batch + 16 * L.tg1 - 1) / (16 * L.tg1);
+    a.m_tiles = L.m_tiles1;
     a.m_rows = a.m_tiles * 16 * L.tg1;
     int rc = run_gemm<EPI_T, PLAIN>(a, L.tg1, L.ks1, s);
     if (rc != NQ_OK) return rc;
@@ -1071,7 +1084,7 @@ static int launch_prefill_as(const PrefillArgs& p, hipStream_t s)
     a.n_tiles = (a.n_rb + kPfWaves - 1) / kPfWaves;
     a.splits = L.splits2; a.steps_per_split = steps_per_split4(a.nst, a.splits, L.ks2);
     a.n_pad = L.n2_pad;
-    a.m_tiles = (p.batch + 16 * L.tg2 - 1) / (16 * L.tg2);
+    a.m_tiles = L.m_tiles2;
     a.m_rows = a.m_tiles * 16 * L.tg2;
     return run_gemm<EPI_Y, PLAIN>(a, L.tg2, L.ks2, s);
 }

@@ -36,6 +36,25 @@ def test_tokens_around_half_tiles(nqopt, batch, tg, splits):
     L.close()
 
 
+@pytest.mark.parametrize("shape,batch,tiles", [((2796, 166, 78), 196, (8, 8)), ((2796, 166, 78), 193, (8, 8)), ((2796, 166, 78), 224, (8, 8)), ((2796, 166, 78), 192, (6, 6)),
+                                               ((2722, 431, 207), 461, (16, 16)), ((17245, 497, 94), 458, (16, 15))])
+def test_short_launches_take_whole_eights_of_tiles(nqopt, capfd, shape, batch, tiles):
+    """Seven, 15, .. tiles of 32 tokens that leave every workgroup its CU are launched as eight, 16, ..: the last holds no token, and nothing of it is stored."""
+    L = Layer(*shape, "bf16", seed=13400 + batch)
+    nqopt.set("dense_only", 1)
+    nq.nq_binlr_reserve(L.h, batch)
+    nqopt.set("pf_verbose", 1)
+    capfd.readouterr()
+    x = synth.gen_x(batch, shape[1], 13401, "bf16")
+    y = new_output(batch + 1, shape[0])
+    nq.nq_binlr_forward(L.h, to_device(x, "bf16"), y, batch)
+    got = y.cpu().numpy()
+    line = [l for l in capfd.readouterr().err.splitlines() if "prefill tiling B=%d:" % batch in l][-1]
+    assert np.isnan(got[batch]).all() and rel_err(got[:batch], L.oracle(x)) <= TOL
+    assert tuple(int(w[6:]) for w in line.replace(",", "").split() if w.startswith("tiles=")) == tiles, line
+    L.close()
+
+
 def test_a_reservation_covers_every_number_of_tiles(nqopt):
     nqopt.set("dense_only", 1)
     L = Layer(640, 2300, 300, "bf16", seed=13100)
