@@ -782,10 +782,18 @@ static double along_us(const AlongForm& f, int steps)
            0.0141 / 1024 * f.w * f.pl * 192 * f.d.per + 0.51 / 256 * f.d.n_rb * f.d.groups * s + 0.175 * ((results + 16 * f.w - 1) / (16 * f.w)) + (f.w == 8 ? 0.30 : 0.0);
 }
 
+// ... what it takes longer on the row blocks of several layers, by 7600 timings of plans of two and four layers, 4 to 128 row blocks of 4 to 128 steps at 1 to 8 tokens: there the
+// estimate alone dealt out tokens and kept planes together for gains of hundredths, and plans of 32 to 48 row blocks at 2 to 4 tokens had become slower than with all tokens in a
+// workgroup of two planes (five layers 11008 x 2048 r = 896, 2 tokens: two planes 13.0, as estimated alone 13.4).  Choices 0.28 % slower than the best of each plan, without it 0.54 %.
+static double along_listed_us(const AlongForm& f)
+{
+    return (f.e == 4 ? 0.03 : 0.0) + (f.pl == 8 ? 0.60 : f.pl == 4 ? 0.28 : f.pl == 2 ? 0.12 : 0.0);
+}
+
 // The form of a launch: among those with at most one workgroup per CU, on their XCD (dealt to all XCDs only where more than eight tokens need it), whose
 // fixed point and sums fit LDS, the one of the least estimated time.  us per launch, stage 1 of 8 row blocks of 64 steps at 24 tokens 8.4 with groups of eight and one
 // plane, 6.7 with groups of three and two; 28 of 448 steps at 4 tokens 14.6 after a quantisation launch of 6.2, 14.8 with it.
-static bool along_form_now(int n_rb, int steps, int tokens, AlongForm* best)
+static bool along_form_now(int n_rb, int steps, int tokens, bool listed, AlongForm* best)
 {
     const int cus = device_cu_count(), slots = cus / 8 / ((n_rb + 7) / 8), asked = opt(OPT_LONE_FORM);
     double best_us = 1e30;
@@ -800,7 +808,7 @@ static bool along_form_now(int n_rb, int steps, int tokens, AlongForm* best)
                     if (asked >= 0 ? asked != 100 * per + 10 * pl + (w == 8 ? 2 : e == 4 ? 1 : 0) : spread && (tokens <= 8 || n_rb * groups * (8 / pl) > cus)) continue;
                     const AlongForm f = {LoneDeal{n_rb, tokens, per, groups, spread}, pl, w, e, along_lds_bytes(pl, w, steps, per)};
                     if (f.lds > kLoneLdsBytes) continue;
-                    const double us = along_us(f, steps);
+                    const double us = along_us(f, steps) + (listed ? along_listed_us(f) : 0.0);
                     if (us < best_us) { best_us = us; *best = f; }
                 }
             }
@@ -808,20 +816,20 @@ static bool along_form_now(int n_rb, int steps, int tokens, AlongForm* best)
     return best_us < 1e30;
 }
 
-// (A call asks for the forms of two stages, twice each: 2 us of a host that takes 6 for the call.  The answer depends on nothing but the three numbers.)
-static bool along_form(int n_rb, int steps, int tokens, AlongForm* best)
+// (A call asks for the forms of two stages, twice each: 2 us of a host that takes 6 for the call.  The answer depends on nothing but the four arguments.)
+static bool along_form(int n_rb, int steps, int tokens, bool listed, AlongForm* best)
 {
-    if (opt(OPT_LONE_FORM) >= 0) return along_form_now(n_rb, steps, tokens, best);
+    if (opt(OPT_LONE_FORM) >= 0) return along_form_now(n_rb, steps, tokens, listed, best);
     struct Known {
         int n_rb, steps, tokens;
-        bool fits;
+        bool listed, fits;
         AlongForm form;
     };
     static thread_local Known known[64];                   // (all zero: no launch has no row blocks)
     Known& k = known[(unsigned)(n_rb * 31 + steps * 7 + tokens) % 64];
-    if (k.n_rb != n_rb || k.steps != steps || k.tokens != tokens) {
-        k = Known{n_rb, steps, tokens, false, {}};
-        k.fits = along_form_now(n_rb, steps, tokens, &k.form);
+    if (k.n_rb != n_rb || k.steps != steps || k.tokens != tokens || k.listed != listed) {
+        k = Known{n_rb, steps, tokens, listed, false, {}};
+        k.fits = along_form_now(n_rb, steps, tokens, listed, &k.form);
     }
     if (k.fits) *best = k.form;
     return k.fits;
@@ -841,7 +849,7 @@ bool lone_selfq(int max_steps, int n_rb, int batch)
         const int per = lone_group(batch);
         if (lone_pieces<16>(max_steps) > (per <= 2 ? 12 / per : per == 3 ? 2 : 1)) return false;
     }
-    return along_form(n_rb, max_steps, batch, &f);
+    return along_form(n_rb, max_steps, batch, false, &f);
 }
 
 // The same for the launches of a plan, which quantise along where whole groups of eight tokens fit, as they did when those were the only ones: what a plan does is
@@ -884,7 +892,7 @@ int launch_lone_selfq(const FusedItem* d_items, int n_rb, const QuantDesc& q, co
 {
     if (n_rb < 1) return NQ_OK;
     AlongForm f;
-    if (!along_form(n_rb, max_steps, batch, &f)) {
+    if (!along_form(n_rb, max_steps, batch, d_items != nullptr, &f)) {
         set_error("launch_lone_selfq: input too long for the workgroups to quantise, or not in the form that was asked for");
         return NQ_E_INVALID_ARG;
     }
@@ -995,7 +1003,7 @@ int launch_lone(const FusedItem* d_items, int n_rb, const StageDesc& sd, int max
 double lone_stage_us(int n_rb, int steps, int tokens)
 {
     AlongForm f;
-    if (lone_selfq(steps, n_rb, tokens) && along_form(n_rb, steps, tokens, &f)) return along_us(f, steps);
+    if (lone_selfq(steps, n_rb, tokens) && along_form(n_rb, steps, tokens, false, &f)) return along_us(f, steps);
     LoneForm l;
     return 3.5 + 2.1e-6 * 64.0 * steps * tokens + (lone_form(n_rb, steps, tokens, &l) ? lone_us(l, steps) : 0.0);
 }
