@@ -159,7 +159,8 @@ int nq_binlr_reserved(nq_handle h, int* max_batch, size_t* workspace_bytes);
 /* y = s_out (.) (U (V^T (s_in (.) x))) for `batch` tokens (Eq. 1).
  * x: device, [batch, d_in] of x_dtype;  y: device, [batch, d_out] of y_dtype; both 16-byte
  * aligned, must not overlap.  Asynchronous on `stream`.  Allocates nothing when
- * batch <= the reserved batch (otherwise it reserves first, which synchronises).
+ * batch <= the reserved batch (otherwise it makes room first, which synchronises; a call on the dense path makes
+ * room for every smaller batch as well).
  * Not re-entrant on one handle (the handle's workspace is shared); different
  * handles may run concurrently on different streams.
  * batch <= 8: streaming kernels (exact integer accumulation); >= 9: the same (nq_binlr_forward_exact) for few tokens and

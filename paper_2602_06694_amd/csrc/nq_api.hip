@@ -597,9 +597,25 @@ static int grow_prefill_workspace(nq_handle h, size_t need)
     return NQ_OK;
 }
 
-static int ensure_prefill_workspace(nq_handle h, int batch)
+static bool forward_exact_pays(nq_handle h, int batch);
+static size_t exact_workspace_bytes(nq_handle h, int batch) { return carve_workspace(nullptr, nullptr, h->d_in, h->r, (int)round_up(batch, 16)); }
+static size_t dense_workspace_bytes(nq_handle h, int batch) { return prefill_workspace_bytes(h->d_out, h->d_in, h->r, batch, h->pf_plain); }
+
+// The workspace of an nq_binlr_forward on the dense path.  Where it has to grow it is made large enough for every smaller batch on the path that that one takes (the need is monotone
+// on neither: fewer tokens may be split into more parts, and the exact path's fixed point is larger than fp16 operands), so that a smaller call after it allocates nothing and can be captured.
+static int ensure_dense_workspace(nq_handle h, int batch)
 {
-    return grow_prefill_workspace(h, prefill_workspace_bytes(h->d_out, h->d_in, h->r, batch, h->pf_plain));
+    size_t need = dense_workspace_bytes(h, batch);
+    if (need <= h->pf.bytes) return NQ_OK;
+    const int most_exact = std::min(batch - 1, exact_pass_tokens(h));
+    for (int b = NQ_PREFILL_MIN_BATCH, told = 0; b < batch; b = b < most_exact ? b + 1 : (int)round_up(b + 1, 32)) {
+        if (b <= most_exact && forward_exact_pays(h, b)) need = std::max(need, exact_workspace_bytes(h, b));
+        else if ((b + 31) / 32 != told) {                  // (it depends on the batch only through the number of its 32-token tiles)
+            told = (b + 31) / 32;
+            need = std::max(need, dense_workspace_bytes(h, b));
+        }
+    }
+    return grow_prefill_workspace(h, need);
 }
 
 extern "C" int nq_binlr_reserve(nq_handle h, int max_batch)
@@ -615,7 +631,7 @@ extern "C" int nq_binlr_reserve(nq_handle h, int max_batch)
     const bool dense = max_batch >= NQ_PREFILL_MIN_BATCH && !(h->flags & NQ_FLAG_NO_PREFILL);
     for (int64_t b = 32; dense; b += 32) {
         const int bb = (int)std::min<int64_t>(b, max_batch);
-        need = std::max(need, prefill_workspace_bytes(h->d_out, h->d_in, h->r, bb, h->pf_plain));
+        need = std::max(need, dense_workspace_bytes(h, bb));
         if (b >= max_batch) break;
     }
     int rc = grow_prefill_workspace(h, need);
@@ -834,10 +850,10 @@ extern "C" int nq_binlr_forward(nq_handle h, const void* x, void* y, int batch, 
     if (batch <= NQ_DECODE_MAX_BATCH) return decode_once(h, h->ws, x, y, batch, s);
     if (batch >= NQ_PREFILL_MIN_BATCH && !(h->flags & (NQ_FLAG_NO_PREFILL | NQ_FLAG_DECODE_VALU))) {
         if (forward_exact_pays(h, batch)) {
-            rc = grow_prefill_workspace(h, carve_workspace(nullptr, nullptr, h->d_in, h->r, (int)round_up(batch, 16)));
+            rc = grow_prefill_workspace(h, exact_workspace_bytes(h, batch));
             return rc != NQ_OK ? rc : run_in_passes(h, x, y, batch, s, false);
         }
-        if ((rc = ensure_prefill_workspace(h, batch)) != NQ_OK) return rc;
+        if ((rc = ensure_dense_workspace(h, batch)) != NQ_OK) return rc;
         note_capture(h->pf, s);
         PrefillArgs a;
         a.vt_tiles = h->vt_tiles; a.u_tiles = h->u_tiles; a.s_in = h->s_in; a.s_out = h->s_out;

@@ -152,3 +152,41 @@ def test_transposed_graphs_captured_before_the_workspace_grew():
         assert torch.equal(w, eager), rep
     del graph
     L.close()
+
+
+FEWER = [((1038, 129, 93), 373, 178), ((1202, 245, 109), 257, 234), ((2623, 351, 86), 249, 156),      # the dense path's call, then fewer tokens on the exact one
+         ((1313, 8385, 886), 361, 327), ((13969, 8296, 3202), 164, 138)]                               # both dense, the smaller one with more parts of its reduction
+
+
+@pytest.mark.parametrize("shape,tokens,fewer", FEWER)
+def test_a_forward_leaves_room_for_every_smaller_one(shape, tokens, fewer):
+    L = Layer(*shape, "bf16", seed=9700)
+    x, y = to_device(synth.gen_x(tokens, shape[1], 9701, "bf16"), "bf16"), new_output(tokens, shape[0])
+    nq.nq_binlr_forward(L.h, x, y, tokens)                # nothing reserved
+    held = nq.nq_binlr_reserved(L.h)[1]
+    for batch in (fewer, 9, 16, 33, tokens // 2, tokens - 1):
+        nq.nq_binlr_forward(L.h, x, y, batch)
+        assert nq.nq_binlr_reserved(L.h)[1] == held, batch
+    L.close()
+
+
+@pytest.mark.parametrize("shape,tokens,fewer", FEWER)
+def test_a_smaller_forward_can_be_captured_without_a_reservation(shape, tokens, fewer):
+    import torch
+    L = Layer(*shape, "bf16", seed=9700)
+    x, y, eager = to_device(synth.gen_x(tokens, shape[1], 9702, "bf16"), "bf16"), new_output(tokens, shape[0]), new_output(tokens, shape[0])
+    nq.nq_binlr_forward(L.h, x, y, tokens)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        nq.nq_binlr_forward(L.h, x, y, fewer)
+    for rep in range(3):
+        x.copy_(to_device(synth.gen_x(tokens, shape[1], 9710 + rep, "bf16"), "bf16"))
+        nq.nq_binlr_forward(L.h, x, eager, fewer)
+        y.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y[:fewer], eager[:fewer]), rep
+    del graph
+    L.close()
