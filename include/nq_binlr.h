@@ -52,7 +52,7 @@ extern "C" {
 #define NQ_E_SHAPE       (-2)  /* a dimension is < 1 or beyond what the kernels support */
 #define NQ_E_ALIGN       (-3)  /* a device pointer is not 16-byte aligned */
 #define NQ_E_NULL        (-4)  /* a required pointer is NULL */
-#define NQ_E_UNSUPPORTED (-5)  /* valid request that this build does not implement */
+#define NQ_E_UNSUPPORTED (-5)  /* valid request that the library does not implement */
 #define NQ_E_HIP         (-6)  /* a HIP runtime call failed (see nq_last_error_string) */
 #define NQ_E_TIMEOUT     (-7)  /* a bounded wait inside a kernel ran into its limit (nq_exec_status) */
 
@@ -113,7 +113,7 @@ int nq_pack_signs_device(const void* d_signs, int dtype, int64_t rows, int64_t c
 /* Build a layer on the current HIP device.
  * U_words: host, canonical [d_out, ceil(r/32)];  V_words: host, canonical [d_in, ceil(r/32)];
  * s_out_fp16: host, d_out IEEE binary16 values;  s_in_fp16: host, d_in values.
- * x_dtype: NQ_F32, NQ_F16 or NQ_BF16;  y_dtype: NQ_F32 (default of the build's parity bar),
+ * x_dtype: NQ_F32, NQ_F16 or NQ_BF16;  y_dtype: NQ_F32 (the default),
  * NQ_F16 or NQ_BF16: the fp32 result rounded once more, to nearest even (a value beyond the
  * fp16 range becomes infinity, as in IEEE conversion; the paper does not state an output
  * type, its models run in bf16/fp16).
@@ -177,7 +177,7 @@ int nq_binlr_forward(nq_handle h, const void* x, void* y, int batch, void* strea
  * fixed-point copies of x' and t, the token constants, the intermediate t) is a static array of
  * NQ_STATIC_SCRATCH_BYTES inside the library, one copy per GPU, held until the process ends,
  * instead of the layer's own workspace.  A layer and batch that need more (about
- * batch * 3.2 * (d_in + r) bytes: any BASELINE shape at batch 8 fits) -> NQ_E_SHAPE.  The call
+ * batch * 3.2 * (d_in + r) bytes: 28672 x 8192 r = 3520 at batch 8 fits) -> NQ_E_SHAPE.  The call
  * allocates and frees nothing and clears nothing (every byte read was written earlier in the
  * same call).  Every call on one GPU uses that GPU's one array: calls that overlap in time on one
  * GPU (two streams, two threads) race; calls on one stream follow one another safely.
@@ -258,14 +258,15 @@ int nq_plan_forward_timed(nq_plan p, void* stream, float ms[4]);
 /* Debug: which schedule each of the plan's two stage launches uses.  w[0] stage 1, w[1] stage 2:
  * 1 = one wave per item, 4 / 16 = that many waves share a row block, 8 = the waves of a workgroup share an op's
  * input through LDS (batch 4..8), 9 = the same with the whole input resident in LDS (reductions of at
- * most 16 steps), 10 / 11 = the two on 16-bit fixed point ("two_slice_b8"), 12 = eight waves share a row block
- * (batch 6..8, long reductions), 32 = short batch-1 launch with reductions of 4097..16384 elements in which every
+ * most 16 steps), 10 / 11 = the two on 16-bit fixed point ("two_slice_b8"), 12 = as 16, told apart for batch 6..8
+ * and long reductions, 32 = short batch-1 launch with reductions of 4097..16384 elements in which every
  * workgroup (16 waves per row block) quantises the input for itself,
  * 33 / 34 = batch-1 launch whose waves quantise their own share of the input (one / four waves per
  * row block; reductions of at most 1024 / 4096 elements), 35 = short launch at batch 2..8 in which every workgroup
- * quantises the input for itself.  A launch with at most one row block per CU may run as 35 (32 at batch 1: as its form with several
- * workgroups per row block) or 16 where it is said to be 4, 12 or 16: more than four layers at batch 2, reductions of more than 176
- * steps; nq_plan_forward_timed shows whether it quantises its input itself. */
+ * quantises the input for itself.  The codes name what a launch was planned as.  One with at most one row block per CU may run
+ * in another form with the same bits: 16 and 12 with eight or 16 waves and several workgroups to a row block; 4, 12 and 16 as 35 or 16 (more
+ * than four layers at batch 2, reductions of more than 176 steps); 32, 33 and 34 with at most one row block to two CUs as 35 at batch 1,
+ * several workgroups to a row block.  nq_plan_forward_timed shows whether a launch quantises its input itself. */
 int nq_plan_schedules(nq_plan p, int w[2]);
 int nq_plan_destroy(nq_plan p);
 
@@ -349,14 +350,14 @@ int nq_probe_mfma(int dtype, double* tera_ops_per_s);
  * default and none changes a result beyond the documented tolerances -- with ONE exception:
  * "two_slice_b8" (off by default) makes plans created at batch 6..8 feed their shared-input
  * launches 16-bit instead of 24-bit fixed point (faster; about 3e-4 of the largest output instead
- * of 2e-6, and about 2e-3 -- outside this build's 1e-3 bar -- for inputs with outlier channels
+ * of 2e-6, and about 2e-3 -- more than 1e-3 -- for inputs with outlier channels
  * 20 times the rest).  Names: "slab_mb",
  * "force_w", "split_steps", "selfq4_min_steps", "share_steps", "share_min_batch", "stream_steps",
  * "schedule_full", "fuse_max_mb", "no_fuse", "no_selfq", "no_selfq_c2", "no_resident",
  * "no_quant_wave", "pf_splits1", "pf_splits2", "pf_tg1", "pf_tg2", "pf_ks1", "pf_ks2", "pf_verbose",
  * "exec_spin_limit_us", "no_small_layer", "small_layer_kb", "dgemm_tile", "admm_no_overlap",
  * "two_slice_b8", "admm_no_prio", "admm_product_mode", "admm_inline_svid",
- * "admm_no_fused_step", "dense_only" (see the source for the meaning of each).  value < 0 restores the default.
+ * "admm_no_fused_step", "dense_only", "lone_form" (see the source for the meaning of each).  value < 0 restores the default.
  * The environment variable NQ_<NAME IN CAPITALS> gives an option its initial value; it is read once,
  * when the library first consults an option, never on a launch path.  Plans keep the schedules
  * chosen when they were created.  Not thread-safe against forwards running at the same time.

@@ -32,7 +32,6 @@ template <int W, int E> constexpr int lone_share_units() { return kLoneMaxElemen
 // ... of a kernel that takes four at a time only where they are few
 constexpr int kFewElements = 16384;
 template <int W, int E> constexpr int along_units() { return (E == 4 ? kFewElements : kLoneMaxElements) / (64 * E) / W; }
-constexpr int kLonePlaneInts = 4 * 68;     // a wave's sums of one bit plane in LDS: four row groups of 16 columns x 4 rows, 68 ints apart (banks)
 
 template <int E> __host__ __device__ inline int lone_pieces(int nst) { return (nst + E - 1) / E; }      // units per token
 // fixed point of a token in LDS: [step][chunk][slice][16 bytes], tokens 48 mod 256 bytes apart: the 15 (token, slice) operands of a
@@ -201,7 +200,8 @@ __device__ __forceinline__ void lone_quantise(Value value, const LoneShare& shar
     }
     __syncthreads();
     sh = share;
-    int sum = 0;                                           // |q| <= 2^22: a lane's 32 at most fit
+    int sum = 0;                                           // |q| <= 2^22, and kU E <= 64 of them: 2^28 at most
+    static_assert(kU * E <= 64, "a lane's sum of q");
 #pragma unroll
     for (int c = 0; c < kU; ++c) {
         if (c < share.n) {
@@ -782,7 +782,7 @@ static double along_us(const AlongForm& f, int steps)
            0.0141 / 1024 * f.w * f.pl * 192 * f.d.per + 0.51 / 256 * f.d.n_rb * f.d.groups * s + 0.175 * ((results + 16 * f.w - 1) / (16 * f.w)) + (f.w == 8 ? 0.30 : 0.0);
 }
 
-// ... what it takes longer on the row blocks of several layers, by 7600 timings of plans of two and four layers, 4 to 128 row blocks of 4 to 128 steps at 1 to 8 tokens: there the
+// ... what it takes longer on the row blocks of several layers, by 11900 timings of plans of two and four layers, 4 to 128 row blocks of 4 to 128 steps at 1 to 8 tokens: there the
 // estimate alone dealt out tokens and kept planes together for gains of hundredths, and plans of 32 to 48 row blocks at 2 to 4 tokens had become slower than with all tokens in a
 // workgroup of two planes (five layers 11008 x 2048 r = 896, 2 tokens: two planes 13.0, as estimated alone 13.4).  Choices 0.28 % slower than the best of each plan, without it 0.54 %.
 static double along_listed_us(const AlongForm& f)
@@ -852,15 +852,15 @@ bool lone_selfq(int max_steps, int n_rb, int batch)
     return along_form(n_rb, max_steps, batch, false, &f);
 }
 
-// The same for the launches of a plan, which quantise along where whole groups of eight tokens fit, as they did when those were the only ones: what a plan does is
-// part of its answers (nq_plan_schedules, and the times of nq_plan_forward_timed, where a launch that is not there takes none).
+// The same for the launches of a plan, which quantise along where they did when whole groups of eight tokens were the only ones: what a plan does is part of its answers
+// (nq_plan_schedules, and the times of nq_plan_forward_timed, where a launch that is not there takes none).  The line that was drawn then: the fixed point of all tokens in LDS beside the
+// sums of 8 (whole row blocks) or 16 waves, 1088 bytes for each plane and column group of up to four that pass at a time.
 bool lone_plan_selfq(int max_steps, int n_rb, int batch)
 {
-    const int pl = lone_planes(n_rb), pieces = lone_pieces<16>(max_steps);
+    const int pl = lone_planes(n_rb), nb = batch <= 5 ? 1 : 2;
     const int most = pl < 8 ? kLoneMaxElements / 1024 / batch : batch <= 2 ? 12 / batch : batch == 3 ? 2 : 1;
-    const int nb = batch <= 5 ? 1 : 2;
-    const size_t sums = (size_t)(pl == 8 ? 8 : 16) * nb * std::min(pl, 4 / nb) * kLonePlaneInts * 4;
-    return pieces <= most && sums + sizeof(LoneTokens) + (size_t)batch * lone_tok_bytes(max_steps) <= kLoneLdsBytes && lone_selfq(max_steps, n_rb, batch);
+    const size_t sums = (size_t)(pl == 8 ? 8 : 16) * std::min(nb * pl, 4) * 1088;
+    return lone_pieces<16>(max_steps) <= most && sums + sizeof(LoneTokens) + (size_t)batch * lone_tok_bytes(max_steps) <= kLoneLdsBytes && lone_selfq(max_steps, n_rb, batch);
 }
 
 // Up to half as many pairs of row block and group of eight tokens as CUs: several workgroups share every pair.
