@@ -866,15 +866,18 @@ bool lone_plan_selfq(int max_steps, int n_rb, int batch)
 // Up to half as many pairs of row block and group of eight tokens as CUs: several workgroups share every pair.
 bool lone_shared_pairs(int n_rb, int batch) { return 2 * n_rb * lone_groups(batch) <= device_cu_count(); }
 
-// Whether a stage of more than eight tokens is faster dealt out here than in the groups of 16 of nq_exact.hip: where two workgroups or more share a pair, and up to one pair per
-// CU and 64 steps where rows do not start 16-byte aligned or end inside 16 elements, which the quantisation launch in front of the groups of 16 takes two to three us longer for.  us per stage
-// with its input's fixed point, groups of 16 / dealt out, by pairs (row blocks, steps, tokens): 2 (1, 7, 15) 6.6 / 4.2; 20 (5, 48, 30) 9.3 / 5.7; 32 (2, 162, 127) 20.5 / 9.6; 60 (10, 4, 48)
-// 6.5 / 5.0; 84 (6, 199, 107) 22.5 / 18.6; 120 (40, 26, 22) 9.1 / 7.1; past it 144 (72, 4, 16) 6.9 / 7.2, 165 (5, 23, 258) 9.8 / 11.3, 225 (15, 127, 114) 19.0 / 19.4; ragged rows
-// 40 (4, 9, 78) 9.6 / 5.1, 128 (16, 34, 64) 12.2 / 8.2, 140 (5, 11, 217) 10.7 / 6.7, 236 (118, 44, 10) 12.8 / 11.8, past it 290 (5, 5, 459) 11.1 / 18.3, 207 (9, 161, 183)
-// 18 / 20.
+// Whether a stage of more than eight tokens is faster dealt out here than in the groups of 16 of nq_exact.hip: where two workgroups or more share a pair (of 600 stages of 24 to 128
+// pairs one was slower).  Rows that do not start 16-byte aligned or end inside 16 elements, which the quantisation launch in front of the groups of 16 takes two to three us longer for,
+// also up to one pair per CU where the workgroups quantise along (16 steps), and of 32 to 64 steps up to five pairs to eight CUs (four row blocks and fewer, and groups of
+// five tokens: one per CU).  us per stage with its input's fixed point, groups of 16 / dealt out, by pairs (row blocks, steps, tokens): 2 (1, 7, 15) 6.6 / 4.2; 20 (5, 48, 30) 9.3 / 5.7; 32 (2, 162, 127) 20.5 / 9.6; 60
+// (10, 4, 48) 6.5 / 5.0; 84 (6, 199, 107) 22.5 / 18.6; 120 (40, 26, 22) 9.1 / 7.1; past it 144 (72, 4, 16) 6.9 / 7.2, 165 (5, 23, 258) 9.8 / 11.3, 225 (15, 127, 114) 19.0 / 19.4; ragged rows
+// 40 (4, 9, 78) 9.6 / 5.1, 128 (16, 34, 64) 12.2 / 8.2, 140 (5, 11, 217) 10.7 / 6.7, 236 (118, 44, 10) 12.8 / 11.8, past it 290 (5, 5, 459) 11.1 / 18.3, 207 (9, 161, 183) 18 / 20.  Of 540 forwards with one such stage
+// of 128 to 256 pairs: 16 steps and fewer all 0 to 3.9 us faster dealt out, 20 to 28 steps 0.3 to 2.5 slower, 32 to 64 steps 0.2 to 3 faster up to those lines and mostly 0.3 to 1.4
+// slower past them.
 bool lone_deals_out(int n_rb, int steps, bool whole, int batch)
 {
-    return lone_shared_pairs(n_rb, batch) || (!whole && steps <= 64 && n_rb * lone_groups(batch) <= device_cu_count());
+    const int pairs = n_rb * lone_groups(batch), cus = device_cu_count();
+    return lone_shared_pairs(n_rb, batch) || (!whole && ((steps <= 16 && pairs <= cus) || (steps >= 32 && steps <= 64 && 8 * pairs <= (n_rb <= 4 || lone_group(batch) <= 5 ? 8 : 5) * cus)));
 }
 
 template <int NB, int PL, int W, int E>

@@ -46,7 +46,7 @@ def test_plans(nqopt, shapes, batches):
 
 
 @pytest.mark.parametrize("shape,batches", [((260, 40000, 130), (9, 17, 24, 65)), ((140, 16000, 700), (10, 33, 40)), ((100, 9000, 2040), (9, 15, 16)),
-                                           ((90, 2555, 99 * 128 + 7), (12, 13, 16))])       # ragged rows, 100 row blocks: whole ones on all XCDs, eight waves
+                                           ((90, 2555, 79 * 128 + 7), (12, 13, 16))])       # ragged rows, 80 row blocks: whole ones on all XCDs, eight waves
 def test_more_than_eight_tokens(nqopt, shape, batches):
     L = Layer(*shape, "bf16", seed=12800 + shape[1])
     nq.nq_binlr_reserve(L.h, max(batches))
