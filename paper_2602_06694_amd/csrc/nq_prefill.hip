@@ -851,7 +851,7 @@ static int steps_per_split4(int nst, int splits, int ks = 1)
 //    partial sums, 0.29 us per MB.
 // Tiles are counted over the tokens that are there: 32-token tiles leave out the half of a last 64 that holds none (its rows of T stay unwritten and are only read
 // for tokens that are not stored), and either tile is split.  us per forward, 64-token tiles alone split and 32-token ones in pairs / so: 11005 x 4095 r = 1663 at 333 tokens 45.9 / 38.7,
-// 5000 x 5000 r = 1300 at 800 47.5 / 41.9, 4096 x 11008 r = 1664 at 150 41.1 / 38.7, 3262 x 4081 r = 820 at 137 31.9 / 29.9; 40 layers from 600 to 28672 a side at 60 to 2048
+// 5000 x 5000 r = 1300 at 800 47.5 / 41.9, 4096 x 11008 r = 1664 at 150 41.1 / 38.7, 3262 x 4081 r = 820 at 137 31.9 / 29.9 (on this path; by default it takes the exact one); 40 layers from 600 to 28672 a side at 60 to 2048
 // tokens on average 0.7 % slower than the best tiling of each GEMM.
 // One column at a time (`plain`) the steps take 0.60, 1.05, 0.97, 0.49 and 0.35 us (each of ten tilings
 // of the two GEMMs of six layers at 24 to 2048 tokens, against the same in pairs), the rest is the same.
